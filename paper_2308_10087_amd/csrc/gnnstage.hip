@@ -93,11 +93,11 @@ Tuning read_tuning() {
 
 // Longest piece of a row that one wavefront handles in an aggregation over `entries` entries.  A wave
 // streams roughly 16 entries per microsecond, so the longest task bounds the tail of the launch: pieces
-// shrink with the launch (about 16k pieces' worth of work per launch), within [256, 4096].
-int split_edges_for(const Tuning &t, int64_t entries) {
+// shrink with the launch (about 16k pieces' worth of work per launch), within [least, 4096].
+int split_edges_for(const Tuning &t, int64_t entries, int least) {
   if (t.split_edges >= 64) return t.split_edges;
-  int64_t s = (entries / 16384 + 63) / 64 * 64;
-  if (s < 256) s = 256;
+  int64_t s = (entries / 16384 + least - 1) / least * least;
+  if (s < least) s = least;
   if (s > 4096) s = 4096;
   return (int)s;
 }
@@ -223,7 +223,7 @@ struct PlanCounts {
 // Upper bounds (from row lengths alone) on tasks / cut rows / slots of every chunk: a row cut by
 // source class adds at most one extra piece per class.
 PlanCounts count_plan(const Tuning &tune, const int64_t *ptr, const std::vector<int64_t> &chunk_ptr, int classes, int min_row,
-                      const uint8_t *force = nullptr) {
+                      int least_piece, const uint8_t *force = nullptr) {
   PlanCounts pc;
   const int K = (int)chunk_ptr.size() - 1;
   pc.tasks.assign(K, 0);
@@ -231,7 +231,7 @@ PlanCounts count_plan(const Tuning &tune, const int64_t *ptr, const std::vector<
   pc.slots.assign(K, 0);
   pc.split.assign(K, 0);
   for (int c = 0; c < K; ++c) {
-    const int split = split_edges_for(tune, ptr[chunk_ptr[c + 1]] - ptr[chunk_ptr[c]]);
+    const int split = split_edges_for(tune, ptr[chunk_ptr[c + 1]] - ptr[chunk_ptr[c]], least_piece);
     pc.split[c] = split;
     for (int64_t r = chunk_ptr[c]; r < chunk_ptr[c + 1]; ++r) {
       const int64_t len = ptr[r + 1] - ptr[r];
@@ -281,7 +281,7 @@ struct HostDir {
 void host_mask_set(ChunkMask &m, int c) { m.w[c >> 6] |= 1ull << (c & 63); }
 
 bool make_host_dir(const Tuning &tune, const int64_t *ptr, const int32_t *idx, int64_t n, const std::vector<int64_t> &chunk_ptr,
-                   int classes, bool hot, bool want_orig, bool try_dense, int dense_width, HostDir &h) {
+                   int classes, bool hot, bool want_orig, bool try_dense, int dense_width, int least_piece, HostDir &h) {
   const int K = (int)chunk_ptr.size() - 1;
   h.ptr = ptr;
   h.idx = idx;
@@ -335,7 +335,7 @@ bool make_host_dir(const Tuning &tune, const int64_t *ptr, const int32_t *idx, i
     if (!build_hot_order(h.ptr, h.idx, n, h.min_row, want_orig, h.hot)) return false;
     h.idx = h.hot.idx.data();
   }
-  h.pc = count_plan(tune, h.ptr, chunk_ptr, classes, h.min_row, h.force_ptr());
+  h.pc = count_plan(tune, h.ptr, chunk_ptr, classes, h.min_row, least_piece, h.force_ptr());
   return true;
 }
 
@@ -405,6 +405,19 @@ struct Shape {
   int classes() const {
     if (hot()) return hot_classes_setting(tune, n * widest_row_bytes());
     return xcd_classes_setting(tune, n * widest_row_bytes());
+  }
+  // Shortest piece that long rows of small launches are cut into.  The vector-ALU kernel has 8 row pieces of a task in
+  // flight, the matrix-core kernel turns 128 entries at a time into gathers.  Measured with pieces of 32 / 64 / 128
+  // entries on the vector-ALU kernel: 5 k vertices of width 1000, 32 chunks 23.1 / 23.5 / 24.6 ms per step; 89 k vertices of
+  // width 100 16.1 / 16.6 / 18.1 ms.  64 / 128 / 256 on the matrix-core kernel: 9.45 / 9.61 / 9.59 ms (300 k vertices of
+  // width 128), 13.9 / 13.3 / 13.6 ms (169 k vertices of width 256).
+  int least_piece() const {
+    int valu = 0;
+    for (int j = 0; j < L; ++j) {
+      const bool f32_rows = dtype == GNNSTAGE_F32 || (j == 0 && level0_f32 && !tf[j]);
+      valu += f32_rows || (tf[j] ? dims[j + 1] : dims[j]) % 8 != 0 || tune.spmm_valu;
+    }
+    return valu == L ? 32 : valu > 0 ? 64 : 128;
   }
   // dense blocks serve the matrix-core aggregation only: every aggregation of the stage must gather bf16 rows
   // of width 128 or 256
@@ -1211,8 +1224,8 @@ int make_host_plan(const gnnstage_desc *d, const Shape &s, bool want_edge, HostP
     return GNNSTAGE_EINVAL;
   }
   const bool dense = s.dense_ok();
-  if (!make_host_dir(s.tune, d->row_ptr, d->col_idx, s.n, s.chunk_ptr, s.classes(), s.hot(), want_edge, dense, s.dense_width(), hp.f) ||
-      !make_host_dir(s.tune, hp.t_ptr.data(), hp.t_row.data(), s.n, s.chunk_ptr, s.classes(), s.hot(), want_edge, dense, s.dense_width(), hp.b)) {
+  if (!make_host_dir(s.tune, d->row_ptr, d->col_idx, s.n, s.chunk_ptr, s.classes(), s.hot(), want_edge, dense, s.dense_width(), s.least_piece(), hp.f) ||
+      !make_host_dir(s.tune, hp.t_ptr.data(), hp.t_row.data(), s.n, s.chunk_ptr, s.classes(), s.hot(), want_edge, dense, s.dense_width(), s.least_piece(), hp.b)) {
     err = "cannot plan the aggregation";
     return GNNSTAGE_EINVAL;
   }

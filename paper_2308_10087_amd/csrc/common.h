@@ -219,6 +219,7 @@ struct GemmNtArgs {
   int32_t out_pad;  // columns [N, out_pad) of every output row are written as zeros (0: none)
   int32_t vec_epi;  // set by the launcher: the epilogue may use 16-byte accesses
   float mask_scale = 1.f;  // EPI_MASK: what passes the mask is scaled (1 / (1 - rate) of that dropout)
+  LnDropout drop{};        // EPI_FWD_GCN / EPI_FWD_ADD: dropout of the layer's output (threshold 0: none)
   int32_t ws_min_rows = 65536;  // rows from which the weight-stationary kernel is used (tests force it on small inputs)
 };
 int launch_gemm_nt(const GemmNtArgs &a, int compute_dtype, hipStream_t s);
@@ -236,7 +237,7 @@ struct GemmTnArgs {
   float *dW;       // fp32 [I][O]
   float *partial;  // fp32 scratch [splits][I][O]
   int32_t max_splits;
-  float *dbias;         // optional (bf16 product only): dbias[o] += column sums of B, fused into the product
+  float *dbias;         // optional: dbias[o] += column sums of B, fused into the product
   float *bias_partial;  // fp32 scratch [splits][O]
   int32_t wide_min_rows = 65536;  // bf16 operands from this many rows on, with more than one 128 x 128 output tile: one
                                   // workgroup per row split computes the whole output (tests force it on small inputs)

@@ -4,7 +4,7 @@
 //   TN:  dW[I x O] += s * A[M x I]^T . B[M x O]    weight gradient (reduction over chunk rows)
 //
 // bf16 operands go through the gfx950 matrix cores (v_mfma_f32_32x32x16_bf16, fp32
-// accumulation); the fp32 variants are plain LDS-tiled FMA kernels used by the fp32 stage.
+// accumulation), fp32 operands of the fp32 stage through v_mfma_f32_32x32x2_f32 / 16x16x4.
 // Bias / ReLU / GCNII residual terms are applied in the epilogue on the fp32 accumulators.
 // Bt and B always live in the library's zero-padded internal buffers (16-byte aligned rows);
 // A may also be a caller-owned level buffer of any width and of fp32 or bf16 type, in which case
@@ -18,6 +18,7 @@ namespace {
 typedef bf16_t bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));  // of a row that is only known to be 4-byte aligned
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -36,10 +37,12 @@ __device__ inline void store_f32(void *p, int dtype, size_t idx, float v) {
     static_cast<float *>(p)[idx] = v;
 }
 
-// One output element of an NT product: epilogue + store.
+// One output element of an NT product: epilogue + store.  DROP: the dropout of the layer's output too.
+// EPI: the epilogue to apply (negative: a.epilogue).
+template <int EPI = -1, bool DROP = false>
 __device__ inline void epilogue_store(const GemmNtArgs &a, int m, int n, float acc) {
   float r;
-  switch (a.epilogue) {
+  switch (EPI >= 0 ? EPI : a.epilogue) {
     case EPI_FWD_GCN: {
       r = acc + a.bias[n];
       r = r > 0.f ? r : 0.f;
@@ -76,6 +79,8 @@ __device__ inline void epilogue_store(const GemmNtArgs &a, int m, int n, float a
       break;
     }
   }
+  if constexpr (DROP)
+    if (a.drop.threshold > 0) r = dropout_keep(a.drop, a.drop.u0 + m, a.N, n) ? r * a.drop.scale : 0.f;
   store_f32(a.out, a.out_dtype, (size_t)m * a.out_ld + n, r);
 }
 
@@ -825,120 +830,349 @@ __global__ __launch_bounds__(512) void gemm_tn_bf16_wide_kernel(const GemmTnArgs
       }
 }
 
-// ------------------------------------------------------------------------------------ fp32 NT
-template <bool VEC>
-__global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const GemmNtArgs a) {
-  constexpr int T = 64, KB = 16;
-  __shared__ float As[KB][T + 4];
-  __shared__ float Bs[KB][T + 4];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.x * T, n0 = blockIdx.y * T;
-  const float *A = static_cast<const float *>(a.A);
-  const float *Bt = static_cast<const float *>(a.Bt);
-  float acc[4][4] = {};
-  const int lr = tid >> 2, lk = (tid & 3) * 4;
-  for (int k0 = 0; k0 < a.Kp; k0 += KB) {
-    f32x4 va = {0.f, 0.f, 0.f, 0.f}, vb = {0.f, 0.f, 0.f, 0.f};
-    if (m0 + lr < a.M) {
-      const float *p = A + (size_t)(m0 + lr) * a.lda + k0 + lk;
-      if constexpr (VEC) {
-        if (k0 + lk < a.Kp) va = *reinterpret_cast<const f32x4 *>(p);
-      } else {
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-          if (k0 + lk + t < a.K) va[t] = p[t];
-      }
-    }
-    if (n0 + lr < a.N && k0 + lk < a.Kp) vb = *reinterpret_cast<const f32x4 *>(Bt + (size_t)(n0 + lr) * a.ldb + k0 + lk);
-    __syncthreads();
-#pragma unroll
+// ------------------------------------------------------------------------------------ fp32
+// fp32 products run on the matrix cores too (v_mfma_f32_32x32x2_f32 and 16x16x4: fp32 operands, fp32 multiply-adds, the
+// same 157 TFLOP/s as the vector ALU's best, without its operand traffic).  Operands go straight from memory into
+// registers, 16 bytes per lane: the order in which a matrix instruction walks the reduction index is free as long as both
+// operands walk it alike, so four consecutive elements of a row feed four instructions.
+
+// Four consecutive output columns n .. n + 3 of row m: epilogue, dropout of the layer's output, store.  Columns from N on
+// are padding (zeros up to out_pad).
+// (The epilogue is a template parameter: one kernel for all of them carries all of their code past every launch.)
+template <int EPI>
+__device__ inline void epilogue_store4_f32(const GemmNtArgs &a, int m, int n, const f32x4 acc) {
+  if (n + 4 > a.N) {
+#pragma unroll 1
     for (int t = 0; t < 4; ++t) {
-      As[lk + t][lr] = va[t];
-      Bs[lk + t][lr] = vb[t];
+      if (n + t < a.N)
+        epilogue_store<EPI, true>(a, m, n + t, acc[t]);
+      else if (n + t < a.out_pad)
+        static_cast<float *>(a.out)[(size_t)m * a.out_ld + n + t] = 0.f;
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < KB; ++k) {
-      float x[4], y[4];
+    return;
+  }
+  f32x4 r = acc, x = {0.f, 0.f, 0.f, 0.f};
+  if (EPI != EPI_FWD_GCN && EPI != EPI_PLAIN)
+    x = *reinterpret_cast<const f32x4_u *>(static_cast<const float *>(a.aux) + (size_t)m * a.aux_ld + n);
+  switch (EPI) {
+    case EPI_FWD_GCN:
+    case EPI_FWD_ADD:
+    case EPI_RES: {
+      const f32x4 b = *reinterpret_cast<const f32x4_u *>(a.bias + n);
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        x[t] = As[k][ty * 4 + t];
-        y[t] = Bs[k][tx * 4 + t];
+        const float y = EPI == EPI_FWD_GCN ? acc[t] + b[t] : acc[t] + b[t] + x[t];
+        r[t] = (EPI == EPI_RES || y > 0.f) ? y : 0.f;
       }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += x[i] * y[j];
+      break;
     }
+    case EPI_FWD_GCNII: {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const float y = (1.f - a.beta) * x[t] + a.beta * acc[t];
+        r[t] = y > 0.f ? y : 0.f;
+      }
+      break;
+    }
+    case EPI_MASK: {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) r[t] = x[t] > 0.f ? acc[t] * a.mask_scale : 0.f;
+      break;
+    }
+    case EPI_DGRAD_GCNII: {
+      f32x4 dp;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        dp[t] = (1.f - a.beta) * x[t] + a.beta * acc[t];
+        r[t] = (1.f - a.alpha) * dp[t];
+      }
+      if (a.h0grad) {
+        f32x4_u *h = reinterpret_cast<f32x4_u *>(a.h0grad + (size_t)m * a.h0_ld + n);
+        f32x4 v = *h;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] += a.alpha * dp[t];
+        *h = v;
+      }
+      break;
+    }
+    default: break;  // EPI_PLAIN
   }
+  if ((EPI == EPI_FWD_GCN || EPI == EPI_FWD_ADD) && a.drop.threshold > 0) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < a.M && n < a.N)
-        epilogue_store(a, m, n, acc[i][j]);
-      else if (m < a.M && n < a.out_pad)
-        store_f32(a.out, a.out_dtype, (size_t)m * a.out_ld + n, 0.f);
-    }
+    for (int t = 0; t < 4; ++t) r[t] = dropout_keep(a.drop, a.drop.u0 + m, a.N, n + t) ? r[t] * a.drop.scale : 0.f;
+  }
+  *reinterpret_cast<f32x4_u *>(static_cast<float *>(a.out) + (size_t)m * a.out_ld + n) = r;
 }
 
-// ------------------------------------------------------------------------------------ fp32 TN
-template <bool VEC>
-__global__ __launch_bounds__(256) void gemm_tn_f32_kernel(const GemmTnArgs a, int rows_per_split) {
-  constexpr int T = 64, RB = 16;
-  __shared__ float As[RB][T + 4];
-  __shared__ float Bs[RB][T + 4];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int i0 = blockIdx.x * T, o0 = blockIdx.y * T;
-  const int r_begin = blockIdx.z * rows_per_split;
-  const int r_end = min(a.M, r_begin + rows_per_split);
-  const float *A = static_cast<const float *>(a.A);
-  const float *B = static_cast<const float *>(a.B);
-  float acc[4][4] = {};
-  const int lr = tid >> 4, lc = (tid & 15) * 4;
-  for (int r0 = r_begin; r0 < r_end; r0 += RB) {
-    f32x4 va = {0.f, 0.f, 0.f, 0.f}, vb = {0.f, 0.f, 0.f, 0.f};
-    if (r0 + lr < r_end) {
-      const float *p = A + (size_t)(r0 + lr) * a.lda + i0 + lc;
-      if constexpr (VEC) {
-        if (i0 + lc < a.lda) va = *reinterpret_cast<const f32x4 *>(p);
-      } else {
+// C[M x N] = A[M x K] . Bt[N x Kp]^T in 32 x 32 wave tiles.
+// KS = 4: the four waves of a workgroup share ONE tile and split K between them (every fourth group of 16); their sums are
+// added in LDS.  A chunk's product is small (162 x 1000 x 1000 in a 32-chunk pass over 5 k vertices: 192 tiles for 1,024
+// SIMDs), so what bounds it is the serial chain over K, which this cuts by four: 72 -> 11.2 us for that product (half of it
+// matrix instructions on three quarters of the CUs), 13 -> 4.5 us for 1,078 x 100 x 100 (64 x 64 vector-ALU tiles through
+// LDS before).  Eight waves per tile: 11.3 us.
+// KS = 1: a wave per quadrant of a 64 x 64 tile, for products of many tiles: half the operand bytes per product through L2.
+template <int KS, int EPI>
+__global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const GemmNtArgs a) {
+  constexpr int T = KS == 4 ? 32 : 64;  // rows and columns of a workgroup's tile
+  constexpr int D = 4;                  // groups of 16 reduction elements in flight per wave
+  constexpr int PS = 36;                // padded row stride (floats) of a 32 x 32 patch
+  constexpr int LS = 20;                // row stride (floats) of a staged operand: conflict-free 16-byte reads
+  __shared__ __attribute__((aligned(16))) float lds_all[4][2 * 4 * 16 * LS];
+  static_assert(32 * PS <= 2 * 4 * 16 * LS, "the result patch reuses the staging memory");
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  float *lds = lds_all[wave];
+  // Workgroups go round-robin over the 8 XCDs; each takes a contiguous run of tiles that share a block of A rows (row
+  // tiles outside) or a block of Bt rows (column tiles outside), whichever moves fewer bytes into the eight L2s.
+  const int mt = (a.M + T - 1) / T, nt = (a.N + T - 1) / T;
+  const int work = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (work >= mt * nt) return;
+  const bool cols_outside = a.M < a.N;
+  int m0 = (cols_outside ? work % mt : work / nt) * T, n0 = (cols_outside ? work / mt : work % nt) * T;
+  if constexpr (KS == 1) {
+    m0 += (wave >> 1) * 32;
+    n0 += (wave & 1) * 32;
+    if (m0 >= a.M || n0 >= a.N) return;  // the padding columns lie inside the tile that holds column N - 1
+  }
+  // A wave instruction loads 16 rows x 64 bytes, four lanes per row, and the pieces change lanes in a wave-private LDS
+  // patch, one group ahead of the products.  (Loaded in the operand layout of the matrix instruction, a row per lane,
+  // every quarter of a wave touches 16 cache lines: nothing for small products, 6 % of a step whose products are large.)
+  const int lrow = lane >> 2, lk = (lane & 3) * 4, l16 = lane & 15, kq = (lane >> 4) * 4;
+  const float *A[2], *B[2];
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-          if (i0 + lc + t < a.I) va[t] = p[t];
+  for (int h = 0; h < 2; ++h) {
+    const int ml = m0 + 16 * h + lrow, nl = n0 + 16 * h + lrow;
+    A[h] = static_cast<const float *>(a.A) + (size_t)(ml < a.M ? ml : a.M - 1) * a.lda + lk;
+    B[h] = static_cast<const float *>(a.Bt) + (size_t)(nl < a.N ? nl : a.N - 1) * a.ldb + lk;
+  }
+  f32x4 acc[2][2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 fa[D][2], fb[D][2];
+  const int g0 = KS == 4 ? wave : 0;
+  auto load = [&](int i, int u) {  // the wave's i-th group of 16 into slot u
+    const int k = (g0 + i * KS) * 16;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      fa[u][h] = *reinterpret_cast<const f32x4_u *>(A[h] + k);
+      fb[u][h] = *reinterpret_cast<const f32x4_u *>(B[h] + k);
+    }
+  };
+  auto stage = [&](int u) {  // slot u goes to LDS patch u & 1
+    float *p = lds + (u & 1) * (4 * 16 * LS) + lrow * LS + lk;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      *reinterpret_cast<f32x4 *>(p + h * 16 * LS) = fa[u][h];
+      *reinterpret_cast<f32x4 *>(p + (2 + h) * 16 * LS) = fb[u][h];
+    }
+  };
+  auto consume = [&](int u) {
+    __builtin_amdgcn_wave_barrier();
+    const float *p = lds + (u & 1) * (4 * 16 * LS) + l16 * LS + kq;
+    f32x4 x4[2], y4[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      x4[h] = *reinterpret_cast<const f32x4 *>(p + h * 16 * LS);
+      y4[h] = *reinterpret_cast<const f32x4 *>(p + (2 + h) * 16 * LS);
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(x4[x][t], y4[y][t], acc[x][y], 0, 0, 0);
+  };
+  const int full = a.K / 16;  // groups without a bounds check
+  const int cnt = full > g0 ? (full - g0 + KS - 1) / KS : 0;
+  // Loads past the wave's last group repeat it (exact wait counts, and half the code of a loop with a drain: a launch this
+  // short pays for every line of code it fetches).
+  if (cnt <= D) {
+#pragma unroll
+    for (int u = 0; u < D; ++u)
+      if (u < cnt) load(u, u);
+#pragma unroll
+    for (int u = 0; u < D; ++u)
+      if (u < cnt) {
+        stage(u);
+        consume(u);
       }
-      if (o0 + lc < a.ldb) vb = *reinterpret_cast<const f32x4 *>(B + (size_t)(r0 + lr) * a.ldb + o0 + lc);
-    }
-    __syncthreads();
+  } else {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      As[lr][lc + t] = va[t];
-      Bs[lr][lc + t] = vb[t];
-    }
-    __syncthreads();
+    for (int u = 0; u < D; ++u) load(u, u);
+    stage(0);
+    int i = 0;
+    for (; i + D < cnt; i += D) {
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      float x[4], y[4];
+      for (int u = 0; u < D; ++u) {
+        load(i + D + u < cnt ? i + D + u : cnt - 1, u);  // slot u is in LDS already
+        stage((u + 1) % D);
+        consume(u);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < D; ++u)
+      if (i + u < cnt) {
+        if (i + u + 1 < cnt) stage((u + 1) % D);
+        consume(u);
+      }
+  }
+  if (full * 16 < a.K && (KS == 1 || (full & 3) == wave)) {  // the last, partial group
+    const int k = full * 16;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        x[t] = As[r][ty * 4 + t];
-        y[t] = Bs[r][tx * 4 + t];
+        const bool in = k + lk + t < a.K;
+        fa[0][h][t] = in ? A[h][k + t] : 0.f;
+        fb[0][h][t] = in ? B[h][k + t] : 0.f;
       }
+    __builtin_amdgcn_wave_barrier();
+    stage(0);
+    consume(0);
+  }
+  // element e of lane l of an instruction tile is row 4 * (l / 16) + e, column l % 16
+  __builtin_amdgcn_wave_barrier();
+  float *patch = lds;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+  for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += x[i] * y[j];
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) patch[(16 * x + kq + e) * PS + 16 * y + l16] = acc[x][y][e];
+  if constexpr (KS == 4) {
+    __syncthreads();
+    const int r = tid >> 3, c = (tid & 7) * 4;
+    f32x4 v = *reinterpret_cast<const f32x4 *>(&lds_all[0][r * PS + c]);
+#pragma unroll
+    for (int w = 1; w < 4; ++w) v += *reinterpret_cast<const f32x4 *>(&lds_all[w][r * PS + c]);
+    if (m0 + r < a.M) epilogue_store4_f32<EPI>(a, m0 + r, n0 + c, v);
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int ps = 0; ps < 4; ++ps) {
+      const int r = ps * 8 + (lane >> 3), c = (lane & 7) * 4;
+      const f32x4 v = *reinterpret_cast<const f32x4 *>(&patch[r * PS + c]);
+      if (m0 + r < a.M) epilogue_store4_f32<EPI>(a, m0 + r, n0 + c, v);
     }
   }
-  float *P = a.partial + (size_t)blockIdx.z * a.I * a.O;
+}
+
+// dW[I x O] += A[M x I]^T . B[M x O] over a split of the rows.  A wave owns 16 V x 16 V outputs; a load takes four rows,
+// 4 V bytes per lane, and element t of a lane's vector is the operand of output tile t: tile (ta, tb) holds the columns
+// 4 m + ta of A and 4 n + tb of B (V = 4), so V^2 matrix instructions share one pair of loads and nothing passes through
+// LDS.  The four waves of a workgroup take the steps of four rows in turn and add their tiles in LDS at the end.  The last
+// vector of a row moves back inside the row (those outputs are computed by two lanes alike).  V = 1 serves operands
+// narrower than four columns.  10.4 GFLOP over 5,196 rows (1000 x 1000): 160 -> 112 us (93 TFLOP/s); 34 k rows,
+// 100 x 100 outputs: 24 -> 18 us; the bias gradient (column sums of B) rides along, 17 - 27 us as a kernel of its own
+// before.
+template <int V>
+__global__ __launch_bounds__(256) void gemm_tn_f32_kernel(const GemmTnArgs a, int rows_per_split, int splits) {
+  constexpr int T = 16 * V;
+  constexpr int D = 4;  // steps of four rows in flight per wave
+  typedef float vec_t __attribute__((ext_vector_type(V), aligned(4)));
+  __shared__ float red[4][T * T];
+  __shared__ float bred[4][T];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int ti = (a.I + T - 1) / T, tiles = ti * ((a.O + T - 1) / T);
+  // an XCD takes a contiguous run of (split, tile) pairs: the tiles that read the same rows share its L2
+  const int work = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int tile = work % tiles, split = work / tiles;
+  if (split >= splits) return;
+  const int i0 = (tile % ti) * T, o0 = (tile / ti) * T;
+  const int r_begin = split * rows_per_split;
+  const int r_end = min(a.M, r_begin + rows_per_split);
+  const int lr = lane >> 4, lc = (lane & 15) * V;
+  const int ci = min(i0 + lc, a.I - V), co = min(o0 + lc, a.O - V);
+  const float *A = static_cast<const float *>(a.A) + ci;
+  const float *B = static_cast<const float *>(a.B) + co;
+  f32x4 acc[V][V];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int x = 0; x < V; ++x)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int ii = i0 + ty * 4 + i, oo = o0 + tx * 4 + j;
-      if (ii < a.I && oo < a.O) P[(size_t)ii * a.O + oo] = acc[i][j];
+    for (int y = 0; y < V; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bool do_bias = a.bias_partial != nullptr && i0 == 0;
+  float bsum[V];
+#pragma unroll
+  for (int t = 0; t < V; ++t) bsum[t] = 0.f;
+  float fa[D][V], fb[D][V];
+  const int steps = (r_end - r_begin + 3) / 4;
+  const int cnt = steps > wave ? (steps - wave + 3) / 4 : 0;  // of this wave: steps wave, wave + 4, ...
+  auto load = [&](int i, int u) {
+    const int r = r_begin + (wave + 4 * i) * 4 + lr;
+    const size_t rr = (size_t)(r < r_end ? r : r_end - 1);
+    const vec_t x = *reinterpret_cast<const vec_t *>(A + rr * a.lda), y = *reinterpret_cast<const vec_t *>(B + rr * a.ldb);
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+      fa[u][t] = x[t];
+      fb[u][t] = y[t];
     }
+  };
+  auto consume = [&](int i, int u) {
+    const bool in = r_begin + (wave + 4 * i) * 4 + lr < r_end;  // rows past the end add nothing
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+      fa[u][t] = in ? fa[u][t] : 0.f;
+      fb[u][t] = in ? fb[u][t] : 0.f;
+    }
+    if (do_bias) {
+#pragma unroll
+      for (int t = 0; t < V; ++t) bsum[t] += fb[u][t];
+    }
+#pragma unroll
+    for (int x = 0; x < V; ++x)
+#pragma unroll
+      for (int y = 0; y < V; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[u][x], fb[u][y], acc[x][y], 0, 0, 0);
+  };
+#pragma unroll
+  for (int u = 0; u < D; ++u)
+    if (u < cnt) load(u, u);
+  int i = 0;
+  for (; i + 2 * D <= cnt; i += D) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      consume(i + u, u);
+      load(i + D + u, u);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < D; ++u) {
+    if (i + u < cnt) consume(i + u, u);
+    if (i + D + u < cnt) load(i + D + u, u);
+  }
+#pragma unroll
+  for (int u = 0; u < D; ++u)
+    if (i + D + u < cnt) consume(i + D + u, u);
+  // element e of lane l of tile (x, y) is A column vector 4*(l/16) + e, element x, and B column vector l%16, element y
+#pragma unroll
+  for (int x = 0; x < V; ++x)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int y = 0; y < V; ++y) red[wave][((4 * (lane >> 4) + e) * V + x) * T + (lane & 15) * V + y] = acc[x][y][e];
+  if (do_bias) {
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+      bsum[t] += __shfl_xor(bsum[t], 16);
+      bsum[t] += __shfl_xor(bsum[t], 32);
+    }
+    if (lane < 16) {
+#pragma unroll
+      for (int t = 0; t < V; ++t) bred[wave][lane * V + t] = bsum[t];
+    }
+  }
+  __syncthreads();
+  float *P = a.partial + (size_t)split * a.I * a.O;
+  for (int idx = tid; idx < T * T; idx += 256) {
+    const int r = idx / T, c = idx % T, rv = i0 + r / V * V, cv = o0 + c / V * V;  // first columns of the two vectors
+    if (rv < a.I && cv < a.O)
+      P[(size_t)(min(rv, a.I - V) + r % V) * a.O + min(cv, a.O - V) + c % V] = (red[0][idx] + red[1][idx]) + (red[2][idx] + red[3][idx]);
+  }
+  if (do_bias && tid < T && o0 + tid / V * V < a.O)
+    a.bias_partial[(size_t)split * a.O + min(o0 + tid / V * V, a.O - V) + tid % V] = (bred[0][tid] + bred[1][tid]) + (bred[2][tid] + bred[3][tid]);
 }
 
 // dst[e] += scale * sum_s partial[s][e].  Fixed summation order => reproducible.  64 outputs per block,
@@ -1043,65 +1277,85 @@ bool vec_ok(const void *p, int ld, int mult) { return (reinterpret_cast<uintptr_
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 static bool pair_ok(const void *p, int ld) { return (reinterpret_cast<uintptr_t>(p) & 7u) == 0 && ld % 2 == 0; }
 
+static int launch_gemm_nt_bf16(const GemmNtArgs &a, hipStream_t s) {
+  const int mt = (a.M + BM - 1) / BM, ntiles = (a.N + BN - 1) / BN;
+  dim3 grid((unsigned)(((mt + 7) / 8) * 8 * ntiles));
+  const bool vec = a.a_dtype == DT_BF16 && vec_ok(a.A, a.lda, 8) && a.lda >= a.Kp;
+  if (a.a_dtype == DT_F32 && pair_ok(a.A, a.lda))
+    hipLaunchKernelGGL((gemm_nt_bf16_kernel<float, false, true>), grid, dim3(256), 0, s, a);
+  else if (a.a_dtype == DT_F32)
+    hipLaunchKernelGGL((gemm_nt_bf16_kernel<float, false>), grid, dim3(256), 0, s, a);
+  else if (vec && vec_ok(a.Bt, a.ldb, 8) && a.Kp <= 256 && a.N <= 256 && a.M >= a.ws_min_rows) {
+    // long operands: persistent weight-stationary kernel (needs a few row tiles per workgroup to pay
+    // for loading its panel of Bt into registers)
+    if (a.N <= 128 && a.Kp <= 128) return launch_ws<2, 8>(a, s);
+    if (a.N <= 128) return launch_ws<2, 16>(a, s);
+    if (a.Kp <= 128) return launch_ws<4, 8>(a, s);
+    return launch_ws<4, 16>(a, s);
+  } else if (vec && a.Kp >= 128 && (long long)mt * ntiles <= 1024)
+    // short operands: every workgroup is resident at once, the product is its chain of K steps
+    hipLaunchKernelGGL((gemm_nt_bf16_kernel<bf16_t, true, false, 64>), grid, dim3(256), 0, s, a);
+  else if (vec)
+    hipLaunchKernelGGL((gemm_nt_bf16_kernel<bf16_t, true>), grid, dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL((gemm_nt_bf16_kernel<bf16_t, false>), grid, dim3(256), 0, s, a);
+  return (int)hipGetLastError();
+}
+
+typedef void (*nt_f32_fn)(const GemmNtArgs);
 int launch_gemm_nt(const GemmNtArgs &a_in, int compute_dtype, hipStream_t s) {
   if (a_in.M <= 0 || a_in.N <= 0) return hipSuccess;
   GemmNtArgs a = a_in;
+  if (compute_dtype != DT_BF16) {
+    if (a.a_dtype != DT_F32) return hipErrorInvalidValue;
+    // 64 x 64 tiles from two workgroups per compute unit on (a wave then walks all of K), below that 32 x 32 tiles with K
+    // split over the waves
+    const long long mt64 = (a.M + 63) / 64, nt64 = (a.N + 63) / 64;
+    const bool wide = mt64 * nt64 >= 512;
+    const long long tiles = wide ? mt64 * nt64 : (long long)((a.M + 31) / 32) * ((a.N + 31) / 32);
+#define NT_F32(KS) {gemm_nt_f32_kernel<KS, 0>, gemm_nt_f32_kernel<KS, 1>, gemm_nt_f32_kernel<KS, 2>, gemm_nt_f32_kernel<KS, 3>, \
+                    gemm_nt_f32_kernel<KS, 4>, gemm_nt_f32_kernel<KS, 5>, gemm_nt_f32_kernel<KS, 6>}
+    static const nt_f32_fn table[2][7] = {NT_F32(4), NT_F32(1)};  // indexed by GemmEpilogue
+#undef NT_F32
+    if (a.epilogue < 0 || a.epilogue > 6) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(table[wide][a.epilogue], dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), 0, s, a);
+    return (int)hipGetLastError();
+  }
   const bool has_aux = a.epilogue == EPI_FWD_GCNII || a.epilogue == EPI_MASK || a.epilogue == EPI_DGRAD_GCNII ||
                        a.epilogue == EPI_FWD_ADD || a.epilogue == EPI_RES;
   a.vec_epi = a.N % 8 == 0 && a.out_ld % 8 == 0 && aligned16(a.out) && (a.out_pad <= a.N) &&
               (!has_aux || (a.aux_ld % 8 == 0 && aligned16(a.aux))) &&
               ((a.epilogue != EPI_FWD_GCN && a.epilogue != EPI_FWD_ADD && a.epilogue != EPI_RES) || aligned16(a.bias)) &&
               (a.epilogue != EPI_DGRAD_GCNII || !a.h0grad || (a.h0_ld % 4 == 0 && aligned16(a.h0grad)));
-  if (compute_dtype == DT_BF16) {
-    const int mt = (a.M + BM - 1) / BM, ntiles = (a.N + BN - 1) / BN;
-    dim3 grid((unsigned)(((mt + 7) / 8) * 8 * ntiles));
-    const bool vec = a.a_dtype == DT_BF16 && vec_ok(a.A, a.lda, 8) && a.lda >= a.Kp;
-    if (a.a_dtype == DT_F32 && pair_ok(a.A, a.lda))
-      hipLaunchKernelGGL((gemm_nt_bf16_kernel<float, false, true>), grid, dim3(256), 0, s, a);
-    else if (a.a_dtype == DT_F32)
-      hipLaunchKernelGGL((gemm_nt_bf16_kernel<float, false>), grid, dim3(256), 0, s, a);
-    else if (vec && vec_ok(a.Bt, a.ldb, 8) && a.Kp <= 256 && a.N <= 256 && a.M >= a.ws_min_rows) {
-      // long operands: persistent weight-stationary kernel (needs a few row tiles per workgroup to pay
-      // for loading its panel of Bt into registers)
-      if (a.N <= 128 && a.Kp <= 128) return launch_ws<2, 8>(a, s);
-      if (a.N <= 128) return launch_ws<2, 16>(a, s);
-      if (a.Kp <= 128) return launch_ws<4, 8>(a, s);
-      return launch_ws<4, 16>(a, s);
-    } else if (vec && a.Kp >= 128 && (long long)mt * ntiles <= 1024)
-      // short operands: every workgroup is resident at once, the product is its chain of K steps
-      hipLaunchKernelGGL((gemm_nt_bf16_kernel<bf16_t, true, false, 64>), grid, dim3(256), 0, s, a);
-    else if (vec)
-      hipLaunchKernelGGL((gemm_nt_bf16_kernel<bf16_t, true>), grid, dim3(256), 0, s, a);
-    else
-      hipLaunchKernelGGL((gemm_nt_bf16_kernel<bf16_t, false>), grid, dim3(256), 0, s, a);
-  } else {
-    if (a.a_dtype != DT_F32) return hipErrorInvalidValue;
-    dim3 grid((a.M + 63) / 64, (a.N + 63) / 64);
-    if (vec_ok(a.A, a.lda, 4) && a.lda >= a.Kp)
-      hipLaunchKernelGGL(gemm_nt_f32_kernel<true>, grid, dim3(256), 0, s, a);
-    else
-      hipLaunchKernelGGL(gemm_nt_f32_kernel<false>, grid, dim3(256), 0, s, a);
-  }
-  return (int)hipGetLastError();
+  // drawing inside the epilogues of the bf16 kernels costs them registers they do not have (the forward products of a
+  // 233 k vertex stage went from 0.68 to 2.65 ms with dropout off): a pass of its own behind the product
+  a.drop = LnDropout{};
+  const int e = launch_gemm_nt_bf16(a, s);
+  if (e != 0 || a_in.drop.threshold == 0) return e;
+  return launch_dropout_rows(a.out, a.out_dtype, a.M, a.N, a.out_ld, a_in.drop, s);
 }
 
 int launch_gemm_tn(const GemmTnArgs &a, int compute_dtype, hipStream_t s) {
   if (a.M <= 0 || a.I <= 0 || a.O <= 0) return hipSuccess;
-  const int tile = compute_dtype == DT_BF16 ? 128 : 64;
+  const bool narrow = a.I < 4 || a.O < 4;  // fp32 operands of fewer columns than a 16-byte vector
+  const int tile = compute_dtype == DT_BF16 ? 128 : narrow ? 16 : 64;
   const int step = compute_dtype == DT_BF16 ? TR : 16;
   const int ti = (a.I + tile - 1) / tile, to = (a.O + tile - 1) / tile;
-  int splits = 1024 / (ti * to);  // about four blocks per compute unit ...
+  int splits = (compute_dtype == DT_BF16 ? 1024 : 512) / (ti * to);  // about four (fp32: two) blocks per compute unit ...
   // ... but the fp32 partials (write + read, 8 bytes per output element and split) should not move more than
   // twice the operands themselves (2 bytes per element of A and B); below that the kernel is latency-bound and
   // more blocks win
   const long long cap = (long long)a.M * (a.I + a.O) / (2LL * a.I * a.O);
-  if (splits > cap) splits = (int)cap;
+  if (compute_dtype == DT_BF16) {
+    if (splits > cap) splits = (int)cap;
+  } else if (splits > a.M / 64) {  // fp32: at least 16 rows per wave
+    splits = a.M / 64;
+  }
   if (splits < 1) splits = 1;
   if (splits > a.max_splits) splits = a.max_splits;
   int rows_per = (a.M + splits - 1) / splits;
   rows_per = (rows_per + step - 1) / step * step;
   splits = (a.M + rows_per - 1) / rows_per;
-  dim3 grid(ti, to, splits);
   // long operands with more than one 128 x 128 output tile: one workgroup per row split computes all of the output
   const bool wide = compute_dtype == DT_BF16 && a.a_dtype == DT_BF16 && a.M >= a.wide_min_rows && ti * to > 1 && a.I <= 256 &&
                     a.O <= 256 && vec_ok(a.A, a.lda, 8) && vec_ok(a.B, a.ldb, 8);
@@ -1123,15 +1377,15 @@ int launch_gemm_tn(const GemmTnArgs &a, int compute_dtype, hipStream_t s) {
       hipLaunchKernelGGL((gemm_tn_bf16_kernel<bf16_t, false>), g1, dim3(256), 0, s, a, rows_per, splits);
   } else {
     if (a.a_dtype != DT_F32) return hipErrorInvalidValue;
-    if (vec_ok(a.A, a.lda, 4))
-      hipLaunchKernelGGL(gemm_tn_f32_kernel<true>, grid, dim3(256), 0, s, a, rows_per);
+    dim3 g1((unsigned)((splits * ti * to + 7) / 8 * 8));
+    if (narrow)
+      hipLaunchKernelGGL(gemm_tn_f32_kernel<1>, g1, dim3(256), 0, s, a, rows_per, splits);
     else
-      hipLaunchKernelGGL(gemm_tn_f32_kernel<false>, grid, dim3(256), 0, s, a, rows_per);
+      hipLaunchKernelGGL(gemm_tn_f32_kernel<4>, g1, dim3(256), 0, s, a, rows_per, splits);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return (int)e;
   const size_t count = (size_t)a.I * a.O;
-  if (a.dbias != nullptr && compute_dtype != DT_BF16) return hipErrorInvalidValue;  // the fp32 stage sums columns separately
   const unsigned blocks1 = (unsigned)((count + 63) / 64), blocks2 = a.dbias != nullptr ? (unsigned)((a.O + 63) / 64) : 0u;
   hipLaunchKernelGGL(reduce_add_kernel, dim3(blocks1 + blocks2), dim3(256), 0, s, a.partial, splits, count, a.scale, a.dW, blocks1,
                      a.bias_partial, (size_t)a.O, a.dbias);

@@ -1109,11 +1109,6 @@ int res_backward_chunk(gnnstage *st, int k, const void *grad_out_rows, hipStream
   }
   for (int j = s.L - 1; j >= 0 && M > 0; --j) {
     const char *dY = G[gi];
-    const bool fuse_bias = cd == DT_BF16;
-    if (!fuse_bias) {
-      Timed t(st, stream, 4, j);
-      HIP_TRY(st, launch_colsum_add(dY, cd, s.ld[j + 1], (int)M, s.dims[j + 1], bias_partial, kMaxSplits, st->dbias[j], stream));
-    }
     {
       Timed t(st, stream, 4, j);
       GemmTnArgs w{};
@@ -1130,10 +1125,8 @@ int res_backward_chunk(gnnstage *st, int k, const void *grad_out_rows, hipStream
       w.dW = st->dW[j];
       w.partial = gemm_partial;
       w.max_splits = kMaxSplits;
-      if (fuse_bias) {
-        w.dbias = st->dbias[j];
-        w.bias_partial = bias_partial;
-      }
+      w.dbias = st->dbias[j];  // column sums of dY, fused into the product
+      w.bias_partial = bias_partial;
       HIP_TRY(st, launch_gemm_tn(w, cd, stream));
     }
     char *dZj = st->at<char>(st->lay.dZ[j]);
@@ -1829,9 +1822,8 @@ extern "C" int stage_forward_chunk(gnnstage_t *st, int32_t k, int32_t pos, void 
       g.out = static_cast<char *>(st->cur[j + 1]) + (size_t)row0 * s.dims[j + 1] * celt;
       g.out_dtype = cd;
       g.out_ld = s.dims[j + 1];
+      if (st->output_dropout()) g.drop = st->dropout(j, row0);
       HIP_TRY(st, launch_gemm_nt(g, cd, stream));
-      if (st->output_dropout())  // on the rows just written, in place
-        HIP_TRY(st, launch_dropout_rows(g.out, cd, M, s.dims[j + 1], s.dims[j + 1], st->dropout(j, row0), stream));
     }
   }
   return GNNSTAGE_OK;
@@ -1864,10 +1856,7 @@ int flush_deferred_wgrad(gnnstage *st, hipStream_t stream) {
     for (int j = s.L - 1; j >= 0; --j) {
       if (s.tf[j]) continue;  // transform-first layers: finish_transform_first
       const char *dY = st->at<char>(st->lay.dY[j]) + (size_t)r0 * s.ld[j + 1] * celt;
-      const bool fuse_bias = s.has_bias() && cd == DT_BF16;
       Timed t(st, stream, 4, j);
-      if (s.has_bias() && !fuse_bias)
-        HIP_TRY(st, launch_colsum_add(dY, cd, s.ld[j + 1], (int)M, s.dims[j + 1], bias_partial, kMaxSplits, st->dbias[j], stream));
       GemmTnArgs w{};
       w.wide_min_rows = st->s.tune.gemm_wide_min_rows;
       w.A = st->at<char>(st->lay.Z[j]) + (size_t)r0 * s.ld[j] * celt;
@@ -1882,7 +1871,7 @@ int flush_deferred_wgrad(gnnstage *st, hipStream_t stream) {
       w.dW = st->dW[j] + (s.sage() ? s.w_half(j) : 0);  // GraphSage: W_neigh is the lower half
       w.partial = gemm_partial;
       w.max_splits = kMaxSplits;
-      if (fuse_bias) {
+      if (s.has_bias()) {
         w.dbias = st->dbias[j];
         w.bias_partial = bias_partial;
       }
@@ -1961,10 +1950,8 @@ extern "C" int stage_backward_chunk(gnnstage_t *st, int32_t k, const void *grad_
   for (int j = s.L - 1; j >= 0; --j) {
     const char *dY = dY_rows(j);
     // bias gradient = column sums of dY: fused into the weight-gradient product where that product reads dY
-    // (aggregate-first layers of the bf16 stage), a kernel of its own otherwise; aggregate-first layers with
-    // deferred weight gradients take it with the deferred product
-    const bool fuse_bias = s.has_bias() && !s.tf[j] && cd == DT_BF16;
-    if (s.has_bias() && !fuse_bias && !(defer && !s.tf[j])) {
+    // (aggregate-first layers), a kernel of its own for transform-first layers
+    if (s.has_bias() && s.tf[j]) {
       Timed t(st, stream, 4, j);
       HIP_TRY(st, launch_colsum_add(dY, cd, s.ld[j + 1], (int)M, s.dims[j + 1], bias_partial, kMaxSplits, st->dbias[j], stream));
     }
@@ -2068,7 +2055,7 @@ extern "C" int stage_backward_chunk(gnnstage_t *st, int32_t k, const void *grad_
       w.dW = st->dW[j] + (s.sage() ? s.w_half(j) : 0);  // GraphSage: W_neigh is the lower half
       w.partial = gemm_partial;
       w.max_splits = kMaxSplits;
-      if (fuse_bias) {
+      if (s.has_bias()) {
         w.dbias = st->dbias[j];
         w.bias_partial = bias_partial;
       }

@@ -553,13 +553,9 @@ extern "C" int gnntrain_epoch(gnntrain_t *tr, int64_t epoch, float *loss, void *
       w.dW = tr->head_dW;
       w.partial = tr->at<float>(lay.gemm_partial);
       w.max_splits = kMaxSplits;
-      if (cd == DT_BF16) {  // the bias gradient (column sums of the logit gradients) rides along
-        w.dbias = tr->head_db;
-        w.bias_partial = tr->at<float>(lay.bias_partial);
-      }
+      w.dbias = tr->head_db;  // the bias gradient (column sums of the logit gradients) rides along
+      w.bias_partial = tr->at<float>(lay.bias_partial);
       TRAIN_HIP(tr, launch_gemm_tn(w, cd, stream));
-      if (cd != DT_BF16)
-        TRAIN_HIP(tr, launch_colsum_add(dl, cd, x.Cp, (int)M, x.C, tr->at<float>(lay.bias_partial), kMaxSplits, tr->head_db, stream));
       GemmNtArgs g{};
       g.A = dl;
       g.a_dtype = cd;

@@ -24,3 +24,17 @@ def test_vector_alu_aggregation_at_tile_edges(dtype, widths):
     p = make_problem(w, chunk_ptr=graphs.ragged_chunks(1201, 4, 3), bias_std=0.05, first_stage=False)
     assert np.diff(p.row_ptr).max() > 3 * 32
     _parity(p, TOL_F32 if dtype == "f32" else TOL_BF16)
+
+
+@pytest.mark.parametrize("dims,n,k,variant,drop", [
+    ((1, 2, 3, 5), 301, 3, "gcn", 0.0), ((3, 4, 1), 130, 2, "sage", 0.3), ((15, 16, 17, 33), 517, 4, "gcn", 0.5),
+    ((31, 32, 36, 65), 260, 2, "sage", 0.5), ((100, 100, 100), 700, 5, "gcnii", 0.0), ((67, 67), 411, 3, "resgcn", 0.0),
+    ((300, 130, 72), 90, 3, "gcn", 0.0),
+    ((70, 132, 260), 12001, 1, "gcn", 0.5), ((68, 68), 33001, 1, "gcnii", 0.0)])  # 64 x 64 tiles: 512 and more of them
+def test_fp32_products_at_tile_edges(dims, n, k, variant, drop):
+    """Rows, columns and reduction lengths on both sides of the 16-, 32- and 64-wide tiles, partial reduction groups,
+    operands narrower than a 16-byte vector, chunks of a few rows; every epilogue, dropout in the forward one."""
+    w = small(n=n, k=k, dims=dims, variant=variant, deg=3.0)
+    cp = None if k == 1 else graphs.ragged_chunks(n, k, 12)
+    p = make_problem(w, chunk_ptr=cp, bias_std=0.05, dropout_p=drop, dropout_seed=99, first_stage=False)
+    _parity(p, TOL_F32)

@@ -117,6 +117,7 @@ struct SpmmArgs {
   float mask_scale = 1.f;  // SPMM_MASK / SPMM_ADD_MASK: what passes the mask is scaled (1 / (1 - rate) of that dropout)
   // kernel choice (measurement and test switches, set by the stage from what it read at create)
   int32_t force_valu = 0;  // vector-ALU aggregation for bf16 rows too
+  int32_t long_pieces = 0; // rows are cut into pieces of 256 entries or more (forward aggregations of fp32 stages)
   int32_t unroll = 2;      // gather slots per wave of the matrix-core aggregation: 2, 4 or 8
 };
 

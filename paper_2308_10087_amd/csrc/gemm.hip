@@ -832,9 +832,7 @@ __global__ __launch_bounds__(512) void gemm_tn_bf16_wide_kernel(const GemmTnArgs
 
 // ------------------------------------------------------------------------------------ fp32
 // fp32 products run on the matrix cores too (v_mfma_f32_32x32x2_f32 and 16x16x4: fp32 operands, fp32 multiply-adds, the
-// same 157 TFLOP/s as the vector ALU's best, without its operand traffic).  Operands go straight from memory into
-// registers, 16 bytes per lane: the order in which a matrix instruction walks the reduction index is free as long as both
-// operands walk it alike, so four consecutive elements of a row feed four instructions.
+// same 157 TFLOP/s as the vector ALU's best, without its operand traffic).
 
 // Four consecutive output columns n .. n + 3 of row m: epilogue, dropout of the layer's output, store.  Columns from N on
 // are padding (zeros up to out_pad).
@@ -904,21 +902,23 @@ __device__ inline void epilogue_store4_f32(const GemmNtArgs &a, int m, int n, co
   *reinterpret_cast<f32x4_u *>(static_cast<float *>(a.out) + (size_t)m * a.out_ld + n) = r;
 }
 
-// C[M x N] = A[M x K] . Bt[N x Kp]^T in 32 x 32 wave tiles.
-// KS = 4: the four waves of a workgroup share ONE tile and split K between them (every fourth group of 16); their sums are
-// added in LDS.  A chunk's product is small (162 x 1000 x 1000 in a 32-chunk pass over 5 k vertices: 192 tiles for 1,024
-// SIMDs), so what bounds it is the serial chain over K, which this cuts by four: 72 -> 11.2 us for that product (half of it
-// matrix instructions on three quarters of the CUs), 13 -> 4.5 us for 1,078 x 100 x 100 (64 x 64 vector-ALU tiles through
-// LDS before).  Eight waves per tile: 11.3 us.
-// KS = 1: a wave per quadrant of a 64 x 64 tile, for products of many tiles: half the operand bytes per product through L2.
-template <int KS, int EPI>
+// C[M x N] = A[M x K] . Bt[N x Kp]^T, a wave per 16 Q x 16 Q tile, four waves (a 2 x 2 square of tiles) per workgroup.
+// Every output is ONE chain of fused multiply-adds over k = 0, 1, ..., K - 1: v_mfma_f32_16x16x4_f32 adds its four products in
+// the order of its lane groups, each with a rounding of its own, and its operands are laid out so that lane group g of step s
+// holds k = 4 s + g.  Which of an activation's elements pass ReLU hangs on the last bit of such a sum, so the order is part of
+// the result: it depends on no tile size, row count or chunk, and a vector-ALU loop over k gives the same bits.
+// Q = 1: a chunk's product is small (162 x 1000 x 1000 in a 32-chunk pass over 5 k vertices: 693 tiles of 16 x 16 for 1,024
+// SIMDs), so what bounds it is the chain over K, 250 dependent matrix instructions of 32 cycles; everything else (the loads D
+// groups ahead, the change of lanes in LDS, the operand reads one group ahead) has to run in its shadow.
+// Q = 2: for products of many tiles; half the operand bytes per product through L2.
+template <int Q, int EPI>
 __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const GemmNtArgs a) {
-  constexpr int T = KS == 4 ? 32 : 64;  // rows and columns of a workgroup's tile
-  constexpr int D = 4;                  // groups of 16 reduction elements in flight per wave
-  constexpr int PS = 36;                // padded row stride (floats) of a 32 x 32 patch
-  constexpr int LS = 20;                // row stride (floats) of a staged operand: conflict-free 16-byte reads
-  __shared__ __attribute__((aligned(16))) float lds_all[4][2 * 4 * 16 * LS];
-  static_assert(32 * PS <= 2 * 4 * 16 * LS, "the result patch reuses the staging memory");
+  constexpr int T = 32 * Q;          // rows and columns of a workgroup's tile
+  constexpr int D = Q == 1 ? 12 : 4; // groups of 16 reduction elements in flight per wave
+  constexpr int PS = 16 * Q + 4;     // padded row stride (floats) of the result patch
+  constexpr int LS = 20;             // row stride (floats) of a staged operand: conflict-free 4-byte writes and 16-byte reads
+  __shared__ __attribute__((aligned(16))) float lds_all[4][2 * Q * 16 * LS];
+  static_assert(16 * Q * PS <= 2 * Q * 16 * LS, "the result patch reuses the staging memory");
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   float *lds = lds_all[wave];
   // Workgroups go round-robin over the 8 XCDs; each takes a contiguous run of tiles that share a block of A rows (row
@@ -927,137 +927,131 @@ __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const GemmNtArgs a) {
   const int work = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
   if (work >= mt * nt) return;
   const bool cols_outside = a.M < a.N;
-  int m0 = (cols_outside ? work % mt : work / nt) * T, n0 = (cols_outside ? work / mt : work % nt) * T;
-  if constexpr (KS == 1) {
-    m0 += (wave >> 1) * 32;
-    n0 += (wave & 1) * 32;
-    if (m0 >= a.M || n0 >= a.N) return;  // the padding columns lie inside the tile that holds column N - 1
-  }
-  // A wave instruction loads 16 rows x 64 bytes, four lanes per row, and the pieces change lanes in a wave-private LDS
-  // patch, one group ahead of the products.  (Loaded in the operand layout of the matrix instruction, a row per lane,
-  // every quarter of a wave touches 16 cache lines: nothing for small products, 6 % of a step whose products are large.)
-  const int lrow = lane >> 2, lk = (lane & 3) * 4, l16 = lane & 15, kq = (lane >> 4) * 4;
-  const float *A[2], *B[2];
+  const int m0 = (cols_outside ? work % mt : work / nt) * T + (wave >> 1) * (16 * Q);
+  const int n0 = (cols_outside ? work / mt : work % nt) * T + (wave & 1) * (16 * Q);
+  if (m0 >= a.M || n0 >= a.N) return;  // no barrier below; the padding columns lie inside the tile of column N - 1
+  // A wave instruction loads 16 rows x 64 bytes, four lanes per row; a lane's four elements belong to the four lane groups
+  // of one matrix instruction, which they reach through a wave-private LDS patch, one group ahead of the products.
+  const int lrow = lane >> 2, ls = lane & 3, lk = ls * 4, l16 = lane & 15, kq = (lane >> 4) * 4;
+  const float *A[Q], *B[Q];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
+  for (int h = 0; h < Q; ++h) {
     const int ml = m0 + 16 * h + lrow, nl = n0 + 16 * h + lrow;
     A[h] = static_cast<const float *>(a.A) + (size_t)(ml < a.M ? ml : a.M - 1) * a.lda + lk;
     B[h] = static_cast<const float *>(a.Bt) + (size_t)(nl < a.N ? nl : a.N - 1) * a.ldb + lk;
   }
-  f32x4 acc[2][2];
+  f32x4 acc[Q][Q];
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+  for (int x = 0; x < Q; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 fa[D][2], fb[D][2];
-  const int g0 = KS == 4 ? wave : 0;
-  auto load = [&](int i, int u) {  // the wave's i-th group of 16 into slot u
-    const int k = (g0 + i * KS) * 16;
+    for (int y = 0; y < Q; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 fa[D][Q], fb[D][Q];  // loads in flight
+  f32x4 pa[Q], pb[Q];        // the last, partial group
+  f32x4 x4[Q], y4[Q];        // operands of the next products: element s for step s
+  const int cnt = a.K / 16;  // groups without a bounds check
+  const bool part = cnt * 16 < a.K;
+  auto load = [&](int i, int u) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      fa[u][h] = *reinterpret_cast<const f32x4_u *>(A[h] + k);
-      fb[u][h] = *reinterpret_cast<const f32x4_u *>(B[h] + k);
+    for (int h = 0; h < Q; ++h) {
+      fa[u][h] = *reinterpret_cast<const f32x4_u *>(A[h] + i * 16);
+      fb[u][h] = *reinterpret_cast<const f32x4_u *>(B[h] + i * 16);
     }
   };
-  auto stage = [&](int u) {  // slot u goes to LDS patch u & 1
-    float *p = lds + (u & 1) * (4 * 16 * LS) + lrow * LS + lk;
+  // a group goes through LDS and comes back as operands (LDS serves a wave in order: one patch is enough)
+  auto turn = [&](const f32x4(&va)[Q], const f32x4(&vb)[Q]) {
+    float *w = lds + lrow * LS + ls;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      *reinterpret_cast<f32x4 *>(p + h * 16 * LS) = fa[u][h];
-      *reinterpret_cast<f32x4 *>(p + (2 + h) * 16 * LS) = fb[u][h];
-    }
-  };
-  auto consume = [&](int u) {
-    __builtin_amdgcn_wave_barrier();
-    const float *p = lds + (u & 1) * (4 * 16 * LS) + l16 * LS + kq;
-    f32x4 x4[2], y4[2];
+    for (int h = 0; h < Q; ++h)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      x4[h] = *reinterpret_cast<const f32x4 *>(p + h * 16 * LS);
-      y4[h] = *reinterpret_cast<const f32x4 *>(p + (2 + h) * 16 * LS);
-    }
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(x4[x][t], y4[y][t], acc[x][y], 0, 0, 0);
-  };
-  const int full = a.K / 16;  // groups without a bounds check
-  const int cnt = full > g0 ? (full - g0 + KS - 1) / KS : 0;
-  // Loads past the wave's last group repeat it (exact wait counts, and half the code of a loop with a drain: a launch this
-  // short pays for every line of code it fetches).
-  if (cnt <= D) {
-#pragma unroll
-    for (int u = 0; u < D; ++u)
-      if (u < cnt) load(u, u);
-#pragma unroll
-    for (int u = 0; u < D; ++u)
-      if (u < cnt) {
-        stage(u);
-        consume(u);
+      for (int t = 0; t < 4; ++t) {
+        w[h * 16 * LS + 4 * t] = va[h][t];
+        w[(Q + h) * 16 * LS + 4 * t] = vb[h][t];
       }
-  } else {
+    __builtin_amdgcn_wave_barrier();
+    const float *p = lds + l16 * LS + kq;
 #pragma unroll
-    for (int u = 0; u < D; ++u) load(u, u);
-    stage(0);
-    int i = 0;
+    for (int h = 0; h < Q; ++h) {
+      x4[h] = *reinterpret_cast<const f32x4 *>(p + h * 16 * LS);
+      y4[h] = *reinterpret_cast<const f32x4 *>(p + (Q + h) * 16 * LS);
+    }
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto mul = [&](const f32x4(&xa)[Q], const f32x4(&yb)[Q]) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int x = 0; x < Q; ++x)
+#pragma unroll
+        for (int y = 0; y < Q; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[x][s], yb[y][s], acc[x][y], 0, 0, 0);
+  };
+  // the products of the group whose operands are held, behind the turn of the next group (which is then held)
+  auto step = [&](const f32x4(&va)[Q], const f32x4(&vb)[Q]) {
+    f32x4 xa[Q], yb[Q];
+#pragma unroll
+    for (int h = 0; h < Q; ++h) {
+      xa[h] = x4[h];
+      yb[h] = y4[h];
+    }
+    turn(va, vb);
+    mul(xa, yb);
+  };
+  if (part) {
+    const int k = cnt * 16 + lk;
+#pragma unroll
+    for (int h = 0; h < Q; ++h) {
+      pa[h] = pb[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (k + 4 <= a.K) {
+        pa[h] = *reinterpret_cast<const f32x4_u *>(A[h] + cnt * 16);
+        pb[h] = *reinterpret_cast<const f32x4_u *>(B[h] + cnt * 16);
+      } else {
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+          if (k + t < a.K) {
+            pa[h][t] = A[h][cnt * 16 + t];
+            pb[h][t] = B[h][cnt * 16 + t];
+          }
+      }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < D; ++u)
+    if (u < cnt) load(u, u);
+  int i = 0;
+  if (cnt > 0) {
+    turn(fa[0], fb[0]);
+    // loads past the last group repeat it: exact wait counts without a drain of its own
     for (; i + D < cnt; i += D) {
 #pragma unroll
       for (int u = 0; u < D; ++u) {
-        load(i + D + u < cnt ? i + D + u : cnt - 1, u);  // slot u is in LDS already
-        stage((u + 1) % D);
-        consume(u);
+        load(i + D + u < cnt ? i + D + u : cnt - 1, u);  // slot u is held already
+        step(fa[(u + 1) % D], fb[(u + 1) % D]);
       }
     }
 #pragma unroll
     for (int u = 0; u < D; ++u)
-      if (i + u < cnt) {
-        if (i + u + 1 < cnt) stage((u + 1) % D);
-        consume(u);
-      }
+      if (u + 1 < D && i + u + 1 < cnt) step(fa[(u + 1) % D], fb[(u + 1) % D]);
+    if (part) step(pa, pb);
+  } else {
+    turn(pa, pb);
   }
-  if (full * 16 < a.K && (KS == 1 || (full & 3) == wave)) {  // the last, partial group
-    const int k = full * 16;
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const bool in = k + lk + t < a.K;
-        fa[0][h][t] = in ? A[h][k + t] : 0.f;
-        fb[0][h][t] = in ? B[h][k + t] : 0.f;
-      }
-    __builtin_amdgcn_wave_barrier();
-    stage(0);
-    consume(0);
-  }
+  mul(x4, y4);
   // element e of lane l of an instruction tile is row 4 * (l / 16) + e, column l % 16
   __builtin_amdgcn_wave_barrier();
-  float *patch = lds;
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+  for (int x = 0; x < Q; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
+    for (int y = 0; y < Q; ++y)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) patch[(16 * x + kq + e) * PS + 16 * y + l16] = acc[x][y][e];
-  if constexpr (KS == 4) {
-    __syncthreads();
-    const int r = tid >> 3, c = (tid & 7) * 4;
-    f32x4 v = *reinterpret_cast<const f32x4 *>(&lds_all[0][r * PS + c]);
+      for (int e = 0; e < 4; ++e) lds[(16 * x + kq + e) * PS + 16 * y + l16] = acc[x][y][e];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  constexpr int LPR = 4 * Q;  // lanes per row of the tile
 #pragma unroll
-    for (int w = 1; w < 4; ++w) v += *reinterpret_cast<const f32x4 *>(&lds_all[w][r * PS + c]);
+  for (int ps = 0; ps < Q * Q; ++ps) {
+    const int r = ps * (64 / LPR) + lane / LPR, c = (lane % LPR) * 4;
+    const f32x4 v = *reinterpret_cast<const f32x4 *>(&lds[r * PS + c]);
     if (m0 + r < a.M) epilogue_store4_f32<EPI>(a, m0 + r, n0 + c, v);
-  } else {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int ps = 0; ps < 4; ++ps) {
-      const int r = ps * 8 + (lane >> 3), c = (lane & 7) * 4;
-      const f32x4 v = *reinterpret_cast<const f32x4 *>(&patch[r * PS + c]);
-      if (m0 + r < a.M) epilogue_store4_f32<EPI>(a, m0 + r, n0 + c, v);
-    }
   }
 }
 
@@ -1308,14 +1302,13 @@ int launch_gemm_nt(const GemmNtArgs &a_in, int compute_dtype, hipStream_t s) {
   GemmNtArgs a = a_in;
   if (compute_dtype != DT_BF16) {
     if (a.a_dtype != DT_F32) return hipErrorInvalidValue;
-    // 64 x 64 tiles from two workgroups per compute unit on (a wave then walks all of K), below that 32 x 32 tiles with K
-    // split over the waves
+    // 64 x 64 tiles per workgroup from two workgroups per compute unit on, below that 32 x 32
     const long long mt64 = (a.M + 63) / 64, nt64 = (a.N + 63) / 64;
     const bool wide = mt64 * nt64 >= 512;
     const long long tiles = wide ? mt64 * nt64 : (long long)((a.M + 31) / 32) * ((a.N + 31) / 32);
 #define NT_F32(KS) {gemm_nt_f32_kernel<KS, 0>, gemm_nt_f32_kernel<KS, 1>, gemm_nt_f32_kernel<KS, 2>, gemm_nt_f32_kernel<KS, 3>, \
                     gemm_nt_f32_kernel<KS, 4>, gemm_nt_f32_kernel<KS, 5>, gemm_nt_f32_kernel<KS, 6>}
-    static const nt_f32_fn table[2][7] = {NT_F32(4), NT_F32(1)};  // indexed by GemmEpilogue
+    static const nt_f32_fn table[2][7] = {NT_F32(1), NT_F32(2)};  // indexed by GemmEpilogue
 #undef NT_F32
     if (a.epilogue < 0 || a.epilogue > 6) return hipErrorInvalidValue;
     hipLaunchKernelGGL(table[wide][a.epilogue], dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), 0, s, a);

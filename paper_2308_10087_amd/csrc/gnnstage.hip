@@ -91,12 +91,19 @@ Tuning read_tuning() {
   return t;
 }
 
+// Forward aggregations of fp32 stages.  What ReLU passes hangs on the last bit of a pre-activation: a stage of 5 k vertices
+// of width 1000 has one or two of 20 M elements so close to zero that another order of the same sum decides otherwise, and one
+// such element moves a weight gradient by 2e-3.  So these sums keep one order whatever a launch's size suggests: whole pieces
+// of at least 256 entries, added entry by entry.  (Pieces of 32 here: 6.7 against 7.1 ms per step of that stage.)
+constexpr int kLeastPieceF32Fwd = 256;
+
 // Longest piece of a row that one wavefront handles in an aggregation over `entries` entries.  A wave
 // streams roughly 16 entries per microsecond, so the longest task bounds the tail of the launch: pieces
 // shrink with the launch (about 16k pieces' worth of work per launch), within [least, 4096].
 int split_edges_for(const Tuning &t, int64_t entries, int least) {
   if (t.split_edges >= 64) return t.split_edges;
-  int64_t s = (entries / 16384 + least - 1) / least * least;
+  const int64_t step = least == kLeastPieceF32Fwd ? 64 : least;
+  int64_t s = (entries / 16384 + step - 1) / step * step;
   if (s < least) s = least;
   if (s > 4096) s = 4096;
   return (int)s;
@@ -406,12 +413,13 @@ struct Shape {
     if (hot()) return hot_classes_setting(tune, n * widest_row_bytes());
     return xcd_classes_setting(tune, n * widest_row_bytes());
   }
-  // Shortest piece that long rows of small launches are cut into.  The vector-ALU kernel has 8 row pieces of a task in
+  // Shortest piece that long rows of small launches are cut into (backward, and bf16 stages).  The vector-ALU kernel has 8 row pieces of a task in
   // flight, the matrix-core kernel turns 128 entries at a time into gathers.  Measured with pieces of 32 / 64 / 128
   // entries on the vector-ALU kernel: 5 k vertices of width 1000, 32 chunks 23.1 / 23.5 / 24.6 ms per step; 89 k vertices of
   // width 100 16.1 / 16.6 / 18.1 ms.  64 / 128 / 256 on the matrix-core kernel: 9.45 / 9.61 / 9.59 ms (300 k vertices of
   // width 128), 13.9 / 13.3 / 13.6 ms (169 k vertices of width 256).
-  int least_piece() const {
+  int least_piece(bool transposed) const {
+    if (dtype == GNNSTAGE_F32 && !transposed) return kLeastPieceF32Fwd;
     int valu = 0;
     for (int j = 0; j < L; ++j) {
       const bool f32_rows = dtype == GNNSTAGE_F32 || (j == 0 && level0_f32 && !tf[j]);
@@ -877,6 +885,7 @@ SpmmArgs base_spmm(const gnnstage *st, bool transposed, int chunk) {
   a.vbits = st->vbits;
   a.force_valu = st->s.tune.spmm_valu ? 1 : 0;
   a.unroll = st->s.tune.spmm_unroll;
+  a.long_pieces = st->s.least_piece(transposed) == kLeastPieceF32Fwd ? 1 : 0;
   a.mask = transposed ? st->bmask : st->fmask;
   const int dir = transposed ? 1 : 0;
   if (st->dense_on[dir]) {
@@ -1217,8 +1226,8 @@ int make_host_plan(const gnnstage_desc *d, const Shape &s, bool want_edge, HostP
     return GNNSTAGE_EINVAL;
   }
   const bool dense = s.dense_ok();
-  if (!make_host_dir(s.tune, d->row_ptr, d->col_idx, s.n, s.chunk_ptr, s.classes(), s.hot(), want_edge, dense, s.dense_width(), s.least_piece(), hp.f) ||
-      !make_host_dir(s.tune, hp.t_ptr.data(), hp.t_row.data(), s.n, s.chunk_ptr, s.classes(), s.hot(), want_edge, dense, s.dense_width(), s.least_piece(), hp.b)) {
+  if (!make_host_dir(s.tune, d->row_ptr, d->col_idx, s.n, s.chunk_ptr, s.classes(), s.hot(), want_edge, dense, s.dense_width(), s.least_piece(false), hp.f) ||
+      !make_host_dir(s.tune, hp.t_ptr.data(), hp.t_row.data(), s.n, s.chunk_ptr, s.classes(), s.hot(), want_edge, dense, s.dense_width(), s.least_piece(true), hp.b)) {
     err = "cannot plan the aggregation";
     return GNNSTAGE_EINVAL;
   }

@@ -12,6 +12,8 @@
 //    broadcast through lane permutes; dropped entries are first compacted inside the wave.
 //  * spmm_ring_kernel, for bf16 rows whose width is a multiple of 8: entries become address
 //    records in a wave-private LDS ring and the weighted sum runs on the matrix cores.
+#include <type_traits>
+
 #include "common.h"
 
 namespace {
@@ -95,14 +97,16 @@ __device__ inline void zero_pad_cols(const SpmmArgs &a, int64_t row, int lane) {
 // The vector-ALU aggregation (fp32 rows; bf16 rows whose width is no multiple of 8).  A wave runs one task over one tile
 // of LPR * VEC columns; G = 64 / LPR groups of lanes each own every G-th entry, U entries of a group are in flight.
 // What bounds it is how many row pieces are outstanding: of a wave (a loop that gathers one step, adds it and goes on
-// waits for memory once per step) and of the launch (column tiles of wide rows run as waves of their own, and long rows
-// are cut into pieces of 32 entries where the launch is small).  Measured, one launch before and after: 12 k entries of
+// waits for memory once per step; a wave that works out every entry's address by itself spends 25 instructions on it) and
+// of the launch (column tiles of wide rows run as waves of their own, and long rows are cut into short pieces where the
+// launch is small and the sums are not the ones that decide which elements pass ReLU).  Measured, one launch before and after: 12 k entries of
 // 4,000-byte rows 117 -> 7.9 us, 17 k entries of 400-byte rows 20 -> 6.0 us, 111 k entries of 200-byte bf16 rows
 // 72 -> 8.1 us (2.7 TB/s gathered), 312 k entries of 512-byte fp32 rows 60 -> 24 us (6.7 TB/s).
 // A row's last vector moves back so that it ends with the row: it repeats columns of its neighbour lane, which both
 // lanes sum and store alike, and every width is read in 16-byte accesses.
 template <typename Tin, typename Tout, int VEC, int LPR, int U>
 __global__ __launch_bounds__(256) void spmm_kernel(const SpmmArgs a) {
+  typedef Tin vec_t __attribute__((ext_vector_type(VEC), aligned(4)));
   constexpr int G = 64 / LPR;
   constexpr int TILE_W = LPR * VEC;
   const int lane = threadIdx.x & 63;
@@ -123,67 +127,79 @@ __global__ __launch_bounds__(256) void spmm_kernel(const SpmmArgs a) {
   const int slot = __builtin_amdgcn_readfirstlane(a.task_slot[task]);
   const uint32_t vmask = (1u << a.vbits) - 1u;
   const bool drop_unsel = a.src_unsel == nullptr;
-  const Tin *src_sel = static_cast<const Tin *>(a.src_sel) + c;
-  const Tin *src_unsel = static_cast<const Tin *>(a.src_unsel) + c;
-  const size_t ld = (size_t)a.src_ld;
+  const char *base_sel = static_cast<const char *>(a.src_sel);
+  const char *base_unsel = drop_unsel ? base_sel : static_cast<const char *>(a.src_unsel);
+  const uint32_t row_bytes = (uint32_t)a.src_ld * (uint32_t)sizeof(Tin), col_bytes = (uint32_t)c * (uint32_t)sizeof(Tin);
 
   float acc[VEC];
 #pragma unroll
   for (int t = 0; t < VEC; ++t) acc[t] = 0.f;
 
+  // the index words and weights of the next 64 entries are in flight while the current ones are gathered
+  uint32_t pc_next = 0;
+  float w_next = 0.f;
+  auto load_meta = [&](int base) {
+    if (base + lane < ne) {
+      pc_next = a.pidx[e0 + base + lane];
+      w_next = a.val[e0 + base + lane];
+    }
+  };
+  load_meta(0);
   for (int base = 0; base < ne; base += 64) {
     int n = ne - base < 64 ? ne - base : 64;
-    uint32_t info = 0;
-    float w = 0.f;
-    bool keep = false;
-    if (lane < n) {
-      const int64_t e = e0 + base + lane;
-      const uint32_t pc = a.pidx[e];
-      const bool sel = mask_test(a.mask, pc >> a.vbits);
-      keep = sel || !drop_unsel;
-      info = (pc & vmask) | (sel ? 0x80000000u : 0u);
-      w = a.val[e];
-    }
+    // one lane works out the row address of one entry; the lanes that gather it only add their column
+    const bool sel = mask_test(a.mask, pc_next >> a.vbits);
+    const uint64_t at = reinterpret_cast<uint64_t>(sel ? base_sel : base_unsel) + (uint64_t)(pc_next & vmask) * row_bytes;
+    int at_lo = (int)(uint32_t)at, at_hi = (int)(at >> 32), w = __float_as_int(w_next);
+    const bool keep = lane < n && (sel || !drop_unsel);
+    load_meta(base + 64);
     if (drop_unsel) {  // wave-uniform: compact the kept entries to the low lanes
       const uint64_t bal = __ballot(keep);
       const int nk = __popcll(bal);
       const int rk = __popcll(bal & ((1ull << lane) - 1ull));
       const int dest = keep ? rk : nk + (lane - rk);
-      info = (uint32_t)__builtin_amdgcn_ds_permute(dest << 2, (int)info);
-      w = __int_as_float(__builtin_amdgcn_ds_permute(dest << 2, __float_as_int(w)));
+      at_lo = __builtin_amdgcn_ds_permute(dest << 2, at_lo);
+      at_hi = __builtin_amdgcn_ds_permute(dest << 2, at_hi);
+      w = __builtin_amdgcn_ds_permute(dest << 2, w);
       n = __builtin_amdgcn_readfirstlane(nk);
     }
-    for (int i = 0; i < n; i += G * U) {
-      Pack<Tin, VEC> x[U];
-      uint32_t inf[U];
-      float ww[U];
+    // entries i, i + G, ... of every group: N of them in flight; CHECK: some may lie past the end
+    auto gather = [&](auto count, auto check, int i) {
+      constexpr int N = decltype(count)::value;
+      constexpr bool CHECK = decltype(check)::value;
+      Pack<Tin, VEC> x[N];
+      float ww[N];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
+      for (int u = 0; u < N; ++u) {
         const int idx = i + u * G + grp;
-        const int from = idx < n ? idx : n - 1;  // past the end: a valid entry with weight 0
-        if constexpr (G == 1) {                  // the entry is the same for the whole wave
-          inf[u] = (uint32_t)__builtin_amdgcn_readlane((int)info, from);
-          ww[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), from));
+        uint64_t rp;
+        if constexpr (G == 1) {  // the entry is the same for the whole wave
+          rp = (uint32_t)__builtin_amdgcn_readlane(at_lo, idx & 63) | (uint64_t)(uint32_t)__builtin_amdgcn_readlane(at_hi, idx & 63) << 32;
+          ww[u] = __int_as_float(__builtin_amdgcn_readlane(w, idx & 63));
         } else {
-          inf[u] = (uint32_t)__shfl((int)info, from);
-          ww[u] = __shfl(w, from);
+          rp = (uint32_t)__shfl(at_lo, idx & 63) | (uint64_t)(uint32_t)__shfl(at_hi, idx & 63) << 32;
+          ww[u] = __int_as_float(__shfl(w, idx & 63));
         }
-        if (idx >= n) ww[u] = 0.f;
-      }
+        if (!CHECK || idx < n) {
+          const vec_t v = *(const __attribute__((address_space(1))) vec_t *)(rp + col_bytes);
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (u == 0 || i + u * G < n) {  // wave-uniform
-          x[u] = *reinterpret_cast<const Pack<Tin, VEC> *>(((inf[u] >> 31) ? src_sel : src_unsel) + (size_t)(inf[u] & 0x7fffffffu) * ld);
+          for (int t = 0; t < VEC; ++t) x[u].v[t] = v[t];
         } else {
+          ww[u] = 0.f;
 #pragma unroll
           for (int t = 0; t < VEC; ++t) x[u].v[t] = from_f32<Tin>(0.f);
         }
       }
+      __builtin_amdgcn_sched_barrier(0);  // every load is issued before the first is waited for
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+      for (int u = 0; u < N; ++u)
 #pragma unroll
         for (int t = 0; t < VEC; ++t) acc[t] = __builtin_fmaf(ww[u], to_f32(x[u].v[t]), acc[t]);
-    }
+    };
+    int i = 0;
+    for (; i + G * U <= n; i += G * U) gather(std::integral_constant<int, U>{}, std::false_type{}, i);
+    constexpr int TU = U < 8 ? U : 8;
+    for (; i < n; i += G * TU) gather(std::integral_constant<int, TU>{}, std::true_type{}, i);
   }
   // add the G groups' partial rows (same columns live LPR lanes apart)
 #pragma unroll
@@ -575,23 +591,33 @@ constexpr Shape shape_of() {
 
 // 16 bytes per lane wherever the row has that many, as few lanes per row as cover it (more rows in flight per wave), rows
 // wider than 64 lanes cut into tiles; 4 bytes per lane for the narrowest rows.
+// deep: 16 entries of a group in flight instead of 4 or 8, for launches of few waves with long pieces, where a wave has
+// only its own loads to hide latency behind.  fp32 stages, 32 chunks, deep / not: 34 k vertices of width 100 5.07 / 5.51 ms per
+// step, 89 k 11.2 / 11.8, 5 k of width 1000 7.13 / 7.34.  Short pieces lose the registers for nothing: 47 k vertices of
+// width 100 in bf16 (pieces of 32) 4.01 / 3.74 ms.
 template <typename Tin, typename Tout>
-const Shape *pick_for(int d) {
+const Shape *pick_for(int d, bool deep) {
   constexpr int V = 16 / sizeof(Tin), V1 = 4 / sizeof(Tin);
   static const Shape tab[] = {shape_of<Tin, Tout, V1, 16, 4>(), shape_of<Tin, Tout, V, 16, 4>(), shape_of<Tin, Tout, V, 32, 4>(),
                               shape_of<Tin, Tout, V, 64, 8>()};
-  if (d < V) return &tab[0];
-  return d <= 16 * V ? &tab[1] : d <= 32 * V ? &tab[2] : &tab[3];
+  if constexpr (std::is_same_v<Tin, float> && std::is_same_v<Tout, float>) {
+    static const Shape deep_tab[] = {shape_of<Tin, Tout, V1, 16, 16>(), shape_of<Tin, Tout, V, 16, 16>(), shape_of<Tin, Tout, V, 32, 16>(),
+                                     shape_of<Tin, Tout, V, 64, 16>()};
+    if (deep) return &deep_tab[d < V ? 0 : d <= 16 * V ? 1 : d <= 32 * V ? 2 : 3];
+  }
+  return &tab[d < V ? 0 : d <= 16 * V ? 1 : d <= 32 * V ? 2 : 3];
 }
+constexpr int64_t kDeepWaves = 8192;  // two rounds of the four waves per SIMD that the deep instances' registers leave
 
 }  // namespace
 
 static const Shape *pick_shape(const SpmmArgs &a, int src_dtype, int out_dtype) {
+  const bool deep = a.long_pieces && (a.n_class_blocks * (int64_t)4 + a.n_tasks - a.tail_task0) * ((a.d + 255) / 256) <= kDeepWaves;
   if (src_dtype == DT_BF16) {
     if (a.d % 2 != 0) return nullptr;  // rejected at create time
-    return out_dtype == DT_BF16 ? pick_for<bf16_t, bf16_t>(a.d) : pick_for<bf16_t, float>(a.d);
+    return out_dtype == DT_BF16 ? pick_for<bf16_t, bf16_t>(a.d, deep) : pick_for<bf16_t, float>(a.d, deep);
   }
-  return out_dtype == DT_BF16 ? pick_for<float, bf16_t>(a.d) : pick_for<float, float>(a.d);
+  return out_dtype == DT_BF16 ? pick_for<float, bf16_t>(a.d, deep) : pick_for<float, float>(a.d, deep);
 }
 
 static bool mfma_path(const SpmmArgs &a, int src_dtype) {

@@ -4,10 +4,12 @@ or dispatch rule, against the CPU oracle.  Tolerances are those of the whole sui
 rounding, a handful of storage points deep)."""
 import numpy as np
 import pytest
+import torch
 
 from synth import graphs
 from synth.configs import CONFIGS, Workload
 
+from gpu_harness import GpuRun
 from helpers import make_problem
 from test_gpu_parity import TOL_BF16, TOL_F32, _parity, small
 
@@ -38,3 +40,27 @@ def test_fp32_products_at_tile_edges(dims, n, k, variant, drop):
     cp = None if k == 1 else graphs.ragged_chunks(n, k, 12)
     p = make_problem(w, chunk_ptr=cp, bias_std=0.05, dropout_p=drop, dropout_seed=99, first_stage=False)
     _parity(p, TOL_F32)
+
+
+@pytest.mark.parametrize("widths", [(3, 5), (64, 100), (128, 130), (257, 516)])
+def test_fp32_aggregation_of_rows_longer_than_a_piece(widths, monkeypatch):
+    """Forward pieces of 256 entries (full batches of 64 entries and of 16 in flight, and their remainders) and the sum of the
+    pieces; without source classes, which would cut these rows into shorter ones."""
+    monkeypatch.setenv("GNNSTAGE_XCD_CLASSES", "1")
+    w = Workload("edges", "rmat", 1201, 91, list(widths), 4, dtype="f32", n_candidates=14_000)
+    p = make_problem(w, chunk_ptr=graphs.ragged_chunks(1201, 4, 3), bias_std=0.05, first_stage=False)
+    assert np.diff(p.row_ptr).max() > 256 + 64
+    _parity(p, TOL_F32)
+
+
+@pytest.mark.parametrize("dims", [(100, 128), (65, 300), (128, 64)])
+def test_fp32_forward_sums_do_not_depend_on_the_chunks(dims):
+    """One layer over rows that are never cut: every element is one chain of multiply-adds in a fixed order, whichever
+    tile computes it (one chunk: 64 x 64 tiles per workgroup, 33 chunks: 32 x 32), so the results are the same bits."""
+    top = []
+    for k in (1, 33):
+        p = make_problem(small(n=33001, k=k, dims=dims, deg=4.0), bias_std=0.05)
+        assert np.diff(p.row_ptr).max() < 128
+        top.append(GpuRun(p, alias_hist0=True, need_input_grad=False))
+        top[-1].forward()
+    assert torch.equal(top[0].cur[1], top[1].cur[1])

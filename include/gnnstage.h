@@ -165,6 +165,15 @@ int stage_forward_chunk(gnnstage_t *st, int32_t chunk_id, int32_t pos_in_pass, v
  */
 int stage_backward_chunk(gnnstage_t *st, int32_t chunk_id, const void *grad_out_rows, void *hip_stream);
 
+/* A whole forward / backward pass in one call: the same work and results as stage_forward_chunk for order[0], order[1], ...
+ * at positions 0, 1, ..., and as stage_backward_chunk for order[n_order - 1], ..., order[0] (order is the FORWARD order;
+ * grad_out: DEVICE, n_vertices x d_L, level dtype, all rows).  When order names every chunk once, layers of different chunks
+ * that do not depend on each other run side by side: layer j of the chunk at position p with layer j + 1 of the one at
+ * position p - 1, and so on.  Anything else (fewer chunks, a wrong order) is walked chunk by chunk, with the errors of the
+ * calls above.  Asynchronous on hip_stream. */
+int gnnstage_forward_pass(gnnstage_t *st, const int32_t *order, int32_t n_order, void *hip_stream);
+int gnnstage_backward_pass(gnnstage_t *st, const int32_t *order, int32_t n_order, const void *grad_out, void *hip_stream);
+
 /* The library takes the weight gradient of a layer in ONE product over all rows once the backward pass is complete
  * (the last stage_backward_chunk call of a pass does it), not chunk by chunk.  A caller that stops a backward pass
  * early calls this to have dW / dbias hold the contributions of the backward calls made so far; it is a no-op when

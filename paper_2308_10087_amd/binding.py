@@ -79,6 +79,10 @@ def _load():
     lib.gnnstage_create.argtypes = [C.POINTER(gnnstage_desc), C.POINTER(C.c_void_p)]
     lib.stage_forward_chunk.restype = C.c_int
     lib.stage_forward_chunk.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p]
+    lib.gnnstage_forward_pass.restype = C.c_int
+    lib.gnnstage_forward_pass.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p]
+    lib.gnnstage_backward_pass.restype = C.c_int
+    lib.gnnstage_backward_pass.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]
     lib.stage_backward_chunk.restype = C.c_int
     lib.stage_backward_chunk.argtypes = [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]
     lib.gnnstage_flush_weight_gradients.restype = C.c_int
@@ -500,13 +504,26 @@ class GnnStage:
     def rows(self, k: int) -> slice:
         return slice(int(self.chunk_ptr[k]), int(self.chunk_ptr[k + 1]))
 
+    def _names_every_chunk_once(self, order) -> bool:
+        return len(order) == self.K and sorted(order) == list(range(self.K))
+
     def forward_pass(self, order, stream=None) -> None:
+        order = [int(k) for k in order]
+        if self._names_every_chunk_once(order):
+            ks = np.asarray(order, dtype=np.int32)
+            self._check(lib.gnnstage_forward_pass(self._h, ks.ctypes.data, self.K, self._stream(stream)))
+            return
         for pos, k in enumerate(order):
-            self.stage_forward_chunk(int(k), pos, stream)
+            self.stage_forward_chunk(k, pos, stream)
 
     def backward_pass(self, order, grad_out, stream=None) -> None:
-        for k in reversed(list(order)):
-            self.stage_backward_chunk(int(k), grad_out[self.rows(int(k))], stream)
+        order = [int(k) for k in order]
+        if self._names_every_chunk_once(order) and tuple(grad_out.shape) == (int(self.chunk_ptr[-1]), int(self.dims[-1])) and grad_out.is_contiguous():
+            ks = np.asarray(order, dtype=np.int32)
+            self._check(lib.gnnstage_backward_pass(self._h, ks.ctypes.data, self.K, grad_out.data_ptr(), self._stream(stream)))
+            return
+        for k in reversed(order):
+            self.stage_backward_chunk(k, grad_out[self.rows(k)], stream)
 
 
 # ---- training loop (include/gnntrain.h) -------------------------------------------------------

@@ -12,7 +12,6 @@ struct ChunkMask {
 };
 constexpr int kMaxChunks = 256;
 constexpr int kMaxClasses = 32;  // source-id classes of the aggregation schedule (a 32-bit activity mask)
-constexpr int kMaxSegs = 12;     // class segments one XCD may serve in a launch
 
 // The word is picked with selects, not with an indexed access: a kernel that holds the mask as an argument
 // would otherwise fetch the word from memory and wait for it (and for every other load in flight).
@@ -68,13 +67,13 @@ struct SpmmArgs {
   // takes them off n_tasks; the vector-ALU kernel ignores the field and serves them like any other task.
   int64_t n_short;
   int64_t n_main_blocks;  // set by the launcher: workgroups from this index on serve the short rows
-  // XCD-aware serving order.  Tasks [0, tail_task0) are pieces grouped by source-id class (class c at
-  // cls_task0[c], cls_ntasks[c] of them).  Workgroups are dealt round-robin to the 8 XCDs; XCD x
-  // (workgroups with index % 8 == x) serves up to kMaxSegs segments, segment s being the groups of four tasks
-  // seg_g0[x][s] .. seg_g0[x][s] + seg_cnt[x][s] - 1 of class seg_cls[x][s].  Workgroups from
-  // n_class_blocks on serve the tail.
-  int32_t cls_task0[kMaxClasses], cls_ntasks[kMaxClasses];
-  int32_t seg_cls[8][kMaxSegs], seg_g0[8][kMaxSegs], seg_cnt[8][kMaxSegs];
+  // XCD-aware serving order.  Tasks [0, tail_task0) are pieces grouped by source-id class (class c: tasks cls_off[c] ..
+  // cls_off[c + 1]).  Workgroups are dealt round-robin to the 8 XCDs; the groups of four tasks of the active classes,
+  // one class after the other, are cut into eight runs, and XCD x (workgroups with index % 8 == x) serves xcd_groups[x] of
+  // them from group xcd_group0[x] of class xcd_cls[x] on.  Workgroups from n_class_blocks on serve the tail.
+  const int32_t *cls_off;
+  int32_t xcd_group0[8], xcd_groups[8];
+  uint8_t xcd_cls[8];
   int32_t n_class_blocks;
   int64_t tail_task0;
   const uint8_t *slot_class;  // class of every partial slot (255: none); pieces of inactive classes are not run
@@ -125,22 +124,39 @@ struct SpmmArgs {
 __device__ inline int64_t spmm_task_index(const SpmmArgs &a, unsigned b, int wave) {
   if (b < (unsigned)a.n_class_blocks) {
     const int x = b & 7;
-    int j = b >> 3;
-#pragma unroll
-    for (int s = 0; s < kMaxSegs; ++s) {
-      const int cnt = a.seg_cnt[x][s];
-      if (j < cnt) {
-        const int cls = a.seg_cls[x][s];
-        const int64_t t = ((int64_t)a.seg_g0[x][s] + j) * 4 + wave;
-        return t < a.cls_ntasks[cls] ? a.cls_task0[cls] + t : -1;
+    int g = (int)(b >> 3);
+    if (g >= a.xcd_groups[x]) return -1;
+    g += a.xcd_group0[x];
+    for (int q = a.xcd_cls[x]; q < kMaxClasses; ++q) {  // the runs cover exactly the active classes' groups
+      const int t0 = a.cls_off[q], nt = a.cls_off[q + 1] - t0, ng = ((a.active_classes >> q) & 1u) ? (nt + 3) >> 2 : 0;
+      if (g < ng) {
+        const int t = g * 4 + wave;
+        return t < nt ? t0 + t : -1;
       }
-      j -= cnt;
+      g -= ng;
     }
     return -1;
   }
   const int64_t t = a.tail_task0 + (int64_t)(b - a.n_class_blocks) * 4 + wave;
   return t < a.n_tasks ? t : -1;
 }
+
+// ---- several launches in one -------------------------------------------------------------------
+// The cells (chunk, layer) of a pass on one anti-diagonal do not depend on each other; their launches of the same kernel run
+// as one, operand sets side by side: sub-launch i is workgroups off[i] .. off[i + 1] - 1.
+constexpr int kBatch = 8;  // the kernel arguments stay below 4 KB
+template <typename A>
+struct Batch {
+  int32_t n;
+  uint32_t off[kBatch + 1];
+  A sub[kBatch];
+  __device__ int find(unsigned b) const {  // wave-uniform
+    int i = 0;
+    while (i + 1 < n && b >= off[i + 1]) ++i;
+    return i;
+  }
+};
+static_assert(sizeof(Batch<SpmmArgs>) <= 4096, "kernel arguments");
 
 // ---- dense blocks of an aggregation (bf16 rows of width 128 or 256) ---------------------------
 // After ordering rows and columns by degree, the blocks that hold many entries are multiplied as dense
@@ -182,8 +198,13 @@ enum DType : int { DT_F32 = 0, DT_BF16 = 1 };
 
 // src dtype -> out dtype; returns hipError_t as int.  launch_spmm runs the per-task kernel,
 // launch_spmm_reduce adds the pieces of long rows (needed whenever a.n_long > 0).
-int launch_spmm(const SpmmArgs &a, int src_dtype, int out_dtype, hipStream_t s);
-int launch_spmm_reduce(const SpmmArgs &a, int src_dtype, int out_dtype, hipStream_t s);
+// Both take n launches that do not depend on each other and merge them where they run the same kernel.
+struct SpmmLaunch {
+  SpmmArgs a;
+  int src_dtype, out_dtype;
+};
+int launch_spmm(const SpmmLaunch *l, int n, hipStream_t s);
+int launch_spmm_reduce(const SpmmLaunch *l, int n, hipStream_t s);
 
 // ---- dense transforms -------------------------------------------------------------------
 enum GemmEpilogue : int {
@@ -223,7 +244,9 @@ struct GemmNtArgs {
   LnDropout drop{};        // EPI_FWD_GCN / EPI_FWD_ADD: dropout of the layer's output (threshold 0: none)
   int32_t ws_min_rows = 65536;  // rows from which the weight-stationary kernel is used (tests force it on small inputs)
 };
-int launch_gemm_nt(const GemmNtArgs &a, int compute_dtype, hipStream_t s);
+int launch_gemm_nt(const GemmNtArgs *a, int n, int compute_dtype, hipStream_t s);  // n products that do not depend on each other
+inline int launch_gemm_nt(const GemmNtArgs &a, int compute_dtype, hipStream_t s) { return launch_gemm_nt(&a, 1, compute_dtype, s); }
+static_assert(sizeof(Batch<GemmNtArgs>) <= 4096, "kernel arguments");
 
 // dW[I x O] += scale * A[M x I]^T . B[M x O]   (reduction over the M rows of the chunk).
 // B is an internal padded buffer in the compute dtype; A as for the NT product.

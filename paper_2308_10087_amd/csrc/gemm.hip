@@ -212,7 +212,10 @@ constexpr int BM = 128, BN = 128;
 // 32 floats = one 128-byte line, read by 16 lanes as float pairs (four whole rows per wave instruction,
 // fully coalesced) instead of eight scalars per lane.
 template <typename TA, bool VEC, bool PAIR = false, int BK = 32>
-__global__ __launch_bounds__(256) void gemm_nt_bf16_kernel(const GemmNtArgs a) {
+__global__ __launch_bounds__(256) void gemm_nt_bf16_kernel(const Batch<GemmNtArgs> ba) {
+  const int bi = ba.find(blockIdx.x);
+  const GemmNtArgs &a = ba.sub[bi];
+  const unsigned block = blockIdx.x - ba.off[bi];  // inside the sub-launch, which starts at a multiple of 8
   constexpr int LDS_K = BK + 8;   // padded K stride (elements)
   constexpr int KV = BK / 8;      // 16-byte vectors per tile row
   constexpr int NV = BM * KV / 256;  // vectors per thread and operand tile
@@ -223,7 +226,7 @@ __global__ __launch_bounds__(256) void gemm_nt_bf16_kernel(const GemmNtArgs a) {
   // Workgroups go round-robin over the 8 XCDs (each with its own L2).  The column tiles that share a
   // block of A rows are given consecutive slots on ONE XCD, so A is fetched into that L2 once.
   const int nt = (a.N + BN - 1) / BN;
-  const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
+  const int xcd = block & 7, q = block >> 3;
   const int m0 = ((q / nt) * 8 + xcd) * BM, n0 = (q % nt) * BN;
   if (m0 >= a.M) return;  // padding slots of the last group of 8 row tiles
   const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
@@ -912,7 +915,10 @@ __device__ inline void epilogue_store4_f32(const GemmNtArgs &a, int m, int n, co
 // groups ahead, the change of lanes in LDS, the operand reads one group ahead) has to run in its shadow.
 // Q = 2: for products of many tiles; half the operand bytes per product through L2.
 template <int Q, int EPI>
-__global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const GemmNtArgs a) {
+__global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const Batch<GemmNtArgs> ba) {
+  const int bi = ba.find(blockIdx.x);
+  const GemmNtArgs &a = ba.sub[bi];
+  const unsigned block = blockIdx.x - ba.off[bi], blocks = ba.off[bi + 1] - ba.off[bi];  // inside the sub-launch; multiples of 8
   constexpr int T = 32 * Q;          // rows and columns of a workgroup's tile
   constexpr int D = Q == 1 ? 12 : 4; // groups of 16 reduction elements in flight per wave
   constexpr int PS = 16 * Q + 4;     // padded row stride (floats) of the result patch
@@ -924,7 +930,7 @@ __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const GemmNtArgs a) {
   // Workgroups go round-robin over the 8 XCDs; each takes a contiguous run of tiles that share a block of A rows (row
   // tiles outside) or a block of Bt rows (column tiles outside), whichever moves fewer bytes into the eight L2s.
   const int mt = (a.M + T - 1) / T, nt = (a.N + T - 1) / T;
-  const int work = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int work = (block & 7) * (blocks >> 3) + (block >> 3);
   if (work >= mt * nt) return;
   const bool cols_outside = a.M < a.N;
   const int m0 = (cols_outside ? work % mt : work / nt) * T + (wave >> 1) * (16 * Q);
@@ -1271,61 +1277,96 @@ bool vec_ok(const void *p, int ld, int mult) { return (reinterpret_cast<uintptr_
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 static bool pair_ok(const void *p, int ld) { return (reinterpret_cast<uintptr_t>(p) & 7u) == 0 && ld % 2 == 0; }
 
-static int launch_gemm_nt_bf16(const GemmNtArgs &a, hipStream_t s) {
+typedef void (*nt_fn)(const Batch<GemmNtArgs>);
+
+// the kernel of one bf16 product; nullptr: the persistent weight-stationary kernel, which runs on its own
+static nt_fn nt_bf16_fn(const GemmNtArgs &a) {
   const int mt = (a.M + BM - 1) / BM, ntiles = (a.N + BN - 1) / BN;
-  dim3 grid((unsigned)(((mt + 7) / 8) * 8 * ntiles));
   const bool vec = a.a_dtype == DT_BF16 && vec_ok(a.A, a.lda, 8) && a.lda >= a.Kp;
-  if (a.a_dtype == DT_F32 && pair_ok(a.A, a.lda))
-    hipLaunchKernelGGL((gemm_nt_bf16_kernel<float, false, true>), grid, dim3(256), 0, s, a);
-  else if (a.a_dtype == DT_F32)
-    hipLaunchKernelGGL((gemm_nt_bf16_kernel<float, false>), grid, dim3(256), 0, s, a);
-  else if (vec && vec_ok(a.Bt, a.ldb, 8) && a.Kp <= 256 && a.N <= 256 && a.M >= a.ws_min_rows) {
-    // long operands: persistent weight-stationary kernel (needs a few row tiles per workgroup to pay
-    // for loading its panel of Bt into registers)
-    if (a.N <= 128 && a.Kp <= 128) return launch_ws<2, 8>(a, s);
-    if (a.N <= 128) return launch_ws<2, 16>(a, s);
-    if (a.Kp <= 128) return launch_ws<4, 8>(a, s);
-    return launch_ws<4, 16>(a, s);
-  } else if (vec && a.Kp >= 128 && (long long)mt * ntiles <= 1024)
-    // short operands: every workgroup is resident at once, the product is its chain of K steps
-    hipLaunchKernelGGL((gemm_nt_bf16_kernel<bf16_t, true, false, 64>), grid, dim3(256), 0, s, a);
-  else if (vec)
-    hipLaunchKernelGGL((gemm_nt_bf16_kernel<bf16_t, true>), grid, dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL((gemm_nt_bf16_kernel<bf16_t, false>), grid, dim3(256), 0, s, a);
-  return (int)hipGetLastError();
+  if (a.a_dtype == DT_F32) return pair_ok(a.A, a.lda) ? gemm_nt_bf16_kernel<float, false, true> : gemm_nt_bf16_kernel<float, false>;
+  // long operands: persistent weight-stationary kernel (needs a few row tiles per workgroup to pay
+  // for loading its panel of Bt into registers)
+  if (vec && vec_ok(a.Bt, a.ldb, 8) && a.Kp <= 256 && a.N <= 256 && a.M >= a.ws_min_rows) return nullptr;
+  // short operands: every workgroup is resident at once, the product is its chain of K steps
+  if (vec && a.Kp >= 128 && (long long)mt * ntiles <= 1024) return gemm_nt_bf16_kernel<bf16_t, true, false, 64>;
+  return vec ? gemm_nt_bf16_kernel<bf16_t, true> : gemm_nt_bf16_kernel<bf16_t, false>;
 }
 
-typedef void (*nt_f32_fn)(const GemmNtArgs);
-int launch_gemm_nt(const GemmNtArgs &a_in, int compute_dtype, hipStream_t s) {
-  if (a_in.M <= 0 || a_in.N <= 0) return hipSuccess;
-  GemmNtArgs a = a_in;
-  if (compute_dtype != DT_BF16) {
-    if (a.a_dtype != DT_F32) return hipErrorInvalidValue;
-    // 64 x 64 tiles per workgroup from two workgroups per compute unit on, below that 32 x 32
-    const long long mt64 = (a.M + 63) / 64, nt64 = (a.N + 63) / 64;
-    const bool wide = mt64 * nt64 >= 512;
-    const long long tiles = wide ? mt64 * nt64 : (long long)((a.M + 31) / 32) * ((a.N + 31) / 32);
-#define NT_F32(KS) {gemm_nt_f32_kernel<KS, 0>, gemm_nt_f32_kernel<KS, 1>, gemm_nt_f32_kernel<KS, 2>, gemm_nt_f32_kernel<KS, 3>, \
-                    gemm_nt_f32_kernel<KS, 4>, gemm_nt_f32_kernel<KS, 5>, gemm_nt_f32_kernel<KS, 6>}
-    static const nt_f32_fn table[2][7] = {NT_F32(1), NT_F32(2)};  // indexed by GemmEpilogue
+static int launch_ws_any(const GemmNtArgs &a, hipStream_t s) {
+  if (a.N <= 128 && a.Kp <= 128) return launch_ws<2, 8>(a, s);
+  if (a.N <= 128) return launch_ws<2, 16>(a, s);
+  if (a.Kp <= 128) return launch_ws<4, 8>(a, s);
+  return launch_ws<4, 16>(a, s);
+}
+
+int launch_gemm_nt(const GemmNtArgs *a_in, int n, int compute_dtype, hipStream_t s) {
+  if (n > kBatch) return hipErrorInvalidValue;
+  GemmNtArgs args[kBatch];
+  nt_fn fn[kBatch];
+  unsigned gx[kBatch];
+  long long tiles64 = 0;  // fp32: 64 x 64 tiles of all products
+  for (int i = 0; i < n; ++i)
+    if (a_in[i].M > 0 && a_in[i].N > 0) tiles64 += (long long)((a_in[i].M + 63) / 64) * ((a_in[i].N + 63) / 64);
+  for (int i = 0; i < n; ++i) {
+    GemmNtArgs &a = args[i] = a_in[i];
+    fn[i] = nullptr;
+    gx[i] = 0;
+    if (a.M <= 0 || a.N <= 0) continue;
+    if (compute_dtype != DT_BF16) {
+      if (a.a_dtype != DT_F32) return hipErrorInvalidValue;
+      // 64 x 64 tiles per workgroup from two workgroups per compute unit on, below that 32 x 32
+      const bool wide = tiles64 >= 512;
+      const int T = wide ? 64 : 32;
+#define NT_F32(Q) {gemm_nt_f32_kernel<Q, 0>, gemm_nt_f32_kernel<Q, 1>, gemm_nt_f32_kernel<Q, 2>, gemm_nt_f32_kernel<Q, 3>, \
+                   gemm_nt_f32_kernel<Q, 4>, gemm_nt_f32_kernel<Q, 5>, gemm_nt_f32_kernel<Q, 6>}
+      static const nt_fn table[2][7] = {NT_F32(1), NT_F32(2)};  // indexed by GemmEpilogue
 #undef NT_F32
-    if (a.epilogue < 0 || a.epilogue > 6) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(table[wide][a.epilogue], dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), 0, s, a);
-    return (int)hipGetLastError();
+      if (a.epilogue < 0 || a.epilogue > 6) return hipErrorInvalidValue;
+      fn[i] = table[wide][a.epilogue];
+      gx[i] = (unsigned)(((long long)((a.M + T - 1) / T) * ((a.N + T - 1) / T) + 7) / 8 * 8);
+      continue;
+    }
+    const bool has_aux = a.epilogue == EPI_FWD_GCNII || a.epilogue == EPI_MASK || a.epilogue == EPI_DGRAD_GCNII ||
+                         a.epilogue == EPI_FWD_ADD || a.epilogue == EPI_RES;
+    a.vec_epi = a.N % 8 == 0 && a.out_ld % 8 == 0 && aligned16(a.out) && (a.out_pad <= a.N) &&
+                (!has_aux || (a.aux_ld % 8 == 0 && aligned16(a.aux))) &&
+                ((a.epilogue != EPI_FWD_GCN && a.epilogue != EPI_FWD_ADD && a.epilogue != EPI_RES) || aligned16(a.bias)) &&
+                (a.epilogue != EPI_DGRAD_GCNII || !a.h0grad || (a.h0_ld % 4 == 0 && aligned16(a.h0grad)));
+    // drawing inside the epilogues of the bf16 kernels costs them registers they do not have (the forward products of a
+    // 233 k vertex stage went from 0.68 to 2.65 ms with dropout off): a pass of its own behind the product
+    a.drop = LnDropout{};
+    fn[i] = nt_bf16_fn(a);
+    if (fn[i] == nullptr) {
+      const int e = launch_ws_any(a, s);
+      if (e != 0) return e;
+      continue;
+    }
+    gx[i] = (unsigned)(((a.M + BM - 1) / BM + 7) / 8 * 8 * ((a.N + BN - 1) / BN));
   }
-  const bool has_aux = a.epilogue == EPI_FWD_GCNII || a.epilogue == EPI_MASK || a.epilogue == EPI_DGRAD_GCNII ||
-                       a.epilogue == EPI_FWD_ADD || a.epilogue == EPI_RES;
-  a.vec_epi = a.N % 8 == 0 && a.out_ld % 8 == 0 && aligned16(a.out) && (a.out_pad <= a.N) &&
-              (!has_aux || (a.aux_ld % 8 == 0 && aligned16(a.aux))) &&
-              ((a.epilogue != EPI_FWD_GCN && a.epilogue != EPI_FWD_ADD && a.epilogue != EPI_RES) || aligned16(a.bias)) &&
-              (a.epilogue != EPI_DGRAD_GCNII || !a.h0grad || (a.h0_ld % 4 == 0 && aligned16(a.h0grad)));
-  // drawing inside the epilogues of the bf16 kernels costs them registers they do not have (the forward products of a
-  // 233 k vertex stage went from 0.68 to 2.65 ms with dropout off): a pass of its own behind the product
-  a.drop = LnDropout{};
-  const int e = launch_gemm_nt_bf16(a, s);
-  if (e != 0 || a_in.drop.threshold == 0) return e;
-  return launch_dropout_rows(a.out, a.out_dtype, a.M, a.N, a.out_ld, a_in.drop, s);
+  bool done[kBatch] = {};
+  for (int i = 0; i < n; ++i) {
+    if (done[i] || gx[i] == 0) continue;
+    Batch<GemmNtArgs> b;
+    b.n = 0;
+    b.off[0] = 0;
+    for (int j = i; j < n; ++j) {
+      if (done[j] || gx[j] == 0 || fn[j] != fn[i]) continue;
+      done[j] = true;
+      b.sub[b.n] = args[j];
+      b.off[b.n + 1] = b.off[b.n] + gx[j];
+      ++b.n;
+    }
+    hipLaunchKernelGGL(fn[i], dim3(b.off[b.n]), dim3(256), 0, s, b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
+  }
+  if (compute_dtype == DT_BF16)
+    for (int i = 0; i < n; ++i)
+      if (a_in[i].M > 0 && a_in[i].N > 0 && a_in[i].drop.threshold > 0) {
+        const int e = launch_dropout_rows(args[i].out, args[i].out_dtype, args[i].M, args[i].N, args[i].out_ld, a_in[i].drop, s);
+        if (e != 0) return e;
+      }
+  return hipSuccess;
 }
 
 int launch_gemm_tn(const GemmTnArgs &a, int compute_dtype, hipStream_t s) {

@@ -209,6 +209,7 @@ struct TaskList {
   // class sections of the task list (class c = tasks [cls_off[c], cls_off[c+1]); tail from cls_off[8])
   int n_classes = 0;                      // 0: no class sections
   int64_t cls_off[kMaxClasses + 1] = {};  // tail starts at cls_off[n_classes]
+  int32_t *d_cls_off = nullptr;           // the same on the device
   uint8_t *slot_class = nullptr;
   // entries of every class section by the chunk of the gathered vertex ([class * K + chunk]): what a launch
   // that drops unselected entries really gathers from each class
@@ -360,6 +361,7 @@ struct Layout {
   size_t f_task_row, f_task_e0, f_task_ne, f_task_slot, f_lr_row, f_lr_slot0, f_lr_n;
   size_t b_task_row, b_task_e0, b_task_ne, b_task_slot, b_lr_row, b_lr_slot0, b_lr_n;
   size_t f_slot_class, b_slot_class;
+  size_t cls_off[2];  // [chunk][kMaxClasses + 1] per direction
   size_t rem_ptr[2];  // row pointers of the remainder index per direction (dense plan active), else unused
   // dense plan per direction (0 forward, 1 transposed)
   size_t d_blk_cb[2], d_blk_e0[2], d_ent_pos[2], d_ent_w[2], d_colslot[2], d_tiles[2];
@@ -367,7 +369,9 @@ struct Layout {
   size_t d_item_rb[2], d_item_b0[2], d_item_nb[2], d_item_chunks[2];
   size_t d_lr_dense0[2], d_lr_ndense[2], d_lr_item0[2];
   size_t dense_partial, zero_row;
+  int cells;  // that run side by side
   size_t partial;
+  size_t dense_stride, partial_stride, self_stride, row_stride, ln_stride;  // elements of one cell's scratch
   std::vector<size_t> Z, dZ, Wt, Wn, Tc, Th;
   std::vector<size_t> dY;  // deferred weight gradients: dL/d(pre-activation) of every aggregate-first layer, all n rows
   std::vector<size_t> Wt_self, Wn_self;  // GraphSage: staged copies of W_self (Wt / Wn then hold W_neigh)
@@ -389,10 +393,18 @@ struct Shape {
   bool has_bias() const { return variant != GNNSTAGE_GCNII; }
   // One weight-gradient product per layer over all rows at the end of the backward pass instead of one per chunk
   // (the rows of dL/d(pre-activation) are kept for the whole pass): a per-chunk product of a few ten thousand rows
-  // runs at its launch and latency floor.  Not for ResGCN+ stages (their backward is a path of its own).
-  bool defer_wgrad() const { return tune.wgrad_defer && variant != GNNSTAGE_RESGCN; }
+  // runs at its launch and latency floor.
+  bool defer_wgrad() const { return tune.wgrad_defer; }
   bool sage() const { return variant == GNNSTAGE_SAGE; }
   bool res() const { return variant == GNNSTAGE_RESGCN; }
+  // Cells (chunk, layer) of a pass that run side by side.  One where a launch fills the chip for long anyway: an
+  // aggregation over 2 M entries takes 100 us and up, and every further cell needs scratch of its own.  One with dense blocks
+  // too: the sums of their blocks, 37 MB for a chunk of 4 M entries, are read back from a cache only right behind the kernel
+  // that wrote them (80 k vertices, 16 M entries, 4 chunks: 4.09 ms per step cell by cell, 4.23 four at a time).
+  int cells_at_once(bool dense_blocks) const {
+    if (!defer_wgrad() || dense_blocks || nnz / K >= 2000000) return 1;
+    return std::min(kBatch, std::min(K, L));
+  }
   // elements of one weight matrix: GraphSage stacks [W_self ; W_neigh]
   size_t w_half(int j) const { return (size_t)dims[j] * dims[j + 1]; }
   int elt() const { return dtype == GNNSTAGE_BF16 ? 2 : 4; }
@@ -542,7 +554,11 @@ Layout make_layout(const Shape &s, const HostDir &hf, const HostDir &hb, bool ra
     l.d_lr_item0[dir] = w.take(sizeof(int32_t) * nl);
     max_items = std::max(max_items, h.max_items);
   }
-  l.dense_partial = w.take(sizeof(float) * (size_t)max_items * kDenseRB * 256);
+  // scratch of one cell times the cells that run side by side
+  l.cells = s.cells_at_once(hf.dense() || hb.dense());
+  const size_t B = (size_t)l.cells;
+  l.dense_stride = (size_t)max_items * kDenseRB * 256;
+  l.dense_partial = w.take(sizeof(float) * l.dense_stride * B);
   l.zero_row = w.take(max_items > 0 ? 512 : 0);
   l.f_task_row = w.take(sizeof(int32_t) * f.total_tasks);
   l.f_task_e0 = w.take(sizeof(int64_t) * f.total_tasks);
@@ -560,6 +576,7 @@ Layout make_layout(const Shape &s, const HostDir &hf, const HostDir &hb, bool ra
   l.b_lr_n = w.take(sizeof(int32_t) * b.total_longs);
   l.f_slot_class = w.take((size_t)f.total_slots);
   l.b_slot_class = w.take((size_t)b.total_slots);
+  for (int dir = 0; dir < 2; ++dir) l.cls_off[dir] = w.take(sizeof(int32_t) * (size_t)s.K * (kMaxClasses + 1));
   int max_d = 0, max_ld = 0;
   size_t max_io = 0;
   for (int j = 0; j <= s.L; ++j) {
@@ -567,7 +584,11 @@ Layout make_layout(const Shape &s, const HostDir &hf, const HostDir &hb, bool ra
     max_ld = std::max(max_ld, s.ld[j]);
   }
   for (int j = 0; j < s.L; ++j) max_io = std::max(max_io, (size_t)s.dims[j] * s.dims[j + 1]);
-  l.partial = w.take(sizeof(float) * (size_t)std::max(f.max_slots, b.max_slots) * max_d);
+  l.partial_stride = (size_t)std::max(f.max_slots, b.max_slots) * max_d;
+  l.partial = w.take(sizeof(float) * l.partial_stride * B);
+  l.row_stride = (size_t)round_up((int)std::min<int64_t>(s.max_rows(), 0x7ffffff0), 8) * max_ld;  // rows of a chunk
+  l.self_stride = l.row_stride;
+  l.ln_stride = (size_t)(kLnMaxWaves / 4) * 2 * max_d;
   const size_t elt = s.elt();
   l.Z.resize(s.L);
   l.dZ.resize(s.L);
@@ -583,10 +604,11 @@ Layout make_layout(const Shape &s, const HostDir &hf, const HostDir &hb, bool ra
     l.Th[j] = w.take((size_t)s.n * s.ld[j] * elt);
     l.Z[j] = w.take((size_t)s.n * s.ld[j] * elt);
     l.dZ[j] = w.take((size_t)s.n * s.ld[j] * elt);
+    if (s.defer_wgrad()) l.dY[j] = w.take((size_t)s.n * s.ld[j + 1] * elt);
   }
   if (s.res()) {
-    l.res_dr = w.take((size_t)s.max_rows() * max_ld * elt);
-    l.ln_partial = w.take(sizeof(float) * (size_t)(kLnMaxWaves / 4) * 2 * max_d);
+    l.res_dr = w.take(l.row_stride * elt * B);
+    l.ln_partial = w.take(sizeof(float) * l.ln_stride);
   }
   for (int j = 0; j < s.L && !s.res(); ++j) {
     if (s.tf[j]) {
@@ -612,11 +634,11 @@ Layout make_layout(const Shape &s, const HostDir &hf, const HostDir &hb, bool ra
       l.Wt_self[j] = w.take((size_t)s.dims[j + 1] * s.ld[j] * elt);
       l.Wn_self[j] = w.take((size_t)s.dims[j] * s.ld[j + 1] * elt);
     }
-    l.self_fwd = w.take(sizeof(float) * (size_t)s.max_rows() * max_ld);
-    l.self_bwd = w.take((size_t)s.max_rows() * max_ld * elt);
+    l.self_fwd = w.take(sizeof(float) * l.self_stride * B);
+    l.self_bwd = w.take(l.self_stride * elt * B);
   }
-  l.G[0] = w.take((size_t)s.max_rows() * max_ld * elt);
-  l.G[1] = w.take((size_t)s.max_rows() * max_ld * elt);
+  l.G[0] = w.take(l.row_stride * elt * B);
+  l.G[1] = w.take(s.defer_wgrad() ? 0 : l.row_stride * elt);
   l.gemm_partial = w.take(sizeof(float) * kMaxSplits * max_io);
   l.bias_partial = w.take(sizeof(float) * kMaxSplits * max_d);
   l.total = w.off;
@@ -725,6 +747,7 @@ struct gnnstage {
   ChunkMask fmask{}, bmask{};
   int n_bwd = 0;
   bool cur_stale = false;  // the levels traded places and no complete pass has rewritten the current ones yet
+  int gi = 0;              // without deferred weight gradients: which of the two scratch matrices holds dY
   std::vector<char> wgrad_pending;  // per chunk: its backward call ran, its rows' weight-gradient products are still owed
   std::string err;
   Profiler prof;
@@ -784,89 +807,67 @@ void assign_xcds(const gnnstage *st, const TaskList &t, const ChunkMask &mask, b
   const int C = t.n_classes, K = st->s.K;
   a.tail_task0 = t.cls_off[C];
   a.slot_class = t.slot_class;
+  a.cls_off = t.d_cls_off;
   a.active_classes = 0;
   a.all_classes_active = 1;
   a.n_class_blocks = 0;
   int groups[kMaxClasses];
   double unit[kMaxClasses];  // cost of one group of four tasks
   double total = 0;
-  for (int x = 0; x < 8; ++x)
-    for (int sgm = 0; sgm < kMaxSegs; ++sgm) a.seg_cls[x][sgm] = a.seg_g0[x][sgm] = a.seg_cnt[x][sgm] = 0;
-  for (int q = 0; q < kMaxClasses; ++q) {
-    a.cls_task0[q] = a.cls_ntasks[q] = 0;
+  for (int x = 0; x < 8; ++x) {
+    a.xcd_group0[x] = a.xcd_groups[x] = 0;
+    a.xcd_cls[x] = 0;
+  }
+  for (int q = 0; q < C; ++q) {
+    const int64_t ntasks = t.cls_off[q + 1] - t.cls_off[q];
     groups[q] = 0;
     unit[q] = 0;
-    if (q >= C) continue;
-    a.cls_task0[q] = (int32_t)t.cls_off[q];
-    a.cls_ntasks[q] = (int32_t)(t.cls_off[q + 1] - t.cls_off[q]);
     int64_t kept = 0, all = 0;
     for (int c = 0; c < K; ++c) {
       const int64_t e = t.cls_chunk_entries[(size_t)q * K + c];
       all += e;
       if (!drop || mask_test(mask, c)) kept += e;
     }
-    const bool on = a.cls_ntasks[q] > 0 && kept > 0;
+    const bool on = ntasks > 0 && kept > 0;
     if (!on) a.all_classes_active = 0;
     if (!on) continue;
     a.active_classes |= 1u << q;
-    groups[q] = (a.cls_ntasks[q] + 3) / 4;
-    const double cost = 32.0 * a.cls_ntasks[q] + (double)kept + 0.125 * (double)(all - kept);
+    groups[q] = (int)((ntasks + 3) / 4);
+    const double cost = 32.0 * (double)ntasks + (double)kept + 0.125 * (double)(all - kept);
     unit[q] = cost / groups[q];
     total += cost;
   }
   if (total == 0) return;
   const double quota = total / 8;
-  int x = 0, nseg = 0, most = 0, load = 0;
+  int x = 0, most = 0;
   double used = 0;
-  bool fits = true;
-  for (int q = 0; q < C && fits; ++q) {
+  for (int q = 0; q < C; ++q) {
     int g = 0;
     while (g < groups[q]) {
-      if (x < 7 && (used >= quota - 0.5 * unit[q] || nseg == kMaxSegs)) {
+      if (x < 7 && used >= quota - 0.5 * unit[q]) {
         ++x;
         used = 0;
-        nseg = 0;
-        load = 0;
-      }
-      if (nseg == kMaxSegs) {  // many tiny classes left for the last XCD
-        fits = false;
-        break;
       }
       int take = groups[q] - g;
       if (x < 7) {
         const int room = (int)((quota - used) / unit[q] + 0.5);
         take = std::min(take, std::max(room, 1));
       }
-      a.seg_cls[x][nseg] = q;
-      a.seg_g0[x][nseg] = g;
-      a.seg_cnt[x][nseg] = take;
-      ++nseg;
+      if (a.xcd_groups[x] == 0) {
+        a.xcd_cls[x] = (uint8_t)q;
+        a.xcd_group0[x] = g;
+      }
+      a.xcd_groups[x] += take;
       g += take;
       used += take * unit[q];
-      load += take;
-      most = std::max(most, load);
-    }
-  }
-  if (!fits) {  // fallback that always fits: class q goes whole to XCD q % 8 (at most 4 segments each)
-    most = 0;
-    int cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0}, ld[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int xx = 0; xx < 8; ++xx)
-      for (int sgm = 0; sgm < kMaxSegs; ++sgm) a.seg_cls[xx][sgm] = a.seg_g0[xx][sgm] = a.seg_cnt[xx][sgm] = 0;
-    for (int q = 0; q < C; ++q) {
-      if (groups[q] == 0) continue;
-      const int xx = q & 7;
-      a.seg_cls[xx][cnt[xx]] = q;
-      a.seg_g0[xx][cnt[xx]] = 0;
-      a.seg_cnt[xx][cnt[xx]] = groups[q];
-      ++cnt[xx];
-      ld[xx] += groups[q];
-      most = std::max(most, ld[xx]);
+      most = std::max(most, a.xcd_groups[x]);
     }
   }
   a.n_class_blocks = 8 * most;
 }
 
-SpmmArgs base_spmm(const gnnstage *st, bool transposed, int chunk) {
+// slot: whose scratch the launch uses (cells that run side by side have one each)
+SpmmArgs base_spmm(const gnnstage *st, bool transposed, int chunk, const ChunkMask &mask, int slot) {
   SpmmArgs a{};
   const TaskList &t = transposed ? st->btasks[chunk] : st->ftasks[chunk];
   a.pidx = st->at<uint32_t>(transposed ? st->lay.prow : st->lay.pcol);
@@ -881,36 +882,49 @@ SpmmArgs base_spmm(const gnnstage *st, bool transposed, int chunk) {
   a.lr_slot0 = t.lr_slot0;
   a.lr_nslots = t.lr_nslots;
   a.n_long = t.n_long;
-  a.partial = st->at<float>(st->lay.partial);
+  a.partial = st->at<float>(st->lay.partial) + (size_t)slot * st->lay.partial_stride;
   a.vbits = st->vbits;
   a.force_valu = st->s.tune.spmm_valu ? 1 : 0;
   a.unroll = st->s.tune.spmm_unroll;
   a.long_pieces = st->s.least_piece(transposed) == kLeastPieceF32Fwd ? 1 : 0;
-  a.mask = transposed ? st->bmask : st->fmask;
+  a.mask = mask;
   const int dir = transposed ? 1 : 0;
   if (st->dense_on[dir]) {
     a.lr_dense0 = t.lr_dense0;
     a.lr_ndense = t.lr_ndense;
     a.lr_item0 = t.lr_item0;
     a.item_chunks = st->at<ChunkMask>(st->lay.d_item_chunks[dir]) + t.item0;
-    a.dense_partial = st->at<float>(st->lay.dense_partial);
+    a.dense_partial = st->at<float>(st->lay.dense_partial) + (size_t)slot * st->lay.dense_stride;
   }
   assign_xcds(st, t, a.mask, transposed, a);  // every transposed launch drops unselected entries
   return a;
 }
 
-// aggregation kernel and (when the chunk has long rows) the reduce of their pieces, timed apart
-// (with dense blocks: their kernel first, timed together with the sparse kernel)
-int run_spmm(gnnstage *st, const SpmmArgs &a_in, bool transposed, int chunk, int src_dtype, int out_dtype,
-             hipStream_t stream, int kind, int layer) {
-  SpmmArgs a = a_in;
-  a.drop_unselected = a.src_unsel == nullptr ? 1 : 0;
-  const int dir = transposed ? 1 : 0;
-  const TaskList &t = transposed ? st->btasks[chunk] : st->ftasks[chunk];
+// One aggregation of a cell.
+struct CellSpmm {
+  SpmmLaunch l;
+  bool transposed;
+  int chunk;
+};
+
+// n <= kBatch aggregations that do not depend on each other: dense blocks first, then the sparse kernels, then (where
+// chunks have long rows) the reduce of their pieces, timed apart.
+int run_spmm(gnnstage *st, CellSpmm *cells, int n, hipStream_t stream, int kind, int layer) {
+  SpmmLaunch l[kBatch];
+  int64_t n_long = 0;
+  for (int i = 0; i < n; ++i) {
+    cells[i].l.a.drop_unselected = cells[i].l.a.src_unsel == nullptr ? 1 : 0;
+    l[i] = cells[i].l;
+    n_long += l[i].a.n_long;
+  }
   {
     Timed tm(st, stream, kind, layer);
-    if (st->dense_on[dir] && t.n_items > 0) {
-      if (src_dtype != DT_BF16 || (a.d != 128 && a.d != 256) || a.src_ld != a.d) return hipErrorInvalidValue;
+    for (int i = 0; i < n; ++i) {
+      const SpmmArgs &a = l[i].a;
+      const int dir = cells[i].transposed ? 1 : 0, chunk = cells[i].chunk;
+      const TaskList &t = dir ? st->btasks[chunk] : st->ftasks[chunk];
+      if (!st->dense_on[dir] || t.n_items <= 0) continue;
+      if (l[i].src_dtype != DT_BF16 || (a.d != 128 && a.d != 256) || a.src_ld != a.d) return hipErrorInvalidValue;
       const Layout &lay = st->lay;
       DenseArgs da{};
       da.item_rb = st->at<int32_t>(lay.d_item_rb[dir]) + t.item0;
@@ -934,18 +948,281 @@ int run_spmm(gnnstage *st, const SpmmArgs &a_in, bool transposed, int chunk, int
       da.src_ld = a.src_ld;
       da.vbits = a.vbits;
       da.mask = a.mask;
-      da.partial = st->at<float>(lay.dense_partial);
+      da.partial = const_cast<float *>(a.dense_partial);
       const int e = launch_spmm_dense(da, stream);
       if (e != 0) return e;
     }
-    const int e = launch_spmm(a, src_dtype, out_dtype, stream);
+    const int e = launch_spmm(l, n, stream);
     if (e != 0) return e;
   }
-  if (a.n_long > 0) {
+  if (n_long > 0) {
     Timed tm(st, stream, 7, layer);
-    return launch_spmm_reduce(a, src_dtype, out_dtype, stream);
+    return launch_spmm_reduce(l, n, stream);
   }
   return 0;
+}
+
+// Runs [0, n) in turns of at most the cells that have scratch of their own; f(first, count).
+template <typename F>
+int in_turns(const gnnstage *st, int n, F f) {
+  const int B = st->lay.cells;
+  for (int i = 0; i < n; i += B) {
+    const int rc = f(i, std::min(B, n - i));
+    if (rc != GNNSTAGE_OK) return rc;
+  }
+  return GNNSTAGE_OK;
+}
+
+// The unit of work of a pass: one layer of one chunk.  slot: whose scratch it uses; mask: the processed chunks as it sees
+// them (its own among them).
+struct Cell {
+  int k, j, slot;
+  ChunkMask mask;
+};
+
+int64_t cell_row0(const gnnstage *st, int k) { return st->s.chunk_ptr[(size_t)k]; }
+int64_t cell_rows(const gnnstage *st, int k) { return st->s.chunk_ptr[(size_t)k + 1] - st->s.chunk_ptr[(size_t)k]; }
+
+// C[M x N] = A . Bt^T for a chunk's rows of a level or of an internal matrix
+GemmNtArgs nt_args(const gnnstage *st, const void *A, int a_dtype, int lda, size_t Bt, int ldb, int64_t M, int N, int K) {
+  GemmNtArgs g{};
+  g.ws_min_rows = st->s.tune.gemm_ws_min_rows;
+  g.A = A;
+  g.a_dtype = a_dtype;
+  g.lda = lda;
+  g.Bt = st->at<char>(Bt);
+  g.ldb = ldb;
+  g.M = (int)M;
+  g.N = N;
+  g.K = K;
+  g.Kp = ldb;
+  g.epilogue = EPI_PLAIN;
+  return g;
+}
+void nt_out(GemmNtArgs &g, void *out, int dtype, int ld) {
+  g.out = out;
+  g.out_dtype = dtype;
+  g.out_ld = ld;
+}
+GemmTnArgs tn_args(const gnnstage *st, const void *A, int a_dtype, int lda, const void *B, int ldb, int64_t M, int I, int O, float scale, float *dW) {
+  GemmTnArgs w{};
+  w.wide_min_rows = st->s.tune.gemm_wide_min_rows;
+  w.A = A;
+  w.a_dtype = a_dtype;
+  w.lda = lda;
+  w.B = B;
+  w.ldb = ldb;
+  w.M = (int)M;
+  w.I = I;
+  w.O = O;
+  w.scale = scale;
+  w.dW = dW;
+  w.partial = st->at<float>(st->lay.gemm_partial);
+  w.max_splits = kMaxSplits;
+  return w;
+}
+const char *level_rows(const gnnstage *st, const std::vector<void *> &level, int j, int64_t row0) {
+  return static_cast<const char *>(level[(size_t)j]) + (size_t)row0 * st->s.dims[(size_t)j] * st->level_elt(j);
+}
+
+// What a pass needs before its first chunk: staged weights; ResGCN+: Rh = f(hist[j]), the activated historical rows; the
+// transformed historical rows of transform-first layers (constants of the pass).
+int begin_forward(gnnstage *st, hipStream_t stream) {
+  const Shape &s = st->s;
+  const int cd = st->cdtype();
+  st->order.clear();
+  st->fmask = ChunkMask{};
+  st->bmask = ChunkMask{};
+  st->n_bwd = 0;
+  st->wgrad_pending.assign((size_t)s.K, 0);  // what an abandoned backward pass still owed is dropped with it
+  st->dropout_p = st->next_dropout_p;
+  st->dropout_seed = st->next_dropout_seed;
+  {
+    Timed t(st, stream, 6);
+    for (int j = 0; j < s.L; ++j) {
+      // GraphSage: W[j] = [W_self ; W_neigh]; Wt / Wn take the half that multiplies the aggregation
+      const char *Wagg = static_cast<const char *>(st->W[j]) + (s.sage() ? s.w_half(j) * s.elt() : 0);
+      HIP_TRY(st, launch_stage_weights(Wagg, cd, s.dims[j], s.dims[j + 1], st->at<char>(st->lay.Wt[j]), s.ld[j],
+                                       st->at<char>(st->lay.Wn[j]), s.ld[j + 1], stream));
+      if (s.sage())
+        HIP_TRY(st, launch_stage_weights(st->W[j], cd, s.dims[j], s.dims[j + 1], st->at<char>(st->lay.Wt_self[j]), s.ld[j],
+                                         st->at<char>(st->lay.Wn_self[j]), s.ld[j + 1], stream));
+    }
+  }
+  for (int j = 0; j < s.L; ++j) {
+    if (s.res()) {
+      Timed t(st, stream, 1, j);
+      HIP_TRY(st, launch_ln_relu(st->hist[j], st->level_dtype(j), s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, s.n, s.dims[j],
+                                 st->at<char>(st->lay.Th[j]), cd, s.ld[j], st->dropout(j, 0), stream));
+    } else if (s.tf[j]) {
+      Timed t(st, stream, 1, j);
+      GemmNtArgs g = nt_args(st, st->hist[j], st->level_dtype(j), s.dims[j], st->lay.Wt[j], s.ld[j], s.n, s.dims[j + 1], s.dims[j]);
+      nt_out(g, st->at<char>(st->lay.Th[j]), cd, s.ld[j + 1]);
+      HIP_TRY(st, launch_gemm_nt(g, cd, stream));
+    }
+  }
+  return GNNSTAGE_OK;
+}
+
+// Forward work of n <= Layout::cells cells that do not depend on each other (all of chunks with rows).
+//   aggregate first:  Z = A_hat (cur | hist); cur[j + 1] = epilogue(Z W)             GraphSage: + h_v W_self
+//   transform first:  Tc = cur W; cur[j + 1] = ReLU(A_hat (Tc | Th) + b)
+//   ResGCN+:          r_u = ReLU(LayerNorm_j(h_u)) on whichever row of u is read, z_v = sum_u A_vu r_u,
+//                     h'_v = h_v + z_v W_j + b_j; Rc[C_k] = f(cur[j][C_k]) is computed with the chunk
+int forward_cells(gnnstage *st, const Cell *cells, int n, hipStream_t stream) {
+  const Shape &s = st->s;
+  const int cd = st->cdtype();
+  const size_t celt = s.elt();
+  GemmNtArgs nt[kBatch];
+  int n_nt = 0;
+  for (int i = 0; i < n; ++i) {
+    const Cell &c = cells[i];
+    const int j = c.j;
+    const int64_t row0 = cell_row0(st, c.k), M = cell_rows(st, c.k);
+    const bool shared = st->hist[j] == st->cur[j];  // the level never changes: one table of its rows serves both
+    if (s.res() && !shared) {
+      Timed t(st, stream, 1, j);
+      HIP_TRY(st, launch_ln_relu(level_rows(st, st->cur, j, row0), st->level_dtype(j), s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, M, s.dims[j],
+                                 st->at<char>(st->lay.Tc[j]) + (size_t)row0 * s.ld[j] * celt, cd, s.ld[j], st->dropout(j, row0), stream));
+    } else if (s.tf[j] && !shared) {  // the chunk's current rows
+      GemmNtArgs &g = nt[n_nt++] = nt_args(st, level_rows(st, st->cur, j, row0), st->level_dtype(j), s.dims[j], st->lay.Wt[j], s.ld[j], M, s.dims[j + 1], s.dims[j]);
+      nt_out(g, st->at<char>(st->lay.Tc[j]) + (size_t)row0 * s.ld[j + 1] * celt, cd, s.ld[j + 1]);
+    } else if (s.sage()) {  // the vertex's own row through W_self, kept in fp32 until the layer's epilogue adds it
+      GemmNtArgs &g = nt[n_nt++] = nt_args(st, level_rows(st, st->cur, j, row0), st->level_dtype(j), s.dims[j], st->lay.Wt_self[j], s.ld[j], M, s.dims[j + 1], s.dims[j]);
+      nt_out(g, st->at<float>(st->lay.self_fwd) + (size_t)c.slot * st->lay.self_stride, DT_F32, s.ld[j + 1]);
+    }
+  }
+  if (n_nt > 0) {
+    Timed t(st, stream, 1, cells[0].j);
+    HIP_TRY(st, launch_gemm_nt(nt, n_nt, cd, stream));
+  }
+  CellSpmm sp[kBatch];
+  for (int i = 0; i < n; ++i) {
+    const Cell &c = cells[i];
+    const int j = c.j;
+    const bool shared = st->hist[j] == st->cur[j];
+    sp[i] = CellSpmm{{base_spmm(st, false, c.k, c.mask, c.slot), cd, cd}, false, c.k};
+    SpmmArgs &a = sp[i].l.a;
+    a.out_row0 = 0;
+    a.epilogue = SPMM_PLAIN;
+    if (s.tf[j] || s.res()) {
+      a.src_unsel = st->at<char>(st->lay.Th[j]);
+      a.src_sel = shared ? a.src_unsel : st->at<char>(st->lay.Tc[j]);
+      a.d = s.tf[j] ? s.dims[j + 1] : s.dims[j];
+      a.src_ld = s.tf[j] ? s.ld[j + 1] : s.ld[j];
+    } else {
+      a.src_sel = st->cur[j];
+      a.src_unsel = st->hist[j];
+      a.d = s.dims[j];
+      a.src_ld = s.dims[j];
+      sp[i].l.src_dtype = st->level_dtype(j);
+    }
+    if (s.tf[j]) {
+      a.out = st->cur[j + 1];
+      a.out_ld = s.dims[j + 1];
+      a.epilogue = SPMM_BIAS_RELU;
+      a.bias = static_cast<const float *>(st->bias[j]);
+    } else {
+      a.out = st->at<char>(st->lay.Z[j]);
+      a.out_ld = s.ld[j];
+    }
+    if (s.variant == GNNSTAGE_GCNII) {
+      a.epilogue = SPMM_MIX;
+      a.aux = st->h0;
+      a.aux_ld = s.dims[j];
+      a.s_acc = 1.f - st->alpha;
+      a.s_aux = st->alpha;
+    }
+  }
+  HIP_TRY(st, run_spmm(st, sp, n, stream, 0, cells[0].j));
+  n_nt = 0;
+  for (int i = 0; i < n; ++i) {
+    const Cell &c = cells[i];
+    const int j = c.j;
+    const int64_t row0 = cell_row0(st, c.k), M = cell_rows(st, c.k);
+    char *out = static_cast<char *>(st->cur[j + 1]) + (size_t)row0 * s.dims[j + 1] * celt;
+    if (s.tf[j]) {
+      if (st->output_dropout())  // on the rows just written, in place
+        HIP_TRY(st, launch_dropout_rows(out, cd, M, s.dims[j + 1], s.dims[j + 1], st->dropout(j, row0), stream));
+      continue;
+    }
+    GemmNtArgs &g = nt[n_nt++] = nt_args(st, st->at<char>(st->lay.Z[j]) + (size_t)row0 * s.ld[j] * celt, cd, s.ld[j], st->lay.Wt[j], s.ld[j], M, s.dims[j + 1], s.dims[j]);
+    if (s.variant == GNNSTAGE_GCNII) {
+      g.epilogue = EPI_FWD_GCNII;
+      g.aux = g.A;
+      g.aux_dtype = cd;
+      g.aux_ld = s.ld[j];
+      g.beta = st->beta[j];
+    } else {
+      g.epilogue = EPI_FWD_GCN;
+      g.bias = static_cast<const float *>(st->bias[j]);
+      if (s.sage()) {
+        g.epilogue = EPI_FWD_ADD;
+        g.aux = st->at<float>(st->lay.self_fwd) + (size_t)c.slot * st->lay.self_stride;
+        g.aux_dtype = DT_F32;
+        g.aux_ld = s.ld[j + 1];
+      } else if (s.res()) {
+        g.epilogue = EPI_RES;
+        g.aux = level_rows(st, st->cur, j, row0);
+        g.aux_dtype = st->level_dtype(j);
+        g.aux_ld = s.dims[j];
+      }
+    }
+    nt_out(g, out, cd, s.dims[j + 1]);
+    if (st->output_dropout()) g.drop = st->dropout(j, row0);
+  }
+  if (n_nt > 0) {
+    Timed t(st, stream, 1, cells[0].j);
+    HIP_TRY(st, launch_gemm_nt(nt, n_nt, cd, stream));
+  }
+  return GNNSTAGE_OK;
+}
+
+// dW_j += scale * Z_j^T dY (and the bias gradient) over rows [r0, r0 + M) of an aggregate-first layer
+int wgrad_rows(gnnstage *st, int j, int64_t r0, int64_t M, const char *dY, hipStream_t stream) {
+  const Shape &s = st->s;
+  const int cd = st->cdtype();
+  Timed t(st, stream, 4, j);
+  GemmTnArgs w = tn_args(st, st->at<char>(st->lay.Z[j]) + (size_t)r0 * s.ld[j] * s.elt(), cd, s.ld[j], dY, s.ld[j + 1], M, s.dims[j], s.dims[j + 1],
+                         s.variant == GNNSTAGE_GCNII ? st->beta[j] : 1.f,
+                         st->dW[j] + (s.sage() ? s.w_half(j) : 0));  // GraphSage: W_neigh is the lower half
+  if (s.has_bias()) {
+    w.dbias = st->dbias[j];
+    w.bias_partial = st->at<float>(st->lay.bias_partial);
+  }
+  HIP_TRY(st, launch_gemm_tn(w, cd, stream));
+  if (s.sage())  // dW_self += h_v^T dY over the rows' own (current) level-j values
+    HIP_TRY(st, launch_gemm_tn(tn_args(st, level_rows(st, st->cur, j, r0), st->level_dtype(j), s.dims[j], dY, s.ld[j + 1], M, s.dims[j], s.dims[j + 1], 1.f, st->dW[j]),
+                               cd, stream));
+  return GNNSTAGE_OK;
+}
+
+// Weight (and bias) gradients of the aggregate-first layers that the backward calls made so far still owe:
+// dW_j += scale * Z_j^T dY_j over the rows of every maximal run of chunks whose backward call has run.  A complete
+// pass is one run, i.e. one product per layer over all n rows.
+int flush_deferred_wgrad(gnnstage *st, hipStream_t stream) {
+  const Shape &s = st->s;
+  if (!s.defer_wgrad() || st->wgrad_pending.empty()) return GNNSTAGE_OK;
+  const size_t celt = s.elt();
+  int c = 0;
+  while (c < s.K) {
+    if (!st->wgrad_pending[(size_t)c]) {
+      ++c;
+      continue;
+    }
+    int c1 = c;
+    while (c1 < s.K && st->wgrad_pending[(size_t)c1]) st->wgrad_pending[(size_t)c1++] = 0;
+    const int64_t r0 = s.chunk_ptr[c], M = s.chunk_ptr[c1] - r0;
+    c = c1;
+    if (M <= 0) continue;
+    if (M > 0x7fffffff) return fail(st, GNNSTAGE_ENOTSUP, "more than 2^31 - 1 rows in one weight-gradient product");
+    for (int j = s.L - 1; j >= 0; --j) {
+      if (s.tf[j]) continue;  // transform-first layers: finish_transform_first
+      const int rc = wgrad_rows(st, j, r0, M, st->at<char>(st->lay.dY[j]) + (size_t)r0 * s.ld[j + 1] * celt, stream);
+      if (rc != GNNSTAGE_OK) return rc;
+    }
+  }
+  return GNNSTAGE_OK;
 }
 
 // After the last backward call of a pass: the history-side weight gradient of every transform-first
@@ -955,241 +1232,318 @@ int finish_transform_first(gnnstage *st, hipStream_t stream) {
   const int cd = st->cdtype();
   ChunkMask all{};
   for (int c = 0; c < s.K; ++c) mask_set(all, c);
-  char *dT = st->at<char>(st->lay.G[0]);
-  for (int j = 0; j < s.L; ++j) {
-    if (!s.tf[j]) continue;
-    for (int c = 0; c < s.K; ++c) {
-      const int64_t row0 = s.chunk_ptr[c], M = s.chunk_ptr[c + 1] - row0;
-      if (M == 0) continue;
-      SpmmArgs a = base_spmm(st, true, c);
-      a.mask = all;
-      assign_xcds(st, st->btasks[c], all, true, a);
-      a.src_sel = st->at<char>(st->lay.dZ[j]);
+  std::vector<Cell> cells;
+  for (int j = 0; j < s.L; ++j)
+    for (int c = 0; c < s.K && s.tf[j]; ++c)
+      if (cell_rows(st, c) > 0) cells.push_back(Cell{c, j, 0, all});
+  return in_turns(st, (int)cells.size(), [&](int first, int n) {
+    CellSpmm sp[kBatch];
+    for (int i = 0; i < n; ++i) {
+      const Cell &c = cells[(size_t)(first + i)];
+      sp[i] = CellSpmm{{base_spmm(st, true, c.k, all, i), cd, cd}, true, c.k};
+      SpmmArgs &a = sp[i].l.a;
+      a.src_sel = st->at<char>(st->lay.dZ[c.j]);
       a.src_unsel = nullptr;
-      a.d = s.dims[j + 1];
-      a.src_ld = s.ld[j + 1];
-      a.out = dT;
-      a.out_ld = s.ld[j + 1];
-      a.out_row0 = row0;
+      a.d = s.dims[c.j + 1];
+      a.src_ld = s.ld[c.j + 1];
+      a.out = st->at<char>(st->lay.G[0]) + (size_t)i * st->lay.row_stride * s.elt();
+      a.out_ld = s.ld[c.j + 1];
+      a.out_row0 = cell_row0(st, c.k);
       a.epilogue = SPMM_PLAIN;
-      HIP_TRY(st, run_spmm(st, a, true, c, cd, cd, stream, 2, j));
-      Timed t(st, stream, 4, j);
-      GemmTnArgs w{};
-      w.wide_min_rows = st->s.tune.gemm_wide_min_rows;
-      w.A = static_cast<const char *>(st->hist[j]) + (size_t)row0 * s.dims[j] * st->level_elt(j);
-      w.a_dtype = st->level_dtype(j);
-      w.lda = s.dims[j];
-      w.B = dT;
-      w.ldb = s.ld[j + 1];
-      w.M = (int)M;
-      w.I = s.dims[j];
-      w.O = s.dims[j + 1];
-      w.scale = 1.f;
-      w.dW = st->dW[j];
-      w.partial = st->at<float>(st->lay.gemm_partial);
-      w.max_splits = kMaxSplits;
-      HIP_TRY(st, launch_gemm_tn(w, cd, stream));
     }
-  }
-  return GNNSTAGE_OK;
+    HIP_TRY(st, run_spmm(st, sp, n, stream, 2, cells[(size_t)first].j));
+    for (int i = 0; i < n; ++i) {
+      const Cell &c = cells[(size_t)(first + i)];
+      Timed t(st, stream, 4, c.j);
+      HIP_TRY(st, launch_gemm_tn(tn_args(st, level_rows(st, st->hist, c.j, cell_row0(st, c.k)), st->level_dtype(c.j), s.dims[c.j], sp[i].l.a.out, s.ld[c.j + 1],
+                                         cell_rows(st, c.k), s.dims[c.j], s.dims[c.j + 1], 1.f, st->dW[c.j]), cd, stream));
+    }
+    return (int)GNNSTAGE_OK;
+  });
 }
 
-// ---- ResGCN+ (LayerNorm -> ReLU -> GCN convolution, plus the residual) ------------------------------------
-// Layer j: r_u = ReLU(LayerNorm_j(h_u)) on whichever row of u is read (current or historical),
-// z_v = sum_u A_vu r_u, h'_v = h_v + z_v W_j + b_j.  The activated rows are tables: Rh = f(hist[j]) once per
-// pass, Rc[C_k] = f(cur[j][C_k]) when the chunk is computed.
-int res_pass_start(gnnstage *st, hipStream_t stream) {
-  const Shape &s = st->s;
-  const int cd = st->cdtype();
-  for (int j = 0; j < s.L; ++j) {
-    Timed t(st, stream, 1, j);
-    HIP_TRY(st, launch_ln_relu(st->hist[j], st->level_dtype(j), s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, s.n, s.dims[j],
-                               st->at<char>(st->lay.Th[j]), cd, s.ld[j], st->dropout(j, 0), stream));
-  }
-  return GNNSTAGE_OK;
-}
-
-int res_forward_chunk(gnnstage *st, int k, hipStream_t stream) {
-  const Shape &s = st->s;
-  const int cd = st->cdtype();
-  const size_t celt = s.elt();
-  const int64_t row0 = s.chunk_ptr[k], M = s.chunk_ptr[k + 1] - row0;
-  for (int j = 0; j < s.L; ++j) {
-    const bool shared = st->hist[j] == st->cur[j];  // the level never changes: one activated table serves both
-    char *Rh = st->at<char>(st->lay.Th[j]);
-    char *Rc = shared ? Rh : st->at<char>(st->lay.Tc[j]);
-    const char *xrows = static_cast<const char *>(st->cur[j]) + (size_t)row0 * s.dims[j] * st->level_elt(j);
-    if (!shared) {
-      Timed t(st, stream, 1, j);
-      HIP_TRY(st, launch_ln_relu(xrows, st->level_dtype(j), s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, M, s.dims[j],
-                                 Rc + (size_t)row0 * s.ld[j] * celt, cd, s.ld[j], st->dropout(j, row0), stream));
-    }
-    char *Zj = st->at<char>(st->lay.Z[j]);
-    {
-      SpmmArgs a = base_spmm(st, false, k);
-      a.src_sel = Rc;
-      a.src_unsel = Rh;
-      a.d = s.dims[j];
-      a.src_ld = s.ld[j];
-      a.out = Zj;
-      a.out_ld = s.ld[j];
-      a.out_row0 = 0;
-      a.epilogue = SPMM_PLAIN;
-      HIP_TRY(st, run_spmm(st, a, false, k, cd, cd, stream, 0, j));
-    }
-    {
-      Timed t(st, stream, 1, j);
-      GemmNtArgs g{};
-      g.ws_min_rows = st->s.tune.gemm_ws_min_rows;
-      g.A = Zj + (size_t)row0 * s.ld[j] * celt;
-      g.a_dtype = cd;
-      g.lda = s.ld[j];
-      g.Bt = st->at<char>(st->lay.Wt[j]);
-      g.ldb = s.ld[j];
-      g.M = (int)M;
-      g.N = s.dims[j + 1];
-      g.K = s.dims[j];
-      g.Kp = s.ld[j];
-      g.epilogue = EPI_RES;
-      g.bias = static_cast<const float *>(st->bias[j]);
-      g.aux = xrows;
-      g.aux_dtype = st->level_dtype(j);
-      g.aux_ld = s.dims[j];
-      g.out = static_cast<char *>(st->cur[j + 1]) + (size_t)row0 * s.dims[j + 1] * celt;
-      g.out_dtype = cd;
-      g.out_ld = s.dims[j + 1];
-      HIP_TRY(st, launch_gemm_nt(g, cd, stream));
-    }
-  }
-  return GNNSTAGE_OK;
-}
-
-// After the last backward chunk: the LayerNorm of layer j was also applied to the historical rows, so its
+// ResGCN+, after the last backward chunk: the LayerNorm of layer j was also applied to the historical rows, so its
 // parameters receive gradient through every edge whose reader saw the historical row of u: the readers whose
 // chunk came before u's chunk in the forward order.
 int res_backward_finish(gnnstage *st, hipStream_t stream) {
   const Shape &s = st->s;
   const int cd = st->cdtype();
-  const size_t celt = s.elt();
-  char *dR = st->at<char>(st->lay.res_dr);
+  std::vector<Cell> cells;
   ChunkMask earlier{};  // chunks in front of the current one, grown along the forward order
   for (size_t pos = 0; pos < st->order.size(); ++pos) {
     const int c = st->order[pos];
-    const int64_t row0 = s.chunk_ptr[c], M = s.chunk_ptr[c + 1] - row0;
-    if (pos > 0 && M > 0) {
-      for (int j = 0; j < s.L; ++j) {
-        SpmmArgs a = base_spmm(st, true, c);
-        a.mask = earlier;
-        assign_xcds(st, st->btasks[c], earlier, true, a);
-        a.src_sel = st->at<char>(st->lay.dZ[j]);
-        a.src_unsel = nullptr;
-        a.d = s.dims[j];
-        a.src_ld = s.ld[j];
-        a.out = dR;
-        a.out_ld = s.ld[j];
-        a.out_row0 = row0;
-        a.epilogue = SPMM_PLAIN;
-        HIP_TRY(st, run_spmm(st, a, true, c, cd, cd, stream, 2, j));
-        Timed t(st, stream, 4, j);
-        const char *xrows = static_cast<const char *>(st->hist[j]) + (size_t)row0 * s.dims[j] * st->level_elt(j);
-        HIP_TRY(st, launch_ln_relu_backward(xrows, st->level_dtype(j), s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, dR, cd, s.ld[j],
-                                            nullptr, cd, 0, M, s.dims[j], nullptr, cd, 0, st->at<float>(st->lay.ln_partial),
-                                            st->d_ln_g[j], st->d_ln_b[j], st->dropout(j, row0), stream));
-      }
-    }
+    for (int j = 0; j < s.L && pos > 0 && cell_rows(st, c) > 0; ++j) cells.push_back(Cell{c, j, 0, earlier});
     mask_set(earlier, c);
   }
+  return in_turns(st, (int)cells.size(), [&](int first, int n) {
+    CellSpmm sp[kBatch];
+    for (int i = 0; i < n; ++i) {
+      const Cell &c = cells[(size_t)(first + i)];
+      sp[i] = CellSpmm{{base_spmm(st, true, c.k, c.mask, i), cd, cd}, true, c.k};
+      SpmmArgs &a = sp[i].l.a;
+      a.src_sel = st->at<char>(st->lay.dZ[c.j]);
+      a.src_unsel = nullptr;
+      a.d = s.dims[c.j];
+      a.src_ld = s.ld[c.j];
+      a.out = st->at<char>(st->lay.res_dr) + (size_t)i * st->lay.row_stride * s.elt();
+      a.out_ld = s.ld[c.j];
+      a.out_row0 = cell_row0(st, c.k);
+      a.epilogue = SPMM_PLAIN;
+    }
+    HIP_TRY(st, run_spmm(st, sp, n, stream, 2, cells[(size_t)first].j));
+    for (int i = 0; i < n; ++i) {
+      const Cell &c = cells[(size_t)(first + i)];
+      const int j = c.j;
+      const int64_t row0 = cell_row0(st, c.k);
+      Timed t(st, stream, 4, j);
+      HIP_TRY(st, launch_ln_relu_backward(level_rows(st, st->hist, j, row0), st->level_dtype(j), s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, sp[i].l.a.out, cd,
+                                          s.ld[j], nullptr, cd, 0, cell_rows(st, c.k), s.dims[j], nullptr, cd, 0, st->at<float>(st->lay.ln_partial),
+                                          st->d_ln_g[j], st->d_ln_b[j], st->dropout(j, row0), stream));
+    }
+    return (int)GNNSTAGE_OK;
+  });
+}
+
+// Where dY_j = dL/d(pre-activation of layer j) of a chunk's rows lives, [M x ld_{j+1}], zero in the padding
+// columns.  With deferred weight gradients: the chunk's rows of a matrix over all n rows (transform-first layers
+// keep that matrix anyway, it is what later chunks' transposed aggregations gather); otherwise one of two
+// chunk-sized scratch matrices, used alternately.
+char *full_dY(const gnnstage *st, int j) { return st->at<char>(st->s.tf[j] ? st->lay.dZ[j] : st->lay.dY[j]); }
+char *dY_rows(const gnnstage *st, int k, int j) {
+  if (!st->s.defer_wgrad()) return st->at<char>(st->lay.G[st->gi]);
+  return full_dY(st, j) + (size_t)cell_row0(st, k) * st->s.ld[(size_t)j + 1] * st->s.elt();
+}
+
+// dY of the top layer for rows [row0, row0 + M): the upstream gradient behind the activation's derivative (ResGCN+: no
+// activation after the convolution)
+int top_dY(gnnstage *st, const void *grad_rows, int64_t row0, int64_t M, char *out, hipStream_t stream) {
+  const Shape &s = st->s;
+  Timed t(st, stream, 6);
+  if (s.res())
+    HIP_TRY(st, launch_copy_rows(grad_rows, s.dims[s.L], out, s.ld[s.L], M, s.dims[s.L], st->cdtype(), stream));
+  else
+    HIP_TRY(st, launch_relu_mask(grad_rows, static_cast<const char *>(st->cur[s.L]) + (size_t)row0 * s.dims[s.L] * s.elt(), st->cdtype(), M, s.dims[s.L],
+                                 out, s.ld[s.L], st->mask_scale(), stream));
   return GNNSTAGE_OK;
 }
 
-int res_backward_chunk(gnnstage *st, int k, const void *grad_out_rows, hipStream_t stream) {
+// Backward work of n <= Layout::cells cells that do not depend on each other (all of chunks with rows).  whole_pass: the bias
+// gradients of transform-first layers are taken over all rows at the end of the pass.
+int backward_cells(gnnstage *st, const Cell *cells, int n, bool whole_pass, hipStream_t stream) {
   const Shape &s = st->s;
   const int cd = st->cdtype();
   const size_t celt = s.elt();
-  const int64_t row0 = s.chunk_ptr[k], M = s.chunk_ptr[k + 1] - row0;
-  char *G[2] = {st->at<char>(st->lay.G[0]), st->at<char>(st->lay.G[1])};
-  char *dR = st->at<char>(st->lay.res_dr);
-  float *gemm_partial = st->at<float>(st->lay.gemm_partial);
-  float *bias_partial = st->at<float>(st->lay.bias_partial);
-  int gi = 0;
-  if (M > 0) {
-    Timed t(st, stream, 6);  // no activation after the convolution: dY of the top layer is the upstream gradient
-    HIP_TRY(st, launch_copy_rows(grad_out_rows, s.dims[s.L], G[gi], s.ld[s.L], M, s.dims[s.L], cd, stream));
+  const bool defer = s.defer_wgrad();
+  auto need_prev = [&](int j) { return j > 0 || s.need_input_grad; };
+  auto shared = [&](int j) { return st->hist[j] == st->cur[j]; };
+  // ---- bias gradients of transform-first layers, weight gradients that are not deferred; input-gradient products
+  GemmNtArgs nt[kBatch], nt_self[kBatch];
+  int n_nt = 0, n_self = 0;
+  for (int i = 0; i < n; ++i) {
+    const Cell &c = cells[i];
+    const int j = c.j;
+    const int64_t row0 = cell_row0(st, c.k), M = cell_rows(st, c.k);
+    const char *dY = dY_rows(st, c.k, j);
+    if (s.tf[j]) {
+      // bias gradient = column sums of dY: fused into the weight-gradient product where that product reads dY
+      // (aggregate-first layers), a kernel of its own for transform-first layers
+      if (s.has_bias() && !whole_pass) {
+        Timed t(st, stream, 4, j);
+        HIP_TRY(st, launch_colsum_add(dY, cd, s.ld[j + 1], (int)M, s.dims[j + 1], st->at<float>(st->lay.bias_partial), kMaxSplits, st->dbias[j], stream));
+      }
+      if (!defer) {
+        Timed t(st, stream, 6);
+        HIP_TRY(st, launch_copy(dY, full_dY(st, j) + (size_t)row0 * s.ld[j + 1] * celt, (size_t)M * s.ld[j + 1] * celt, stream));
+      }
+      continue;
+    }
+    if (!defer) {
+      const int rc = wgrad_rows(st, j, row0, M, dY, stream);
+      if (rc != GNNSTAGE_OK) return rc;
+    }
+    if (!s.res() && !need_prev(j)) continue;
+    GemmNtArgs &g = nt[n_nt++] = nt_args(st, dY, cd, s.ld[j + 1], st->lay.Wn[j], s.ld[j + 1], M, s.dims[j], s.dims[j + 1]);
+    nt_out(g, st->at<char>(st->lay.dZ[j]) + (size_t)row0 * s.ld[j] * celt, cd, s.ld[j]);
+    if (s.variant == GNNSTAGE_GCNII) {
+      g.epilogue = EPI_DGRAD_GCNII;
+      g.aux = dY;
+      g.aux_dtype = cd;
+      g.aux_ld = s.ld[j + 1];
+      g.alpha = st->alpha;
+      g.beta = st->beta[j];
+      g.h0grad = st->grad_h0 ? st->grad_h0 + (size_t)row0 * s.dims[j] : nullptr;
+      g.h0_ld = s.dims[j];
+    }
+    if (s.sage()) {  // the gradient that reaches the chunk's own rows directly: dY W_self^T
+      GemmNtArgs &gs = nt_self[n_self++] = g;
+      gs.Bt = st->at<char>(st->lay.Wn_self[j]);
+      gs.out = st->at<char>(st->lay.self_bwd) + (size_t)c.slot * st->lay.self_stride * celt;
+    }
   }
-  for (int j = s.L - 1; j >= 0 && M > 0; --j) {
-    const char *dY = G[gi];
-    {
+  if (n_nt > 0) {
+    Timed t(st, stream, 3, cells[0].j);
+    HIP_TRY(st, launch_gemm_nt(nt, n_nt, cd, stream));
+    if (n_self > 0) HIP_TRY(st, launch_gemm_nt(nt_self, n_self, cd, stream));
+  }
+  // ---- transposed aggregations; Section 3.4: nothing flows back from unprocessed vertices
+  CellSpmm sp[kBatch];
+  int n_sp = 0, of[kBatch];
+  for (int i = 0; i < n; ++i) {
+    const Cell &c = cells[i];
+    const int j = c.j;
+    const int64_t row0 = cell_row0(st, c.k);
+    // transform first: see below; nothing else depends on dT_cur when the level is shared and has no gradient.
+    if (s.tf[j] ? shared(j) && !need_prev(j) : !s.res() && !need_prev(j)) continue;
+    of[n_sp] = i;
+    CellSpmm &x = sp[n_sp++] = CellSpmm{{base_spmm(st, true, c.k, c.mask, c.slot), cd, cd}, true, c.k};
+    SpmmArgs &a = x.l.a;
+    a.src_sel = s.tf[j] ? full_dY(st, j) : st->at<char>(st->lay.dZ[j]);
+    a.src_unsel = nullptr;
+    a.d = s.tf[j] ? s.dims[j + 1] : s.dims[j];
+    a.src_ld = s.tf[j] ? s.ld[j + 1] : s.ld[j];
+    a.epilogue = SPMM_PLAIN;
+    a.out_row0 = row0;
+    a.out_ld = a.src_ld;
+    if (s.tf[j]) {
+      a.out = st->at<char>(st->lay.G[defer ? 0 : st->gi ^ 1]) + (size_t)c.slot * st->lay.row_stride * celt;
+    } else if (s.res()) {
+      a.out = st->at<char>(st->lay.res_dr) + (size_t)c.slot * st->lay.row_stride * celt;
+    } else {
+      if (s.sage()) {
+        a.add = st->at<char>(st->lay.self_bwd) + (size_t)c.slot * st->lay.self_stride * celt;
+        a.add_ld = s.ld[j];
+        a.add_row0 = row0;
+      }
+      if (j > 0) {
+        if (defer) {  // straight into the chunk's rows of dY_{j-1}
+          a.out = full_dY(st, j - 1);
+          a.out_row0 = 0;
+        } else {
+          a.out = st->at<char>(st->lay.G[st->gi ^ 1]);
+        }
+        a.epilogue = s.sage() ? SPMM_ADD_MASK : SPMM_MASK;
+        a.mask_scale = st->mask_scale();
+        a.aux = st->cur[j];
+        a.aux_ld = s.dims[j];
+      } else {
+        a.out = st->grad_in;
+        a.out_ld = s.dims[0];
+        a.out_row0 = 0;
+        a.epilogue = s.sage() ? SPMM_ADD : SPMM_PLAIN;
+        x.l.out_dtype = st->level_dtype(0);
+      }
+    }
+  }
+  if (n_sp > 0) HIP_TRY(st, run_spmm(st, sp, n_sp, stream, 2, cells[of[0]].j));
+  // ---- behind them
+  n_nt = 0;
+  for (int x = 0; x < n_sp; ++x) {
+    const Cell &c = cells[of[x]];
+    const int j = c.j;
+    const int64_t row0 = cell_row0(st, c.k), M = cell_rows(st, c.k);
+    const void *dT = sp[x].l.a.out;
+    if (s.res()) {  // back through ReLU and LayerNorm of the chunk's own (current) rows, plus the residual branch
       Timed t(st, stream, 4, j);
-      GemmTnArgs w{};
-      w.wide_min_rows = st->s.tune.gemm_wide_min_rows;
-      w.A = st->at<char>(st->lay.Z[j]) + (size_t)row0 * s.ld[j] * celt;
-      w.a_dtype = cd;
-      w.lda = s.ld[j];
-      w.B = dY;
-      w.ldb = s.ld[j + 1];
-      w.M = (int)M;
-      w.I = s.dims[j];
-      w.O = s.dims[j + 1];
-      w.scale = 1.f;
-      w.dW = st->dW[j];
-      w.partial = gemm_partial;
-      w.max_splits = kMaxSplits;
-      w.dbias = st->dbias[j];  // column sums of dY, fused into the product
-      w.bias_partial = bias_partial;
-      HIP_TRY(st, launch_gemm_tn(w, cd, stream));
-    }
-    char *dZj = st->at<char>(st->lay.dZ[j]);
-    {
-      Timed t(st, stream, 3, j);
-      GemmNtArgs g{};
-      g.ws_min_rows = st->s.tune.gemm_ws_min_rows;
-      g.A = dY;
-      g.a_dtype = cd;
-      g.lda = s.ld[j + 1];
-      g.Bt = st->at<char>(st->lay.Wn[j]);
-      g.ldb = s.ld[j + 1];
-      g.M = (int)M;
-      g.N = s.dims[j];
-      g.K = s.dims[j + 1];
-      g.Kp = s.ld[j + 1];
-      g.epilogue = EPI_PLAIN;
-      g.out = dZj + (size_t)row0 * s.ld[j] * celt;
-      g.out_dtype = cd;
-      g.out_ld = s.ld[j];
-      HIP_TRY(st, launch_gemm_nt(g, cd, stream));
-    }
-    {
-      SpmmArgs a = base_spmm(st, true, k);
-      a.src_sel = dZj;
-      a.src_unsel = nullptr;  // Section 3.4: nothing flows back from unprocessed vertices
-      a.d = s.dims[j];
-      a.src_ld = s.ld[j];
-      a.out = dR;
-      a.out_ld = s.ld[j];
-      a.out_row0 = row0;
-      a.epilogue = SPMM_PLAIN;
-      HIP_TRY(st, run_spmm(st, a, true, k, cd, cd, stream, 2, j));
-    }
-    {
-      // back through ReLU and LayerNorm of the chunk's own (current) rows, plus the residual branch
-      Timed t(st, stream, 4, j);
-      const char *xrows = static_cast<const char *>(st->cur[j]) + (size_t)row0 * s.dims[j] * st->level_elt(j);
       void *out = nullptr;
       int out_ld = 0;
       if (j > 0) {
-        out = G[gi ^ 1];
+        out = defer ? dY_rows(st, c.k, j - 1) : st->at<char>(st->lay.G[st->gi ^ 1]);
         out_ld = s.ld[j];
       } else if (s.need_input_grad) {
         out = static_cast<char *>(st->grad_in) + (size_t)row0 * s.dims[0] * st->level_elt(0);
         out_ld = s.dims[0];
       }
-      HIP_TRY(st, launch_ln_relu_backward(xrows, st->level_dtype(j), s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, dR, cd, s.ld[j], dY,
-                                          cd, s.ld[j + 1], M, s.dims[j], out, st->level_dtype(j), out_ld,
+      HIP_TRY(st, launch_ln_relu_backward(level_rows(st, st->cur, j, row0), st->level_dtype(j), s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, dT, cd, s.ld[j],
+                                          dY_rows(st, c.k, j), cd, s.ld[j + 1], M, s.dims[j], out, st->level_dtype(j), out_ld,
                                           st->at<float>(st->lay.ln_partial), st->d_ln_g[j], st->d_ln_b[j], st->dropout(j, row0), stream));
+      continue;
     }
-    gi ^= 1;
+    if (!s.tf[j]) continue;
+    // Layer computed as A_hat (H W).  With T = H W:  dL/dW = cur^T dT_cur + hist^T dT_hist, where
+    // dT_cur[u] sums A_vu dY[v] over the readers v that saw u's CURRENT row (exactly the vertices
+    // already processed in this backward pass) and dT_hist over the readers that saw its history.
+    // dT_cur + dT_hist is the unmasked transposed aggregation, known only when every chunk's dY is:
+    //   dW += (cur - hist)[C_k]^T dT_cur[C_k]   here, per chunk,
+    //   dW += hist^T (A_hat^T dY)                after the last chunk (finish_transform_first).
+    if (!shared(j)) {
+      Timed t(st, stream, 4, j);
+      GemmTnArgs w = tn_args(st, level_rows(st, st->cur, j, row0), st->level_dtype(j), s.dims[j], dT, s.ld[j + 1], M, s.dims[j], s.dims[j + 1], 1.f, st->dW[j]);
+      HIP_TRY(st, launch_gemm_tn(w, cd, stream));
+      w.A = level_rows(st, st->hist, j, row0);
+      w.scale = -1.f;
+      HIP_TRY(st, launch_gemm_tn(w, cd, stream));
+    }
+    if (!need_prev(j)) continue;
+    GemmNtArgs &g = nt[n_nt++] = nt_args(st, dT, cd, s.ld[j + 1], st->lay.Wn[j], s.ld[j + 1], M, s.dims[j], s.dims[j + 1]);
+    if (j > 0) {
+      g.epilogue = EPI_MASK;
+      g.mask_scale = st->mask_scale();
+      g.aux = level_rows(st, st->cur, j, row0);
+      g.aux_dtype = cd;
+      g.aux_ld = s.dims[j];
+      nt_out(g, defer ? dY_rows(st, c.k, j - 1) : st->at<char>(st->lay.G[st->gi]), cd, s.ld[j]);  // without deferral dY_j is dead by now and its scratch is reused
+      g.out_pad = s.ld[j];
+    } else {
+      nt_out(g, static_cast<char *>(st->grad_in) + (size_t)row0 * s.dims[0] * st->level_elt(0), st->level_dtype(0), s.dims[0]);
+    }
   }
-  if (st->n_bwd == s.K) return res_backward_finish(st, stream);
+  if (n_nt > 0) {
+    Timed t(st, stream, 3, cells[0].j);
+    HIP_TRY(st, launch_gemm_nt(nt, n_nt, cd, stream));
+  }
+  if (!defer && !s.tf[cells[0].j]) st->gi ^= 1;  // one cell at a time then
+  return GNNSTAGE_OK;
+}
+
+// what the last call of a pass owes beyond its own rows: the deferred weight-gradient products, then the
+// history-side gradients
+int end_backward(gnnstage *st, hipStream_t stream) {
+  if (st->n_bwd != st->s.K) return GNNSTAGE_OK;
+  const int rc = flush_deferred_wgrad(st, stream);
+  if (rc != GNNSTAGE_OK) return rc;
+  return st->s.res() ? res_backward_finish(st, stream) : finish_transform_first(st, stream);
+}
+
+// A whole pass in anti-diagonals.  In the forward pass layer j of the chunk at position p reads level j of the chunks at
+// positions up to p, which are written by layer j - 1 at positions up to p; so the cells with p + j = t depend only on
+// those with smaller sums, and the launches of a diagonal run as one.  Backward the same with positions from the end and
+// layers from the top: layer j at position b gathers the gradient rows of layer j at positions up to b.  What a pass of K
+// chunks and L layers costs is then K + L - 1 rounds of launches of up to min(K, L) times the work instead of K * L.
+bool whole_pass_ok(const gnnstage *st, const int32_t *order, int n) {
+  if (n != st->s.K || st->lay.cells <= 1 || st->prof.kinds != 0) return false;  // (timed launches belong to one layer each)
+  // a level above 0 that is its own history: what a chunk does not select are the rows of the last pass, which a later
+  // chunk's cell of the same diagonal would be overwriting
+  for (int j = 1; j < st->s.L; ++j)
+    if (st->hist[j] == st->cur[j]) return false;
+  std::vector<char> seen((size_t)n, 0);
+  for (int i = 0; i < n; ++i) {
+    if (order[i] < 0 || order[i] >= n || seen[(size_t)order[i]]) return false;
+    seen[(size_t)order[i]] = 1;
+  }
+  return true;
+}
+
+// order[i]: the chunk at position i; layer_of(step of the cell along its chunk); run(cells, n)
+template <typename L, typename F>
+int run_diagonals(gnnstage *st, const std::vector<int32_t> &order, L layer_of, F run) {
+  const Shape &s = st->s;
+  std::vector<ChunkMask> mask((size_t)s.K);
+  ChunkMask m{};
+  for (int i = 0; i < s.K; ++i) {
+    mask_set(m, order[(size_t)i]);
+    mask[(size_t)i] = m;
+  }
+  std::vector<Cell> cells;
+  for (int t = 0; t < s.K + s.L - 1; ++t) {
+    cells.clear();
+    for (int i = std::max(0, t - (s.L - 1)); i <= std::min(s.K - 1, t); ++i)
+      if (cell_rows(st, order[(size_t)i]) > 0) cells.push_back(Cell{order[(size_t)i], layer_of(t - i), 0, mask[(size_t)i]});
+    const int rc = in_turns(st, (int)cells.size(), [&](int first, int n) {
+      for (int i = 0; i < n; ++i) cells[(size_t)(first + i)].slot = i;
+      return run(&cells[(size_t)first], n);
+    });
+    if (rc != GNNSTAGE_OK) return rc;
+  }
   return GNNSTAGE_OK;
 }
 
@@ -1425,6 +1779,12 @@ extern "C" int gnnstage_create(const gnnstage_desc *d, gnnstage_t **out) try {
       if (got < 0 || got > cap || ns > pc.slots[c]) return GNNSTAGE_EINVAL;
       tl.n_classes = classes > 1 ? classes : 0;
       for (int q = 0; q <= tl.n_classes; ++q) tl.cls_off[q] = coff[q];
+      for (int q = tl.n_classes + 1; q <= kMaxClasses; ++q) tl.cls_off[q] = tl.cls_off[tl.n_classes];
+      int32_t off32[kMaxClasses + 1];
+      for (int q = 0; q <= kMaxClasses; ++q) off32[q] = (int32_t)tl.cls_off[q];
+      if (tl.cls_off[kMaxClasses] > 0x7fffffff) return GNNSTAGE_ENOTSUP;
+      tl.d_cls_off = st->at<int32_t>(lay.cls_off[dir]) + (size_t)c * (kMaxClasses + 1);
+      if (hipMemcpy(tl.d_cls_off, off32, sizeof off32, hipMemcpyHostToDevice) != hipSuccess) return GNNSTAGE_EHIP;
       tl.cls_chunk_entries.assign((size_t)tl.n_classes * s.K, 0);
       for (int q = 0; q < tl.n_classes; ++q)
         for (int64_t t = coff[q]; t < coff[q + 1]; ++t)
@@ -1661,252 +2021,42 @@ extern "C" int stage_forward_chunk(gnnstage_t *st, int32_t k, int32_t pos, void 
   const Shape &s = st->s;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   if (k < 0 || k >= s.K) return fail(st, GNNSTAGE_ERANGE, "chunk id out of range");
-  const int cd = st->cdtype();
-  const size_t celt = s.elt();
   if (pos == 0) {  // a new pass: V_processed <- empty
-    st->order.clear();
-    st->fmask = ChunkMask{};
-    st->bmask = ChunkMask{};
-    st->n_bwd = 0;
-    st->wgrad_pending.assign((size_t)s.K, 0);  // what an abandoned backward pass still owed is dropped with it
-    st->dropout_p = st->next_dropout_p;
-    st->dropout_seed = st->next_dropout_seed;
-    {
-      Timed t(st, stream, 6);
-      for (int j = 0; j < s.L; ++j) {
-        // GraphSage: W[j] = [W_self ; W_neigh]; Wt / Wn take the half that multiplies the aggregation
-        const char *Wagg = static_cast<const char *>(st->W[j]) + (s.sage() ? s.w_half(j) * s.elt() : 0);
-        HIP_TRY(st, launch_stage_weights(Wagg, cd, s.dims[j], s.dims[j + 1], st->at<char>(st->lay.Wt[j]), s.ld[j],
-                                         st->at<char>(st->lay.Wn[j]), s.ld[j + 1], stream));
-        if (s.sage())
-          HIP_TRY(st, launch_stage_weights(st->W[j], cd, s.dims[j], s.dims[j + 1], st->at<char>(st->lay.Wt_self[j]), s.ld[j],
-                                           st->at<char>(st->lay.Wn_self[j]), s.ld[j + 1], stream));
-      }
-    }
-    if (s.res()) {
-      const int rc = res_pass_start(st, stream);
-      if (rc != GNNSTAGE_OK) return rc;
-    }
-    // transform-first layers: the historical rows are constants of the pass, transform them once
-    for (int j = 0; j < s.L; ++j) {
-      if (!s.tf[j]) continue;
-      Timed t(st, stream, 1, j);
-      GemmNtArgs g{};
-      g.ws_min_rows = st->s.tune.gemm_ws_min_rows;
-      g.A = st->hist[j];
-      g.a_dtype = st->level_dtype(j);
-      g.lda = s.dims[j];
-      g.Bt = st->at<char>(st->lay.Wt[j]);
-      g.ldb = s.ld[j];
-      g.M = (int)s.n;
-      g.N = s.dims[j + 1];
-      g.K = s.dims[j];
-      g.Kp = s.ld[j];
-      g.epilogue = EPI_PLAIN;
-      g.out = st->at<char>(st->lay.Th[j]);
-      g.out_dtype = cd;
-      g.out_ld = s.ld[j + 1];
-      HIP_TRY(st, launch_gemm_nt(g, cd, stream));
-    }
+    const int rc = begin_forward(st, stream);
+    if (rc != GNNSTAGE_OK) return rc;
   }
   if (pos != (int32_t)st->order.size()) return fail(st, GNNSTAGE_EORDER, "pos_in_pass does not continue the current pass");
   if (mask_test(st->fmask, (uint32_t)k)) return fail(st, GNNSTAGE_EORDER, "chunk already processed in this pass");
   st->order.push_back(k);
   mask_set(st->fmask, k);  // C_k joins V_processed before its layers run
   if ((int)st->order.size() == s.K) st->cur_stale = false;  // after this call every current row is of this pass
-
-  const int64_t row0 = s.chunk_ptr[k], M = s.chunk_ptr[k + 1] - row0;
-  if (M == 0) return GNNSTAGE_OK;
-  if (s.res()) return res_forward_chunk(st, k, stream);
-  for (int j = 0; j < s.L; ++j) {
-    if (s.tf[j]) {
-      // transform the chunk's current rows, then aggregate transformed rows (current or historical)
-      const bool shared = st->hist[j] == st->cur[j];  // level never changes: one transformed table serves both
-      char *Th = st->at<char>(st->lay.Th[j]);
-      char *Tc = shared ? Th : st->at<char>(st->lay.Tc[j]);
-      if (!shared) {
-        Timed t(st, stream, 1, j);
-        GemmNtArgs g{};
-        g.ws_min_rows = st->s.tune.gemm_ws_min_rows;
-        g.A = static_cast<const char *>(st->cur[j]) + (size_t)row0 * s.dims[j] * st->level_elt(j);
-        g.a_dtype = st->level_dtype(j);
-        g.lda = s.dims[j];
-        g.Bt = st->at<char>(st->lay.Wt[j]);
-        g.ldb = s.ld[j];
-        g.M = (int)M;
-        g.N = s.dims[j + 1];
-        g.K = s.dims[j];
-        g.Kp = s.ld[j];
-        g.epilogue = EPI_PLAIN;
-        g.out = Tc + (size_t)row0 * s.ld[j + 1] * celt;
-        g.out_dtype = cd;
-        g.out_ld = s.ld[j + 1];
-        HIP_TRY(st, launch_gemm_nt(g, cd, stream));
-      }
-      SpmmArgs a = base_spmm(st, false, k);
-      a.src_sel = Tc;
-      a.src_unsel = Th;
-      a.d = s.dims[j + 1];
-      a.src_ld = s.ld[j + 1];
-      a.out = st->cur[j + 1];
-      a.out_ld = s.dims[j + 1];
-      a.out_row0 = 0;
-      a.epilogue = SPMM_BIAS_RELU;
-      a.bias = static_cast<const float *>(st->bias[j]);
-      HIP_TRY(st, run_spmm(st, a, false, k, cd, cd, stream, 0, j));
-      if (st->output_dropout())  // on the rows just written, in place
-        HIP_TRY(st, launch_dropout_rows(static_cast<char *>(st->cur[j + 1]) + (size_t)row0 * s.dims[j + 1] * celt, cd, M, s.dims[j + 1],
-                                        s.dims[j + 1], st->dropout(j, row0), stream));
-      continue;
-    }
-    char *Zj = st->at<char>(st->lay.Z[j]);
-    {
-      SpmmArgs a = base_spmm(st, false, k);
-      a.src_sel = st->cur[j];
-      a.src_unsel = st->hist[j];
-      a.d = s.dims[j];
-      a.src_ld = s.dims[j];
-      a.out = Zj;
-      a.out_ld = s.ld[j];
-      a.out_row0 = 0;
-      if (s.variant == GNNSTAGE_GCNII) {
-        a.epilogue = SPMM_MIX;
-        a.aux = st->h0;
-        a.aux_ld = s.dims[j];
-        a.s_acc = 1.f - st->alpha;
-        a.s_aux = st->alpha;
-      } else {
-        a.epilogue = SPMM_PLAIN;
-      }
-      HIP_TRY(st, run_spmm(st, a, false, k, st->level_dtype(j), cd, stream, 0, j));
-    }
-    if (s.sage()) {  // the vertex's own row through W_self, kept in fp32 until the layer's epilogue adds it
-      Timed t(st, stream, 1, j);
-      GemmNtArgs g{};
-      g.ws_min_rows = st->s.tune.gemm_ws_min_rows;
-      g.A = static_cast<const char *>(st->cur[j]) + (size_t)row0 * s.dims[j] * st->level_elt(j);
-      g.a_dtype = st->level_dtype(j);
-      g.lda = s.dims[j];
-      g.Bt = st->at<char>(st->lay.Wt_self[j]);
-      g.ldb = s.ld[j];
-      g.M = (int)M;
-      g.N = s.dims[j + 1];
-      g.K = s.dims[j];
-      g.Kp = s.ld[j];
-      g.epilogue = EPI_PLAIN;
-      g.out = st->at<float>(st->lay.self_fwd);
-      g.out_dtype = DT_F32;
-      g.out_ld = s.ld[j + 1];
-      HIP_TRY(st, launch_gemm_nt(g, cd, stream));
-    }
-    {
-      Timed t(st, stream, 1, j);
-      GemmNtArgs g{};
-      g.ws_min_rows = st->s.tune.gemm_ws_min_rows;
-      g.A = Zj + (size_t)row0 * s.ld[j] * celt;
-      g.a_dtype = cd;
-      g.lda = s.ld[j];
-      g.Bt = st->at<char>(st->lay.Wt[j]);
-      g.ldb = s.ld[j];
-      g.M = (int)M;
-      g.N = s.dims[j + 1];
-      g.K = s.dims[j];
-      g.Kp = s.ld[j];
-      if (s.variant == GNNSTAGE_GCNII) {
-        g.epilogue = EPI_FWD_GCNII;
-        g.aux = g.A;
-        g.aux_dtype = cd;
-        g.aux_ld = s.ld[j];
-        g.beta = st->beta[j];
-      } else {
-        g.epilogue = EPI_FWD_GCN;
-        g.bias = static_cast<const float *>(st->bias[j]);
-        if (s.sage()) {
-          g.epilogue = EPI_FWD_ADD;
-          g.aux = st->at<float>(st->lay.self_fwd);
-          g.aux_dtype = DT_F32;
-          g.aux_ld = s.ld[j + 1];
-        }
-      }
-      g.out = static_cast<char *>(st->cur[j + 1]) + (size_t)row0 * s.dims[j + 1] * celt;
-      g.out_dtype = cd;
-      g.out_ld = s.dims[j + 1];
-      if (st->output_dropout()) g.drop = st->dropout(j, row0);
-      HIP_TRY(st, launch_gemm_nt(g, cd, stream));
-    }
+  for (int j = 0; j < s.L && cell_rows(st, k) > 0; ++j) {
+    const Cell c{k, j, 0, st->fmask};
+    const int rc = forward_cells(st, &c, 1, stream);
+    if (rc != GNNSTAGE_OK) return rc;
   }
   return GNNSTAGE_OK;
 }
 GNNSTAGE_GUARD_INT
 
-namespace {
-// Weight (and bias) gradients of the aggregate-first layers that the backward calls made so far still owe:
-// dW_j += scale * Z_j^T dY_j over the rows of every maximal run of chunks whose backward call has run.  A complete
-// pass is one run, i.e. one product per layer over all n rows.
-int flush_deferred_wgrad(gnnstage *st, hipStream_t stream) {
-  const Shape &s = st->s;
-  if (!s.defer_wgrad() || st->wgrad_pending.empty()) return GNNSTAGE_OK;
-  const int cd = st->cdtype();
-  const size_t celt = s.elt();
-  float *gemm_partial = st->at<float>(st->lay.gemm_partial);
-  float *bias_partial = st->at<float>(st->lay.bias_partial);
-  int c = 0;
-  while (c < s.K) {
-    if (!st->wgrad_pending[(size_t)c]) {
-      ++c;
-      continue;
+extern "C" int gnnstage_forward_pass(gnnstage_t *st, const int32_t *order, int32_t n_order, void *hip_stream) try {
+  if (!st || (n_order > 0 && !order)) return GNNSTAGE_EINVAL;
+  if (!whole_pass_ok(st, order, n_order)) {
+    for (int32_t p = 0; p < n_order; ++p) {
+      const int rc = stage_forward_chunk(st, order[p], p, hip_stream);
+      if (rc != GNNSTAGE_OK) return rc;
     }
-    int c1 = c;
-    while (c1 < s.K && st->wgrad_pending[(size_t)c1]) st->wgrad_pending[(size_t)c1++] = 0;
-    const int64_t r0 = s.chunk_ptr[c], M = s.chunk_ptr[c1] - r0;
-    c = c1;
-    if (M <= 0) continue;
-    if (M > 0x7fffffff) return fail(st, GNNSTAGE_ENOTSUP, "more than 2^31 - 1 rows in one weight-gradient product");
-    for (int j = s.L - 1; j >= 0; --j) {
-      if (s.tf[j]) continue;  // transform-first layers: finish_transform_first
-      const char *dY = st->at<char>(st->lay.dY[j]) + (size_t)r0 * s.ld[j + 1] * celt;
-      Timed t(st, stream, 4, j);
-      GemmTnArgs w{};
-      w.wide_min_rows = st->s.tune.gemm_wide_min_rows;
-      w.A = st->at<char>(st->lay.Z[j]) + (size_t)r0 * s.ld[j] * celt;
-      w.a_dtype = cd;
-      w.lda = s.ld[j];
-      w.B = dY;
-      w.ldb = s.ld[j + 1];
-      w.M = (int)M;
-      w.I = s.dims[j];
-      w.O = s.dims[j + 1];
-      w.scale = s.variant == GNNSTAGE_GCNII ? st->beta[j] : 1.f;
-      w.dW = st->dW[j] + (s.sage() ? s.w_half(j) : 0);  // GraphSage: W_neigh is the lower half
-      w.partial = gemm_partial;
-      w.max_splits = kMaxSplits;
-      if (s.has_bias()) {
-        w.dbias = st->dbias[j];
-        w.bias_partial = bias_partial;
-      }
-      HIP_TRY(st, launch_gemm_tn(w, cd, stream));
-      if (s.sage()) {  // dW_self += h_v^T dY over the rows' own (current) level-j values
-        GemmTnArgs ws{};
-        ws.wide_min_rows = st->s.tune.gemm_wide_min_rows;
-        ws.A = static_cast<const char *>(st->cur[j]) + (size_t)r0 * s.dims[j] * st->level_elt(j);
-        ws.a_dtype = st->level_dtype(j);
-        ws.lda = s.dims[j];
-        ws.B = dY;
-        ws.ldb = s.ld[j + 1];
-        ws.M = (int)M;
-        ws.I = s.dims[j];
-        ws.O = s.dims[j + 1];
-        ws.scale = 1.f;
-        ws.dW = st->dW[j];
-        ws.partial = gemm_partial;
-        ws.max_splits = kMaxSplits;
-        HIP_TRY(st, launch_gemm_tn(ws, cd, stream));
-      }
-    }
+    return GNNSTAGE_OK;
   }
-  return GNNSTAGE_OK;
+  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  int rc = begin_forward(st, stream);
+  if (rc != GNNSTAGE_OK) return rc;
+  st->order.assign(order, order + n_order);
+  for (int32_t p = 0; p < n_order; ++p) mask_set(st->fmask, order[p]);
+  st->cur_stale = false;
+  return run_diagonals(st, st->order, [](int step) { return step; }, [&](const Cell *c, int n) { return forward_cells(st, c, n, stream); });
 }
-}  // namespace
+GNNSTAGE_GUARD_INT
 
 extern "C" int gnnstage_flush_weight_gradients(gnnstage_t *st, void *hip_stream) try {
   if (!st) return GNNSTAGE_EINVAL;
@@ -1922,244 +2072,55 @@ extern "C" int stage_backward_chunk(gnnstage_t *st, int32_t k, const void *grad_
   if ((int)st->order.size() != s.K) return fail(st, GNNSTAGE_EORDER, "backward before the forward pass covered every chunk");
   if (st->n_bwd >= s.K) return fail(st, GNNSTAGE_EORDER, "backward pass already complete");
   if (st->order[s.K - 1 - st->n_bwd] != k) return fail(st, GNNSTAGE_EORDER, "backward must walk the chunks in reverse forward order");
-  const int64_t row0 = s.chunk_ptr[k], M = s.chunk_ptr[k + 1] - row0;
+  const int64_t row0 = cell_row0(st, k), M = cell_rows(st, k);
   if (M > 0 && !grad_out_rows) return fail(st, GNNSTAGE_EINVAL, "grad_out_rows is NULL");
   st->n_bwd += 1;
   mask_set(st->bmask, k);
-  if (s.res()) return res_backward_chunk(st, k, grad_out_rows, stream);
-  // what the last call of a pass owes beyond its own rows: the deferred weight-gradient products, then the
-  // history-side weight gradient of the transform-first layers
-  auto end_of_pass = [&]() -> int {
-    if (st->n_bwd != s.K) return GNNSTAGE_OK;
-    const int rc = flush_deferred_wgrad(st, stream);
-    return rc != GNNSTAGE_OK ? rc : finish_transform_first(st, stream);
-  };
   // an empty chunk has no rows of its own, but the end-of-pass work still runs when it is the last call of the pass
-  if (M == 0) return end_of_pass();
+  if (M > 0) {
+    if (s.defer_wgrad()) st->wgrad_pending[(size_t)k] = 1;
+    st->gi = 0;
+    int rc = top_dY(st, grad_out_rows, row0, M, dY_rows(st, k, s.L - 1), stream);
+    for (int j = s.L - 1; j >= 0 && rc == GNNSTAGE_OK; --j) {
+      const Cell c{k, j, 0, st->bmask};
+      rc = backward_cells(st, &c, 1, false, stream);
+    }
+    if (rc != GNNSTAGE_OK) return rc;
+  }
+  return end_backward(st, stream);
+}
+GNNSTAGE_GUARD_INT
 
-  const int cd = st->cdtype();
-  const size_t celt = s.elt();
-  const bool defer = s.defer_wgrad();
-  char *G[2] = {st->at<char>(st->lay.G[0]), st->at<char>(st->lay.G[1])};
-  float *gemm_partial = st->at<float>(st->lay.gemm_partial);
-  float *bias_partial = st->at<float>(st->lay.bias_partial);
-  // Where dY_j = dL/d(pre-activation of layer j) of the chunk's rows lives, [M x ld_{j+1}], zero in the padding
-  // columns.  With deferred weight gradients: the chunk's rows of a matrix over all n rows (transform-first layers
-  // keep that matrix anyway, it is what later chunks' transposed aggregations gather); otherwise one of two
-  // chunk-sized scratch matrices, used alternately.
-  int gi = 0;
-  auto full_dY = [&](int j) { return st->at<char>(s.tf[j] ? st->lay.dZ[j] : st->lay.dY[j]); };
-  auto dY_rows = [&](int j) -> char * { return defer ? full_dY(j) + (size_t)row0 * s.ld[j + 1] * celt : G[gi]; };
-  if (defer) st->wgrad_pending[(size_t)k] = 1;
-  {
-    Timed t(st, stream, 6);
-    const char *top = static_cast<const char *>(st->cur[s.L]) + (size_t)row0 * s.dims[s.L] * celt;
-    HIP_TRY(st, launch_relu_mask(grad_out_rows, top, cd, M, s.dims[s.L], dY_rows(s.L - 1), s.ld[s.L], st->mask_scale(), stream));
+extern "C" int gnnstage_backward_pass(gnnstage_t *st, const int32_t *order, int32_t n_order, const void *grad_out, void *hip_stream) try {
+  if (!st || (n_order > 0 && !order)) return GNNSTAGE_EINVAL;
+  const Shape &s = st->s;
+  if (!grad_out || !whole_pass_ok(st, order, n_order) || st->n_bwd != 0 || (int)st->order.size() != s.K ||
+      !std::equal(st->order.begin(), st->order.end(), order)) {
+    for (int32_t p = n_order - 1; p >= 0; --p) {
+      const int32_t k = order[p];
+      if (k < 0 || k >= s.K) return fail(st, GNNSTAGE_ERANGE, "chunk id out of range");
+      const char *rows = static_cast<const char *>(grad_out);
+      const int rc = stage_backward_chunk(st, k, rows ? rows + (size_t)cell_row0(st, k) * s.dims[s.L] * s.elt() : nullptr, hip_stream);
+      if (rc != GNNSTAGE_OK) return rc;
+    }
+    return GNNSTAGE_OK;
   }
-  for (int j = s.L - 1; j >= 0; --j) {
-    const char *dY = dY_rows(j);
-    // bias gradient = column sums of dY: fused into the weight-gradient product where that product reads dY
-    // (aggregate-first layers), a kernel of its own for transform-first layers
-    if (s.has_bias() && s.tf[j]) {
-      Timed t(st, stream, 4, j);
-      HIP_TRY(st, launch_colsum_add(dY, cd, s.ld[j + 1], (int)M, s.dims[j + 1], bias_partial, kMaxSplits, st->dbias[j], stream));
-    }
-    const bool need_prev = j > 0 || s.need_input_grad;
-    if (s.tf[j]) {
-      // Layer computed as A_hat (H W).  With T = H W:  dL/dW = cur^T dT_cur + hist^T dT_hist, where
-      // dT_cur[u] sums A_vu dY[v] over the readers v that saw u's CURRENT row (exactly the vertices
-      // already processed in this backward pass) and dT_hist over the readers that saw its history.
-      // dT_cur + dT_hist is the unmasked transposed aggregation, known only when every chunk's dY is:
-      //   dW += (cur - hist)[C_k]^T dT_cur[C_k]   here, per chunk,
-      //   dW += hist^T (A_hat^T dY)                after the last chunk (finish_transform_first).
-      const bool shared = st->hist[j] == st->cur[j];
-      char *dYfull = st->at<char>(st->lay.dZ[j]);
-      if (!defer) {
-        Timed t(st, stream, 6);
-        HIP_TRY(st, launch_copy(dY, dYfull + (size_t)row0 * s.ld[j + 1] * celt, (size_t)M * s.ld[j + 1] * celt, stream));
-      }
-      if (shared && !need_prev) continue;  // nothing else depends on dT_cur
-      char *dT = defer ? G[0] : G[gi ^ 1];
-      {
-        SpmmArgs a = base_spmm(st, true, k);
-        a.src_sel = dYfull;
-        a.src_unsel = nullptr;  // Section 3.4: nothing flows back from unprocessed vertices
-        a.d = s.dims[j + 1];
-        a.src_ld = s.ld[j + 1];
-        a.out = dT;
-        a.out_ld = s.ld[j + 1];
-        a.out_row0 = row0;
-        a.epilogue = SPMM_PLAIN;
-        HIP_TRY(st, run_spmm(st, a, true, k, cd, cd, stream, 2, j));
-      }
-      if (!shared) {
-        Timed t(st, stream, 4, j);
-        GemmTnArgs w{};
-        w.wide_min_rows = st->s.tune.gemm_wide_min_rows;
-        w.a_dtype = st->level_dtype(j);
-        w.lda = s.dims[j];
-        w.B = dT;
-        w.ldb = s.ld[j + 1];
-        w.M = (int)M;
-        w.I = s.dims[j];
-        w.O = s.dims[j + 1];
-        w.dW = st->dW[j];
-        w.partial = gemm_partial;
-        w.max_splits = kMaxSplits;
-        w.A = static_cast<const char *>(st->cur[j]) + (size_t)row0 * s.dims[j] * st->level_elt(j);
-        w.scale = 1.f;
-        HIP_TRY(st, launch_gemm_tn(w, cd, stream));
-        w.A = static_cast<const char *>(st->hist[j]) + (size_t)row0 * s.dims[j] * st->level_elt(j);
-        w.scale = -1.f;
-        HIP_TRY(st, launch_gemm_tn(w, cd, stream));
-      }
-      if (!need_prev) continue;
-      {
-        Timed t(st, stream, 3, j);
-        GemmNtArgs g{};
-        g.ws_min_rows = st->s.tune.gemm_ws_min_rows;
-        g.A = dT;
-        g.a_dtype = cd;
-        g.lda = s.ld[j + 1];
-        g.Bt = st->at<char>(st->lay.Wn[j]);
-        g.ldb = s.ld[j + 1];
-        g.M = (int)M;
-        g.N = s.dims[j];
-        g.K = s.dims[j + 1];
-        g.Kp = s.ld[j + 1];
-        if (j > 0) {
-          g.epilogue = EPI_MASK;
-          g.mask_scale = st->mask_scale();
-          g.aux = static_cast<const char *>(st->cur[j]) + (size_t)row0 * s.dims[j] * celt;
-          g.aux_dtype = cd;
-          g.aux_ld = s.dims[j];
-          g.out = defer ? dY_rows(j - 1) : G[gi];  // without deferral dY_j is dead by now and its scratch is reused
-          g.out_dtype = cd;
-          g.out_ld = s.ld[j];
-          g.out_pad = s.ld[j];
-        } else {
-          g.epilogue = EPI_PLAIN;
-          g.out = static_cast<char *>(st->grad_in) + (size_t)row0 * s.dims[0] * st->level_elt(0);
-          g.out_dtype = st->level_dtype(0);
-          g.out_ld = s.dims[0];
-        }
-        HIP_TRY(st, launch_gemm_nt(g, cd, stream));
-      }
-      continue;  // without deferral the next dY sits in G[gi] again
-    }
-    if (!defer) {
-      const char *Zrows = st->at<char>(st->lay.Z[j]) + (size_t)row0 * s.ld[j] * celt;
-      Timed t(st, stream, 4, j);
-      GemmTnArgs w{};
-      w.wide_min_rows = st->s.tune.gemm_wide_min_rows;
-      w.A = Zrows;
-      w.a_dtype = cd;
-      w.lda = s.ld[j];
-      w.B = dY;
-      w.ldb = s.ld[j + 1];
-      w.M = (int)M;
-      w.I = s.dims[j];
-      w.O = s.dims[j + 1];
-      w.scale = s.variant == GNNSTAGE_GCNII ? st->beta[j] : 1.f;
-      w.dW = st->dW[j] + (s.sage() ? s.w_half(j) : 0);  // GraphSage: W_neigh is the lower half
-      w.partial = gemm_partial;
-      w.max_splits = kMaxSplits;
-      if (s.has_bias()) {
-        w.dbias = st->dbias[j];
-        w.bias_partial = bias_partial;
-      }
-      HIP_TRY(st, launch_gemm_tn(w, cd, stream));
-      if (s.sage()) {  // dW_self += h_v^T dY over the chunk's own (current) rows
-        GemmTnArgs ws{};
-        ws.wide_min_rows = st->s.tune.gemm_wide_min_rows;
-        ws.A = static_cast<const char *>(st->cur[j]) + (size_t)row0 * s.dims[j] * st->level_elt(j);
-        ws.a_dtype = st->level_dtype(j);
-        ws.lda = s.dims[j];
-        ws.B = dY;
-        ws.ldb = s.ld[j + 1];
-        ws.M = (int)M;
-        ws.I = s.dims[j];
-        ws.O = s.dims[j + 1];
-        ws.scale = 1.f;
-        ws.dW = st->dW[j];
-        ws.partial = gemm_partial;
-        ws.max_splits = kMaxSplits;
-        HIP_TRY(st, launch_gemm_tn(ws, cd, stream));
-      }
-    }
-    if (!need_prev) break;
-    char *dZj = st->at<char>(st->lay.dZ[j]);
-    {
-      Timed t(st, stream, 3, j);
-      GemmNtArgs g{};
-      g.ws_min_rows = st->s.tune.gemm_ws_min_rows;
-      g.A = dY;
-      g.a_dtype = cd;
-      g.lda = s.ld[j + 1];
-      g.Bt = st->at<char>(st->lay.Wn[j]);
-      g.ldb = s.ld[j + 1];
-      g.M = (int)M;
-      g.N = s.dims[j];
-      g.K = s.dims[j + 1];
-      g.Kp = s.ld[j + 1];
-      if (s.variant == GNNSTAGE_GCNII) {
-        g.epilogue = EPI_DGRAD_GCNII;
-        g.aux = dY;
-        g.aux_dtype = cd;
-        g.aux_ld = s.ld[j + 1];
-        g.alpha = st->alpha;
-        g.beta = st->beta[j];
-        g.h0grad = st->grad_h0 ? st->grad_h0 + (size_t)row0 * s.dims[j] : nullptr;
-        g.h0_ld = s.dims[j];
-      } else {
-        g.epilogue = EPI_PLAIN;
-      }
-      g.out = dZj + (size_t)row0 * s.ld[j] * celt;
-      g.out_dtype = cd;
-      g.out_ld = s.ld[j];
-      HIP_TRY(st, launch_gemm_nt(g, cd, stream));
-      if (s.sage()) {  // the gradient that reaches the chunk's own rows directly: dY W_self^T
-        g.Bt = st->at<char>(st->lay.Wn_self[j]);
-        g.out = st->at<char>(st->lay.self_bwd);
-        HIP_TRY(st, launch_gemm_nt(g, cd, stream));
-      }
-    }
-    {
-      SpmmArgs a = base_spmm(st, true, k);
-      a.src_sel = dZj;
-      a.src_unsel = nullptr;  // Section 3.4: nothing flows back from unprocessed vertices
-      a.d = s.dims[j];
-      a.src_ld = s.ld[j];
-      if (s.sage()) {
-        a.add = st->at<char>(st->lay.self_bwd);
-        a.add_ld = s.ld[j];
-        a.add_row0 = row0;
-      }
-      if (j > 0) {
-        if (defer) {  // straight into the chunk's rows of dY_{j-1}
-          a.out = full_dY(j - 1);
-          a.out_row0 = 0;
-        } else {
-          a.out = G[gi ^ 1];
-          a.out_row0 = row0;
-        }
-        a.out_ld = s.ld[j];
-        a.epilogue = s.sage() ? SPMM_ADD_MASK : SPMM_MASK;
-        a.mask_scale = st->mask_scale();
-        a.aux = st->cur[j];
-        a.aux_ld = s.dims[j];
-        HIP_TRY(st, run_spmm(st, a, true, k, cd, cd, stream, 2, j));
-      } else {
-        a.out = st->grad_in;
-        a.out_ld = s.dims[0];
-        a.out_row0 = 0;
-        a.epilogue = s.sage() ? SPMM_ADD : SPMM_PLAIN;
-        HIP_TRY(st, run_spmm(st, a, true, k, cd, st->level_dtype(0), stream, 2, j));
-      }
-    }
-    gi ^= 1;
+  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  const std::vector<int32_t> back(st->order.rbegin(), st->order.rend());
+  for (int32_t k = 0; k < s.K; ++k) {
+    mask_set(st->bmask, k);
+    st->wgrad_pending[(size_t)k] = cell_rows(st, k) > 0 ? 1 : 0;
   }
-  return end_of_pass();
+  st->n_bwd = s.K;
+  int rc = top_dY(st, grad_out, 0, s.n, full_dY(st, s.L - 1), stream);
+  if (rc != GNNSTAGE_OK) return rc;
+  rc = run_diagonals(st, back, [&](int step) { return s.L - 1 - step; }, [&](const Cell *c, int n) { return backward_cells(st, c, n, true, stream); });
+  if (rc != GNNSTAGE_OK) return rc;
+  for (int j = 0; j < s.L; ++j)
+    if (s.tf[j] && s.has_bias())
+      HIP_TRY(st, launch_colsum_add(full_dY(st, j), st->cdtype(), s.ld[j + 1], (int)s.n, s.dims[j + 1], st->at<float>(st->lay.bias_partial), kMaxSplits,
+                                    st->dbias[j], stream));
+  return end_backward(st, stream);
 }
 GNNSTAGE_GUARD_INT
 

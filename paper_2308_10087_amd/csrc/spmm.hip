@@ -105,12 +105,15 @@ __device__ inline void zero_pad_cols(const SpmmArgs &a, int64_t row, int lane) {
 // A row's last vector moves back so that it ends with the row: it repeats columns of its neighbour lane, which both
 // lanes sum and store alike, and every width is read in 16-byte accesses.
 template <typename Tin, typename Tout, int VEC, int LPR, int U>
-__global__ __launch_bounds__(256) void spmm_kernel(const SpmmArgs a) {
+__global__ __launch_bounds__(256) void spmm_kernel(const Batch<SpmmArgs> ba) {
+  const int bi = ba.find(blockIdx.x);
+  const SpmmArgs &a = ba.sub[bi];
+  const unsigned block = blockIdx.x - ba.off[bi];  // inside the sub-launch
   typedef Tin vec_t __attribute__((ext_vector_type(VEC), aligned(4)));
   constexpr int G = 64 / LPR;
   constexpr int TILE_W = LPR * VEC;
   const int lane = threadIdx.x & 63;
-  const int64_t task = spmm_task_index(a, blockIdx.x, threadIdx.x >> 6);
+  const int64_t task = spmm_task_index(a, block, threadIdx.x >> 6);
   if (task < 0) return;  // whole wave leaves together
   const int grp = lane / LPR, lig = lane % LPR;
   const int d = a.d;
@@ -230,9 +233,12 @@ __global__ __launch_bounds__(256) void spmm_kernel(const SpmmArgs a) {
 // that did not run in this launch holds stale sums) are loaded anyway, together with the word that says so,
 // and left out by a select; the epilogue's auxiliary row is asked for before the sums.
 template <typename Tin, typename Tout, int VEC>
-__global__ __launch_bounds__(256) void spmm_reduce_kernel(const SpmmArgs a) {
+__global__ __launch_bounds__(256) void spmm_reduce_kernel(const Batch<SpmmArgs> ba) {
   __shared__ float red[8][32][VEC];
-  const int64_t i = blockIdx.x;
+  const int bi = ba.find(blockIdx.x);
+  const SpmmArgs &a = ba.sub[bi];
+  const unsigned block = blockIdx.x - ba.off[bi];  // inside the sub-launch
+  const int64_t i = block;
   const int ph = threadIdx.x >> 5, cv = threadIdx.x & 31;
   const bool dense = a.lr_ndense != nullptr;
   const int64_t row = a.lr_row[i];
@@ -374,19 +380,22 @@ __device__ __forceinline__ void spmm_short_rows(const SpmmArgs &a, int64_t first
 // and U - 1 steps of gathers stay in flight while one is consumed.  Per step the vector ALU only adds
 // the lane offset to the record's address and expands the weight (one byte permute, four selects).
 template <typename Tout, int NT, int U, bool FULL>
-__global__ __launch_bounds__(256, (NT * U <= 8) ? 7 : 1) void spmm_ring_kernel(const SpmmArgs a) {
+__global__ __launch_bounds__(256, (NT * U <= 8) ? 7 : 1) void spmm_ring_kernel(const Batch<SpmmArgs> ba) {
+  const int bi = ba.find(blockIdx.x);
+  const SpmmArgs &a = ba.sub[bi];
+  const unsigned block = blockIdx.x - ba.off[bi];  // inside the sub-launch
   constexpr int TILE_W = NT * 128;
   constexpr int KB = 2;    // metadata batches per phase
   constexpr int R = 256;   // ring capacity in records: a phase appends at most 64 * KB, fewer than 8 * U are left over
   static_assert(TILE_W * sizeof(float) <= R * sizeof(u32x4_t), "the output row reuses the ring's memory");
   static_assert((U & (U - 1)) == 0 && U <= 8, "slot count");
   __shared__ u32x4_t ring_all[4][R];
-  if ((int64_t)blockIdx.x >= a.n_main_blocks) {  // the workgroups behind the main part serve the short rows, 16 each
-    if constexpr (NT <= 2) spmm_short_rows<Tout, NT, FULL>(a, ((int64_t)blockIdx.x - a.n_main_blocks) * 16);
+  if ((int64_t)block >= a.n_main_blocks) {  // the workgroups behind the main part serve the short rows, 16 each
+    if constexpr (NT <= 2) spmm_short_rows<Tout, NT, FULL>(a, ((int64_t)block - a.n_main_blocks) * 16);
     return;
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t task = spmm_task_index(a, blockIdx.x, wave);
+  const int64_t task = spmm_task_index(a, block, wave);
   if (task < 0) return;  // whole wave leaves together (no block-wide barrier below)
   u32x4_t *ring = ring_all[wave];
   const int g = lane >> 4, lig = lane & 15;
@@ -578,7 +587,7 @@ __global__ __launch_bounds__(256, (NT * U <= 8) ? 7 : 1) void spmm_ring_kernel(c
   if (slot < 0 && blockIdx.y == 0) zero_pad_cols<Tout>(a, row, lane);
 }
 
-typedef void (*spmm_fn)(const SpmmArgs);
+typedef void (*spmm_fn)(const Batch<SpmmArgs>);
 struct Shape {
   int vec, lpr;
   spmm_fn main, reduce;
@@ -628,59 +637,94 @@ static bool mfma_path(const SpmmArgs &a, int src_dtype) {
 }
 
 template <typename Tout, int NT>
-static void launch_ring(const SpmmArgs &a, hipStream_t s, dim3 grid, int unroll) {
+static spmm_fn ring_fn(const SpmmArgs &a, int unroll) {
   const bool full = a.d == NT * 128;
-  if (unroll >= 8) {
-    if (full) hipLaunchKernelGGL((spmm_ring_kernel<Tout, NT, 8, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((spmm_ring_kernel<Tout, NT, 8, false>), grid, dim3(256), 0, s, a);
-  } else if (unroll >= 4) {
-    if (full) hipLaunchKernelGGL((spmm_ring_kernel<Tout, NT, 4, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((spmm_ring_kernel<Tout, NT, 4, false>), grid, dim3(256), 0, s, a);
-  } else {
-    if (full) hipLaunchKernelGGL((spmm_ring_kernel<Tout, NT, 2, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((spmm_ring_kernel<Tout, NT, 2, false>), grid, dim3(256), 0, s, a);
-  }
+  if (unroll >= 8) return full ? spmm_ring_kernel<Tout, NT, 8, true> : spmm_ring_kernel<Tout, NT, 8, false>;
+  if (unroll >= 4) return full ? spmm_ring_kernel<Tout, NT, 4, true> : spmm_ring_kernel<Tout, NT, 4, false>;
+  return full ? spmm_ring_kernel<Tout, NT, 2, true> : spmm_ring_kernel<Tout, NT, 2, false>;
 }
-
 template <typename Tout>
-static int launch_mfma(const SpmmArgs &a_in, hipStream_t s) {
-  SpmmArgs a = a_in;
-  // short whole rows (the tail of the task list) are served a row per 16-lane group, by extra workgroups of the
-  // same launch, when a row fits the registers of such a group
-  const int64_t n_short = (a.d <= 256 && a.n_short > 0 && a.n_short <= a.n_tasks - a.tail_task0) ? a.n_short : 0;
-  a.n_tasks -= n_short;
-  a.n_short = n_short;
-  a.n_main_blocks = a.n_class_blocks + (a.n_tasks - a.tail_task0 + 3) / 4;
-  const unsigned gx = (unsigned)(a.n_main_blocks + (n_short + 15) / 16);
-  if (gx == 0) return hipSuccess;  // only class pieces, none of them active
+static spmm_fn ring_for(const SpmmArgs &a) {
   const int unroll = a.unroll;  // 4 or 8 trade waves per SIMD for deeper per-wave queues (tests run all three)
-  if (a.d <= 128)
-    launch_ring<Tout, 1>(a, s, dim3(gx, 1), unroll);
-  else if (a.d <= 256)
-    launch_ring<Tout, 2>(a, s, dim3(gx, 1), unroll);
-  else
-    launch_ring<Tout, 4>(a, s, dim3(gx, (unsigned)((a.d + 511) / 512)), unroll >= 8 ? 4 : 2);
-  return (int)hipGetLastError();
+  return a.d <= 128 ? ring_fn<Tout, 1>(a, unroll) : a.d <= 256 ? ring_fn<Tout, 2>(a, unroll) : ring_fn<Tout, 4>(a, unroll >= 8 ? 4 : 2);
 }
 
-int launch_spmm(const SpmmArgs &a, int src_dtype, int out_dtype, hipStream_t s) {
-  if (a.n_tasks <= 0) return hipSuccess;
-  if (mfma_path(a, src_dtype)) return out_dtype == DT_BF16 ? launch_mfma<bf16_t>(a, s) : launch_mfma<float>(a, s);
-  const Shape *best = pick_shape(a, src_dtype, out_dtype);
-  if (!best) return hipErrorInvalidValue;
-  const int tile_w = best->lpr * best->vec;
-  dim3 grid((unsigned)(a.n_class_blocks + (a.n_tasks - a.tail_task0 + 3) / 4), (unsigned)((a.d + tile_w - 1) / tile_w));
-  if (grid.x == 0) return hipSuccess;
-  if (grid.y > 1) grid.x = (grid.x + 7) / 8 * 8;  // every column tile starts on the same XCD (tasks past the end do nothing)
-  hipLaunchKernelGGL(best->main, grid, dim3(256), 0, s, a);
-  return (int)hipGetLastError();
+// Runs launches [0, n) (kernel fn[i], gx[i] workgroups in x, gy[i] in y; gx = 0: nothing to do), those of one kernel and gy
+// together.  align: a sub-launch starts at a multiple of so many workgroups (8: its workgroup i runs on XCD i % 8).
+static int launch_merged(const SpmmArgs *const *a, const spmm_fn *fn, const unsigned *gx, const unsigned *gy, int n, unsigned align, hipStream_t s) {
+  bool done[kBatch] = {};
+  for (int i = 0; i < n; ++i) {
+    if (done[i] || gx[i] == 0) continue;
+    Batch<SpmmArgs> b;
+    b.n = 0;
+    b.off[0] = 0;
+    for (int j = i; j < n; ++j) {
+      if (done[j] || gx[j] == 0 || fn[j] != fn[i] || gy[j] != gy[i]) continue;
+      done[j] = true;
+      b.sub[b.n] = *a[j];
+      b.off[b.n + 1] = b.off[b.n] + (gx[j] + align - 1) / align * align;
+      ++b.n;
+    }
+    hipLaunchKernelGGL(fn[i], dim3(b.n == 1 ? gx[i] : b.off[b.n], gy[i]), dim3(256), 0, s, b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
+  }
+  return hipSuccess;
 }
 
-int launch_spmm_reduce(const SpmmArgs &a, int src_dtype, int out_dtype, hipStream_t s) {
-  if (a.n_long <= 0) return hipSuccess;
-  const Shape *best = pick_shape(a, src_dtype, out_dtype);
-  if (!best) return hipErrorInvalidValue;
-  const unsigned tiles = (unsigned)((a.d + 32 * best->vec - 1) / (32 * best->vec));
-  hipLaunchKernelGGL(best->reduce, dim3((unsigned)a.n_long, tiles), dim3(256), 0, s, a);
-  return (int)hipGetLastError();
+int launch_spmm(const SpmmLaunch *l, int n, hipStream_t s) {
+  if (n > kBatch) return hipErrorInvalidValue;
+  SpmmArgs args[kBatch];
+  const SpmmArgs *ptr[kBatch];
+  spmm_fn fn[kBatch];
+  unsigned gx[kBatch], gy[kBatch];
+  for (int i = 0; i < n; ++i) {
+    SpmmArgs &a = args[i] = l[i].a;
+    ptr[i] = &a;
+    gx[i] = 0;
+    gy[i] = 1;
+    fn[i] = nullptr;
+    if (a.n_tasks <= 0) continue;
+    if (mfma_path(a, l[i].src_dtype)) {
+      // short whole rows (the tail of the task list) are served a row per 16-lane group, by extra workgroups of the
+      // same launch, when a row fits the registers of such a group
+      const int64_t n_short = (a.d <= 256 && a.n_short > 0 && a.n_short <= a.n_tasks - a.tail_task0) ? a.n_short : 0;
+      a.n_tasks -= n_short;
+      a.n_short = n_short;
+      a.n_main_blocks = a.n_class_blocks + (a.n_tasks - a.tail_task0 + 3) / 4;
+      gx[i] = (unsigned)(a.n_main_blocks + (n_short + 15) / 16);  // 0: only class pieces, none of them active
+      fn[i] = l[i].out_dtype == DT_BF16 ? ring_for<bf16_t>(a) : ring_for<float>(a);
+      gy[i] = a.d <= 256 ? 1u : (unsigned)((a.d + 511) / 512);
+    } else {
+      const Shape *best = pick_shape(a, l[i].src_dtype, l[i].out_dtype);
+      if (!best) return hipErrorInvalidValue;
+      const int tile_w = best->lpr * best->vec;
+      fn[i] = best->main;
+      gx[i] = (unsigned)(a.n_class_blocks + (a.n_tasks - a.tail_task0 + 3) / 4);
+      gy[i] = (unsigned)((a.d + tile_w - 1) / tile_w);
+      if (gy[i] > 1) gx[i] = (gx[i] + 7) / 8 * 8;  // every column tile starts on the same XCD (tasks past the end do nothing)
+    }
+  }
+  return launch_merged(ptr, fn, gx, gy, n, 8, s);
+}
+
+int launch_spmm_reduce(const SpmmLaunch *l, int n, hipStream_t s) {
+  if (n > kBatch) return hipErrorInvalidValue;
+  const SpmmArgs *ptr[kBatch];
+  spmm_fn fn[kBatch];
+  unsigned gx[kBatch], gy[kBatch];
+  for (int i = 0; i < n; ++i) {
+    const SpmmArgs &a = l[i].a;
+    ptr[i] = &a;
+    gx[i] = 0;
+    gy[i] = 1;
+    fn[i] = nullptr;
+    if (a.n_long <= 0) continue;
+    const Shape *best = pick_shape(a, l[i].src_dtype, l[i].out_dtype);
+    if (!best) return hipErrorInvalidValue;
+    fn[i] = best->reduce;
+    gx[i] = (unsigned)a.n_long;
+    gy[i] = (unsigned)((a.d + 32 * best->vec - 1) / (32 * best->vec));
+  }
+  return launch_merged(ptr, fn, gx, gy, n, 1, s);
 }

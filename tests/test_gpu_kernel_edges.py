@@ -64,3 +64,63 @@ def test_fp32_forward_sums_do_not_depend_on_the_chunks(dims):
         top.append(GpuRun(p, alias_hist0=True, need_input_grad=False))
         top[-1].forward()
     assert torch.equal(top[0].cur[1], top[1].cur[1])
+
+
+@pytest.mark.parametrize("variant,dtype,dims,k,kw", [
+    ("gcn", "f32", (20, 24, 40, 16, 32), 5, {}), ("gcn", "bf16", (100, 128, 64, 64), 7, {}), ("sage", "f32", (33, 36, 20), 4, {"dropout_p": 0.4}),
+    ("sage", "bf16", (64, 128, 128), 3, {}), ("gcnii", "bf16", (64,) * 12, 11, {}), ("gcnii", "f32", (40, 40), 6, {}),
+    ("resgcn", "f32", (36,) * 5, 6, {"dropout_p": 0.3}), ("resgcn", "bf16", (128,) * 4, 9, {}), ("gcn", "bf16", (602, 100, 100), 1, {})])
+def test_whole_pass_calls_equal_the_chunk_calls(variant, dtype, dims, k, kw):
+    """More and fewer chunks than layers, more of both than cells run side by side, an empty chunk, one chunk only: levels and
+    what flows back are the same bits; parameter gradients the same sums in another order (fp32, a few hundred terms)."""
+    n = 700
+    cp = np.sort(np.concatenate([[0, n], np.random.default_rng(3).integers(1, n, k - 1)])).astype(np.int64)
+    if k > 3:
+        cp[2] = cp[1]
+    p = make_problem(small(n=n, k=k, dims=dims, variant=variant, dtype=dtype, deg=9.0), chunk_ptr=cp, bias_std=0.05, first_stage=False, dropout_seed=5, **kw)
+    whole, by_chunk = GpuRun(p), GpuRun(p)
+    for _ in range(2):  # the second pass finds the scratch of the first
+        whole.run()
+    for _ in range(2):
+        if p.dropout_p > 0:
+            by_chunk.stage.gnnstage_set_dropout_seed(p.dropout_seed)
+        for pos, c in enumerate(p.order):
+            by_chunk.stage.stage_forward_chunk(int(c), pos)
+        for c in reversed(list(p.order)):
+            by_chunk.stage.stage_backward_chunk(int(c), by_chunk.grad_out[by_chunk.stage.rows(int(c))])
+    torch.cuda.synchronize()
+    for a, b in zip(whole.cur + [whole.grad_in], by_chunk.cur + [by_chunk.grad_in]):
+        assert torch.equal(a, b)
+    if whole.grad_h0 is not None:
+        assert torch.equal(whole.grad_h0, by_chunk.grad_h0)
+    for name in ("dW", "dbias", "d_ln_gamma", "d_ln_beta"):
+        for a, b in zip(getattr(whole, name) or [], getattr(by_chunk, name) or []):
+            assert (a - b).abs().max() <= 1e-5 * b.abs().max() + 1e-30, name
+
+
+def test_passes_that_cannot_run_whole_behave_like_the_chunk_calls():
+    """Levels that are their own history (what is not selected are rows of the last pass), and orders that are none."""
+    import paper_2308_10087_amd as g
+    p = make_problem(small(n=500, k=5, dims=(24, 24, 24, 24), deg=9.0), bias_std=0.05, first_stage=False)
+    runs = [GpuRun(p), GpuRun(p)]
+    for r in runs:
+        r.hist[1:] = r.cur[1:3]
+        r.stage = g.GnnStage(p.row_ptr, p.col, p.chunk_ptr, p.dims, W=r.W, cur=r.cur, hist=r.hist, dW=r.dW, bias=r.bias, dbias=r.dbias, edge_val=p.val,
+                             variant=g.GNNSTAGE_GCN, dtype=g.GNNSTAGE_F32, grad_in=r.grad_in, device=r.device)
+    for _ in range(2):
+        runs[0].run()
+        for pos, c in enumerate(p.order):
+            runs[1].stage.stage_forward_chunk(int(c), pos)
+        for c in reversed(list(p.order)):
+            runs[1].stage.stage_backward_chunk(int(c), runs[1].grad_out[runs[1].stage.rows(int(c))])
+    torch.cuda.synchronize()
+    for a, b in zip(runs[0].cur + [runs[0].grad_in], runs[1].cur + [runs[1].grad_in]):
+        assert torch.equal(a, b)
+    st = runs[0].stage
+    with pytest.raises(g.GnnStageError) as e:
+        st.forward_pass([0, 1, 1, 2, 3])
+    assert e.value.code == -3
+    st.forward_pass([0, 1, 2, 3, 4])
+    with pytest.raises(g.GnnStageError) as e:
+        st.backward_pass([1, 0, 2, 3, 4][::-1], runs[0].grad_out)
+    assert e.value.code == -3

@@ -127,7 +127,7 @@ struct Layout {
 };
 
 struct Dims {
-  int64_t n = 0, max_rows = 0, n_param_elems = 0;
+  int64_t n = 0, head_rows = 0, n_param_elems = 0;  // head_rows: of one block of the head's work
   int K = 0, d_top = 0, C = 0, Cp = 0, Kp = 0, dtype = 0, elt = 4;
 };
 
@@ -150,9 +150,7 @@ bool read_dims(const gnntrain_desc *d, Dims &x, std::string &err) {
   x.C = d->n_classes;
   x.Cp = round_up(x.C, 8);
   x.Kp = round_up(x.d_top, 8);
-  x.max_rows = 0;
-  for (int c = 0; c < x.K; ++c)
-    x.max_rows = std::max<int64_t>(x.max_rows, gnnstage_query(last, GNNSTAGE_Q_CHUNK_PTR, c + 1) - gnnstage_query(last, GNNSTAGE_Q_CHUNK_PTR, c));
+  x.head_rows = std::min<int64_t>(x.n, 131072);
   x.n_param_elems = 0;
   for (int i = 0; i < d->n_params; ++i) {
     const gnntrain_param &p = d->params[i];
@@ -174,9 +172,9 @@ Layout make_layout(const gnntrain_desc *d, const Dims &x) {
   const size_t moments = d->optimizer == GNNTRAIN_ADAM ? sizeof(float) * (size_t)x.n_param_elems : 0;
   l.m = take(moments);
   l.v = take(moments);
-  l.logits = take(sizeof(float) * (size_t)x.max_rows * x.Cp);
+  l.logits = take(sizeof(float) * (size_t)x.head_rows * x.Cp);
   l.dlogits = take((size_t)x.elt * x.n * x.Cp);
-  l.dtop = take((size_t)x.elt * x.max_rows * x.d_top);
+  l.dtop = take((size_t)x.elt * x.n * x.d_top);
   l.row_loss = take(sizeof(float) * (size_t)x.n);
   l.scratch = take(sizeof(float) * 1024);
   l.loss = take(256);
@@ -507,12 +505,19 @@ extern "C" int gnntrain_epoch(gnntrain_t *tr, int64_t epoch, float *loss, void *
   char *dlogits = tr->at<char>(lay.dlogits);
   float *row_loss = tr->at<float>(lay.row_loss);
   const float inv_n = (float)(1.0 / (double)tr->n_train);
-  // ---- forward: every chunk through all stages, then through the head
-  for (int pos = 0; pos < x.K; ++pos) {
-    const int k = tr->order[(size_t)pos];
-    for (int s = 0; s < S; ++s) TRAIN_STAGE(tr, s, stage_forward_chunk(tr->stages[(size_t)s], k, pos, stream));
-    const int64_t row0 = tr->chunk_ptr[(size_t)k], M = tr->chunk_ptr[(size_t)k + 1] - row0;
-    if (M == 0) continue;
+  // ---- forward: the stages one after the other (a stage reads the rows below it of the chunks it has processed, all of
+  // which are there by then), then the head, in blocks of rows: what it computes of a row depends on that row alone
+  bool by_stage = true;  // not where a stage's history IS the rows below it: what it does not select then has to be of the last epoch
+  for (int s = 1; s < S; ++s)
+    by_stage = by_stage && gnnstage_buffer(tr->stages[(size_t)s], GNNSTAGE_B_HIST, 0) != gnnstage_buffer(tr->stages[(size_t)s], GNNSTAGE_B_CUR, 0);
+  if (by_stage) {
+    for (int s = 0; s < S; ++s) TRAIN_STAGE(tr, s, gnnstage_forward_pass(tr->stages[(size_t)s], tr->order.data(), x.K, stream));
+  } else {
+    for (int pos = 0; pos < x.K; ++pos)
+      for (int s = 0; s < S; ++s) TRAIN_STAGE(tr, s, stage_forward_chunk(tr->stages[(size_t)s], tr->order[(size_t)pos], pos, stream));
+  }
+  for (int64_t row0 = 0; row0 < x.n; row0 += x.head_rows) {
+    const int64_t M = std::min(x.head_rows, x.n - row0);
     GemmNtArgs g{};
     g.A = static_cast<const char *>(tr->top) + (size_t)row0 * x.d_top * x.elt;
     g.a_dtype = cd;
@@ -532,55 +537,47 @@ extern "C" int gnntrain_epoch(gnntrain_t *tr, int64_t epoch, float *loss, void *
                                          M, x.C, inv_n, dlogits + (size_t)row0 * x.Cp * x.elt, cd, x.Cp, row_loss + row0, stream);
     if (rc != GNNSTAGE_OK) return fail(tr, rc, "softmax cross-entropy launch failed");
   }
-  // ---- backward: reverse order, head first, then the stages from the last to the first
-  for (int pos = x.K - 1; pos >= 0; --pos) {
-    const int k = tr->order[(size_t)pos];
-    const int64_t row0 = tr->chunk_ptr[(size_t)k], M = tr->chunk_ptr[(size_t)k + 1] - row0;
+  // ---- backward: the head, then the stages from the last to the first, each in reverse chunk order
+  for (int64_t row0 = 0; row0 < x.n; row0 += x.head_rows) {
+    const int64_t M = std::min(x.head_rows, x.n - row0);
     const char *dl = dlogits + (size_t)row0 * x.Cp * x.elt;
-    const char *top_rows = static_cast<const char *>(tr->top) + (size_t)row0 * x.d_top * x.elt;
-    char *dtop = tr->at<char>(lay.dtop);
-    if (M > 0) {
-      GemmTnArgs w{};
-      w.A = top_rows;
-      w.a_dtype = cd;
-      w.lda = x.d_top;
-      w.B = dl;
-      w.ldb = x.Cp;
-      w.M = (int)M;
-      w.I = x.d_top;
-      w.O = x.C;
-      w.scale = 1.f;
-      w.dW = tr->head_dW;
-      w.partial = tr->at<float>(lay.gemm_partial);
-      w.max_splits = kMaxSplits;
-      w.dbias = tr->head_db;  // the bias gradient (column sums of the logit gradients) rides along
-      w.bias_partial = tr->at<float>(lay.bias_partial);
-      TRAIN_HIP(tr, launch_gemm_tn(w, cd, stream));
-      GemmNtArgs g{};
-      g.A = dl;
-      g.a_dtype = cd;
-      g.lda = x.Cp;
-      g.Bt = tr->at<char>(lay.Wn);
-      g.ldb = x.Cp;
-      g.M = (int)M;
-      g.N = x.d_top;
-      g.K = x.C;
-      g.Kp = x.Cp;
-      g.epilogue = EPI_PLAIN;
-      g.out = dtop;
-      g.out_dtype = cd;
-      g.out_ld = x.d_top;
-      TRAIN_HIP(tr, launch_gemm_nt(g, cd, stream));
-    }
-    const char *gout = dtop;
-    for (int s = S - 1; s >= 0; --s) {
-      gnnstage_t *st = tr->stages[(size_t)s];
-      TRAIN_STAGE(tr, s, stage_backward_chunk(st, k, gout, stream));
-      if (s > 0) {
-        const int d0 = (int)gnnstage_query(st, GNNSTAGE_Q_WIDTH, 0);
-        gout = static_cast<const char *>(gnnstage_buffer(st, GNNSTAGE_B_GRAD_IN, 0)) + (size_t)row0 * d0 * x.elt;
-      }
-    }
+    GemmTnArgs w{};
+    w.A = static_cast<const char *>(tr->top) + (size_t)row0 * x.d_top * x.elt;
+    w.a_dtype = cd;
+    w.lda = x.d_top;
+    w.B = dl;
+    w.ldb = x.Cp;
+    w.M = (int)M;
+    w.I = x.d_top;
+    w.O = x.C;
+    w.scale = 1.f;
+    w.dW = tr->head_dW;
+    w.partial = tr->at<float>(lay.gemm_partial);
+    w.max_splits = kMaxSplits;
+    w.dbias = tr->head_db;  // the bias gradient (column sums of the logit gradients) rides along
+    w.bias_partial = tr->at<float>(lay.bias_partial);
+    TRAIN_HIP(tr, launch_gemm_tn(w, cd, stream));
+    GemmNtArgs g{};
+    g.A = dl;
+    g.a_dtype = cd;
+    g.lda = x.Cp;
+    g.Bt = tr->at<char>(lay.Wn);
+    g.ldb = x.Cp;
+    g.M = (int)M;
+    g.N = x.d_top;
+    g.K = x.C;
+    g.Kp = x.Cp;
+    g.epilogue = EPI_PLAIN;
+    g.out = tr->at<char>(lay.dtop) + (size_t)row0 * x.d_top * x.elt;
+    g.out_dtype = cd;
+    g.out_ld = x.d_top;
+    TRAIN_HIP(tr, launch_gemm_nt(g, cd, stream));
+  }
+  const void *gout = tr->at<char>(lay.dtop);
+  for (int s = S - 1; s >= 0; --s) {
+    gnnstage_t *st = tr->stages[(size_t)s];
+    TRAIN_STAGE(tr, s, gnnstage_backward_pass(st, tr->order.data(), x.K, gout, stream));
+    if (s > 0) gout = gnnstage_buffer(st, GNNSTAGE_B_GRAD_IN, 0);
   }
   // ---- the loss of this pass
   TRAIN_HIP(tr, launch_sum(row_loss, x.n, inv_n, tr->at<float>(lay.scratch), tr->at<float>(lay.loss), stream));

@@ -143,18 +143,12 @@ __device__ inline int64_t spmm_task_index(const SpmmArgs &a, unsigned b, int wav
 
 // ---- several launches in one -------------------------------------------------------------------
 // The cells (chunk, layer) of a pass on one anti-diagonal do not depend on each other; their launches of the same kernel run
-// as one, operand sets side by side: sub-launch i is workgroups off[i] .. off[i + 1] - 1.
+// as one, operand sets side by side: sub-launch z is the grid's plane z, so that a workgroup's operands are one load away.
+// Planes are as wide as the widest sub-launch; workgroups past the end of theirs return.
 constexpr int kBatch = 8;  // the kernel arguments stay below 4 KB
 template <typename A>
 struct Batch {
-  int32_t n;
-  uint32_t off[kBatch + 1];
   A sub[kBatch];
-  __device__ int find(unsigned b) const {  // wave-uniform
-    int i = 0;
-    while (i + 1 < n && b >= off[i + 1]) ++i;
-    return i;
-  }
 };
 static_assert(sizeof(Batch<SpmmArgs>) <= 4096, "kernel arguments");
 
@@ -240,6 +234,7 @@ struct GemmNtArgs {
   int32_t out_ld;
   int32_t out_pad;  // columns [N, out_pad) of every output row are written as zeros (0: none)
   int32_t vec_epi;  // set by the launcher: the epilogue may use 16-byte accesses
+  int32_t ws_blocks;  // set by the launcher: workgroups of a persistent kernel that share this product's row tiles
   float mask_scale = 1.f;  // EPI_MASK: what passes the mask is scaled (1 / (1 - rate) of that dropout)
   LnDropout drop{};        // EPI_FWD_GCN / EPI_FWD_ADD: dropout of the layer's output (threshold 0: none)
   int32_t ws_min_rows = 65536;  // rows from which the weight-stationary kernel is used (tests force it on small inputs)
@@ -276,15 +271,34 @@ constexpr int kLnMaxWidth = 1024;  // a row lives in the registers of one wavefr
 constexpr int kLnMaxWaves = 8192;  // wavefronts of one backward launch; the parameter-gradient scratch holds one
                                    // 2 x d block of sums per workgroup of four
 // out[r][c] = Dropout(ReLU(gamma[c] * (x[r][c] - mean_r) / sqrt(var_r + eps) + beta[c])), c < d; zeros up to out_ld
-int launch_ln_relu(const void *x, int x_dtype, int x_ld, const float *gamma, const float *beta, float eps, int64_t M, int d, void *out,
-                   int out_dtype, int out_ld, const LnDropout &dp, hipStream_t s);
-// Backward of the same for M rows: dr is the gradient of the activated rows.  out (may be NULL) receives the
-// gradient of x plus, when res is not NULL, the rows of res (the residual branch); dgamma / dbeta get "+=" of
-// the column sums in a fixed order (partial: fp32 scratch, kLnMaxWaves / 4 * 2 * d).
-int launch_ln_relu_backward(const void *x, int x_dtype, int x_ld, const float *gamma, const float *beta, float eps, const void *dr,
-                            int dr_dtype, int dr_ld, const void *res, int res_dtype, int res_ld, int64_t M, int d, void *out,
-                            int out_dtype, int out_ld, float *partial, float *dgamma, float *dbeta, const LnDropout &dp,
-                            hipStream_t s);
+struct LnArgs {
+  const void *x;
+  int32_t x_dtype, x_ld;
+  const float *gamma, *beta;
+  float eps;
+  int64_t M;
+  int32_t d;
+  void *out;
+  int32_t out_dtype, out_ld;
+  LnDropout drop;
+  int32_t blocks;  // set by the launcher
+};
+// Backward of the same for M rows (the fields above: out, which may be NULL, receives the gradient of x): dr is the gradient of
+// the activated rows, res (or NULL) rows that are added to out (the residual branch); dgamma / dbeta get "+=" of the column
+// sums in a fixed order (partial: fp32 scratch, kLnMaxWaves / 4 * 2 * d).
+struct LnBackArgs {
+  LnArgs f;
+  const void *dr;
+  int32_t dr_dtype, dr_ld;
+  const void *res;
+  int32_t res_dtype, res_ld;
+  float *partial;
+  float *dgamma, *dbeta;
+};
+static_assert(sizeof(Batch<LnBackArgs>) <= 4096, "kernel arguments");
+// n <= kBatch of them that do not depend on each other (backward: with scratch and parameters of their own)
+int launch_ln_relu(const LnArgs *a, int n, hipStream_t s);
+int launch_ln_relu_backward(const LnBackArgs *a, int n, hipStream_t s);
 // dst[r][c] = src[r][c] for c < d, zero for d <= c < dst_ld
 int launch_copy_rows(const void *src, int src_ld, void *dst, int dst_ld, int64_t M, int d, int dtype, hipStream_t s);
 

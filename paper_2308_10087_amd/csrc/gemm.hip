@@ -9,7 +9,7 @@
 // Bt and B always live in the library's zero-padded internal buffers (16-byte aligned rows);
 // A may also be a caller-owned level buffer of any width and of fp32 or bf16 type, in which case
 // it is read element-wise with bounds checks and converted while it is staged into LDS.
-#include <stdlib.h>
+#include <algorithm>
 
 #include "common.h"
 
@@ -213,9 +213,7 @@ constexpr int BM = 128, BN = 128;
 // fully coalesced) instead of eight scalars per lane.
 template <typename TA, bool VEC, bool PAIR = false, int BK = 32>
 __global__ __launch_bounds__(256) void gemm_nt_bf16_kernel(const Batch<GemmNtArgs> ba) {
-  const int bi = ba.find(blockIdx.x);
-  const GemmNtArgs &a = ba.sub[bi];
-  const unsigned block = blockIdx.x - ba.off[bi];  // inside the sub-launch, which starts at a multiple of 8
+  const GemmNtArgs a = ba.sub[blockIdx.z];  // a copy: fields in registers instead of loads inside the loops
   constexpr int LDS_K = BK + 8;   // padded K stride (elements)
   constexpr int KV = BK / 8;      // 16-byte vectors per tile row
   constexpr int NV = BM * KV / 256;  // vectors per thread and operand tile
@@ -226,7 +224,7 @@ __global__ __launch_bounds__(256) void gemm_nt_bf16_kernel(const Batch<GemmNtArg
   // Workgroups go round-robin over the 8 XCDs (each with its own L2).  The column tiles that share a
   // block of A rows are given consecutive slots on ONE XCD, so A is fetched into that L2 once.
   const int nt = (a.N + BN - 1) / BN;
-  const int xcd = block & 7, q = block >> 3;
+  const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
   const int m0 = ((q / nt) * 8 + xcd) * BM, n0 = (q % nt) * BN;
   if (m0 >= a.M) return;  // padding slots of the last group of 8 row tiles
   const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
@@ -384,9 +382,16 @@ __global__ __launch_bounds__(256) void gemm_nt_bf16_kernel(const Batch<GemmNtArg
 // and walk over row tiles, and the loads of the next A tile are in flight while the current one is
 // multiplied and stored.  WN = column panels per workgroup (4: N <= 256 with 64-row tiles, 2: N <= 128
 // with 128-row tiles); KS = number of 16-wide k-steps held (Kp <= 16 * KS).
+// Several products of a diagonal share a launch (each workgroup works on one of them); it is taken from 64 k rows in all on,
+// below that the tiled kernel is as fast or faster: 4 products of 21.9 k x 256 x 256 36 -> 32 us, 9.15 -> 8.73 ms per step
+// of 700 k vertices; 8 of 21.2 k (GCNII) 11.09 -> 10.92 ms.  Counting products of other widths, which don't share the
+// launch, cost an evaluation pass of 169 k vertices 1.12 against 1.09 ms.
 // GCNF: the instance for the GCN forward epilogue (bias + ReLU applied to the accumulators, see below).
 template <int WN, int KS, bool GCNF>
-__global__ __launch_bounds__(256, 2) void gemm_nt_bf16_ws_kernel(const GemmNtArgs a) {
+__global__ __launch_bounds__(256, 2) void gemm_nt_bf16_ws_kernel(const Batch<GemmNtArgs> ba) {
+  const GemmNtArgs a = ba.sub[blockIdx.z];  // a copy: fields in registers instead of loads inside the loops
+  const int blocks = a.ws_blocks;
+  if ((int)blockIdx.x >= blocks) return;
   constexpr int WR = 4 / WN, TM = 64 * WR;  // row groups, rows per tile
   constexpr int LDK = KS * 16 + 8;          // LDS row stride (elements): conflict-free 16-byte fragment reads
   constexpr int NV = TM * (KS * 2) / 256;   // 16-byte vectors of an A tile per thread
@@ -461,8 +466,8 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_bf16_ws_kernel(const GemmNtArg
   __syncthreads();
   float *patch = patches + wave * (16 * PS);
   int buf = 0;
-  for (; tile < n_tiles; tile += gridDim.x, buf ^= 1) {
-    const int next = tile + gridDim.x;
+  for (; tile < n_tiles; tile += blocks, buf ^= 1) {
+    const int next = tile + blocks;
     if (next < n_tiles) gload(next);  // in flight during the products and the stores below
     const bf16_t *At = As + buf * TM * LDK + (rg * 64) * LDK;
     const int m_wave = tile * TM + rg * 64;
@@ -541,26 +546,30 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_bf16_ws_kernel(const GemmNtArg
   }
 }
 
+typedef void (*nt_fn)(const Batch<GemmNtArgs>);
+struct WsKernel {
+  nt_fn fn;
+  int tm;  // rows per tile
+  size_t smem;
+};
 template <int WN, int KS, bool GCNF>
-static int launch_ws_k(const GemmNtArgs &a, hipStream_t s) {
+static WsKernel ws_instance() {
   constexpr int TM = 64 * (4 / WN), LDK = KS * 16 + 8;
-  const size_t smem = (size_t)2 * TM * LDK * sizeof(bf16_t) + (size_t)4 * 16 * 40 * sizeof(float);
-  static bool attr_done = false;
-  if (!attr_done) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_nt_bf16_ws_kernel<WN, KS, GCNF>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    attr_done = true;
-  }
-  const int n_tiles = (a.M + TM - 1) / TM;
-  const int blocks = n_tiles < 512 ? n_tiles : 512;  // two persistent workgroups per compute unit
-  hipLaunchKernelGGL((gemm_nt_bf16_ws_kernel<WN, KS, GCNF>), dim3(blocks), dim3(256), smem, s, a);
-  return (int)hipGetLastError();
+  constexpr size_t smem = (size_t)2 * TM * LDK * sizeof(bf16_t) + (size_t)4 * 16 * 40 * sizeof(float);
+  static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_nt_bf16_ws_kernel<WN, KS, GCNF>),
+                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  (void)set;
+  return WsKernel{gemm_nt_bf16_ws_kernel<WN, KS, GCNF>, TM, smem};
 }
-
 template <int WN, int KS>
-static int launch_ws(const GemmNtArgs &a, hipStream_t s) {
-  if (a.epilogue == EPI_FWD_GCN && a.vec_epi) return launch_ws_k<WN, KS, true>(a, s);
-  return launch_ws_k<WN, KS, false>(a, s);
+static WsKernel ws_for(const GemmNtArgs &a) {
+  return a.epilogue == EPI_FWD_GCN && a.vec_epi ? ws_instance<WN, KS, true>() : ws_instance<WN, KS, false>();
+}
+static WsKernel ws_kernel(const GemmNtArgs &a) {
+  if (a.N <= 128 && a.Kp <= 128) return ws_for<2, 8>(a);
+  if (a.N <= 128) return ws_for<2, 16>(a);
+  if (a.Kp <= 128) return ws_for<4, 8>(a);
+  return ws_for<4, 16>(a);
 }
 
 // ------------------------------------------------------------------------------------ bf16 TN
@@ -916,9 +925,7 @@ __device__ inline void epilogue_store4_f32(const GemmNtArgs &a, int m, int n, co
 // Q = 2: for products of many tiles; half the operand bytes per product through L2.
 template <int Q, int EPI>
 __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const Batch<GemmNtArgs> ba) {
-  const int bi = ba.find(blockIdx.x);
-  const GemmNtArgs &a = ba.sub[bi];
-  const unsigned block = blockIdx.x - ba.off[bi], blocks = ba.off[bi + 1] - ba.off[bi];  // inside the sub-launch; multiples of 8
+  const GemmNtArgs a = ba.sub[blockIdx.z];  // a copy: fields in registers instead of loads inside the loops
   constexpr int T = 32 * Q;          // rows and columns of a workgroup's tile
   constexpr int D = Q == 1 ? 12 : 4; // groups of 16 reduction elements in flight per wave
   constexpr int PS = 16 * Q + 4;     // padded row stride (floats) of the result patch
@@ -930,8 +937,9 @@ __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const Batch<GemmNtArgs
   // Workgroups go round-robin over the 8 XCDs; each takes a contiguous run of tiles that share a block of A rows (row
   // tiles outside) or a block of Bt rows (column tiles outside), whichever moves fewer bytes into the eight L2s.
   const int mt = (a.M + T - 1) / T, nt = (a.N + T - 1) / T;
-  const int work = (block & 7) * (blocks >> 3) + (block >> 3);
-  if (work >= mt * nt) return;
+  const int run = (mt * nt + 7) >> 3;  // tiles per XCD
+  const int work = (blockIdx.x & 7) * run + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= run || work >= mt * nt) return;
   const bool cols_outside = a.M < a.N;
   const int m0 = (cols_outside ? work % mt : work / nt) * T + (wave >> 1) * (16 * Q);
   const int n0 = (cols_outside ? work / mt : work % nt) * T + (wave & 1) * (16 * Q);
@@ -1277,40 +1285,38 @@ bool vec_ok(const void *p, int ld, int mult) { return (reinterpret_cast<uintptr_
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 static bool pair_ok(const void *p, int ld) { return (reinterpret_cast<uintptr_t>(p) & 7u) == 0 && ld % 2 == 0; }
 
-typedef void (*nt_fn)(const Batch<GemmNtArgs>);
+static bool nt_vec(const GemmNtArgs &a) { return a.a_dtype == DT_BF16 && vec_ok(a.A, a.lda, 8) && a.lda >= a.Kp; }
+static bool ws_ok(const GemmNtArgs &a) { return nt_vec(a) && vec_ok(a.Bt, a.ldb, 8) && a.Kp <= 256 && a.N <= 256; }
 
-// the kernel of one bf16 product; nullptr: the persistent weight-stationary kernel, which runs on its own
+// the tiled kernel of one bf16 product
 static nt_fn nt_bf16_fn(const GemmNtArgs &a) {
   const int mt = (a.M + BM - 1) / BM, ntiles = (a.N + BN - 1) / BN;
-  const bool vec = a.a_dtype == DT_BF16 && vec_ok(a.A, a.lda, 8) && a.lda >= a.Kp;
   if (a.a_dtype == DT_F32) return pair_ok(a.A, a.lda) ? gemm_nt_bf16_kernel<float, false, true> : gemm_nt_bf16_kernel<float, false>;
-  // long operands: persistent weight-stationary kernel (needs a few row tiles per workgroup to pay
-  // for loading its panel of Bt into registers)
-  if (vec && vec_ok(a.Bt, a.ldb, 8) && a.Kp <= 256 && a.N <= 256 && a.M >= a.ws_min_rows) return nullptr;
-  // short operands: every workgroup is resident at once, the product is its chain of K steps
-  if (vec && a.Kp >= 128 && (long long)mt * ntiles <= 1024) return gemm_nt_bf16_kernel<bf16_t, true, false, 64>;
-  return vec ? gemm_nt_bf16_kernel<bf16_t, true> : gemm_nt_bf16_kernel<bf16_t, false>;
-}
-
-static int launch_ws_any(const GemmNtArgs &a, hipStream_t s) {
-  if (a.N <= 128 && a.Kp <= 128) return launch_ws<2, 8>(a, s);
-  if (a.N <= 128) return launch_ws<2, 16>(a, s);
-  if (a.Kp <= 128) return launch_ws<4, 8>(a, s);
-  return launch_ws<4, 16>(a, s);
+  if (!nt_vec(a)) return gemm_nt_bf16_kernel<bf16_t, false>;
+  // short operands: the product is its chain of K steps
+  return a.Kp >= 128 && (long long)mt * ntiles <= 1024 ? gemm_nt_bf16_kernel<bf16_t, true, false, 64> : gemm_nt_bf16_kernel<bf16_t, true>;
 }
 
 int launch_gemm_nt(const GemmNtArgs *a_in, int n, int compute_dtype, hipStream_t s) {
   if (n > kBatch) return hipErrorInvalidValue;
   GemmNtArgs args[kBatch];
   nt_fn fn[kBatch];
-  unsigned gx[kBatch];
-  long long tiles64 = 0;  // fp32: 64 x 64 tiles of all products
+  unsigned gx[kBatch];  // workgroups; of a persistent kernel: tiles
+  int tm[kBatch];       // rows per tile of a persistent kernel, else 0
+  size_t smem[kBatch];
+  // fp32: 64 x 64 tiles of all products; bf16: rows of those that would share a launch of the weight-stationary kernel
+  long long tiles64 = 0, ws_rows[2][2] = {};
   for (int i = 0; i < n; ++i)
-    if (a_in[i].M > 0 && a_in[i].N > 0) tiles64 += (long long)((a_in[i].M + 63) / 64) * ((a_in[i].N + 63) / 64);
+    if (a_in[i].M > 0 && a_in[i].N > 0) {
+      tiles64 += (long long)((a_in[i].M + 63) / 64) * ((a_in[i].N + 63) / 64);
+      if (ws_ok(a_in[i])) ws_rows[a_in[i].N > 128][a_in[i].Kp > 128] += a_in[i].M;
+    }
   for (int i = 0; i < n; ++i) {
     GemmNtArgs &a = args[i] = a_in[i];
     fn[i] = nullptr;
     gx[i] = 0;
+    tm[i] = 0;
+    smem[i] = 0;
     if (a.M <= 0 || a.N <= 0) continue;
     if (compute_dtype != DT_BF16) {
       if (a.a_dtype != DT_F32) return hipErrorInvalidValue;
@@ -1335,28 +1341,49 @@ int launch_gemm_nt(const GemmNtArgs *a_in, int n, int compute_dtype, hipStream_t
     // drawing inside the epilogues of the bf16 kernels costs them registers they do not have (the forward products of a
     // 233 k vertex stage went from 0.68 to 2.65 ms with dropout off): a pass of its own behind the product
     a.drop = LnDropout{};
-    fn[i] = nt_bf16_fn(a);
-    if (fn[i] == nullptr) {
-      const int e = launch_ws_any(a, s);
-      if (e != 0) return e;
-      continue;
+    if (ws_ok(a) && ws_rows[a.N > 128][a.Kp > 128] >= a.ws_min_rows) {
+      const WsKernel w = ws_kernel(a);
+      fn[i] = w.fn;
+      tm[i] = w.tm;
+      smem[i] = w.smem;
+      gx[i] = (unsigned)((a.M + w.tm - 1) / w.tm);
+    } else {
+      fn[i] = nt_bf16_fn(a);
+      gx[i] = (unsigned)(((a.M + BM - 1) / BM + 7) / 8 * 8 * ((a.N + BN - 1) / BN));
     }
-    gx[i] = (unsigned)(((a.M + BM - 1) / BM + 7) / 8 * 8 * ((a.N + BN - 1) / BN));
   }
   bool done[kBatch] = {};
   for (int i = 0; i < n; ++i) {
     if (done[i] || gx[i] == 0) continue;
     Batch<GemmNtArgs> b;
-    b.n = 0;
-    b.off[0] = 0;
+    int of[kBatch];
+    unsigned m = 0, width = 0;
     for (int j = i; j < n; ++j) {
       if (done[j] || gx[j] == 0 || fn[j] != fn[i]) continue;
       done[j] = true;
-      b.sub[b.n] = args[j];
-      b.off[b.n + 1] = b.off[b.n] + gx[j];
-      ++b.n;
+      of[m] = j;
+      b.sub[m++] = args[j];
     }
-    hipLaunchKernelGGL(fn[i], dim3(b.off[b.n]), dim3(256), 0, s, b);
+    // a persistent kernel gets two workgroups per compute unit, each with as many row tiles of one product as that takes
+    unsigned per = 1;
+    if (tm[i] > 0) {
+      unsigned tiles = 0;
+      for (unsigned q = 0; q < m; ++q) tiles += gx[of[q]];
+      per = std::max(1u, tiles / 512u);
+      auto need = [&](unsigned p) {
+        unsigned w = 0;
+        for (unsigned q = 0; q < m; ++q) w += (gx[of[q]] + p - 1) / p;
+        return w;
+      };
+      while (need(per) > 512u) ++per;  // at most eight products: ends at the latest with one workgroup each
+    }
+    for (unsigned q = 0; q < m; ++q) {
+      const unsigned w = (gx[of[q]] + per - 1) / per;
+      b.sub[q].ws_blocks = (int32_t)w;
+      width = std::max(width, w);
+    }
+    if (m > 1) width = (width + 7) / 8 * 8;  // workgroup i of every product on XCD i % 8
+    hipLaunchKernelGGL(fn[i], dim3(width, 1, m), dim3(256), smem[i], s, b);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
   }

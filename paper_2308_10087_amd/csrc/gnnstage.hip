@@ -399,8 +399,8 @@ struct Shape {
   bool res() const { return variant == GNNSTAGE_RESGCN; }
   // Cells (chunk, layer) of a pass that run side by side.  One where a launch fills the chip for long anyway: an
   // aggregation over 2 M entries takes 100 us and up, and every further cell needs scratch of its own.  One with dense blocks
-  // too: the sums of their blocks, 37 MB for a chunk of 4 M entries, are read back from a cache only right behind the kernel
-  // that wrote them (80 k vertices, 16 M entries, 4 chunks: 4.09 ms per step cell by cell, 4.23 four at a time).
+  // too, whose partial tiles are most of it (37 MB for a chunk of 4 M entries; 80 k vertices, 16 M entries, 4 chunks: 4.22 ms
+  // per step cell by cell and four at a time).
   int cells_at_once(bool dense_blocks) const {
     if (!defer_wgrad() || dense_blocks || nnz / K >= 2000000) return 1;
     return std::min(kBatch, std::min(K, L));
@@ -608,7 +608,7 @@ Layout make_layout(const Shape &s, const HostDir &hf, const HostDir &hb, bool ra
   }
   if (s.res()) {
     l.res_dr = w.take(l.row_stride * elt * B);
-    l.ln_partial = w.take(sizeof(float) * l.ln_stride);
+    l.ln_partial = w.take(sizeof(float) * l.ln_stride * B);
   }
   for (int j = 0; j < s.L && !s.res(); ++j) {
     if (s.tf[j]) {
@@ -1025,6 +1025,17 @@ const char *level_rows(const gnnstage *st, const std::vector<void *> &level, int
   return static_cast<const char *>(level[(size_t)j]) + (size_t)row0 * st->s.dims[(size_t)j] * st->level_elt(j);
 }
 
+// ResGCN+: LayerNorm, ReLU, dropout of rows [row0, row0 + M) of a level, and the way back (dr: gradient of the activated rows,
+// res: rows [M x ld_{j+1}] of the residual branch or NULL)
+LnArgs ln_args(const gnnstage *st, const std::vector<void *> &level, int j, int64_t row0, int64_t M, void *out, int out_dtype, int out_ld) {
+  return LnArgs{level_rows(st, level, j, row0), st->level_dtype(j), st->s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, M, st->s.dims[j], out, out_dtype, out_ld,
+                st->dropout(j, row0), 0};
+}
+LnBackArgs ln_back_args(const gnnstage *st, const LnArgs &f, int j, int slot, const void *dr, const void *res) {
+  return LnBackArgs{f, dr, st->cdtype(), st->s.ld[j], res, st->cdtype(), st->s.ld[j + 1], st->at<float>(st->lay.ln_partial) + (size_t)slot * st->lay.ln_stride,
+                    st->d_ln_g[j], st->d_ln_b[j]};
+}
+
 // What a pass needs before its first chunk: staged weights; ResGCN+: Rh = f(hist[j]), the activated historical rows; the
 // transformed historical rows of transform-first layers (constants of the pass).
 int begin_forward(gnnstage *st, hipStream_t stream) {
@@ -1052,8 +1063,8 @@ int begin_forward(gnnstage *st, hipStream_t stream) {
   for (int j = 0; j < s.L; ++j) {
     if (s.res()) {
       Timed t(st, stream, 1, j);
-      HIP_TRY(st, launch_ln_relu(st->hist[j], st->level_dtype(j), s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, s.n, s.dims[j],
-                                 st->at<char>(st->lay.Th[j]), cd, s.ld[j], st->dropout(j, 0), stream));
+      const LnArgs a = ln_args(st, st->hist, j, 0, s.n, st->at<char>(st->lay.Th[j]), cd, s.ld[j]);
+      HIP_TRY(st, launch_ln_relu(&a, 1, stream));
     } else if (s.tf[j]) {
       Timed t(st, stream, 1, j);
       GemmNtArgs g = nt_args(st, st->hist[j], st->level_dtype(j), s.dims[j], st->lay.Wt[j], s.ld[j], s.n, s.dims[j + 1], s.dims[j]);
@@ -1074,16 +1085,15 @@ int forward_cells(gnnstage *st, const Cell *cells, int n, hipStream_t stream) {
   const int cd = st->cdtype();
   const size_t celt = s.elt();
   GemmNtArgs nt[kBatch];
-  int n_nt = 0;
+  LnArgs ln[kBatch];
+  int n_nt = 0, n_ln = 0;
   for (int i = 0; i < n; ++i) {
     const Cell &c = cells[i];
     const int j = c.j;
     const int64_t row0 = cell_row0(st, c.k), M = cell_rows(st, c.k);
     const bool shared = st->hist[j] == st->cur[j];  // the level never changes: one table of its rows serves both
     if (s.res() && !shared) {
-      Timed t(st, stream, 1, j);
-      HIP_TRY(st, launch_ln_relu(level_rows(st, st->cur, j, row0), st->level_dtype(j), s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, M, s.dims[j],
-                                 st->at<char>(st->lay.Tc[j]) + (size_t)row0 * s.ld[j] * celt, cd, s.ld[j], st->dropout(j, row0), stream));
+      ln[n_ln++] = ln_args(st, st->cur, j, row0, M, st->at<char>(st->lay.Tc[j]) + (size_t)row0 * s.ld[j] * celt, cd, s.ld[j]);
     } else if (s.tf[j] && !shared) {  // the chunk's current rows
       GemmNtArgs &g = nt[n_nt++] = nt_args(st, level_rows(st, st->cur, j, row0), st->level_dtype(j), s.dims[j], st->lay.Wt[j], s.ld[j], M, s.dims[j + 1], s.dims[j]);
       nt_out(g, st->at<char>(st->lay.Tc[j]) + (size_t)row0 * s.ld[j + 1] * celt, cd, s.ld[j + 1]);
@@ -1092,9 +1102,10 @@ int forward_cells(gnnstage *st, const Cell *cells, int n, hipStream_t stream) {
       nt_out(g, st->at<float>(st->lay.self_fwd) + (size_t)c.slot * st->lay.self_stride, DT_F32, s.ld[j + 1]);
     }
   }
-  if (n_nt > 0) {
+  if (n_nt + n_ln > 0) {
     Timed t(st, stream, 1, cells[0].j);
     HIP_TRY(st, launch_gemm_nt(nt, n_nt, cd, stream));
+    HIP_TRY(st, launch_ln_relu(ln, n_ln, stream));
   }
   CellSpmm sp[kBatch];
   for (int i = 0; i < n; ++i) {
@@ -1291,15 +1302,14 @@ int res_backward_finish(gnnstage *st, hipStream_t stream) {
       a.epilogue = SPMM_PLAIN;
     }
     HIP_TRY(st, run_spmm(st, sp, n, stream, 2, cells[(size_t)first].j));
+    // no more cells at once than layers, and the layers of a chunk follow each other: no parameter comes twice
+    LnBackArgs ln[kBatch];
     for (int i = 0; i < n; ++i) {
       const Cell &c = cells[(size_t)(first + i)];
-      const int j = c.j;
-      const int64_t row0 = cell_row0(st, c.k);
-      Timed t(st, stream, 4, j);
-      HIP_TRY(st, launch_ln_relu_backward(level_rows(st, st->hist, j, row0), st->level_dtype(j), s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, sp[i].l.a.out, cd,
-                                          s.ld[j], nullptr, cd, 0, cell_rows(st, c.k), s.dims[j], nullptr, cd, 0, st->at<float>(st->lay.ln_partial),
-                                          st->d_ln_g[j], st->d_ln_b[j], st->dropout(j, row0), stream));
+      ln[i] = ln_back_args(st, ln_args(st, st->hist, c.j, cell_row0(st, c.k), cell_rows(st, c.k), nullptr, cd, 0), c.j, i, sp[i].l.a.out, nullptr);
     }
+    Timed t(st, stream, 4, cells[(size_t)first].j);
+    HIP_TRY(st, launch_ln_relu_backward(ln, n, stream));
     return (int)GNNSTAGE_OK;
   });
 }
@@ -1436,6 +1446,8 @@ int backward_cells(gnnstage *st, const Cell *cells, int n, bool whole_pass, hipS
   }
   if (n_sp > 0) HIP_TRY(st, run_spmm(st, sp, n_sp, stream, 2, cells[of[0]].j));
   // ---- behind them
+  LnBackArgs ln[kBatch];
+  int n_ln = 0;
   n_nt = 0;
   for (int x = 0; x < n_sp; ++x) {
     const Cell &c = cells[of[x]];
@@ -1443,7 +1455,6 @@ int backward_cells(gnnstage *st, const Cell *cells, int n, bool whole_pass, hipS
     const int64_t row0 = cell_row0(st, c.k), M = cell_rows(st, c.k);
     const void *dT = sp[x].l.a.out;
     if (s.res()) {  // back through ReLU and LayerNorm of the chunk's own (current) rows, plus the residual branch
-      Timed t(st, stream, 4, j);
       void *out = nullptr;
       int out_ld = 0;
       if (j > 0) {
@@ -1453,9 +1464,7 @@ int backward_cells(gnnstage *st, const Cell *cells, int n, bool whole_pass, hipS
         out = static_cast<char *>(st->grad_in) + (size_t)row0 * s.dims[0] * st->level_elt(0);
         out_ld = s.dims[0];
       }
-      HIP_TRY(st, launch_ln_relu_backward(level_rows(st, st->cur, j, row0), st->level_dtype(j), s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, dT, cd, s.ld[j],
-                                          dY_rows(st, c.k, j), cd, s.ld[j + 1], M, s.dims[j], out, st->level_dtype(j), out_ld,
-                                          st->at<float>(st->lay.ln_partial), st->d_ln_g[j], st->d_ln_b[j], st->dropout(j, row0), stream));
+      ln[n_ln++] = ln_back_args(st, ln_args(st, st->cur, j, row0, M, out, st->level_dtype(j), out_ld), j, c.slot, dT, dY_rows(st, c.k, j));
       continue;
     }
     if (!s.tf[j]) continue;
@@ -1486,6 +1495,10 @@ int backward_cells(gnnstage *st, const Cell *cells, int n, bool whole_pass, hipS
     } else {
       nt_out(g, static_cast<char *>(st->grad_in) + (size_t)row0 * s.dims[0] * st->level_elt(0), st->level_dtype(0), s.dims[0]);
     }
+  }
+  if (n_ln > 0) {
+    Timed t(st, stream, 4, cells[0].j);
+    HIP_TRY(st, launch_ln_relu_backward(ln, n_ln, stream));
   }
   if (n_nt > 0) {
     Timed t(st, stream, 3, cells[0].j);

@@ -29,11 +29,19 @@ __device__ inline float wave_sum(float v) {
 
 // NI = columns per lane (lane, lane + 64, ...): the row lives in registers between the passes
 template <int NI>
-__global__ __launch_bounds__(256) void ln_relu_kernel(const void *x, int x_dtype, int x_ld, const float *gamma, const float *beta,
-                                                      float eps, int64_t M, int d, void *out, int out_dtype, int out_ld,
-                                                      const LnDropout dp) {
+__global__ __launch_bounds__(256) void ln_relu_kernel(const Batch<LnArgs> ba) {
+  const LnArgs a = ba.sub[blockIdx.z];
+  const unsigned block = blockIdx.x, blocks = a.blocks;
+  if (block >= blocks) return;
+  const void *x = a.x;
+  void *out = a.out;
+  const float *gamma = a.gamma, *beta = a.beta;
+  const float eps = a.eps;
+  const int64_t M = a.M;
+  const int x_dtype = a.x_dtype, x_ld = a.x_ld, d = a.d, out_dtype = a.out_dtype, out_ld = a.out_ld;
+  const LnDropout dp = a.drop;
   const int lane = threadIdx.x & 63;
-  const int64_t w0 = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), nw = (int64_t)gridDim.x * 4;
+  const int64_t w0 = (int64_t)block * 4 + (threadIdx.x >> 6), nw = (int64_t)blocks * 4;
   for (int64_t r = w0; r < M; r += nw) {
     float v[NI];
     float sum = 0.f;
@@ -72,14 +80,23 @@ __global__ __launch_bounds__(256) void ln_relu_kernel(const void *x, int x_dtype
 // four wavefronts of a workgroup in LDS and go to partial[workgroup][0][c] (gamma) and partial[workgroup][1][c]
 // (beta); ln_param_reduce_kernel adds those in a fixed order.
 template <int NI>
-__global__ __launch_bounds__(256) void ln_relu_backward_kernel(const void *x, int x_dtype, int x_ld, const float *gamma,
-                                                               const float *beta, float eps, const void *dr, int dr_dtype, int dr_ld,
-                                                               const void *res, int res_dtype, int res_ld, int64_t M, int d,
-                                                               void *out, int out_dtype, int out_ld, float *partial,
-                                                               const LnDropout dp) {
+__global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBackArgs> ba) {
+  const LnBackArgs b = ba.sub[blockIdx.z];
+  const LnArgs &a = b.f;
+  const unsigned block = blockIdx.x, blocks = a.blocks;
+  if (block >= blocks) return;
+  const void *x = a.x, *dr = b.dr, *res = b.res;
+  void *out = a.out;
+  const float *gamma = a.gamma, *beta = a.beta;
+  float *partial = b.partial;
+  const float eps = a.eps;
+  const int64_t M = a.M;
+  const int x_dtype = a.x_dtype, x_ld = a.x_ld, d = a.d, out_dtype = a.out_dtype, out_ld = a.out_ld;
+  const int dr_dtype = b.dr_dtype, dr_ld = b.dr_ld, res_dtype = b.res_dtype, res_ld = b.res_ld;
+  const LnDropout dp = a.drop;
   __shared__ float red[3][2][NI * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t w0 = (int64_t)blockIdx.x * 4 + wave, nw = (int64_t)gridDim.x * 4;
+  const int64_t w0 = (int64_t)block * 4 + (threadIdx.x >> 6), nw = (int64_t)blocks * 4;
   float dg[NI], db[NI], gam[NI], bet[NI];
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
@@ -153,8 +170,8 @@ __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const void *x, in
     for (int i = 0; i < NI; ++i) {
       const int c = lane + 64 * i;
       if (c < d) {
-        partial[((size_t)blockIdx.x * 2 + 0) * d + c] = ((dg[i] + red[0][0][c]) + red[1][0][c]) + red[2][0][c];
-        partial[((size_t)blockIdx.x * 2 + 1) * d + c] = ((db[i] + red[0][1][c]) + red[1][1][c]) + red[2][1][c];
+        partial[((size_t)block * 2 + 0) * d + c] = ((dg[i] + red[0][0][c]) + red[1][0][c]) + red[2][0][c];
+        partial[((size_t)block * 2 + 1) * d + c] = ((db[i] + red[0][1][c]) + red[1][1][c]) + red[2][1][c];
       }
     }
   }
@@ -174,11 +191,20 @@ __device__ inline float group_sum(float v) {
 }
 
 template <int LPR>
-__global__ __launch_bounds__(256) void ln_relu_vec_kernel(const bf16_t *x, int x_ld, const float *gamma, const float *beta, float eps,
-                                                          int64_t M, bf16_t *out, int out_ld, const LnDropout dp) {
+__global__ __launch_bounds__(256) void ln_relu_vec_kernel(const Batch<LnArgs> ba) {
+  const LnArgs a = ba.sub[blockIdx.z];
+  const unsigned block = blockIdx.x, blocks = a.blocks;
+  if (block >= blocks) return;
+  const bf16_t *x = static_cast<const bf16_t *>(a.x);
+  bf16_t *out = static_cast<bf16_t *>(a.out);
+  const float *gamma = a.gamma, *beta = a.beta;
+  const float eps = a.eps;
+  const int64_t M = a.M;
+  const int x_ld = a.x_ld, out_ld = a.out_ld;
+  const LnDropout dp = a.drop;
   constexpr int RPW = 64 / LPR, d = LPR * 8;
   const int lane = threadIdx.x & 63, sub = lane % LPR, rw = lane / LPR;
-  const int64_t w0 = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), nw = (int64_t)gridDim.x * 4;
+  const int64_t w0 = (int64_t)block * 4 + (threadIdx.x >> 6), nw = (int64_t)blocks * 4;
   float gam[8], bet[8];
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
@@ -214,14 +240,23 @@ __global__ __launch_bounds__(256) void ln_relu_vec_kernel(const bf16_t *x, int x
 }
 
 template <int LPR>
-__global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const bf16_t *x, int x_ld, const float *gamma, const float *beta,
-                                                                   float eps, const bf16_t *dr, int dr_ld, const bf16_t *res, int res_ld,
-                                                                   int64_t M, bf16_t *out, int out_ld, float *partial,
-                                                                   const LnDropout dp) {
+__global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<LnBackArgs> ba) {
+  const LnBackArgs b = ba.sub[blockIdx.z];
+  const LnArgs &a = b.f;
+  const unsigned block = blockIdx.x, blocks = a.blocks;
+  if (block >= blocks) return;
+  const bf16_t *x = static_cast<const bf16_t *>(a.x), *dr = static_cast<const bf16_t *>(b.dr), *res = static_cast<const bf16_t *>(b.res);
+  bf16_t *out = static_cast<bf16_t *>(a.out);
+  const float *gamma = a.gamma, *beta = a.beta;
+  float *partial = b.partial;
+  const float eps = a.eps;
+  const int64_t M = a.M;
+  const int x_ld = a.x_ld, out_ld = a.out_ld, dr_ld = b.dr_ld, res_ld = b.res_ld;
+  const LnDropout dp = a.drop;
   constexpr int RPW = 64 / LPR, d = LPR * 8;
   __shared__ float red[3][2][LPR * 8];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane % LPR, rw = lane / LPR;
-  const int64_t w0 = (int64_t)blockIdx.x * 4 + wave, nw = (int64_t)gridDim.x * 4;
+  const int64_t w0 = (int64_t)block * 4 + (threadIdx.x >> 6), nw = (int64_t)blocks * 4;
   float gam[8], bet[8], dg[8], db[8];
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
@@ -298,8 +333,8 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const bf16_t 
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       const int c = sub * 8 + t;
-      partial[((size_t)blockIdx.x * 2 + 0) * d + c] = ((dg[t] + red[0][0][c]) + red[1][0][c]) + red[2][0][c];
-      partial[((size_t)blockIdx.x * 2 + 1) * d + c] = ((db[t] + red[0][1][c]) + red[1][1][c]) + red[2][1][c];
+      partial[((size_t)block * 2 + 0) * d + c] = ((dg[t] + red[0][0][c]) + red[1][0][c]) + red[2][0][c];
+      partial[((size_t)block * 2 + 1) * d + c] = ((db[t] + red[0][1][c]) + red[1][1][c]) + red[2][1][c];
     }
   }
 }
@@ -310,10 +345,21 @@ inline int vec_lanes(int d, int dtype, const void *p, int ld) {
   return (d == 64 || d == 128 || d == 256 || d == 512) ? d / 8 : 0;
 }
 
-__global__ __launch_bounds__(1024) void ln_param_reduce_kernel(const float *partial, int n_parts, int d, float *dgamma, float *dbeta) {
+// n_parts: the partial rows of a sub-launch are its workgroups in the launch before
+struct LnReduceArgs {
+  const float *partial;
+  int32_t n_parts, d;
+  float *dgamma, *dbeta;
+};
+__global__ __launch_bounds__(1024) void ln_param_reduce_kernel(const Batch<LnReduceArgs> ba) {
+  const LnReduceArgs &a = ba.sub[blockIdx.z];
+  const unsigned block = blockIdx.x;
+  const float *partial = a.partial;
+  float *dgamma = a.dgamma, *dbeta = a.dbeta;
+  const int n_parts = a.n_parts, d = a.d;
   __shared__ float red[16][64];
   const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
-  const int idx = blockIdx.x * 64 + lane;  // position in [gamma sums | beta sums]
+  const int idx = block * 64 + lane;  // position in [gamma sums | beta sums]
   float s = 0.f;
   if (idx < 2 * d) {
 #pragma unroll 8
@@ -347,81 +393,97 @@ int waves_for(int64_t M, int max_waves) {
 
 }  // namespace
 
-int launch_ln_relu(const void *x, int x_dtype, int x_ld, const float *gamma, const float *beta, float eps, int64_t M, int d, void *out,
-                   int out_dtype, int out_ld, const LnDropout &dp, hipStream_t s) {
-  if (M <= 0) return hipSuccess;
-  if (d > kLnMaxWidth || out_ld > kLnMaxWidth) return hipErrorInvalidValue;
-  const int lpr = (out_dtype == DT_BF16 && out_ld == d && vec_lanes(d, out_dtype, out, out_ld)) ? vec_lanes(d, x_dtype, x, x_ld) : 0;
-  if (lpr) {
-    const int rpw = 64 / lpr;
-    dim3 vgrid((unsigned)(waves_for((M + rpw - 1) / rpw, 16384) / 4));
-    const bf16_t *xb = static_cast<const bf16_t *>(x);
-    bf16_t *ob = static_cast<bf16_t *>(out);
-#define LN_FWD_VEC(L) hipLaunchKernelGGL(ln_relu_vec_kernel<L>, vgrid, dim3(256), 0, s, xb, x_ld, gamma, beta, eps, M, ob, out_ld, dp)
-    if (lpr == 8) LN_FWD_VEC(8);
-    else if (lpr == 16) LN_FWD_VEC(16);
-    else if (lpr == 32) LN_FWD_VEC(32);
-    else LN_FWD_VEC(64);
-#undef LN_FWD_VEC
-    return (int)hipGetLastError();
+static void set_blocks(LnArgs &a, unsigned g) { a.blocks = (int32_t)g; }
+static void set_blocks(LnBackArgs &a, unsigned g) { a.f.blocks = (int32_t)g; }
+static void set_blocks(LnReduceArgs &, unsigned) {}
+// Runs sub-launches [0, n) (kernel fn[i], gx[i] workgroups; 0: nothing to do), those of one kernel together.
+template <typename A, typename Fn>
+static int launch_merged(const A *const *a, const Fn *fn, const unsigned *gx, int n, unsigned threads, hipStream_t s) {
+  bool done[kBatch] = {};
+  for (int i = 0; i < n; ++i) {
+    if (done[i] || gx[i] == 0) continue;
+    Batch<A> b;
+    unsigned m = 0, width = 0;
+    for (int j = i; j < n; ++j) {
+      if (done[j] || gx[j] == 0 || fn[j] != fn[i]) continue;
+      done[j] = true;
+      b.sub[m] = *a[j];
+      set_blocks(b.sub[m++], gx[j]);
+      width = std::max(width, gx[j]);
+    }
+    hipLaunchKernelGGL(fn[i], dim3(width, 1, m), dim3(threads), 0, s, b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
   }
-  const int ni = (std::max(d, out_ld) + 63) / 64;
-  dim3 grid((unsigned)(waves_for(M, 16384) / 4));
-#define LN_FWD(NI) hipLaunchKernelGGL(ln_relu_kernel<NI>, grid, dim3(256), 0, s, x, x_dtype, x_ld, gamma, beta, eps, M, d, out, out_dtype, out_ld, dp)
-  if (ni <= 1) LN_FWD(1);
-  else if (ni <= 2) LN_FWD(2);
-  else if (ni <= 4) LN_FWD(4);
-  else if (ni <= 8) LN_FWD(8);
-  else LN_FWD(16);
-#undef LN_FWD
-  return (int)hipGetLastError();
+  return hipSuccess;
 }
 
-int launch_ln_relu_backward(const void *x, int x_dtype, int x_ld, const float *gamma, const float *beta, float eps, const void *dr,
-                            int dr_dtype, int dr_ld, const void *res, int res_dtype, int res_ld, int64_t M, int d, void *out,
-                            int out_dtype, int out_ld, float *partial, float *dgamma, float *dbeta, const LnDropout &dp,
-                            hipStream_t s) {
-  if (M <= 0) return hipSuccess;
-  if (d > kLnMaxWidth || (out && out_ld > kLnMaxWidth)) return hipErrorInvalidValue;
-  int lpr = vec_lanes(d, x_dtype, x, x_ld);
-  if (lpr && (!vec_lanes(d, dr_dtype, dr, dr_ld) || (res && !vec_lanes(d, res_dtype, res, res_ld)) ||
-              (out && !vec_lanes(d, out_dtype, out, out_ld))))
-    lpr = 0;
-  if (lpr) {
-    const int rpw = 64 / lpr;
-    const int vwaves = waves_for((M + rpw - 1) / rpw, kLnMaxWaves);
-    dim3 vgrid((unsigned)(vwaves / 4));
-    const bf16_t *xb = static_cast<const bf16_t *>(x), *db = static_cast<const bf16_t *>(dr), *rb = static_cast<const bf16_t *>(res);
-    bf16_t *ob = static_cast<bf16_t *>(out);
-#define LN_BWD_VEC(L)                                                                                                          \
-  hipLaunchKernelGGL(ln_relu_backward_vec_kernel<L>, vgrid, dim3(256), 0, s, xb, x_ld, gamma, beta, eps, db, dr_ld, rb, res_ld, M, ob, \
-                     out_ld, partial, dp)
-    if (lpr == 8) LN_BWD_VEC(8);
-    else if (lpr == 16) LN_BWD_VEC(16);
-    else if (lpr == 32) LN_BWD_VEC(32);
-    else LN_BWD_VEC(64);
-#undef LN_BWD_VEC
-    hipError_t ev = hipGetLastError();
-    if (ev != hipSuccess) return (int)ev;
-    hipLaunchKernelGGL(ln_param_reduce_kernel, dim3((unsigned)((2 * d + 63) / 64)), dim3(1024), 0, s, partial, vwaves / 4, d, dgamma, dbeta);
-    return (int)hipGetLastError();
+int launch_ln_relu(const LnArgs *l, int n, hipStream_t s) {
+  if (n > kBatch) return hipErrorInvalidValue;
+  typedef void (*fn_t)(const Batch<LnArgs>);
+  const LnArgs *ptr[kBatch];
+  fn_t fn[kBatch];
+  unsigned gx[kBatch];
+  for (int i = 0; i < n; ++i) {
+    const LnArgs &a = l[i];
+    ptr[i] = &a;
+    fn[i] = nullptr;
+    gx[i] = 0;
+    if (a.M <= 0) continue;
+    if (a.d > kLnMaxWidth || a.out_ld > kLnMaxWidth) return hipErrorInvalidValue;
+    const int lpr = (a.out_dtype == DT_BF16 && a.out_ld == a.d && vec_lanes(a.d, a.out_dtype, a.out, a.out_ld)) ? vec_lanes(a.d, a.x_dtype, a.x, a.x_ld) : 0;
+    if (lpr) {
+      const int rpw = 64 / lpr;
+      gx[i] = (unsigned)(waves_for((a.M + rpw - 1) / rpw, 16384) / 4);
+      fn[i] = lpr == 8 ? ln_relu_vec_kernel<8> : lpr == 16 ? ln_relu_vec_kernel<16> : lpr == 32 ? ln_relu_vec_kernel<32> : ln_relu_vec_kernel<64>;
+    } else {
+      const int ni = (std::max(a.d, a.out_ld) + 63) / 64;
+      gx[i] = (unsigned)(waves_for(a.M, 16384) / 4);
+      fn[i] = ni <= 1 ? ln_relu_kernel<1> : ni <= 2 ? ln_relu_kernel<2> : ni <= 4 ? ln_relu_kernel<4> : ni <= 8 ? ln_relu_kernel<8> : ln_relu_kernel<16>;
+    }
   }
-  const int ni = (std::max(d, out ? out_ld : d) + 63) / 64;
-  const int waves = waves_for(M, kLnMaxWaves);
-  dim3 grid((unsigned)(waves / 4));
-#define LN_BWD(NI)                                                                                                              \
-  hipLaunchKernelGGL(ln_relu_backward_kernel<NI>, grid, dim3(256), 0, s, x, x_dtype, x_ld, gamma, beta, eps, dr, dr_dtype, dr_ld, res, \
-                     res_dtype, res_ld, M, d, out, out_dtype, out_ld, partial, dp)
-  if (ni <= 1) LN_BWD(1);
-  else if (ni <= 2) LN_BWD(2);
-  else if (ni <= 4) LN_BWD(4);
-  else if (ni <= 8) LN_BWD(8);
-  else LN_BWD(16);
-#undef LN_BWD
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return (int)e;
-  hipLaunchKernelGGL(ln_param_reduce_kernel, dim3((unsigned)((2 * d + 63) / 64)), dim3(1024), 0, s, partial, waves / 4, d, dgamma, dbeta);
-  return (int)hipGetLastError();
+  return launch_merged(ptr, fn, gx, n, 256, s);
+}
+
+int launch_ln_relu_backward(const LnBackArgs *l, int n, hipStream_t s) {
+  if (n > kBatch) return hipErrorInvalidValue;
+  typedef void (*fn_t)(const Batch<LnBackArgs>);
+  const LnBackArgs *ptr[kBatch];
+  fn_t fn[kBatch];
+  unsigned gx[kBatch], gr[kBatch];
+  LnReduceArgs red[kBatch];
+  const LnReduceArgs *rptr[kBatch];
+  void (*rfn[kBatch])(const Batch<LnReduceArgs>);
+  for (int i = 0; i < n; ++i) {
+    const LnBackArgs &b = l[i];
+    const LnArgs &a = b.f;
+    ptr[i] = &b;
+    fn[i] = nullptr;
+    gx[i] = gr[i] = 0;
+    rptr[i] = &red[i];
+    rfn[i] = ln_param_reduce_kernel;
+    if (a.M <= 0) continue;
+    if (a.d > kLnMaxWidth || (a.out && a.out_ld > kLnMaxWidth)) return hipErrorInvalidValue;
+    int lpr = vec_lanes(a.d, a.x_dtype, a.x, a.x_ld);
+    if (lpr && (!vec_lanes(a.d, b.dr_dtype, b.dr, b.dr_ld) || (b.res && !vec_lanes(a.d, b.res_dtype, b.res, b.res_ld)) ||
+                (a.out && !vec_lanes(a.d, a.out_dtype, a.out, a.out_ld))))
+      lpr = 0;
+    if (lpr) {
+      const int rpw = 64 / lpr;
+      gx[i] = (unsigned)(waves_for((a.M + rpw - 1) / rpw, kLnMaxWaves) / 4);
+      fn[i] = lpr == 8 ? ln_relu_backward_vec_kernel<8> : lpr == 16 ? ln_relu_backward_vec_kernel<16>
+            : lpr == 32 ? ln_relu_backward_vec_kernel<32> : ln_relu_backward_vec_kernel<64>;
+    } else {
+      const int ni = (std::max(a.d, a.out ? a.out_ld : a.d) + 63) / 64;
+      gx[i] = (unsigned)(waves_for(a.M, kLnMaxWaves) / 4);
+      fn[i] = ni <= 1 ? ln_relu_backward_kernel<1> : ni <= 2 ? ln_relu_backward_kernel<2> : ni <= 4 ? ln_relu_backward_kernel<4>
+            : ni <= 8 ? ln_relu_backward_kernel<8> : ln_relu_backward_kernel<16>;
+    }
+    red[i] = LnReduceArgs{b.partial, (int32_t)gx[i], a.d, b.dgamma, b.dbeta};
+    gr[i] = (unsigned)((2 * a.d + 63) / 64);
+  }
+  const int e = launch_merged(ptr, fn, gx, n, 256, s);
+  return e != 0 ? e : launch_merged(rptr, rfn, gr, n, 1024, s);
 }
 
 int launch_copy_rows(const void *src, int src_ld, void *dst, int dst_ld, int64_t M, int d, int dtype, hipStream_t s) {

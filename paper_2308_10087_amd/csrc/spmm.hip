@@ -20,9 +20,9 @@
 namespace {
 
 // V consecutive elements of a row.  Rows are only known to be 4-byte aligned (a width of 100 bf16 columns, say); a global
-// access of 4, 8 or 16 bytes needs no more than that.
+// access of 4, 8 or 16 bytes needs no more than that.  (bf16 columns from an odd one on are not even that: store_cols.)
 template <typename T, int V>
-struct alignas(4) Pack {
+struct alignas(sizeof(T) * V < 4 ? sizeof(T) * V : 4) Pack {
   T v[V];
 };
 
@@ -44,6 +44,24 @@ __device__ inline Pack<Tin, VEC> load_aux(const SpmmArgs &a, int64_t row, int c)
 #pragma unroll
   for (int t = 0; t < VEC; ++t) z.v[t] = from_f32<Tin>(0.f);
   return z;
+}
+
+// Stores columns c .. c + VEC - 1 of an output row.  fp32 rows of odd width that are aggregated into bf16 rows (raw features)
+// end in a vector that starts at an odd column, two bytes off the 4-byte grid: that one goes element by element.  Rows of
+// bf16 sources have even widths and even first columns throughout.
+template <typename Tin, typename Tout, int VEC>
+__device__ inline void store_cols(Tout *p, int c, const float (&r)[VEC]) {
+  if constexpr (sizeof(Tout) < sizeof(Tin)) {
+    if (c & 1) {
+#pragma unroll
+      for (int t = 0; t < VEC; ++t) p[c + t] = from_f32<Tout>(r[t]);
+      return;
+    }
+  }
+  Pack<Tout, VEC> o;
+#pragma unroll
+  for (int t = 0; t < VEC; ++t) o.v[t] = from_f32<Tout>(r[t]);
+  *reinterpret_cast<Pack<Tout, VEC> *>(p + c) = o;
 }
 
 // Applies the epilogue to VEC consecutive columns of one output row and stores them; x is load_aux of the
@@ -78,10 +96,7 @@ __device__ inline void finish_cols(const SpmmArgs &a, int64_t row, int c, const 
 #pragma unroll
     for (int t = 0; t < VEC; ++t) r[t] = to_f32(x.v[t]) > 0.f ? acc[t] * a.mask_scale : 0.f;
   }
-  Pack<Tout, VEC> o;
-#pragma unroll
-  for (int t = 0; t < VEC; ++t) o.v[t] = from_f32<Tout>(r[t]);
-  *reinterpret_cast<Pack<Tout, VEC> *>(static_cast<Tout *>(a.out) + (size_t)(row - a.out_row0) * a.out_ld + c) = o;
+  store_cols<Tin, Tout, VEC>(static_cast<Tout *>(a.out) + (size_t)(row - a.out_row0) * a.out_ld, c, r);
 }
 
 template <typename Tin, typename Tout, int VEC>

@@ -28,6 +28,16 @@ def test_vector_alu_aggregation_at_tile_edges(dtype, widths):
     _parity(p, TOL_F32 if dtype == "f32" else TOL_BF16)
 
 
+@pytest.mark.parametrize("d0", [1, 3, 5, 67, 201, 301])
+def test_raw_features_of_odd_width_become_bf16_rows(d0):
+    """fp32 rows of odd width aggregated into bf16 rows: the last vector of a row starts at an odd column, off the 4-byte grid
+    of a vector store.  Whole rows and rows cut into pieces, one tile of columns and more."""
+    w = Workload("edges", "rmat", 1201, 91, [d0, 32, 24], 4, variant="sage", dtype="bf16", level0_f32=True, n_candidates=14_000)
+    p = make_problem(w, chunk_ptr=graphs.ragged_chunks(1201, 4, 3), bias_std=0.05)
+    assert np.diff(p.row_ptr).max() > 3 * 64
+    _parity(p, TOL_BF16, need_input_grad=False, alias_hist0=True)
+
+
 @pytest.mark.parametrize("dims,n,k,variant,drop", [
     ((1, 2, 3, 5), 301, 3, "gcn", 0.0), ((3, 4, 1), 130, 2, "sage", 0.3), ((15, 16, 17, 33), 517, 4, "gcn", 0.5),
     ((31, 32, 36, 65), 260, 2, "sage", 0.5), ((100, 100, 100), 700, 5, "gcnii", 0.0), ((67, 67), 411, 3, "resgcn", 0.0),

@@ -1302,7 +1302,7 @@ int res_backward_finish(gnnstage *st, hipStream_t stream) {
       a.epilogue = SPMM_PLAIN;
     }
     HIP_TRY(st, run_spmm(st, sp, n, stream, 2, cells[(size_t)first].j));
-    // no more cells at once than layers, and the layers of a chunk follow each other: no parameter comes twice
+    // no more cells at once than layers, and the layers of a chunk follow each other: every layer comes once
     LnBackArgs ln[kBatch];
     for (int i = 0; i < n; ++i) {
       const Cell &c = cells[(size_t)(first + i)];

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <functional>
 
 #include "common.h"
 
@@ -418,6 +419,15 @@ static int launch_merged(const A *const *a, const Fn *fn, const unsigned *gx, in
   return hipSuccess;
 }
 
+// whether two parameter reduces have elements of their destinations in common
+static bool adds_to_the_same(const LnReduceArgs &a, const LnReduceArgs &b) {
+  const float *da[2] = {a.dgamma, a.dbeta}, *db[2] = {b.dgamma, b.dbeta};
+  for (const float *x : da)
+    for (const float *y : db)
+      if (std::less<const float *>()(x, y + b.d) && std::less<const float *>()(y, x + a.d)) return true;
+  return false;
+}
+
 int launch_ln_relu(const LnArgs *l, int n, hipStream_t s) {
   if (n > kBatch) return hipErrorInvalidValue;
   typedef void (*fn_t)(const Batch<LnArgs>);
@@ -451,7 +461,7 @@ int launch_ln_relu_backward(const LnBackArgs *l, int n, hipStream_t s) {
   const LnBackArgs *ptr[kBatch];
   fn_t fn[kBatch];
   unsigned gx[kBatch], gr[kBatch];
-  LnReduceArgs red[kBatch];
+  LnReduceArgs red[kBatch] = {};
   const LnReduceArgs *rptr[kBatch];
   void (*rfn[kBatch])(const Batch<LnReduceArgs>);
   for (int i = 0; i < n; ++i) {
@@ -482,8 +492,18 @@ int launch_ln_relu_backward(const LnBackArgs *l, int n, hipStream_t s) {
     red[i] = LnReduceArgs{b.partial, (int32_t)gx[i], a.d, b.dgamma, b.dbeta};
     gr[i] = (unsigned)((2 * a.d + 63) / 64);
   }
-  const int e = launch_merged(ptr, fn, gx, n, 256, s);
-  return e != 0 ? e : launch_merged(rptr, rfn, gr, n, 1024, s);
+  int e = launch_merged(ptr, fn, gx, n, 256, s);
+  // The sums are added to the parameter gradients without atomics.  Layers may share those buffers (tied parameters), so a
+  // launch takes the cells up to the first one that would add to a buffer again; that one starts the next launch.
+  for (int i0 = 0, i1; i0 < n && e == 0; i0 = i1) {
+    for (i1 = i0 + 1; i1 < n; ++i1) {
+      bool again = false;
+      for (int i = i0; i < i1; ++i) again = again || adds_to_the_same(red[i], red[i1]);
+      if (again) break;
+    }
+    e = launch_merged(rptr + i0, rfn + i0, gr + i0, i1 - i0, 1024, s);
+  }
+  return e;
 }
 
 int launch_copy_rows(const void *src, int src_ld, void *dst, int dst_ld, int64_t M, int d, int dtype, hipStream_t s) {

@@ -10,7 +10,7 @@ from synth import graphs
 from synth.configs import CONFIGS, Workload
 
 from gpu_harness import GpuRun
-from helpers import make_problem
+from helpers import make_problem, max_rel, run_oracle
 from test_gpu_parity import TOL_BF16, TOL_F32, _parity, small
 
 pytestmark = pytest.mark.gpu
@@ -106,6 +106,23 @@ def test_whole_pass_calls_equal_the_chunk_calls(variant, dtype, dims, k, kw):
     for name in ("dW", "dbias", "d_ln_gamma", "d_ln_beta"):
         for a, b in zip(getattr(whole, name) or [], getattr(by_chunk, name) or []):
             assert (a - b).abs().max() <= 1e-5 * b.abs().max() + 1e-30, name
+
+
+@pytest.mark.parametrize("dtype,width", [("f32", 36), ("bf16", 128)])
+def test_layers_with_one_layernorm_gradient_buffer(dtype, width):
+    """Tied LayerNorm parameters: the layers' gradients add up in the buffer that they share, in passes whose cells run side by
+    side and in the part of a backward pass that follows its last chunk."""
+    import paper_2308_10087_amd as g
+    p = make_problem(small(n=900, k=6, dims=(width,) * 5, variant="resgcn", dtype=dtype, deg=9.0), bias_std=0.05, first_stage=False)
+    ref = run_oracle(p)
+    r = GpuRun(p)
+    dg, db = torch.zeros(width, device=r.device), torch.zeros(width, device=r.device)
+    r.stage = g.GnnStage(p.row_ptr, p.col, p.chunk_ptr, p.dims, W=r.W, cur=r.cur, hist=r.hist, dW=r.dW, bias=r.bias, dbias=r.dbias, edge_val=p.val,
+                         variant=g.GNNSTAGE_RESGCN, dtype=g.GNNSTAGE_BF16 if p.quant else g.GNNSTAGE_F32, grad_in=r.grad_in, device=r.device,
+                         ln_gamma=r.ln_gamma, ln_beta=r.ln_beta, d_ln_gamma=[dg] * 4, d_ln_beta=[db] * 4)
+    r.run()
+    tol = TOL_BF16 if p.quant else TOL_F32
+    assert max_rel(r.np(dg), sum(ref.d_ln_g)) <= tol and max_rel(r.np(db), sum(ref.d_ln_b)) <= tol
 
 
 def test_passes_that_cannot_run_whole_behave_like_the_chunk_calls():

@@ -1,0 +1,125 @@
+"""What the library launches, on a CPU: its host side runs in a process of its own over host_launches.c, which lists kernel
+launches instead of running them."""
+import ctypes as C
+import json
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("host") / "libhostlaunches.so")
+    subprocess.run(["cc", "-O1", "-shared", "-fPIC", os.path.join(HERE, "host_launches.c"), "-o", so], check=True)
+    return so
+
+
+def _child(runtime, what, *args):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), runtime, what, json.dumps(args)], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return json.loads(r.stdout.splitlines()[-1])
+
+
+# ---- in the child -----------------------------------------------------------------------------------------------
+class _Launch(C.Structure):
+    _fields_ = [("name", C.c_char_p), ("grid", C.c_uint32 * 3), ("args", C.c_uint8 * 256)]
+
+
+class _Stage:
+    """A stage handle over host buffers (values never matter: nothing is computed)."""
+
+    def __init__(self, variant, dims, K, n=400, tied=False):
+        import paper_2308_10087_amd as g
+        from paper_2308_10087_amd import binding
+        self.g, self.lib = g, binding.lib
+        L = len(dims) - 1
+        col = (np.arange(n)[:, None] + np.array([0, 1, 7, 50])) % n
+        row_ptr, col = np.arange(n + 1, dtype=np.int64) * 4, np.sort(col, axis=1).astype(np.int32).ravel()
+        chunk_ptr, dims = (np.arange(K + 1, dtype=np.int64) * n) // K, np.asarray(dims, np.int32)
+        rows = lambda ws: [np.zeros((n, int(w)), np.float32) for w in ws]
+        vec = lambda ws: [np.zeros(int(w), np.float32) for w in ws]
+        self.keep = dict(row_ptr=row_ptr, col_idx=col, chunk_ptr=chunk_ptr, dims=dims)
+        lists = dict(W=[np.zeros((int(dims[j]), int(dims[j + 1])), np.float32) for j in range(L)], cur=rows(dims), hist=rows(dims[:-1]),
+                     dW=[np.zeros((int(dims[j]), int(dims[j + 1])), np.float32) for j in range(L)], bias=vec(dims[1:]), dbias=vec(dims[1:]))
+        if variant == "resgcn":
+            lists.update(ln_gamma=vec(dims[:-1]), ln_beta=vec(dims[:-1]))
+            for i, name in enumerate(("d_ln_gamma", "d_ln_beta")):
+                lists[name] = [np.zeros(int(dims[0]), np.float32)] * L if tied else vec(dims[:-1])
+        d = binding.gnnstage_desc()
+        d.n_vertices, d.nnz, d.n_chunks, d.n_layers = n, len(col), K, L
+        for name, a in self.keep.items():
+            setattr(d, name, a.ctypes.data)
+        for name, a in lists.items():
+            p = (C.c_void_p * len(a))(*[x.ctypes.data for x in a])
+            self.keep["list " + name] = (a, p)
+            setattr(d, name, C.cast(p, C.c_void_p))
+        self.grad_in, self.grad_out = np.zeros((n, int(dims[0])), np.float32), np.zeros((n, int(dims[-1])), np.float32)
+        d.variant, d.dtype, d.need_input_grad, d.grad_in, d.ln_eps = dict(gcn=0, resgcn=3)[variant], g.GNNSTAGE_F32, 1, self.grad_in.ctypes.data, 1e-5
+        size = self.lib.gnnstage_workspace_size(C.byref(d))
+        self.ws = np.zeros(size + 256, np.uint8)
+        d.workspace, d.workspace_bytes = (self.ws.ctypes.data + 255) // 256 * 256, size
+        self.h = C.c_void_p(None)
+        rc = self.lib.gnnstage_create(C.byref(d), C.byref(self.h))
+        assert rc == 0, (rc, self.lib.gnnstage_last_error(None))
+        self.K, self.L, self.chunk_ptr, self.order = K, L, chunk_ptr, np.arange(K, dtype=np.int32)[::-1].copy()
+
+    def forward(self):
+        return self.lib.gnnstage_forward_pass(self.h, self.order.ctypes.data, self.K, None)
+
+    def backward(self):
+        return self.lib.gnnstage_backward_pass(self.h, self.order.ctypes.data, self.K, self.grad_out.ctypes.data, None)
+
+    def by_chunk(self):
+        for pos, k in enumerate(self.order):
+            assert self.lib.stage_forward_chunk(self.h, int(k), pos, None) == 0
+        for k in self.order[::-1]:
+            assert self.lib.stage_backward_chunk(self.h, int(k), self.grad_out[self.chunk_ptr[k]:].ctypes.data, None) == 0
+
+
+def _launches(rt):
+    return [rt.host_launch(i).contents for i in range(rt.host_launches())]
+
+
+def _ln_reduces(rt, tied, whole):
+    """Destinations (gamma, beta) of every launch that adds up LayerNorm parameter gradients, a list per launch."""
+    st = _Stage("resgcn", [32] * 5, 6, tied=tied)
+    rt.host_clear(-1)
+    if whole:
+        assert st.forward() == 0 and st.backward() == 0
+    else:
+        st.by_chunk()
+    out = []
+    for l in _launches(rt):
+        if b"ln_param_reduce" in l.name:
+            a = np.frombuffer(bytes(l.args), np.uint64).reshape(8, 4)  # per plane: partial, (n_parts, d), dgamma, dbeta
+            out.append([int(x) for x in a[:l.grid[2], 2:].ravel()])
+    return out
+
+
+if __name__ == "__main__":
+    _rt = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)  # before the library, whose calls it takes
+    _rt.host_launches.restype = C.c_size_t
+    _rt.host_launch.restype, _rt.host_launch.argtypes = C.POINTER(_Launch), [C.c_size_t]
+    _rt.host_clear.argtypes = [C.c_int64]
+    sys.path.insert(0, os.path.dirname(HERE))
+    print(json.dumps(globals()[sys.argv[2]](_rt, *json.loads(sys.argv[3]))))
+    sys.stdout.flush()
+    os._exit(0)  # the handles' buffers are never freed one by one
+
+
+# ---- tests ------------------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("whole", [True, False])
+@pytest.mark.parametrize("tied", [True, False])
+def test_no_launch_adds_to_a_layernorm_gradient_twice(runtime, tied, whole):
+    """Layers may share a parameter-gradient buffer (tied parameters): the cells of one launch run side by side and add without
+    atomics, so a buffer may come up once per launch; buffers of their own go together."""
+    launches = _child(runtime, "_ln_reduces", tied, whole)
+    assert sum(len(l) for l in launches) == 2 * (6 + 5) * 4  # every cell, and the historical rows of all chunks but the first
+    for l in launches:
+        assert len(set(l)) == len(l)
+    assert tied or max(len(l) for l in launches) == 2 * 4

@@ -962,10 +962,11 @@ int run_spmm(gnnstage *st, CellSpmm *cells, int n, hipStream_t stream, int kind,
   return 0;
 }
 
-// Runs [0, n) in turns of at most the cells that have scratch of their own; f(first, count).
+// Runs [0, n) in turns of at most the cells that have scratch of their own; f(first, count).  One by one while launches are
+// timed: a timed launch belongs to one layer.
 template <typename F>
 int in_turns(const gnnstage *st, int n, F f) {
-  const int B = st->lay.cells;
+  const int B = st->prof.kinds != 0 ? 1 : st->lay.cells;
   for (int i = 0; i < n; i += B) {
     const int rc = f(i, std::min(B, n - i));
     if (rc != GNNSTAGE_OK) return rc;

@@ -101,6 +101,20 @@ def _ln_reduces(rt, tied, whole):
     return out
 
 
+def _timed(rt, variant, dims):
+    """[kind][layer] timed launches of a whole pass with every kind switched on."""
+    st = _Stage(variant, dims, 6)
+    assert st.lib.gnnstage_profile_enable(st.h, 1) == 0
+    assert st.forward() == 0 and st.backward() == 0
+    ms, n, out = C.c_double(0), C.c_int64(0), []
+    for kind in range(8):
+        out.append([])
+        for j in range(st.L):
+            assert st.lib.gnnstage_profile_read(st.h, kind, j, C.byref(ms), C.byref(n)) == 0
+            out[-1].append(n.value)
+    return out
+
+
 if __name__ == "__main__":
     _rt = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)  # before the library, whose calls it takes
     _rt.host_launches.restype = C.c_size_t
@@ -123,3 +137,13 @@ def test_no_launch_adds_to_a_layernorm_gradient_twice(runtime, tied, whole):
     for l in launches:
         assert len(set(l)) == len(l)
     assert tied or max(len(l) for l in launches) == 2 * 4
+
+
+@pytest.mark.parametrize("variant,dims", [("resgcn", [32] * 5), ("gcn", [64, 32, 16, 8])])
+def test_timed_launches_are_booked_on_their_own_layer(runtime, variant, dims):
+    """Six chunks: an aggregation per chunk and layer, and after the last chunk another one for every chunk (ResGCN+: but the
+    first) behind the parameters that historical rows went through."""
+    timed = _child(runtime, "_timed", variant, dims)
+    L = len(dims) - 1
+    assert timed[0] == [6] * L and timed[2] == [6 + (5 if variant == "resgcn" else 6)] * L
+    assert timed[4] == [timed[4][0]] * L

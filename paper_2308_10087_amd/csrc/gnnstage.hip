@@ -2063,12 +2063,16 @@ extern "C" int gnnstage_forward_pass(gnnstage_t *st, const int32_t *order, int32
     return GNNSTAGE_OK;
   }
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  std::vector<int32_t> ks(order, order + n_order);
   int rc = begin_forward(st, stream);
   if (rc != GNNSTAGE_OK) return rc;
-  st->order.assign(order, order + n_order);
-  for (int32_t p = 0; p < n_order; ++p) mask_set(st->fmask, order[p]);
+  rc = run_diagonals(st, ks, [](int step) { return step; }, [&](const Cell *c, int n) { return forward_cells(st, c, n, stream); });
+  if (rc != GNNSTAGE_OK) return rc;
+  // only now: a pass that failed half-way is none to run backward or to refresh the history from
+  st->order.swap(ks);
+  for (int32_t k : st->order) mask_set(st->fmask, k);
   st->cur_stale = false;
-  return run_diagonals(st, st->order, [](int step) { return step; }, [&](const Cell *c, int n) { return forward_cells(st, c, n, stream); });
+  return GNNSTAGE_OK;
 }
 GNNSTAGE_GUARD_INT
 
@@ -2121,15 +2125,13 @@ extern "C" int gnnstage_backward_pass(gnnstage_t *st, const int32_t *order, int3
   }
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const std::vector<int32_t> back(st->order.rbegin(), st->order.rend());
-  for (int32_t k = 0; k < s.K; ++k) {
-    mask_set(st->bmask, k);
-    st->wgrad_pending[(size_t)k] = cell_rows(st, k) > 0 ? 1 : 0;
-  }
-  st->n_bwd = s.K;
+  st->n_bwd = s.K;  // there is no second try, whatever fails below: part of the sums may be added by then
+  for (int32_t k = 0; k < s.K; ++k) mask_set(st->bmask, k);
   int rc = top_dY(st, grad_out, 0, s.n, full_dY(st, s.L - 1), stream);
   if (rc != GNNSTAGE_OK) return rc;
   rc = run_diagonals(st, back, [&](int step) { return s.L - 1 - step; }, [&](const Cell *c, int n) { return backward_cells(st, c, n, true, stream); });
   if (rc != GNNSTAGE_OK) return rc;
+  for (int32_t k = 0; k < s.K; ++k) st->wgrad_pending[(size_t)k] = cell_rows(st, k) > 0 ? 1 : 0;
   for (int j = 0; j < s.L; ++j)
     if (s.tf[j] && s.has_bias())
       HIP_TRY(st, launch_colsum_add(full_dY(st, j), st->cdtype(), s.ld[j + 1], (int)s.n, s.dims[j + 1], st->at<float>(st->lay.bias_partial), kMaxSplits,

@@ -115,6 +115,32 @@ def _timed(rt, variant, dims):
     return out
 
 
+def _refused(rt, variant, dims):
+    """A pass in which one launch is refused, at a few places: return codes of the pass and of the calls that follow it."""
+    out = {"forward": [], "backward": []}
+    st = _Stage(variant, dims, 6)
+    rt.host_clear(-1)
+    assert st.forward() == 0
+    n_fwd = rt.host_launches()
+    assert st.backward() == 0
+    n_bwd = rt.host_launches() - n_fwd
+    for at in (0, n_fwd // 2, n_fwd - 1):
+        rt.host_clear(at)
+        rc = st.forward()
+        rt.host_clear(-1)
+        out["forward"].append([rc, st.backward(), st.lib.gnnstage_update_history_swap(st.h, None), rt.host_launches()])
+    for at in (0, n_bwd // 3, n_bwd // 2):
+        rt.host_clear(-1)
+        assert st.forward() == 0
+        rt.host_clear(at)
+        rc = st.backward()
+        rt.host_clear(-1)
+        out["backward"].append([rc, st.lib.gnnstage_flush_weight_gradients(st.h, None), st.backward(), rt.host_launches()])
+    rt.host_clear(-1)
+    assert st.forward() == 0 and st.backward() == 0 and rt.host_launches() == n_fwd + n_bwd  # the handle is as good as new
+    return out
+
+
 if __name__ == "__main__":
     _rt = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)  # before the library, whose calls it takes
     _rt.host_launches.restype = C.c_size_t
@@ -147,3 +173,13 @@ def test_timed_launches_are_booked_on_their_own_layer(runtime, variant, dims):
     L = len(dims) - 1
     assert timed[0] == [6] * L and timed[2] == [6 + (5 if variant == "resgcn" else 6)] * L
     assert timed[4] == [timed[4][0]] * L
+
+
+@pytest.mark.parametrize("variant,dims", [("resgcn", [32] * 5), ("gcn", [64, 32, 40, 8])])
+def test_a_pass_that_fails_does_not_count_as_run(runtime, variant, dims):
+    """A whole pass in which a launch is refused returns that error.  A forward pass that failed is no pass to run backward or to
+    take the history from; one that failed on its way back leaves no weight gradients of rows that it never reached to add."""
+    EHIP, EORDER = -5, -3
+    got = _child(runtime, "_refused", variant, dims)
+    assert got["forward"] == [[EHIP, EORDER, EORDER, 0]] * 3
+    assert got["backward"] == [[EHIP, 0, EORDER, 0]] * 3

@@ -1078,13 +1078,17 @@ __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const Batch<GemmNtArgs
 // 4 m + ta of A and 4 n + tb of B (V = 4), so V^2 matrix instructions share one pair of loads and nothing passes through
 // LDS.  The four waves of a workgroup take the steps of four rows in turn and add their tiles in LDS at the end.  The last
 // vector of a row moves back inside the row (those outputs are computed by two lanes alike).  V = 1 serves operands
-// narrower than four columns.  10.4 GFLOP over 5,196 rows (1000 x 1000): 160 -> 112 us (93 TFLOP/s); 34 k rows,
+// narrower than four columns.  A wave's rows are added up in blocks of BLOCK steps (chains of 32 products) and the blocks then:
+// one chain over all of its rows (650 of 5,196 with 1000 x 1000 outputs) is further from 64 bits, 3.3e-7 against 1.2e-7, for
+// the same time (wide fp32 stage 4.10 ms per step either way).
+// 10.4 GFLOP over 5,196 rows (1000 x 1000): 160 -> 112 us (93 TFLOP/s); 34 k rows,
 // 100 x 100 outputs: 24 -> 18 us; the bias gradient (column sums of B) rides along, 17 - 27 us as a kernel of its own
 // before.
 template <int V>
 __global__ __launch_bounds__(256) void gemm_tn_f32_kernel(const GemmTnArgs a, int rows_per_split, int splits) {
   constexpr int T = 16 * V;
-  constexpr int D = 4;  // steps of four rows in flight per wave
+  constexpr int D = 4;      // steps of four rows in flight per wave
+  constexpr int BLOCK = 8;  // steps of one chain of additions
   typedef float vec_t __attribute__((ext_vector_type(V), aligned(4)));
   __shared__ float red[4][T * T];
   __shared__ float bred[4][T];
@@ -1101,15 +1105,15 @@ __global__ __launch_bounds__(256) void gemm_tn_f32_kernel(const GemmTnArgs a, in
   const int ci = min(i0 + lc, a.I - V), co = min(o0 + lc, a.O - V);
   const float *A = static_cast<const float *>(a.A) + ci;
   const float *B = static_cast<const float *>(a.B) + co;
-  f32x4 acc[V][V];
+  f32x4 acc[V][V], sum[V][V];
 #pragma unroll
   for (int x = 0; x < V; ++x)
 #pragma unroll
-    for (int y = 0; y < V; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int y = 0; y < V; ++y) acc[x][y] = sum[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
   const bool do_bias = a.bias_partial != nullptr && i0 == 0;
-  float bsum[V];
+  float bacc[V], bsum[V];
 #pragma unroll
-  for (int t = 0; t < V; ++t) bsum[t] = 0.f;
+  for (int t = 0; t < V; ++t) bacc[t] = bsum[t] = 0.f;
   float fa[D][V], fb[D][V];
   const int steps = (r_end - r_begin + 3) / 4;
   const int cnt = steps > wave ? (steps - wave + 3) / 4 : 0;  // of this wave: steps wave, wave + 4, ...
@@ -1132,12 +1136,26 @@ __global__ __launch_bounds__(256) void gemm_tn_f32_kernel(const GemmTnArgs a, in
     }
     if (do_bias) {
 #pragma unroll
-      for (int t = 0; t < V; ++t) bsum[t] += fb[u][t];
+      for (int t = 0; t < V; ++t) bacc[t] += fb[u][t];
     }
 #pragma unroll
     for (int x = 0; x < V; ++x)
 #pragma unroll
       for (int y = 0; y < V; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[u][x], fb[u][y], acc[x][y], 0, 0, 0);
+  };
+  auto close_block = [&]() {
+#pragma unroll
+    for (int x = 0; x < V; ++x)
+#pragma unroll
+      for (int y = 0; y < V; ++y) {
+        sum[x][y] += acc[x][y];
+        acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+      bsum[t] += bacc[t];
+      bacc[t] = 0.f;
+    }
   };
 #pragma unroll
   for (int u = 0; u < D; ++u)
@@ -1149,6 +1167,7 @@ __global__ __launch_bounds__(256) void gemm_tn_f32_kernel(const GemmTnArgs a, in
       consume(i + u, u);
       load(i + D + u, u);
     }
+    if ((i / D) % (BLOCK / D) == BLOCK / D - 1) close_block();
   }
 #pragma unroll
   for (int u = 0; u < D; ++u) {
@@ -1158,13 +1177,14 @@ __global__ __launch_bounds__(256) void gemm_tn_f32_kernel(const GemmTnArgs a, in
 #pragma unroll
   for (int u = 0; u < D; ++u)
     if (i + D + u < cnt) consume(i + D + u, u);
+  close_block();
   // element e of lane l of tile (x, y) is A column vector 4*(l/16) + e, element x, and B column vector l%16, element y
 #pragma unroll
   for (int x = 0; x < V; ++x)
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int y = 0; y < V; ++y) red[wave][((4 * (lane >> 4) + e) * V + x) * T + (lane & 15) * V + y] = acc[x][y][e];
+      for (int y = 0; y < V; ++y) red[wave][((4 * (lane >> 4) + e) * V + x) * T + (lane & 15) * V + y] = sum[x][y][e];
   if (do_bias) {
 #pragma unroll
     for (int t = 0; t < V; ++t) {

@@ -129,6 +129,21 @@ def test_bias_gradients_over_all_rows_are_as_exact_as_by_chunk(dtype, n, bound):
         assert err <= bound
 
 
+@pytest.mark.parametrize("n,d", [(5196, 1000), (33333, 100), (2077, 3)])
+def test_fp32_weight_gradients_over_all_rows_against_64_bits(n, d):
+    """x0^T dY and the column sums of dY of one layer over self-loops of weight 1 (the aggregation hands the rows on), errors
+    relative to the products of the factors' norms over the root of n.  One chain of additions over all rows of a wave came to
+    3.3e-7, 1.6e-7 and 0.9e-7; the bound is a sixth over what chains of 32 products, added up afterwards, come to."""
+    loops = (np.arange(n + 1, dtype=np.int64), np.arange(n, dtype=np.int32))
+    p = make_problem(small(n=n, k=1, dims=(d, d)), graph=loops, bias_std=0.05, history="random")
+    p.val[:] = 1.0
+    r = GpuRun(p, need_input_grad=False, alias_hist0=True).run()
+    x, dY = r.cur[0].double(), r.grad_out.double() * (r.cur[1] > 0)
+    err = ((r.dW[0].double() - x.T @ dY).norm() / (x.square().sum(0).sqrt()[:, None] * dY.square().sum(0).sqrt() / n ** 0.5).norm()).item()
+    errb = ((r.dbias[0].double() - dY.sum(0)).norm() / dY.square().sum(0).sqrt().norm()).item()
+    assert err <= 1.5e-7 and errb <= 1.5e-7
+
+
 @pytest.mark.parametrize("dtype,width", [("f32", 36), ("bf16", 128)])
 def test_layers_with_one_layernorm_gradient_buffer(dtype, width):
     """Tied LayerNorm parameters: the layers' gradients add up in the buffer that they share, in passes whose cells run side by

@@ -604,7 +604,9 @@ Layout make_layout(const Shape &s, const HostDir &hf, const HostDir &hb, bool ra
     l.Th[j] = w.take((size_t)s.n * s.ld[j] * elt);
     l.Z[j] = w.take((size_t)s.n * s.ld[j] * elt);
     l.dZ[j] = w.take((size_t)s.n * s.ld[j] * elt);
-    if (s.defer_wgrad()) l.dY[j] = w.take((size_t)s.n * s.ld[j + 1] * elt);
+    // deferred weight gradients keep dY of all rows in the table of activated current rows (of the same width): a chunk's rows
+    // of that table are written before they are read in a forward pass, and no backward pass reads them
+    l.dY[j] = l.Tc[j];
   }
   if (s.res()) {
     l.res_dr = w.take(l.row_stride * elt * B);

@@ -431,6 +431,25 @@ def test_workspace_size_and_validation_without_a_gpu():
     assert g.lib.gnnstage_destroy(None) == -1
 
 
+def _workspace(variant, n, dims, chunk_ptr):
+    """Workspace bytes of an fp32 stage over self-loops."""
+    g = _lib()
+    arrays = dict(row_ptr=np.arange(n + 1, dtype=np.int64), col_idx=np.arange(n, dtype=np.int32), chunk_ptr=np.asarray(chunk_ptr, np.int64),
+                  dims=np.asarray(dims, np.int32))
+    d, keep = _desc(g, variant=variant, n_vertices=n, nnz=n, n_chunks=len(chunk_ptr) - 1, n_layers=len(dims) - 1, need_input_grad=1, ln_eps=1e-5,
+                    **{k: a.ctypes.data for k, a in arrays.items()})
+    return g.lib.gnnstage_workspace_size(C.byref(d))
+
+
+def test_resgcn_workspace_holds_four_tables_per_layer():
+    """Activated current and historical rows, the saved aggregation and its gradient; the gradient rows that deferred weight
+    gradients keep take the place of the first, which a backward pass has no use for."""
+    n, L, d = 50000, 8, 256
+    table = n * d * 4
+    size = _workspace(3, n, [d] * (L + 1), (np.arange(65) * n) // 64)
+    assert 4 * L * table < size < (4 * L + 4) * table
+
+
 def test_generated_graphs_are_symmetric_sorted_and_reproducible():
     w = CONFIGS["c3_s"]
     a_ptr, a_col = make_graph(w)

@@ -519,7 +519,7 @@ bool read_shape(const gnnstage_desc *d, Shape &s, std::string &err) {
   return true;
 }
 
-Layout make_layout(const Shape &s, const HostDir &hf, const HostDir &hb, bool rank1) {
+Layout layout_for(const Shape &s, const HostDir &hf, const HostDir &hb, bool rank1, int cells) {
   const PlanCounts &f = hf.pc, &b = hb.pc;
   Layout l;
   Bump w;
@@ -555,7 +555,7 @@ Layout make_layout(const Shape &s, const HostDir &hf, const HostDir &hb, bool ra
     max_items = std::max(max_items, h.max_items);
   }
   // scratch of one cell times the cells that run side by side
-  l.cells = s.cells_at_once(hf.dense() || hb.dense());
+  l.cells = cells;
   const size_t B = (size_t)l.cells;
   l.dense_stride = (size_t)max_items * kDenseRB * 256;
   l.dense_partial = w.take(sizeof(float) * l.dense_stride * B);
@@ -645,6 +645,18 @@ Layout make_layout(const Shape &s, const HostDir &hf, const HostDir &hb, bool ra
   l.bias_partial = w.take(sizeof(float) * kMaxSplits * max_d);
   l.total = w.off;
   return l;
+}
+
+// The cells that run side by side share a budget of scratch beyond that of one: 1 GiB, or a sixteenth of the workspace where
+// that is more.  Chunks of equal size stay far below it (700 k vertices of width 256, 32 chunks: 24 MB for four cells); of a
+// graph with nearly all vertices in one chunk every cell would add up to 12 bytes per element of a whole level.
+Layout make_layout(const Shape &s, const HostDir &hf, const HostDir &hb, bool rank1) {
+  const Layout one = layout_for(s, hf, hb, rank1, 1);
+  const int most = s.cells_at_once(hf.dense() || hb.dense());
+  if (most <= 1) return one;
+  const size_t budget = std::max<size_t>((size_t)1 << 30, one.total / 16);
+  const size_t more = layout_for(s, hf, hb, rank1, 2).total - one.total;  // what a cell takes
+  return layout_for(s, hf, hb, rank1, (int)std::min<size_t>((size_t)most, 1 + budget / std::max<size_t>(more, 1)));
 }
 
 struct Profiler {

@@ -450,6 +450,15 @@ def test_resgcn_workspace_holds_four_tables_per_layer():
     assert 4 * L * table < size < (4 * L + 4) * table
 
 
+def test_scratch_of_cells_that_run_side_by_side_is_bounded():
+    """Equal chunks: a little more than one cell's.  Nearly all rows in one chunk: a cell takes 1.8 GB of scratch, and the stage
+    no more than 1 GiB beyond what it takes with one chunk, which runs one cell at a time."""
+    n, dims = 300000, [512] * 5
+    one = _workspace(2, n, dims, [0, n])
+    assert _workspace(2, n, dims, (np.arange(33) * n) // 32) < one  # chunk-sized scratch
+    assert _workspace(2, n, dims, [0, n - 300, n - 200, n - 100, n]) <= one + (1 << 30)
+
+
 def test_generated_graphs_are_symmetric_sorted_and_reproducible():
     w = CONFIGS["c3_s"]
     a_ptr, a_col = make_graph(w)

@@ -192,7 +192,6 @@ struct gnntrain {
   Dims x;
   Layout lay;
   std::vector<gnnstage_t *> stages;
-  std::vector<int64_t> chunk_ptr;
   std::vector<gnntrain_param> params;
   std::vector<size_t> moment_off;  // element offset of every parameter inside m / v
   const void *top = nullptr;
@@ -430,8 +429,6 @@ extern "C" int gnntrain_create(const gnntrain_desc *d, gnntrain_t **out) try {
   tr->x = x;
   tr->lay = lay;
   tr->stages.assign(d->stages, d->stages + d->n_stages);
-  tr->chunk_ptr.resize((size_t)x.K + 1);
-  for (int c = 0; c <= x.K; ++c) tr->chunk_ptr[(size_t)c] = gnnstage_query(d->stages[0], GNNSTAGE_Q_CHUNK_PTR, c);
   tr->params.assign(d->params, d->params + d->n_params);
   size_t off = 0;
   for (const gnntrain_param &p : tr->params) {

@@ -72,7 +72,7 @@ class GpuTrainRun:
     """A TrainProblem on the GPU: chained stages, head, parameter list in the oracle trainer's order
     (per stage all W then all biases, then the head's W and b)."""
 
-    def __init__(self, tp, device="cuda:0", chain=True, **opt):
+    def __init__(self, tp, device="cuda:0", chain=True, alias_hist0=False, **opt):
         self.tp = tp
         bf = tp.quant
         sdt = torch.bfloat16 if bf else torch.float32
@@ -92,7 +92,7 @@ class GpuTrainRun:
             bias = [_dev(tp.b[si][j], torch.float32, device) for j in range(L)]
             level0 = _dev(tp.x0, l0, device) if first else (prev_top if chain else torch.zeros((n, dims[0]), dtype=sdt, device=device))
             cur = [level0] + [torch.zeros((n, dims[j]), dtype=sdt, device=device) for j in range(1, L + 1)]
-            hist = [cur[0] if first else torch.zeros((n, dims[0]), dtype=sdt, device=device)] + \
+            hist = [cur[0] if first or alias_hist0 else torch.zeros((n, dims[0]), dtype=sdt, device=device)] + \
                    [torch.zeros((n, dims[j]), dtype=sdt, device=device) for j in range(1, L)]
             dW = [torch.zeros(tuple(tp.W[si][j].shape), dtype=torch.float32, device=device) for j in range(L)]
             dbias = [torch.zeros(dims[j + 1], dtype=torch.float32, device=device) for j in range(L)]

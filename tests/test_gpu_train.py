@@ -193,6 +193,24 @@ def test_sgd_epochs_with_empty_chunks_and_shuffling():
     assert set(firsts) <= {0, 2}, firsts
 
 
+@pytest.mark.parametrize("variants", [("gcn", "gcn"), ("sage", "sage")])
+def test_a_later_stage_whose_history_is_the_level_below_it(variants):
+    """hist[0] of the second stage is the buffer that the first one writes: what a chunk does not select are rows of the last
+    epoch, which are there only as long as the chunks go through both stages one after the other."""
+    from gpu_harness import GpuTrainRun
+    tp = make_train_problem(n=1500, n_classes=5, stage_dims=((24, 24, 24), (24, 24, 24, 24)), K=5, ragged=True, variants=variants)
+    opt = dict(optimizer="sgd", lr=0.05, shuffle=True, seed=7, alpha_hist=1)
+    ref = new_oracle_trainer(tp, **{k: (F(v) if isinstance(v, float) else v) for k, v in opt.items()})
+    ref.stages[1].hist[0] = ref.stages[1].cur[0]
+    ref.stages[1]._refresh()
+    run = GpuTrainRun(tp, alias_hist0=True, **opt)
+    for e in range(3):
+        lr_, lg = ref.epoch(e), run.epoch(e)
+        assert abs(lg - lr_) <= 1e-4 * lr_
+        for a, b in zip(run.grads(), ref.grads()):
+            assert max_rel(a.reshape(b.shape), b) <= 1e-4, e
+
+
 def test_sgd_epochs_with_dropout_in_the_resgcn_stage():
     """A fresh set of dropout decisions every epoch, the same on both sides."""
     tp = make_train_problem(n=1500, n_classes=5, stage_dims=((24, 16), (16, 16, 16), (16, 8)), K=4, ragged=True,

@@ -1402,9 +1402,12 @@ int launch_gemm_nt(const GemmNtArgs *a_in, int n, int compute_dtype, hipStream_t
       of[m] = j;
       b.sub[m++] = args[j];
     }
-    // a persistent kernel gets two workgroups per compute unit, each with as many row tiles of one product as that takes
+    // A persistent kernel gets two workgroups per compute unit.  Several products share them: every workgroup gets as many row
+    // tiles of one product as that takes.  One product is dealt out evenly: with the rule for several, 66,000 x 256 x 200 ran
+    // in 344 workgroups of 3 tiles instead of 512 of 2 or 3, 25.1 against 23.0 us (131,500 rows 34.4 against 32.7).
     unsigned per = 1;
-    if (tm[i] > 0) {
+    const unsigned even = tm[i] > 0 && m == 1 ? std::min(gx[i], 512u) : 0;
+    if (tm[i] > 0 && m > 1) {
       unsigned tiles = 0;
       for (unsigned q = 0; q < m; ++q) tiles += gx[of[q]];
       per = std::max(1u, tiles / 512u);
@@ -1416,7 +1419,7 @@ int launch_gemm_nt(const GemmNtArgs *a_in, int n, int compute_dtype, hipStream_t
       while (need(per) > 512u) ++per;  // at most eight products: ends at the latest with one workgroup each
     }
     for (unsigned q = 0; q < m; ++q) {
-      const unsigned w = (gx[of[q]] + per - 1) / per;
+      const unsigned w = even > 0 ? even : (gx[of[q]] + per - 1) / per;
       b.sub[q].ws_blocks = (int32_t)w;
       width = std::max(width, w);
     }

@@ -33,7 +33,7 @@ class _Launch(C.Structure):
 class _Stage:
     """A stage handle over host buffers (values never matter: nothing is computed)."""
 
-    def __init__(self, variant, dims, K, n=400, tied=False):
+    def __init__(self, variant, dims, K, n=400, tied=False, bf16=False):
         import paper_2308_10087_amd as g
         from paper_2308_10087_amd import binding
         self.g, self.lib = g, binding.lib
@@ -59,7 +59,7 @@ class _Stage:
             self.keep["list " + name] = (a, p)
             setattr(d, name, C.cast(p, C.c_void_p))
         self.grad_in, self.grad_out = np.zeros((n, int(dims[0])), np.float32), np.zeros((n, int(dims[-1])), np.float32)
-        d.variant, d.dtype, d.need_input_grad, d.grad_in, d.ln_eps = dict(gcn=0, resgcn=3)[variant], g.GNNSTAGE_F32, 1, self.grad_in.ctypes.data, 1e-5
+        d.variant, d.dtype, d.need_input_grad, d.grad_in, d.ln_eps = dict(gcn=0, resgcn=3)[variant], g.GNNSTAGE_BF16 if bf16 else g.GNNSTAGE_F32, 1, self.grad_in.ctypes.data, 1e-5
         size = self.lib.gnnstage_workspace_size(C.byref(d))
         self.ws = np.zeros(size + 256, np.uint8)
         d.workspace, d.workspace_bytes = (self.ws.ctypes.data + 255) // 256 * 256, size
@@ -99,6 +99,14 @@ def _ln_reduces(rt, tied, whole):
             a = np.frombuffer(bytes(l.args), np.uint64).reshape(8, 4)  # per plane: partial, (n_parts, d), dgamma, dbeta
             out.append([int(x) for x in a[:l.grid[2], 2:].ravel()])
     return out
+
+
+def _long_products(rt, n, K):
+    """Grids of the weight-stationary products of a forward pass over one transform-first bf16 layer, 256 -> 200."""
+    st = _Stage("gcn", [256, 200], K, n=n, bf16=True)
+    rt.host_clear(-1)
+    assert st.forward() == 0
+    return [list(l.grid) for l in _launches(rt) if b"gemm_nt_bf16_ws" in l.name]
 
 
 def _timed(rt, variant, dims):
@@ -183,3 +191,10 @@ def test_a_pass_that_fails_does_not_count_as_run(runtime, variant, dims):
     got = _child(runtime, "_refused", variant, dims)
     assert got["forward"] == [[EHIP, EORDER, EORDER, 0]] * 3
     assert got["backward"] == [[EHIP, 0, EORDER, 0]] * 3
+
+
+@pytest.mark.parametrize("n", [65600, 66000, 98000, 131500])
+def test_one_long_product_fills_the_chip(runtime, n):
+    """Two persistent workgroups on each of the 256 compute units whatever the number of 64-row tiles (historical and current
+    rows of a single chunk: two products, one after the other)."""
+    assert _child(runtime, "_long_products", n, 1) == [[512, 1, 1]] * 2

@@ -1112,9 +1112,6 @@ int forward_cells(gnnstage *st, const Cell *cells, int n, hipStream_t stream) {
     } else if (s.tf[j] && !shared) {  // the chunk's current rows
       GemmNtArgs &g = nt[n_nt++] = nt_args(st, level_rows(st, st->cur, j, row0), st->level_dtype(j), s.dims[j], st->lay.Wt[j], s.ld[j], M, s.dims[j + 1], s.dims[j]);
       nt_out(g, st->at<char>(st->lay.Tc[j]) + (size_t)row0 * s.ld[j + 1] * celt, cd, s.ld[j + 1]);
-    } else if (s.sage()) {  // the vertex's own row through W_self, kept in fp32 until the layer's epilogue adds it
-      GemmNtArgs &g = nt[n_nt++] = nt_args(st, level_rows(st, st->cur, j, row0), st->level_dtype(j), s.dims[j], st->lay.Wt_self[j], s.ld[j], M, s.dims[j + 1], s.dims[j]);
-      nt_out(g, st->at<float>(st->lay.self_fwd) + (size_t)c.slot * st->lay.self_stride, DT_F32, s.ld[j + 1]);
     }
   }
   if (n_nt + n_ln > 0) {
@@ -1161,6 +1158,17 @@ int forward_cells(gnnstage *st, const Cell *cells, int n, hipStream_t stream) {
     }
   }
   HIP_TRY(st, run_spmm(st, sp, n, stream, 0, cells[0].j));
+  if (s.sage()) {  // the vertex's own row through W_self, kept in fp32 until the layer's epilogue adds it
+    for (int i = 0; i < n; ++i) {
+      const Cell &c = cells[i];
+      const int j = c.j;
+      GemmNtArgs &g = nt[i] = nt_args(st, level_rows(st, st->cur, j, cell_row0(st, c.k)), st->level_dtype(j), s.dims[j], st->lay.Wt_self[j], s.ld[j],
+                                      cell_rows(st, c.k), s.dims[j + 1], s.dims[j]);
+      nt_out(g, st->at<float>(st->lay.self_fwd) + (size_t)c.slot * st->lay.self_stride, DT_F32, s.ld[j + 1]);
+    }
+    Timed t(st, stream, 1, cells[0].j);
+    HIP_TRY(st, launch_gemm_nt(nt, n, cd, stream));
+  }
   n_nt = 0;
   for (int i = 0; i < n; ++i) {
     const Cell &c = cells[i];

@@ -37,15 +37,15 @@ class _Stage:
         import paper_2308_10087_amd as g
         from paper_2308_10087_amd import binding
         self.g, self.lib = g, binding.lib
-        L = len(dims) - 1
+        L, two = len(dims) - 1, 2 if variant == "sage" else 1  # GraphSage: [W_self ; W_neigh]
         col = (np.arange(n)[:, None] + np.array([0, 1, 7, 50])) % n
         row_ptr, col = np.arange(n + 1, dtype=np.int64) * 4, np.sort(col, axis=1).astype(np.int32).ravel()
         chunk_ptr, dims = (np.arange(K + 1, dtype=np.int64) * n) // K, np.asarray(dims, np.int32)
         rows = lambda ws: [np.zeros((n, int(w)), np.float32) for w in ws]
         vec = lambda ws: [np.zeros(int(w), np.float32) for w in ws]
         self.keep = dict(row_ptr=row_ptr, col_idx=col, chunk_ptr=chunk_ptr, dims=dims)
-        lists = dict(W=[np.zeros((int(dims[j]), int(dims[j + 1])), np.float32) for j in range(L)], cur=rows(dims), hist=rows(dims[:-1]),
-                     dW=[np.zeros((int(dims[j]), int(dims[j + 1])), np.float32) for j in range(L)], bias=vec(dims[1:]), dbias=vec(dims[1:]))
+        lists = dict(W=[np.zeros((two * int(dims[j]), int(dims[j + 1])), np.float32) for j in range(L)], cur=rows(dims), hist=rows(dims[:-1]),
+                     dW=[np.zeros((two * int(dims[j]), int(dims[j + 1])), np.float32) for j in range(L)], bias=vec(dims[1:]), dbias=vec(dims[1:]))
         if variant == "resgcn":
             lists.update(ln_gamma=vec(dims[:-1]), ln_beta=vec(dims[:-1]))
             for i, name in enumerate(("d_ln_gamma", "d_ln_beta")):
@@ -59,7 +59,7 @@ class _Stage:
             self.keep["list " + name] = (a, p)
             setattr(d, name, C.cast(p, C.c_void_p))
         self.grad_in, self.grad_out = np.zeros((n, int(dims[0])), np.float32), np.zeros((n, int(dims[-1])), np.float32)
-        d.variant, d.dtype, d.need_input_grad, d.grad_in, d.ln_eps = dict(gcn=0, resgcn=3)[variant], g.GNNSTAGE_BF16 if bf16 else g.GNNSTAGE_F32, 1, self.grad_in.ctypes.data, 1e-5
+        d.variant, d.dtype, d.need_input_grad, d.grad_in, d.ln_eps = dict(gcn=0, sage=2, resgcn=3)[variant], g.GNNSTAGE_BF16 if bf16 else g.GNNSTAGE_F32, 1, self.grad_in.ctypes.data, 1e-5
         size = self.lib.gnnstage_workspace_size(C.byref(d))
         self.ws = np.zeros(size + 256, np.uint8)
         d.workspace, d.workspace_bytes = (self.ws.ctypes.data + 255) // 256 * 256, size
@@ -107,6 +107,14 @@ def _long_products(rt, n, K):
     rt.host_clear(-1)
     assert st.forward() == 0
     return [list(l.grid) for l in _launches(rt) if b"gemm_nt_bf16_ws" in l.name]
+
+
+def _forward_kinds(rt, variant, dims, K):
+    """Aggregations (a) and products (p) of a forward pass in the order of their launches."""
+    st = _Stage(variant, dims, K)
+    rt.host_clear(-1)
+    assert st.forward() == 0
+    return "".join("a" if b"spmm" in l.name else "p" if b"gemm_nt" in l.name else "" for l in _launches(rt))
 
 
 def _timed(rt, variant, dims):
@@ -198,3 +206,11 @@ def test_one_long_product_fills_the_chip(runtime, n):
     """Two persistent workgroups on each of the 256 compute units whatever the number of 64-row tiles (historical and current
     rows of a single chunk: two products, one after the other)."""
     assert _child(runtime, "_long_products", n, 1) == [[512, 1, 1]] * 2
+
+
+@pytest.mark.parametrize("K", [1, 3])
+def test_graphsage_adds_its_two_products_one_after_the_other(runtime, K):
+    """The product with W_self writes fp32 rows that the layer's other product reads: with the aggregation between the two they
+    have left the caches."""
+    got = _child(runtime, "_forward_kinds", "sage", [32, 24, 40], K)
+    assert set(got.replace("aa", "a").split("a")[1:]) == {"pp"}

@@ -392,8 +392,11 @@ __device__ __forceinline__ void spmm_short_rows(const SpmmArgs &a, int64_t first
 // step s + U, unconditionally, so the number of younger loads at every wait is a compile-time constant
 // and U - 1 steps of gathers stay in flight while one is consumed.  Per step the vector ALU only adds
 // the lane offset to the record's address and expands the weight (one byte permute, four selects).
+// Waves per SIMD: seven where their registers hold the loop.  Four column blocks need 86; held to 72 they went through scratch
+// memory inside the loop, more so with the operand sets side by side: two forward aggregations of 250 k rows of width 512 took
+// 890 us, 1,015 with the operand sets, and take 597 us with five waves (width 384 1,090 -> 584; six waves still spill: 742, 753).
 template <typename Tout, int NT, int U, bool FULL>
-__global__ __launch_bounds__(256, (NT * U <= 8) ? 7 : 1) void spmm_ring_kernel(const Batch<SpmmArgs> ba) {
+__global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ring_kernel(const Batch<SpmmArgs> ba) {
   const SpmmArgs &a = ba.sub[blockIdx.z];  // (a copy holds more registers than the gather loop has to spare: 47.7 -> 48.8 us)
   constexpr int TILE_W = NT * 128;
   constexpr int KB = 2;    // metadata batches per phase

@@ -459,6 +459,36 @@ def test_scratch_of_cells_that_run_side_by_side_is_bounded():
     assert _workspace(2, n, dims, [0, n - 300, n - 200, n - 100, n]) <= one + (1 << 30)
 
 
+def _scratch_bytes():
+    """{kernel: bytes of scratch memory per lane} from the metadata of the built code object."""
+    import struct
+    import subprocess
+    import tempfile
+    data, out = open(os.path.join(ROOT, "paper_2308_10087_amd", "libgnnstage.so"), "rb").read(), {}
+    for m in re.finditer(b"\x7fELF", data):
+        at = m.start()
+        if struct.unpack_from("<H", data, at + 18)[0] != 224:  # e_machine: AMDGPU
+            continue
+        sections, = struct.unpack_from("<Q", data, at + 40)
+        size, count = struct.unpack_from("<HH", data, at + 58)
+        with tempfile.NamedTemporaryFile(suffix=".co") as f:
+            f.write(data[at:at + sections + size * count])
+            f.flush()
+            notes = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", f.name], capture_output=True, text=True, check=True).stdout
+        for k in notes.split("- .agpr_count:")[1:]:
+            out[re.search(r"\.name:\s+(\S+)", k)[1]] = int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", k)[1])
+    return out
+
+
+def test_aggregation_kernels_keep_their_loops_in_registers():
+    """Spills of the gather loop cost wide rows half of their rate.  (Not held to it: the deeper queues that only
+    GNNSTAGE_SPMM_UNROLL selects.)"""
+    scratch = {k: v for k, v in _scratch_bytes().items() if "spmm" in k}
+    assert len(scratch) > 40
+    deeper = re.compile(r"spmm_ring_kernelI\w+Li[124]ELi[48]E")
+    assert not {k: v for k, v in scratch.items() if v > 0 and not deeper.search(k)}
+
+
 def test_generated_graphs_are_symmetric_sorted_and_reproducible():
     w = CONFIGS["c3_s"]
     a_ptr, a_col = make_graph(w)

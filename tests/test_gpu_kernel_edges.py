@@ -76,18 +76,7 @@ def test_fp32_forward_sums_do_not_depend_on_the_chunks(dims):
     assert torch.equal(top[0].cur[1], top[1].cur[1])
 
 
-@pytest.mark.parametrize("variant,dtype,dims,k,kw", [
-    ("gcn", "f32", (20, 24, 40, 16, 32), 5, {}), ("gcn", "bf16", (100, 128, 64, 64), 7, {}), ("sage", "f32", (33, 36, 20), 4, {"dropout_p": 0.4}),
-    ("sage", "bf16", (64, 128, 128), 3, {}), ("gcnii", "bf16", (64,) * 12, 11, {}), ("gcnii", "f32", (40, 40), 6, {}),
-    ("resgcn", "f32", (36,) * 5, 6, {"dropout_p": 0.3}), ("resgcn", "bf16", (128,) * 4, 9, {}), ("gcn", "bf16", (602, 100, 100), 1, {})])
-def test_whole_pass_calls_equal_the_chunk_calls(variant, dtype, dims, k, kw):
-    """More and fewer chunks than layers, more of both than cells run side by side, an empty chunk, one chunk only: levels and
-    what flows back are the same bits; parameter gradients the same sums in another order (fp32, a few hundred terms)."""
-    n = 700
-    cp = np.sort(np.concatenate([[0, n], np.random.default_rng(3).integers(1, n, k - 1)])).astype(np.int64)
-    if k > 3:
-        cp[2] = cp[1]
-    p = make_problem(small(n=n, k=k, dims=dims, variant=variant, dtype=dtype, deg=9.0), chunk_ptr=cp, bias_std=0.05, first_stage=False, dropout_seed=5, **kw)
+def _whole_equals_chunks(p):
     whole, by_chunk = GpuRun(p), GpuRun(p)
     for _ in range(2):  # the second pass finds the scratch of the first
         whole.run()
@@ -106,6 +95,29 @@ def test_whole_pass_calls_equal_the_chunk_calls(variant, dtype, dims, k, kw):
     for name in ("dW", "dbias", "d_ln_gamma", "d_ln_beta"):
         for a, b in zip(getattr(whole, name) or [], getattr(by_chunk, name) or []):
             assert (a - b).abs().max() <= 1e-5 * b.abs().max() + 1e-30, name
+
+
+@pytest.mark.parametrize("variant,dtype,dims,k,kw", [
+    ("gcn", "f32", (20, 24, 40, 16, 32), 5, {}), ("gcn", "bf16", (100, 128, 64, 64), 7, {}), ("sage", "f32", (33, 36, 20), 4, {"dropout_p": 0.4}),
+    ("sage", "bf16", (64, 128, 128), 3, {}), ("gcnii", "bf16", (64,) * 12, 11, {}), ("gcnii", "f32", (40, 40), 6, {}),
+    ("resgcn", "f32", (36,) * 5, 6, {"dropout_p": 0.3}), ("resgcn", "bf16", (128,) * 4, 9, {}), ("gcn", "bf16", (602, 100, 100), 3, {})])
+def test_whole_pass_calls_equal_the_chunk_calls(variant, dtype, dims, k, kw):
+    """More and fewer chunks than layers, more of both than cells run side by side, an empty chunk: levels and what flows back
+    are the same bits; parameter gradients the same sums in another order (fp32, a few hundred terms)."""
+    n = 700
+    cp = np.sort(np.concatenate([[0, n], np.random.default_rng(3).integers(1, n, k - 1)])).astype(np.int64)
+    if k > 3:
+        cp[2] = cp[1]
+    p = make_problem(small(n=n, k=k, dims=dims, variant=variant, dtype=dtype, deg=9.0), chunk_ptr=cp, bias_std=0.05, first_stage=False, dropout_seed=5, **kw)
+    _whole_equals_chunks(p)
+
+
+@pytest.mark.parametrize("variant,dims", [("gcn", (64, 128, 128, 256, 256)), ("gcnii", (128,) * 6)])
+def test_whole_pass_products_that_only_together_are_long(variant, dims, monkeypatch):
+    """Chunks of 100 rows: below the rows from which the weight-stationary product runs, a diagonal of three and more above them.
+    Whole passes take that kernel, several products in a launch, the chunk calls the tiled one; the results are the same bits."""
+    monkeypatch.setenv("GNNSTAGE_GEMM_WS_MIN_ROWS", "250")
+    _whole_equals_chunks(make_problem(small(n=700, k=7, dims=dims, variant=variant, dtype="bf16", deg=9.0), bias_std=0.05, first_stage=False))
 
 
 @pytest.mark.parametrize("dtype,n,bound", [("f32", 169343, 1.8e-7), ("bf16", 300000, 1.2e-7)])

@@ -327,12 +327,12 @@ def test_weight_gradients_per_chunk_instead_of_one_product_per_layer(monkeypatch
     _parity(p, TOL_F32 if name == "c0" else TOL_BF16)
 
 
-@pytest.mark.parametrize("variant,dtype", [("gcn", "f32"), ("gcn", "bf16"), ("sage", "bf16"), ("gcnii", "bf16")])
+@pytest.mark.parametrize("variant,dtype", [("gcn", "f32"), ("gcn", "bf16"), ("sage", "bf16"), ("gcnii", "bf16"), ("resgcn", "f32"), ("resgcn", "bf16")])
 def test_flushing_the_weight_gradients_of_a_backward_pass_that_stops_early(variant, dtype):
     """gnnstage_flush_weight_gradients after every backward call: the gradients then hold exactly the
     contributions of the calls made so far (compared with the oracle after each call), nothing is added twice,
     and the last call of the pass leaves the same totals."""
-    dims = (16, 16, 16) if variant == "gcnii" else (24, 40, 48)
+    dims = (16, 16, 16) if variant in ("gcnii", "resgcn") else (24, 40, 48)
     w = small(n=900, k=5, dims=dims, variant=variant, dtype=dtype)
     p = make_problem(w, chunk_ptr=graphs.ragged_chunks(900, 5, 9), first_stage=False)
     tol = TOL_F32 if dtype == "f32" else TOL_BF16

@@ -2,8 +2,9 @@
  * gnntrain — the epoch loop of Algorithm 1 around gnnstage handles, on one MI355X (gfx950).  C ABI.
  *
  * One epoch: draw the chunk order (Section 3.4, first technique: shuffled at the beginning of every
- * epoch); every chunk, in that order, goes through all stages (first to last) and the loss head; the
- * backward pass walks the chunks in the reverse order, last stage first; the weights are updated
+ * epoch); every stage, first to last, takes all chunks in that order (gnnstage_forward_pass; chunk by chunk through all
+ * stages where a stage's level-0 history is the level below it), then the loss head all rows; the
+ * backward pass walks the stages from the last to the first, chunks in the reverse order; the weights are updated
  * (Algorithm 1, last line: the plain gradient step; Section 5 trains with Adam, learning rate 0.001);
  * the historical embeddings are refreshed after the epochs alpha, 2 alpha, ... (Section 3.4, second
  * technique: epoch t reads the embeddings of epoch alpha * floor((t - 1) / alpha)).
@@ -51,7 +52,7 @@ typedef struct {
   int32_t n_classes;
   const void *head_W;        /* DEVICE d_top x n_classes, dtype of the last stage */
   const float *head_b;       /* DEVICE fp32 n_classes */
-  float *head_dW;            /* DEVICE fp32 d_top x n_classes, "+=" over the chunks */
+  float *head_dW;            /* DEVICE fp32 d_top x n_classes, "+=" over the rows */
   float *head_db;            /* DEVICE fp32 n_classes */
   const int32_t *labels;     /* DEVICE, one class id in [0, n_classes) per vertex */
   const uint8_t *train_mask; /* DEVICE, one byte per vertex (non-zero = labelled); NULL = all vertices */
@@ -71,9 +72,9 @@ typedef struct {
   size_t workspace_bytes;
 } gnntrain_desc;
 
-/* Device bytes the loop needs: optimiser moments, logits of one chunk, gradient of the logits for all
- * vertices, gradient rows of the last level for one chunk, per-vertex losses, staged head weights,
- * split-reduction scratch.  Host-only; 0 on an invalid descriptor. */
+/* Device bytes the loop needs: optimiser moments, logits of up to 131,072 vertices, gradient of the logits and
+ * gradient rows of the last level for all vertices, per-vertex losses, staged head weights, split-reduction
+ * scratch.  Host-only; 0 on an invalid descriptor. */
 size_t gnntrain_workspace_size(const gnntrain_desc *desc);
 
 /* Validates the descriptor against the stage handles (chaining of the level buffers, label range),

@@ -4,7 +4,7 @@
 //   TN:  dW[I x O] += s * A[M x I]^T . B[M x O]    weight gradient (reduction over chunk rows)
 //
 // bf16 operands go through the gfx950 matrix cores (v_mfma_f32_32x32x16_bf16, fp32
-// accumulation), fp32 operands of the fp32 stage through v_mfma_f32_32x32x2_f32 / 16x16x4.
+// accumulation), fp32 operands of the fp32 stage through v_mfma_f32_16x16x4_f32.
 // Bias / ReLU / GCNII residual terms are applied in the epilogue on the fp32 accumulators.
 // Bt and B always live in the library's zero-padded internal buffers (16-byte aligned rows);
 // A may also be a caller-owned level buffer of any width and of fp32 or bf16 type, in which case
@@ -843,7 +843,7 @@ __global__ __launch_bounds__(512) void gemm_tn_bf16_wide_kernel(const GemmTnArgs
 }
 
 // ------------------------------------------------------------------------------------ fp32
-// fp32 products run on the matrix cores too (v_mfma_f32_32x32x2_f32 and 16x16x4: fp32 operands, fp32 multiply-adds, the
+// fp32 products run on the matrix cores too (v_mfma_f32_16x16x4_f32: fp32 operands, fp32 multiply-adds, the
 // same 157 TFLOP/s as the vector ALU's best, without its operand traffic).
 
 // Four consecutive output columns n .. n + 3 of row m: epilogue, dropout of the layer's output, store.  Columns from N on

@@ -93,8 +93,11 @@ Tuning read_tuning() {
 
 // Forward aggregations of fp32 stages.  What ReLU passes hangs on the last bit of a pre-activation: a stage of 5 k vertices
 // of width 1000 has one or two of 20 M elements so close to zero that another order of the same sum decides otherwise, and one
-// such element moves a weight gradient by 2e-3.  So these sums keep one order whatever a launch's size suggests: whole pieces
-// of at least 256 entries, added entry by entry.  (Pieces of 32 here: 6.7 against 7.1 ms per step of that stage.)
+// such element moves a weight gradient by 2e-3.  So these pieces don't get shorter with the launch: 256 entries at least, as in
+// large launches (4.2 M entries and more: longer, see below).  The order of a row's sum follows from the plan of its chunk and the
+// row width alone: the pieces (rows of class_min_row entries and more are cut at source-class bounds too, which depend on the
+// chunk's entries), the lane groups of the kernel, the phases of the reduce.  (Pieces of 32 here: 6.7 against 7.1 ms per step
+// of that stage.)
 constexpr int kLeastPieceF32Fwd = 256;
 
 // Longest piece of a row that one wavefront handles in an aggregation over `entries` entries.  A wave

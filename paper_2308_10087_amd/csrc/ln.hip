@@ -178,8 +178,6 @@ __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBac
   }
 }
 
-// One workgroup per 64 entries of the 2 x d sums: 16 wavefronts each add every 16th partial row, then the 16
-// slice sums are added in order.
 // ---- bf16 rows whose width is 8 x a power of two: LPR lanes per row, 16 bytes per lane, 64 / LPR rows per
 // wavefront at a time (the same arithmetic as above, with the loads and stores vectorised)
 typedef bf16_t bf16x8_ln __attribute__((ext_vector_type(8)));
@@ -346,7 +344,8 @@ inline int vec_lanes(int d, int dtype, const void *p, int ld) {
   return (d == 64 || d == 128 || d == 256 || d == 512) ? d / 8 : 0;
 }
 
-// n_parts: the partial rows of a sub-launch are its workgroups in the launch before
+// One workgroup per 64 entries of the 2 x d sums: 16 wavefronts each add every 16th partial row, then the 16
+// slice sums are added in order.  n_parts: the partial rows of a sub-launch are its workgroups in the launch before.
 struct LnReduceArgs {
   const float *partial;
   int32_t n_parts, d;

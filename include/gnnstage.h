@@ -135,8 +135,8 @@ typedef struct {
 } gnnstage_desc;
 
 /* Device bytes the stage needs inside desc->workspace (graph tables, transposed index,
- * launch schedule, saved aggregations for backward, gradient rows, scratch of up to eight layers
- * that run side by side in whole passes: at most 1 GiB, or a sixteenth of the workspace, beyond one's).  Host-only computation;
+ * launch schedule, saved aggregations for backward, gradient rows, room for the partial sums
+ * of all chunks at once: at most 1 GiB, or a sixteenth of the workspace, beyond one chunk's).  Host-only computation;
  * returns 0 when the descriptor's sizes are invalid.  Reads row_ptr, col_idx, chunk_ptr and
  * dims; no other pointer field is dereferenced. */
 size_t gnnstage_workspace_size(const gnnstage_desc *desc);
@@ -168,13 +168,12 @@ int stage_backward_chunk(gnnstage_t *st, int32_t chunk_id, const void *grad_out_
 
 /* A whole forward / backward pass in one call: the same work as stage_forward_chunk for order[0], order[1], ...
  * at positions 0, 1, ..., and as stage_backward_chunk for order[n_order - 1], ..., order[0] (order is the FORWARD order;
- * grad_out: DEVICE, n_vertices x d_L, level dtype, all rows).  When order names every chunk once, layers of different chunks
- * that do not depend on each other run side by side: layer j of the chunk at position p with layer j + 1 of the one at
- * position p - 1, and so on.  Anything else (fewer chunks, a wrong order) is walked chunk by chunk, with the errors of the
+ * grad_out: DEVICE, n_vertices x d_L, level dtype, all rows).  When order names every chunk once, all chunks of a layer run side by
+ * side: layer j of a chunk reads rows of level j (on the way back gradient rows of layer j) alone, and history does not change inside a pass, so a
+ * pass is one round of launches per layer.  Anything else (fewer chunks, a wrong order) is walked chunk by chunk, with the errors of the
  * calls above.  Levels, grad_in and grad_h0 are the same bits as from the chunk calls; parameter gradients (dW, dbias,
  * d_ln_gamma, d_ln_beta) are the same sums, partly in another order.  One by one run the chunks also where launches are timed
- * (gnnstage_profile_enable), where a level above 0 is its own history, with dense blocks and with 2 M entries and more per
- * chunk on average.  A call that returns an error halfway has not run the pass: a new forward pass has to follow.
+ * (gnnstage_profile_enable) and where a level above 0 is its own history.  A call that returns an error halfway has not run the pass: a new forward pass has to follow.
  * Asynchronous on hip_stream. */
 int gnnstage_forward_pass(gnnstage_t *st, const int32_t *order, int32_t n_order, void *hip_stream);
 int gnnstage_backward_pass(gnnstage_t *st, const int32_t *order, int32_t n_order, const void *grad_out, void *hip_stream);
@@ -354,8 +353,8 @@ int gnnstage_dense_plan_destroy(gnnstage_dense_plan *plan);
  * gnnstage_profile_enable switches all kinds on or off; gnnstage_profile_select takes a bit mask of kinds
  * (bit k = kind k), for callers that want the events of a few kinds only inside a timed region (every
  * timed launch costs two event records on the stream).
- * While any kind is on, whole passes run chunk by chunk and what follows the last chunk layer by layer, so that every timed
- * launch belongs to one layer: the times are those of the chunk calls, not of passes that run layers side by side.
+ * While any kind is on, whole passes and what follows their last chunk run chunk by chunk: the times are those of the chunk
+ * calls, not of passes whose chunks run side by side.
  */
 enum { GNNSTAGE_NKINDS = 8 };
 int gnnstage_profile_enable(gnnstage_t *st, int32_t on);

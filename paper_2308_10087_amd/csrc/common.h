@@ -21,6 +21,26 @@ __host__ __device__ inline bool mask_test(const ChunkMask &m, uint32_t c) {
 }
 
 // ---- aggregation (SpMM with current/history select) ---------------------------------
+// The same for a mask that a whole wave holds, all of whose lanes ask at once.  Up to 64 chunks (many false, uniform) it is one
+// shift of the first word; above that lane i holds the mask's 32-bit word i and answers for it.  Selects among four words
+// instead cost an aggregation kernel eight registers, which it does not have to spare (62 against 54).
+struct WaveMask {
+  uint64_t first;
+  uint32_t word;
+};
+__device__ inline WaveMask wave_mask(const ChunkMask &m, bool many) {
+  WaveMask w{m.w[0], 0u};
+  if (many) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w.word = (threadIdx.x & 63) == i ? (uint32_t)(m.w[i >> 1] >> (32 * (i & 1))) : w.word;
+  }
+  return w;
+}
+__device__ inline bool mask_test(const WaveMask &m, uint32_t c, bool many) {
+  if (many) return (((uint32_t)__builtin_amdgcn_ds_bpermute((int)(c >> 5) << 2, (int)m.word) >> (c & 31u)) & 1u) != 0;
+  return ((m.first >> (c & 63u)) & 1ull) != 0;
+}
+
 enum SpmmEpilogue : int {
   SPMM_PLAIN = 0,     // out = acc
   SPMM_MIX = 1,       // out = s_acc * acc + s_aux * aux[row]      (GCNII initial residual)
@@ -51,47 +71,63 @@ __host__ __device__ inline bool dropout_keep(const LnDropout &dp, int64_t u, int
   return (uint32_t)(r >> 40) >= dp.threshold;
 }
 
+// What a row chunk selects in a launch over many chunks: the source chunks it reads as processed, and the source classes
+// from which it gathers anything (launches that drop unselected entries).  One entry per row chunk, written by
+// launch_pass_tables; 64 bytes, read through the scalar cache.
+struct PassChunk {
+  ChunkMask mask;
+  uint32_t classes;
+  uint32_t pad[7];
+};
+static_assert(sizeof(PassChunk) == 64, "one scalar load of sixteen words");
+
+// One scalar load.  (Three arrays indexed by the XCD, one of them of bytes, are not: the compiler takes the index of one as
+// the base of the next, and the scalar unit drops the low bits of such an address.)
+struct alignas(16) XcdRun {
+  int32_t cls, group0, groups, unused;
+};
+
 struct SpmmArgs {
   // sparse structure: packed index words (vertex | chunk << vbits) and weights
   const uint32_t *pidx;
   const float *val;
   // launch schedule
-  const int32_t *task_row;
+  const int32_t *task_row;   // -1: a filler behind a chunk's short rows
   const int64_t *task_e0;
-  const int32_t *task_ne;
-  const int32_t *task_slot;
-  int64_t n_tasks;
-  // The last n_short tasks are whole rows of at most a few entries (no partial slot).  The matrix-core kernel gives
-  // them to extra workgroups of the same launch in which every 16-lane group owns a row of its own: a wave per
-  // row would spend its life waiting for three dependent round trips to move a kilobyte or two.  The launcher
-  // takes them off n_tasks; the vector-ALU kernel ignores the field and serves them like any other task.
-  int64_t n_short;
-  int64_t n_main_blocks;  // set by the launcher: workgroups from this index on serve the short rows
-  // XCD-aware serving order.  Tasks [0, tail_task0) are pieces grouped by source-id class (class c: tasks cls_off[c] ..
-  // cls_off[c + 1]).  Workgroups are dealt round-robin to the 8 XCDs; the groups of four tasks of the active classes,
-  // one class after the other, are cut into eight runs, and XCD x (workgroups with index % 8 == x) serves xcd_groups[x] of
-  // them from group xcd_group0[x] of class xcd_cls[x] on.  Workgroups from n_class_blocks on serve the tail.
-  const int32_t *cls_off;
-  int32_t xcd_group0[8], xcd_groups[8];
-  uint8_t xcd_cls[8];
+  const uint32_t *task_ne;   // entries | row chunk << kTaskChunkShift
+  const int32_t *task_slot;  // partial row, counted over all chunks; -1: the task finishes its row
+  // XCD-aware serving order.  Class c's pieces are tasks [cls_begin[c], cls_end[c]).  Workgroups are dealt round-robin to the
+  // 8 XCDs; the groups of four tasks of the active classes, one class after the other, are cut into eight runs, and XCD x
+  // (workgroups with index % 8 == x) serves xcd[x].groups of them from group xcd[x].group0 of class xcd[x].cls on.
+  // Workgroups from n_class_blocks on serve the tail: tasks [tail0, tail0 + n_tail), then the short rows.
+  int32_t cls_begin[kMaxClasses], cls_end[kMaxClasses];
+  XcdRun xcd[8];
   int32_t n_class_blocks;
-  int64_t tail_task0;
+  int64_t tail0, n_tail;
+  // Whole rows of at most a few entries (no partial slot), every chunk's filled up to a multiple of four.  The matrix-core
+  // kernel gives them to extra workgroups of the same launch in which every 16-lane group owns a row of its own: a wave per
+  // row would spend its life waiting for three dependent round trips to move a kilobyte or two.  The vector-ALU kernel and
+  // rows wider than 256 columns take them like any other task.
+  int64_t short0, n_short;
+  int64_t n_main_blocks;  // set by the launcher: workgroups from this index on serve the short rows
   const uint8_t *slot_class;  // class of every partial slot (255: none); pieces of inactive classes are not run
   uint32_t active_classes;
   int32_t all_classes_active;
   // long rows: pieces summed by the reduce kernel
   const int32_t *lr_row;
   const int32_t *lr_slot0;
-  const int32_t *lr_nslots;
+  const uint32_t *lr_nslots;  // pieces | row chunk << kTaskChunkShift
   int64_t n_long;
-  float *partial;  // [n_slots][d] fp32
-  // dense-block partial sums of a cut row: rows lr_dense0[i] + 128 * g (g < lr_ndense[i]) of dense_partial,
-  // one per item of the row's row block; lr_item0[i] is the first of those items (for the activity test)
+  float *partial;   // [n_slots][d] fp32, first row: slot slot0
+  int64_t slot0;
+  // dense-block partial sums of a cut row: rows lr_dense0[i] + 128 * g (g < lr_ndense[i]), counted over all chunks, of
+  // dense_partial, one per item of the row's row block; lr_item0[i] is the first of those items (for the activity test)
   const int32_t *lr_dense0;
   const int32_t *lr_ndense;
   const int32_t *lr_item0;
   const ChunkMask *item_chunks;
-  const float *dense_partial;
+  const float *dense_partial;  // first row: item item0
+  int64_t item0;
   int32_t drop_unselected;  // the launch skips unselected entries: items without a chunk in the mask were not run
   // gathered operand: rows of width d, leading dimension src_ld
   const void *src_sel;    // read when the neighbour's chunk is in the mask
@@ -99,6 +135,8 @@ struct SpmmArgs {
   int32_t d;
   int32_t src_ld;
   int32_t vbits;
+  int32_t many_chunks;    // more than 64
+  const PassChunk *pass;  // masks by row chunk; nullptr: mask for all rows
   ChunkMask mask;
   // output rows: out[(row - out_row0) * out_ld + c], c < d; columns [d, out_ld) get zeros
   void *out;
@@ -110,8 +148,8 @@ struct SpmmArgs {
   int32_t aux_ld;
   float s_acc, s_aux;
   const float *bias;  // SPMM_BIAS_RELU
-  const void *add;    // SPMM_ADD / SPMM_ADD_MASK: rows indexed by row - add_row0, same dtype as src
-  int32_t add_ld;
+  const void *add;    // SPMM_ADD / SPMM_ADD_MASK: rows indexed by row - add_row0, same dtype as src; may be the output rows
+  int32_t add_ld;     // themselves where d is a multiple of 8 (no column then belongs to two lanes)
   int64_t add_row0;
   float mask_scale = 1.f;  // SPMM_MASK / SPMM_ADD_MASK: what passes the mask is scaled (1 / (1 - rate) of that dropout)
   // kernel choice (measurement and test switches, set by the stage from what it read at create)
@@ -119,38 +157,58 @@ struct SpmmArgs {
   int32_t long_pieces = 0; // rows are cut into pieces of 256 entries or more (forward aggregations of fp32 stages)
   int32_t unroll = 2;      // gather slots per wave of the matrix-core aggregation: 2, 4 or 8
 };
+constexpr int kTaskChunkShift = 24;  // a piece or an uncut row has fewer than 2^24 entries
+constexpr uint32_t kTaskCountMask = (1u << kTaskChunkShift) - 1u;
+static_assert(kMaxChunks <= 256, "the chunk shares a word with a count");
+static_assert(sizeof(SpmmArgs) <= 4096, "kernel arguments");
 
-// which task the wave `wave` of workgroup `b` runs (-1: none)
-__device__ inline int64_t spmm_task_index(const SpmmArgs &a, unsigned b, int wave) {
+// which task the wave `wave` of workgroup `b` runs (-1: none); cls: its class (-1: none)
+__device__ inline int64_t spmm_task_index(const SpmmArgs &a, unsigned b, int wave, int &cls) {
+  cls = -1;
   if (b < (unsigned)a.n_class_blocks) {
-    const int x = b & 7;
+    const XcdRun run = a.xcd[b & 7];
     int g = (int)(b >> 3);
-    if (g >= a.xcd_groups[x]) return -1;
-    g += a.xcd_group0[x];
-    for (int q = a.xcd_cls[x]; q < kMaxClasses; ++q) {  // the runs cover exactly the active classes' groups
-      const int t0 = a.cls_off[q], nt = a.cls_off[q + 1] - t0, ng = ((a.active_classes >> q) & 1u) ? (nt + 3) >> 2 : 0;
+    if (g >= run.groups) return -1;
+    g += run.group0;
+    for (int q = run.cls; q < kMaxClasses; ++q) {  // the runs cover exactly the active classes' groups
+      const int t0 = a.cls_begin[q], nt = a.cls_end[q] - t0, ng = ((a.active_classes >> q) & 1u) ? (nt + 3) >> 2 : 0;
       if (g < ng) {
         const int t = g * 4 + wave;
+        cls = q;
         return t < nt ? t0 + t : -1;
       }
       g -= ng;
     }
     return -1;
   }
-  const int64_t t = a.tail_task0 + (int64_t)(b - a.n_class_blocks) * 4 + wave;
-  return t < a.n_tasks ? t : -1;
+  int64_t t = (int64_t)(b - a.n_class_blocks) * 4 + wave;
+  if (t < a.n_tail) return a.tail0 + t;
+  t -= (a.n_tail + 3) / 4 * 4;
+  return t >= 0 && t < a.n_short ? a.short0 + t : -1;
+}
+// The mask of a row chunk; chunk is the same for the whole wave.  The table is read through the scalar cache: by the time
+// a wave has its index words it has its mask.
+__device__ inline ChunkMask spmm_row_mask(const PassChunk *pass, const ChunkMask &mask, uint32_t chunk, uint32_t &classes) {
+  classes = 0xffffffffu;
+  if (pass == nullptr) return mask;
+  typedef __attribute__((address_space(4))) const PassChunk const_chunk;
+  const const_chunk *p = (const const_chunk *)(uintptr_t)(pass + chunk);
+  ChunkMask m;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) m.w[i] = p->mask.w[i];
+  classes = p->classes;
+  return m;
 }
 
 // ---- several launches in one -------------------------------------------------------------------
-// The cells (chunk, layer) of a pass on one anti-diagonal do not depend on each other; their launches of the same kernel run
-// as one, operand sets side by side: sub-launch z is the grid's plane z, so that a workgroup's operands are one load away.
-// Planes are as wide as the widest sub-launch; workgroups past the end of theirs return.
+// Launches of one kernel that do not depend on each other run as one, operand sets side by side: sub-launch z is the grid's
+// plane z, so that a workgroup's operands are one load away.  Planes are as wide as the widest sub-launch; workgroups past the
+// end of theirs return.
 constexpr int kBatch = 8;  // the kernel arguments stay below 4 KB
 template <typename A>
 struct Batch {
   A sub[kBatch];
 };
-static_assert(sizeof(Batch<SpmmArgs>) <= 4096, "kernel arguments");
 
 // ---- dense blocks of an aggregation (bf16 rows of width 128 or 256) ---------------------------
 // After ordering rows and columns by degree, the blocks that hold many entries are multiplied as dense
@@ -160,7 +218,8 @@ static_assert(sizeof(Batch<SpmmArgs>) <= 4096, "kernel arguments");
 constexpr int kDenseRB = 128, kDenseCB = 64;
 constexpr int kDenseMaxItemBlocks = 32;  // blocks one workgroup multiplies before it writes its partial tile
 struct DenseArgs {
-  const int32_t *item_rb;         // row block (inside the chunk) of every item of this launch
+  const int32_t *item_rs;         // first row-scale slot of every item of this launch
+  const int32_t *item_chunk;      // its row chunk
   const int64_t *item_b0;         // its first block
   const int32_t *item_nb;         // and how many
   const ChunkMask *item_chunks;   // chunks its blocks' columns come from
@@ -172,12 +231,13 @@ struct DenseArgs {
   // (word t: row t / 2, columns 32 * (t % 2) ..), s per column slot (0 = padding) and per row position of the chunk
   const uint32_t *bits;
   const float *colscale;
-  const float *rowscale;          // [row blocks of the chunk * 128], zero past the chunk's last row
+  const float *rowscale;          // 128 slots per row block, zero past a chunk's last row
   const void *zero_row;           // at least 512 bytes of zeros, 16-byte aligned
   const uint32_t *colslot;        // vertex | chunk << vbits of every column slot, 0xffffffff = padding
   const void *src_sel;            // rows of vertices whose chunk is in the mask
   const void *src_unsel;          // rows of the others; nullptr => they contribute zero
   int32_t d, src_ld, vbits;
+  const PassChunk *pass;          // as in SpmmArgs
   ChunkMask mask;
   float *partial;                 // [n_items][128][d]
 };
@@ -192,13 +252,20 @@ enum DType : int { DT_F32 = 0, DT_BF16 = 1 };
 
 // src dtype -> out dtype; returns hipError_t as int.  launch_spmm runs the per-task kernel,
 // launch_spmm_reduce adds the pieces of long rows (needed whenever a.n_long > 0).
-// Both take n launches that do not depend on each other and merge them where they run the same kernel.
-struct SpmmLaunch {
-  SpmmArgs a;
-  int src_dtype, out_dtype;
+int launch_spmm(const SpmmArgs &a, int src_dtype, int out_dtype, hipStream_t s);
+int launch_spmm_reduce(const SpmmArgs &a, int src_dtype, int out_dtype, hipStream_t s);
+
+// The tables of a pass whose chunks run side by side, from the chunks' places in the forward order (pos[chunk]).  Row chunk c
+// selects: forward, the chunks up to its own; backward, those from its own on (their backward work comes first); earlier,
+// those in front of it (the readers that saw the historical rows of c).  classes_*: see PassChunk, for the last two.
+struct PassTableArgs {
+  PassChunk *forward, *backward, *earlier;  // [K] each
+  int32_t K;
+  uint8_t pos[kMaxChunks];
+  uint32_t classes_backward[kMaxChunks], classes_earlier[kMaxChunks];
 };
-int launch_spmm(const SpmmLaunch *l, int n, hipStream_t s);
-int launch_spmm_reduce(const SpmmLaunch *l, int n, hipStream_t s);
+static_assert(sizeof(PassTableArgs) <= 4096, "kernel arguments");
+int launch_pass_tables(const PassTableArgs &a, hipStream_t s);
 
 // ---- dense transforms -------------------------------------------------------------------
 enum GemmEpilogue : int {
@@ -234,14 +301,11 @@ struct GemmNtArgs {
   int32_t out_ld;
   int32_t out_pad;  // columns [N, out_pad) of every output row are written as zeros (0: none)
   int32_t vec_epi;  // set by the launcher: the epilogue may use 16-byte accesses
-  int32_t ws_blocks;  // set by the launcher: workgroups of a persistent kernel that share this product's row tiles
   float mask_scale = 1.f;  // EPI_MASK: what passes the mask is scaled (1 / (1 - rate) of that dropout)
   LnDropout drop{};        // EPI_FWD_GCN / EPI_FWD_ADD: dropout of the layer's output (threshold 0: none)
   int32_t ws_min_rows = 65536;  // rows from which the weight-stationary kernel is used (tests force it on small inputs)
 };
-int launch_gemm_nt(const GemmNtArgs *a, int n, int compute_dtype, hipStream_t s);  // n products that do not depend on each other
-inline int launch_gemm_nt(const GemmNtArgs &a, int compute_dtype, hipStream_t s) { return launch_gemm_nt(&a, 1, compute_dtype, s); }
-static_assert(sizeof(Batch<GemmNtArgs>) <= 4096, "kernel arguments");
+int launch_gemm_nt(const GemmNtArgs &a, int compute_dtype, hipStream_t s);
 
 // dW[I x O] += scale * A[M x I]^T . B[M x O]   (reduction over the M rows of the chunk).
 // B is an internal padded buffer in the compute dtype; A as for the NT product.
@@ -296,9 +360,16 @@ struct LnBackArgs {
   float *dgamma, *dbeta;
 };
 static_assert(sizeof(Batch<LnBackArgs>) <= 4096, "kernel arguments");
-// n <= kBatch of them that do not depend on each other (backward: with scratch and parameters of their own)
-int launch_ln_relu(const LnArgs *a, int n, hipStream_t s);
-int launch_ln_relu_backward(const LnBackArgs *a, int n, hipStream_t s);
+// What a backward launch leaves to add up: n_parts blocks of [gamma sums | beta sums] that go to dgamma and dbeta.
+struct LnReduceArgs {
+  const float *partial;
+  int32_t n_parts, d;
+  float *dgamma, *dbeta;
+};
+int launch_ln_relu(const LnArgs &a, hipStream_t s);
+// n <= kBatch of them, with scratch of their own, of at most max_waves wavefronts each; red[i]: what is left to add up
+int launch_ln_relu_backward(const LnBackArgs *a, int n, int max_waves, LnReduceArgs *red, hipStream_t s);
+int launch_ln_param_reduce(const LnReduceArgs *red, int n, hipStream_t s);
 // dst[r][c] = src[r][c] for c < d, zero for d <= c < dst_ld
 int launch_copy_rows(const void *src, int src_ld, void *dst, int dst_ld, int64_t M, int d, int dtype, hipStream_t s);
 

@@ -100,7 +100,9 @@ __global__ __launch_bounds__(256, 2) void spmm_dense_blocks_kernel(const DenseAr
   }
   const int col0 = half * DH;
   const bool drop = a.src_unsel == nullptr;
-  if (drop && !masks_meet(a.item_chunks[item], a.mask)) return;  // whole workgroup
+  uint32_t classes;
+  const ChunkMask mask = spmm_row_mask(a.pass, a.mask, (uint32_t)__builtin_amdgcn_readfirstlane(a.item_chunk[item]), classes);
+  if (drop && !masks_meet(a.item_chunks[item], mask)) return;  // whole workgroup
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wm = wave * 32, g = lane >> 5, r32 = lane & 31;
   const uint32_t vmask = (1u << a.vbits) - 1u;
@@ -141,7 +143,7 @@ __global__ __launch_bounds__(256, 2) void spmm_dense_blocks_kernel(const DenseAr
       const int i = tid + 256 * q;
       uint64_t addr = zrow;
       if (pc[q] != 0xffffffffu) {
-        const bool sel = mask_test(a.mask, pc[q] >> a.vbits);
+        const bool sel = mask_test(mask, pc[q] >> a.vbits);
         if (sel || !drop) addr = reinterpret_cast<uint64_t>((sel ? src_sel : src_unsel) + (size_t)(pc[q] & vmask) * ld);
       }
       if (i < nb * kDenseCB) rows[i] = addr;
@@ -310,7 +312,7 @@ __global__ __launch_bounds__(256, 2) void spmm_dense_blocks_kernel(const DenseAr
 #pragma unroll
     for (int t = 0; t < 16; ++t) rsv[t] = 1.f;
   } else {
-    const float *rs = a.rowscale + (size_t)a.item_rb[item] * kDenseRB;  // zero past the last row of the chunk
+    const float *rs = a.rowscale + a.item_rs[item];  // zero past the last row of the chunk
 #pragma unroll
     for (int t = 0; t < 16; ++t) rsv[t] = rs[wm + 8 * (t >> 2) + 4 * g + (t & 3)];
   }

@@ -212,8 +212,7 @@ constexpr int BM = 128, BN = 128;
 // 32 floats = one 128-byte line, read by 16 lanes as float pairs (four whole rows per wave instruction,
 // fully coalesced) instead of eight scalars per lane.
 template <typename TA, bool VEC, bool PAIR = false, int BK = 32>
-__global__ __launch_bounds__(256) void gemm_nt_bf16_kernel(const Batch<GemmNtArgs> ba) {
-  const GemmNtArgs a = ba.sub[blockIdx.z];  // a copy: fields in registers instead of loads inside the loops
+__global__ __launch_bounds__(256) void gemm_nt_bf16_kernel(const GemmNtArgs a) {
   constexpr int LDS_K = BK + 8;   // padded K stride (elements)
   constexpr int KV = BK / 8;      // 16-byte vectors per tile row
   constexpr int NV = BM * KV / 256;  // vectors per thread and operand tile
@@ -382,16 +381,11 @@ __global__ __launch_bounds__(256) void gemm_nt_bf16_kernel(const Batch<GemmNtArg
 // and walk over row tiles, and the loads of the next A tile are in flight while the current one is
 // multiplied and stored.  WN = column panels per workgroup (4: N <= 256 with 64-row tiles, 2: N <= 128
 // with 128-row tiles); KS = number of 16-wide k-steps held (Kp <= 16 * KS).
-// Several products of a diagonal share a launch (each workgroup works on one of them); it is taken from 64 k rows in all on,
-// below that the tiled kernel is as fast or faster: 4 products of 21.9 k x 256 x 256 36 -> 32 us, 9.15 -> 8.73 ms per step
-// of 700 k vertices; 8 of 21.2 k (GCNII) 11.09 -> 10.92 ms.  Counting products of other widths, which don't share the
-// launch, cost an evaluation pass of 169 k vertices 1.12 against 1.09 ms.
+// Taken from 64 k rows on; below that the tiled kernel is as fast or faster.
 // GCNF: the instance for the GCN forward epilogue (bias + ReLU applied to the accumulators, see below).
 template <int WN, int KS, bool GCNF>
-__global__ __launch_bounds__(256, 2) void gemm_nt_bf16_ws_kernel(const Batch<GemmNtArgs> ba) {
-  const GemmNtArgs a = ba.sub[blockIdx.z];  // a copy: fields in registers instead of loads inside the loops
-  const int blocks = a.ws_blocks;
-  if ((int)blockIdx.x >= blocks) return;
+__global__ __launch_bounds__(256, 2) void gemm_nt_bf16_ws_kernel(const GemmNtArgs a) {
+  const int blocks = (int)gridDim.x;
   constexpr int WR = 4 / WN, TM = 64 * WR;  // row groups, rows per tile
   constexpr int LDK = KS * 16 + 8;          // LDS row stride (elements): conflict-free 16-byte fragment reads
   constexpr int NV = TM * (KS * 2) / 256;   // 16-byte vectors of an A tile per thread
@@ -546,7 +540,7 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_bf16_ws_kernel(const Batch<Gem
   }
 }
 
-typedef void (*nt_fn)(const Batch<GemmNtArgs>);
+typedef void (*nt_fn)(const GemmNtArgs);
 struct WsKernel {
   nt_fn fn;
   int tm;  // rows per tile
@@ -919,17 +913,14 @@ __device__ inline void epilogue_store4_f32(const GemmNtArgs &a, int m, int n, co
 // the order of its lane groups, each with a rounding of its own, and its operands are laid out so that lane group g of step s
 // holds k = 4 s + g.  Which of an activation's elements pass ReLU hangs on the last bit of such a sum, so the order is part of
 // the result: it depends on no tile size, row count or chunk, and a vector-ALU loop over k gives the same bits.
-// Q = 1: a chunk's product is small (162 x 1000 x 1000 in a 32-chunk pass over 5 k vertices: 693 tiles of 16 x 16 for 1,024
+// Q = 1: a chunk's product is small (162 x 1000 x 1000, one of 32 chunks of 5 k vertices: 693 tiles of 16 x 16 for 1,024
 // SIMDs), so what bounds it is the chain over K, 250 dependent matrix instructions of 32 cycles; everything else (the loads D
 // groups ahead, the change of lanes in LDS, the operand reads one group ahead) has to run in its shadow.
-// 72 us on the vector ALU, 11.5 us here, 26.7 us for four such products of a diagonal (49 TFLOP/s).  1,078 x 100 x 100:
-// 13 -> 4.6 us.
+// 72 us on the vector ALU, 11.5 us here.  1,078 x 100 x 100: 13 -> 4.6 us.
 // Q = 2: for products of many tiles; half the operand bytes per product through L2.  Taken from 512 of its 64 x 64 workgroup
-// tiles on; from 192 / 96 on, the diagonals of 89 k / 34 k vertices of width 100 took 4.61 / 2.52 ms per step instead of
-// 4.47 / 2.13, those of 5 k of width 1000 4.06 instead of 4.12.
+// tiles on.
 template <int Q, int EPI>
-__global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const Batch<GemmNtArgs> ba) {
-  const GemmNtArgs a = ba.sub[blockIdx.z];  // a copy: fields in registers instead of loads inside the loops
+__global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const GemmNtArgs a) {
   constexpr int T = 32 * Q;          // rows and columns of a workgroup's tile
   constexpr int D = Q == 1 ? 12 : 4; // groups of 16 reduction elements in flight per wave
   constexpr int PS = 16 * Q + 4;     // padded row stride (floats) of the result patch
@@ -1335,41 +1326,25 @@ static nt_fn nt_bf16_fn(const GemmNtArgs &a) {
   return a.Kp >= 128 && (long long)mt * ntiles <= 1024 ? gemm_nt_bf16_kernel<bf16_t, true, false, 64> : gemm_nt_bf16_kernel<bf16_t, true>;
 }
 
-int launch_gemm_nt(const GemmNtArgs *a_in, int n, int compute_dtype, hipStream_t s) {
-  if (n > kBatch) return hipErrorInvalidValue;
-  GemmNtArgs args[kBatch];
-  nt_fn fn[kBatch];
-  unsigned gx[kBatch];  // workgroups; of a persistent kernel: tiles
-  int tm[kBatch];       // rows per tile of a persistent kernel, else 0
-  size_t smem[kBatch];
-  // fp32: 64 x 64 tiles of all products; bf16: rows of those that would share a launch of the weight-stationary kernel
-  long long tiles64 = 0, ws_rows[2][2] = {};
-  for (int i = 0; i < n; ++i)
-    if (a_in[i].M > 0 && a_in[i].N > 0) {
-      tiles64 += (long long)((a_in[i].M + 63) / 64) * ((a_in[i].N + 63) / 64);
-      if (ws_ok(a_in[i])) ws_rows[a_in[i].N > 128][a_in[i].Kp > 128] += a_in[i].M;
-    }
-  for (int i = 0; i < n; ++i) {
-    GemmNtArgs &a = args[i] = a_in[i];
-    fn[i] = nullptr;
-    gx[i] = 0;
-    tm[i] = 0;
-    smem[i] = 0;
-    if (a.M <= 0 || a.N <= 0) continue;
-    if (compute_dtype != DT_BF16) {
-      if (a.a_dtype != DT_F32) return hipErrorInvalidValue;
-      // 64 x 64 tiles per workgroup from two workgroups per compute unit on, below that 32 x 32
-      const bool wide = tiles64 >= 512;
-      const int T = wide ? 64 : 32;
+int launch_gemm_nt(const GemmNtArgs &a_in, int compute_dtype, hipStream_t s) {
+  GemmNtArgs a = a_in;
+  if (a.M <= 0 || a.N <= 0) return hipSuccess;
+  nt_fn fn;
+  unsigned gx;
+  size_t smem = 0;
+  if (compute_dtype != DT_BF16) {
+    if (a.a_dtype != DT_F32) return hipErrorInvalidValue;
+    // 64 x 64 tiles per workgroup from two workgroups per compute unit on, below that 32 x 32
+    const bool wide = (long long)((a.M + 63) / 64) * ((a.N + 63) / 64) >= 512;
+    const int T = wide ? 64 : 32;
 #define NT_F32(Q) {gemm_nt_f32_kernel<Q, 0>, gemm_nt_f32_kernel<Q, 1>, gemm_nt_f32_kernel<Q, 2>, gemm_nt_f32_kernel<Q, 3>, \
                    gemm_nt_f32_kernel<Q, 4>, gemm_nt_f32_kernel<Q, 5>, gemm_nt_f32_kernel<Q, 6>}
-      static const nt_fn table[2][7] = {NT_F32(1), NT_F32(2)};  // indexed by GemmEpilogue
+    static const nt_fn table[2][7] = {NT_F32(1), NT_F32(2)};  // indexed by GemmEpilogue
 #undef NT_F32
-      if (a.epilogue < 0 || a.epilogue > 6) return hipErrorInvalidValue;
-      fn[i] = table[wide][a.epilogue];
-      gx[i] = (unsigned)(((long long)((a.M + T - 1) / T) * ((a.N + T - 1) / T) + 7) / 8 * 8);
-      continue;
-    }
+    if (a.epilogue < 0 || a.epilogue > 6) return hipErrorInvalidValue;
+    fn = table[wide][a.epilogue];
+    gx = (unsigned)(((long long)((a.M + T - 1) / T) * ((a.N + T - 1) / T) + 7) / 8 * 8);
+  } else {
     const bool has_aux = a.epilogue == EPI_FWD_GCNII || a.epilogue == EPI_MASK || a.epilogue == EPI_DGRAD_GCNII ||
                          a.epilogue == EPI_FWD_ADD || a.epilogue == EPI_RES;
     a.vec_epi = a.N % 8 == 0 && a.out_ld % 8 == 0 && aligned16(a.out) && (a.out_pad <= a.N) &&
@@ -1379,61 +1354,21 @@ int launch_gemm_nt(const GemmNtArgs *a_in, int n, int compute_dtype, hipStream_t
     // drawing inside the epilogues of the bf16 kernels costs them registers they do not have (the forward products of a
     // 233 k vertex stage went from 0.68 to 2.65 ms with dropout off): a pass of its own behind the product
     a.drop = LnDropout{};
-    if (ws_ok(a) && ws_rows[a.N > 128][a.Kp > 128] >= a.ws_min_rows) {
+    if (ws_ok(a) && a.M >= a.ws_min_rows) {  // persistent: two workgroups per compute unit
       const WsKernel w = ws_kernel(a);
-      fn[i] = w.fn;
-      tm[i] = w.tm;
-      smem[i] = w.smem;
-      gx[i] = (unsigned)((a.M + w.tm - 1) / w.tm);
+      fn = w.fn;
+      smem = w.smem;
+      gx = std::min((unsigned)((a.M + w.tm - 1) / w.tm), 512u);
     } else {
-      fn[i] = nt_bf16_fn(a);
-      gx[i] = (unsigned)(((a.M + BM - 1) / BM + 7) / 8 * 8 * ((a.N + BN - 1) / BN));
+      fn = nt_bf16_fn(a);
+      gx = (unsigned)(((a.M + BM - 1) / BM + 7) / 8 * 8 * ((a.N + BN - 1) / BN));
     }
   }
-  bool done[kBatch] = {};
-  for (int i = 0; i < n; ++i) {
-    if (done[i] || gx[i] == 0) continue;
-    Batch<GemmNtArgs> b;
-    int of[kBatch];
-    unsigned m = 0, width = 0;
-    for (int j = i; j < n; ++j) {
-      if (done[j] || gx[j] == 0 || fn[j] != fn[i]) continue;
-      done[j] = true;
-      of[m] = j;
-      b.sub[m++] = args[j];
-    }
-    // A persistent kernel gets two workgroups per compute unit.  Several products share them: every workgroup gets as many row
-    // tiles of one product as that takes.  One product is dealt out evenly: with the rule for several, 66,000 x 256 x 200 ran
-    // in 344 workgroups of 3 tiles instead of 512 of 2 or 3, 25.1 against 23.0 us (131,500 rows 34.4 against 32.7).
-    unsigned per = 1;
-    const unsigned even = tm[i] > 0 && m == 1 ? std::min(gx[i], 512u) : 0;
-    if (tm[i] > 0 && m > 1) {
-      unsigned tiles = 0;
-      for (unsigned q = 0; q < m; ++q) tiles += gx[of[q]];
-      per = std::max(1u, tiles / 512u);
-      auto need = [&](unsigned p) {
-        unsigned w = 0;
-        for (unsigned q = 0; q < m; ++q) w += (gx[of[q]] + p - 1) / p;
-        return w;
-      };
-      while (need(per) > 512u) ++per;  // at most eight products: ends at the latest with one workgroup each
-    }
-    for (unsigned q = 0; q < m; ++q) {
-      const unsigned w = even > 0 ? even : (gx[of[q]] + per - 1) / per;
-      b.sub[q].ws_blocks = (int32_t)w;
-      width = std::max(width, w);
-    }
-    if (m > 1) width = (width + 7) / 8 * 8;  // workgroup i of every product on XCD i % 8
-    hipLaunchKernelGGL(fn[i], dim3(width, 1, m), dim3(256), smem[i], s, b);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return (int)e;
-  }
-  if (compute_dtype == DT_BF16)
-    for (int i = 0; i < n; ++i)
-      if (a_in[i].M > 0 && a_in[i].N > 0 && a_in[i].drop.threshold > 0) {
-        const int e = launch_dropout_rows(args[i].out, args[i].out_dtype, args[i].M, args[i].N, args[i].out_ld, a_in[i].drop, s);
-        if (e != 0) return e;
-      }
+  hipLaunchKernelGGL(fn, dim3(gx), dim3(256), smem, s, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return (int)e;
+  if (compute_dtype == DT_BF16 && a_in.drop.threshold > 0)
+    return launch_dropout_rows(a.out, a.out_dtype, a.M, a.N, a.out_ld, a_in.drop, s);
   return hipSuccess;
 }
 

@@ -23,6 +23,8 @@ namespace {
 // 1024 splits take 3.08 / 2.62 / 2.56 / 3.24 / 3.01 / 2.91 ms per step.
 constexpr int kMaxSplits = 512;
 constexpr size_t kAlign = 256;
+// Rows of a GraphSage layer whose two products follow each other (the first one's rows are fp32 and are read by the second).
+constexpr int64_t kSelfRows = 65536;
 
 std::string g_create_error;
 
@@ -201,26 +203,20 @@ int64_t dense_max_items(int widest) { return (int64_t)(2 * 256 * 11 / 10) / std:
 // Tuning::dense_min_entries per chunk on average (the sparse kernel gathers about 40 entries per nanosecond).
 constexpr int kDenseItemBlocks = kDenseMaxItemBlocks;
 
-struct TaskList {
-  int64_t n_tasks = 0, n_long = 0, n_slots = 0;
-  int64_t n_short = 0;  // the last n_short tasks are whole rows of at most Tuning::short_row entries
-  int32_t *task_row = nullptr;
-  int64_t *task_e0 = nullptr;
-  int32_t *task_ne = nullptr;
-  int32_t *task_slot = nullptr;
-  int32_t *lr_row = nullptr, *lr_slot0 = nullptr, *lr_nslots = nullptr;
-  // class sections of the task list (class c = tasks [cls_off[c], cls_off[c+1]); tail from cls_off[8])
-  int n_classes = 0;                      // 0: no class sections
-  int64_t cls_off[kMaxClasses + 1] = {};  // tail starts at cls_off[n_classes]
-  int32_t *d_cls_off = nullptr;           // the same on the device
-  uint8_t *slot_class = nullptr;
-  // entries of every class section by the chunk of the gathered vertex ([class * K + chunk]): what a launch
+// Launch schedule of one direction.  The task arrays are made of sections, each chunk after chunk: the pieces of source class 0,
+// 1, ..., then pieces without a class and whole rows, then short rows.  So a launch over any run of chunks finds each section's
+// tasks in one stretch.
+struct DirTasks {
+  int K = 0;
+  int n_classes = 0;               // 0: no class sections
+  std::vector<int64_t> sec;        // [section][K + 1]: first task of every chunk
+  std::vector<int64_t> slot_off, lr_off, item_off;  // K + 1: partial rows, cut rows, dense items of the chunks
+  // entries of every chunk's class pieces by the chunk of the gathered vertex ([chunk][class][source chunk]): what a launch
   // that drops unselected entries really gathers from each class
-  std::vector<int64_t> cls_chunk_entries;
-  // dense-block parts of the cut rows and the items of this chunk (dense plan active only)
-  int32_t *lr_dense0 = nullptr, *lr_ndense = nullptr, *lr_item0 = nullptr;
-  int64_t item0 = 0;  // first item of the chunk in the direction's item arrays
-  int n_items = 0;
+  std::vector<int64_t> cls_entries;
+  int64_t first(int section, int c) const { return sec[(size_t)section * (K + 1) + c]; }
+  int64_t count(int section, int c0, int c1) const { return first(section, c1) - first(section, c0); }
+  int64_t entries(int c, int q, int from) const { return cls_entries[((size_t)c * n_classes + q) * K + from]; }
 };
 
 // Sizes that depend only on row lengths: number of tasks / long rows / slots of every chunk.
@@ -364,22 +360,25 @@ struct Layout {
   size_t f_task_row, f_task_e0, f_task_ne, f_task_slot, f_lr_row, f_lr_slot0, f_lr_n;
   size_t b_task_row, b_task_e0, b_task_ne, b_task_slot, b_lr_row, b_lr_slot0, b_lr_n;
   size_t f_slot_class, b_slot_class;
-  size_t cls_off[2];  // [chunk][kMaxClasses + 1] per direction
+  size_t pass_tables;  // three tables of K entries (launch_pass_tables)
   size_t rem_ptr[2];  // row pointers of the remainder index per direction (dense plan active), else unused
   // dense plan per direction (0 forward, 1 transposed)
   size_t d_blk_cb[2], d_blk_e0[2], d_ent_pos[2], d_ent_w[2], d_colslot[2], d_tiles[2];
   size_t d_bits[2], d_colscale[2], d_rowscale[2];  // weights of the form s(row) * s(column): patterns and scales
-  size_t d_item_rb[2], d_item_b0[2], d_item_nb[2], d_item_chunks[2];
+  size_t d_item_rs[2], d_item_chunk[2], d_item_b0[2], d_item_nb[2], d_item_chunks[2];
   size_t d_lr_dense0[2], d_lr_ndense[2], d_lr_item0[2];
   size_t dense_partial, zero_row;
-  int cells;  // that run side by side
   size_t partial;
-  size_t dense_stride, partial_stride, self_stride, row_stride, ln_stride;  // elements of one cell's scratch
+  int64_t item_cap, slot_cap;  // dense items and partial rows that one launch may use
+  int64_t self_rows;           // GraphSage: rows of self_fwd
+  size_t row_stride;           // elements of a chunk's rows
+  size_t ln_stride;            // of the parameter sums of one layer
+  int ln_layers;               // layers whose parameter sums wait to be added up at a time
   std::vector<size_t> Z, dZ, Wt, Wn, Tc, Th;
   std::vector<size_t> dY;  // deferred weight gradients: dL/d(pre-activation) of every aggregate-first layer, all n rows
   std::vector<size_t> Wt_self, Wn_self;  // GraphSage: staged copies of W_self (Wt / Wn then hold W_neigh)
-  size_t self_fwd = 0, self_bwd = 0;      // GraphSage: h_v W_self of a chunk (fp32), dY W_self^T of a chunk
-  size_t res_dr = 0, ln_partial = 0;      // ResGCN+: gradient of the activated rows of a chunk; parameter-gradient scratch
+  size_t self_fwd = 0, self_bwd = 0;      // GraphSage: h_v W_self (fp32), dY W_self^T where it can't wait in the output rows
+  size_t ln_partial = 0;                  // ResGCN+: parameter-gradient scratch
   size_t G[2];
   size_t gemm_partial, bias_partial;
   size_t total;
@@ -400,14 +399,9 @@ struct Shape {
   bool defer_wgrad() const { return tune.wgrad_defer; }
   bool sage() const { return variant == GNNSTAGE_SAGE; }
   bool res() const { return variant == GNNSTAGE_RESGCN; }
-  // Cells (chunk, layer) of a pass that run side by side.  One where a launch fills the chip for long anyway: an
-  // aggregation over 2 M entries takes 100 us and up, and every further cell needs scratch of its own.  One with dense blocks
-  // too, whose partial tiles are most of it (37 MB for a chunk of 4 M entries; 80 k vertices, 16 M entries, 4 chunks: 4.22 ms
-  // per step cell by cell and four at a time).
-  int cells_at_once(bool dense_blocks) const {
-    if (!defer_wgrad() || dense_blocks || nnz / K >= 2000000) return 1;
-    return std::min(kBatch, std::min(K, L));
-  }
+  // dY W_self^T of layer j waits in the rows that the layer's transposed aggregation writes and adds it to: those are of the
+  // gradient rows' type, and no column of them belongs to two lanes
+  bool self_in_place(int j) const { return dims[j] % 8 == 0 && level_elt(j) == elt(); }
   // elements of one weight matrix: GraphSage stacks [W_self ; W_neigh]
   size_t w_half(int j) const { return (size_t)dims[j] * dims[j + 1]; }
   int elt() const { return dtype == GNNSTAGE_BF16 ? 2 : 4; }
@@ -458,6 +452,8 @@ struct Shape {
     }
     return true;
   }
+  // tasks, and what fills every chunk's short rows up to a multiple of four
+  int64_t task_capacity(int64_t tasks) const { return tasks + 3 * (int64_t)K; }
   int64_t max_rows() const {
     int64_t m = 0;
     for (int c = 0; c < K; ++c) m = std::max<int64_t>(m, chunk_ptr[c + 1] - chunk_ptr[c]);
@@ -522,7 +518,7 @@ bool read_shape(const gnnstage_desc *d, Shape &s, std::string &err) {
   return true;
 }
 
-Layout layout_for(const Shape &s, const HostDir &hf, const HostDir &hb, bool rank1, int cells) {
+Layout layout_for(const Shape &s, const HostDir &hf, const HostDir &hb, bool rank1, int64_t item_cap, int64_t slot_cap) {
   const PlanCounts &f = hf.pc, &b = hb.pc;
   Layout l;
   Bump w;
@@ -532,7 +528,6 @@ Layout layout_for(const Shape &s, const HostDir &hf, const HostDir &hb, bool ran
   l.t_ptr = w.take(sizeof(int64_t) * (s.n + 1));
   l.prow = w.take(sizeof(uint32_t) * hb.nnz);
   l.tval = w.take(sizeof(float) * hb.nnz);
-  int64_t max_items = 0;
   for (int dir = 0; dir < 2; ++dir) {
     const HostDir &h = dir ? hb : hf;
     const bool on = h.dense();
@@ -548,38 +543,37 @@ Layout layout_for(const Shape &s, const HostDir &hf, const HostDir &hb, bool ran
     l.d_bits[dir] = w.take(rank1 ? sizeof(uint32_t) * nb * 256 : 0);
     l.d_colscale[dir] = w.take(on && rank1 ? sizeof(float) * h.dp.colslot_vertex.size() : 0);
     l.d_rowscale[dir] = w.take(on && rank1 ? sizeof(float) * (size_t)h.rowscale_off.back() : 0);
-    l.d_item_rb[dir] = w.take(sizeof(int32_t) * ni);
+    l.d_item_rs[dir] = w.take(sizeof(int32_t) * ni);
+    l.d_item_chunk[dir] = w.take(sizeof(int32_t) * ni);
     l.d_item_b0[dir] = w.take(sizeof(int64_t) * ni);
     l.d_item_nb[dir] = w.take(sizeof(int32_t) * ni);
     l.d_item_chunks[dir] = w.take(sizeof(ChunkMask) * ni);
     l.d_lr_dense0[dir] = w.take(sizeof(int32_t) * nl);
     l.d_lr_ndense[dir] = w.take(sizeof(int32_t) * nl);
     l.d_lr_item0[dir] = w.take(sizeof(int32_t) * nl);
-    max_items = std::max(max_items, h.max_items);
   }
-  // scratch of one cell times the cells that run side by side
-  l.cells = cells;
-  const size_t B = (size_t)l.cells;
-  l.dense_stride = (size_t)max_items * kDenseRB * 256;
-  l.dense_partial = w.take(sizeof(float) * l.dense_stride * B);
-  l.zero_row = w.take(max_items > 0 ? 512 : 0);
-  l.f_task_row = w.take(sizeof(int32_t) * f.total_tasks);
-  l.f_task_e0 = w.take(sizeof(int64_t) * f.total_tasks);
-  l.f_task_ne = w.take(sizeof(int32_t) * f.total_tasks);
-  l.f_task_slot = w.take(sizeof(int32_t) * f.total_tasks);
+  l.item_cap = item_cap;
+  l.slot_cap = slot_cap;
+  l.dense_partial = w.take(sizeof(float) * (size_t)item_cap * kDenseRB * s.dense_width());
+  l.zero_row = w.take(item_cap > 0 ? 512 : 0);
+  const int64_t f_tasks = s.task_capacity(f.total_tasks), b_tasks = s.task_capacity(b.total_tasks);
+  l.f_task_row = w.take(sizeof(int32_t) * f_tasks);
+  l.f_task_e0 = w.take(sizeof(int64_t) * f_tasks);
+  l.f_task_ne = w.take(sizeof(int32_t) * f_tasks);
+  l.f_task_slot = w.take(sizeof(int32_t) * f_tasks);
   l.f_lr_row = w.take(sizeof(int32_t) * f.total_longs);
   l.f_lr_slot0 = w.take(sizeof(int32_t) * f.total_longs);
   l.f_lr_n = w.take(sizeof(int32_t) * f.total_longs);
-  l.b_task_row = w.take(sizeof(int32_t) * b.total_tasks);
-  l.b_task_e0 = w.take(sizeof(int64_t) * b.total_tasks);
-  l.b_task_ne = w.take(sizeof(int32_t) * b.total_tasks);
-  l.b_task_slot = w.take(sizeof(int32_t) * b.total_tasks);
+  l.b_task_row = w.take(sizeof(int32_t) * b_tasks);
+  l.b_task_e0 = w.take(sizeof(int64_t) * b_tasks);
+  l.b_task_ne = w.take(sizeof(int32_t) * b_tasks);
+  l.b_task_slot = w.take(sizeof(int32_t) * b_tasks);
   l.b_lr_row = w.take(sizeof(int32_t) * b.total_longs);
   l.b_lr_slot0 = w.take(sizeof(int32_t) * b.total_longs);
   l.b_lr_n = w.take(sizeof(int32_t) * b.total_longs);
   l.f_slot_class = w.take((size_t)f.total_slots);
   l.b_slot_class = w.take((size_t)b.total_slots);
-  for (int dir = 0; dir < 2; ++dir) l.cls_off[dir] = w.take(sizeof(int32_t) * (size_t)s.K * (kMaxClasses + 1));
+  l.pass_tables = w.take(sizeof(PassChunk) * 3 * (size_t)s.K);
   int max_d = 0, max_ld = 0;
   size_t max_io = 0;
   for (int j = 0; j <= s.L; ++j) {
@@ -587,11 +581,10 @@ Layout layout_for(const Shape &s, const HostDir &hf, const HostDir &hb, bool ran
     max_ld = std::max(max_ld, s.ld[j]);
   }
   for (int j = 0; j < s.L; ++j) max_io = std::max(max_io, (size_t)s.dims[j] * s.dims[j + 1]);
-  l.partial_stride = (size_t)std::max(f.max_slots, b.max_slots) * max_d;
-  l.partial = w.take(sizeof(float) * l.partial_stride * B);
+  l.partial = w.take(sizeof(float) * (size_t)slot_cap * max_d);
   l.row_stride = (size_t)round_up((int)std::min<int64_t>(s.max_rows(), 0x7ffffff0), 8) * max_ld;  // rows of a chunk
-  l.self_stride = l.row_stride;
   l.ln_stride = (size_t)(kLnMaxWaves / 4) * 2 * max_d;
+  l.ln_layers = std::min(s.L, kBatch);
   const size_t elt = s.elt();
   l.Z.resize(s.L);
   l.dZ.resize(s.L);
@@ -608,13 +601,11 @@ Layout layout_for(const Shape &s, const HostDir &hf, const HostDir &hb, bool ran
     l.Z[j] = w.take((size_t)s.n * s.ld[j] * elt);
     l.dZ[j] = w.take((size_t)s.n * s.ld[j] * elt);
     // deferred weight gradients keep dY of all rows in the table of activated current rows (of the same width): a chunk's rows
-    // of that table are written before they are read in a forward pass, and no backward pass reads them
+    // of that table are written before they are read in a forward pass, and no backward pass reads them.  The gradient of the
+    // activated rows of a backward pass waits in the table of historical ones for the same reason.
     l.dY[j] = l.Tc[j];
   }
-  if (s.res()) {
-    l.res_dr = w.take(l.row_stride * elt * B);
-    l.ln_partial = w.take(sizeof(float) * l.ln_stride * B);
-  }
+  if (s.res()) l.ln_partial = w.take(sizeof(float) * l.ln_stride * l.ln_layers);
   for (int j = 0; j < s.L && !s.res(); ++j) {
     if (s.tf[j]) {
       // transform-first layer: transformed current / historical rows, and the masked upstream gradient
@@ -639,10 +630,15 @@ Layout layout_for(const Shape &s, const HostDir &hf, const HostDir &hb, bool ran
       l.Wt_self[j] = w.take((size_t)s.dims[j + 1] * s.ld[j] * elt);
       l.Wn_self[j] = w.take((size_t)s.dims[j] * s.ld[j + 1] * elt);
     }
-    l.self_fwd = w.take(sizeof(float) * l.self_stride * B);
-    l.self_bwd = w.take(l.self_stride * elt * B);
+    // the rows of a chunk, or a block of 64 k of a whole pass: its fp32 rows are read back from a cache
+    l.self_rows = std::max<int64_t>(s.max_rows(), std::min<int64_t>(s.n, kSelfRows));
+    l.self_fwd = w.take(sizeof(float) * (size_t)l.self_rows * max_ld);
+    int wait_ld = 0;
+    for (int j = s.need_input_grad ? 0 : 1; j < s.L; ++j)
+      if (!s.self_in_place(j)) wait_ld = std::max(wait_ld, s.ld[j]);
+    l.self_bwd = w.take((size_t)s.n * wait_ld * elt);
   }
-  l.G[0] = w.take(l.row_stride * elt * B);
+  l.G[0] = w.take(l.row_stride * elt);
   l.G[1] = w.take(s.defer_wgrad() ? 0 : l.row_stride * elt);
   l.gemm_partial = w.take(sizeof(float) * kMaxSplits * max_io);
   l.bias_partial = w.take(sizeof(float) * kMaxSplits * max_d);
@@ -650,16 +646,17 @@ Layout layout_for(const Shape &s, const HostDir &hf, const HostDir &hb, bool ran
   return l;
 }
 
-// The cells that run side by side share a budget of scratch beyond that of one: 1 GiB, or a sixteenth of the workspace where
-// that is more.  Chunks of equal size stay far below it (700 k vertices of width 256, 32 chunks: 24 MB for four cells); of a
-// graph with nearly all vertices in one chunk every cell would add up to 12 bytes per element of a whole level.
+// One launch over a whole layer needs room for the partial sums of every chunk: at most 1 GiB beyond that of the largest chunk,
+// or a sixteenth of the workspace where that is more; a layer whose sums need more is served in several launches.
 Layout make_layout(const Shape &s, const HostDir &hf, const HostDir &hb, bool rank1) {
-  const Layout one = layout_for(s, hf, hb, rank1, 1);
-  const int most = s.cells_at_once(hf.dense() || hb.dense());
-  if (most <= 1) return one;
-  const size_t budget = std::max<size_t>((size_t)1 << 30, one.total / 16);
-  const size_t more = layout_for(s, hf, hb, rank1, 2).total - one.total;  // what a cell takes
-  return layout_for(s, hf, hb, rank1, (int)std::min<size_t>((size_t)most, 1 + budget / std::max<size_t>(more, 1)));
+  const int64_t one_items = std::max(hf.max_items, hb.max_items), one_slots = std::max(hf.pc.max_slots, hb.pc.max_slots);
+  const Layout one = layout_for(s, hf, hb, rank1, one_items, one_slots);
+  const int64_t all_items = (int64_t)std::max(hf.item_rb.size(), hb.item_rb.size()), all_slots = std::max(hf.pc.total_slots, hb.pc.total_slots);
+  const size_t half = std::max<size_t>((size_t)1 << 30, one.total / 16) / 2;
+  int widest = 1;
+  for (const int d : s.dims) widest = std::max(widest, d);
+  const int64_t item_room = (int64_t)(half / (sizeof(float) * kDenseRB * (size_t)s.dense_width())), slot_room = (int64_t)(half / (sizeof(float) * (size_t)widest));
+  return layout_for(s, hf, hb, rank1, std::min(all_items, one_items + item_room), std::min(all_slots, one_slots + slot_room));
 }
 
 struct Profiler {
@@ -753,11 +750,14 @@ struct gnnstage {
   std::vector<int64_t> h_row_ptr;
   std::vector<uint32_t> h_pcol;
   // schedules
-  std::vector<TaskList> ftasks, btasks;
+  DirTasks tasks[2];  // 0 forward, 1 transposed
+  // of a pass whose chunks run side by side: entries that backward launches gather from every class ([chunk][class]), of the
+  // chunks from the row's own on (0) and of those in front of it (1)
+  std::vector<int64_t> kept[2];
+  bool tables_written = false;  // the tables in the workspace are those of the present order
   bool dense_on[2] = {false, false};  // dense blocks per direction (0 forward, 1 transposed)
   int64_t dense_entries[2] = {0, 0};  // entries that live in dense blocks
   bool dense_rank1 = false;           // their weights are kept as pattern bits and row / column scales
-  std::vector<int64_t> rowscale_off[2];
   int n_classes = 1;
   // pass state (Section 3.3: V_processed, and its backward twin)
   std::vector<int32_t> order;
@@ -815,35 +815,59 @@ void mask_set(ChunkMask &m, int c) { m.w[c >> 6] |= 1ull << (c & 63); }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// XCD assignment of the class sections for one launch.  `drop` = the launch skips unselected entries:
-// a class with no entry from a chunk in the mask has no work and is not served at all.  Every class gets
+// What a launch selects: a mask by value (of the chunk that it serves, or one for all rows), or a table of a whole pass.
+enum Select { SEL_MASK, SEL_FORWARD, SEL_BACKWARD, SEL_EARLIER };
+
+// A run of chunks that a layer's launches serve: one chunk, which sees mask, or all of a pass, whose rows see the masks of
+// the pass tables.
+struct Span {
+  int c0, c1;
+  bool whole;
+  ChunkMask mask;
+};
+int64_t span_row0(const gnnstage *st, const Span &sp) { return st->s.chunk_ptr[(size_t)sp.c0]; }
+int64_t span_rows(const gnnstage *st, const Span &sp) { return st->s.chunk_ptr[(size_t)sp.c1] - st->s.chunk_ptr[(size_t)sp.c0]; }
+Span chunk_span(int k, const ChunkMask &mask) { return Span{k, k + 1, false, mask}; }
+// A single chunk needs no table: its rows select it (forward and on the way back), or nothing (earlier).
+bool by_table(const gnnstage *st) { return st->s.K > 1; }
+Span whole_span(const gnnstage *st) {
+  Span sp{0, st->s.K, true, ChunkMask{}};
+  if (!by_table(st)) sp.mask.w[0] = 1;
+  return sp;
+}
+Select span_select(const gnnstage *st, const Span &sp, Select table) { return sp.whole && by_table(st) ? table : SEL_MASK; }
+
+// XCD assignment of the class sections for one launch over chunks [c0, c1).  `drop` = the launch skips unselected entries:
+// a class with no entry from a selected chunk has no work and is not served at all.  Every class gets
 // a cost (a fixed part per task, one unit per gathered entry, a small part per entry that is read and
 // dropped), and the groups of the active classes are dealt to the 8 XCDs like water into buckets of equal
 // cost, a class being split between neighbouring XCDs where a bucket boundary falls inside it.
-void assign_xcds(const gnnstage *st, const TaskList &t, const ChunkMask &mask, bool drop, SpmmArgs &a) {
+void assign_xcds(const gnnstage *st, const DirTasks &t, int c0, int c1, Select sel, const ChunkMask &mask, bool drop, SpmmArgs &a) {
   const int C = t.n_classes, K = st->s.K;
-  a.tail_task0 = t.cls_off[C];
-  a.slot_class = t.slot_class;
-  a.cls_off = t.d_cls_off;
   a.active_classes = 0;
   a.all_classes_active = 1;
   a.n_class_blocks = 0;
   int groups[kMaxClasses];
   double unit[kMaxClasses];  // cost of one group of four tasks
   double total = 0;
-  for (int x = 0; x < 8; ++x) {
-    a.xcd_group0[x] = a.xcd_groups[x] = 0;
-    a.xcd_cls[x] = 0;
-  }
+  for (XcdRun &x : a.xcd) x = XcdRun{};
+  for (int q = 0; q < kMaxClasses; ++q) a.cls_begin[q] = a.cls_end[q] = 0;
   for (int q = 0; q < C; ++q) {
-    const int64_t ntasks = t.cls_off[q + 1] - t.cls_off[q];
+    a.cls_begin[q] = (int32_t)t.first(q, c0);
+    a.cls_end[q] = (int32_t)t.first(q, c1);
+    const int64_t ntasks = t.count(q, c0, c1);
     groups[q] = 0;
     unit[q] = 0;
     int64_t kept = 0, all = 0;
-    for (int c = 0; c < K; ++c) {
-      const int64_t e = t.cls_chunk_entries[(size_t)q * K + c];
-      all += e;
-      if (!drop || mask_test(mask, c)) kept += e;
+    for (int r = c0; r < c1; ++r) {
+      int64_t sum = 0, in = 0;
+      for (int c = 0; c < K; ++c) {
+        const int64_t e = t.entries(r, q, c);
+        sum += e;
+        if (sel == SEL_MASK && mask_test(mask, (uint32_t)c)) in += e;
+      }
+      all += sum;
+      kept += !drop ? sum : sel == SEL_MASK ? in : st->kept[sel == SEL_EARLIER ? 1 : 0][(size_t)r * C + q];
     }
     const bool on = ntasks > 0 && kept > 0;
     if (!on) a.all_classes_active = 0;
@@ -870,136 +894,142 @@ void assign_xcds(const gnnstage *st, const TaskList &t, const ChunkMask &mask, b
         const int room = (int)((quota - used) / unit[q] + 0.5);
         take = std::min(take, std::max(room, 1));
       }
-      if (a.xcd_groups[x] == 0) {
-        a.xcd_cls[x] = (uint8_t)q;
-        a.xcd_group0[x] = g;
+      if (a.xcd[x].groups == 0) {
+        a.xcd[x].cls = q;
+        a.xcd[x].group0 = g;
       }
-      a.xcd_groups[x] += take;
+      a.xcd[x].groups += take;
       g += take;
       used += take * unit[q];
-      most = std::max(most, a.xcd_groups[x]);
+      most = std::max(most, a.xcd[x].groups);
     }
   }
   a.n_class_blocks = 8 * most;
 }
 
-// slot: whose scratch the launch uses (cells that run side by side have one each)
-SpmmArgs base_spmm(const gnnstage *st, bool transposed, int chunk, const ChunkMask &mask, int slot) {
-  SpmmArgs a{};
-  const TaskList &t = transposed ? st->btasks[chunk] : st->ftasks[chunk];
-  a.pidx = st->at<uint32_t>(transposed ? st->lay.prow : st->lay.pcol);
-  a.val = st->at<float>(transposed ? st->lay.tval : st->lay.val);
-  a.task_row = t.task_row;
-  a.task_e0 = t.task_e0;
-  a.task_ne = t.task_ne;
-  a.task_slot = t.task_slot;
-  a.n_tasks = t.n_tasks;
-  a.n_short = t.n_short;
-  a.lr_row = t.lr_row;
-  a.lr_slot0 = t.lr_slot0;
-  a.lr_nslots = t.lr_nslots;
-  a.n_long = t.n_long;
-  a.partial = st->at<float>(st->lay.partial) + (size_t)slot * st->lay.partial_stride;
-  a.vbits = st->vbits;
-  a.force_valu = st->s.tune.spmm_valu ? 1 : 0;
-  a.unroll = st->s.tune.spmm_unroll;
-  a.long_pieces = st->s.least_piece(transposed) == kLeastPieceF32Fwd ? 1 : 0;
-  a.mask = mask;
-  const int dir = transposed ? 1 : 0;
-  if (st->dense_on[dir]) {
-    a.lr_dense0 = t.lr_dense0;
-    a.lr_ndense = t.lr_ndense;
-    a.lr_item0 = t.lr_item0;
-    a.item_chunks = st->at<ChunkMask>(st->lay.d_item_chunks[dir]) + t.item0;
-    a.dense_partial = st->at<float>(st->lay.dense_partial) + (size_t)slot * st->lay.dense_stride;
-  }
-  assign_xcds(st, t, a.mask, transposed, a);  // every transposed launch drops unselected entries
-  return a;
-}
-
-// One aggregation of a cell.
-struct CellSpmm {
-  SpmmLaunch l;
-  bool transposed;
-  int chunk;
-};
-
-// n <= kBatch aggregations that do not depend on each other: dense blocks first, then the sparse kernels, then (where
-// chunks have long rows) the reduce of their pieces, timed apart.
-int run_spmm(gnnstage *st, CellSpmm *cells, int n, hipStream_t stream, int kind, int layer) {
-  SpmmLaunch l[kBatch];
-  int64_t n_long = 0;
-  for (int i = 0; i < n; ++i) {
-    cells[i].l.a.drop_unselected = cells[i].l.a.src_unsel == nullptr ? 1 : 0;
-    l[i] = cells[i].l;
-    n_long += l[i].a.n_long;
-  }
-  {
-    Timed tm(st, stream, kind, layer);
-    for (int i = 0; i < n; ++i) {
-      const SpmmArgs &a = l[i].a;
-      const int dir = cells[i].transposed ? 1 : 0, chunk = cells[i].chunk;
-      const TaskList &t = dir ? st->btasks[chunk] : st->ftasks[chunk];
-      if (!st->dense_on[dir] || t.n_items <= 0) continue;
-      if (l[i].src_dtype != DT_BF16 || (a.d != 128 && a.d != 256) || a.src_ld != a.d) return hipErrorInvalidValue;
-      const Layout &lay = st->lay;
-      DenseArgs da{};
-      da.item_rb = st->at<int32_t>(lay.d_item_rb[dir]) + t.item0;
-      da.item_b0 = st->at<int64_t>(lay.d_item_b0[dir]) + t.item0;
-      da.item_nb = st->at<int32_t>(lay.d_item_nb[dir]) + t.item0;
-      da.item_chunks = st->at<ChunkMask>(lay.d_item_chunks[dir]) + t.item0;
-      da.n_items = t.n_items;
-      da.blk_cb = st->at<int32_t>(lay.d_blk_cb[dir]);
-      if (st->dense_rank1) {
-        da.bits = st->at<uint32_t>(lay.d_bits[dir]);
-        da.colscale = st->at<float>(lay.d_colscale[dir]);
-        da.rowscale = st->at<float>(lay.d_rowscale[dir]) + st->rowscale_off[dir][(size_t)chunk];
-      } else {
-        da.tiles = st->at<bf16_t>(lay.d_tiles[dir]);
-      }
-      da.zero_row = st->at<char>(lay.zero_row);
-      da.colslot = st->at<uint32_t>(lay.d_colslot[dir]);
-      da.src_sel = a.src_sel;
-      da.src_unsel = a.src_unsel;
-      da.d = a.d;
-      da.src_ld = a.src_ld;
-      da.vbits = a.vbits;
-      da.mask = a.mask;
-      da.partial = const_cast<float *>(a.dense_partial);
-      const int e = launch_spmm_dense(da, stream);
-      if (e != 0) return e;
+// Writes the tables of a pass over all chunks in st->order (begin: the order of a pass that is just starting), once.
+int write_pass_tables(gnnstage *st, const std::vector<int32_t> &order, hipStream_t stream) {
+  if (st->tables_written || !by_table(st)) return GNNSTAGE_OK;
+  const Shape &s = st->s;
+  const DirTasks &t = st->tasks[1];
+  PassTableArgs a{};
+  a.K = s.K;
+  PassChunk *p = st->at<PassChunk>(st->lay.pass_tables);
+  a.forward = p;
+  a.backward = p + s.K;
+  a.earlier = p + 2 * s.K;
+  for (int i = 0; i < s.K; ++i) a.pos[order[(size_t)i]] = (uint8_t)i;
+  for (auto &k : st->kept) k.assign((size_t)s.K * t.n_classes, 0);
+  for (int r = 0; r < s.K; ++r) {
+    a.classes_backward[r] = a.classes_earlier[r] = 0;
+    for (int q = 0; q < t.n_classes; ++q) {
+      int64_t sum[2] = {0, 0};
+      for (int c = 0; c < s.K; ++c) sum[a.pos[c] < a.pos[r] ? 1 : 0] += t.entries(r, q, c);
+      for (int i = 0; i < 2; ++i) st->kept[i][(size_t)r * t.n_classes + q] = sum[i];
+      if (sum[0] > 0) a.classes_backward[r] |= 1u << q;
+      if (sum[1] > 0) a.classes_earlier[r] |= 1u << q;
     }
-    const int e = launch_spmm(l, n, stream);
-    if (e != 0) return e;
   }
-  if (n_long > 0) {
-    Timed tm(st, stream, 7, layer);
-    return launch_spmm_reduce(l, n, stream);
-  }
-  return 0;
-}
-
-// Runs [0, n) in turns of at most the cells that have scratch of their own; f(first, count).  One by one while launches are
-// timed: a timed launch belongs to one layer.
-template <typename F>
-int in_turns(const gnnstage *st, int n, F f) {
-  const int B = st->prof.kinds != 0 ? 1 : st->lay.cells;
-  for (int i = 0; i < n; i += B) {
-    const int rc = f(i, std::min(B, n - i));
-    if (rc != GNNSTAGE_OK) return rc;
-  }
+  HIP_TRY(st, launch_pass_tables(a, stream));
+  st->tables_written = true;
   return GNNSTAGE_OK;
 }
 
-// The unit of work of a pass: one layer of one chunk.  slot: whose scratch it uses; mask: the processed chunks as it sees
-// them (its own among them).
-struct Cell {
-  int k, j, slot;
-  ChunkMask mask;
-};
+// The schedule of chunks [c0, c1) of a launch whose operands are in place.
+void set_schedule(const gnnstage *st, int dir, int c0, int c1, Select sel, const ChunkMask &mask, SpmmArgs &a) {
+  const Layout &lay = st->lay;
+  const DirTasks &t = st->tasks[dir];
+  a.pidx = st->at<uint32_t>(dir ? lay.prow : lay.pcol);
+  a.val = st->at<float>(dir ? lay.tval : lay.val);
+  a.task_row = st->at<int32_t>(dir ? lay.b_task_row : lay.f_task_row);
+  a.task_e0 = st->at<int64_t>(dir ? lay.b_task_e0 : lay.f_task_e0);
+  a.task_ne = st->at<uint32_t>(dir ? lay.b_task_ne : lay.f_task_ne);
+  a.task_slot = st->at<int32_t>(dir ? lay.b_task_slot : lay.f_task_slot);
+  a.tail0 = t.first(t.n_classes, c0);
+  a.n_tail = t.count(t.n_classes, c0, c1);
+  a.short0 = t.first(t.n_classes + 1, c0);
+  a.n_short = t.count(t.n_classes + 1, c0, c1);
+  a.slot_class = st->at<uint8_t>(dir ? lay.b_slot_class : lay.f_slot_class);
+  const int64_t l0 = t.lr_off[(size_t)c0];
+  a.lr_row = st->at<int32_t>(dir ? lay.b_lr_row : lay.f_lr_row) + l0;
+  a.lr_slot0 = st->at<int32_t>(dir ? lay.b_lr_slot0 : lay.f_lr_slot0) + l0;
+  a.lr_nslots = st->at<uint32_t>(dir ? lay.b_lr_n : lay.f_lr_n) + l0;
+  a.n_long = t.lr_off[(size_t)c1] - l0;
+  a.partial = st->at<float>(lay.partial);
+  a.slot0 = t.slot_off[(size_t)c0];
+  a.vbits = st->vbits;
+  a.many_chunks = st->s.K > 64 ? 1 : 0;
+  a.force_valu = st->s.tune.spmm_valu ? 1 : 0;
+  a.unroll = st->s.tune.spmm_unroll;
+  a.long_pieces = st->s.least_piece(dir == 1) == kLeastPieceF32Fwd ? 1 : 0;
+  a.mask = mask;
+  a.pass = sel == SEL_MASK ? nullptr : st->at<PassChunk>(lay.pass_tables) + (size_t)(sel == SEL_FORWARD ? 0 : sel == SEL_BACKWARD ? 1 : 2) * st->s.K;
+  a.drop_unselected = a.src_unsel == nullptr ? 1 : 0;
+  if (st->dense_on[dir]) {
+    a.lr_dense0 = st->at<int32_t>(lay.d_lr_dense0[dir]) + l0;
+    a.lr_ndense = st->at<int32_t>(lay.d_lr_ndense[dir]) + l0;
+    a.lr_item0 = st->at<int32_t>(lay.d_lr_item0[dir]) + l0;
+    a.item_chunks = st->at<ChunkMask>(lay.d_item_chunks[dir]);
+    a.dense_partial = st->at<float>(lay.dense_partial);
+    a.item0 = t.item_off[(size_t)c0];
+  }
+  assign_xcds(st, t, c0, c1, sel, mask, dir == 1, a);  // every transposed launch drops unselected entries
+}
 
-int64_t cell_row0(const gnnstage *st, int k) { return st->s.chunk_ptr[(size_t)k]; }
-int64_t cell_rows(const gnnstage *st, int k) { return st->s.chunk_ptr[(size_t)k + 1] - st->s.chunk_ptr[(size_t)k]; }
+// One aggregation over the rows of a span: dense blocks first, then the sparse kernels, then (where chunks have long rows)
+// the reduce of their pieces, timed apart; as many chunks at a time as have room for their partial sums.
+int run_spmm(gnnstage *st, SpmmArgs a, int src_dtype, int out_dtype, bool transposed, const Span &sp, Select sel, hipStream_t stream, int kind, int layer) {
+  const Layout &lay = st->lay;
+  const int dir = transposed ? 1 : 0;
+  const DirTasks &t = st->tasks[dir];
+  for (int c0 = sp.c0, c1; c0 < sp.c1; c0 = c1) {
+    for (c1 = c0 + 1; c1 < sp.c1; ++c1)
+      if (t.slot_off[(size_t)c1 + 1] - t.slot_off[(size_t)c0] > lay.slot_cap || t.item_off[(size_t)c1 + 1] - t.item_off[(size_t)c0] > lay.item_cap) break;
+    set_schedule(st, dir, c0, c1, sel, sp.mask, a);
+    {
+      Timed tm(st, stream, kind, layer);
+      const int64_t i0 = t.item_off[(size_t)c0], n_items = t.item_off[(size_t)c1] - i0;
+      if (st->dense_on[dir] && n_items > 0) {
+        if (src_dtype != DT_BF16 || (a.d != 128 && a.d != 256) || a.src_ld != a.d) return hipErrorInvalidValue;
+        DenseArgs da{};
+        da.item_rs = st->at<int32_t>(lay.d_item_rs[dir]) + i0;
+        da.item_chunk = st->at<int32_t>(lay.d_item_chunk[dir]) + i0;
+        da.item_b0 = st->at<int64_t>(lay.d_item_b0[dir]) + i0;
+        da.item_nb = st->at<int32_t>(lay.d_item_nb[dir]) + i0;
+        da.item_chunks = st->at<ChunkMask>(lay.d_item_chunks[dir]) + i0;
+        da.n_items = (int32_t)n_items;
+        da.blk_cb = st->at<int32_t>(lay.d_blk_cb[dir]);
+        if (st->dense_rank1) {
+          da.bits = st->at<uint32_t>(lay.d_bits[dir]);
+          da.colscale = st->at<float>(lay.d_colscale[dir]);
+          da.rowscale = st->at<float>(lay.d_rowscale[dir]);
+        } else {
+          da.tiles = st->at<bf16_t>(lay.d_tiles[dir]);
+        }
+        da.zero_row = st->at<char>(lay.zero_row);
+        da.colslot = st->at<uint32_t>(lay.d_colslot[dir]);
+        da.src_sel = a.src_sel;
+        da.src_unsel = a.src_unsel;
+        da.d = a.d;
+        da.src_ld = a.src_ld;
+        da.vbits = a.vbits;
+        da.pass = a.pass;
+        da.mask = a.mask;
+        da.partial = st->at<float>(lay.dense_partial);
+        const int e = launch_spmm_dense(da, stream);
+        if (e != 0) return e;
+      }
+      const int e = launch_spmm(a, src_dtype, out_dtype, stream);
+      if (e != 0) return e;
+    }
+    if (a.n_long > 0) {
+      Timed tm(st, stream, 7, layer);
+      const int e = launch_spmm_reduce(a, src_dtype, out_dtype, stream);
+      if (e != 0) return e;
+    }
+  }
+  return 0;
+}
 
 // C[M x N] = A . Bt^T for a chunk's rows of a level or of an internal matrix
 GemmNtArgs nt_args(const gnnstage *st, const void *A, int a_dtype, int lda, size_t Bt, int ldb, int64_t M, int N, int K) {
@@ -1049,9 +1079,55 @@ LnArgs ln_args(const gnnstage *st, const std::vector<void *> &level, int j, int6
   return LnArgs{level_rows(st, level, j, row0), st->level_dtype(j), st->s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, M, st->s.dims[j], out, out_dtype, out_ld,
                 st->dropout(j, row0), 0};
 }
-LnBackArgs ln_back_args(const gnnstage *st, const LnArgs &f, int j, int slot, const void *dr, const void *res) {
-  return LnBackArgs{f, dr, st->cdtype(), st->s.ld[j], res, st->cdtype(), st->s.ld[j + 1], st->at<float>(st->lay.ln_partial) + (size_t)slot * st->lay.ln_stride,
-                    st->d_ln_g[j], st->d_ln_b[j]};
+
+// LayerNorm parameter sums of whole passes, which wait in scratch until all layers' (or as many as there is scratch for) are
+// added up: a sum over few rows is a launch of its own for each layer otherwise.  The rows of a layer are summed in groups
+// of chunks, a group's sums of all layers in one launch.
+struct LnSums {
+  int n_groups = 0, n_layers = 0;
+  LnReduceArgs red[kBatch][kBatch];  // [layer][group]
+  int add_up(gnnstage *st, hipStream_t stream) {
+    LnReduceArgs list[kBatch * kBatch];
+    int n = 0;
+    for (int g = 0; g < n_groups; ++g)
+      for (int i = 0; i < n_layers; ++i)
+        if (red[i][g].n_parts > 0) list[n++] = red[i][g];
+    n_layers = 0;
+    HIP_TRY(st, launch_ln_param_reduce(list, n, stream));
+    return GNNSTAGE_OK;
+  }
+};
+// Backward of layer j's LayerNorm over the rows of a span whose chunks are not in `without`: x = level rows, dr (n rows of ld_j)
+// the gradient of the activated rows, out (leading dimension out_ld, indexed by absolute row, or NULL) the gradient of x, res (n rows of ld_{j+1} or NULL)
+// the residual branch.
+int ln_backward(gnnstage *st, LnSums &sums, const std::vector<void *> &level, int j, const Span &sp, int without, const char *dr, char *out, int out_dtype, int out_ld,
+                const char *res, hipStream_t stream) {
+  const Shape &s = st->s;
+  const size_t celt = s.elt();
+  LnBackArgs l[kBatch];
+  const int n_groups = std::min(sp.c1 - sp.c0, kBatch), max_waves = kLnMaxWaves / n_groups / 4 * 4;
+  float *scratch = st->at<float>(st->lay.ln_partial) + (size_t)sums.n_layers * st->lay.ln_stride;
+  int n = 0;
+  for (int g = 0; g < n_groups; ++g) {
+    const int a = sp.c0 + (int)((int64_t)(sp.c1 - sp.c0) * g / n_groups), b = sp.c0 + (int)((int64_t)(sp.c1 - sp.c0) * (g + 1) / n_groups);
+    const int64_t row0 = s.chunk_ptr[(size_t)a], M = s.chunk_ptr[(size_t)b] - row0;
+    LnBackArgs &x = l[n++];
+    x = LnBackArgs{};
+    x.f = ln_args(st, level, j, row0, a == without && b == a + 1 ? 0 : M, out ? out + (size_t)row0 * out_ld * (out_dtype == DT_BF16 ? 2 : 4) : nullptr, out_dtype, out_ld);
+    x.dr = dr + (size_t)row0 * s.ld[j] * celt;
+    x.dr_dtype = st->cdtype();
+    x.dr_ld = s.ld[j];
+    x.res = res ? res + (size_t)row0 * s.ld[j + 1] * celt : nullptr;
+    x.res_dtype = st->cdtype();
+    x.res_ld = s.ld[j + 1];
+    x.partial = scratch + (size_t)g * (max_waves / 4) * 2 * s.dims[j];
+    x.dgamma = st->d_ln_g[j];
+    x.dbeta = st->d_ln_b[j];
+  }
+  HIP_TRY(st, launch_ln_relu_backward(l, n, max_waves, sums.red[sums.n_layers], stream));
+  sums.n_groups = n_groups;
+  sums.n_layers += 1;
+  return !sp.whole || sums.n_layers == st->lay.ln_layers ? sums.add_up(st, stream) : (int)GNNSTAGE_OK;
 }
 
 // What a pass needs before its first chunk: staged weights; ResGCN+: Rh = f(hist[j]), the activated historical rows; the
@@ -1060,6 +1136,7 @@ int begin_forward(gnnstage *st, hipStream_t stream) {
   const Shape &s = st->s;
   const int cd = st->cdtype();
   st->order.clear();
+  st->tables_written = false;
   st->fmask = ChunkMask{};
   st->bmask = ChunkMask{};
   st->n_bwd = 0;
@@ -1082,7 +1159,7 @@ int begin_forward(gnnstage *st, hipStream_t stream) {
     if (s.res()) {
       Timed t(st, stream, 1, j);
       const LnArgs a = ln_args(st, st->hist, j, 0, s.n, st->at<char>(st->lay.Th[j]), cd, s.ld[j]);
-      HIP_TRY(st, launch_ln_relu(&a, 1, stream));
+      HIP_TRY(st, launch_ln_relu(a, stream));
     } else if (s.tf[j]) {
       Timed t(st, stream, 1, j);
       GemmNtArgs g = nt_args(st, st->hist[j], st->level_dtype(j), s.dims[j], st->lay.Wt[j], s.ld[j], s.n, s.dims[j + 1], s.dims[j]);
@@ -1093,97 +1170,78 @@ int begin_forward(gnnstage *st, hipStream_t stream) {
   return GNNSTAGE_OK;
 }
 
-// Forward work of n <= Layout::cells cells that do not depend on each other (all of chunks with rows).
+// Layer j of a span's chunks (which have rows).  The chunks of a whole pass go side by side: layer j of a chunk reads rows of
+// level j alone, of the chunks processed up to its own the current ones and of the others the historical ones, whatever has been computed of
+// the levels above; so a pass is one round of launches per layer, not per chunk and layer, and a launch's rows gather from the
+// tables of one layer.
 //   aggregate first:  Z = A_hat (cur | hist); cur[j + 1] = epilogue(Z W)             GraphSage: + h_v W_self
 //   transform first:  Tc = cur W; cur[j + 1] = ReLU(A_hat (Tc | Th) + b)
 //   ResGCN+:          r_u = ReLU(LayerNorm_j(h_u)) on whichever row of u is read, z_v = sum_u A_vu r_u,
 //                     h'_v = h_v + z_v W_j + b_j; Rc[C_k] = f(cur[j][C_k]) is computed with the chunk
-int forward_cells(gnnstage *st, const Cell *cells, int n, hipStream_t stream) {
+int forward_layer(gnnstage *st, int j, const Span &sp, hipStream_t stream) {
   const Shape &s = st->s;
   const int cd = st->cdtype();
   const size_t celt = s.elt();
-  GemmNtArgs nt[kBatch];
-  LnArgs ln[kBatch];
-  int n_nt = 0, n_ln = 0;
-  for (int i = 0; i < n; ++i) {
-    const Cell &c = cells[i];
-    const int j = c.j;
-    const int64_t row0 = cell_row0(st, c.k), M = cell_rows(st, c.k);
-    const bool shared = st->hist[j] == st->cur[j];  // the level never changes: one table of its rows serves both
-    if (s.res() && !shared) {
-      ln[n_ln++] = ln_args(st, st->cur, j, row0, M, st->at<char>(st->lay.Tc[j]) + (size_t)row0 * s.ld[j] * celt, cd, s.ld[j]);
-    } else if (s.tf[j] && !shared) {  // the chunk's current rows
-      GemmNtArgs &g = nt[n_nt++] = nt_args(st, level_rows(st, st->cur, j, row0), st->level_dtype(j), s.dims[j], st->lay.Wt[j], s.ld[j], M, s.dims[j + 1], s.dims[j]);
-      nt_out(g, st->at<char>(st->lay.Tc[j]) + (size_t)row0 * s.ld[j + 1] * celt, cd, s.ld[j + 1]);
-    }
+  const int64_t row0 = span_row0(st, sp), M = span_rows(st, sp);
+  const bool shared = st->hist[j] == st->cur[j];  // the level never changes: one table of its rows serves both
+  if (!shared && s.res()) {
+    Timed t(st, stream, 1, j);
+    HIP_TRY(st, launch_ln_relu(ln_args(st, st->cur, j, row0, M, st->at<char>(st->lay.Tc[j]) + (size_t)row0 * s.ld[j] * celt, cd, s.ld[j]), stream));
+  } else if (!shared && s.tf[j]) {  // the span's current rows
+    Timed t(st, stream, 1, j);
+    GemmNtArgs g = nt_args(st, level_rows(st, st->cur, j, row0), st->level_dtype(j), s.dims[j], st->lay.Wt[j], s.ld[j], M, s.dims[j + 1], s.dims[j]);
+    nt_out(g, st->at<char>(st->lay.Tc[j]) + (size_t)row0 * s.ld[j + 1] * celt, cd, s.ld[j + 1]);
+    HIP_TRY(st, launch_gemm_nt(g, cd, stream));
   }
-  if (n_nt + n_ln > 0) {
-    Timed t(st, stream, 1, cells[0].j);
-    HIP_TRY(st, launch_gemm_nt(nt, n_nt, cd, stream));
-    HIP_TRY(st, launch_ln_relu(ln, n_ln, stream));
+  SpmmArgs a{};
+  int src_dtype = cd;
+  a.epilogue = SPMM_PLAIN;
+  if (s.tf[j] || s.res()) {
+    a.src_unsel = st->at<char>(st->lay.Th[j]);
+    a.src_sel = shared ? a.src_unsel : st->at<char>(st->lay.Tc[j]);
+    a.d = s.tf[j] ? s.dims[j + 1] : s.dims[j];
+    a.src_ld = s.tf[j] ? s.ld[j + 1] : s.ld[j];
+  } else {
+    a.src_sel = st->cur[j];
+    a.src_unsel = st->hist[j];
+    a.d = s.dims[j];
+    a.src_ld = s.dims[j];
+    src_dtype = st->level_dtype(j);
   }
-  CellSpmm sp[kBatch];
-  for (int i = 0; i < n; ++i) {
-    const Cell &c = cells[i];
-    const int j = c.j;
-    const bool shared = st->hist[j] == st->cur[j];
-    sp[i] = CellSpmm{{base_spmm(st, false, c.k, c.mask, c.slot), cd, cd}, false, c.k};
-    SpmmArgs &a = sp[i].l.a;
-    a.out_row0 = 0;
-    a.epilogue = SPMM_PLAIN;
-    if (s.tf[j] || s.res()) {
-      a.src_unsel = st->at<char>(st->lay.Th[j]);
-      a.src_sel = shared ? a.src_unsel : st->at<char>(st->lay.Tc[j]);
-      a.d = s.tf[j] ? s.dims[j + 1] : s.dims[j];
-      a.src_ld = s.tf[j] ? s.ld[j + 1] : s.ld[j];
-    } else {
-      a.src_sel = st->cur[j];
-      a.src_unsel = st->hist[j];
-      a.d = s.dims[j];
-      a.src_ld = s.dims[j];
-      sp[i].l.src_dtype = st->level_dtype(j);
-    }
-    if (s.tf[j]) {
-      a.out = st->cur[j + 1];
-      a.out_ld = s.dims[j + 1];
-      a.epilogue = SPMM_BIAS_RELU;
-      a.bias = static_cast<const float *>(st->bias[j]);
-    } else {
-      a.out = st->at<char>(st->lay.Z[j]);
-      a.out_ld = s.ld[j];
-    }
-    if (s.variant == GNNSTAGE_GCNII) {
-      a.epilogue = SPMM_MIX;
-      a.aux = st->h0;
-      a.aux_ld = s.dims[j];
-      a.s_acc = 1.f - st->alpha;
-      a.s_aux = st->alpha;
-    }
+  if (s.tf[j]) {
+    a.out = st->cur[j + 1];
+    a.out_ld = s.dims[j + 1];
+    a.epilogue = SPMM_BIAS_RELU;
+    a.bias = static_cast<const float *>(st->bias[j]);
+  } else {
+    a.out = st->at<char>(st->lay.Z[j]);
+    a.out_ld = s.ld[j];
   }
-  HIP_TRY(st, run_spmm(st, sp, n, stream, 0, cells[0].j));
-  if (s.sage()) {  // the vertex's own row through W_self, kept in fp32 until the layer's epilogue adds it
-    for (int i = 0; i < n; ++i) {
-      const Cell &c = cells[i];
-      const int j = c.j;
-      GemmNtArgs &g = nt[i] = nt_args(st, level_rows(st, st->cur, j, cell_row0(st, c.k)), st->level_dtype(j), s.dims[j], st->lay.Wt_self[j], s.ld[j],
-                                      cell_rows(st, c.k), s.dims[j + 1], s.dims[j]);
-      nt_out(g, st->at<float>(st->lay.self_fwd) + (size_t)c.slot * st->lay.self_stride, DT_F32, s.ld[j + 1]);
-    }
-    Timed t(st, stream, 1, cells[0].j);
-    HIP_TRY(st, launch_gemm_nt(nt, n, cd, stream));
+  if (s.variant == GNNSTAGE_GCNII) {
+    a.epilogue = SPMM_MIX;
+    a.aux = st->h0;
+    a.aux_ld = s.dims[j];
+    a.s_acc = 1.f - st->alpha;
+    a.s_aux = st->alpha;
   }
-  n_nt = 0;
-  for (int i = 0; i < n; ++i) {
-    const Cell &c = cells[i];
-    const int j = c.j;
-    const int64_t row0 = cell_row0(st, c.k), M = cell_rows(st, c.k);
-    char *out = static_cast<char *>(st->cur[j + 1]) + (size_t)row0 * s.dims[j + 1] * celt;
-    if (s.tf[j]) {
-      if (st->output_dropout())  // on the rows just written, in place
-        HIP_TRY(st, launch_dropout_rows(out, cd, M, s.dims[j + 1], s.dims[j + 1], st->dropout(j, row0), stream));
-      continue;
+  HIP_TRY(st, run_spmm(st, a, src_dtype, cd, false, sp, span_select(st, sp, SEL_FORWARD), stream, 0, j));
+  char *const level = static_cast<char *>(st->cur[j + 1]);
+  if (s.tf[j]) {
+    if (st->output_dropout())  // on the rows just written, in place
+      HIP_TRY(st, launch_dropout_rows(level + (size_t)row0 * s.dims[j + 1] * celt, cd, M, s.dims[j + 1], s.dims[j + 1], st->dropout(j, row0), stream));
+    return GNNSTAGE_OK;
+  }
+  Timed t(st, stream, 1, j);
+  // GraphSage: blocks of rows, the vertex's own row through W_self kept in fp32 until the layer's epilogue adds it
+  const int64_t step = s.sage() ? st->lay.self_rows : M;
+  for (int64_t r = row0; r < row0 + M; r += step) {
+    const int64_t m = std::min(step, row0 + M - r);
+    if (s.sage()) {
+      GemmNtArgs g = nt_args(st, level_rows(st, st->cur, j, r), st->level_dtype(j), s.dims[j], st->lay.Wt_self[j], s.ld[j], m, s.dims[j + 1], s.dims[j]);
+      nt_out(g, st->at<float>(st->lay.self_fwd), DT_F32, s.ld[j + 1]);
+      HIP_TRY(st, launch_gemm_nt(g, cd, stream));
     }
-    GemmNtArgs &g = nt[n_nt++] = nt_args(st, st->at<char>(st->lay.Z[j]) + (size_t)row0 * s.ld[j] * celt, cd, s.ld[j], st->lay.Wt[j], s.ld[j], M, s.dims[j + 1], s.dims[j]);
+    GemmNtArgs g = nt_args(st, st->at<char>(st->lay.Z[j]) + (size_t)r * s.ld[j] * celt, cd, s.ld[j], st->lay.Wt[j], s.ld[j], m, s.dims[j + 1], s.dims[j]);
     if (s.variant == GNNSTAGE_GCNII) {
       g.epilogue = EPI_FWD_GCNII;
       g.aux = g.A;
@@ -1195,22 +1253,19 @@ int forward_cells(gnnstage *st, const Cell *cells, int n, hipStream_t stream) {
       g.bias = static_cast<const float *>(st->bias[j]);
       if (s.sage()) {
         g.epilogue = EPI_FWD_ADD;
-        g.aux = st->at<float>(st->lay.self_fwd) + (size_t)c.slot * st->lay.self_stride;
+        g.aux = st->at<float>(st->lay.self_fwd);
         g.aux_dtype = DT_F32;
         g.aux_ld = s.ld[j + 1];
       } else if (s.res()) {
         g.epilogue = EPI_RES;
-        g.aux = level_rows(st, st->cur, j, row0);
+        g.aux = level_rows(st, st->cur, j, r);
         g.aux_dtype = st->level_dtype(j);
         g.aux_ld = s.dims[j];
       }
     }
-    nt_out(g, out, cd, s.dims[j + 1]);
-    if (st->output_dropout()) g.drop = st->dropout(j, row0);
-  }
-  if (n_nt > 0) {
-    Timed t(st, stream, 1, cells[0].j);
-    HIP_TRY(st, launch_gemm_nt(nt, n_nt, cd, stream));
+    nt_out(g, level + (size_t)r * s.dims[j + 1] * celt, cd, s.dims[j + 1]);
+    if (st->output_dropout()) g.drop = st->dropout(j, r);
+    HIP_TRY(st, launch_gemm_nt(g, cd, stream));
   }
   return GNNSTAGE_OK;
 }
@@ -1262,41 +1317,56 @@ int flush_deferred_wgrad(gnnstage *st, hipStream_t stream) {
   return GNNSTAGE_OK;
 }
 
-// After the last backward call of a pass: the history-side weight gradient of every transform-first
-// layer, dW += hist^T (A_hat^T dY), chunk by chunk through the gradient scratch rows.
+// The spans of the work behind a pass's last backward call: all chunks side by side, one by one while launches are timed (a
+// timed launch belongs to one chunk's share).  earlier: with the masks of the chunks in front of each in the forward order.
+int finish_spans(gnnstage *st, bool earlier, std::vector<Span> &spans, hipStream_t stream) {
+  spans.clear();
+  ChunkMask m{};
+  if (st->prof.kinds == 0) {
+    spans.push_back(whole_span(st));
+    spans[0].mask = ChunkMask{};
+    for (int c = 0; c < st->s.K && !earlier; ++c) mask_set(spans[0].mask, (uint32_t)c);
+    return earlier ? write_pass_tables(st, st->order, stream) : (int)GNNSTAGE_OK;
+  }
+  for (int c = 0; c < st->s.K && !earlier; ++c) mask_set(m, c);
+  for (size_t i = 0; i < st->order.size(); ++i) {
+    const int c = st->order[i];
+    if (st->s.chunk_ptr[(size_t)c + 1] > st->s.chunk_ptr[(size_t)c]) spans.push_back(chunk_span(c, m));
+    if (earlier) mask_set(m, c);
+  }
+  return GNNSTAGE_OK;
+}
+
+// After the last backward call of a pass: the history-side weight gradient of every transform-first layer, dW += hist^T dT.
+// dT sums over the readers that saw the historical row; over all readers where the current side has not been taken (a level
+// that serves as both and has no gradient of its own, see backward_layer).
 int finish_transform_first(gnnstage *st, hipStream_t stream) {
   const Shape &s = st->s;
   const int cd = st->cdtype();
-  ChunkMask all{};
-  for (int c = 0; c < s.K; ++c) mask_set(all, c);
-  std::vector<Cell> cells;
-  for (int j = 0; j < s.L; ++j)
-    for (int c = 0; c < s.K && s.tf[j]; ++c)
-      if (cell_rows(st, c) > 0) cells.push_back(Cell{c, j, 0, all});
-  return in_turns(st, (int)cells.size(), [&](int first, int n) {
-    CellSpmm sp[kBatch];
-    for (int i = 0; i < n; ++i) {
-      const Cell &c = cells[(size_t)(first + i)];
-      sp[i] = CellSpmm{{base_spmm(st, true, c.k, all, i), cd, cd}, true, c.k};
-      SpmmArgs &a = sp[i].l.a;
-      a.src_sel = st->at<char>(st->lay.dZ[c.j]);
+  std::vector<Span> spans;
+  for (int j = 0; j < s.L; ++j) {
+    if (!s.tf[j]) continue;
+    const bool all = st->hist[j] == st->cur[j] && j == 0 && !s.need_input_grad;
+    const int rc = finish_spans(st, !all, spans, stream);
+    if (rc != GNNSTAGE_OK) return rc;
+    for (const Span &sp : spans) {
+      SpmmArgs a{};
+      a.src_sel = st->at<char>(st->lay.dZ[j]);
       a.src_unsel = nullptr;
-      a.d = s.dims[c.j + 1];
-      a.src_ld = s.ld[c.j + 1];
-      a.out = st->at<char>(st->lay.G[0]) + (size_t)i * st->lay.row_stride * s.elt();
-      a.out_ld = s.ld[c.j + 1];
-      a.out_row0 = cell_row0(st, c.k);
+      a.d = s.dims[j + 1];
+      a.src_ld = s.ld[j + 1];
+      a.out = st->at<char>(st->lay.Th[j]);  // the transformed historical rows have been read for the last time
+      a.out_ld = s.ld[j + 1];
       a.epilogue = SPMM_PLAIN;
+      HIP_TRY(st, run_spmm(st, a, cd, cd, true, sp, all ? SEL_MASK : span_select(st, sp, SEL_EARLIER), stream, 2, j));
+      Timed t(st, stream, 4, j);
+      const int64_t row0 = span_row0(st, sp);
+      HIP_TRY(st, launch_gemm_tn(tn_args(st, level_rows(st, st->hist, j, row0), st->level_dtype(j), s.dims[j],
+                                         st->at<char>(st->lay.Th[j]) + (size_t)row0 * s.ld[j + 1] * s.elt(), s.ld[j + 1], span_rows(st, sp), s.dims[j], s.dims[j + 1],
+                                         1.f, st->dW[j]), cd, stream));
     }
-    HIP_TRY(st, run_spmm(st, sp, n, stream, 2, cells[(size_t)first].j));
-    for (int i = 0; i < n; ++i) {
-      const Cell &c = cells[(size_t)(first + i)];
-      Timed t(st, stream, 4, c.j);
-      HIP_TRY(st, launch_gemm_tn(tn_args(st, level_rows(st, st->hist, c.j, cell_row0(st, c.k)), st->level_dtype(c.j), s.dims[c.j], sp[i].l.a.out, s.ld[c.j + 1],
-                                         cell_rows(st, c.k), s.dims[c.j], s.dims[c.j + 1], 1.f, st->dW[c.j]), cd, stream));
-    }
-    return (int)GNNSTAGE_OK;
-  });
+  }
+  return GNNSTAGE_OK;
 }
 
 // ResGCN+, after the last backward chunk: the LayerNorm of layer j was also applied to the historical rows, so its
@@ -1305,39 +1375,28 @@ int finish_transform_first(gnnstage *st, hipStream_t stream) {
 int res_backward_finish(gnnstage *st, hipStream_t stream) {
   const Shape &s = st->s;
   const int cd = st->cdtype();
-  std::vector<Cell> cells;
-  ChunkMask earlier{};  // chunks in front of the current one, grown along the forward order
-  for (size_t pos = 0; pos < st->order.size(); ++pos) {
-    const int c = st->order[pos];
-    for (int j = 0; j < s.L && pos > 0 && cell_rows(st, c) > 0; ++j) cells.push_back(Cell{c, j, 0, earlier});
-    mask_set(earlier, c);
-  }
-  return in_turns(st, (int)cells.size(), [&](int first, int n) {
-    CellSpmm sp[kBatch];
-    for (int i = 0; i < n; ++i) {
-      const Cell &c = cells[(size_t)(first + i)];
-      sp[i] = CellSpmm{{base_spmm(st, true, c.k, c.mask, i), cd, cd}, true, c.k};
-      SpmmArgs &a = sp[i].l.a;
-      a.src_sel = st->at<char>(st->lay.dZ[c.j]);
+  std::vector<Span> spans;
+  const int rc = finish_spans(st, true, spans, stream);
+  if (rc != GNNSTAGE_OK) return rc;
+  LnSums sums;
+  for (int j = 0; j < s.L; ++j)
+    for (const Span &sp : spans) {
+      if (!sp.whole && sp.c0 == st->order[0]) continue;  // nothing of it was read as historical rows
+      SpmmArgs a{};
+      a.src_sel = st->at<char>(st->lay.dZ[j]);
       a.src_unsel = nullptr;
-      a.d = s.dims[c.j];
-      a.src_ld = s.ld[c.j];
-      a.out = st->at<char>(st->lay.res_dr) + (size_t)i * st->lay.row_stride * s.elt();
-      a.out_ld = s.ld[c.j];
-      a.out_row0 = cell_row0(st, c.k);
+      a.d = s.dims[j];
+      a.src_ld = s.ld[j];
+      a.out = st->at<char>(st->lay.Th[j]);
+      a.out_ld = s.ld[j];
       a.epilogue = SPMM_PLAIN;
+      HIP_TRY(st, run_spmm(st, a, cd, cd, true, sp, span_select(st, sp, SEL_EARLIER), stream, 2, j));
+      Timed t(st, stream, 4, j);
+      // no row of the chunk that came first was read as a historical one
+      const int e = ln_backward(st, sums, st->hist, j, sp, st->order[0], st->at<char>(st->lay.Th[j]), nullptr, cd, 0, nullptr, stream);
+      if (e != GNNSTAGE_OK) return e;
     }
-    HIP_TRY(st, run_spmm(st, sp, n, stream, 2, cells[(size_t)first].j));
-    // no more cells at once than layers, and the layers of a chunk follow each other: every layer comes once
-    LnBackArgs ln[kBatch];
-    for (int i = 0; i < n; ++i) {
-      const Cell &c = cells[(size_t)(first + i)];
-      ln[i] = ln_back_args(st, ln_args(st, st->hist, c.j, cell_row0(st, c.k), cell_rows(st, c.k), nullptr, cd, 0), c.j, i, sp[i].l.a.out, nullptr);
-    }
-    Timed t(st, stream, 4, cells[(size_t)first].j);
-    HIP_TRY(st, launch_ln_relu_backward(ln, n, stream));
-    return (int)GNNSTAGE_OK;
-  });
+  return sums.add_up(st, stream);
 }
 
 // Where dY_j = dL/d(pre-activation of layer j) of a chunk's rows lives, [M x ld_{j+1}], zero in the padding
@@ -1345,9 +1404,9 @@ int res_backward_finish(gnnstage *st, hipStream_t stream) {
 // keep that matrix anyway, it is what later chunks' transposed aggregations gather); otherwise one of two
 // chunk-sized scratch matrices, used alternately.
 char *full_dY(const gnnstage *st, int j) { return st->at<char>(st->s.tf[j] ? st->lay.dZ[j] : st->lay.dY[j]); }
-char *dY_rows(const gnnstage *st, int k, int j) {
+char *dY_rows(const gnnstage *st, int64_t row0, int j) {
   if (!st->s.defer_wgrad()) return st->at<char>(st->lay.G[st->gi]);
-  return full_dY(st, j) + (size_t)cell_row0(st, k) * st->s.ld[(size_t)j + 1] * st->s.elt();
+  return full_dY(st, j) + (size_t)row0 * st->s.ld[(size_t)j + 1] * st->s.elt();
 }
 
 // dY of the top layer for rows [row0, row0 + M): the upstream gradient behind the activation's derivative (ResGCN+: no
@@ -1363,174 +1422,133 @@ int top_dY(gnnstage *st, const void *grad_rows, int64_t row0, int64_t M, char *o
   return GNNSTAGE_OK;
 }
 
-// Backward work of n <= Layout::cells cells that do not depend on each other (all of chunks with rows).  whole_pass: the bias
-// gradients of transform-first layers are taken over all rows at the end of the pass.
-int backward_cells(gnnstage *st, const Cell *cells, int n, bool whole_pass, hipStream_t stream) {
+// Layer j of a span's chunks on the way back; layers from the top.  Layer j of a chunk gathers gradient rows of layer j alone, of the chunks
+// whose turn has come, so the chunks of a whole pass go side by side here too.
+int backward_layer(gnnstage *st, LnSums &sums, int j, const Span &sp, hipStream_t stream) {
   const Shape &s = st->s;
   const int cd = st->cdtype();
   const size_t celt = s.elt();
-  const bool defer = s.defer_wgrad();
-  auto need_prev = [&](int j) { return j > 0 || s.need_input_grad; };
-  auto shared = [&](int j) { return st->hist[j] == st->cur[j]; };
+  const int64_t row0 = span_row0(st, sp), M = span_rows(st, sp);
+  const bool defer = s.defer_wgrad(), need_prev = j > 0 || s.need_input_grad, shared = st->hist[j] == st->cur[j];
+  char *const dY = dY_rows(st, row0, j);
+  // where the gradient of level j goes: leading dimension, type, first row (of all rows, or of the span's alone)
+  const int prev_ld = j > 0 ? s.ld[j] : s.dims[0], prev_dtype = st->level_dtype(j);
+  const bool prev_all = j == 0 || defer;
+  char *const prev = j == 0 ? static_cast<char *>(st->grad_in) : defer ? full_dY(st, j - 1) : st->at<char>(st->lay.G[st->gi ^ 1]);
+  char *const prev_rows = prev == nullptr ? nullptr : prev + (prev_all ? (size_t)row0 * prev_ld * (prev_dtype == DT_BF16 ? 2 : 4) : 0);
   // ---- bias gradients of transform-first layers, weight gradients that are not deferred; input-gradient products
-  GemmNtArgs nt[kBatch], nt_self[kBatch];
-  int n_nt = 0, n_self = 0;
-  for (int i = 0; i < n; ++i) {
-    const Cell &c = cells[i];
-    const int j = c.j;
-    const int64_t row0 = cell_row0(st, c.k), M = cell_rows(st, c.k);
-    const char *dY = dY_rows(st, c.k, j);
-    if (s.tf[j]) {
-      // bias gradient = column sums of dY: fused into the weight-gradient product where that product reads dY
-      // (aggregate-first layers), a kernel of its own for transform-first layers
-      if (s.has_bias() && !whole_pass) {
-        Timed t(st, stream, 4, j);
-        HIP_TRY(st, launch_colsum_add(dY, cd, s.ld[j + 1], (int)M, s.dims[j + 1], st->at<float>(st->lay.bias_partial), kMaxSplits, st->dbias[j], stream));
-      }
-      if (!defer) {
-        Timed t(st, stream, 6);
-        HIP_TRY(st, launch_copy(dY, full_dY(st, j) + (size_t)row0 * s.ld[j + 1] * celt, (size_t)M * s.ld[j + 1] * celt, stream));
-      }
-      continue;
+  SpmmArgs a{};
+  if (s.tf[j]) {
+    // bias gradient = column sums of dY: fused into the weight-gradient product where that product reads dY
+    // (aggregate-first layers), a kernel of its own for transform-first layers
+    if (s.has_bias()) {
+      Timed t(st, stream, 4, j);
+      HIP_TRY(st, launch_colsum_add(dY, cd, s.ld[j + 1], (int)M, s.dims[j + 1], st->at<float>(st->lay.bias_partial), kMaxSplits, st->dbias[j], stream));
     }
+    if (!defer) {
+      Timed t(st, stream, 6);
+      HIP_TRY(st, launch_copy(dY, full_dY(st, j) + (size_t)row0 * s.ld[j + 1] * celt, (size_t)M * s.ld[j + 1] * celt, stream));
+    }
+  } else {
     if (!defer) {
       const int rc = wgrad_rows(st, j, row0, M, dY, stream);
       if (rc != GNNSTAGE_OK) return rc;
     }
-    if (!s.res() && !need_prev(j)) continue;
-    GemmNtArgs &g = nt[n_nt++] = nt_args(st, dY, cd, s.ld[j + 1], st->lay.Wn[j], s.ld[j + 1], M, s.dims[j], s.dims[j + 1]);
-    nt_out(g, st->at<char>(st->lay.dZ[j]) + (size_t)row0 * s.ld[j] * celt, cd, s.ld[j]);
-    if (s.variant == GNNSTAGE_GCNII) {
-      g.epilogue = EPI_DGRAD_GCNII;
-      g.aux = dY;
-      g.aux_dtype = cd;
-      g.aux_ld = s.ld[j + 1];
-      g.alpha = st->alpha;
-      g.beta = st->beta[j];
-      g.h0grad = st->grad_h0 ? st->grad_h0 + (size_t)row0 * s.dims[j] : nullptr;
-      g.h0_ld = s.dims[j];
-    }
-    if (s.sage()) {  // the gradient that reaches the chunk's own rows directly: dY W_self^T
-      GemmNtArgs &gs = nt_self[n_self++] = g;
-      gs.Bt = st->at<char>(st->lay.Wn_self[j]);
-      gs.out = st->at<char>(st->lay.self_bwd) + (size_t)c.slot * st->lay.self_stride * celt;
-    }
-  }
-  if (n_nt > 0) {
-    Timed t(st, stream, 3, cells[0].j);
-    HIP_TRY(st, launch_gemm_nt(nt, n_nt, cd, stream));
-    if (n_self > 0) HIP_TRY(st, launch_gemm_nt(nt_self, n_self, cd, stream));
-  }
-  // ---- transposed aggregations; Section 3.4: nothing flows back from unprocessed vertices
-  CellSpmm sp[kBatch];
-  int n_sp = 0, of[kBatch];
-  for (int i = 0; i < n; ++i) {
-    const Cell &c = cells[i];
-    const int j = c.j;
-    const int64_t row0 = cell_row0(st, c.k);
-    // transform first: see below; nothing else depends on dT_cur when the level is shared and has no gradient.
-    if (s.tf[j] ? shared(j) && !need_prev(j) : !s.res() && !need_prev(j)) continue;
-    of[n_sp] = i;
-    CellSpmm &x = sp[n_sp++] = CellSpmm{{base_spmm(st, true, c.k, c.mask, c.slot), cd, cd}, true, c.k};
-    SpmmArgs &a = x.l.a;
-    a.src_sel = s.tf[j] ? full_dY(st, j) : st->at<char>(st->lay.dZ[j]);
-    a.src_unsel = nullptr;
-    a.d = s.tf[j] ? s.dims[j + 1] : s.dims[j];
-    a.src_ld = s.tf[j] ? s.ld[j + 1] : s.ld[j];
-    a.epilogue = SPMM_PLAIN;
-    a.out_row0 = row0;
-    a.out_ld = a.src_ld;
-    if (s.tf[j]) {
-      a.out = st->at<char>(st->lay.G[defer ? 0 : st->gi ^ 1]) + (size_t)c.slot * st->lay.row_stride * celt;
-    } else if (s.res()) {
-      a.out = st->at<char>(st->lay.res_dr) + (size_t)c.slot * st->lay.row_stride * celt;
-    } else {
-      if (s.sage()) {
-        a.add = st->at<char>(st->lay.self_bwd) + (size_t)c.slot * st->lay.self_stride * celt;
-        a.add_ld = s.ld[j];
+    if (s.res() || need_prev) {
+      Timed t(st, stream, 3, j);
+      GemmNtArgs g = nt_args(st, dY, cd, s.ld[j + 1], st->lay.Wn[j], s.ld[j + 1], M, s.dims[j], s.dims[j + 1]);
+      nt_out(g, st->at<char>(st->lay.dZ[j]) + (size_t)row0 * s.ld[j] * celt, cd, s.ld[j]);
+      if (s.variant == GNNSTAGE_GCNII) {
+        g.epilogue = EPI_DGRAD_GCNII;
+        g.aux = dY;
+        g.aux_dtype = cd;
+        g.aux_ld = s.ld[j + 1];
+        g.alpha = st->alpha;
+        g.beta = st->beta[j];
+        g.h0grad = st->grad_h0 ? st->grad_h0 + (size_t)row0 * s.dims[j] : nullptr;
+        g.h0_ld = s.dims[j];
+      }
+      HIP_TRY(st, launch_gemm_nt(g, cd, stream));
+      if (s.sage()) {  // the gradient that reaches the chunk's own rows directly: dY W_self^T
+        g.Bt = st->at<char>(st->lay.Wn_self[j]);
+        const bool in_place = s.self_in_place(j);
+        char *const at = in_place ? prev_rows : st->at<char>(st->lay.self_bwd) + (size_t)row0 * s.ld[j] * celt;
+        nt_out(g, at, cd, in_place ? prev_ld : s.ld[j]);
+        a.add = at;
+        a.add_ld = g.out_ld;
         a.add_row0 = row0;
-      }
-      if (j > 0) {
-        if (defer) {  // straight into the chunk's rows of dY_{j-1}
-          a.out = full_dY(st, j - 1);
-          a.out_row0 = 0;
-        } else {
-          a.out = st->at<char>(st->lay.G[st->gi ^ 1]);
-        }
-        a.epilogue = s.sage() ? SPMM_ADD_MASK : SPMM_MASK;
-        a.mask_scale = st->mask_scale();
-        a.aux = st->cur[j];
-        a.aux_ld = s.dims[j];
-      } else {
-        a.out = st->grad_in;
-        a.out_ld = s.dims[0];
-        a.out_row0 = 0;
-        a.epilogue = s.sage() ? SPMM_ADD : SPMM_PLAIN;
-        x.l.out_dtype = st->level_dtype(0);
+        HIP_TRY(st, launch_gemm_nt(g, cd, stream));
       }
     }
   }
-  if (n_sp > 0) HIP_TRY(st, run_spmm(st, sp, n_sp, stream, 2, cells[of[0]].j));
-  // ---- behind them
-  LnBackArgs ln[kBatch];
-  int n_ln = 0;
-  n_nt = 0;
-  for (int x = 0; x < n_sp; ++x) {
-    const Cell &c = cells[of[x]];
-    const int j = c.j;
-    const int64_t row0 = cell_row0(st, c.k), M = cell_rows(st, c.k);
-    const void *dT = sp[x].l.a.out;
-    if (s.res()) {  // back through ReLU and LayerNorm of the chunk's own (current) rows, plus the residual branch
-      void *out = nullptr;
-      int out_ld = 0;
-      if (j > 0) {
-        out = defer ? dY_rows(st, c.k, j - 1) : st->at<char>(st->lay.G[st->gi ^ 1]);
-        out_ld = s.ld[j];
-      } else if (s.need_input_grad) {
-        out = static_cast<char *>(st->grad_in) + (size_t)row0 * s.dims[0] * st->level_elt(0);
-        out_ld = s.dims[0];
-      }
-      ln[n_ln++] = ln_back_args(st, ln_args(st, st->cur, j, row0, M, out, st->level_dtype(j), out_ld), j, c.slot, dT, dY_rows(st, c.k, j));
-      continue;
+  // ---- transposed aggregation; Section 3.4: nothing flows back from unprocessed vertices
+  // transform first: see below; nothing else depends on dT_cur when the level is shared and has no gradient.
+  if (s.tf[j] ? shared && !need_prev : !s.res() && !need_prev) {
+    if (!defer && !s.tf[j]) st->gi ^= 1;
+    return GNNSTAGE_OK;
+  }
+  int out_dtype = cd;
+  a.src_sel = s.tf[j] ? full_dY(st, j) : st->at<char>(st->lay.dZ[j]);
+  a.src_unsel = nullptr;
+  a.d = s.tf[j] ? s.dims[j + 1] : s.dims[j];
+  a.src_ld = s.tf[j] ? s.ld[j + 1] : s.ld[j];
+  a.epilogue = SPMM_PLAIN;
+  a.out_ld = a.src_ld;
+  if (s.tf[j] && defer) {
+    a.out = st->at<char>(st->lay.Tc[j]);  // the transformed current rows have been read for the last time
+  } else if (s.tf[j]) {
+    a.out = st->at<char>(st->lay.G[st->gi ^ 1]);
+    a.out_row0 = row0;
+  } else if (s.res()) {
+    a.out = st->at<char>(st->lay.Th[j]);  // and the activated historical ones
+  } else {
+    a.out = prev;
+    a.out_row0 = prev_all ? 0 : row0;
+    a.out_ld = prev_ld;
+    out_dtype = prev_dtype;
+    if (j > 0) {
+      a.epilogue = s.sage() ? SPMM_ADD_MASK : SPMM_MASK;
+      a.mask_scale = st->mask_scale();
+      a.aux = st->cur[j];
+      a.aux_ld = s.dims[j];
+    } else {
+      a.epilogue = s.sage() ? SPMM_ADD : SPMM_PLAIN;
     }
-    if (!s.tf[j]) continue;
+  }
+  HIP_TRY(st, run_spmm(st, a, cd, out_dtype, true, sp, span_select(st, sp, SEL_BACKWARD), stream, 2, j));
+  // ---- behind it
+  if (s.res()) {  // back through ReLU and LayerNorm of the span's own (current) rows, plus the residual branch
+    Timed t(st, stream, 4, j);
+    char *const all = !need_prev ? nullptr : prev_all ? prev : prev - (size_t)row0 * prev_ld * celt;
+    const int rc = ln_backward(st, sums, st->cur, j, sp, -1, st->at<char>(st->lay.Th[j]), all, prev_dtype, prev_ld, dY - (size_t)row0 * s.ld[j + 1] * celt, stream);
+    if (rc != GNNSTAGE_OK) return rc;
+  } else if (s.tf[j]) {
     // Layer computed as A_hat (H W).  With T = H W:  dL/dW = cur^T dT_cur + hist^T dT_hist, where
     // dT_cur[u] sums A_vu dY[v] over the readers v that saw u's CURRENT row (exactly the vertices
-    // already processed in this backward pass) and dT_hist over the readers that saw its history.
-    // dT_cur + dT_hist is the unmasked transposed aggregation, known only when every chunk's dY is:
-    //   dW += (cur - hist)[C_k]^T dT_cur[C_k]   here, per chunk,
-    //   dW += hist^T (A_hat^T dY)                after the last chunk (finish_transform_first).
-    if (!shared(j)) {
+    // already processed in this backward pass) and dT_hist over the readers that saw its history.  The first is taken here, the
+    // second, which is known only when every chunk's dY is, after the last chunk (finish_transform_first).
+    const char *dT = static_cast<const char *>(a.out) + (defer ? (size_t)row0 * s.ld[j + 1] * celt : 0);
+    {
       Timed t(st, stream, 4, j);
-      GemmTnArgs w = tn_args(st, level_rows(st, st->cur, j, row0), st->level_dtype(j), s.dims[j], dT, s.ld[j + 1], M, s.dims[j], s.dims[j + 1], 1.f, st->dW[j]);
-      HIP_TRY(st, launch_gemm_tn(w, cd, stream));
-      w.A = level_rows(st, st->hist, j, row0);
-      w.scale = -1.f;
-      HIP_TRY(st, launch_gemm_tn(w, cd, stream));
+      HIP_TRY(st, launch_gemm_tn(tn_args(st, level_rows(st, st->cur, j, row0), st->level_dtype(j), s.dims[j], dT, s.ld[j + 1], M, s.dims[j], s.dims[j + 1], 1.f, st->dW[j]),
+                                 cd, stream));
     }
-    if (!need_prev(j)) continue;
-    GemmNtArgs &g = nt[n_nt++] = nt_args(st, dT, cd, s.ld[j + 1], st->lay.Wn[j], s.ld[j + 1], M, s.dims[j], s.dims[j + 1]);
-    if (j > 0) {
-      g.epilogue = EPI_MASK;
-      g.mask_scale = st->mask_scale();
-      g.aux = level_rows(st, st->cur, j, row0);
-      g.aux_dtype = cd;
-      g.aux_ld = s.dims[j];
-      nt_out(g, defer ? dY_rows(st, c.k, j - 1) : st->at<char>(st->lay.G[st->gi]), cd, s.ld[j]);  // without deferral dY_j is dead by now and its scratch is reused
-      g.out_pad = s.ld[j];
-    } else {
-      nt_out(g, static_cast<char *>(st->grad_in) + (size_t)row0 * s.dims[0] * st->level_elt(0), st->level_dtype(0), s.dims[0]);
+    if (need_prev) {
+      Timed t(st, stream, 3, j);
+      GemmNtArgs g = nt_args(st, dT, cd, s.ld[j + 1], st->lay.Wn[j], s.ld[j + 1], M, s.dims[j], s.dims[j + 1]);
+      nt_out(g, j > 0 && !defer ? st->at<char>(st->lay.G[st->gi]) : prev_rows, prev_dtype, prev_ld);  // without deferral dY_j is dead by now and its scratch is reused
+      if (j > 0) {
+        g.epilogue = EPI_MASK;
+        g.mask_scale = st->mask_scale();
+        g.aux = level_rows(st, st->cur, j, row0);
+        g.aux_dtype = cd;
+        g.aux_ld = s.dims[j];
+        g.out_pad = s.ld[j];
+      }
+      HIP_TRY(st, launch_gemm_nt(g, cd, stream));
     }
   }
-  if (n_ln > 0) {
-    Timed t(st, stream, 4, cells[0].j);
-    HIP_TRY(st, launch_ln_relu_backward(ln, n_ln, stream));
-  }
-  if (n_nt > 0) {
-    Timed t(st, stream, 3, cells[0].j);
-    HIP_TRY(st, launch_gemm_nt(nt, n_nt, cd, stream));
-  }
-  if (!defer && !s.tf[cells[0].j]) st->gi ^= 1;  // one cell at a time then
+  if (!defer && !s.tf[j]) st->gi ^= 1;
   return GNNSTAGE_OK;
 }
 
@@ -1543,15 +1561,11 @@ int end_backward(gnnstage *st, hipStream_t stream) {
   return st->s.res() ? res_backward_finish(st, stream) : finish_transform_first(st, stream);
 }
 
-// A whole pass in anti-diagonals.  In the forward pass layer j of the chunk at position p reads level j of the chunks at
-// positions up to p, which are written by layer j - 1 at positions up to p; so the cells with p + j = t depend only on
-// those with smaller sums, and the launches of a diagonal run as one.  Backward the same with positions from the end and
-// layers from the top: layer j at position b gathers the gradient rows of layer j at positions up to b.  What a pass of K
-// chunks and L layers costs is then K + L - 1 rounds of launches of up to min(K, L) times the work instead of K * L.
+// Whether a pass may run layer by layer over all of its chunks.
 bool whole_pass_ok(const gnnstage *st, const int32_t *order, int n) {
-  if (n != st->s.K || st->lay.cells <= 1 || st->prof.kinds != 0) return false;  // (timed launches belong to one layer each)
-  // a level above 0 that is its own history: what a chunk does not select are the rows of the last pass, which a later
-  // chunk's cell of the same diagonal would be overwriting
+  if (n != st->s.K || !st->s.defer_wgrad() || st->prof.kinds != 0) return false;  // (timed launches belong to one chunk each)
+  // a level above 0 that is its own history: what a chunk does not select are the rows of the last pass, which the level below
+  // would have overwritten
   for (int j = 1; j < st->s.L; ++j)
     if (st->hist[j] == st->cur[j]) return false;
   std::vector<char> seen((size_t)n, 0);
@@ -1560,30 +1574,6 @@ bool whole_pass_ok(const gnnstage *st, const int32_t *order, int n) {
     seen[(size_t)order[i]] = 1;
   }
   return true;
-}
-
-// order[i]: the chunk at position i; layer_of(step of the cell along its chunk); run(cells, n)
-template <typename L, typename F>
-int run_diagonals(gnnstage *st, const std::vector<int32_t> &order, L layer_of, F run) {
-  const Shape &s = st->s;
-  std::vector<ChunkMask> mask((size_t)s.K);
-  ChunkMask m{};
-  for (int i = 0; i < s.K; ++i) {
-    mask_set(m, order[(size_t)i]);
-    mask[(size_t)i] = m;
-  }
-  std::vector<Cell> cells;
-  for (int t = 0; t < s.K + s.L - 1; ++t) {
-    cells.clear();
-    for (int i = std::max(0, t - (s.L - 1)); i <= std::min(s.K - 1, t); ++i)
-      if (cell_rows(st, order[(size_t)i]) > 0) cells.push_back(Cell{order[(size_t)i], layer_of(t - i), 0, mask[(size_t)i]});
-    const int rc = in_turns(st, (int)cells.size(), [&](int first, int n) {
-      for (int i = 0; i < n; ++i) cells[(size_t)(first + i)].slot = i;
-      return run(&cells[(size_t)first], n);
-    });
-    if (rc != GNNSTAGE_OK) return rc;
-  }
-  return GNNSTAGE_OK;
 }
 
 }  // namespace
@@ -1767,39 +1757,45 @@ extern "C" int gnnstage_create(const gnnstage_desc *d, gnnstage_t **out) try {
     st->h_pcol = pcol;
   }
 
-  // schedules: build on the host chunk by chunk, upload into the preallocated arrays
+  // schedules: built on the host chunk by chunk, put into sections (DirTasks), uploaded into the preallocated arrays
   const int classes = s.classes();
-  auto build = [&](const HostDir &h, const uint32_t *packed, bool transposed, std::vector<TaskList> &lists) -> int {
+  auto build = [&](const HostDir &h, const uint32_t *packed, int dir) -> int {
     const int64_t *ptr = h.ptr;
     const int32_t *idx = h.idx;
     const PlanCounts &pc = h.pc;
-    const int dir = transposed ? 1 : 0;
-    lists.resize(s.K);
-    int64_t t_off = 0, l_off = 0, s_off = 0;
-    for (int c = 0; c < s.K; ++c) {
-      TaskList &tl = lists[c];
-      tl.slot_class = st->at<uint8_t>(transposed ? lay.b_slot_class : lay.f_slot_class) + s_off;
-      s_off += pc.slots[c];
-      tl.task_row = st->at<int32_t>(transposed ? lay.b_task_row : lay.f_task_row) + t_off;
-      tl.task_e0 = st->at<int64_t>(transposed ? lay.b_task_e0 : lay.f_task_e0) + t_off;
-      tl.task_ne = st->at<int32_t>(transposed ? lay.b_task_ne : lay.f_task_ne) + t_off;
-      tl.task_slot = st->at<int32_t>(transposed ? lay.b_task_slot : lay.f_task_slot) + t_off;
-      tl.lr_row = st->at<int32_t>(transposed ? lay.b_lr_row : lay.f_lr_row) + l_off;
-      tl.lr_slot0 = st->at<int32_t>(transposed ? lay.b_lr_slot0 : lay.f_lr_slot0) + l_off;
-      tl.lr_nslots = st->at<int32_t>(transposed ? lay.b_lr_n : lay.f_lr_n) + l_off;
-      if (h.dense()) {
-        tl.lr_dense0 = st->at<int32_t>(lay.d_lr_dense0[dir]) + l_off;
-        tl.lr_ndense = st->at<int32_t>(lay.d_lr_ndense[dir]) + l_off;
-        tl.lr_item0 = st->at<int32_t>(lay.d_lr_item0[dir]) + l_off;
-        tl.item0 = h.chunk_item_off[(size_t)c];
-        tl.n_items = (int)(h.chunk_item_off[(size_t)c + 1] - h.chunk_item_off[(size_t)c]);
+    DirTasks &t = st->tasks[dir];
+    t.K = s.K;
+    t.n_classes = classes > 1 ? classes : 0;
+    const int n_sec = t.n_classes + 2;
+    struct Section {
+      std::vector<int32_t> row, slot;
+      std::vector<int64_t> e0;
+      std::vector<uint32_t> ne;
+      void add(int32_t r, int64_t e, uint32_t n, int32_t sl) {
+        row.push_back(r);
+        e0.push_back(e);
+        ne.push_back(n);
+        slot.push_back(sl);
       }
-      t_off += pc.tasks[c];  // the arrays were sized from the upper bounds
-      l_off += pc.longs[c];
-      const int64_t cap = pc.tasks[c];
-      if (cap == 0 && tl.n_items == 0) continue;
-      std::vector<int32_t> row((size_t)std::max<int64_t>(cap, 1)), ne((size_t)std::max<int64_t>(cap, 1)), slot((size_t)std::max<int64_t>(cap, 1));
-      std::vector<int64_t> e0((size_t)std::max<int64_t>(cap, 1));
+    };
+    std::vector<Section> sec((size_t)n_sec);
+    std::vector<std::vector<int64_t>> upto((size_t)n_sec, std::vector<int64_t>(1, 0));  // tasks of a section up to every chunk's end
+    t.slot_off.assign(1, 0);
+    t.lr_off.assign(1, 0);
+    t.item_off.assign(h.chunk_item_off.begin(), h.chunk_item_off.end());
+    t.cls_entries.assign((size_t)s.K * t.n_classes * s.K, 0);
+    std::vector<uint8_t> slot_class;
+    std::vector<int32_t> lrow, lslot0, ldense0, lndense, litem0;
+    std::vector<uint32_t> ln;
+    const int short_row = s.short_row();
+    std::vector<int32_t> row, ne, slot;
+    std::vector<int64_t> e0;
+    for (int c = 0; c < s.K; ++c) {
+      const int64_t cap = std::max<int64_t>(pc.tasks[c], 1);
+      row.resize((size_t)cap);
+      ne.resize((size_t)cap);
+      slot.resize((size_t)cap);
+      e0.resize((size_t)cap);
       int64_t ns = 0;
       std::vector<int64_t> coff(classes + 1, 0);
       std::vector<uint8_t> sclass((size_t)std::max<int64_t>(pc.slots[c], 1), 255);
@@ -1812,116 +1808,92 @@ extern "C" int gnnstage_create(const gnnstage_desc *d, gnnstage_t **out) try {
       } else {
         cls_lo = class_bounds_by_entries(ptr, idx, s.n, s.chunk_ptr[c], s.chunk_ptr[c + 1], classes, s.chunk_ptr);
       }
-      const int64_t got = gnnstage_plan_tasks(ptr, h.hot.active ? h.hot.rank.data() : idx, s.n, s.chunk_ptr[c], s.chunk_ptr[c + 1],
+      const int64_t got = pc.tasks[c] == 0 ? 0 : gnnstage_plan_tasks(ptr, h.hot.active ? h.hot.rank.data() : idx, s.n, s.chunk_ptr[c], s.chunk_ptr[c + 1],
                                               pc.split[c], classes, cls_lo.data(), h.min_row, h.force_ptr(), cap, row.data(),
                                               e0.data(), ne.data(), slot.data(), &ns, coff.data(), sclass.data());
-      if (got < 0 || got > cap || ns > pc.slots[c]) return GNNSTAGE_EINVAL;
-      tl.n_classes = classes > 1 ? classes : 0;
-      for (int q = 0; q <= tl.n_classes; ++q) tl.cls_off[q] = coff[q];
-      for (int q = tl.n_classes + 1; q <= kMaxClasses; ++q) tl.cls_off[q] = tl.cls_off[tl.n_classes];
-      int32_t off32[kMaxClasses + 1];
-      for (int q = 0; q <= kMaxClasses; ++q) off32[q] = (int32_t)tl.cls_off[q];
-      if (tl.cls_off[kMaxClasses] > 0x7fffffff) return GNNSTAGE_ENOTSUP;
-      tl.d_cls_off = st->at<int32_t>(lay.cls_off[dir]) + (size_t)c * (kMaxClasses + 1);
-      if (hipMemcpy(tl.d_cls_off, off32, sizeof off32, hipMemcpyHostToDevice) != hipSuccess) return GNNSTAGE_EHIP;
-      tl.cls_chunk_entries.assign((size_t)tl.n_classes * s.K, 0);
-      for (int q = 0; q < tl.n_classes; ++q)
-        for (int64_t t = coff[q]; t < coff[q + 1]; ++t)
-          for (int64_t e = e0[t]; e < e0[t] + ne[t]; ++e) tl.cls_chunk_entries[(size_t)q * s.K + (packed[e] >> vbits)] += 1;
-      if (ns > 0 && hipMemcpy(tl.slot_class, sclass.data(), (size_t)ns, hipMemcpyHostToDevice) != hipSuccess)
-        return GNNSTAGE_EHIP;
-      tl.n_tasks = got;
-      tl.n_slots = ns;
-      // whole rows come last in the list: move the short ones behind the others (both parts keep their row order)
-      const int short_row = s.short_row();
-      if (short_row > 0) {
-        int64_t first_whole = got;
-        while (first_whole > 0 && slot[(size_t)first_whole - 1] < 0) --first_whole;
-        std::vector<int64_t> ord;
-        ord.reserve((size_t)(got - first_whole));
-        for (int64_t t = first_whole; t < got; ++t)
-          if (ne[(size_t)t] > short_row) ord.push_back(t);
-        const int64_t n_other = (int64_t)ord.size();
-        for (int64_t t = first_whole; t < got; ++t)
-          if (ne[(size_t)t] <= short_row) ord.push_back(t);
-        tl.n_short = (int64_t)ord.size() - n_other;
-        if (tl.n_short > 0 && n_other > 0) {
-          std::vector<int32_t> r2(ord.size()), n2(ord.size());
-          std::vector<int64_t> e2(ord.size());
-          for (size_t i = 0; i < ord.size(); ++i) {
-            r2[i] = row[(size_t)ord[i]];
-            n2[i] = ne[(size_t)ord[i]];
-            e2[i] = e0[(size_t)ord[i]];
-          }
-          std::copy(r2.begin(), r2.end(), row.begin() + first_whole);
-          std::copy(n2.begin(), n2.end(), ne.begin() + first_whole);
-          std::copy(e2.begin(), e2.end(), e0.begin() + first_whole);
-        }
+      if (got < 0 || got > pc.tasks[c] || ns > pc.slots[c]) return GNNSTAGE_EINVAL;
+      const int64_t slot0 = t.slot_off.back(), l0 = t.lr_off.back();
+      const uint32_t chunk_bits = (uint32_t)c << kTaskChunkShift;
+      int64_t first_whole = got;  // whole rows come last in the list
+      while (first_whole > 0 && slot[(size_t)first_whole - 1] < 0) --first_whole;
+      for (int64_t i = 0; i < got; ++i) {
+        int q = 0;
+        while (q < t.n_classes && i >= coff[(size_t)q + 1]) ++q;  // t.n_classes: the tail
+        if (i >= first_whole && short_row > 0 && ne[(size_t)i] <= short_row) q = t.n_classes + 1;
+        if ((uint32_t)ne[(size_t)i] > kTaskCountMask) return GNNSTAGE_ENOTSUP;
+        sec[(size_t)q].add(row[(size_t)i], e0[(size_t)i], (uint32_t)ne[(size_t)i] | chunk_bits, slot[(size_t)i] < 0 ? -1 : (int32_t)(slot0 + slot[(size_t)i]));
+        if (q < t.n_classes)
+          for (int64_t e = e0[(size_t)i]; e < e0[(size_t)i] + ne[(size_t)i]; ++e) t.cls_entries[((size_t)c * t.n_classes + q) * s.K + (packed[e] >> vbits)] += 1;
       }
+      while (sec[(size_t)n_sec - 1].row.size() % 4 != 0) sec[(size_t)n_sec - 1].add(-1, 0, chunk_bits, -1);
+      for (int q = 0; q < n_sec; ++q) upto[(size_t)q].push_back((int64_t)sec[(size_t)q].row.size());
+      slot_class.insert(slot_class.end(), sclass.begin(), sclass.begin() + ns);
+      t.slot_off.push_back(slot0 + ns);
       // cut rows: their slots are consecutive, so sorting the pieces by slot groups them by row
       std::vector<std::pair<int32_t, int32_t>> sr;
-      for (int64_t t = 0; t < got; ++t)
-        if (slot[t] >= 0) sr.emplace_back(slot[t], row[t]);
+      for (int64_t i = 0; i < got; ++i)
+        if (slot[(size_t)i] >= 0) sr.emplace_back(slot[(size_t)i], row[(size_t)i]);
       std::sort(sr.begin(), sr.end());
-      std::vector<int32_t> lrow, lslot0, ln;
+      auto add_long = [&](int32_t r, int32_t first_slot) {
+        lrow.push_back(r);
+        lslot0.push_back(first_slot);
+        ln.push_back(chunk_bits);
+        ldense0.push_back(0);
+        lndense.push_back(0);
+        litem0.push_back(0);
+      };
       for (const auto &p : sr) {
-        if (lrow.empty() || lrow.back() != p.second) {
-          lrow.push_back(p.second);
-          lslot0.push_back(p.first);
-          ln.push_back(0);
-        }
+        if ((int64_t)lrow.size() == l0 || lrow.back() != p.second) add_long(p.second, (int32_t)(slot0 + p.first));
         ln.back() += 1;
       }
       // rows of dense row blocks: their dense partial rows join the pieces (a row without any piece is added)
-      std::vector<int32_t> ldense0(lrow.size(), 0), lndense(lrow.size(), 0), litem0(lrow.size(), 0);
-      if (tl.n_items > 0) {
-        std::vector<int32_t> where((size_t)(s.chunk_ptr[c + 1] - s.chunk_ptr[c]), -1);
-        for (size_t i = 0; i < lrow.size(); ++i) where[(size_t)(lrow[i] - s.chunk_ptr[c])] = (int32_t)i;
-        int64_t it = tl.item0;
-        const int64_t it_end = tl.item0 + tl.n_items;
+      const int64_t it_end = t.item_off[(size_t)c + 1];
+      if (it_end > t.item_off[(size_t)c]) {
+        std::vector<int64_t> where((size_t)(s.chunk_ptr[c + 1] - s.chunk_ptr[c]), -1);
+        for (size_t i = (size_t)l0; i < lrow.size(); ++i) where[(size_t)(lrow[i] - s.chunk_ptr[c])] = (int64_t)i;
+        int64_t it = t.item_off[(size_t)c];
         while (it < it_end) {
           int64_t it2 = it;
           while (it2 < it_end && h.item_rb[(size_t)it2] == h.item_rb[(size_t)it]) ++it2;
           const int64_t p0 = (int64_t)h.item_rb[(size_t)it] * kDenseRB;
           const int64_t p1 = std::min<int64_t>(p0 + kDenseRB, s.chunk_ptr[c + 1] - s.chunk_ptr[c]);
+          if ((it + 1) * kDenseRB > 0x7fffffff) return GNNSTAGE_ENOTSUP;
           for (int64_t pp = p0; pp < p1; ++pp) {
             const int32_t r = h.dp.row_perm[(size_t)(s.chunk_ptr[c] + pp)];
-            int32_t at = where[(size_t)(r - s.chunk_ptr[c])];
+            int64_t at = where[(size_t)(r - s.chunk_ptr[c])];
             if (at < 0) {
-              at = (int32_t)lrow.size();
-              lrow.push_back(r);
-              lslot0.push_back(0);
-              ln.push_back(0);
-              ldense0.push_back(0);
-              lndense.push_back(0);
-              litem0.push_back(0);
+              at = (int64_t)lrow.size();
+              add_long(r, (int32_t)slot0);
             }
-            ldense0[(size_t)at] = (int32_t)((it - tl.item0) * kDenseRB + (pp - p0));
+            ldense0[(size_t)at] = (int32_t)(it * kDenseRB + (pp - p0));
             lndense[(size_t)at] = (int32_t)(it2 - it);
-            litem0[(size_t)at] = (int32_t)(it - tl.item0);
+            litem0[(size_t)at] = (int32_t)it;
           }
           it = it2;
         }
       }
-      tl.n_long = (int64_t)lrow.size();
-      if (tl.n_long > pc.longs[c]) return GNNSTAGE_EINVAL;
-      if (h.dense() && tl.n_long > 0 &&
-          (hipMemcpy(tl.lr_dense0, ldense0.data(), sizeof(int32_t) * tl.n_long, hipMemcpyHostToDevice) != hipSuccess ||
-           hipMemcpy(tl.lr_ndense, lndense.data(), sizeof(int32_t) * tl.n_long, hipMemcpyHostToDevice) != hipSuccess ||
-           hipMemcpy(tl.lr_item0, litem0.data(), sizeof(int32_t) * tl.n_long, hipMemcpyHostToDevice) != hipSuccess))
-        return GNNSTAGE_EHIP;
-      if (got > 0 &&
-          (hipMemcpy(tl.task_row, row.data(), sizeof(int32_t) * got, hipMemcpyHostToDevice) != hipSuccess ||
-           hipMemcpy(tl.task_e0, e0.data(), sizeof(int64_t) * got, hipMemcpyHostToDevice) != hipSuccess ||
-           hipMemcpy(tl.task_ne, ne.data(), sizeof(int32_t) * got, hipMemcpyHostToDevice) != hipSuccess ||
-           hipMemcpy(tl.task_slot, slot.data(), sizeof(int32_t) * got, hipMemcpyHostToDevice) != hipSuccess))
-        return GNNSTAGE_EHIP;
-      if (tl.n_long > 0 &&
-          (hipMemcpy(tl.lr_row, lrow.data(), sizeof(int32_t) * tl.n_long, hipMemcpyHostToDevice) != hipSuccess ||
-           hipMemcpy(tl.lr_slot0, lslot0.data(), sizeof(int32_t) * tl.n_long, hipMemcpyHostToDevice) != hipSuccess ||
-           hipMemcpy(tl.lr_nslots, ln.data(), sizeof(int32_t) * tl.n_long, hipMemcpyHostToDevice) != hipSuccess))
-        return GNNSTAGE_EHIP;
+      t.lr_off.push_back((int64_t)lrow.size());
+      if (t.lr_off.back() - l0 > pc.longs[c] || t.slot_off.back() > 0x7fffffff) return GNNSTAGE_ENOTSUP;
     }
+    int64_t at = 0;
+    auto up = [&](size_t off, const void *src, size_t elt, size_t count, int64_t first) {
+      return count == 0 || hipMemcpy(st->at<char>(off) + (size_t)first * elt, src, count * elt, hipMemcpyHostToDevice) == hipSuccess;
+    };
+    for (int q = 0; q < n_sec; ++q) {
+      const Section &x = sec[(size_t)q];
+      for (const int64_t u : upto[(size_t)q]) t.sec.push_back(at + u);
+      if (!up(dir ? lay.b_task_row : lay.f_task_row, x.row.data(), 4, x.row.size(), at) || !up(dir ? lay.b_task_e0 : lay.f_task_e0, x.e0.data(), 8, x.e0.size(), at) ||
+          !up(dir ? lay.b_task_ne : lay.f_task_ne, x.ne.data(), 4, x.ne.size(), at) || !up(dir ? lay.b_task_slot : lay.f_task_slot, x.slot.data(), 4, x.slot.size(), at))
+        return GNNSTAGE_EHIP;
+      at += (int64_t)x.row.size();
+    }
+    if (at > s.task_capacity(pc.total_tasks) || at > 0x7fffffff) return GNNSTAGE_ENOTSUP;
+    if (!up(dir ? lay.b_slot_class : lay.f_slot_class, slot_class.data(), 1, slot_class.size(), 0) || !up(dir ? lay.b_lr_row : lay.f_lr_row, lrow.data(), 4, lrow.size(), 0) ||
+        !up(dir ? lay.b_lr_slot0 : lay.f_lr_slot0, lslot0.data(), 4, lslot0.size(), 0) || !up(dir ? lay.b_lr_n : lay.f_lr_n, ln.data(), 4, ln.size(), 0))
+      return GNNSTAGE_EHIP;
+    if (h.dense() && (!up(lay.d_lr_dense0[dir], ldense0.data(), 4, ldense0.size(), 0) || !up(lay.d_lr_ndense[dir], lndense.data(), 4, lndense.size(), 0) ||
+                      !up(lay.d_lr_item0[dir], litem0.data(), 4, litem0.size(), 0)))
+      return GNNSTAGE_EHIP;
     return GNNSTAGE_OK;
   };
 
@@ -1936,6 +1908,12 @@ extern "C" int gnnstage_create(const gnnstage_desc *d, gnnstage_t **out) try {
     if (!h.dense()) continue;
     const DensePlan &dp = h.dp;
     const size_t nb = (size_t)dp.n_blocks(), ne = dp.ent_pos.size(), ni = h.item_rb.size();  // ne: real entries, without padding
+    std::vector<int32_t> item_rs(ni), item_chunk(ni);
+    for (int c = 0; c < s.K; ++c)
+      for (int64_t i = h.chunk_item_off[(size_t)c]; i < h.chunk_item_off[(size_t)c + 1]; ++i) {
+        item_chunk[(size_t)i] = c;
+        item_rs[(size_t)i] = (int32_t)(h.rowscale_off[(size_t)c] + (int64_t)h.item_rb[(size_t)i] * kDenseRB);
+      }
     std::vector<uint32_t> colslot(dp.colslot_vertex.size());
     std::vector<int32_t> chunk_of((size_t)s.n);
     for (int c = 0; c < s.K; ++c)
@@ -1947,7 +1925,8 @@ extern "C" int gnnstage_create(const gnnstage_desc *d, gnnstage_t **out) try {
     if (hipMemcpy(st->at<int64_t>(lay.rem_ptr[dir]), dp.rem_ptr.data(), sizeof(int64_t) * (s.n + 1), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(st->at<int32_t>(lay.d_blk_cb[dir]), dp.blk_cb.data(), sizeof(int32_t) * nb, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(st->at<uint32_t>(lay.d_colslot[dir]), colslot.data(), sizeof(uint32_t) * colslot.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(st->at<int32_t>(lay.d_item_rb[dir]), h.item_rb.data(), sizeof(int32_t) * ni, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(st->at<int32_t>(lay.d_item_rs[dir]), item_rs.data(), sizeof(int32_t) * ni, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(st->at<int32_t>(lay.d_item_chunk[dir]), item_chunk.data(), sizeof(int32_t) * ni, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(st->at<int64_t>(lay.d_item_b0[dir]), h.item_b0.data(), sizeof(int64_t) * ni, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(st->at<int32_t>(lay.d_item_nb[dir]), h.item_nb.data(), sizeof(int32_t) * ni, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(st->at<ChunkMask>(lay.d_item_chunks[dir]), h.item_chunks.data(), sizeof(ChunkMask) * ni, hipMemcpyHostToDevice) != hipSuccess)
@@ -1977,7 +1956,6 @@ extern "C" int gnnstage_create(const gnnstage_desc *d, gnnstage_t **out) try {
           hipMemcpy(st->at<float>(lay.d_colscale[dir]), colscale.data(), sizeof(float) * colscale.size(), hipMemcpyHostToDevice) != hipSuccess ||
           hipMemcpy(st->at<float>(lay.d_rowscale[dir]), rowscale.data(), sizeof(float) * rowscale.size(), hipMemcpyHostToDevice) != hipSuccess)
         return bail(GNNSTAGE_EHIP, "uploading the dense patterns failed");
-      st->rowscale_off[dir] = h.rowscale_off;
     } else {
       const size_t ne_pad = (size_t)h.padded_entries();
       std::vector<uint32_t> ent_w(ne_pad, 0u);
@@ -2037,8 +2015,8 @@ extern "C" int gnnstage_create(const gnnstage_desc *d, gnnstage_t **out) try {
         launch_gcn_norm(bp, st->at<uint32_t>(lay.prow), vbits, rp, s.n, st->at<float>(lay.tval), nullptr) != 0)
       return bail(GNNSTAGE_EHIP, "normalisation kernel launch failed");
   }
-  rc = build(hp.f, pcol.data(), false, st->ftasks);
-  if (rc == GNNSTAGE_OK) rc = build(hp.b, prow.data(), true, st->btasks);
+  rc = build(hp.f, pcol.data(), 0);
+  if (rc == GNNSTAGE_OK) rc = build(hp.b, prow.data(), 1);
   if (rc != GNNSTAGE_OK) return bail(rc, "building the launch schedule failed");
   if (hipDeviceSynchronize() != hipSuccess) return bail(GNNSTAGE_EHIP, "device synchronisation failed after create");
   *out = holder.release();
@@ -2069,9 +2047,9 @@ extern "C" int stage_forward_chunk(gnnstage_t *st, int32_t k, int32_t pos, void 
   st->order.push_back(k);
   mask_set(st->fmask, k);  // C_k joins V_processed before its layers run
   if ((int)st->order.size() == s.K) st->cur_stale = false;  // after this call every current row is of this pass
-  for (int j = 0; j < s.L && cell_rows(st, k) > 0; ++j) {
-    const Cell c{k, j, 0, st->fmask};
-    const int rc = forward_cells(st, &c, 1, stream);
+  const Span sp = chunk_span(k, st->fmask);
+  for (int j = 0; j < s.L && span_rows(st, sp) > 0; ++j) {
+    const int rc = forward_layer(st, j, sp, stream);
     if (rc != GNNSTAGE_OK) return rc;
   }
   return GNNSTAGE_OK;
@@ -2091,7 +2069,8 @@ extern "C" int gnnstage_forward_pass(gnnstage_t *st, const int32_t *order, int32
   std::vector<int32_t> ks(order, order + n_order);
   int rc = begin_forward(st, stream);
   if (rc != GNNSTAGE_OK) return rc;
-  rc = run_diagonals(st, ks, [](int step) { return step; }, [&](const Cell *c, int n) { return forward_cells(st, c, n, stream); });
+  rc = write_pass_tables(st, ks, stream);
+  for (int j = 0; j < st->s.L && rc == GNNSTAGE_OK; ++j) rc = forward_layer(st, j, whole_span(st), stream);
   if (rc != GNNSTAGE_OK) return rc;
   // only now: a pass that failed half-way is none to run backward or to refresh the history from
   st->order.swap(ks);
@@ -2115,7 +2094,7 @@ extern "C" int stage_backward_chunk(gnnstage_t *st, int32_t k, const void *grad_
   if ((int)st->order.size() != s.K) return fail(st, GNNSTAGE_EORDER, "backward before the forward pass covered every chunk");
   if (st->n_bwd >= s.K) return fail(st, GNNSTAGE_EORDER, "backward pass already complete");
   if (st->order[s.K - 1 - st->n_bwd] != k) return fail(st, GNNSTAGE_EORDER, "backward must walk the chunks in reverse forward order");
-  const int64_t row0 = cell_row0(st, k), M = cell_rows(st, k);
+  const int64_t row0 = s.chunk_ptr[(size_t)k], M = s.chunk_ptr[(size_t)k + 1] - row0;
   if (M > 0 && !grad_out_rows) return fail(st, GNNSTAGE_EINVAL, "grad_out_rows is NULL");
   st->n_bwd += 1;
   mask_set(st->bmask, k);
@@ -2123,11 +2102,9 @@ extern "C" int stage_backward_chunk(gnnstage_t *st, int32_t k, const void *grad_
   if (M > 0) {
     if (s.defer_wgrad()) st->wgrad_pending[(size_t)k] = 1;
     st->gi = 0;
-    int rc = top_dY(st, grad_out_rows, row0, M, dY_rows(st, k, s.L - 1), stream);
-    for (int j = s.L - 1; j >= 0 && rc == GNNSTAGE_OK; --j) {
-      const Cell c{k, j, 0, st->bmask};
-      rc = backward_cells(st, &c, 1, false, stream);
-    }
+    int rc = top_dY(st, grad_out_rows, row0, M, dY_rows(st, row0, s.L - 1), stream);
+    LnSums sums;
+    for (int j = s.L - 1; j >= 0 && rc == GNNSTAGE_OK; --j) rc = backward_layer(st, sums, j, chunk_span(k, st->bmask), stream);
     if (rc != GNNSTAGE_OK) return rc;
   }
   return end_backward(st, stream);
@@ -2143,24 +2120,22 @@ extern "C" int gnnstage_backward_pass(gnnstage_t *st, const int32_t *order, int3
       const int32_t k = order[p];
       if (k < 0 || k >= s.K) return fail(st, GNNSTAGE_ERANGE, "chunk id out of range");
       const char *rows = static_cast<const char *>(grad_out);
-      const int rc = stage_backward_chunk(st, k, rows ? rows + (size_t)cell_row0(st, k) * s.dims[s.L] * s.elt() : nullptr, hip_stream);
+      const int rc = stage_backward_chunk(st, k, rows ? rows + (size_t)s.chunk_ptr[(size_t)k] * s.dims[s.L] * s.elt() : nullptr, hip_stream);
       if (rc != GNNSTAGE_OK) return rc;
     }
     return GNNSTAGE_OK;
   }
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  const std::vector<int32_t> back(st->order.rbegin(), st->order.rend());
+  int rc = write_pass_tables(st, st->order, stream);
+  if (rc != GNNSTAGE_OK) return rc;
   st->n_bwd = s.K;  // there is no second try, whatever fails below: part of the sums may be added by then
   for (int32_t k = 0; k < s.K; ++k) mask_set(st->bmask, k);
-  int rc = top_dY(st, grad_out, 0, s.n, full_dY(st, s.L - 1), stream);
+  LnSums sums;
+  rc = top_dY(st, grad_out, 0, s.n, full_dY(st, s.L - 1), stream);
+  for (int j = s.L - 1; j >= 0 && rc == GNNSTAGE_OK; --j) rc = backward_layer(st, sums, j, whole_span(st), stream);
+  if (rc == GNNSTAGE_OK) rc = sums.add_up(st, stream);
   if (rc != GNNSTAGE_OK) return rc;
-  rc = run_diagonals(st, back, [&](int step) { return s.L - 1 - step; }, [&](const Cell *c, int n) { return backward_cells(st, c, n, true, stream); });
-  if (rc != GNNSTAGE_OK) return rc;
-  for (int32_t k = 0; k < s.K; ++k) st->wgrad_pending[(size_t)k] = cell_rows(st, k) > 0 ? 1 : 0;
-  for (int j = 0; j < s.L; ++j)
-    if (s.tf[j] && s.has_bias())
-      HIP_TRY(st, launch_colsum_add(full_dY(st, j), st->cdtype(), s.ld[j + 1], (int)s.n, s.dims[j + 1], st->at<float>(st->lay.bias_partial), kMaxSplits,
-                                    st->dbias[j], stream));
+  for (int32_t k = 0; k < s.K; ++k) st->wgrad_pending[(size_t)k] = s.chunk_ptr[(size_t)k + 1] > s.chunk_ptr[(size_t)k] ? 1 : 0;
   return end_backward(st, stream);
 }
 GNNSTAGE_GUARD_INT

@@ -30,10 +30,8 @@ __device__ inline float wave_sum(float v) {
 
 // NI = columns per lane (lane, lane + 64, ...): the row lives in registers between the passes
 template <int NI>
-__global__ __launch_bounds__(256) void ln_relu_kernel(const Batch<LnArgs> ba) {
-  const LnArgs a = ba.sub[blockIdx.z];
-  const unsigned block = blockIdx.x, blocks = a.blocks;
-  if (block >= blocks) return;
+__global__ __launch_bounds__(256) void ln_relu_kernel(const LnArgs a) {
+  const unsigned block = blockIdx.x, blocks = gridDim.x;
   const void *x = a.x;
   void *out = a.out;
   const float *gamma = a.gamma, *beta = a.beta;
@@ -190,10 +188,8 @@ __device__ inline float group_sum(float v) {
 }
 
 template <int LPR>
-__global__ __launch_bounds__(256) void ln_relu_vec_kernel(const Batch<LnArgs> ba) {
-  const LnArgs a = ba.sub[blockIdx.z];
-  const unsigned block = blockIdx.x, blocks = a.blocks;
-  if (block >= blocks) return;
+__global__ __launch_bounds__(256) void ln_relu_vec_kernel(const LnArgs a) {
+  const unsigned block = blockIdx.x, blocks = gridDim.x;
   const bf16_t *x = static_cast<const bf16_t *>(a.x);
   bf16_t *out = static_cast<bf16_t *>(a.out);
   const float *gamma = a.gamma, *beta = a.beta;
@@ -346,11 +342,6 @@ inline int vec_lanes(int d, int dtype, const void *p, int ld) {
 
 // One workgroup per 64 entries of the 2 x d sums: 16 wavefronts each add every 16th partial row, then the 16
 // slice sums are added in order.  n_parts: the partial rows of a sub-launch are its workgroups in the launch before.
-struct LnReduceArgs {
-  const float *partial;
-  int32_t n_parts, d;
-  float *dgamma, *dbeta;
-};
 __global__ __launch_bounds__(1024) void ln_param_reduce_kernel(const Batch<LnReduceArgs> ba) {
   const LnReduceArgs &a = ba.sub[blockIdx.z];
   const unsigned block = blockIdx.x;
@@ -393,7 +384,6 @@ int waves_for(int64_t M, int max_waves) {
 
 }  // namespace
 
-static void set_blocks(LnArgs &a, unsigned g) { a.blocks = (int32_t)g; }
 static void set_blocks(LnBackArgs &a, unsigned g) { a.f.blocks = (int32_t)g; }
 static void set_blocks(LnReduceArgs &, unsigned) {}
 // Runs sub-launches [0, n) (kernel fn[i], gx[i] workgroups; 0: nothing to do), those of one kernel together.
@@ -427,50 +417,38 @@ static bool adds_to_the_same(const LnReduceArgs &a, const LnReduceArgs &b) {
   return false;
 }
 
-int launch_ln_relu(const LnArgs *l, int n, hipStream_t s) {
-  if (n > kBatch) return hipErrorInvalidValue;
-  typedef void (*fn_t)(const Batch<LnArgs>);
-  const LnArgs *ptr[kBatch];
-  fn_t fn[kBatch];
-  unsigned gx[kBatch];
-  for (int i = 0; i < n; ++i) {
-    const LnArgs &a = l[i];
-    ptr[i] = &a;
-    fn[i] = nullptr;
-    gx[i] = 0;
-    if (a.M <= 0) continue;
-    if (a.d > kLnMaxWidth || a.out_ld > kLnMaxWidth) return hipErrorInvalidValue;
-    const int lpr = (a.out_dtype == DT_BF16 && a.out_ld == a.d && vec_lanes(a.d, a.out_dtype, a.out, a.out_ld)) ? vec_lanes(a.d, a.x_dtype, a.x, a.x_ld) : 0;
-    if (lpr) {
-      const int rpw = 64 / lpr;
-      gx[i] = (unsigned)(waves_for((a.M + rpw - 1) / rpw, 16384) / 4);
-      fn[i] = lpr == 8 ? ln_relu_vec_kernel<8> : lpr == 16 ? ln_relu_vec_kernel<16> : lpr == 32 ? ln_relu_vec_kernel<32> : ln_relu_vec_kernel<64>;
-    } else {
-      const int ni = (std::max(a.d, a.out_ld) + 63) / 64;
-      gx[i] = (unsigned)(waves_for(a.M, 16384) / 4);
-      fn[i] = ni <= 1 ? ln_relu_kernel<1> : ni <= 2 ? ln_relu_kernel<2> : ni <= 4 ? ln_relu_kernel<4> : ni <= 8 ? ln_relu_kernel<8> : ln_relu_kernel<16>;
-    }
+int launch_ln_relu(const LnArgs &a, hipStream_t s) {
+  if (a.M <= 0) return hipSuccess;
+  if (a.d > kLnMaxWidth || a.out_ld > kLnMaxWidth) return hipErrorInvalidValue;
+  void (*fn)(const LnArgs);
+  unsigned gx;
+  const int lpr = (a.out_dtype == DT_BF16 && a.out_ld == a.d && vec_lanes(a.d, a.out_dtype, a.out, a.out_ld)) ? vec_lanes(a.d, a.x_dtype, a.x, a.x_ld) : 0;
+  if (lpr) {
+    const int rpw = 64 / lpr;
+    gx = (unsigned)(waves_for((a.M + rpw - 1) / rpw, 16384) / 4);
+    fn = lpr == 8 ? ln_relu_vec_kernel<8> : lpr == 16 ? ln_relu_vec_kernel<16> : lpr == 32 ? ln_relu_vec_kernel<32> : ln_relu_vec_kernel<64>;
+  } else {
+    const int ni = (std::max(a.d, a.out_ld) + 63) / 64;
+    gx = (unsigned)(waves_for(a.M, 16384) / 4);
+    fn = ni <= 1 ? ln_relu_kernel<1> : ni <= 2 ? ln_relu_kernel<2> : ni <= 4 ? ln_relu_kernel<4> : ni <= 8 ? ln_relu_kernel<8> : ln_relu_kernel<16>;
   }
-  return launch_merged(ptr, fn, gx, n, 256, s);
+  hipLaunchKernelGGL(fn, dim3(gx), dim3(256), 0, s, a);
+  return (int)hipGetLastError();
 }
 
-int launch_ln_relu_backward(const LnBackArgs *l, int n, hipStream_t s) {
+int launch_ln_relu_backward(const LnBackArgs *l, int n, int max_waves, LnReduceArgs *red, hipStream_t s) {
   if (n > kBatch) return hipErrorInvalidValue;
   typedef void (*fn_t)(const Batch<LnBackArgs>);
   const LnBackArgs *ptr[kBatch];
   fn_t fn[kBatch];
-  unsigned gx[kBatch], gr[kBatch];
-  LnReduceArgs red[kBatch] = {};
-  const LnReduceArgs *rptr[kBatch];
-  void (*rfn[kBatch])(const Batch<LnReduceArgs>);
+  unsigned gx[kBatch];
   for (int i = 0; i < n; ++i) {
     const LnBackArgs &b = l[i];
     const LnArgs &a = b.f;
     ptr[i] = &b;
     fn[i] = nullptr;
-    gx[i] = gr[i] = 0;
-    rptr[i] = &red[i];
-    rfn[i] = ln_param_reduce_kernel;
+    gx[i] = 0;
+    red[i] = LnReduceArgs{};
     if (a.M <= 0) continue;
     if (a.d > kLnMaxWidth || (a.out && a.out_ld > kLnMaxWidth)) return hipErrorInvalidValue;
     int lpr = vec_lanes(a.d, a.x_dtype, a.x, a.x_ld);
@@ -479,30 +457,40 @@ int launch_ln_relu_backward(const LnBackArgs *l, int n, hipStream_t s) {
       lpr = 0;
     if (lpr) {
       const int rpw = 64 / lpr;
-      gx[i] = (unsigned)(waves_for((a.M + rpw - 1) / rpw, kLnMaxWaves) / 4);
+      gx[i] = (unsigned)(waves_for((a.M + rpw - 1) / rpw, max_waves) / 4);
       fn[i] = lpr == 8 ? ln_relu_backward_vec_kernel<8> : lpr == 16 ? ln_relu_backward_vec_kernel<16>
             : lpr == 32 ? ln_relu_backward_vec_kernel<32> : ln_relu_backward_vec_kernel<64>;
     } else {
       const int ni = (std::max(a.d, a.out ? a.out_ld : a.d) + 63) / 64;
-      gx[i] = (unsigned)(waves_for(a.M, kLnMaxWaves) / 4);
+      gx[i] = (unsigned)(waves_for(a.M, max_waves) / 4);
       fn[i] = ni <= 1 ? ln_relu_backward_kernel<1> : ni <= 2 ? ln_relu_backward_kernel<2> : ni <= 4 ? ln_relu_backward_kernel<4>
             : ni <= 8 ? ln_relu_backward_kernel<8> : ln_relu_backward_kernel<16>;
     }
     red[i] = LnReduceArgs{b.partial, (int32_t)gx[i], a.d, b.dgamma, b.dbeta};
-    gr[i] = (unsigned)((2 * a.d + 63) / 64);
   }
-  int e = launch_merged(ptr, fn, gx, n, 256, s);
-  // The sums are added to the parameter gradients without atomics.  Layers may share those buffers (tied parameters), so a
-  // launch takes the cells up to the first one that would add to a buffer again; that one starts the next launch.
-  for (int i0 = 0, i1; i0 < n && e == 0; i0 = i1) {
-    for (i1 = i0 + 1; i1 < n; ++i1) {
+  return launch_merged(ptr, fn, gx, n, 256, s);
+}
+
+// The sums are added to the parameter gradients without atomics.  Layers may share those buffers (tied parameters), and the
+// groups of a layer's rows do, so a launch takes the sums up to the first that would add to a buffer again; that one starts
+// the next launch.
+int launch_ln_param_reduce(const LnReduceArgs *red, int n, hipStream_t s) {
+  for (int i0 = 0, i1; i0 < n; i0 = i1) {
+    const LnReduceArgs *ptr[kBatch];
+    void (*fn[kBatch])(const Batch<LnReduceArgs>);
+    unsigned gx[kBatch];
+    for (i1 = i0; i1 < n && i1 - i0 < kBatch; ++i1) {
       bool again = false;
       for (int i = i0; i < i1; ++i) again = again || adds_to_the_same(red[i], red[i1]);
       if (again) break;
+      ptr[i1 - i0] = &red[i1];
+      fn[i1 - i0] = ln_param_reduce_kernel;
+      gx[i1 - i0] = red[i1].n_parts > 0 ? (unsigned)((2 * red[i1].d + 63) / 64) : 0;
     }
-    e = launch_merged(rptr + i0, rfn + i0, gr + i0, i1 - i0, 1024, s);
+    const int e = launch_merged(ptr, fn, gx, i1 - i0, 1024, s);
+    if (e != 0) return e;
   }
-  return e;
+  return hipSuccess;
 }
 
 int launch_copy_rows(const void *src, int src_ld, void *dst, int dst_ld, int64_t M, int d, int dtype, hipStream_t s) {

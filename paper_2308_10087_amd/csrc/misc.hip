@@ -133,7 +133,40 @@ __global__ __launch_bounds__(256) void gcn_norm_kernel(const int64_t *ptr, const
   }
 }
 
+// One workgroup; thread c writes the entries of row chunk c.
+__global__ __launch_bounds__(kMaxChunks) void pass_tables_kernel(const PassTableArgs a) {
+  __shared__ int pos[kMaxChunks];
+  const int c = threadIdx.x;
+  const int p = c < a.K ? a.pos[c] : 0;
+  pos[c] = p;
+  __syncthreads();
+  if (c >= a.K) return;
+  PassChunk f{}, b{}, e{};
+  for (int k = 0; k < a.K; ++k) {
+    const uint64_t bit = 1ull << (k & 63);
+    const int pk = pos[k];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (k >> 6 != i) continue;
+      f.mask.w[i] |= pk <= p ? bit : 0;
+      b.mask.w[i] |= pk >= p ? bit : 0;
+      e.mask.w[i] |= pk < p ? bit : 0;
+    }
+  }
+  f.classes = 0xffffffffu;
+  b.classes = a.classes_backward[c];
+  e.classes = a.classes_earlier[c];
+  a.forward[c] = f;
+  a.backward[c] = b;
+  a.earlier[c] = e;
+}
+
 }  // namespace
+
+int launch_pass_tables(const PassTableArgs &a, hipStream_t s) {
+  hipLaunchKernelGGL(pass_tables_kernel, dim3(1), dim3(kMaxChunks), 0, s, a);
+  return (int)hipGetLastError();
+}
 
 int launch_stage_weights(const void *W, int w_dtype, int K, int N, void *Wt, int Kp, void *Wn, int Np, hipStream_t s) {
   const int total = (N * Kp > K * Np) ? N * Kp : K * Np;

@@ -121,13 +121,13 @@ __device__ inline void zero_pad_cols(const SpmmArgs &a, int64_t row, int lane) {
 // A row's last vector moves back so that it ends with the row: it repeats columns of its neighbour lane, which both
 // lanes sum and store alike, and every width is read in 16-byte accesses.
 template <typename Tin, typename Tout, int VEC, int LPR, int U>
-__global__ __launch_bounds__(256) void spmm_kernel(const Batch<SpmmArgs> ba) {
-  const SpmmArgs &a = ba.sub[blockIdx.z];
+__global__ __launch_bounds__(256) void spmm_kernel(const SpmmArgs a) {
   typedef Tin vec_t __attribute__((ext_vector_type(VEC), aligned(4)));
   constexpr int G = 64 / LPR;
   constexpr int TILE_W = LPR * VEC;
   const int lane = threadIdx.x & 63;
-  const int64_t task = spmm_task_index(a, blockIdx.x, threadIdx.x >> 6);
+  int cls;
+  const int64_t task = spmm_task_index(a, blockIdx.x, threadIdx.x >> 6, cls);
   if (task < 0) return;  // whole wave leaves together
   const int grp = lane / LPR, lig = lane % LPR;
   const int d = a.d;
@@ -136,12 +136,21 @@ __global__ __launch_bounds__(256) void spmm_kernel(const Batch<SpmmArgs> ba) {
   const int c = col + VEC <= d ? col : d - VEC;
   // task fields are the same for the whole wave: keep them in scalar registers, so that every loop
   // bound below is provably wave-uniform (the lane permutes need all lanes in step)
-  const int64_t row = __builtin_amdgcn_readfirstlane(a.task_row[task]);
+  const int32_t row_raw = a.task_row[task], slot_raw = a.task_slot[task];
   const int64_t e0_raw = a.task_e0[task];
+  const uint32_t ne_raw = a.task_ne[task];
+  __builtin_amdgcn_sched_barrier(0);  // one round trip, also for the wave whose task turns out to be a filler
+  const int64_t row = __builtin_amdgcn_readfirstlane(row_raw);
+  if (row < 0) return;  // filler
   const int64_t e0 = ((int64_t)__builtin_amdgcn_readfirstlane((int)(e0_raw >> 32)) << 32) |
                      (uint32_t)__builtin_amdgcn_readfirstlane((int)(e0_raw & 0xffffffff));
-  const int ne = __builtin_amdgcn_readfirstlane(a.task_ne[task]);
-  const int slot = __builtin_amdgcn_readfirstlane(a.task_slot[task]);
+  const uint32_t ne_chunk = (uint32_t)__builtin_amdgcn_readfirstlane((int)ne_raw);
+  const int ne = (int)(ne_chunk & kTaskCountMask);
+  const int slot = __builtin_amdgcn_readfirstlane(slot_raw);
+  uint32_t chunk_classes;
+  const bool many = a.many_chunks != 0;
+  const WaveMask mask = wave_mask(spmm_row_mask(a.pass, a.mask, ne_chunk >> kTaskChunkShift, chunk_classes), many);
+  if (cls >= 0 && !((chunk_classes >> cls) & 1u)) return;  // nothing of this class is gathered for the row's chunk
   const uint32_t vmask = (1u << a.vbits) - 1u;
   const bool drop_unsel = a.src_unsel == nullptr;
   const char *base_sel = static_cast<const char *>(a.src_sel);
@@ -165,7 +174,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(const Batch<SpmmArgs> ba) {
   for (int base = 0; base < ne; base += 64) {
     int n = ne - base < 64 ? ne - base : 64;
     // one lane works out the row address of one entry; the lanes that gather it only add their column
-    const bool sel = mask_test(a.mask, pc_next >> a.vbits);
+    const bool sel = mask_test(mask, pc_next >> a.vbits, many);
     const uint64_t at = reinterpret_cast<uint64_t>(sel ? base_sel : base_unsel) + (uint64_t)(pc_next & vmask) * row_bytes;
     int at_lo = (int)(uint32_t)at, at_hi = (int)(at >> 32), w = __float_as_int(w_next);
     const bool keep = lane < n && (sel || !drop_unsel);
@@ -230,7 +239,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(const Batch<SpmmArgs> ba) {
         Pack<float, VEC> o;
 #pragma unroll
         for (int t = 0; t < VEC; ++t) o.v[t] = acc[t];
-        *reinterpret_cast<Pack<float, VEC> *>(a.partial + (size_t)slot * d + c) = o;
+        *reinterpret_cast<Pack<float, VEC> *>(a.partial + (size_t)(slot - a.slot0) * d + c) = o;
       } else {
         finish_cols<Tin, Tout, VEC>(a, row, c, acc);
       }
@@ -247,19 +256,25 @@ __global__ __launch_bounds__(256) void spmm_kernel(const Batch<SpmmArgs> ba) {
 // that did not run in this launch holds stale sums) are loaded anyway, together with the word that says so,
 // and left out by a select; the epilogue's auxiliary row is asked for before the sums.
 template <typename Tin, typename Tout, int VEC>
-__global__ __launch_bounds__(256) void spmm_reduce_kernel(const Batch<SpmmArgs> ba) {
+__global__ __launch_bounds__(256) void spmm_reduce_kernel(const SpmmArgs a) {
   __shared__ float red[8][32][VEC];
-  const SpmmArgs a = ba.sub[blockIdx.z];  // a copy: its few fields come in one go, 18.1 -> 16.7 us for 10 k rows
   const int64_t i = blockIdx.x;
-  if (i >= a.n_long) return;
   const int ph = threadIdx.x >> 5, cv = threadIdx.x & 31;
   const bool dense = a.lr_ndense != nullptr;
   const int64_t row = a.lr_row[i];
-  const int slot0 = a.lr_slot0[i], ns = a.lr_nslots[i];
+  const int slot0 = a.lr_slot0[i];
+  const uint32_t ns_chunk = a.lr_nslots[i], chunk = ns_chunk >> kTaskChunkShift;
+  const int ns = (int)(ns_chunk & kTaskCountMask);
   const int nd = dense ? a.lr_ndense[i] : 0;
   const int dense0 = dense ? a.lr_dense0[i] : 0, item0 = dense ? a.lr_item0[i] : 0;
   // pieces of classes that were not run in this launch (all their entries unselected) hold stale data
-  const bool check = a.slot_class != nullptr && a.all_classes_active == 0;
+  const bool check = a.slot_class != nullptr && (a.all_classes_active == 0 || a.pass != nullptr) && a.drop_unselected;
+  ChunkMask mask = a.mask;
+  uint32_t classes = a.active_classes;
+  if (a.pass != nullptr && a.drop_unselected) {
+    mask = a.pass[chunk].mask;
+    classes &= a.pass[chunk].classes;
+  }
   {
     const int col = (int)blockIdx.y * 32 * VEC + cv * VEC;
     const bool on = col < a.d;
@@ -272,8 +287,9 @@ __global__ __launch_bounds__(256) void spmm_reduce_kernel(const Batch<SpmmArgs> 
       if (ph == 0) xa = load_aux<Tin, VEC>(a, row, c);
       for (int s = ph; s < ns; s += 8) {
         const uint32_t sc = check ? a.slot_class[slot0 + s] : 32u;
-        const Pack<float, VEC> x = *reinterpret_cast<const Pack<float, VEC> *>(a.partial + (size_t)(slot0 + s) * a.d + c);
-        const bool use = sc >= 32u || ((a.active_classes >> sc) & 1u);
+        const Pack<float, VEC> x = *reinterpret_cast<const Pack<float, VEC> *>(a.partial + (size_t)(slot0 + s - a.slot0) * a.d + c);
+        __builtin_amdgcn_sched_barrier(0);
+        const bool use = sc >= 32u || ((classes >> sc) & 1u);
 #pragma unroll
         for (int t = 0; t < VEC; ++t) acc[t] += use ? x.v[t] : 0.f;
       }
@@ -282,10 +298,10 @@ __global__ __launch_bounds__(256) void spmm_reduce_kernel(const Batch<SpmmArgs> 
         bool use = true;
         if (a.drop_unselected) {  // an item without a selected chunk was not run
           const ChunkMask m = a.item_chunks[item0 + g];
-          use = ((m.w[0] & a.mask.w[0]) | (m.w[1] & a.mask.w[1]) | (m.w[2] & a.mask.w[2]) | (m.w[3] & a.mask.w[3])) != 0;
+          use = ((m.w[0] & mask.w[0]) | (m.w[1] & mask.w[1]) | (m.w[2] & mask.w[2]) | (m.w[3] & mask.w[3])) != 0;
         }
         const Pack<float, VEC> x =
-            *reinterpret_cast<const Pack<float, VEC> *>(a.dense_partial + ((size_t)dense0 + (size_t)g * kDenseRB) * a.d + c);
+            *reinterpret_cast<const Pack<float, VEC> *>(a.dense_partial + ((size_t)dense0 + (size_t)(g - a.item0) * kDenseRB) * a.d + c);
 #pragma unroll
         for (int t = 0; t < VEC; ++t) acc[t] += use ? x.v[t] : 0.f;
       }
@@ -325,28 +341,31 @@ typedef __attribute__((address_space(1))) bf16x8_t global_bf16x8_t;  // a load t
 // would need several rounds of waves.  Here every 16-lane group owns one row: a lane keeps 8 columns of each
 // 128-column tile in fp32 registers and the sum runs on the vector ALU; two to four of the row's entries are in
 // flight per lane.  Entries that a backward launch drops are not loaded at all.  `first` = index of the first row
-// of this workgroup among the launch's short rows.
-template <typename Tout, int NT, bool FULL>
+// of this workgroup among the launch's short rows.  The four rows of a wave are of one chunk (fillers see to it).
+template <typename Tout, int NT, bool FULL, bool MANY>
 __device__ __forceinline__ void spmm_short_rows(const SpmmArgs &a, int64_t first) {
   const int lane = threadIdx.x & 63, lig = lane & 15;
   const int64_t t = first + (threadIdx.x >> 4);
-  if (t >= a.n_short) return;
-  const int64_t task = a.n_tasks + t;  // the short rows follow the tasks of the main part
+  if (first + (threadIdx.x >> 6) * 4 >= a.n_short) return;  // whole waves: n_short is a multiple of four
+  const int64_t task = a.short0 + t;
+  const uint32_t ne_chunk = a.task_ne[task];
+  const int64_t row = a.task_row[task], e0 = a.task_e0[task];
+  uint32_t classes;
+  const ChunkMask mask = spmm_row_mask(a.pass, a.mask, (uint32_t)__builtin_amdgcn_readfirstlane((int)ne_chunk) >> kTaskChunkShift, classes);
   const uint32_t vmask = (1u << a.vbits) - 1u;
   const bool drop_unsel = a.src_unsel == nullptr;
   const char *base_sel = static_cast<const char *>(a.src_sel);
   const char *base_unsel = drop_unsel ? base_sel : static_cast<const char *>(a.src_unsel);
   const size_t row_bytes = (size_t)a.src_ld * 2u;
   const int d = a.d;
-  const int64_t row = a.task_row[task];
-  const int64_t e0 = a.task_e0[task];
-  const int ne = a.task_ne[task];
+  if (row < 0) return;
+  const int ne = (int)(ne_chunk & kTaskCountMask);
   float acc[NT][8];
 #pragma unroll
   for (int h = 0; h < NT; ++h)
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[h][c] = 0.f;
-  constexpr int SU = NT == 1 ? 4 : 2;  // entries in flight per lane (16 bytes x NT each)
+  constexpr int SU = MANY ? 1 : NT == 1 ? 4 : 2;  // entries in flight per lane (16 bytes x NT each); MANY: more than 64 chunks
   for (int i = 0; i < ne; i += SU) {
     bf16x8_t x[SU][NT];
     float w[SU];
@@ -357,7 +376,7 @@ __device__ __forceinline__ void spmm_short_rows(const SpmmArgs &a, int64_t first
       for (int h = 0; h < NT; ++h) x[u][h] = bf16x8_t{0, 0, 0, 0, 0, 0, 0, 0};
       if (i + u < ne) {
         const uint32_t pc = a.pidx[e0 + i + u];
-        const bool sel = mask_test(a.mask, pc >> a.vbits);
+        const bool sel = MANY ? mask_test(mask, pc >> a.vbits) : ((mask.w[0] >> (pc >> a.vbits)) & 1ull) != 0;
         if (sel || !drop_unsel) {
           w[u] = a.val[e0 + i + u];
           const char *p = (sel ? base_sel : base_unsel) + (size_t)(pc & vmask) * row_bytes + (size_t)lig * 16u;
@@ -393,11 +412,10 @@ __device__ __forceinline__ void spmm_short_rows(const SpmmArgs &a, int64_t first
 // and U - 1 steps of gathers stay in flight while one is consumed.  Per step the vector ALU only adds
 // the lane offset to the record's address and expands the weight (one byte permute, four selects).
 // Waves per SIMD: seven where their registers hold the loop.  Four column blocks need 86; held to 72 they went through scratch
-// memory inside the loop, more so with the operand sets side by side: two forward aggregations of 250 k rows of width 512 took
-// 890 us, 1,015 with the operand sets, and take 597 us with five waves (width 384 1,090 -> 584; six waves still spill: 742, 753).
+// memory inside the loop: two forward aggregations of 250 k rows of width 512 took 890 us and take 597 us with five waves
+// (width 384 1,090 -> 584; six waves still spill: 742, 753).
 template <typename Tout, int NT, int U, bool FULL>
-__global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ring_kernel(const Batch<SpmmArgs> ba) {
-  const SpmmArgs &a = ba.sub[blockIdx.z];  // (a copy holds more registers than the gather loop has to spare: 47.7 -> 48.8 us)
+__global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ring_kernel(const SpmmArgs a) {
   constexpr int TILE_W = NT * 128;
   constexpr int KB = 2;    // metadata batches per phase
   constexpr int R = 256;   // ring capacity in records: a phase appends at most 64 * KB, fewer than 8 * U are left over
@@ -405,23 +423,39 @@ __global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ri
   static_assert((U & (U - 1)) == 0 && U <= 8, "slot count");
   __shared__ u32x4_t ring_all[4][R];
   if ((int64_t)blockIdx.x >= a.n_main_blocks) {  // the workgroups behind the main part serve the short rows, 16 each
-    if constexpr (NT <= 2) spmm_short_rows<Tout, NT, FULL>(a, ((int64_t)blockIdx.x - a.n_main_blocks) * 16);
+    if constexpr (NT <= 2) {
+      const int64_t first = ((int64_t)blockIdx.x - a.n_main_blocks) * 16;
+      if (a.many_chunks != 0)
+        spmm_short_rows<Tout, NT, FULL, true>(a, first);
+      else
+        spmm_short_rows<Tout, NT, FULL, false>(a, first);
+    }
     return;
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t task = spmm_task_index(a, blockIdx.x, wave);
+  int cls;
+  const int64_t task = spmm_task_index(a, blockIdx.x, wave, cls);
   if (task < 0) return;  // whole wave leaves together (no block-wide barrier below)
   u32x4_t *ring = ring_all[wave];
   const int g = lane >> 4, lig = lane & 15;
   const int tile0 = blockIdx.y * TILE_W;
   // Task fields are the same for the whole wave: keep them in scalar registers.  The matrix instruction
   // ignores the execution mask, so all control flow around it must be provably wave-uniform.
-  const int64_t row = __builtin_amdgcn_readfirstlane(a.task_row[task]);
+  const int32_t row_raw = a.task_row[task], slot_raw = a.task_slot[task];
   const int64_t e0_raw = a.task_e0[task];
+  const uint32_t ne_raw = a.task_ne[task];
+  __builtin_amdgcn_sched_barrier(0);  // one round trip, also for the wave whose task turns out to be a filler
+  const int64_t row = __builtin_amdgcn_readfirstlane(row_raw);
+  if (row < 0) return;  // filler
   const int64_t e0 = ((int64_t)__builtin_amdgcn_readfirstlane((int)(e0_raw >> 32)) << 32) |
                      (uint32_t)__builtin_amdgcn_readfirstlane((int)(e0_raw & 0xffffffff));
-  const int ne = __builtin_amdgcn_readfirstlane(a.task_ne[task]);
-  const int slot = __builtin_amdgcn_readfirstlane(a.task_slot[task]);
+  const uint32_t ne_chunk = (uint32_t)__builtin_amdgcn_readfirstlane((int)ne_raw);
+  const int ne = (int)(ne_chunk & kTaskCountMask);
+  const int slot = __builtin_amdgcn_readfirstlane(slot_raw);
+  uint32_t chunk_classes;
+  const bool many = a.many_chunks != 0;
+  const WaveMask mask = wave_mask(spmm_row_mask(a.pass, a.mask, ne_chunk >> kTaskChunkShift, chunk_classes), many);
+  if (cls >= 0 && !((chunk_classes >> cls) & 1u)) return;  // nothing of this class is gathered for the row's chunk
   const uint32_t vmask = (1u << a.vbits) - 1u;
   const bool drop_unsel = a.src_unsel == nullptr;
   const char *base_sel = static_cast<const char *>(a.src_sel) + (size_t)tile0 * 2;
@@ -436,7 +470,6 @@ __global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ri
   const uint32_t b0 = lo_part ? 2u : 0u;
   const uint32_t selw = (pos & 1) ? (((b0 + 1u) << 24) | (b0 << 16) | 0x0c0cu) : (0x0c0c0000u | ((b0 + 1u) << 8) | b0);
   const int wword = pos >> 1;
-  const uint64_t mask0 = a.mask.w[0], mask1 = a.mask.w[1], mask2 = a.mask.w[2], mask3 = a.mask.w[3];
 
   f32x4_t acc[NT];
 #pragma unroll
@@ -502,10 +535,7 @@ __global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ri
       const int nraw = ne - ((bprod + k) << 6);  // entries left from this batch on (may be <= 0)
       const uint32_t pc = pcs[k];
       const float w = ws[k];
-      // the chunk's bit of the processed mask, picked with register selects (no indexed access)
-      const uint32_t ci = pc >> a.vbits;
-      const uint64_t mlo = (ci & 64u) ? mask1 : mask0, mhi = (ci & 64u) ? mask3 : mask2;
-      const bool sel = ((((ci & 128u) ? mhi : mlo) >> (ci & 63u)) & 1ull) != 0;
+      const bool sel = mask_test(mask, pc >> a.vbits, many);
       const bool keep = lane < nraw && (sel || !drop_unsel);
       const uint64_t addr = reinterpret_cast<uint64_t>(sel ? base_sel : base_unsel) + (uint64_t)(pc & vmask) * row_bytes;
       const bf16_t whi = (bf16_t)w;
@@ -592,7 +622,7 @@ __global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ri
         Pack<float, 8> o;
 #pragma unroll
         for (int t = 0; t < 8; ++t) o.v[t] = v[t];
-        *reinterpret_cast<Pack<float, 8> *>(a.partial + (size_t)slot * d + c) = o;
+        *reinterpret_cast<Pack<float, 8> *>(a.partial + (size_t)(slot - a.slot0) * d + c) = o;
       } else {
         finish_cols<bf16_t, Tout, 8>(a, row, c, v);
       }
@@ -601,7 +631,7 @@ __global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ri
   if (slot < 0 && blockIdx.y == 0) zero_pad_cols<Tout>(a, row, lane);
 }
 
-typedef void (*spmm_fn)(const Batch<SpmmArgs>);
+typedef void (*spmm_fn)(const SpmmArgs);
 struct Shape {
   int vec, lpr;
   spmm_fn main, reduce;
@@ -635,7 +665,7 @@ constexpr int64_t kDeepWaves = 8192;  // two rounds of the four waves per SIMD t
 }  // namespace
 
 static const Shape *pick_shape(const SpmmArgs &a, int src_dtype, int out_dtype) {
-  const bool deep = a.long_pieces && (a.n_class_blocks * (int64_t)4 + a.n_tasks - a.tail_task0) * ((a.d + 255) / 256) <= kDeepWaves;
+  const bool deep = a.long_pieces && (a.n_class_blocks * (int64_t)4 + a.n_tail + a.n_short) * ((a.d + 255) / 256) <= kDeepWaves;
   if (src_dtype == DT_BF16) {
     if (a.d % 2 != 0) return nullptr;  // rejected at create time
     return out_dtype == DT_BF16 ? pick_for<bf16_t, bf16_t>(a.d, deep) : pick_for<bf16_t, float>(a.d, deep);
@@ -663,81 +693,34 @@ static spmm_fn ring_for(const SpmmArgs &a) {
   return a.d <= 128 ? ring_fn<Tout, 1>(a, unroll) : a.d <= 256 ? ring_fn<Tout, 2>(a, unroll) : ring_fn<Tout, 4>(a, unroll >= 8 ? 4 : 2);
 }
 
-// Runs launches [0, n) (kernel fn[i], gx[i] workgroups in x, gy[i] in y; gx = 0: nothing to do), those of one kernel and gy
-// together.  A plane is a multiple of 8 workgroups: workgroup i of every sub-launch runs on XCD i % 8.
-static int launch_merged(const SpmmArgs *const *a, const spmm_fn *fn, const unsigned *gx, const unsigned *gy, int n, hipStream_t s) {
-  bool done[kBatch] = {};
-  for (int i = 0; i < n; ++i) {
-    if (done[i] || gx[i] == 0) continue;
-    Batch<SpmmArgs> b;
-    unsigned m = 0, width = 0;
-    for (int j = i; j < n; ++j) {
-      if (done[j] || gx[j] == 0 || fn[j] != fn[i] || gy[j] != gy[i]) continue;
-      done[j] = true;
-      b.sub[m++] = *a[j];
-      width = std::max(width, gx[j]);
-    }
-    if (m > 1) width = (width + 7) / 8 * 8;
-    hipLaunchKernelGGL(fn[i], dim3(width, gy[i], m), dim3(256), 0, s, b);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return (int)e;
-  }
-  return hipSuccess;
+static int launch_checked(spmm_fn fn, dim3 grid, const SpmmArgs &a, hipStream_t s) {
+  hipLaunchKernelGGL(fn, grid, dim3(256), 0, s, a);
+  return (int)hipGetLastError();
 }
 
-int launch_spmm(const SpmmLaunch *l, int n, hipStream_t s) {
-  if (n > kBatch) return hipErrorInvalidValue;
-  SpmmArgs args[kBatch];
-  const SpmmArgs *ptr[kBatch];
-  spmm_fn fn[kBatch];
-  unsigned gx[kBatch], gy[kBatch];
-  for (int i = 0; i < n; ++i) {
-    SpmmArgs &a = args[i] = l[i].a;
-    ptr[i] = &a;
-    gx[i] = 0;
-    gy[i] = 1;
-    fn[i] = nullptr;
-    if (a.n_tasks <= 0) continue;
-    if (mfma_path(a, l[i].src_dtype)) {
-      // short whole rows (the tail of the task list) are served a row per 16-lane group, by extra workgroups of the
-      // same launch, when a row fits the registers of such a group
-      const int64_t n_short = (a.d <= 256 && a.n_short > 0 && a.n_short <= a.n_tasks - a.tail_task0) ? a.n_short : 0;
-      a.n_tasks -= n_short;
-      a.n_short = n_short;
-      a.n_main_blocks = a.n_class_blocks + (a.n_tasks - a.tail_task0 + 3) / 4;
-      gx[i] = (unsigned)(a.n_main_blocks + (n_short + 15) / 16);  // 0: only class pieces, none of them active
-      fn[i] = l[i].out_dtype == DT_BF16 ? ring_for<bf16_t>(a) : ring_for<float>(a);
-      gy[i] = a.d <= 256 ? 1u : (unsigned)((a.d + 511) / 512);
-    } else {
-      const Shape *best = pick_shape(a, l[i].src_dtype, l[i].out_dtype);
-      if (!best) return hipErrorInvalidValue;
-      const int tile_w = best->lpr * best->vec;
-      fn[i] = best->main;
-      gx[i] = (unsigned)(a.n_class_blocks + (a.n_tasks - a.tail_task0 + 3) / 4);
-      gy[i] = (unsigned)((a.d + tile_w - 1) / tile_w);
-      if (gy[i] > 1) gx[i] = (gx[i] + 7) / 8 * 8;  // every column tile starts on the same XCD (tasks past the end do nothing)
-    }
+int launch_spmm(const SpmmArgs &a_in, int src_dtype, int out_dtype, hipStream_t s) {
+  SpmmArgs a = a_in;
+  const int64_t tail_blocks = (a.n_tail + 3) / 4, short_waves = a.n_short;
+  if (a.n_class_blocks + tail_blocks + short_waves <= 0) return hipSuccess;
+  if (mfma_path(a, src_dtype)) {
+    // short rows are served a row per 16-lane group, by extra workgroups of the same launch, when a row fits the registers
+    // of such a group
+    a.n_main_blocks = a.n_class_blocks + tail_blocks + (a.d <= 256 ? 0 : short_waves / 4);
+    const unsigned gx = (unsigned)(a.n_main_blocks + (a.d <= 256 ? (short_waves + 15) / 16 : 0));
+    return launch_checked(out_dtype == DT_BF16 ? ring_for<bf16_t>(a) : ring_for<float>(a), dim3(gx, a.d <= 256 ? 1u : (unsigned)((a.d + 511) / 512)), a, s);
   }
-  return launch_merged(ptr, fn, gx, gy, n, s);
+  const Shape *best = pick_shape(a, src_dtype, out_dtype);
+  if (!best) return hipErrorInvalidValue;
+  const int tile_w = best->lpr * best->vec;
+  int64_t gx = a.n_class_blocks + tail_blocks + short_waves / 4;
+  const unsigned gy = (unsigned)((a.d + tile_w - 1) / tile_w);
+  if (gy > 1) gx = (gx + 7) / 8 * 8;  // every column tile starts on the same XCD (tasks past the end do nothing)
+  return launch_checked(best->main, dim3((unsigned)gx, gy), a, s);
 }
 
-int launch_spmm_reduce(const SpmmLaunch *l, int n, hipStream_t s) {
-  if (n > kBatch) return hipErrorInvalidValue;
-  const SpmmArgs *ptr[kBatch];
-  spmm_fn fn[kBatch];
-  unsigned gx[kBatch], gy[kBatch];
-  for (int i = 0; i < n; ++i) {
-    const SpmmArgs &a = l[i].a;
-    ptr[i] = &a;
-    gx[i] = 0;
-    gy[i] = 1;
-    fn[i] = nullptr;
-    if (a.n_long <= 0) continue;
-    const Shape *best = pick_shape(a, l[i].src_dtype, l[i].out_dtype);
-    if (!best) return hipErrorInvalidValue;
-    fn[i] = best->reduce;
-    gx[i] = (unsigned)a.n_long;
-    gy[i] = (unsigned)((a.d + 32 * best->vec - 1) / (32 * best->vec));
-  }
-  return launch_merged(ptr, fn, gx, gy, n, s);
+int launch_spmm_reduce(const SpmmArgs &a, int src_dtype, int out_dtype, hipStream_t s) {
+  if (a.n_long <= 0) return hipSuccess;
+  const Shape *best = pick_shape(a, src_dtype, out_dtype);
+  if (!best) return hipErrorInvalidValue;
+  return launch_checked(best->reduce, dim3((unsigned)a.n_long, (unsigned)((a.d + 32 * best->vec - 1) / (32 * best->vec))), a, s);
 }

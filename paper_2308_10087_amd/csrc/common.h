@@ -99,7 +99,7 @@ struct SpmmArgs {
   // XCD-aware serving order.  Class c's pieces are tasks [cls_begin[c], cls_end[c]).  Workgroups are dealt round-robin to the
   // 8 XCDs; the groups of four tasks of the active classes, one class after the other, are cut into eight runs, and XCD x
   // (workgroups with index % 8 == x) serves xcd[x].groups of them from group xcd[x].group0 of class xcd[x].cls on.
-  // Workgroups from n_class_blocks on serve the tail: tasks [tail0, tail0 + n_tail), then the short rows.
+  // Workgroups from n_class_blocks on serve the tail, tasks [tail0, tail0 + n_tail), and the short rows.
   int32_t cls_begin[kMaxClasses], cls_end[kMaxClasses];
   XcdRun xcd[8];
   int32_t n_class_blocks;
@@ -109,7 +109,12 @@ struct SpmmArgs {
   // row would spend its life waiting for three dependent round trips to move a kilobyte or two.  The vector-ALU kernel and
   // rows wider than 256 columns take them like any other task.
   int64_t short0, n_short;
-  int64_t n_main_blocks;  // set by the launcher: workgroups from this index on serve the short rows
+  // The two lists' workgroups are dealt out evenly, so that the launch goes through both in about the order of their rows:
+  // workgroup p behind the class pieces serves short rows if p mix crosses a whole number of 2^32 (set by the launcher).
+  // First all of the one and then of the other is slower where the gathers bound the launch: 3.6 M entries of 512-byte rows
+  // 192 against 177 us.
+  uint64_t mix;
+  int32_t short_valu;     // short rows: fp32 weights on the vector ALU
   const uint8_t *slot_class;  // class of every partial slot (255: none); pieces of inactive classes are not run
   uint32_t active_classes;
   int32_t all_classes_active;
@@ -157,11 +162,22 @@ struct SpmmArgs {
   int32_t long_pieces = 0; // rows are cut into pieces of 256 entries or more (forward aggregations of fp32 stages)
   int32_t unroll = 2;      // gather slots per wave of the matrix-core aggregation: 2, 4 or 8
 };
+constexpr int kShortRowMost = 16;    // entries of a short row: one per lane of its group
 constexpr int kTaskChunkShift = 24;  // a piece or an uncut row has fewer than 2^24 entries
 constexpr uint32_t kTaskCountMask = (1u << kTaskChunkShift) - 1u;
 static_assert(kMaxChunks <= 256, "the chunk shares a word with a count");
 static_assert(sizeof(SpmmArgs) <= 4096, "kernel arguments");
 
+// workgroup b behind the class pieces: whether it serves short rows, and how many of its kind come before it
+struct SpmmTurn {
+  bool is_short;
+  uint32_t index;
+};
+__device__ inline SpmmTurn spmm_turn(const SpmmArgs &a, unsigned b) {
+  const uint64_t p = b - (unsigned)a.n_class_blocks;
+  const uint32_t before = (uint32_t)(p * a.mix >> 32), upto = (uint32_t)((p + 1) * a.mix >> 32);
+  return SpmmTurn{upto > before, upto > before ? before : (uint32_t)p - before};
+}
 // which task the wave `wave` of workgroup `b` runs (-1: none); cls: its class (-1: none)
 __device__ inline int64_t spmm_task_index(const SpmmArgs &a, unsigned b, int wave, int &cls) {
   cls = -1;
@@ -181,10 +197,9 @@ __device__ inline int64_t spmm_task_index(const SpmmArgs &a, unsigned b, int wav
     }
     return -1;
   }
-  int64_t t = (int64_t)(b - a.n_class_blocks) * 4 + wave;
-  if (t < a.n_tail) return a.tail0 + t;
-  t -= (a.n_tail + 3) / 4 * 4;
-  return t >= 0 && t < a.n_short ? a.short0 + t : -1;
+  const SpmmTurn w = spmm_turn(a, b);
+  const int64_t t = (int64_t)w.index * 4 + wave;
+  return w.is_short ? (t < a.n_short ? a.short0 + t : -1) : t < a.n_tail ? a.tail0 + t : -1;
 }
 // The mask of a row chunk; chunk is the same for the whole wave.  The table is read through the scalar cache: by the time
 // a wave has its index words it has its mask.

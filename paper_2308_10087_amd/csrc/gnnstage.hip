@@ -47,7 +47,7 @@ std::string g_create_error;
 //   GNNSTAGE_HOT_CLASSES (0 = off, 2..32: on whatever the table size)   classes of the hottest sources
 //   GNNSTAGE_HOT_ROWS                 sources per such class
 //   GNNSTAGE_HOT_MIN_ROW              rows from this length on are cut by hotness class
-//   GNNSTAGE_SHORT_ROW (0 = off)      whole rows of at most this many entries are served a row per 16-lane group
+//   GNNSTAGE_SHORT_ROW (0 = off, up to 16)   whole rows of at most this many entries are served a row per 16-lane group
 struct Tuning {
   int split_edges = 0;          // 0: from the launch size
   int xcd_classes = 0;          // 0: from the size of the gathered table
@@ -65,9 +65,8 @@ struct Tuning {
   int hot_classes = -1;         // -1: 16 for gathered tables beyond 256 MB, none below
   int hot_rows = 0;             // 0: as many rows as fit an XCD's 4 MB L2
   int hot_min_row = 2048;       // measured on the 10 M vertex graph: 512 -> 142.8, 1024 -> 140.6, 2048 -> 140.4 ms per step (off: 143.2)
-  int short_row = -1;           // whole rows of at most this many entries are served a row per 16-lane group (0: none;
-                                // -1: 4 for gathered tables beyond 256 MB, none below: 141.2 against 143.2 ms per step there,
-                                // nothing or a small loss on tables that sit in a cache)
+  // whole rows of at most this many entries are served four to a wave (0: none; -1: see Shape::short_row)
+  int short_row = -1;
 };
 
 Tuning read_tuning() {
@@ -89,7 +88,7 @@ Tuning read_tuning() {
   if ((e = getenv("GNNSTAGE_HOT_CLASSES")) && atoi(e) >= 0 && atoi(e) <= kMaxClasses) t.hot_classes = atoi(e);
   if ((e = getenv("GNNSTAGE_HOT_ROWS")) && atoi(e) >= 1) t.hot_rows = atoi(e);
   if ((e = getenv("GNNSTAGE_HOT_MIN_ROW")) && atoi(e) >= 1) t.hot_min_row = atoi(e);
-  if ((e = getenv("GNNSTAGE_SHORT_ROW")) && atoi(e) >= 0) t.short_row = atoi(e);
+  if ((e = getenv("GNNSTAGE_SHORT_ROW")) && atoi(e) >= 0) t.short_row = std::min(atoi(e), kShortRowMost);
   return t;
 }
 
@@ -417,7 +416,12 @@ struct Shape {
   // classes of the hottest sources instead of id-range classes (tables that fit no cache)
   bool hot() const { return hot_classes_setting(tune, n * widest_row_bytes()) >= 2; }
   int64_t hot_rows() const { return hot_rows_setting(tune, widest_row_bytes()); }
-  int short_row() const { return tune.short_row >= 0 ? tune.short_row : (n * widest_row_bytes() > ((int64_t)256 << 20) ? 4 : 0); }
+  // Short rows.  Tables that fit no cache: up to 4 entries, summed on the vector ALU with fp32 weights (10 M vertices 141.2 against
+  // 143.2 ms per step; up to 8 / 16: 143.2 / 148.0, the launch is bound by the gathers).  Others: up to 16, on the matrix cores.
+  bool short_valu() const { return n * widest_row_bytes() > ((int64_t)256 << 20); }
+  // (None where every aggregation runs on the vector ALU, a row to a wave: 89 k fp32 vertices of width 100 1.99 ms per pass in row
+  // order, 2.08 with the short rows apart.)
+  int short_row() const { return tune.short_row >= 0 ? tune.short_row : valu_layers() == L ? 0 : short_valu() ? 4 : kShortRowMost; }
   int classes() const {
     if (hot()) return hot_classes_setting(tune, n * widest_row_bytes());
     return xcd_classes_setting(tune, n * widest_row_bytes());
@@ -429,12 +433,16 @@ struct Shape {
   // width 128), 13.9 / 13.3 / 13.6 ms (169 k vertices of width 256).
   int least_piece(bool transposed) const {
     if (dtype == GNNSTAGE_F32 && !transposed) return kLeastPieceF32Fwd;
+    const int valu = valu_layers();
+    return valu == L ? 32 : valu > 0 ? 64 : 128;
+  }
+  int valu_layers() const {  // whose aggregations run on the vector ALU
     int valu = 0;
     for (int j = 0; j < L; ++j) {
       const bool f32_rows = dtype == GNNSTAGE_F32 || (j == 0 && level0_f32 && !tf[j]);
       valu += f32_rows || (tf[j] ? dims[j + 1] : dims[j]) % 8 != 0 || tune.spmm_valu;
     }
-    return valu == L ? 32 : valu > 0 ? 64 : 128;
+    return valu;
   }
   // dense blocks serve the matrix-core aggregation only: every aggregation of the stage must gather bf16 rows
   // of width 128 or 256
@@ -949,6 +957,7 @@ void set_schedule(const gnnstage *st, int dir, int c0, int c1, Select sel, const
   a.n_tail = t.count(t.n_classes, c0, c1);
   a.short0 = t.first(t.n_classes + 1, c0);
   a.n_short = t.count(t.n_classes + 1, c0, c1);
+  a.short_valu = st->s.short_valu() ? 1 : 0;
   a.slot_class = st->at<uint8_t>(dir ? lay.b_slot_class : lay.f_slot_class);
   const int64_t l0 = t.lr_off[(size_t)c0];
   a.lr_row = st->at<int32_t>(dir ? lay.b_lr_row : lay.f_lr_row) + l0;
@@ -1767,18 +1776,22 @@ extern "C" int gnnstage_create(const gnnstage_desc *d, gnnstage_t **out) try {
     t.K = s.K;
     t.n_classes = classes > 1 ? classes : 0;
     const int n_sec = t.n_classes + 2;
-    struct Section {
-      std::vector<int32_t> row, slot;
-      std::vector<int64_t> e0;
-      std::vector<uint32_t> ne;
+    struct Section {  // room for the most it can hold, of which only what is written takes memory
+      std::unique_ptr<int32_t[]> row, slot;
+      std::unique_ptr<int64_t[]> e0;
+      std::unique_ptr<uint32_t[]> ne;
+      int64_t size = 0;
+      explicit Section(int64_t most)
+          : row(new int32_t[(size_t)most]), slot(new int32_t[(size_t)most]), e0(new int64_t[(size_t)most]), ne(new uint32_t[(size_t)most]) {}
       void add(int32_t r, int64_t e, uint32_t n, int32_t sl) {
-        row.push_back(r);
-        e0.push_back(e);
-        ne.push_back(n);
-        slot.push_back(sl);
+        row[(size_t)size] = r;
+        e0[(size_t)size] = e;
+        ne[(size_t)size] = n;
+        slot[(size_t)size++] = sl;
       }
     };
-    std::vector<Section> sec((size_t)n_sec);
+    std::vector<Section> sec;
+    for (int q = 0; q < n_sec; ++q) sec.emplace_back(q < t.n_classes ? pc.total_slots : s.task_capacity(pc.total_tasks));  // class pieces have slots
     std::vector<std::vector<int64_t>> upto((size_t)n_sec, std::vector<int64_t>(1, 0));  // tasks of a section up to every chunk's end
     t.slot_off.assign(1, 0);
     t.lr_off.assign(1, 0);
@@ -1787,7 +1800,7 @@ extern "C" int gnnstage_create(const gnnstage_desc *d, gnnstage_t **out) try {
     std::vector<uint8_t> slot_class;
     std::vector<int32_t> lrow, lslot0, ldense0, lndense, litem0;
     std::vector<uint32_t> ln;
-    const int short_row = s.short_row();
+    const int short_row = s.short_row() > 0 ? s.short_row() : -1;  // -1: no row is
     std::vector<int32_t> row, ne, slot;
     std::vector<int64_t> e0;
     for (int c = 0; c < s.K; ++c) {
@@ -1814,19 +1827,24 @@ extern "C" int gnnstage_create(const gnnstage_desc *d, gnnstage_t **out) try {
       if (got < 0 || got > pc.tasks[c] || ns > pc.slots[c]) return GNNSTAGE_EINVAL;
       const int64_t slot0 = t.slot_off.back(), l0 = t.lr_off.back();
       const uint32_t chunk_bits = (uint32_t)c << kTaskChunkShift;
-      int64_t first_whole = got;  // whole rows come last in the list
-      while (first_whole > 0 && slot[(size_t)first_whole - 1] < 0) --first_whole;
-      for (int64_t i = 0; i < got; ++i) {
-        int q = 0;
-        while (q < t.n_classes && i >= coff[(size_t)q + 1]) ++q;  // t.n_classes: the tail
-        if (i >= first_whole && short_row > 0 && ne[(size_t)i] <= short_row) q = t.n_classes + 1;
-        if ((uint32_t)ne[(size_t)i] > kTaskCountMask) return GNNSTAGE_ENOTSUP;
-        sec[(size_t)q].add(row[(size_t)i], e0[(size_t)i], (uint32_t)ne[(size_t)i] | chunk_bits, slot[(size_t)i] < 0 ? -1 : (int32_t)(slot0 + slot[(size_t)i]));
-        if (q < t.n_classes)
-          for (int64_t e = e0[(size_t)i]; e < e0[(size_t)i] + ne[(size_t)i]; ++e) t.cls_entries[((size_t)c * t.n_classes + q) * s.K + (packed[e] >> vbits)] += 1;
+      Section &tail = sec[(size_t)t.n_classes], &shorts = sec[(size_t)n_sec - 1];
+      int64_t i = 0;
+      for (int q = 0; q < t.n_classes; ++q) {
+        Section &x = sec[(size_t)q];
+        int64_t *entries = &t.cls_entries[((size_t)c * t.n_classes + q) * s.K];
+        for (; i < coff[(size_t)q + 1]; ++i) {
+          x.add(row[(size_t)i], e0[(size_t)i], (uint32_t)ne[(size_t)i] | chunk_bits, (int32_t)(slot0 + slot[(size_t)i]));
+          for (int64_t e = e0[(size_t)i]; e < e0[(size_t)i] + ne[(size_t)i]; ++e) entries[packed[e] >> vbits] += 1;
+        }
       }
-      while (sec[(size_t)n_sec - 1].row.size() % 4 != 0) sec[(size_t)n_sec - 1].add(-1, 0, chunk_bits, -1);
-      for (int q = 0; q < n_sec; ++q) upto[(size_t)q].push_back((int64_t)sec[(size_t)q].row.size());
+      for (; i < got; ++i) {
+        if ((uint32_t)ne[(size_t)i] > kTaskCountMask) return GNNSTAGE_ENOTSUP;
+        const bool piece = slot[(size_t)i] >= 0;
+        Section &x = !piece && ne[(size_t)i] <= short_row ? shorts : tail;
+        x.add(row[(size_t)i], e0[(size_t)i], (uint32_t)ne[(size_t)i] | chunk_bits, piece ? (int32_t)(slot0 + slot[(size_t)i]) : -1);
+      }
+      while (shorts.size % 4 != 0) shorts.add(-1, 0, chunk_bits, -1);
+      for (int q = 0; q < n_sec; ++q) upto[(size_t)q].push_back(sec[(size_t)q].size);
       slot_class.insert(slot_class.end(), sclass.begin(), sclass.begin() + ns);
       t.slot_off.push_back(slot0 + ns);
       // cut rows: their slots are consecutive, so sorting the pieces by slot groups them by row
@@ -1882,12 +1900,14 @@ extern "C" int gnnstage_create(const gnnstage_desc *d, gnnstage_t **out) try {
     for (int q = 0; q < n_sec; ++q) {
       const Section &x = sec[(size_t)q];
       for (const int64_t u : upto[(size_t)q]) t.sec.push_back(at + u);
-      if (!up(dir ? lay.b_task_row : lay.f_task_row, x.row.data(), 4, x.row.size(), at) || !up(dir ? lay.b_task_e0 : lay.f_task_e0, x.e0.data(), 8, x.e0.size(), at) ||
-          !up(dir ? lay.b_task_ne : lay.f_task_ne, x.ne.data(), 4, x.ne.size(), at) || !up(dir ? lay.b_task_slot : lay.f_task_slot, x.slot.data(), 4, x.slot.size(), at))
+      const size_t n = (size_t)x.size;
+      if (at + x.size > s.task_capacity(pc.total_tasks)) return GNNSTAGE_ENOTSUP;
+      if (!up(dir ? lay.b_task_row : lay.f_task_row, x.row.get(), 4, n, at) || !up(dir ? lay.b_task_e0 : lay.f_task_e0, x.e0.get(), 8, n, at) ||
+          !up(dir ? lay.b_task_ne : lay.f_task_ne, x.ne.get(), 4, n, at) || !up(dir ? lay.b_task_slot : lay.f_task_slot, x.slot.get(), 4, n, at))
         return GNNSTAGE_EHIP;
-      at += (int64_t)x.row.size();
+      at += x.size;
     }
-    if (at > s.task_capacity(pc.total_tasks) || at > 0x7fffffff) return GNNSTAGE_ENOTSUP;
+    if (at > 0x7fffffff) return GNNSTAGE_ENOTSUP;  // sections are indexed in 32 bits
     if (!up(dir ? lay.b_slot_class : lay.f_slot_class, slot_class.data(), 1, slot_class.size(), 0) || !up(dir ? lay.b_lr_row : lay.f_lr_row, lrow.data(), 4, lrow.size(), 0) ||
         !up(dir ? lay.b_lr_slot0 : lay.f_lr_slot0, lslot0.data(), 4, lslot0.size(), 0) || !up(dir ? lay.b_lr_n : lay.f_lr_n, ln.data(), 4, ln.size(), 0))
       return GNNSTAGE_EHIP;

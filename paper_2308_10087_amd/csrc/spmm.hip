@@ -336,18 +336,179 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) bf16x8_t global_bf16x8_t;  // a load through it is a global load
 
-// Short rows (at most a few entries: the bulk of a power-law graph's rows, a few percent of its entries).  A wave
-// per row would spend its life waiting for three dependent round trips to move a kilobyte or two, and a launch
-// would need several rounds of waves.  Here every 16-lane group owns one row: a lane keeps 8 columns of each
-// 128-column tile in fp32 registers and the sum runs on the vector ALU; two to four of the row's entries are in
-// flight per lane.  Entries that a backward launch drops are not loaded at all.  `first` = index of the first row
-// of this workgroup among the launch's short rows.  The four rows of a wave are of one chunk (fillers see to it).
+// A record of the gather loops: row address and the weight as two bf16.
+__device__ inline uint32_t pack_weight(float w) {
+  const bf16_t hi = (bf16_t)w;
+  const bf16_t lo = (bf16_t)(w - (float)hi);
+  return (uint32_t)__builtin_bit_cast(uint16_t, hi) | ((uint32_t)__builtin_bit_cast(uint16_t, lo) << 16);
+}
+// What a lane contributes to the B operand: selw moves its half of the packed weight (columns 0 .. 7 the upper, 8 .. 15 the lower)
+// into bf16 element pos & 1 of a word and zeroes the other, wword says which of the four words that is.
+struct WeightLane {
+  uint32_t selw;
+  int wword;
+};
+__device__ inline WeightLane weight_lane(int lig) {
+  const int pos = lig & 7;
+  const uint32_t b0 = lig >= 8 ? 2u : 0u;
+  return WeightLane{(pos & 1) ? (((b0 + 1u) << 24) | (b0 << 16) | 0x0c0cu) : (0x0c0c0000u | ((b0 + 1u) << 8) | b0), pos >> 1};
+}
+__device__ inline bf16x8_t weight_operand(const WeightLane &l, uint32_t packed) {
+  const uint32_t wbits = __builtin_amdgcn_perm(0u, packed, l.selw);
+  u32x4_t bw;
+  bw[0] = l.wword == 0 ? wbits : 0u;
+  bw[1] = l.wword == 1 ? wbits : 0u;
+  bw[2] = l.wword == 2 ? wbits : 0u;
+  bw[3] = l.wword == 3 ? wbits : 0u;
+  return __builtin_bit_cast(bf16x8_t, bw);
+}
+// Accumulators of one row -> its columns in LDS.  Element i of lane l is D[m = 4*(l/16) + i][n = l%16]; column = 8m + n%8, the
+// halves n < 8 and n >= 8 are the two parts of the weight.
+template <int NT>
+__device__ inline void row_to_lds(const f32x4_t (&acc)[NT], float *rowbuf, int lane) {
+#pragma unroll
+  for (int h = 0; h < NT; ++h)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float v = acc[h][i] + __shfl_xor(acc[h][i], 8);
+      if (!(lane & 8)) rowbuf[h * 128 + (4 * (lane >> 4) + i) * 8 + (lane & 7)] = v;
+    }
+}
+__device__ inline void lds_written() {  // the wave's own LDS writes have landed
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Short rows (at most kShortRowMost entries: the bulk of a power-law graph's rows).  A wave per row spends its life in a chain
+// of memory round trips (task, index words, gathers, the epilogue's row) to move a kilobyte or two, and what a launch of many
+// short rows takes is rounds of such chains: a backward launch, which gathers half of the entries, took nine tenths of a forward
+// one.  Here a wave serves four rows in one chain: a 16-lane group reads the index words of one, one per lane; the kept
+// entries of the four rows become one run of records, each row's filled up to a multiple of four with zero weights, so that
+// the gather loop sees steps of four records as in spmm_ring_kernel and a row's sum has the same bits as there; at a row's last
+// step its accumulators go to LDS (behind the records, the last row's in their place); the epilogue's rows are asked for with the
+// index words.  `first` = index of the first row of this wave among the launch's short rows.  The four rows are of one chunk
+// (fillers see to it).
+template <typename Tout, int NT, bool FULL>
+__device__ __forceinline__ void spmm_short_rows(const SpmmArgs &a, int64_t first, u32x4_t *ring) {
+  constexpr int U = 2;           // steps in flight
+  constexpr int LR = NT * 16;    // lanes that hold a row's columns behind the sums
+  constexpr int NR = 64 / LR;    // rows stored at a time
+  constexpr int NP = 4 / NR;
+  static_assert(NT == 1 || NT == 2, "the sums of three rows of 256 columns fit behind the records");
+  if (first >= a.n_short) return;  // whole waves: n_short is a multiple of four
+  const int lane = threadIdx.x & 63, lig = lane & 15, g = lane >> 4;
+  auto rowbuf = [&](int r) { return reinterpret_cast<float *>(ring + (r < 3 ? 4 * kShortRowMost + r * (NT * 32) : 0)); };  // NT * 128 floats
+  const int64_t task = a.short0 + first + g;
+  const uint32_t ne_chunk = a.task_ne[task];
+  const int64_t e0 = a.task_e0[task];
+  const bool drop_unsel = a.src_unsel == nullptr, many = a.many_chunks != 0;
+  const int ne = (int)(ne_chunk & kTaskCountMask);  // 0 of a filler
+  const int d = a.d, c_out = (lane % LR) * 8;
+  int32_t row_out[NP];  // rows that this lane stores columns c_out .. of
+  Pack<bf16_t, 8> xa[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) row_out[p] = a.task_row[a.short0 + first + p * NR + lane / LR];
+  uint32_t pc = 0;
+  float w_own = 0.f;
+  if (lig < ne) {
+    pc = a.pidx[e0 + lig];
+    w_own = a.val[e0 + lig];
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p)
+    if (NT == 1 && row_out[p] >= 0 && c_out < d) xa[p] = load_aux<bf16_t, 8>(a, row_out[p], c_out);
+  uint32_t classes;
+  const WaveMask mask = wave_mask(spmm_row_mask(a.pass, a.mask, (uint32_t)__builtin_amdgcn_readfirstlane((int)ne_chunk) >> kTaskChunkShift, classes), many);
+  const bool sel = mask_test(mask, pc >> a.vbits, many);
+  const bool keep = lig < ne && (sel || !drop_unsel);
+  const uint64_t bal = __ballot(keep);
+  int end[4];  // steps up to every row's last
+  int steps = 0, my0 = 0;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (r == g) my0 = steps;
+    steps += (__popc((uint32_t)(bal >> (16 * r)) & 0xffffu) + 3) >> 2;
+    end[r] = steps;
+  }
+  const uint32_t bits = (uint32_t)(bal >> (16 * g)) & 0xffffu;
+  const int nk = __popc(bits);
+  const uint64_t at = reinterpret_cast<uint64_t>(sel ? a.src_sel : a.src_unsel) + (uint64_t)(pc & ((1u << a.vbits) - 1u)) * ((uint32_t)a.src_ld * 2u);
+  // fillers of the last step: a kept row of the same sum, weight zero
+  const int pad_from = (g * 16 + (bits ? __ffs(bits) - 1 : 0)) << 2;
+  const uint32_t pad_lo = (uint32_t)__builtin_amdgcn_ds_bpermute(pad_from, (int)(uint32_t)at);
+  const uint32_t pad_hi = (uint32_t)__builtin_amdgcn_ds_bpermute(pad_from, (int)(uint32_t)(at >> 32));
+  if (keep) ring[my0 * 4 + __popc(bits & ((1u << lig) - 1u))] = u32x4_t{(uint32_t)at, (uint32_t)(at >> 32), pack_weight(w_own), 0u};
+  if (lig >= nk && lig < ((nk + 3) & ~3)) ring[my0 * 4 + lig] = u32x4_t{pad_lo, pad_hi, 0u, 0u};
+  lds_written();
+  const WeightLane wl = weight_lane(lig);
+  const bf16x8_t zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+  f32x4_t acc[NT];
+#pragma unroll
+  for (int h = 0; h < NT; ++h) acc[h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  bf16x8_t x[U][NT];
+  uint32_t wk[U];
+  auto issue = [&](int step, int u) {
+    const u32x4_t rec = ring[step * 4 + g];
+    const global_bf16x8_t *p = reinterpret_cast<const global_bf16x8_t *>(((uint64_t)rec[1] << 32 | rec[0]) + (uint32_t)lig * 16u);
+    wk[u] = rec[2];
+#pragma unroll
+    for (int h = 0; h < NT; ++h) x[u][h] = (FULL || h * 128 + lig * 8 < d) ? p[h * 16] : zero8;
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int r = 0;  // rows finished
+  auto finish_rows = [&](int done) {  // those whose last step is among the first `done`
+    while (r < 4 && (r == 0 ? end[0] : r == 1 ? end[1] : r == 2 ? end[2] : end[3]) <= done) {
+      row_to_lds<NT>(acc, rowbuf(r), lane);
+#pragma unroll
+      for (int h = 0; h < NT; ++h) acc[h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      ++r;
+    }
+  };
+  finish_rows(0);
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (u < steps) issue(u, u);
+  for (int k = 0; k < steps; k += U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (k + u < steps) {  // uniform, like all control flow around the matrix instruction
+        const bf16x8_t bfrag = weight_operand(wl, wk[u]);
+#pragma unroll
+        for (int h = 0; h < NT; ++h) acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[u][h], bfrag, acc[h], 0, 0, 0);
+        if (k + u + U < steps) issue(k + u + U, u);
+        finish_rows(k + u + 1);
+      }
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p)  // (registers for both rows of a lane are free only now)
+    if (NT == 2 && row_out[p] >= 0 && c_out < d) xa[p] = load_aux<bf16_t, 8>(a, row_out[p], c_out);
+  lds_written();
+#pragma unroll 1
+  for (int p = 0; p < NP; ++p) {
+    const float *sums = rowbuf(p * NR + lane / LR) + c_out;
+    const int32_t row = p == 0 ? row_out[0] : row_out[NP - 1];
+    if (row < 0) continue;
+    if (c_out < d) {
+      float v[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) v[t] = sums[t];
+      finish_cols<bf16_t, Tout, 8>(a, row, c_out, v, p == 0 ? xa[0] : xa[NP - 1]);
+    }
+    zero_pad_cols<Tout>(a, row, lane % LR);
+  }
+}
+
+// Short rows of tables that fit no cache (at most four entries, weights in fp32): every 16-lane group owns one row: a lane keeps
+// 8 columns of each 128-column tile in fp32 registers and the sum runs on the vector ALU; two to four of the row's entries are in
+// flight per lane.  Entries that a backward launch drops are not loaded at all.
 template <typename Tout, int NT, bool FULL, bool MANY>
-__device__ __forceinline__ void spmm_short_rows(const SpmmArgs &a, int64_t first) {
+__device__ __forceinline__ void spmm_short_rows_valu(const SpmmArgs &a, int64_t first) {
+  if (first >= a.n_short) return;  // whole waves: n_short is a multiple of four
   const int lane = threadIdx.x & 63, lig = lane & 15;
-  const int64_t t = first + (threadIdx.x >> 4);
-  if (first + (threadIdx.x >> 6) * 4 >= a.n_short) return;  // whole waves: n_short is a multiple of four
-  const int64_t task = a.short0 + t;
+  const int64_t task = a.short0 + first + (lane >> 4);
   const uint32_t ne_chunk = a.task_ne[task];
   const int64_t row = a.task_row[task], e0 = a.task_e0[task];
   uint32_t classes;
@@ -420,17 +581,21 @@ __global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ri
   constexpr int KB = 2;    // metadata batches per phase
   constexpr int R = 256;   // ring capacity in records: a phase appends at most 64 * KB, fewer than 8 * U are left over
   static_assert(TILE_W * sizeof(float) <= R * sizeof(u32x4_t), "the output row reuses the ring's memory");
+  static_assert(NT > 2 || 4 * kShortRowMost * sizeof(u32x4_t) + 3 * TILE_W * sizeof(float) <= R * sizeof(u32x4_t), "and so do those of short rows");
   static_assert((U & (U - 1)) == 0 && U <= 8, "slot count");
   __shared__ u32x4_t ring_all[4][R];
-  if ((int64_t)blockIdx.x >= a.n_main_blocks) {  // the workgroups behind the main part serve the short rows, 16 each
-    if constexpr (NT <= 2) {
-      const int64_t first = ((int64_t)blockIdx.x - a.n_main_blocks) * 16;
-      if (a.many_chunks != 0)
-        spmm_short_rows<Tout, NT, FULL, true>(a, first);
+  if constexpr (NT <= 2) {
+    const SpmmTurn turn = spmm_turn(a, blockIdx.x);
+    if ((int)blockIdx.x >= a.n_class_blocks && turn.is_short) {  // 16 short rows
+      const int64_t first = (int64_t)turn.index * 16 + (threadIdx.x >> 6) * 4;
+      if (a.short_valu == 0)
+        spmm_short_rows<Tout, NT, FULL>(a, first, ring_all[threadIdx.x >> 6]);
+      else if (a.many_chunks != 0)
+        spmm_short_rows_valu<Tout, NT, FULL, true>(a, first);
       else
-        spmm_short_rows<Tout, NT, FULL, false>(a, first);
+        spmm_short_rows_valu<Tout, NT, FULL, false>(a, first);
+      return;
     }
-    return;
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int cls;
@@ -463,13 +628,7 @@ __global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ri
   const int d = a.d;
   const uint32_t row_bytes = (uint32_t)a.src_ld * 2u;
   const uint32_t lane_off = (uint32_t)lig * 16u;
-  const int pos = lig & 7;        // which element of the 8-column block this lane's B column picks
-  const bool lo_part = lig >= 8;  // B columns 8..15 carry the low half of the weight
-  // byte selector that moves this lane's weight half (bytes 0-1 or 2-3 of the packed word) into the
-  // bf16 element `pos & 1` of a B operand word and zeroes the other element
-  const uint32_t b0 = lo_part ? 2u : 0u;
-  const uint32_t selw = (pos & 1) ? (((b0 + 1u) << 24) | (b0 << 16) | 0x0c0cu) : (0x0c0c0000u | ((b0 + 1u) << 8) | b0);
-  const int wword = pos >> 1;
+  const WeightLane wl = weight_lane(lig);
 
   f32x4_t acc[NT];
 #pragma unroll
@@ -498,13 +657,7 @@ __global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ri
     __builtin_amdgcn_sched_barrier(0);
   };
   auto consume = [&](int u) {
-    const uint32_t wbits = __builtin_amdgcn_perm(0u, wk[u], selw);
-    u32x4_t bw;
-    bw[0] = wword == 0 ? wbits : 0u;
-    bw[1] = wword == 1 ? wbits : 0u;
-    bw[2] = wword == 2 ? wbits : 0u;
-    bw[3] = wword == 3 ? wbits : 0u;
-    const bf16x8_t bfrag = __builtin_bit_cast(bf16x8_t, bw);
+    const bf16x8_t bfrag = weight_operand(wl, wk[u]);
 #pragma unroll
     for (int h = 0; h < NT; ++h) acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[u][h], bfrag, acc[h], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
@@ -538,9 +691,7 @@ __global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ri
       const bool sel = mask_test(mask, pc >> a.vbits, many);
       const bool keep = lane < nraw && (sel || !drop_unsel);
       const uint64_t addr = reinterpret_cast<uint64_t>(sel ? base_sel : base_unsel) + (uint64_t)(pc & vmask) * row_bytes;
-      const bf16_t whi = (bf16_t)w;
-      const bf16_t wlo = (bf16_t)(w - (float)whi);
-      const uint32_t wpk = (uint32_t)__builtin_bit_cast(uint16_t, whi) | ((uint32_t)__builtin_bit_cast(uint16_t, wlo) << 16);
+      const uint32_t wpk = pack_weight(w);
       const uint64_t bal = __ballot(keep);
       const int nk = __builtin_amdgcn_readfirstlane(__popcll(bal));
       const int rk = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
@@ -594,21 +745,11 @@ __global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ri
       if (k + U + u < count) consume(u);
     issued = avail;
   }
-  // D layout: element i of lane l is D[m = 4*(l/16) + i][n = l%16]; column = 8m + n%8, halves n<8 / n>=8
   float *rowbuf = reinterpret_cast<float *>(ring);  // every record has been read: the ring's memory is free
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int h = 0; h < NT; ++h)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float v = acc[h][i] + __shfl_xor(acc[h][i], 8);
-      if (!lo_part) rowbuf[h * 128 + (4 * g + i) * 8 + pos] = v;
-    }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the wave's own LDS writes have landed
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  row_to_lds<NT>(acc, rowbuf, lane);
+  lds_written();
   // natural layout again: lane q owns 8 consecutive columns
 #pragma unroll
   for (int r = 0; r < (NT * 16 + 63) / 64; ++r) {
@@ -700,19 +841,19 @@ static int launch_checked(spmm_fn fn, dim3 grid, const SpmmArgs &a, hipStream_t 
 
 int launch_spmm(const SpmmArgs &a_in, int src_dtype, int out_dtype, hipStream_t s) {
   SpmmArgs a = a_in;
-  const int64_t tail_blocks = (a.n_tail + 3) / 4, short_waves = a.n_short;
-  if (a.n_class_blocks + tail_blocks + short_waves <= 0) return hipSuccess;
-  if (mfma_path(a, src_dtype)) {
-    // short rows are served a row per 16-lane group, by extra workgroups of the same launch, when a row fits the registers
-    // of such a group
-    a.n_main_blocks = a.n_class_blocks + tail_blocks + (a.d <= 256 ? 0 : short_waves / 4);
-    const unsigned gx = (unsigned)(a.n_main_blocks + (a.d <= 256 ? (short_waves + 15) / 16 : 0));
-    return launch_checked(out_dtype == DT_BF16 ? ring_for<bf16_t>(a) : ring_for<float>(a), dim3(gx, a.d <= 256 ? 1u : (unsigned)((a.d + 511) / 512)), a, s);
-  }
+  const bool mfma = mfma_path(a, src_dtype);
+  // short rows: 16 to a workgroup where four rows of them fit a wave's registers, else one to a wave like the others
+  const int64_t tail_blocks = (a.n_tail + 3) / 4, short_blocks = mfma && a.d <= 256 ? (a.n_short + 15) / 16 : a.n_short / 4;
+  int64_t gx = a.n_class_blocks + tail_blocks + short_blocks;
+  if (gx <= 0) return hipSuccess;
+  if (gx > 0x7fffffff) return hipErrorInvalidValue;
+  // rounded up: the count of short workgroups comes out exactly (below 2^32 workgroups), and none behind the last one
+  a.mix = short_blocks > 0 ? (((uint64_t)short_blocks << 32) + (uint64_t)(tail_blocks + short_blocks) - 1) / (uint64_t)(tail_blocks + short_blocks) : 0;
+  if (mfma)
+    return launch_checked(out_dtype == DT_BF16 ? ring_for<bf16_t>(a) : ring_for<float>(a), dim3((unsigned)gx, a.d <= 256 ? 1u : (unsigned)((a.d + 511) / 512)), a, s);
   const Shape *best = pick_shape(a, src_dtype, out_dtype);
   if (!best) return hipErrorInvalidValue;
   const int tile_w = best->lpr * best->vec;
-  int64_t gx = a.n_class_blocks + tail_blocks + short_waves / 4;
   const unsigned gy = (unsigned)((a.d + tile_w - 1) / tile_w);
   if (gy > 1) gx = (gx + 7) / 8 * 8;  // every column tile starts on the same XCD (tasks past the end do nothing)
   return launch_checked(best->main, dim3((unsigned)gx, gy), a, s);

@@ -29,7 +29,7 @@ class _Mask(C.Structure):
 class _Spmm(C.Structure):  # SpmmArgs
     _fields_ = [("pidx", P), ("val", P), ("task_row", P), ("task_e0", P), ("task_ne", P), ("task_slot", P), ("cls_begin", I32 * 32), ("cls_end", I32 * 32),
                 ("xcd", (I32 * 4) * 8), ("n_class_blocks", I32), ("tail0", I64), ("n_tail", I64),
-                ("short0", I64), ("n_short", I64), ("n_main_blocks", I64), ("slot_class", P), ("active_classes", U32), ("all_classes_active", I32),
+                ("short0", I64), ("n_short", I64), ("mix", C.c_uint64), ("short_valu", I32), ("slot_class", P), ("active_classes", U32), ("all_classes_active", I32),
                 ("lr_row", P), ("lr_slot0", P), ("lr_nslots", P), ("n_long", I64), ("partial", P), ("slot0", I64), ("lr_dense0", P), ("lr_ndense", P),
                 ("lr_item0", P), ("item_chunks", P), ("dense_partial", P), ("item0", I64), ("drop_unselected", I32), ("src_sel", P), ("src_unsel", P),
                 ("d", I32), ("src_ld", I32), ("vbits", I32), ("many_chunks", I32), ("pass_", P), ("mask", _Mask), ("out", P), ("out_ld", I32), ("out_row0", I64)]
@@ -44,11 +44,13 @@ def _arr(p, n, dtype):
 
 
 def _tasks(a, name, grid):
-    """(task, class) of every wave of a main launch; a short row per 16-lane group behind the main workgroups."""
+    """(task, class) of every wave of a main launch; 16 short rows to a workgroup, or 4, among the others."""
     ring, out = b"ring" in name, []
     for b in range(grid[0]):
-        if ring and a.d <= 256 and b >= a.n_main_blocks:
-            out += [(a.short0 + t, -1) for t in range((b - a.n_main_blocks) * 16, min((b - a.n_main_blocks) * 16 + 16, a.n_short))]
+        p = b - a.n_class_blocks
+        before, upto = p * a.mix >> 32, (p + 1) * a.mix >> 32
+        if ring and a.d <= 256 and p >= 0 and upto > before:
+            out += [(a.short0 + t, -1) for t in range(before * 16, min(before * 16 + 16, a.n_short))]
             continue
         for w in range(4):
             if b < a.n_class_blocks:
@@ -65,11 +67,9 @@ def _tasks(a, name, grid):
                         break
                     g -= ng
                 continue
-            t = (b - a.n_class_blocks) * 4 + w
-            if t < a.n_tail:
-                out.append((a.tail0 + t, -1))
-            elif 0 <= t - (a.n_tail + 3) // 4 * 4 < a.n_short:
-                out.append((a.short0 + t - (a.n_tail + 3) // 4 * 4, -1))
+            t, first, n = (before * 4 + w, a.short0, a.n_short) if upto > before else ((p - before) * 4 + w, a.tail0, a.n_tail)
+            if t < n:
+                out.append((first + t, -1))
     assert len({t for t, _ in out}) == len(out)
     return out
 

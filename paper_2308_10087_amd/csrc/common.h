@@ -279,8 +279,7 @@ struct PassTableArgs {
   uint8_t pos[kMaxChunks];
   uint32_t classes_backward[kMaxChunks], classes_earlier[kMaxChunks];
 };
-static_assert(sizeof(PassTableArgs) <= 4096, "kernel arguments");
-int launch_pass_tables(const PassTableArgs &a, hipStream_t s);
+static_assert(sizeof(PassTableArgs) <= 3072, "kernel arguments");
 
 // ---- dense transforms -------------------------------------------------------------------
 enum GemmEpilogue : int {
@@ -341,6 +340,9 @@ struct GemmTnArgs {
                                   // workgroup per row split computes the whole output (tests force it on small inputs)
 };
 int launch_gemm_tn(const GemmTnArgs &a, int compute_dtype, hipStream_t s);
+// n of them that have the same scratch (partial: partial_floats, bias_partial: bias_floats), as many at a time as it holds and
+// as add to different buffers
+int launch_gemm_tn_list(const GemmTnArgs *a, int n, size_t partial_floats, size_t bias_floats, int compute_dtype, hipStream_t s);
 // dst[o] += sum over the M rows of B[.][o]; partial: fp32 scratch [max_splits][O]
 int launch_colsum_add(const void *B, int dtype, int ldb, int M, int O, float *partial, int max_splits, float *dst,
                       hipStream_t s);
@@ -390,8 +392,16 @@ int launch_copy_rows(const void *src, int src_ld, void *dst, int dst_ld, int64_t
 
 // ---- small kernels ------------------------------------------------------------------------
 // Wt[N][Kp] (transposed) and Wn[K][Np] (plain) zero-padded copies of W[K][N] in the compute dtype
-int launch_stage_weights(const void *W, int w_dtype, int K, int N, void *Wt, int Kp, void *Wn, int Np,
-                         hipStream_t s);
+struct StageWeightsArgs {
+  const void *W;
+  int32_t K, N;
+  void *Wt;
+  int32_t Kp;
+  void *Wn;
+  int32_t Np;
+};
+// n weights in launches of up to kBatch; tables (or NULL): written by a workgroup of the first one
+int launch_stage_weights(const StageWeightsArgs *w, int n, int dtype, const PassTableArgs *tables, hipStream_t s);
 // dY[m][c] = level[m][c] > 0 ? g[m][c] : 0 for c < d, zeros up to out_ld
 // x[r][c] <- survives ? x[r][c] * scale : 0 in place, r < M, c < d (rows of leading dimension ld; dp.u0 = vertex of row 0)
 int launch_dropout_rows(void *x, int dtype, int64_t M, int d, int ld, const LnDropout &dp, hipStream_t s);
@@ -399,6 +409,12 @@ int launch_dropout_rows(void *x, int dtype, int64_t M, int d, int ld, const LnDr
 int launch_relu_mask(const void *g, const void *level, int dtype, int64_t M, int d, void *out, int out_ld, float scale,
                      hipStream_t s);
 int launch_copy(const void *src, void *dst, size_t bytes, hipStream_t s);
+struct CopyArgs {
+  const void *src;
+  void *dst;
+  size_t bytes;
+};
+int launch_copies(const CopyArgs *c, int n, hipStream_t s);  // that do not overlap, in launches of up to kBatch
 int launch_fill_zero(void *dst, size_t bytes, hipStream_t s);
 // symmetric normalisation weights from row lengths: val[e] = 1/sqrt(len(row) * len(other))
 int launch_gcn_norm(const int64_t *ptr, const uint32_t *pidx, int vbits, const int64_t *len_ptr, int64_t n,

@@ -10,6 +10,7 @@
 // A may also be a caller-owned level buffer of any width and of fp32 or bf16 type, in which case
 // it is read element-wise with bounds checks and converted while it is staged into LDS.
 #include <algorithm>
+#include <functional>
 
 #include "common.h"
 
@@ -587,10 +588,20 @@ __device__ __forceinline__ void store_row_pair(uint32_t *dst, const bf16x8 &even
   *reinterpret_cast<u32x4 *>(dst + 4) = hi;
 }
 
+// Products of several layers are planes of one launch (launch_gemm_tn_list).
+struct GemmTnWork {
+  GemmTnArgs a;
+  int32_t rows_per_split, splits;
+};
+static_assert(sizeof(Batch<GemmTnWork>) <= 4096, "kernel arguments");
+
 // PAIR: fp32 A with an even leading dimension and an 8-byte aligned base; a tile row (128 floats) is read by
 // one wave instruction as 64 float pairs.
 template <typename TA, bool VEC, bool PAIR = false>
-__global__ __launch_bounds__(256) void gemm_tn_bf16_kernel(const GemmTnArgs a, int rows_per_split, int splits) {
+__global__ __launch_bounds__(256) void gemm_tn_bf16_kernel(const Batch<GemmTnWork> ba) {
+  const GemmTnWork &work_of = ba.sub[blockIdx.z];
+  const GemmTnArgs a = work_of.a;
+  const int rows_per_split = work_of.rows_per_split, splits = work_of.splits;
   __shared__ __attribute__((aligned(16))) uint32_t As[TR / 2 * LDS_P];
   __shared__ __attribute__((aligned(16))) uint32_t Bs[TR / 2 * LDS_P];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -728,7 +739,10 @@ __global__ __launch_bounds__(256) void gemm_tn_bf16_kernel(const GemmTnArgs a, i
 // only in part through their XCD's L2 (measured on 10 M rows: 16.1 GB fetched for 10.2 GB of operands).  A wave owns
 // 64 rows x 128 columns of the output (eight 32 x 32 accumulators); both operands are bf16 with 16-byte aligned rows.
 constexpr int LDS_PW = 260;  // padded stride, in words, of one row pair of a 256-column LDS tile
-__global__ __launch_bounds__(512) void gemm_tn_bf16_wide_kernel(const GemmTnArgs a, int rows_per_split, int splits) {
+__global__ __launch_bounds__(512) void gemm_tn_bf16_wide_kernel(const Batch<GemmTnWork> ba) {
+  const GemmTnWork &work_of = ba.sub[blockIdx.z];
+  const GemmTnArgs a = work_of.a;
+  const int rows_per_split = work_of.rows_per_split, splits = work_of.splits;
   __shared__ __attribute__((aligned(16))) uint32_t As[TR / 2 * LDS_PW];
   __shared__ __attribute__((aligned(16))) uint32_t Bs[TR / 2 * LDS_PW];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -1076,7 +1090,10 @@ __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const GemmNtArgs a) {
 // 100 x 100 outputs: 24 -> 18 us; the bias gradient (column sums of B) rides along, 17 - 27 us as a kernel of its own
 // before.
 template <int V>
-__global__ __launch_bounds__(256) void gemm_tn_f32_kernel(const GemmTnArgs a, int rows_per_split, int splits) {
+__global__ __launch_bounds__(256) void gemm_tn_f32_kernel(const Batch<GemmTnWork> ba) {
+  const GemmTnWork &work_of = ba.sub[blockIdx.z];
+  const GemmTnArgs a = work_of.a;
+  const int rows_per_split = work_of.rows_per_split, splits = work_of.splits;
   constexpr int T = 16 * V;
   constexpr int D = 4;      // steps of four rows in flight per wave
   constexpr int BLOCK = 8;  // steps of one chain of additions
@@ -1203,18 +1220,32 @@ __global__ __launch_bounds__(256) void gemm_tn_f32_kernel(const GemmTnArgs a, in
 // four phases of splits summed in parallel (8 independent loads in flight each), then combined in LDS.
 // A second sum over the same splits (the bias gradient next to a weight gradient) rides in the same launch:
 // blocks from blocks1 on serve (partial2, count2, dst2) with scale 1.
-__global__ __launch_bounds__(256) void reduce_add_kernel(const float *partial, int splits, size_t count, float scale,
-                                                         float *dst, unsigned blocks1, const float *partial2, size_t count2,
-                                                         float *dst2) {
+struct ReduceAddArgs {
+  const float *partial;
+  int32_t splits;
+  size_t count;
+  float scale;
+  float *dst;
+  uint32_t blocks1, blocks;  // of the first sum, of both
+  const float *partial2;
+  size_t count2;
+  float *dst2;
+};
+__global__ __launch_bounds__(256) void reduce_add_kernel(const Batch<ReduceAddArgs> ba) {
   __shared__ float red[4][64];
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  const ReduceAddArgs &a = ba.sub[blockIdx.z];
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6, splits = a.splits;
+  const float *partial = a.partial;
+  size_t count = a.count;
+  float scale = a.scale, *dst = a.dst;
   unsigned block = blockIdx.x;
-  if (block >= blocks1) {  // whole workgroup
-    block -= blocks1;
-    partial = partial2;
-    count = count2;
+  if (block >= a.blocks) return;
+  if (block >= a.blocks1) {  // whole workgroup
+    block -= a.blocks1;
+    partial = a.partial2;
+    count = a.count2;
     scale = 1.0f;
-    dst = dst2;
+    dst = a.dst2;
   }
   const size_t e = (size_t)block * 64 + tx;
   float s = 0.f;
@@ -1372,8 +1403,14 @@ int launch_gemm_nt(const GemmNtArgs &a_in, int compute_dtype, hipStream_t s) {
   return hipSuccess;
 }
 
-int launch_gemm_tn(const GemmTnArgs &a, int compute_dtype, hipStream_t s) {
-  if (a.M <= 0 || a.I <= 0 || a.O <= 0) return hipSuccess;
+typedef void (*tn_fn)(const Batch<GemmTnWork>);
+struct TnPlan {
+  GemmTnWork w;
+  tn_fn fn;
+  unsigned gx, threads;
+  size_t count() const { return (size_t)w.a.I * w.a.O; }
+};
+static int plan_gemm_tn(const GemmTnArgs &a, int compute_dtype, TnPlan &p) {
   const bool narrow = a.I < 4 || a.O < 4;  // fp32 operands of fewer columns than a 16-byte vector
   const int tile = compute_dtype == DT_BF16 ? 128 : narrow ? 16 : 64;
   const int step = compute_dtype == DT_BF16 ? TR : 16;
@@ -1390,44 +1427,95 @@ int launch_gemm_tn(const GemmTnArgs &a, int compute_dtype, hipStream_t s) {
   }
   if (splits < 1) splits = 1;
   if (splits > a.max_splits) splits = a.max_splits;
-  int rows_per = (a.M + splits - 1) / splits;
-  rows_per = (rows_per + step - 1) / step * step;
-  splits = (a.M + rows_per - 1) / rows_per;
   // long operands with more than one 128 x 128 output tile: one workgroup per row split computes all of the output
   const bool wide = compute_dtype == DT_BF16 && a.a_dtype == DT_BF16 && a.M >= a.wide_min_rows && ti * to > 1 && a.I <= 256 &&
                     a.O <= 256 && vec_ok(a.A, a.lda, 8) && vec_ok(a.B, a.ldb, 8);
+  if (wide) splits = a.max_splits < 256 ? a.max_splits : 256;  // one workgroup per compute unit
+  int rows_per = (a.M + splits - 1) / splits;
+  rows_per = (rows_per + step - 1) / step * step;
+  splits = (a.M + rows_per - 1) / rows_per;
+  p.w = GemmTnWork{a, rows_per, splits};
+  p.threads = wide ? 512 : 256;
   if (wide) {
-    splits = a.max_splits < 256 ? a.max_splits : 256;  // one workgroup per compute unit
-    rows_per = (a.M + splits - 1) / splits;
-    rows_per = (rows_per + step - 1) / step * step;
-    splits = (a.M + rows_per - 1) / rows_per;
-    hipLaunchKernelGGL(gemm_tn_bf16_wide_kernel, dim3((unsigned)splits), dim3(512), 0, s, a, rows_per, splits);
+    p.fn = gemm_tn_bf16_wide_kernel;
+    p.gx = (unsigned)splits;
   } else if (compute_dtype == DT_BF16) {
-    dim3 g1((unsigned)(((splits + 7) / 8) * 8 * ti * to));
-    if (a.a_dtype == DT_F32 && pair_ok(a.A, a.lda))
-      hipLaunchKernelGGL((gemm_tn_bf16_kernel<float, false, true>), g1, dim3(256), 0, s, a, rows_per, splits);
-    else if (a.a_dtype == DT_F32)
-      hipLaunchKernelGGL((gemm_tn_bf16_kernel<float, false>), g1, dim3(256), 0, s, a, rows_per, splits);
-    else if (vec_ok(a.A, a.lda, 8))
-      hipLaunchKernelGGL((gemm_tn_bf16_kernel<bf16_t, true>), g1, dim3(256), 0, s, a, rows_per, splits);
-    else
-      hipLaunchKernelGGL((gemm_tn_bf16_kernel<bf16_t, false>), g1, dim3(256), 0, s, a, rows_per, splits);
+    p.gx = (unsigned)(((splits + 7) / 8) * 8 * ti * to);
+    p.fn = a.a_dtype == DT_F32 ? (pair_ok(a.A, a.lda) ? gemm_tn_bf16_kernel<float, false, true> : gemm_tn_bf16_kernel<float, false>)
+                               : (vec_ok(a.A, a.lda, 8) ? gemm_tn_bf16_kernel<bf16_t, true> : gemm_tn_bf16_kernel<bf16_t, false>);
   } else {
     if (a.a_dtype != DT_F32) return hipErrorInvalidValue;
-    dim3 g1((unsigned)((splits * ti * to + 7) / 8 * 8));
-    if (narrow)
-      hipLaunchKernelGGL(gemm_tn_f32_kernel<1>, g1, dim3(256), 0, s, a, rows_per, splits);
-    else
-      hipLaunchKernelGGL(gemm_tn_f32_kernel<4>, g1, dim3(256), 0, s, a, rows_per, splits);
+    p.gx = (unsigned)((splits * ti * to + 7) / 8 * 8);
+    p.fn = narrow ? gemm_tn_f32_kernel<1> : gemm_tn_f32_kernel<4>;
   }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return (int)e;
-  const size_t count = (size_t)a.I * a.O;
-  const unsigned blocks1 = (unsigned)((count + 63) / 64), blocks2 = a.dbias != nullptr ? (unsigned)((a.O + 63) / 64) : 0u;
-  hipLaunchKernelGGL(reduce_add_kernel, dim3(blocks1 + blocks2), dim3(256), 0, s, a.partial, splits, count, a.scale, a.dW, blocks1,
-                     a.bias_partial, (size_t)a.O, a.dbias);
-  return (int)hipGetLastError();
+  return hipSuccess;
 }
+
+static bool overlap(const float *a, size_t n, const float *b, size_t m) {
+  return a != nullptr && b != nullptr && std::less<const float *>()(a, b + m) && std::less<const float *>()(b, a + n);
+}
+
+// Products of 34 k rows of width 100 take 18 us each and the sums of their splits another 5, a round of latency each; as planes of
+// one launch they fill the chip together.  The splits, and with them every sum, are those of single products.
+int launch_gemm_tn_list(const GemmTnArgs *list, int n, size_t partial_floats, size_t bias_floats, int compute_dtype, hipStream_t s) {
+  TnPlan p[kBatch];
+  int m = 0;
+  size_t used = 0, used_bias = 0;
+  auto flush = [&]() -> int {
+    if (m == 0) return hipSuccess;
+    Batch<GemmTnWork> b{};
+    Batch<ReduceAddArgs> r{};
+    unsigned gx = 0, rx = 0;
+    for (int i = 0; i < m; ++i) {
+      const GemmTnArgs &a = p[i].w.a;
+      b.sub[i] = p[i].w;
+      gx = std::max(gx, p[i].gx);
+      ReduceAddArgs &x = r.sub[i];
+      x.partial = a.partial;
+      x.splits = p[i].w.splits;
+      x.count = p[i].count();
+      x.scale = a.scale;
+      x.dst = a.dW;
+      x.blocks1 = (uint32_t)((x.count + 63) / 64);
+      x.blocks = x.blocks1 + (a.dbias != nullptr ? (uint32_t)((a.O + 63) / 64) : 0u);
+      x.partial2 = a.bias_partial;
+      x.count2 = (size_t)a.O;
+      x.dst2 = a.dbias;
+      rx = std::max(rx, x.blocks);
+    }
+    const unsigned planes = (unsigned)m;
+    m = 0;
+    used = used_bias = 0;
+    hipLaunchKernelGGL(p[0].fn, dim3(gx, 1, planes), dim3(p[0].threads), 0, s, b);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
+    hipLaunchKernelGGL(reduce_add_kernel, dim3(rx, 1, planes), dim3(256), 0, s, r);
+    return (int)hipGetLastError();
+  };
+  for (int i = 0; i < n; ++i) {
+    const GemmTnArgs &a = list[i];
+    if (a.M <= 0 || a.I <= 0 || a.O <= 0) continue;
+    TnPlan q;
+    int rc = plan_gemm_tn(a, compute_dtype, q);
+    if (rc != 0) return rc;
+    const size_t floats = (size_t)q.w.splits * q.count(), bias = a.bias_partial != nullptr ? (size_t)q.w.splits * a.O : 0;
+    bool close = m == kBatch || (m > 0 && (q.fn != p[0].fn || used + floats > partial_floats || used_bias + bias > bias_floats));
+    for (int k = 0; k < m && !close; ++k) {  // sums are added without atomics: a buffer once per launch
+      const GemmTnArgs &o = p[k].w.a;
+      close = overlap(a.dW, q.count(), o.dW, p[k].count()) || overlap(a.dbias, (size_t)a.O, o.dbias, (size_t)o.O) ||
+              overlap(a.dW, q.count(), o.dbias, (size_t)o.O) || overlap(a.dbias, (size_t)a.O, o.dW, p[k].count());
+    }
+    if (close && (rc = flush()) != 0) return rc;
+    q.w.a.partial += used;
+    if (a.bias_partial != nullptr) q.w.a.bias_partial += used_bias;
+    used += floats;
+    used_bias += bias;
+    p[m++] = q;
+  }
+  return flush();
+}
+
+int launch_gemm_tn(const GemmTnArgs &a, int compute_dtype, hipStream_t s) { return launch_gemm_tn_list(&a, 1, 0, 0, compute_dtype, s); }
 
 int launch_colsum_add(const void *B, int dtype, int ldb, int M, int O, float *partial, int max_splits, float *dst,
                       hipStream_t s) {
@@ -1446,7 +1534,9 @@ int launch_colsum_add(const void *B, int dtype, int ldb, int M, int O, float *pa
     hipLaunchKernelGGL(colsum_kernel<float>, grid, dim3(256), 0, s, static_cast<const float *>(B), ldb, M, O, rows_per, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return (int)e;
-  hipLaunchKernelGGL(reduce_add_kernel, dim3((unsigned)((O + 63) / 64)), dim3(256), 0, s, partial, splits, (size_t)O, 1.0f, dst,
-                     (unsigned)((O + 63) / 64), static_cast<const float *>(nullptr), (size_t)0, static_cast<float *>(nullptr));
+  Batch<ReduceAddArgs> r{};
+  const uint32_t blocks = (uint32_t)((O + 63) / 64);
+  r.sub[0] = ReduceAddArgs{partial, splits, (size_t)O, 1.0f, dst, blocks, blocks, nullptr, 0, nullptr};
+  hipLaunchKernelGGL(reduce_add_kernel, dim3(blocks), dim3(256), 0, s, r);
   return (int)hipGetLastError();
 }

@@ -379,7 +379,7 @@ struct Layout {
   size_t self_fwd = 0, self_bwd = 0;      // GraphSage: h_v W_self (fp32), dY W_self^T where it can't wait in the output rows
   size_t ln_partial = 0;                  // ResGCN+: parameter-gradient scratch
   size_t G[2];
-  size_t gemm_partial, bias_partial;
+  size_t gemm_partial, bias_partial, gemm_partial_floats, bias_partial_floats;
   size_t total;
 };
 
@@ -648,8 +648,10 @@ Layout layout_for(const Shape &s, const HostDir &hf, const HostDir &hb, bool ran
   }
   l.G[0] = w.take(l.row_stride * elt);
   l.G[1] = w.take(s.defer_wgrad() ? 0 : l.row_stride * elt);
-  l.gemm_partial = w.take(sizeof(float) * kMaxSplits * max_io);
-  l.bias_partial = w.take(sizeof(float) * kMaxSplits * max_d);
+  l.gemm_partial_floats = (size_t)kMaxSplits * max_io;
+  l.bias_partial_floats = (size_t)kMaxSplits * max_d;
+  l.gemm_partial = w.take(sizeof(float) * l.gemm_partial_floats);
+  l.bias_partial = w.take(sizeof(float) * l.bias_partial_floats);
   l.total = w.off;
   return l;
 }
@@ -915,12 +917,11 @@ void assign_xcds(const gnnstage *st, const DirTasks &t, int c0, int c1, Select s
   a.n_class_blocks = 8 * most;
 }
 
-// Writes the tables of a pass over all chunks in st->order (begin: the order of a pass that is just starting), once.
-int write_pass_tables(gnnstage *st, const std::vector<int32_t> &order, hipStream_t stream) {
-  if (st->tables_written || !by_table(st)) return GNNSTAGE_OK;
+// What launch_stage_weights needs for the tables of a pass over all chunks in this order.
+void plan_pass_tables(gnnstage *st, const std::vector<int32_t> &order, PassTableArgs &a) {
   const Shape &s = st->s;
   const DirTasks &t = st->tasks[1];
-  PassTableArgs a{};
+  a = PassTableArgs{};
   a.K = s.K;
   PassChunk *p = st->at<PassChunk>(st->lay.pass_tables);
   a.forward = p;
@@ -938,7 +939,13 @@ int write_pass_tables(gnnstage *st, const std::vector<int32_t> &order, hipStream
       if (sum[1] > 0) a.classes_earlier[r] |= 1u << q;
     }
   }
-  HIP_TRY(st, launch_pass_tables(a, stream));
+}
+// The tables of the present pass, where they have not been written with its weights.
+int write_pass_tables(gnnstage *st, const std::vector<int32_t> &order, hipStream_t stream) {
+  if (st->tables_written || !by_table(st)) return GNNSTAGE_OK;
+  PassTableArgs a;
+  plan_pass_tables(st, order, a);
+  HIP_TRY(st, launch_stage_weights(nullptr, 0, st->cdtype(), &a, stream));
   st->tables_written = true;
   return GNNSTAGE_OK;
 }
@@ -1141,7 +1148,7 @@ int ln_backward(gnnstage *st, LnSums &sums, const std::vector<void *> &level, in
 
 // What a pass needs before its first chunk: staged weights; ResGCN+: Rh = f(hist[j]), the activated historical rows; the
 // transformed historical rows of transform-first layers (constants of the pass).
-int begin_forward(gnnstage *st, hipStream_t stream) {
+int begin_forward(gnnstage *st, const std::vector<int32_t> *order, hipStream_t stream) {
   const Shape &s = st->s;
   const int cd = st->cdtype();
   st->order.clear();
@@ -1154,15 +1161,19 @@ int begin_forward(gnnstage *st, hipStream_t stream) {
   st->dropout_seed = st->next_dropout_seed;
   {
     Timed t(st, stream, 6);
+    std::vector<StageWeightsArgs> w;
     for (int j = 0; j < s.L; ++j) {
       // GraphSage: W[j] = [W_self ; W_neigh]; Wt / Wn take the half that multiplies the aggregation
       const char *Wagg = static_cast<const char *>(st->W[j]) + (s.sage() ? s.w_half(j) * s.elt() : 0);
-      HIP_TRY(st, launch_stage_weights(Wagg, cd, s.dims[j], s.dims[j + 1], st->at<char>(st->lay.Wt[j]), s.ld[j],
-                                       st->at<char>(st->lay.Wn[j]), s.ld[j + 1], stream));
+      w.push_back(StageWeightsArgs{Wagg, s.dims[j], s.dims[j + 1], st->at<char>(st->lay.Wt[j]), s.ld[j], st->at<char>(st->lay.Wn[j]), s.ld[j + 1]});
       if (s.sage())
-        HIP_TRY(st, launch_stage_weights(st->W[j], cd, s.dims[j], s.dims[j + 1], st->at<char>(st->lay.Wt_self[j]), s.ld[j],
-                                         st->at<char>(st->lay.Wn_self[j]), s.ld[j + 1], stream));
+        w.push_back(StageWeightsArgs{st->W[j], s.dims[j], s.dims[j + 1], st->at<char>(st->lay.Wt_self[j]), s.ld[j], st->at<char>(st->lay.Wn_self[j]), s.ld[j + 1]});
     }
+    PassTableArgs tables;
+    const bool with_tables = order != nullptr && by_table(st);
+    if (with_tables) plan_pass_tables(st, *order, tables);
+    HIP_TRY(st, launch_stage_weights(w.data(), (int)w.size(), cd, with_tables ? &tables : nullptr, stream));
+    st->tables_written = with_tables;
   }
   for (int j = 0; j < s.L; ++j) {
     if (s.res()) {
@@ -1279,11 +1290,10 @@ int forward_layer(gnnstage *st, int j, const Span &sp, hipStream_t stream) {
   return GNNSTAGE_OK;
 }
 
-// dW_j += scale * Z_j^T dY (and the bias gradient) over rows [r0, r0 + M) of an aggregate-first layer
-int wgrad_rows(gnnstage *st, int j, int64_t r0, int64_t M, const char *dY, hipStream_t stream) {
+// dW_j += scale * Z_j^T dY (and the bias gradient) over rows [r0, r0 + M) of an aggregate-first layer: the products of it
+void wgrad_products(gnnstage *st, int j, int64_t r0, int64_t M, const char *dY, std::vector<GemmTnArgs> &out) {
   const Shape &s = st->s;
   const int cd = st->cdtype();
-  Timed t(st, stream, 4, j);
   GemmTnArgs w = tn_args(st, st->at<char>(st->lay.Z[j]) + (size_t)r0 * s.ld[j] * s.elt(), cd, s.ld[j], dY, s.ld[j + 1], M, s.dims[j], s.dims[j + 1],
                          s.variant == GNNSTAGE_GCNII ? st->beta[j] : 1.f,
                          st->dW[j] + (s.sage() ? s.w_half(j) : 0));  // GraphSage: W_neigh is the lower half
@@ -1291,11 +1301,19 @@ int wgrad_rows(gnnstage *st, int j, int64_t r0, int64_t M, const char *dY, hipSt
     w.dbias = st->dbias[j];
     w.bias_partial = st->at<float>(st->lay.bias_partial);
   }
-  HIP_TRY(st, launch_gemm_tn(w, cd, stream));
+  out.push_back(w);
   if (s.sage())  // dW_self += h_v^T dY over the rows' own (current) level-j values
-    HIP_TRY(st, launch_gemm_tn(tn_args(st, level_rows(st, st->cur, j, r0), st->level_dtype(j), s.dims[j], dY, s.ld[j + 1], M, s.dims[j], s.dims[j + 1], 1.f, st->dW[j]),
-                               cd, stream));
+    out.push_back(tn_args(st, level_rows(st, st->cur, j, r0), st->level_dtype(j), s.dims[j], dY, s.ld[j + 1], M, s.dims[j], s.dims[j + 1], 1.f, st->dW[j]));
+}
+int run_products(gnnstage *st, const std::vector<GemmTnArgs> &w, int layer, hipStream_t stream) {
+  Timed t(st, stream, 4, layer);
+  HIP_TRY(st, launch_gemm_tn_list(w.data(), (int)w.size(), st->lay.gemm_partial_floats, st->lay.bias_partial_floats, st->cdtype(), stream));
   return GNNSTAGE_OK;
+}
+int wgrad_rows(gnnstage *st, int j, int64_t r0, int64_t M, const char *dY, hipStream_t stream) {
+  std::vector<GemmTnArgs> w;
+  wgrad_products(st, j, r0, M, dY, w);
+  return run_products(st, w, j, stream);
 }
 
 // Weight (and bias) gradients of the aggregate-first layers that the backward calls made so far still owe:
@@ -1317,11 +1335,17 @@ int flush_deferred_wgrad(gnnstage *st, hipStream_t stream) {
     c = c1;
     if (M <= 0) continue;
     if (M > 0x7fffffff) return fail(st, GNNSTAGE_ENOTSUP, "more than 2^31 - 1 rows in one weight-gradient product");
+    std::vector<GemmTnArgs> w;
     for (int j = s.L - 1; j >= 0; --j) {
       if (s.tf[j]) continue;  // transform-first layers: finish_transform_first
-      const int rc = wgrad_rows(st, j, r0, M, st->at<char>(st->lay.dY[j]) + (size_t)r0 * s.ld[j + 1] * celt, stream);
+      wgrad_products(st, j, r0, M, st->at<char>(st->lay.dY[j]) + (size_t)r0 * s.ld[j + 1] * celt, w);
+      if (st->prof.kinds == 0) continue;  // (a timed launch belongs to one layer)
+      const int rc = run_products(st, w, j, stream);
       if (rc != GNNSTAGE_OK) return rc;
+      w.clear();
     }
+    const int rc = w.empty() ? (int)GNNSTAGE_OK : run_products(st, w, -1, stream);
+    if (rc != GNNSTAGE_OK) return rc;
   }
   return GNNSTAGE_OK;
 }
@@ -2059,7 +2083,7 @@ extern "C" int stage_forward_chunk(gnnstage_t *st, int32_t k, int32_t pos, void 
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   if (k < 0 || k >= s.K) return fail(st, GNNSTAGE_ERANGE, "chunk id out of range");
   if (pos == 0) {  // a new pass: V_processed <- empty
-    const int rc = begin_forward(st, stream);
+    const int rc = begin_forward(st, nullptr, stream);
     if (rc != GNNSTAGE_OK) return rc;
   }
   if (pos != (int32_t)st->order.size()) return fail(st, GNNSTAGE_EORDER, "pos_in_pass does not continue the current pass");
@@ -2087,9 +2111,8 @@ extern "C" int gnnstage_forward_pass(gnnstage_t *st, const int32_t *order, int32
   }
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   std::vector<int32_t> ks(order, order + n_order);
-  int rc = begin_forward(st, stream);
+  int rc = begin_forward(st, &ks, stream);
   if (rc != GNNSTAGE_OK) return rc;
-  rc = write_pass_tables(st, ks, stream);
   for (int j = 0; j < st->s.L && rc == GNNSTAGE_OK; ++j) rc = forward_layer(st, j, whole_span(st), stream);
   if (rc != GNNSTAGE_OK) return rc;
   // only now: a pass that failed half-way is none to run backward or to refresh the history from
@@ -2167,9 +2190,21 @@ extern "C" int update_history(gnnstage_t *st, void *hip_stream) try {
   if (st->cur_stale)
     return fail(st, GNNSTAGE_EORDER, "the current levels hold stale rows until a complete pass follows gnnstage_update_history_swap");
   Timed t(st, stream, 5);
-  for (int j = 0; j < s.L; ++j) {
-    if (st->hist[j] == st->cur[j]) continue;
-    HIP_TRY(st, launch_copy(st->cur[j], st->hist[j], (size_t)s.n * s.dims[j] * st->level_elt(j), stream));
+  std::vector<CopyArgs> c;
+  for (int j = 0; j < s.L; ++j)
+    if (st->hist[j] != st->cur[j]) c.push_back(CopyArgs{st->cur[j], st->hist[j], (size_t)s.n * s.dims[j] * st->level_elt(j)});
+  // in one launch, unless a level's buffer is part of another's
+  bool apart = true;
+  for (size_t i = 0; i < c.size(); ++i)
+    for (size_t k = 0; k < c.size(); ++k) {
+      const char *dst = static_cast<const char *>(c[i].dst), *src = static_cast<const char *>(c[k].src), *other = static_cast<const char *>(c[k].dst);
+      if (dst < src + c[k].bytes && src < dst + c[i].bytes) apart = false;
+      if (i != k && dst < other + c[k].bytes && other < dst + c[i].bytes) apart = false;
+    }
+  if (apart) {
+    HIP_TRY(st, launch_copies(c.data(), (int)c.size(), stream));
+  } else {
+    for (const CopyArgs &x : c) HIP_TRY(st, launch_copies(&x, 1, stream));
   }
   return GNNSTAGE_OK;
 }

@@ -16,17 +16,70 @@ __device__ inline float from_f32<float>(float x) { return x; }
 template <>
 __device__ inline bf16_t from_f32<bf16_t>(float x) { return (bf16_t)x; }
 
-// Wt[n][k] = W[k][n] (k < K, else 0; row stride Kp) and Wn[k][n] = W[k][n] (n < N, else 0; row stride Np)
-template <typename Tw, typename Tc>
-__global__ __launch_bounds__(256) void stage_weights_kernel(const Tw *W, int K, int N, Tc *Wt, int Kp, Tc *Wn, int Np) {
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  if (idx < N * Kp) {
-    const int n = idx / Kp, k = idx % Kp;
-    Wt[idx] = from_f32<Tc>(k < K ? to_f32(W[(size_t)k * N + n]) : 0.f);
+// Row chunk c's entries of a pass's tables; pos: places of the chunks in the forward order, in LDS.
+__device__ inline void write_pass_chunk(const PassTableArgs &a, const int *pos, int c) {
+  PassChunk f{}, b{}, e{};
+  const int p = pos[c];
+  for (int k = 0; k < a.K; ++k) {
+    const uint64_t bit = 1ull << (k & 63);
+    const int pk = pos[k];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (k >> 6 != i) continue;
+      f.mask.w[i] |= pk <= p ? bit : 0;
+      b.mask.w[i] |= pk >= p ? bit : 0;
+      e.mask.w[i] |= pk < p ? bit : 0;
+    }
   }
-  if (idx < K * Np) {
-    const int k = idx / Np, n = idx % Np;
-    Wn[idx] = from_f32<Tc>(n < N ? to_f32(W[(size_t)k * N + n]) : 0.f);
+  f.classes = 0xffffffffu;
+  b.classes = a.classes_backward[c];
+  e.classes = a.classes_earlier[c];
+  a.forward[c] = f;
+  a.backward[c] = b;
+  a.earlier[c] = e;
+}
+
+// Wt[n][k] = W[k][n] (k < K, else 0; row stride Kp) and Wn[k][n] = W[k][n] (n < N, else 0; row stride Np), a 32 x 32 tile of one
+// weight (plane of the grid) per workgroup, turned in LDS; the plane behind the weights writes a pass's tables.  What a pass
+// needs before its first layer is one launch: 5 launches of 2.3 - 2.9 us for four 64 x 64 weights and the tables, 4 of 10 us for
+// 1000 x 1000 (strided reads).
+struct StageArgs {
+  StageWeightsArgs w[kBatch];
+  int32_t n;
+  PassTableArgs tables;
+};
+static_assert(sizeof(StageArgs) <= 4096 && kMaxChunks == 256, "kernel arguments; a thread per chunk");
+template <typename T>
+__global__ __launch_bounds__(256) void stage_weights_kernel(const StageArgs a) {
+  __shared__ T tile[32][33];
+  __shared__ int pos[kMaxChunks];
+  if ((int)blockIdx.y >= a.n) {
+    if (blockIdx.x > 0) return;
+    const int c = threadIdx.x;
+    pos[c] = c < a.tables.K ? a.tables.pos[c] : 0;
+    __syncthreads();
+    if (c < a.tables.K) write_pass_chunk(a.tables, pos, c);
+    return;
+  }
+  const StageWeightsArgs w = a.w[blockIdx.y];
+  const int tk = (max(w.K, w.Kp) + 31) / 32, tn = (max(w.N, w.Np) + 31) / 32;
+  if ((int)blockIdx.x >= tk * tn) return;
+  const int k0 = (int)blockIdx.x / tn * 32, n0 = (int)blockIdx.x % tn * 32;
+  const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+  const T *W = static_cast<const T *>(w.W);
+  T *Wt = static_cast<T *>(w.Wt), *Wn = static_cast<T *>(w.Wn);
+#pragma unroll
+  for (int i = 0; i < 32; i += 8) {
+    const int k = k0 + y + i, n = n0 + x;
+    const T v = k < w.K && n < w.N ? W[(size_t)k * w.N + n] : from_f32<T>(0.f);
+    if (k < w.K && n < w.Np) Wn[(size_t)k * w.Np + n] = v;
+    tile[y + i][x] = v;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 32; i += 8) {
+    const int n = n0 + y + i, k = k0 + x;
+    if (n < w.N && k < w.Kp) Wt[(size_t)n * w.Kp + k] = tile[x][y + i];
   }
 }
 
@@ -92,8 +145,18 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // again soon and need not displace anything in the caches.  Measured against other forms on a 5 GB buffer (read +
 // written per second): grid-stride over 4,096 workgroups 4.6 - 4.8 TB/s, over 65,536 workgroups 5.3 TB/s, this form
 // 5.4 TB/s, a device-to-device hipMemcpyAsync 4.3 TB/s, a read-only pass 5.3 - 5.7 TB/s, a write-only pass 5.1 TB/s.
-__global__ __launch_bounds__(256) void copy_kernel(const u32x4 *src, u32x4 *dst, size_t n16, size_t seg, const uint8_t *tsrc,
-                                                   uint8_t *tdst, int tail) {
+// Several copies that do not overlap are planes of one launch.
+struct CopyPlane {
+  const u32x4 *src;
+  u32x4 *dst;
+  size_t n16, seg;
+  int32_t tail;
+};
+__global__ __launch_bounds__(256) void copy_kernel(const Batch<CopyPlane> ba) {
+  const CopyPlane a = ba.sub[blockIdx.y];
+  const u32x4 *src = a.src;
+  u32x4 *dst = a.dst;
+  const size_t n16 = a.n16, seg = a.seg;
   const size_t nseg = (n16 + seg - 1) / seg;
   for (size_t sg = blockIdx.x; sg < nseg; sg += gridDim.x) {
     const size_t b = sg * seg, e = b + seg < n16 ? b + seg : n16;
@@ -107,7 +170,8 @@ __global__ __launch_bounds__(256) void copy_kernel(const u32x4 *src, u32x4 *dst,
     }
     for (; i < e; i += 256) __builtin_nontemporal_store(__builtin_nontemporal_load(src + i), dst + i);
   }
-  if (blockIdx.x == 0 && (int)threadIdx.x < tail) tdst[threadIdx.x] = tsrc[threadIdx.x];
+  if (blockIdx.x == 0 && (int)threadIdx.x < a.tail)
+    reinterpret_cast<uint8_t *>(dst + n16)[threadIdx.x] = reinterpret_cast<const uint8_t *>(src + n16)[threadIdx.x];
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(u32x4 *dst, size_t n16, uint8_t *tdst, int tail) {
@@ -133,51 +197,25 @@ __global__ __launch_bounds__(256) void gcn_norm_kernel(const int64_t *ptr, const
   }
 }
 
-// One workgroup; thread c writes the entries of row chunk c.
-__global__ __launch_bounds__(kMaxChunks) void pass_tables_kernel(const PassTableArgs a) {
-  __shared__ int pos[kMaxChunks];
-  const int c = threadIdx.x;
-  const int p = c < a.K ? a.pos[c] : 0;
-  pos[c] = p;
-  __syncthreads();
-  if (c >= a.K) return;
-  PassChunk f{}, b{}, e{};
-  for (int k = 0; k < a.K; ++k) {
-    const uint64_t bit = 1ull << (k & 63);
-    const int pk = pos[k];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (k >> 6 != i) continue;
-      f.mask.w[i] |= pk <= p ? bit : 0;
-      b.mask.w[i] |= pk >= p ? bit : 0;
-      e.mask.w[i] |= pk < p ? bit : 0;
-    }
-  }
-  f.classes = 0xffffffffu;
-  b.classes = a.classes_backward[c];
-  e.classes = a.classes_earlier[c];
-  a.forward[c] = f;
-  a.backward[c] = b;
-  a.earlier[c] = e;
-}
-
 }  // namespace
 
-int launch_pass_tables(const PassTableArgs &a, hipStream_t s) {
-  hipLaunchKernelGGL(pass_tables_kernel, dim3(1), dim3(kMaxChunks), 0, s, a);
-  return (int)hipGetLastError();
-}
-
-int launch_stage_weights(const void *W, int w_dtype, int K, int N, void *Wt, int Kp, void *Wn, int Np, hipStream_t s) {
-  const int total = (N * Kp > K * Np) ? N * Kp : K * Np;
-  dim3 grid((total + 255) / 256);
-  if (w_dtype == DT_BF16)
-    hipLaunchKernelGGL((stage_weights_kernel<bf16_t, bf16_t>), grid, dim3(256), 0, s, static_cast<const bf16_t *>(W), K, N,
-                       static_cast<bf16_t *>(Wt), Kp, static_cast<bf16_t *>(Wn), Np);
-  else
-    hipLaunchKernelGGL((stage_weights_kernel<float, float>), grid, dim3(256), 0, s, static_cast<const float *>(W), K, N,
-                       static_cast<float *>(Wt), Kp, static_cast<float *>(Wn), Np);
-  return (int)hipGetLastError();
+int launch_stage_weights(const StageWeightsArgs *w, int n, int dtype, const PassTableArgs *tables, hipStream_t s) {
+  for (int i0 = 0; i0 < n || tables != nullptr; i0 += kBatch) {
+    StageArgs a{};
+    a.n = std::max(0, std::min(kBatch, n - i0));
+    unsigned gx = 1;
+    for (int i = 0; i < a.n; ++i) {
+      a.w[i] = w[i0 + i];
+      gx = std::max(gx, (unsigned)((std::max(a.w[i].K, a.w[i].Kp) + 31) / 32 * ((std::max(a.w[i].N, a.w[i].Np) + 31) / 32)));
+    }
+    const unsigned gy = (unsigned)a.n + (tables != nullptr ? 1u : 0u);
+    if (tables != nullptr) a.tables = *tables;
+    tables = nullptr;
+    hipLaunchKernelGGL(dtype == DT_BF16 ? stage_weights_kernel<bf16_t> : stage_weights_kernel<float>, dim3(gx, gy), dim3(256), 0, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
+  }
+  return hipSuccess;
 }
 
 int launch_dropout_rows(void *x, int dtype, int64_t M, int d, int ld, const LnDropout &dp, hipStream_t s) {
@@ -315,19 +353,30 @@ extern "C" int gnnstage_debug_gather_rate(const void *table, int64_t n_rows, int
   return 0;
 }
 
+int launch_copies(const CopyArgs *c, int n, hipStream_t s) {
+  for (int i0 = 0; i0 < n; i0 += kBatch) {
+    Batch<CopyPlane> b{};
+    unsigned grid = 0, m = 0;
+    for (int i = i0; i < std::min(n, i0 + kBatch); ++i) {
+      if (c[i].bytes == 0) continue;
+      const size_t n16 = c[i].bytes / 16;
+      // segment length in 16-byte words: a 2,048th of the buffer, in steps of 16 KB, between 16 KB and 256 KB
+      size_t seg = ((n16 / 2048 + 1023) / 1024) * 1024;
+      seg = seg < 1024 ? 1024 : seg > 16384 ? 16384 : seg;
+      const size_t nseg = (n16 + seg - 1) / seg;
+      b.sub[m++] = CopyPlane{static_cast<const u32x4 *>(c[i].src), static_cast<u32x4 *>(c[i].dst), n16, seg, (int32_t)(c[i].bytes % 16)};
+      grid = std::max(grid, (unsigned)(nseg < 1 ? 1 : nseg > 2048 ? 2048 : nseg));
+    }
+    if (m == 0) continue;
+    hipLaunchKernelGGL(copy_kernel, dim3(grid, m), dim3(256), 0, s, b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
+  }
+  return hipSuccess;
+}
 int launch_copy(const void *src, void *dst, size_t bytes, hipStream_t s) {
-  if (bytes == 0) return hipSuccess;
-  const size_t n16 = bytes / 16;
-  const int tail = (int)(bytes % 16);
-  // segment length in 16-byte words: a 2,048th of the buffer, in steps of 16 KB, between 16 KB and 256 KB
-  size_t seg = ((n16 / 2048 + 1023) / 1024) * 1024;
-  seg = seg < 1024 ? 1024 : seg > 16384 ? 16384 : seg;
-  const size_t nseg = (n16 + seg - 1) / seg;
-  const unsigned grid = (unsigned)(nseg < 1 ? 1 : nseg > 2048 ? 2048 : nseg);
-  hipLaunchKernelGGL(copy_kernel, dim3(grid), dim3(256), 0, s, static_cast<const u32x4 *>(src),
-                     static_cast<u32x4 *>(dst), n16, seg, static_cast<const uint8_t *>(src) + n16 * 16,
-                     static_cast<uint8_t *>(dst) + n16 * 16, tail);
-  return (int)hipGetLastError();
+  const CopyArgs c{src, dst, bytes};
+  return launch_copies(&c, 1, s);
 }
 
 int launch_fill_zero(void *dst, size_t bytes, hipStream_t s) {

@@ -497,7 +497,8 @@ extern "C" int gnntrain_epoch(gnntrain_t *tr, int64_t epoch, float *loss, void *
 
   for (const gnntrain_param &p : tr->params) TRAIN_HIP(tr, launch_fill_zero(p.grad, sizeof(float) * (size_t)p.count, stream));
   // the head's weights, staged like a layer's: transposed for the logits, plain for the input gradient
-  TRAIN_HIP(tr, launch_stage_weights(tr->head_W, cd, x.d_top, x.C, tr->at<char>(lay.Wt), x.Kp, tr->at<char>(lay.Wn), x.Cp, stream));
+  const StageWeightsArgs head{tr->head_W, x.d_top, x.C, tr->at<char>(lay.Wt), x.Kp, tr->at<char>(lay.Wn), x.Cp};
+  TRAIN_HIP(tr, launch_stage_weights(&head, 1, cd, nullptr, stream));
 
   char *dlogits = tr->at<char>(lay.dlogits);
   float *row_loss = tr->at<float>(lay.row_loss);

@@ -14,6 +14,6 @@ int hipLaunchKernel(const void *f, grid_t grid, grid_t block, void **args, size_
   if (rc != 0) return rc;
   if (at >= cap_operands) operands = realloc(operands, (cap_operands = at + 256) * sizeof *operands);
   if (strstr(list[at].name, "spmm") && !strstr(list[at].name, "dense")) memcpy(operands[at], args[0], spmm_bytes);
-  if (strstr(list[at].name, "pass_tables")) memcpy(operands[at], args[0], table_bytes);
+  if (strstr(list[at].name, "stage_weights")) memcpy(operands[at], args[0], table_bytes);
   return 0;
 }

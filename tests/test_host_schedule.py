@@ -39,6 +39,10 @@ class _Tables(C.Structure):  # PassTableArgs
     _fields_ = [("forward", P), ("backward", P), ("earlier", P), ("K", I32), ("pos", C.c_uint8 * 256), ("classes_backward", U32 * 256), ("classes_earlier", U32 * 256)]
 
 
+class _Begin(C.Structure):  # StageArgs: weights to stage (planes of the grid), and the tables in a plane of their own
+    _fields_ = [("w", C.c_uint8 * 48 * 8), ("n", I32), ("tables", _Tables)]
+
+
 def _arr(p, n, dtype):
     return np.frombuffer((C.c_char * (int(n) * np.dtype(dtype).itemsize)).from_address(p), dtype=dtype, count=int(n)) if n else np.zeros(0, dtype)
 
@@ -84,8 +88,12 @@ def _walk(rt, first, index, chunk_ptr, order):
     tables = main = None
     for i in range(first, rt.host_launches()):
         l = rt.host_launch(i).contents
-        if b"pass_tables" in l.name:
-            tables = _Tables.from_buffer_copy(C.string_at(rt.host_operands(i), C.sizeof(_Tables)))
+        if b"stage_weights" in l.name:
+            begin = _Begin.from_buffer_copy(C.string_at(rt.host_operands(i), C.sizeof(_Begin)))
+            if l.grid[1] == begin.n:
+                continue
+            assert l.grid[1] == begin.n + 1
+            tables = begin.tables
             assert list(tables.pos[:K]) == list(pos)
         if b"spmm" not in l.name or b"dense" in l.name:
             continue
@@ -213,7 +221,7 @@ if __name__ == "__main__":
     _rt.host_launch.restype, _rt.host_launch.argtypes = C.POINTER(_H._Launch), [C.c_size_t]
     _rt.host_operands.restype, _rt.host_operands.argtypes = C.c_void_p, [C.c_size_t]
     _rt.host_operand_bytes.argtypes = [C.c_size_t, C.c_size_t]
-    _rt.host_operand_bytes(C.sizeof(_Spmm), C.sizeof(_Tables))
+    _rt.host_operand_bytes(C.sizeof(_Spmm), C.sizeof(_Begin))
     _rt.host_clear.argtypes = [C.c_int64]
     sys.path.insert(0, os.path.dirname(HERE))
     print(json.dumps(_pass(_rt, *json.loads(sys.argv[2]))))

@@ -22,6 +22,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));  // of a row that is only known to be 4-byte aligned
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
+typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -383,8 +384,13 @@ __global__ __launch_bounds__(256) void gemm_nt_bf16_kernel(const GemmNtArgs a) {
 // multiplied and stored.  WN = column panels per workgroup (4: N <= 256 with 64-row tiles, 2: N <= 128
 // with 128-row tiles); KS = number of 16-wide k-steps held (Kp <= 16 * KS).
 // Taken from 64 k rows on; below that the tiled kernel is as fast or faster.
-// GCNF: the instance for the GCN forward epilogue (bias + ReLU applied to the accumulators, see below).
-template <int WN, int KS, bool GCNF>
+// MODE: an instance per epilogue that has a form of its own.  WS_GCN: bias + ReLU on the accumulators, see below.  WS_GCNII,
+// WS_GCNII_BACK: the identity mapping's other operand is the row that was multiplied, which is in LDS already (its second read from
+// memory, behind the products, was a round trip per piece); the rows of the initial residual's gradient are asked for before
+// the products (half of them, the others behind: registers).  169 k rows of width 256: forward 67 -> 50 us, backward, with 347 MB of
+// fp32 read and written, 147 -> 110 us.
+enum WsMode { WS_ANY, WS_GCN, WS_GCNII, WS_GCNII_BACK };
+template <int WN, int KS, int MODE>
 __global__ __launch_bounds__(256, 2) void gemm_nt_bf16_ws_kernel(const GemmNtArgs a) {
   const int blocks = (int)gridDim.x;
   constexpr int WR = 4 / WN, TM = 64 * WR;  // row groups, rows per tile
@@ -420,7 +426,7 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_bf16_ws_kernel(const GemmNtArg
   // the patch cost a dependent load per piece: 11.2 against 9.5 ms per c4 step for the forward products.
   // An instance of its own, so that the other epilogues do not carry its registers (with one kernel for both, the plain
   // input-gradient products went from 7.0 to 7.5 ms per c4 step).
-  constexpr bool gcn_fwd = GCNF;
+  constexpr bool gcn_fwd = MODE == WS_GCN;
   float bias_col[2] = {0.f, 0.f};
   if constexpr (gcn_fwd) {
 #pragma unroll
@@ -472,6 +478,18 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_bf16_ws_kernel(const GemmNtArg
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
+        f32x4 h0[MODE == WS_GCNII_BACK ? 4 : 1];
+        auto ask_h0 = [&](int hf) {
+          if constexpr (MODE == WS_GCNII_BACK) {
+            const int m = m_wave + i * 32 + 16 * hf + (lane >> 2), n = n_wave + j * 32 + (lane & 3) * 8;
+            if (a.h0grad != nullptr && m < a.M && n < a.N) {
+              const f32x4 *p = reinterpret_cast<const f32x4 *>(a.h0grad + (size_t)m * a.h0_ld + n);
+              h0[2 * hf] = p[0];
+              h0[2 * hf + 1] = p[1];
+            }
+          }
+        };
+        ask_h0(0);
         f32x16 acc;
 #pragma unroll
         for (int t = 0; t < 16; ++t) acc[t] = 0.f;
@@ -480,6 +498,7 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_bf16_ws_kernel(const GemmNtArg
           const bf16x8 fa = *reinterpret_cast<const bf16x8 *>(&At[(i * 32 + (lane & 31)) * LDK + ks * 16 + kl]);
           acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, bfr[ks][j], acc, 0, 0, 0);
         }
+        ask_h0(1);
         const int mt = m_wave + i * 32, ntc = n_wave + j * 32;
         if (mt >= a.M || ntc >= (a.out_pad > a.N ? a.out_pad : a.N)) continue;  // wave-uniform
         if (a.vec_epi) {
@@ -511,16 +530,44 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_bf16_ws_kernel(const GemmNtArg
             for (int t = 0; t < 8; ++t)
               patch[(8 * (t >> 2) + 4 * (lane >> 5) + (t & 3)) * PS + (lane & 31)] = acc[8 * hf + t];
             __builtin_amdgcn_wave_barrier();
-            const int r = lane >> 2, c = (lane & 3) * 8;
-            float v[8];
-            const f32x4 v0 = *reinterpret_cast<const f32x4 *>(&patch[r * PS + c]);
-            const f32x4 v1 = *reinterpret_cast<const f32x4 *>(&patch[r * PS + c + 4]);
+            const int r = lane >> 2, c = (lane & 3) * 8, m = mt + 16 * hf + r, n = ntc + c;
+            if constexpr (MODE == WS_GCNII || MODE == WS_GCNII_BACK) {  // (rounded as in epilogue_store8)
+              if (m < a.M && n < a.N) {
+                const bf16_t *x = &At[(i * 32 + 16 * hf + r) * LDK + n];
+                float y[8];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              v[t] = v0[t];
-              v[4 + t] = v1[t];
+                for (int q = 0; q < 2; ++q) {  // four columns at a time: few registers
+                  const f32x4 v = *reinterpret_cast<const f32x4 *>(&patch[r * PS + c + 4 * q]);
+                  const bf16x4 x4 = *reinterpret_cast<const bf16x4 *>(x + 4 * q);
+#pragma unroll
+                  for (int t = 0; t < 4; ++t) {
+                    const float z = __builtin_fmaf(a.beta, v[t], (1.f - a.beta) * (float)x4[t]);
+                    y[4 * q + t] = MODE == WS_GCNII ? (z > 0.f ? z : 0.f) : z;
+                  }
+                  if constexpr (MODE == WS_GCNII_BACK) {
+                    if (a.h0grad != nullptr) {
+                      f32x4 h = h0[2 * hf + q];
+#pragma unroll
+                      for (int t = 0; t < 4; ++t) h[t] = __builtin_fmaf(a.alpha, y[4 * q + t], h[t]);
+                      *reinterpret_cast<f32x4 *>(a.h0grad + (size_t)m * a.h0_ld + n + 4 * q) = h;
+                    }
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) y[4 * q + t] *= 1.f - a.alpha;
+                  }
+                }
+                store8_f32(a.out, a.out_dtype, (size_t)m * a.out_ld + n, y);
+              }
+            } else {
+              float v[8];
+              const f32x4 v0 = *reinterpret_cast<const f32x4 *>(&patch[r * PS + c]);
+              const f32x4 v1 = *reinterpret_cast<const f32x4 *>(&patch[r * PS + c + 4]);
+#pragma unroll
+              for (int t = 0; t < 4; ++t) {
+                v[t] = v0[t];
+                v[4 + t] = v1[t];
+              }
+              if (m < a.M && n < a.N) epilogue_store8(a, m, n, v, store_epi);
             }
-            if (mt + 16 * hf + r < a.M && ntc + c < a.N) epilogue_store8(a, mt + 16 * hf + r, ntc + c, v, store_epi);
             __builtin_amdgcn_wave_barrier();
           }
         } else {
@@ -547,18 +594,24 @@ struct WsKernel {
   int tm;  // rows per tile
   size_t smem;
 };
-template <int WN, int KS, bool GCNF>
+template <int WN, int KS, int MODE>
 static WsKernel ws_instance() {
   constexpr int TM = 64 * (4 / WN), LDK = KS * 16 + 8;
   constexpr size_t smem = (size_t)2 * TM * LDK * sizeof(bf16_t) + (size_t)4 * 16 * 40 * sizeof(float);
-  static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_nt_bf16_ws_kernel<WN, KS, GCNF>),
+  static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_nt_bf16_ws_kernel<WN, KS, MODE>),
                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   (void)set;
-  return WsKernel{gemm_nt_bf16_ws_kernel<WN, KS, GCNF>, TM, smem};
+  return WsKernel{gemm_nt_bf16_ws_kernel<WN, KS, MODE>, TM, smem};
 }
 template <int WN, int KS>
 static WsKernel ws_for(const GemmNtArgs &a) {
-  return a.epilogue == EPI_FWD_GCN && a.vec_epi ? ws_instance<WN, KS, true>() : ws_instance<WN, KS, false>();
+  if (a.epilogue == EPI_FWD_GCN && a.vec_epi) return ws_instance<WN, KS, WS_GCN>();
+  // the other operand of the identity mapping is the multiplied row itself, all of it in LDS
+  if (a.vec_epi && a.aux == a.A && a.aux_ld == a.lda && a.aux_dtype == DT_BF16 && a.N <= a.Kp) {
+    if (a.epilogue == EPI_FWD_GCNII) return ws_instance<WN, KS, WS_GCNII>();
+    if (a.epilogue == EPI_DGRAD_GCNII) return ws_instance<WN, KS, WS_GCNII_BACK>();
+  }
+  return ws_instance<WN, KS, WS_ANY>();
 }
 static WsKernel ws_kernel(const GemmNtArgs &a) {
   if (a.N <= 128 && a.Kp <= 128) return ws_for<2, 8>(a);

@@ -416,6 +416,12 @@ struct CopyArgs {
 };
 int launch_copies(const CopyArgs *c, int n, hipStream_t s);  // that do not overlap, in launches of up to kBatch
 int launch_fill_zero(void *dst, size_t bytes, hipStream_t s);
+struct FillArgs {
+  void *dst;
+  size_t bytes;
+};
+int launch_fills_zero(const FillArgs *f, int n, hipStream_t s);  // planes of launches of up to kFills
+constexpr int kFills = 32;
 // symmetric normalisation weights from row lengths: val[e] = 1/sqrt(len(row) * len(other))
 int launch_gcn_norm(const int64_t *ptr, const uint32_t *pidx, int vbits, const int64_t *len_ptr, int64_t n,
                     float *val, hipStream_t s);

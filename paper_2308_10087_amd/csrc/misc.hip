@@ -174,11 +174,20 @@ __global__ __launch_bounds__(256) void copy_kernel(const Batch<CopyPlane> ba) {
     reinterpret_cast<uint8_t *>(dst + n16)[threadIdx.x] = reinterpret_cast<const uint8_t *>(src + n16)[threadIdx.x];
 }
 
-__global__ __launch_bounds__(256) void fill_zero_kernel(u32x4 *dst, size_t n16, uint8_t *tdst, int tail) {
+struct FillPlanes {
+  struct {
+    u32x4 *dst;
+    size_t n16;
+    int32_t tail;
+  } p[kFills];
+};
+__global__ __launch_bounds__(256) void fill_zero_kernel(const FillPlanes a) {
+  u32x4 *dst = a.p[blockIdx.y].dst;
+  const size_t n16 = a.p[blockIdx.y].n16;
   const size_t stride = (size_t)gridDim.x * 256;
   const u32x4 z = {0u, 0u, 0u, 0u};
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += stride) dst[i] = z;
-  if (blockIdx.x == 0 && (int)threadIdx.x < tail) tdst[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && (int)threadIdx.x < a.p[blockIdx.y].tail) reinterpret_cast<uint8_t *>(dst + n16)[threadIdx.x] = 0;
 }
 
 // One wave per sparse row: val[e] = 1 / sqrt(len(row) * len(other endpoint)), lengths taken from
@@ -379,13 +388,28 @@ int launch_copy(const void *src, void *dst, size_t bytes, hipStream_t s) {
   return launch_copies(&c, 1, s);
 }
 
+int launch_fills_zero(const FillArgs *f, int n, hipStream_t s) {
+  for (int i = 0; i < n;) {
+    FillPlanes a{};
+    unsigned m = 0, grid = 1;
+    for (; i < n && m < (unsigned)kFills; ++i) {
+      if (f[i].bytes == 0) continue;
+      const size_t n16 = f[i].bytes / 16;
+      a.p[m].dst = static_cast<u32x4 *>(f[i].dst);
+      a.p[m].n16 = n16;
+      a.p[m++].tail = (int32_t)(f[i].bytes % 16);
+      grid = std::max(grid, stream_grid(n16));
+    }
+    if (m == 0) continue;
+    hipLaunchKernelGGL(fill_zero_kernel, dim3(grid, m), dim3(256), 0, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
+  }
+  return hipSuccess;
+}
 int launch_fill_zero(void *dst, size_t bytes, hipStream_t s) {
-  if (bytes == 0) return hipSuccess;
-  const size_t n16 = bytes / 16;
-  const int tail = (int)(bytes % 16);
-  hipLaunchKernelGGL(fill_zero_kernel, dim3(stream_grid(n16)), dim3(256), 0, s, static_cast<u32x4 *>(dst), n16,
-                     static_cast<uint8_t *>(dst) + n16 * 16, tail);
-  return (int)hipGetLastError();
+  const FillArgs f{dst, bytes};
+  return launch_fills_zero(&f, 1, s);
 }
 
 int launch_gcn_norm(const int64_t *ptr, const uint32_t *pidx, int vbits, const int64_t *len_ptr, int64_t n, float *val,

@@ -96,29 +96,99 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(const float *x, int64_t
   if (threadIdx.x == 0) out[blockIdx.x] = red[0] * scale;
 }
 
-__global__ __launch_bounds__(256) void adam_kernel(float *p, const float *g, float *m, float *v, void *compute, int compute_dtype,
-                                                   int64_t n, float lr, float b1, float b2, float eps, float wd, float c1, float c2) {
+// Weight updates: the parameters of a model are planes of one launch, as are the clears of their gradients. An epoch on two ResGCN+
+// stages of four layers made 26 + 26 launches of 2 - 3 us each: 1,636 us before, 1,444 with two.
+constexpr int kUpdates = 32;
+struct Update {
+  float *p;
+  const float *g;
+  float *m, *v;  // Adam
+  void *compute;
+  int32_t compute_dtype;
+  int64_t n;
+};
+struct UpdateArgs {
+  Update u[kUpdates];
+  float lr, b1, b2, eps, wd, c1, c2;
+};
+static_assert(sizeof(UpdateArgs) <= 4096, "kernel arguments");
+
+__global__ __launch_bounds__(256) void adam_kernel(const UpdateArgs a) {
+  const Update &u = a.u[blockIdx.y];
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const float pi = p[i];
-  const float gi = g[i] + wd * pi;
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  const float pn = pi - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-  p[i] = pn;
-  if (compute) store_elt(compute, compute_dtype, (size_t)i, pn);
+  if (i >= u.n) return;
+  const float pi = u.p[i];
+  const float gi = u.g[i] + a.wd * pi;
+  const float mi = fmaf(a.b1, u.m[i], (1.f - a.b1) * gi);  // (written out: the one fused step must not move to the other product)
+  const float vi = fmaf(a.b2, u.v[i], (1.f - a.b2) * gi * gi);
+  u.m[i] = mi;
+  u.v[i] = vi;
+  const float pn = pi - a.lr * (mi * a.c1) / (sqrtf(vi * a.c2) + a.eps);
+  u.p[i] = pn;
+  if (u.compute) store_elt(u.compute, u.compute_dtype, (size_t)i, pn);
 }
 
-__global__ __launch_bounds__(256) void sgd_kernel(float *p, const float *g, void *compute, int compute_dtype, int64_t n, float lr,
-                                                  float wd) {
+__global__ __launch_bounds__(256) void sgd_kernel(const UpdateArgs a) {
+  const Update &u = a.u[blockIdx.y];
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const float pi = p[i];
-  const float pn = pi - lr * (g[i] + wd * pi);
-  p[i] = pn;
-  if (compute) store_elt(compute, compute_dtype, (size_t)i, pn);
+  if (i >= u.n) return;
+  const float pi = u.p[i];
+  const float pn = pi - a.lr * (u.g[i] + a.wd * pi);
+  u.p[i] = pn;
+  if (u.compute) store_elt(u.compute, u.compute_dtype, (size_t)i, pn);
+}
+
+// whether an update writes what another one reads or writes (tied parameters)
+bool touch(const Update &x, const Update &y) {
+  auto meet = [](const void *a, size_t n, const void *b, size_t m) {
+    const char *p = static_cast<const char *>(a), *q = static_cast<const char *>(b);
+    return p != nullptr && q != nullptr && p < q + m && q < p + n;
+  };
+  const size_t nx = (size_t)x.n * 4, ny = (size_t)y.n * 4;  // (compute copies are no longer than that)
+  const void *xs[] = {x.p, x.m, x.v, x.compute}, *ys[] = {y.p, y.m, y.v, y.compute};
+  for (const void *a : xs)
+    for (const void *b : ys)
+      if (meet(a, a == x.compute && x.compute_dtype == DT_BF16 ? nx / 2 : nx, b, b == y.compute && y.compute_dtype == DT_BF16 ? ny / 2 : ny)) return true;
+  return meet(x.p, nx, y.g, ny) || meet(y.p, ny, x.g, nx);
+}
+
+// list[i].n > 0; in order, as many at a time as don't touch each other
+int launch_updates(const Update *list, size_t n, bool adam, UpdateArgs a, hipStream_t s) {
+  for (size_t i0 = 0, i1; i0 < n; i0 = i1) {
+    int64_t most = 0;
+    for (i1 = i0; i1 < n && i1 - i0 < (size_t)kUpdates; ++i1) {
+      bool tied = false;
+      for (size_t i = i0; i < i1; ++i) tied = tied || touch(list[i], list[i1]);
+      if (tied) break;
+      a.u[i1 - i0] = list[i1];
+      most = std::max(most, list[i1].n);
+    }
+    hipLaunchKernelGGL(adam ? adam_kernel : sgd_kernel, dim3((unsigned)((most + 255) / 256), (unsigned)(i1 - i0)), dim3(256), 0, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
+  }
+  return 0;
+}
+// the parts of a parameter's update that its callers check alike
+int check_update(Update &u) {
+  if (u.n < 0) return GNNSTAGE_EINVAL;
+  if (u.n == 0) return GNNSTAGE_OK;
+  if (!u.p || !u.g) return GNNSTAGE_EINVAL;
+  if (u.compute_dtype != GNNSTAGE_F32 && u.compute_dtype != GNNSTAGE_BF16) return GNNSTAGE_EINVAL;
+  if (u.compute == u.p) u.compute = nullptr;
+  return GNNSTAGE_OK;
+}
+UpdateArgs adam_args(float lr, float b1, float b2, float eps, float wd, int64_t step) {
+  UpdateArgs a{};
+  a.lr = lr;
+  a.b1 = b1;
+  a.b2 = b2;
+  a.eps = eps;
+  a.wd = wd;
+  // bias corrections 1 / (1 - beta^t), formed in double on the host
+  a.c1 = (float)(1.0 / (1.0 - std::pow((double)b1, (double)step)));
+  a.c2 = (float)(1.0 / (1.0 - std::pow((double)b2, (double)step)));
+  return a;
 }
 
 struct Layout {
@@ -337,29 +407,20 @@ extern "C" int gnntrain_sum_static(const float *x, int64_t n, float scale, float
 
 extern "C" int gnntrain_adam_step(float *p, const float *g, float *m, float *v, void *compute, int32_t compute_dtype, int64_t count,
                                   float lr, float beta1, float beta2, float eps, float weight_decay, int64_t t, void *hip_stream) {
-  if (count < 0 || t < 1) return GNNSTAGE_EINVAL;
-  if (count == 0) return GNNSTAGE_OK;
-  if (!p || !g || !m || !v) return GNNSTAGE_EINVAL;
-  if (compute_dtype != GNNSTAGE_F32 && compute_dtype != GNNSTAGE_BF16) return GNNSTAGE_EINVAL;
-  if (compute == p) compute = nullptr;
-  // bias corrections 1 / (1 - beta^t), formed in double on the host
-  const float c1 = (float)(1.0 / (1.0 - std::pow((double)beta1, (double)t)));
-  const float c2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)t)));
-  hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, static_cast<hipStream_t>(hip_stream), p, g, m, v,
-                     compute, compute_dtype, count, lr, beta1, beta2, eps, weight_decay, c1, c2);
-  return hipGetLastError() == hipSuccess ? GNNSTAGE_OK : GNNSTAGE_EHIP;
+  if (t < 1) return GNNSTAGE_EINVAL;
+  Update u{p, g, m, v, compute, compute_dtype, count};
+  const int rc = check_update(u);
+  if (rc != GNNSTAGE_OK || count == 0) return rc;
+  if (!m || !v) return GNNSTAGE_EINVAL;
+  return launch_updates(&u, 1, true, adam_args(lr, beta1, beta2, eps, weight_decay, t), static_cast<hipStream_t>(hip_stream)) == 0 ? GNNSTAGE_OK : GNNSTAGE_EHIP;
 }
 
 extern "C" int gnntrain_sgd_step(float *p, const float *g, void *compute, int32_t compute_dtype, int64_t count, float lr,
                                  float weight_decay, void *hip_stream) {
-  if (count < 0) return GNNSTAGE_EINVAL;
-  if (count == 0) return GNNSTAGE_OK;
-  if (!p || !g) return GNNSTAGE_EINVAL;
-  if (compute_dtype != GNNSTAGE_F32 && compute_dtype != GNNSTAGE_BF16) return GNNSTAGE_EINVAL;
-  if (compute == p) compute = nullptr;
-  hipLaunchKernelGGL(sgd_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, static_cast<hipStream_t>(hip_stream), p, g,
-                     compute, compute_dtype, count, lr, weight_decay);
-  return hipGetLastError() == hipSuccess ? GNNSTAGE_OK : GNNSTAGE_EHIP;
+  Update u{p, g, nullptr, nullptr, compute, compute_dtype, count};
+  const int rc = check_update(u);
+  if (rc != GNNSTAGE_OK || count == 0) return rc;
+  return launch_updates(&u, 1, false, adam_args(lr, 0.f, 0.f, 0.f, weight_decay, 1), static_cast<hipStream_t>(hip_stream)) == 0 ? GNNSTAGE_OK : GNNSTAGE_EHIP;
 }
 
 extern "C" size_t gnntrain_workspace_size(const gnntrain_desc *desc) try {
@@ -495,7 +556,9 @@ extern "C" int gnntrain_epoch(gnntrain_t *tr, int64_t epoch, float *loss, void *
   for (int s = 0; s < S; ++s)
     TRAIN_STAGE(tr, s, gnnstage_set_dropout_seed(tr->stages[(size_t)s], splitmix64(tr->seed + (uint64_t)(epoch + 1) * kGolden) + (uint64_t)s));
 
-  for (const gnntrain_param &p : tr->params) TRAIN_HIP(tr, launch_fill_zero(p.grad, sizeof(float) * (size_t)p.count, stream));
+  std::vector<FillArgs> grads;
+  for (const gnntrain_param &p : tr->params) grads.push_back(FillArgs{p.grad, sizeof(float) * (size_t)p.count});
+  TRAIN_HIP(tr, launch_fills_zero(grads.data(), (int)grads.size(), stream));
   // the head's weights, staged like a layer's: transposed for the logits, plain for the input gradient
   const StageWeightsArgs head{tr->head_W, x.d_top, x.C, tr->at<char>(lay.Wt), x.Kp, tr->at<char>(lay.Wn), x.Cp};
   TRAIN_HIP(tr, launch_stage_weights(&head, 1, cd, nullptr, stream));
@@ -581,16 +644,17 @@ extern "C" int gnntrain_epoch(gnntrain_t *tr, int64_t epoch, float *loss, void *
   TRAIN_HIP(tr, launch_sum(row_loss, x.n, inv_n, tr->at<float>(lay.scratch), tr->at<float>(lay.loss), stream));
   // ---- weight update
   ++tr->step;
+  const bool adam = tr->optimizer == GNNTRAIN_ADAM;
+  std::vector<Update> updates;
   for (size_t i = 0; i < tr->params.size(); ++i) {
     const gnntrain_param &p = tr->params[i];
-    int rc;
-    if (tr->optimizer == GNNTRAIN_ADAM)
-      rc = gnntrain_adam_step(p.master, p.grad, tr->at<float>(lay.m) + tr->moment_off[i], tr->at<float>(lay.v) + tr->moment_off[i], p.compute,
-                              p.compute_dtype, p.count, tr->lr, tr->beta1, tr->beta2, tr->eps, tr->wd, tr->step, stream);
-    else
-      rc = gnntrain_sgd_step(p.master, p.grad, p.compute, p.compute_dtype, p.count, tr->lr, tr->wd, stream);
+    Update u{p.master, p.grad, adam ? tr->at<float>(lay.m) + tr->moment_off[i] : nullptr, adam ? tr->at<float>(lay.v) + tr->moment_off[i] : nullptr,
+             p.compute, p.compute_dtype, p.count};
+    const int rc = check_update(u);
     if (rc != GNNSTAGE_OK) return fail(tr, rc, "optimiser launch failed");
+    if (u.n > 0) updates.push_back(u);
   }
+  TRAIN_HIP(tr, launch_updates(updates.data(), updates.size(), adam, adam_args(tr->lr, tr->beta1, tr->beta2, tr->eps, tr->wd, tr->step), stream));
   // ---- Section 3.4, second technique: the history of epoch alpha * floor((t - 1) / alpha)
   if ((epoch + 1) % tr->alpha_hist == 0)
     for (int s = 0; s < S; ++s) {

@@ -1,0 +1,131 @@
+"""Whole passes at the sizes where their launches go wrong: more chunks than a mask word has bits, rows of every short length,
+products whose epilogue reads another operand, weight gradients that must not share a launch.  Tolerances are those of the whole
+suite (1e-5 where everything is fp32, 1e-2 where rows are stored as bf16) or equal bits."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_harness import GpuRun, GpuTrainRun
+from helpers import make_problem, make_train_problem, max_rel, run_oracle
+from test_gpu_kernel_edges import _whole_equals_chunks
+from test_gpu_parity import TOL_BF16, TOL_F32, _parity, small
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("k", [64, 65, 130])
+@pytest.mark.parametrize("variant,dtype,dims", [
+    ("gcn", "bf16", (128, 256, 128)), ("resgcn", "bf16", (128,) * 3), ("sage", "bf16", (100, 102, 64)), ("gcn", "f32", (36, 40, 24))])
+def test_chunks_beyond_one_mask_word(k, variant, dtype, dims, monkeypatch):
+    """64 chunks are one word of selects, more are a table: short rows, whole rows and pieces of long ones on both kernels."""
+    monkeypatch.setenv("GNNSTAGE_CLASS_MIN_ROW", "24")
+    p = make_problem(small(n=1111, k=k, dims=dims, variant=variant, dtype=dtype, deg=14.0), bias_std=0.05, first_stage=False, noise_std=0.3)
+    _whole_equals_chunks(p)
+    _parity(p, TOL_F32 if dtype == "f32" else TOL_BF16)
+
+
+def _graph_of_lengths(n, lengths, seed):
+    """Row i has lengths[i % len] entries, columns drawn without repetition; the transposed rows are of all short lengths too."""
+    rng = np.random.default_rng(seed)
+    ln = np.resize(lengths, n)
+    row_ptr = np.concatenate([[0], np.cumsum(ln)]).astype(np.int64)
+    step = rng.integers(1, max(2, n // 40), n)  # row i: an arithmetic progression from a random start, short enough not to close
+    k = np.arange(row_ptr[-1]) - np.repeat(row_ptr[:-1], ln)
+    col = (np.repeat(rng.integers(0, n, n), ln) + k * np.repeat(step, ln)) % n
+    order = np.lexsort((col, np.repeat(np.arange(n), ln)))
+    return row_ptr, col[order].astype(np.int32)
+
+
+@pytest.mark.parametrize("n,k", [(1283, 3), (61, 1), (5, 2)])
+@pytest.mark.parametrize("dims", [(128, 128, 128), (64, 256, 128), (512, 128)])
+def test_short_rows_are_the_bits_of_whole_waves(n, k, dims, monkeypatch):
+    """Rows of 1 .. 18 entries, four to a wave up to 16: the bits of a row to a wave, whatever rows are left for the last wave."""
+    graph = _graph_of_lengths(n, np.minimum(n - 1, [1, 16, 2, 15, 17, 4, 3, 8, 5, 18, 9, 12, 7, 16, 16, 13, 1]), 7)
+    p = make_problem(small(n=n, k=k, dims=dims, dtype="bf16"), graph=graph, bias_std=0.05, first_stage=False, noise_std=0.3)
+    p.val[:] = np.random.default_rng(2).uniform(0.02, 0.3, p.val.size)  # (of any graph: not from its degrees)
+    runs = []
+    for most in ("0", "4", "16"):
+        monkeypatch.setenv("GNNSTAGE_SHORT_ROW", most)
+        runs.append(GpuRun(p).run())
+    for r in runs[1:]:
+        for a, b in zip(r.cur + [r.grad_in] + r.dW, runs[0].cur + [runs[0].grad_in] + runs[0].dW):
+            assert torch.equal(a, b)
+
+
+def test_short_rows_of_tables_beyond_the_caches(monkeypatch):
+    """Tables of over 256 MB: rows of up to 4 entries on the vector ALU, four to a wave.  Against a row to a wave: weights in fp32 instead
+    of two bf16 parts, another order of at most 4 products, so a bf16 rounding of the result apart."""
+    n = 1_060_001
+    graph = _graph_of_lengths(n, np.array([1, 4, 2, 5, 3, 4, 6, 0]), 3)
+    p = make_problem(small(n=n, k=3, dims=(128, 128), dtype="bf16"), graph=graph, first_stage=False)
+    p.val[:] = np.random.default_rng(2).uniform(0.02, 0.3, p.val.size)
+    runs = []
+    for most in ("0", None):
+        monkeypatch.setenv("GNNSTAGE_SHORT_ROW", most) if most else monkeypatch.delenv("GNNSTAGE_SHORT_ROW")
+        runs.append(GpuRun(p))
+        runs[-1].forward()
+    runs[1].cur[1].copy_(runs[0].cur[1])  # (both decide on the same levels)
+    for r in runs:
+        r.backward()
+    torch.cuda.synchronize()
+    for a, b in ((runs[1].grad_in, runs[0].grad_in), (runs[1].dW[0], runs[0].dW[0])):
+        assert (a.float() - b.float()).abs().max() <= TOL_BF16 * b.float().abs().max()
+    runs[1].forward()
+    torch.cuda.synchronize()
+    a, b = runs[1].cur[1], runs[0].cur[1]
+    assert (a.float() - b.float()).abs().max() <= TOL_BF16 * b.float().abs().max()
+
+
+@pytest.mark.parametrize("width", [64, 128, 256])
+@pytest.mark.parametrize("n,k", [(513, 1), (1031, 4), (37, 2)])
+def test_identity_mapping_in_the_weight_stationary_product(width, n, k, monkeypatch):
+    """GCNII products from every row count on in the weight-stationary kernel (at 256 the other operand comes through LDS, half before
+    and half behind the products): the bits of the tiled kernel, and the oracle's values."""
+    p = make_problem(small(n=n, k=k, dims=(width,) * 4, variant="gcnii", dtype="bf16", deg=min(9.0, n / 8)), first_stage=False, noise_std=0.3)
+    runs = []
+    for least in ("1", "1000000"):
+        monkeypatch.setenv("GNNSTAGE_GEMM_WS_MIN_ROWS", least)
+        runs.append(GpuRun(p).run())
+    a, b = runs
+    for x, y in zip(a.cur + [a.grad_in, a.grad_h0], b.cur + [b.grad_in, b.grad_h0]):
+        assert torch.equal(x, y)
+    monkeypatch.setenv("GNNSTAGE_GEMM_WS_MIN_ROWS", "1")
+    _parity(p, TOL_BF16)
+
+
+@pytest.mark.parametrize("dtype,width", [("f32", 36), ("bf16", 128)])
+def test_layers_with_one_weight_gradient_buffer(dtype, width):
+    """Tied weights: layers of one width go to one launch of weight gradients unless they share a buffer, which then holds their sum."""
+    import paper_2308_10087_amd as g
+    p = make_problem(small(n=900, k=6, dims=(width,) * 5, dtype=dtype, deg=9.0), bias_std=0.05, first_stage=False)
+    ref = run_oracle(p)
+    r = GpuRun(p)
+    dW, db = torch.zeros((width, width), device=r.device), torch.zeros(width, device=r.device)
+    r.stage = g.GnnStage(p.row_ptr, p.col, p.chunk_ptr, p.dims, W=r.W, cur=r.cur, hist=r.hist, dW=[dW] * 4, bias=r.bias, dbias=[db] * 4, edge_val=p.val,
+                         variant=g.GNNSTAGE_GCN, dtype=g.GNNSTAGE_BF16 if p.quant else g.GNNSTAGE_F32, grad_in=r.grad_in, device=r.device)
+    r.forward()
+    torch.cuda.synchronize()
+    for j in range(1, 5):
+        r.cur[j].copy_(torch.from_numpy(ref.cur[j]).to(r.cur[j].dtype))  # ReLU decisions of one side
+    r.backward()
+    torch.cuda.synchronize()
+    tol = TOL_BF16 if p.quant else TOL_F32
+    assert max_rel(r.np(dW), sum(ref.dW)) <= tol and max_rel(r.np(db), sum(ref.db)) <= tol
+
+
+def test_tied_parameters_are_updated_one_after_the_other():
+    """An epoch's update of one parameter listed twice is two updates, the second from the weights of the first; 35 parameters take two
+    launches.  One SGD step without gradients other than a constant per entry: p <- p (1 - lr wd) per listing."""
+    import paper_2308_10087_amd as g
+    tp = make_train_problem(n=600, stage_dims=((16, 16),), K=3)
+    run = GpuTrainRun(tp, optimizer="sgd", lr=0.5, weight_decay=0.25)
+    extra = [torch.full((300 + i,), 2.0, device="cuda:0") for i in range(35)]
+    zeros = [torch.zeros_like(x) for x in extra]
+    run.params += [(x, None, z) for x, z in zip(extra, zeros)] + [(extra[3], None, zeros[3])]
+    run.trainer = g.GnnTrainer(run.stages, head_W=run.head_W, head_b=run.head_b, head_dW=run.head_dW, head_db=run.head_db, labels=run.labels,
+                               train_mask=run.mask, params=run.params, device="cuda:0", optimizer=g.GNNTRAIN_SGD, lr=0.5, beta1=0.9, beta2=0.999,
+                               eps=1e-8, weight_decay=0.25, shuffle=True, seed=0, alpha_hist=1)
+    run.epoch(0)
+    torch.cuda.synchronize()
+    for i, x in enumerate(extra):
+        assert torch.equal(x, torch.full_like(x, 2.0 * (0.875 ** (2 if i == 3 else 1)))), i

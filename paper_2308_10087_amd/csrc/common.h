@@ -13,6 +13,14 @@ struct ChunkMask {
 constexpr int kMaxChunks = 256;
 constexpr int kMaxClasses = 32;  // source-id classes of the aggregation schedule (a 32-bit activity mask)
 
+// Workgroups of 256 along an axis of a grid: the runtime takes fewer than 2^32 work-items there.
+constexpr int64_t kMostBlocks = ((int64_t)1 << 24) - 1;
+// The grid of a kernel with one element (or vector of elements) per thread; kernels walk on by the grid's size behind its end.
+static inline unsigned element_blocks(int64_t threads) {
+  const int64_t b = (threads + 255) / 256;
+  return (unsigned)(b < kMostBlocks ? b : kMostBlocks);
+}
+
 // The word is picked with selects, not with an indexed access: a kernel that holds the mask as an argument
 // would otherwise fetch the word from memory and wait for it (and for every other load in flight).
 __host__ __device__ inline bool mask_test(const ChunkMask &m, uint32_t c) {
@@ -167,6 +175,12 @@ constexpr int kTaskChunkShift = 24;  // a piece or an uncut row has fewer than 2
 constexpr uint32_t kTaskCountMask = (1u << kTaskChunkShift) - 1u;
 static_assert(kMaxChunks <= 256, "the chunk shares a word with a count");
 static_assert(sizeof(SpmmArgs) <= 4096, "kernel arguments");
+// The most workgroups that a launch of these operands, or of the reduce behind it, has along an axis: what a launch over several
+// chunks must keep to kMostBlocks (67 M whole rows, or 16.7 M cut ones).
+static inline int64_t spmm_blocks(const SpmmArgs &a) {
+  const int64_t main = a.n_class_blocks + (a.n_tail + 3) / 4 + a.n_short / 4 + 7;  // + 7: rounded up to eight for wide rows
+  return main > a.n_long ? main : a.n_long;
+}
 
 // workgroup b behind the class pieces: whether it serves short rows, and how many of its kind come before it
 struct SpmmTurn {

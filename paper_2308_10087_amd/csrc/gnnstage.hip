@@ -48,6 +48,7 @@ std::string g_create_error;
 //   GNNSTAGE_HOT_ROWS                 sources per such class
 //   GNNSTAGE_HOT_MIN_ROW              rows from this length on are cut by hotness class
 //   GNNSTAGE_SHORT_ROW (0 = off, up to 16)   whole rows of at most this many entries are served a row per 16-lane group
+//   GNNSTAGE_LAUNCH_BLOCKS            workgroups that one aggregation launch over several chunks may have
 struct Tuning {
   int split_edges = 0;          // 0: from the launch size
   int xcd_classes = 0;          // 0: from the size of the gathered table
@@ -67,6 +68,7 @@ struct Tuning {
   int hot_min_row = 2048;       // measured on the 10 M vertex graph: 512 -> 142.8, 1024 -> 140.6, 2048 -> 140.4 ms per step (off: 143.2)
   // whole rows of at most this many entries are served four to a wave (0: none; -1: see Shape::short_row)
   int short_row = -1;
+  int64_t launch_blocks = kMostBlocks;
 };
 
 Tuning read_tuning() {
@@ -89,6 +91,7 @@ Tuning read_tuning() {
   if ((e = getenv("GNNSTAGE_HOT_ROWS")) && atoi(e) >= 1) t.hot_rows = atoi(e);
   if ((e = getenv("GNNSTAGE_HOT_MIN_ROW")) && atoi(e) >= 1) t.hot_min_row = atoi(e);
   if ((e = getenv("GNNSTAGE_SHORT_ROW")) && atoi(e) >= 0) t.short_row = std::min(atoi(e), kShortRowMost);
+  if ((e = getenv("GNNSTAGE_LAUNCH_BLOCKS")) && atoll(e) >= 1) t.launch_blocks = std::min<int64_t>(atoll(e), kMostBlocks);
   return t;
 }
 
@@ -993,7 +996,7 @@ void set_schedule(const gnnstage *st, int dir, int c0, int c1, Select sel, const
 }
 
 // One aggregation over the rows of a span: dense blocks first, then the sparse kernels, then (where chunks have long rows)
-// the reduce of their pieces, timed apart; as many chunks at a time as have room for their partial sums.
+// the reduce of their pieces, timed apart; as many chunks at a time as have room for their partial sums and fit a launch.
 int run_spmm(gnnstage *st, SpmmArgs a, int src_dtype, int out_dtype, bool transposed, const Span &sp, Select sel, hipStream_t stream, int kind, int layer) {
   const Layout &lay = st->lay;
   const int dir = transposed ? 1 : 0;
@@ -1002,6 +1005,10 @@ int run_spmm(gnnstage *st, SpmmArgs a, int src_dtype, int out_dtype, bool transp
     for (c1 = c0 + 1; c1 < sp.c1; ++c1)
       if (t.slot_off[(size_t)c1 + 1] - t.slot_off[(size_t)c0] > lay.slot_cap || t.item_off[(size_t)c1 + 1] - t.item_off[(size_t)c0] > lay.item_cap) break;
     set_schedule(st, dir, c0, c1, sel, sp.mask, a);
+    while (c1 - c0 > 1 && spmm_blocks(a) > st->s.tune.launch_blocks) {
+      c1 = c0 + (c1 - c0) / 2;
+      set_schedule(st, dir, c0, c1, sel, sp.mask, a);
+    }
     {
       Timed tm(st, stream, kind, layer);
       const int64_t i0 = t.item_off[(size_t)c0], n_items = t.item_off[(size_t)c1] - i0;
@@ -1350,12 +1357,15 @@ int flush_deferred_wgrad(gnnstage *st, hipStream_t stream) {
   return GNNSTAGE_OK;
 }
 
+// Whether a product over all rows can count them (and its tiles' rows beyond them) in 32 bits.
+bool rows_in_one_product(const gnnstage *st) { return st->s.n <= 0x7fff0000; }
+
 // The spans of the work behind a pass's last backward call: all chunks side by side, one by one while launches are timed (a
 // timed launch belongs to one chunk's share).  earlier: with the masks of the chunks in front of each in the forward order.
 int finish_spans(gnnstage *st, bool earlier, std::vector<Span> &spans, hipStream_t stream) {
   spans.clear();
   ChunkMask m{};
-  if (st->prof.kinds == 0) {
+  if (st->prof.kinds == 0 && rows_in_one_product(st)) {
     spans.push_back(whole_span(st));
     spans[0].mask = ChunkMask{};
     for (int c = 0; c < st->s.K && !earlier; ++c) mask_set(spans[0].mask, (uint32_t)c);
@@ -1597,6 +1607,7 @@ int end_backward(gnnstage *st, hipStream_t stream) {
 // Whether a pass may run layer by layer over all of its chunks.
 bool whole_pass_ok(const gnnstage *st, const int32_t *order, int n) {
   if (n != st->s.K || !st->s.defer_wgrad() || st->prof.kinds != 0) return false;  // (timed launches belong to one chunk each)
+  if (!rows_in_one_product(st)) return false;
   // a level above 0 that is its own history: what a chunk does not select are the rows of the last pass, which the level below
   // would have overwritten
   for (int j = 1; j < st->s.L; ++j)

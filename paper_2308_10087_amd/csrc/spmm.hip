@@ -846,7 +846,7 @@ int launch_spmm(const SpmmArgs &a_in, int src_dtype, int out_dtype, hipStream_t 
   const int64_t tail_blocks = (a.n_tail + 3) / 4, short_blocks = mfma && a.d <= 256 ? (a.n_short + 15) / 16 : a.n_short / 4;
   int64_t gx = a.n_class_blocks + tail_blocks + short_blocks;
   if (gx <= 0) return hipSuccess;
-  if (gx > 0x7fffffff) return hipErrorInvalidValue;
+  if (gx + 7 > kMostBlocks) return hipErrorInvalidValue;
   // rounded up: the count of short workgroups comes out exactly (below 2^32 workgroups), and none behind the last one
   a.mix = short_blocks > 0 ? (((uint64_t)short_blocks << 32) + (uint64_t)(tail_blocks + short_blocks) - 1) / (uint64_t)(tail_blocks + short_blocks) : 0;
   if (mfma)
@@ -861,6 +861,7 @@ int launch_spmm(const SpmmArgs &a_in, int src_dtype, int out_dtype, hipStream_t 
 
 int launch_spmm_reduce(const SpmmArgs &a, int src_dtype, int out_dtype, hipStream_t s) {
   if (a.n_long <= 0) return hipSuccess;
+  if (a.n_long > kMostBlocks) return hipErrorInvalidValue;
   const Shape *best = pick_shape(a, src_dtype, out_dtype);
   if (!best) return hipErrorInvalidValue;
   return launch_checked(best->reduce, dim3((unsigned)a.n_long, (unsigned)((a.d + 32 * best->vec - 1) / (32 * best->vec))), a, s);

@@ -59,8 +59,9 @@ int __hipPopCallConfiguration(grid_t *grid, grid_t *block, size_t *smem, void **
 }
 int hipLaunchKernel(const void *f, grid_t grid, grid_t block, void **args, size_t smem, void *stream) {
   size_t i;
-  (void)block, (void)smem, (void)stream;
+  (void)smem, (void)stream;
   if (fail_at >= 0 && fail_at-- == 0) return last = 1;
+  if ((uint64_t)grid.x * block.x >> 32 || (uint64_t)grid.y * block.y >> 32 || (uint64_t)grid.z * block.z >> 32) return last = 9; /* as the runtime does */
   if (n_list == cap_list) list = realloc(list, (cap_list = cap_list ? 2 * cap_list : 1024) * sizeof *list);
   list[n_list].name = "";
   list[n_list].grid = grid;

@@ -129,3 +129,41 @@ def test_tied_parameters_are_updated_one_after_the_other():
     torch.cuda.synchronize()
     for i, x in enumerate(extra):
         assert torch.equal(x, torch.full_like(x, 2.0 * (0.875 ** (2 if i == 3 else 1)))), i
+
+
+@pytest.mark.parametrize("variant,dtype,dims", [("gcn", "bf16", (128, 256, 128)), ("gcn", "f32", (36, 40, 24)), ("resgcn", "bf16", (128,) * 3)])
+@pytest.mark.parametrize("k,blocks", [(7, 150), (70, 100), (5, 1)])
+def test_a_layer_that_is_too_much_for_one_launch(k, blocks, variant, dtype, dims, monkeypatch):
+    """A launch takes as many chunks as keep below the most workgroups, one at least: the bits of the chunk calls."""
+    monkeypatch.setenv("GNNSTAGE_LAUNCH_BLOCKS", str(blocks))
+    monkeypatch.setenv("GNNSTAGE_CLASS_MIN_ROW", "24")
+    _whole_equals_chunks(make_problem(small(n=1111, k=k, dims=dims, variant=variant, dtype=dtype, deg=14.0), bias_std=0.05, first_stage=False, noise_std=0.3))
+
+
+def test_more_elements_than_a_grid_has_threads():
+    """4.29 M rows of 1002 bf16 columns: dropout and the ReLU derivative over all rows walk on behind the end of their grids; the
+    bits of launches over a chunk."""
+    import paper_2308_10087_amd as g
+    n, d0, d1, K, dev = 4_290_001, 1008, 1002, 3, "cuda:0"
+    assert n * d1 > 2 ** 32
+    rows = lambda d, s: torch.randn((5003, d), generator=torch.Generator(device=dev).manual_seed(s), device=dev).to(torch.bfloat16).repeat(n // 5003 + 1, 1)[:n]
+    cur = [rows(d0, 1), torch.zeros((n, d1), dtype=torch.bfloat16, device=dev)]
+    W, bias = (torch.randn((d0, d1), device=dev) / 30).to(torch.bfloat16), torch.randn(d1, device=dev) / 10
+    dW, dbias, grad_in = torch.zeros((d0, d1), device=dev), torch.zeros(d1, device=dev), torch.zeros((n, d0), dtype=torch.bfloat16, device=dev)
+    st = g.GnnStage(np.arange(n + 1, dtype=np.int64), np.arange(n, dtype=np.int32), np.arange(K + 1, dtype=np.int64) * n // K, [d0, d1], W=[W], cur=cur,
+                    hist=[cur[0]], dW=[dW], bias=[bias], dbias=[dbias], variant=g.GNNSTAGE_GCN, dtype=g.GNNSTAGE_BF16, grad_in=grad_in, device=dev, dropout_p=0.5)
+    assert st.gnnstage_layer_order(0) == 1
+    grad_out = rows(d1, 2)
+    st.forward_pass([0, 1, 2])
+    st.backward_pass([0, 1, 2], grad_out)
+    level, back = cur[1].clone(), grad_in.clone()
+    for x in (cur[1], grad_in):
+        x.zero_()
+    for pos in range(K):
+        st.stage_forward_chunk(pos, pos)
+    for c in reversed(range(K)):
+        st.stage_backward_chunk(c, grad_out[st.rows(c)])
+    torch.cuda.synchronize()
+    assert torch.equal(level, cur[1]) and torch.equal(back, grad_in)
+    kept = (level[-4000:] > 0).float().mean().item()  # half of what passes ReLU
+    assert 0.2 < kept < 0.3

@@ -33,7 +33,7 @@ class _Launch(C.Structure):
 class _Stage:
     """A stage handle over host buffers (values never matter: nothing is computed)."""
 
-    def __init__(self, variant, dims, K, n=400, tied=False, bf16=False):
+    def __init__(self, variant, dims, K, n=400, tied=False, bf16=False, dropout_p=0.0):
         import paper_2308_10087_amd as g
         from paper_2308_10087_amd import binding
         self.g, self.lib = g, binding.lib
@@ -59,6 +59,7 @@ class _Stage:
             self.keep["list " + name] = (a, p)
             setattr(d, name, C.cast(p, C.c_void_p))
         self.grad_in, self.grad_out = np.zeros((n, int(dims[0])), np.float32), np.zeros((n, int(dims[-1])), np.float32)
+        d.dropout_p = dropout_p
         d.variant, d.dtype, d.need_input_grad, d.grad_in, d.ln_eps = dict(gcn=0, sage=2, resgcn=3)[variant], g.GNNSTAGE_BF16 if bf16 else g.GNNSTAGE_F32, 1, self.grad_in.ctypes.data, 1e-5
         size = self.lib.gnnstage_workspace_size(C.byref(d))
         self.ws = np.zeros(size + 256, np.uint8)
@@ -131,6 +132,13 @@ def _timed(rt, variant, dims):
     return out
 
 
+def _all_rows(rt, variant, dims, n, bf16):
+    """Return codes of a whole pass, and how many launches it made (its buffers are never touched, so they take no memory)."""
+    st = _Stage(variant, dims, 3, n=n, bf16=bf16, dropout_p=0.5)
+    rt.host_clear(-1)
+    return [st.forward(), st.backward(), rt.host_launches()]
+
+
 def _refused(rt, variant, dims):
     """A pass in which one launch is refused, at a few places: return codes of the pass and of the calls that follow it."""
     out = {"forward": [], "backward": []}
@@ -199,6 +207,15 @@ def test_a_pass_that_fails_does_not_count_as_run(runtime, variant, dims):
     got = _child(runtime, "_refused", variant, dims)
     assert got["forward"] == [[EHIP, EORDER, EORDER, 0]] * 3
     assert got["backward"] == [[EHIP, 0, EORDER, 0]] * 3
+
+
+@pytest.mark.parametrize("variant,dims,bf16,n", [
+    ("gcn", [1008, 1002], True, 4_290_001), ("gcn", [1008, 1000], False, 4_300_001), ("resgcn", [1000, 1000], True, 4_300_001)])
+def test_launches_over_all_rows_stay_below_2_to_32_threads(runtime, variant, dims, bf16, n):
+    """Rows times columns over 2^32: chunk by chunk a thread per element is a launch that the runtime takes, over all rows it is not."""
+    assert n * max(dims) >= 2 ** 32
+    forward, backward, launches = _child(runtime, "_all_rows", variant, dims, n, bf16)
+    assert (forward, backward) == (0, 0) and launches > 0
 
 
 @pytest.mark.parametrize("n", [65600, 66000, 98000, 131500])

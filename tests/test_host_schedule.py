@@ -81,7 +81,7 @@ def _tasks(a, name, grid):
 def _walk(rt, first, index, chunk_ptr, order):
     """Entries gathered by the launches from `first` on, per aggregation (main launches over one source table and output, with
     their reduces): {(transposed, earlier): entries of every (row, source)}; asserts that every row is finished once."""
-    K, n, got = len(chunk_ptr) - 1, chunk_ptr[-1], {}
+    K, n, got, most = len(chunk_ptr) - 1, chunk_ptr[-1], {}, int(os.environ.get("GNNSTAGE_LAUNCH_BLOCKS", 2 ** 24 - 1))
     chunk_of = np.searchsorted(chunk_ptr, np.arange(n), side="right") - 1
     pos = np.empty(K, int)
     pos[order] = np.arange(K)
@@ -115,14 +115,16 @@ def _walk(rt, first, index, chunk_ptr, order):
         if b"reduce" not in l.name:
             main = a
             key = (a.src_sel, a.out, kind, drop)
-            entries, rows, slots = got.setdefault(key, ([], [], set()))
+            entries, rows, slots, chunks = got.setdefault(key, ([], [], set(), []))
             slots.clear()
+            chunks.append(set())
             for t, q in _tasks(a, l.name, l.grid):
                 row, e0, ne, slot = (_arr(p + t * s, 1, d)[0] for p, s, d in ((a.task_row, 4, "i4"), (a.task_e0, 8, "i8"), (a.task_ne, 4, "u4"), (a.task_slot, 4, "i4")))
                 if row < 0:
                     continue
                 c = int(ne) >> 24
                 assert chunk_of[row] == c
+                chunks[-1].add(c)
                 words = _arr(a.pidx + 4 * int(e0), int(ne) & 0xffffff, "u4")
                 src, kept = words & ((1 << a.vbits) - 1), sees(c)[words >> a.vbits]
                 assert (chunk_of[src] == words >> a.vbits).all() and index[drop][0][row] <= e0 and e0 + len(src) <= index[drop][0][row + 1]
@@ -135,9 +137,11 @@ def _walk(rt, first, index, chunk_ptr, order):
                     slots.add(int(slot))
                 else:
                     rows.append(int(row))
+            assert len(chunks[-1]) <= 1 or l.grid[0] <= most
         else:
             assert (a.src_sel, a.out, a.slot0) == (main.src_sel, main.out, main.slot0) and l.grid[0] == a.n_long
-            entries, rows, slots = got[(a.src_sel, a.out, kind, drop)]
+            entries, rows, slots, chunks = got[(a.src_sel, a.out, kind, drop)]
+            assert len(chunks[-1]) <= 1 or l.grid[0] <= most
             for r in range(a.n_long):
                 row, s0, ns = (int(_arr(p + 4 * r, 1, "u4")[0]) for p in (a.lr_row, a.lr_slot0, a.lr_nslots))
                 c, ns = ns >> 24, ns & 0xffffff
@@ -182,7 +186,8 @@ def _stage(variant, dims, chunk_ptr, row_ptr, col, bf16):
 
 
 def _pass(rt, variant, dims, K, n, deg, hub, bf16):
-    """Aggregations of a whole pass that gathered what they should: [forward, backward, historical, all entries]."""
+    """Aggregations of a whole pass that gathered what they should: [forward, backward, historical, all entries], and the launches that
+    each was served in."""
     rng = np.random.default_rng(n + K)
     cols = [np.unique(np.concatenate([[v], rng.integers(0, n, deg if v % 37 else hub)])) for v in range(n)]
     cols[3 % n] = np.zeros(0, np.int64)
@@ -206,11 +211,11 @@ def _pass(rt, variant, dims, K, n, deg, hub, bf16):
     pairs = lambda on: sorted(zip(col[on].tolist(), rows[on].tolist()))
     want = [sorted(zip(rows.tolist(), col.tolist())), pairs(current), pairs(~current), pairs(col >= 0)]
     seen = [0, 0, 0, 0]
-    for (_, _, kind, drop), (entries, done, _) in got.items():
+    for (_, _, kind, drop), (entries, done, _, _) in got.items():
         which = kind if kind else 3 if drop else 0
         assert sorted(entries) == want[which] and sorted(done) == list(range(n))
         seen[which] += 1
-    return seen
+    return seen, [len(chunks) for _, _, _, chunks in got.values()]
 
 
 if __name__ == "__main__":
@@ -229,6 +234,13 @@ if __name__ == "__main__":
     os._exit(0)
 
 
+def _run(runtime, env, *args):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), runtime, json.dumps(args)], capture_output=True, text=True, timeout=300,
+                       env={**os.environ, **env})
+    assert r.returncode == 0, r.stderr[-2000:]
+    return json.loads(r.stdout.splitlines()[-1])
+
+
 @pytest.mark.parametrize("variant,dims,bf16,seen", [
     ("gcn", [24, 24, 24], 0, [2, 2, 0, 0]), ("gcn", [64, 32, 40], 1, [2, 2, 1, 0]), ("sage", [32, 32, 32], 1, [2, 2, 0, 0]), ("resgcn", [32] * 4, 0, [3, 3, 3, 0])])
 @pytest.mark.parametrize("K,n,deg,hub,env", [
@@ -237,7 +249,14 @@ if __name__ == "__main__":
 def test_a_pass_gathers_every_entry_once(runtime, variant, dims, bf16, seen, K, n, deg, hub, env):
     """Every aggregation of a whole pass finishes every row once and gathers what its rows' chunks select, once: ragged and empty
     chunks, hubs cut by length and by source class, classes that a chunk gathers nothing from, short rows, more than 64 chunks."""
-    r = subprocess.run([sys.executable, os.path.abspath(__file__), runtime, json.dumps([variant, dims, K, n, deg, hub, bf16])], capture_output=True, text=True,
-                       timeout=300, env={**os.environ, **env})
-    assert r.returncode == 0, r.stderr[-2000:]
-    assert json.loads(r.stdout.splitlines()[-1]) == seen
+    got, launches = _run(runtime, env, variant, dims, K, n, deg, hub, bf16)
+    assert got == seen and set(launches) == {1}
+
+
+@pytest.mark.parametrize("variant,dims,bf16,seen", [
+    ("gcn", [24, 24, 24], 0, [2, 2, 0, 0]), ("gcn", [64, 32, 40], 1, [2, 2, 1, 0]), ("resgcn", [32] * 4, 0, [3, 3, 3, 0])])
+@pytest.mark.parametrize("K,n,env", [(7, 700, {"GNNSTAGE_LAUNCH_BLOCKS": "90"}), (70, 900, {"GNNSTAGE_LAUNCH_BLOCKS": "60"}), (5, 700, {"GNNSTAGE_LAUNCH_BLOCKS": "1"})])
+def test_a_layer_in_several_launches(runtime, variant, dims, bf16, seen, K, n, env):
+    """A layer that is too much for one launch is served in several runs of chunks, one chunk at least: the same rows and entries."""
+    got, launches = _run(runtime, env, variant, dims, K, n, 5, 300, bf16)
+    assert got == seen and min(launches) > 1

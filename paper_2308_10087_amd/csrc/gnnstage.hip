@@ -1120,7 +1120,7 @@ struct LnSums {
     return GNNSTAGE_OK;
   }
 };
-// Backward of layer j's LayerNorm over the rows of a span whose chunks are not in `without`: x = level rows, dr (n rows of ld_j)
+// Backward of layer j's LayerNorm over the rows of a span but those of chunk `without` (-1: all): x = level rows, dr (n rows of ld_j)
 // the gradient of the activated rows, out (leading dimension out_ld, indexed by absolute row, or NULL) the gradient of x, res (n rows of ld_{j+1} or NULL)
 // the residual branch.
 int ln_backward(gnnstage *st, LnSums &sums, const std::vector<void *> &level, int j, const Span &sp, int without, const char *dr, char *out, int out_dtype, int out_ld,
@@ -1128,15 +1128,21 @@ int ln_backward(gnnstage *st, LnSums &sums, const std::vector<void *> &level, in
   const Shape &s = st->s;
   const size_t celt = s.elt();
   LnBackArgs l[kBatch];
-  const int n_groups = std::min(sp.c1 - sp.c0, kBatch), max_waves = kLnMaxWaves / n_groups / 4 * 4;
+  // runs of chunks in front of `without` and behind it: a group has rows of one of them
+  const int mid = without < 0 ? sp.c1 : without, behind = without < 0 ? sp.c1 : without + 1, ahead = mid - sp.c0, rest = sp.c1 - behind;
+  const int n_groups = std::min(ahead + rest, kBatch);
+  if (n_groups == 0) return GNNSTAGE_OK;
+  int n_ahead = (2 * n_groups * ahead + ahead + rest) / (2 * (ahead + rest));  // rounded share, both sides at least one of theirs
+  n_ahead = std::max(std::min(n_ahead, n_groups - (rest > 0 ? 1 : 0)), ahead > 0 ? 1 : 0);
+  const int max_waves = kLnMaxWaves / n_groups / 4 * 4;
   float *scratch = st->at<float>(st->lay.ln_partial) + (size_t)sums.n_layers * st->lay.ln_stride;
-  int n = 0;
   for (int g = 0; g < n_groups; ++g) {
-    const int a = sp.c0 + (int)((int64_t)(sp.c1 - sp.c0) * g / n_groups), b = sp.c0 + (int)((int64_t)(sp.c1 - sp.c0) * (g + 1) / n_groups);
-    const int64_t row0 = s.chunk_ptr[(size_t)a], M = s.chunk_ptr[(size_t)b] - row0;
-    LnBackArgs &x = l[n++];
+    const bool front = g < n_ahead;
+    const int c0 = front ? sp.c0 : behind, count = front ? ahead : rest, i = front ? g : g - n_ahead, of = front ? n_ahead : n_groups - n_ahead;
+    const int64_t row0 = s.chunk_ptr[(size_t)(c0 + count * i / of)], M = s.chunk_ptr[(size_t)(c0 + count * (i + 1) / of)] - row0;
+    LnBackArgs &x = l[g];
     x = LnBackArgs{};
-    x.f = ln_args(st, level, j, row0, a == without && b == a + 1 ? 0 : M, out ? out + (size_t)row0 * out_ld * (out_dtype == DT_BF16 ? 2 : 4) : nullptr, out_dtype, out_ld);
+    x.f = ln_args(st, level, j, row0, M, out ? out + (size_t)row0 * out_ld * (out_dtype == DT_BF16 ? 2 : 4) : nullptr, out_dtype, out_ld);
     x.dr = dr + (size_t)row0 * s.ld[j] * celt;
     x.dr_dtype = st->cdtype();
     x.dr_ld = s.ld[j];
@@ -1147,7 +1153,7 @@ int ln_backward(gnnstage *st, LnSums &sums, const std::vector<void *> &level, in
     x.dgamma = st->d_ln_g[j];
     x.dbeta = st->d_ln_b[j];
   }
-  HIP_TRY(st, launch_ln_relu_backward(l, n, max_waves, sums.red[sums.n_layers], stream));
+  HIP_TRY(st, launch_ln_relu_backward(l, n_groups, max_waves, sums.red[sums.n_layers], stream));
   sums.n_groups = n_groups;
   sums.n_layers += 1;
   return !sp.whole || sums.n_layers == st->lay.ln_layers ? sums.add_up(st, stream) : (int)GNNSTAGE_OK;
@@ -1418,6 +1424,7 @@ int finish_transform_first(gnnstage *st, hipStream_t stream) {
 int res_backward_finish(gnnstage *st, hipStream_t stream) {
   const Shape &s = st->s;
   const int cd = st->cdtype();
+  if (s.K == 1) return GNNSTAGE_OK;  // no row was read as a historical one
   std::vector<Span> spans;
   const int rc = finish_spans(st, true, spans, stream);
   if (rc != GNNSTAGE_OK) return rc;
@@ -1435,7 +1442,7 @@ int res_backward_finish(gnnstage *st, hipStream_t stream) {
       a.epilogue = SPMM_PLAIN;
       HIP_TRY(st, run_spmm(st, a, cd, cd, true, sp, span_select(st, sp, SEL_EARLIER), stream, 2, j));
       Timed t(st, stream, 4, j);
-      // no row of the chunk that came first was read as a historical one
+      // no row of the chunk that came first was read as a historical one: it may hold anything, also what times zero is no number
       const int e = ln_backward(st, sums, st->hist, j, sp, st->order[0], st->at<char>(st->lay.Th[j]), nullptr, cd, 0, nullptr, stream);
       if (e != GNNSTAGE_OK) return e;
     }

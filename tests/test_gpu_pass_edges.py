@@ -167,3 +167,23 @@ def test_more_elements_than_a_grid_has_threads():
     assert torch.equal(level, cur[1]) and torch.equal(back, grad_in)
     kept = (level[-4000:] > 0).float().mean().item()  # half of what passes ReLU
     assert 0.2 < kept < 0.3
+
+
+@pytest.mark.parametrize("dtype,width", [("f32", 36), ("bf16", 128)])
+@pytest.mark.parametrize("k,first", [(1, 0), (2, 1), (9, 0), (9, 4), (9, 8), (32, 13)])
+def test_history_that_nobody_reads_may_hold_anything(k, first, dtype, width):
+    """The rows of the chunk that comes first in the order are never read as historical ones, also not by the LayerNorm parameters'
+    gradients: rows that hold no numbers there leave every result as it is."""
+    p = make_problem(small(n=900, k=k, dims=(width,) * 4, variant="resgcn", dtype=dtype, deg=9.0), bias_std=0.05, first_stage=False)
+    p.order = np.roll(np.arange(k, dtype=np.int32), -first)
+    runs = [GpuRun(p), GpuRun(p)]
+    for h in runs[1].hist:
+        h[runs[1].stage.rows(first)] = float("nan")
+    for r in runs:
+        r.run()
+    a, b = runs
+    for x, y in zip(a.cur + [a.grad_in] + a.dW + a.d_ln_gamma + a.d_ln_beta, b.cur + [b.grad_in] + b.dW + b.d_ln_gamma + b.d_ln_beta):
+        assert torch.equal(x, y)
+    ref = run_oracle(p)
+    tol = TOL_F32 if dtype == "f32" else TOL_BF16
+    assert max(max_rel(b.np(x), y) for x, y in zip(b.d_ln_gamma + b.d_ln_beta, ref.d_ln_g + ref.d_ln_b)) <= tol

@@ -78,6 +78,9 @@ __global__ __launch_bounds__(256) void ln_relu_kernel(const LnArgs a) {
 // dr -> dx (+ res) for the rows of the launch; the column sums of the parameter gradients are added over the
 // four wavefronts of a workgroup in LDS and go to partial[workgroup][0][c] (gamma) and partial[workgroup][1][c]
 // (beta); ln_param_reduce_kernel adds those in a fixed order.
+// A wavefront adds kLnChain rows in one chain and then to its sums in LDS: over all rows of a layer a wavefront has hundreds (8 M rows
+// in 32 chunks: 977), whose one chain was off 64 bits by 5.2e-7 of the root of the sum of squares; in chains of 32 it is 1.8e-7.
+constexpr int kLnChain = 32;
 template <int NI>
 __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBackArgs> ba) {
   const LnBackArgs b = ba.sub[blockIdx.z];
@@ -93,7 +96,7 @@ __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBac
   const int x_dtype = a.x_dtype, x_ld = a.x_ld, d = a.d, out_dtype = a.out_dtype, out_ld = a.out_ld;
   const int dr_dtype = b.dr_dtype, dr_ld = b.dr_ld, res_dtype = b.res_dtype, res_ld = b.res_ld;
   const LnDropout dp = a.drop;
-  __shared__ float red[3][2][NI * 64];
+  __shared__ float red[4][2][NI * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t w0 = (int64_t)block * 4 + (threadIdx.x >> 6), nw = (int64_t)blocks * 4;
   float dg[NI], db[NI], gam[NI], bet[NI];
@@ -104,7 +107,21 @@ __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBac
     gam[i] = c < d ? gamma[c] : 0.f;
     bet[i] = c < d ? beta[c] : 0.f;
   }
+  int chain = 0;
+  bool waiting = false;  // earlier chains' sums wait in LDS
   for (int64_t r = w0; r < M; r += nw) {
+    if (chain == kLnChain) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        float *g = &red[wave][0][lane + 64 * i], *b = &red[wave][1][lane + 64 * i];
+        *g = waiting ? *g + dg[i] : dg[i];
+        *b = waiting ? *b + db[i] : db[i];
+        dg[i] = db[i] = 0.f;
+      }
+      waiting = true;
+      chain = 0;
+    }
+    ++chain;
     float xh[NI], dxh[NI];
     float sum = 0.f;
 #pragma unroll
@@ -156,12 +173,15 @@ __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBac
       }
     }
   }
-  if (wave > 0) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      red[wave - 1][0][lane + 64 * i] = dg[i];
-      red[wave - 1][1][lane + 64 * i] = db[i];
+  for (int i = 0; i < NI; ++i) {
+    float *g = &red[wave][0][lane + 64 * i], *b = &red[wave][1][lane + 64 * i];
+    if (waiting) {
+      dg[i] += *g;
+      db[i] += *b;
     }
+    *g = dg[i];
+    *b = db[i];
   }
   __syncthreads();
   if (wave == 0) {
@@ -169,8 +189,8 @@ __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBac
     for (int i = 0; i < NI; ++i) {
       const int c = lane + 64 * i;
       if (c < d) {
-        partial[((size_t)block * 2 + 0) * d + c] = ((dg[i] + red[0][0][c]) + red[1][0][c]) + red[2][0][c];
-        partial[((size_t)block * 2 + 1) * d + c] = ((db[i] + red[0][1][c]) + red[1][1][c]) + red[2][1][c];
+        partial[((size_t)block * 2 + 0) * d + c] = ((dg[i] + red[1][0][c]) + red[2][0][c]) + red[3][0][c];
+        partial[((size_t)block * 2 + 1) * d + c] = ((db[i] + red[1][1][c]) + red[2][1][c]) + red[3][1][c];
       }
     }
   }
@@ -249,7 +269,7 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<L
   const int x_ld = a.x_ld, out_ld = a.out_ld, dr_ld = b.dr_ld, res_ld = b.res_ld;
   const LnDropout dp = a.drop;
   constexpr int RPW = 64 / LPR, d = LPR * 8;
-  __shared__ float red[3][2][LPR * 8];
+  __shared__ float red[4][2][RPW][LPR * 8];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane % LPR, rw = lane / LPR;
   const int64_t w0 = (int64_t)block * 4 + (threadIdx.x >> 6), nw = (int64_t)blocks * 4;
   float gam[8], bet[8], dg[8], db[8];
@@ -259,7 +279,21 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<L
     bet[t] = beta[sub * 8 + t];
     dg[t] = db[t] = 0.f;
   }
+  int chain = 0;
+  bool waiting = false;
   for (int64_t r0 = w0 * RPW; r0 < M; r0 += nw * RPW) {
+    if (chain == kLnChain) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        float *g = &red[wave][0][rw][sub * 8 + t], *b = &red[wave][1][rw][sub * 8 + t];
+        *g = waiting ? *g + dg[t] : dg[t];
+        *b = waiting ? *b + db[t] : db[t];
+        dg[t] = db[t] = 0.f;
+      }
+      waiting = true;
+      chain = 0;
+    }
+    ++chain;
     const int64_t r = r0 + rw;
     const bool on = r < M;
     const int64_t rr = on ? r : M - 1;
@@ -310,6 +344,10 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<L
   // column sums: over the row groups of the wavefront (fixed order), then over the four wavefronts in LDS
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
+    if (waiting) {
+      dg[t] += red[wave][0][rw][sub * 8 + t];
+      db[t] += red[wave][1][rw][sub * 8 + t];
+    }
 #pragma unroll
     for (int o = LPR; o < 64; o <<= 1) {
       dg[t] += __shfl_xor(dg[t], o);
@@ -319,8 +357,8 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<L
   if (wave > 0 && rw == 0) {
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-      red[wave - 1][0][sub * 8 + t] = dg[t];
-      red[wave - 1][1][sub * 8 + t] = db[t];
+      red[wave][0][0][sub * 8 + t] = dg[t];
+      red[wave][1][0][sub * 8 + t] = db[t];
     }
   }
   __syncthreads();
@@ -328,8 +366,8 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<L
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       const int c = sub * 8 + t;
-      partial[((size_t)block * 2 + 0) * d + c] = ((dg[t] + red[0][0][c]) + red[1][0][c]) + red[2][0][c];
-      partial[((size_t)block * 2 + 1) * d + c] = ((db[t] + red[0][1][c]) + red[1][1][c]) + red[2][1][c];
+      partial[((size_t)block * 2 + 0) * d + c] = ((dg[t] + red[1][0][0][c]) + red[2][0][0][c]) + red[3][0][0][c];
+      partial[((size_t)block * 2 + 1) * d + c] = ((db[t] + red[1][1][0][c]) + red[2][1][0][c]) + red[3][1][0][c];
     }
   }
 }

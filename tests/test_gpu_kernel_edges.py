@@ -199,3 +199,30 @@ def test_passes_that_cannot_run_whole_behave_like_the_chunk_calls():
     with pytest.raises(g.GnnStageError) as e:
         st.backward_pass([1, 0, 2, 3, 4][::-1], runs[0].grad_out)
     assert e.value.code == -3
+
+
+@pytest.mark.parametrize("n,k,d,dtype,bound", [(8_000_000, 32, 64, "f32", 3.4e-7), (8_000_000, 9, 100, "f32", 3.4e-7), (4_000_000, 9, 512, "bf16", 3.4e-7)])
+def test_layernorm_gradients_over_all_rows_against_64_bits(n, k, d, dtype, bound):
+    """Rows over self-loops of weight 1 behind a unit weight, every activation above zero: the gradient of a LayerNorm's offset is the sum
+    of the upstream rows, that of its scale their products with the normalised rows.  Errors relative to the root of the sum of
+    squares: a wavefront's rows in one chain came to 5e-7 - 6e-7.  A chain of m terms of random sign adds the root of m / 2
+    roundings of 0.4 x 2^-23 or less; 32 rows, 31 chains, 4 wavefronts, 16 parts of 16 each, 8 groups make 107: 3.4e-7."""
+    import paper_2308_10087_amd as g
+    dev, T = "cuda:0", torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device=dev).manual_seed(n + k)
+    x, up = (torch.randn((n, d), generator=gen, device=dev).to(T) for _ in range(2))
+    dg, db, dbias = (torch.zeros(d, device=dev) for _ in range(3))
+    st = g.GnnStage(np.arange(n + 1, dtype=np.int64), np.arange(n, dtype=np.int32), np.arange(k + 1, dtype=np.int64) * n // k, [d, d], W=[torch.eye(d, device=dev).to(T)],
+                    cur=[x, torch.zeros_like(x)], hist=[x.clone()], dW=[torch.zeros((d, d), device=dev)], bias=[torch.zeros(d, device=dev)], dbias=[dbias],
+                    edge_val=np.ones(n, np.float32), variant=g.GNNSTAGE_RESGCN, dtype=g.GNNSTAGE_F32 if dtype == "f32" else g.GNNSTAGE_BF16,
+                    grad_in=torch.zeros_like(x), ln_gamma=[torch.ones(d, device=dev)], ln_beta=[torch.full((d,), 20.0, device=dev)], d_ln_gamma=[dg], d_ln_beta=[db], device=dev)
+    st.forward_pass(np.arange(k))
+    st.backward_pass(np.arange(k), up)
+    torch.cuda.synchronize()
+    sums = torch.zeros((4, d), dtype=torch.float64, device=dev)
+    for i in range(0, n, 500_000):
+        xd, ud = x[i:i + 500_000].double(), up[i:i + 500_000].double()
+        terms = (xd - xd.mean(1, keepdim=True)) / (xd.var(1, unbiased=False, keepdim=True) + 1e-5).sqrt() * ud
+        sums += torch.stack([ud.sum(0), ud.square().sum(0), terms.sum(0), terms.square().sum(0)])
+    for got, total, squares in ((db, sums[0], sums[1]), (dg, sums[2], sums[3])):
+        assert ((got.double() - total) / squares.sqrt()).square().mean().sqrt().item() <= bound

@@ -114,7 +114,12 @@ typedef struct {
   void *const *bias;   /* n_layers fp32 vectors d_{j+1}; GCN only (NULL for GCNII) */
   void *const *cur;    /* n_layers + 1; n x d_j.  The caller fills level-0 rows of chunk c before
                           stage_forward_chunk(c); the library writes rows of c at levels 1..L */
-  void *const *hist;   /* n_layers (levels 0..L-1); hist[0] may alias cur[0] (first stage) */
+  void *const *hist;   /* n_layers (levels 0..L-1); hist[0] may alias cur[0] (first stage, whose features never
+                          change).  A level that is computed may be its own history too (of a stage that hands
+                          a gradient down also level 0): what a chunk does not select are then the rows of the
+                          last pass, as long as they are there.  On the way back they are not: the gradients of
+                          LayerNorm parameters and of the weights of layers that transform first
+                          (gnnstage_layer_order) take this pass's rows in their place. */
   const void *h0;      /* DEVICE n x d, GCNII only */
   float *const *dW;    /* n_layers fp32 d_j x d_{j+1}; "+=" over the backward calls; caller zeroes */
   float *const *dbias; /* n_layers fp32 d_{j+1}; "+="; GCN only */

@@ -1203,6 +1203,12 @@ int begin_forward(gnnstage *st, const std::vector<int32_t> *order, hipStream_t s
   return GNNSTAGE_OK;
 }
 
+// Whether level j never changes: a first stage's input that is its own history.  One table of its rows then serves as current and as
+// historical ones.  (A level that is its own history and is computed - above 0, or level 0 of a stage that hands a gradient
+// down - holds rows of this pass and of the last one: what is made of the historical rows when the pass begins, and of a
+// chunk's current rows with the chunk, are two tables.)
+bool constant_level(const gnnstage *st, int j) { return j == 0 && !st->s.need_input_grad && st->hist[0] == st->cur[0]; }
+
 // Layer j of a span's chunks (which have rows).  The chunks of a whole pass go side by side: layer j of a chunk reads rows of
 // level j alone, of the chunks processed up to its own the current ones and of the others the historical ones, whatever has been computed of
 // the levels above; so a pass is one round of launches per layer, not per chunk and layer, and a launch's rows gather from the
@@ -1216,7 +1222,7 @@ int forward_layer(gnnstage *st, int j, const Span &sp, hipStream_t stream) {
   const int cd = st->cdtype();
   const size_t celt = s.elt();
   const int64_t row0 = span_row0(st, sp), M = span_rows(st, sp);
-  const bool shared = st->hist[j] == st->cur[j];  // the level never changes: one table of its rows serves both
+  const bool shared = constant_level(st, j);
   if (!shared && s.res()) {
     Timed t(st, stream, 1, j);
     HIP_TRY(st, launch_ln_relu(ln_args(st, st->cur, j, row0, M, st->at<char>(st->lay.Tc[j]) + (size_t)row0 * s.ld[j] * celt, cd, s.ld[j]), stream));
@@ -1395,7 +1401,7 @@ int finish_transform_first(gnnstage *st, hipStream_t stream) {
   std::vector<Span> spans;
   for (int j = 0; j < s.L; ++j) {
     if (!s.tf[j]) continue;
-    const bool all = st->hist[j] == st->cur[j] && j == 0 && !s.need_input_grad;
+    const bool all = constant_level(st, j);
     const int rc = finish_spans(st, !all, spans, stream);
     if (rc != GNNSTAGE_OK) return rc;
     for (const Span &sp : spans) {
@@ -1479,7 +1485,7 @@ int backward_layer(gnnstage *st, LnSums &sums, int j, const Span &sp, hipStream_
   const int cd = st->cdtype();
   const size_t celt = s.elt();
   const int64_t row0 = span_row0(st, sp), M = span_rows(st, sp);
-  const bool defer = s.defer_wgrad(), need_prev = j > 0 || s.need_input_grad, shared = st->hist[j] == st->cur[j];
+  const bool defer = s.defer_wgrad(), need_prev = j > 0 || s.need_input_grad;
   char *const dY = dY_rows(st, row0, j);
   // where the gradient of level j goes: leading dimension, type, first row (of all rows, or of the span's alone)
   const int prev_ld = j > 0 ? s.ld[j] : s.dims[0], prev_dtype = st->level_dtype(j);
@@ -1532,8 +1538,8 @@ int backward_layer(gnnstage *st, LnSums &sums, int j, const Span &sp, hipStream_
     }
   }
   // ---- transposed aggregation; Section 3.4: nothing flows back from unprocessed vertices
-  // transform first: see below; nothing else depends on dT_cur when the level is shared and has no gradient.
-  if (s.tf[j] ? shared && !need_prev : !s.res() && !need_prev) {
+  // transform first: see below; nothing else depends on dT_cur of a level that never changes.
+  if (s.tf[j] ? constant_level(st, j) : !s.res() && !need_prev) {
     if (!defer && !s.tf[j]) st->gi ^= 1;
     return GNNSTAGE_OK;
   }

@@ -193,7 +193,7 @@ def test_sgd_epochs_with_empty_chunks_and_shuffling():
     assert set(firsts) <= {0, 2}, firsts
 
 
-@pytest.mark.parametrize("variants", [("gcn", "gcn"), ("sage", "sage")])
+@pytest.mark.parametrize("variants", [("gcn", "gcn"), ("sage", "sage"), ("gcn", "resgcn")])
 def test_a_later_stage_whose_history_is_the_level_below_it(variants):
     """hist[0] of the second stage is the buffer that the first one writes: what a chunk does not select are rows of the last
     epoch, which are there only as long as the chunks go through both stages one after the other."""

@@ -69,7 +69,7 @@ def _load():
 
     if not os.path.exists(_LIB_PATH):
         raise ImportError(
-            f"{_LIB_PATH} is missing: build it with `python -m paper_2308_10087_amd.build` "
+            f"{_LIB_PATH} is missing: build it with `python {os.path.join(os.path.dirname(_LIB_PATH), 'build.py')}` "
             "(there is no CPU fallback for the stage kernels)")
     lib = C.CDLL(_LIB_PATH)
     lib.gnnstage_version.restype = C.c_int

@@ -514,3 +514,19 @@ def test_bench_refuses_more_than_one_gpu():
     assert r.returncode != 0
     assert "ONE GPU" in r.stderr and "--gpus must be 1" in r.stderr
     assert r.stdout.strip() == ""  # no result line
+
+
+def test_the_command_that_a_missing_library_asks_for_runs(tmp_path):
+    """Without the library the package does not import; what the message says to run must not need the package."""
+    import shutil
+    import subprocess
+    import sys
+    src = os.path.dirname(os.path.abspath(_lib().__file__))
+    pkg = tmp_path / os.path.basename(src)
+    shutil.copytree(src, pkg, ignore=shutil.ignore_patterns("*.so", "*.o", "_build", "__pycache__"))
+    r = subprocess.run([sys.executable, "-c", f"import {pkg.name}"], cwd=tmp_path, capture_output=True, text=True)
+    assert r.returncode != 0 and "is missing" in r.stderr
+    command = r.stderr.split("`")[1].split()
+    assert command[0] == "python"
+    r = subprocess.run([sys.executable, *command[1:]], cwd=tmp_path, capture_output=True, text=True, env={**os.environ, "HIPCC": shutil.which("true")})
+    assert r.returncode == 0 and "built" in r.stdout, r.stderr

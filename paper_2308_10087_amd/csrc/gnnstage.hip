@@ -49,6 +49,7 @@ std::string g_create_error;
 //   GNNSTAGE_HOT_MIN_ROW              rows from this length on are cut by hotness class
 //   GNNSTAGE_SHORT_ROW (0 = off, up to 16)   whole rows of at most this many entries are served a row per 16-lane group
 //   GNNSTAGE_LAUNCH_BLOCKS            workgroups that one aggregation launch over several chunks may have
+//   GNNSTAGE_PARTIAL_ROOM             bytes for partial rows, and as many for dense tiles, beyond those of the largest chunk
 struct Tuning {
   int split_edges = 0;          // 0: from the launch size
   int xcd_classes = 0;          // 0: from the size of the gathered table
@@ -69,6 +70,7 @@ struct Tuning {
   // whole rows of at most this many entries are served four to a wave (0: none; -1: see Shape::short_row)
   int short_row = -1;
   int64_t launch_blocks = kMostBlocks;
+  int64_t partial_room = -1;    // -1: see make_layout
 };
 
 Tuning read_tuning() {
@@ -92,6 +94,7 @@ Tuning read_tuning() {
   if ((e = getenv("GNNSTAGE_HOT_MIN_ROW")) && atoi(e) >= 1) t.hot_min_row = atoi(e);
   if ((e = getenv("GNNSTAGE_SHORT_ROW")) && atoi(e) >= 0) t.short_row = std::min(atoi(e), kShortRowMost);
   if ((e = getenv("GNNSTAGE_LAUNCH_BLOCKS")) && atoll(e) >= 1) t.launch_blocks = std::min<int64_t>(atoll(e), kMostBlocks);
+  if ((e = getenv("GNNSTAGE_PARTIAL_ROOM")) && atoll(e) >= 0) t.partial_room = atoll(e);
   return t;
 }
 
@@ -665,7 +668,7 @@ Layout make_layout(const Shape &s, const HostDir &hf, const HostDir &hb, bool ra
   const int64_t one_items = std::max(hf.max_items, hb.max_items), one_slots = std::max(hf.pc.max_slots, hb.pc.max_slots);
   const Layout one = layout_for(s, hf, hb, rank1, one_items, one_slots);
   const int64_t all_items = (int64_t)std::max(hf.item_rb.size(), hb.item_rb.size()), all_slots = std::max(hf.pc.total_slots, hb.pc.total_slots);
-  const size_t half = std::max<size_t>((size_t)1 << 30, one.total / 16) / 2;
+  const size_t half = s.tune.partial_room >= 0 ? (size_t)s.tune.partial_room : std::max<size_t>((size_t)1 << 30, one.total / 16) / 2;
   int widest = 1;
   for (const int d : s.dims) widest = std::max(widest, d);
   const int64_t item_room = (int64_t)(half / (sizeof(float) * kDenseRB * (size_t)s.dense_width())), slot_room = (int64_t)(half / (sizeof(float) * (size_t)widest));

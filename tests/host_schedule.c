@@ -4,16 +4,16 @@
 #undef hipLaunchKernel
 
 static uint8_t (*operands)[4096];
-static size_t cap_operands, spmm_bytes, table_bytes;
+static size_t cap_operands, spmm_bytes, table_bytes, dense_bytes;
 
-void host_operand_bytes(size_t spmm, size_t tables) { spmm_bytes = spmm, table_bytes = tables; }
+void host_operand_bytes(size_t spmm, size_t tables, size_t dense) { spmm_bytes = spmm, table_bytes = tables, dense_bytes = dense; }
 const uint8_t *host_operands(size_t i) { return operands[i]; }
 int hipLaunchKernel(const void *f, grid_t grid, grid_t block, void **args, size_t smem, void *stream) {
   const size_t at = n_list;
   const int rc = listed_launch(f, grid, block, args, smem, stream);
   if (rc != 0) return rc;
   if (at >= cap_operands) operands = realloc(operands, (cap_operands = at + 256) * sizeof *operands);
-  if (strstr(list[at].name, "spmm") && !strstr(list[at].name, "dense")) memcpy(operands[at], args[0], spmm_bytes);
+  if (strstr(list[at].name, "spmm")) memcpy(operands[at], args[0], strstr(list[at].name, "dense") ? dense_bytes : spmm_bytes);
   if (strstr(list[at].name, "stage_weights")) memcpy(operands[at], args[0], table_bytes);
   return 0;
 }

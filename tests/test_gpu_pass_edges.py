@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from gpu_harness import GpuRun, GpuTrainRun
+from synth.configs import Workload
 from helpers import make_problem, make_train_problem, max_rel, run_oracle
 from test_gpu_kernel_edges import _whole_equals_chunks
 from test_gpu_parity import TOL_BF16, TOL_F32, _parity, small
@@ -138,6 +139,24 @@ def test_a_layer_that_is_too_much_for_one_launch(k, blocks, variant, dtype, dims
     monkeypatch.setenv("GNNSTAGE_LAUNCH_BLOCKS", str(blocks))
     monkeypatch.setenv("GNNSTAGE_CLASS_MIN_ROW", "24")
     _whole_equals_chunks(make_problem(small(n=1111, k=k, dims=dims, variant=variant, dtype=dtype, deg=14.0), bias_std=0.05, first_stage=False, noise_std=0.3))
+
+
+@pytest.mark.parametrize("variant,dtype,dims,dense", [
+    ("gcn", "bf16", (128, 256, 128), True), ("resgcn", "bf16", (128,) * 3, True), ("sage", "bf16", (128, 128), True), ("gcn", "f32", (36, 40, 24), False), ("gcnii", "bf16", (64,) * 3, False)])
+@pytest.mark.parametrize("k,room", [(7, 0), (7, 300000), (70, 0), (70, 300000)])
+def test_a_layer_whose_partial_sums_have_no_room_together(k, room, variant, dtype, dims, dense, monkeypatch):
+    """A layer in several launches, one behind the other through the same scratch: the bits of the chunk calls, the oracle's values."""
+    monkeypatch.setenv("GNNSTAGE_PARTIAL_ROOM", str(room))
+    monkeypatch.setenv("GNNSTAGE_CLASS_MIN_ROW", "24")
+    if dense:
+        monkeypatch.setenv("GNNSTAGE_DENSE_MIN_ENTRIES", "0")
+        monkeypatch.setenv("GNNSTAGE_DENSE_MIN_SHARE", "0")
+        monkeypatch.setenv("GNNSTAGE_DENSE_MIN_NNZ", "12")
+    w = Workload("room", "rmat", 1201, 91, list(dims), k, variant=variant, dtype=dtype, n_candidates=20_000)
+    p = make_problem(w, bias_std=0.05, first_stage=False, noise_std=0.3)
+    assert (GpuRun(p).stage.gnnstage_dense_entries(True) > 0) == dense
+    _whole_equals_chunks(p)
+    _parity(p, TOL_F32 if dtype == "f32" else TOL_BF16)
 
 
 def test_more_elements_than_a_grid_has_threads():

@@ -35,6 +35,12 @@ class _Spmm(C.Structure):  # SpmmArgs
                 ("d", I32), ("src_ld", I32), ("vbits", I32), ("many_chunks", I32), ("pass_", P), ("mask", _Mask), ("out", P), ("out_ld", I32), ("out_row0", I64)]
 
 
+class _Dense(C.Structure):  # DenseArgs
+    _fields_ = [("item_rs", P), ("item_chunk", P), ("item_b0", P), ("item_nb", P), ("item_chunks", P), ("n_items", I32), ("blk_cb", P), ("tiles", P), ("bits", P),
+                ("colscale", P), ("rowscale", P), ("zero_row", P), ("colslot", P), ("src_sel", P), ("src_unsel", P), ("d", I32), ("src_ld", I32), ("vbits", I32),
+                ("pass_", P), ("mask", _Mask), ("partial", P)]
+
+
 class _Tables(C.Structure):  # PassTableArgs
     _fields_ = [("forward", P), ("backward", P), ("earlier", P), ("K", I32), ("pos", C.c_uint8 * 256), ("classes_backward", U32 * 256), ("classes_earlier", U32 * 256)]
 
@@ -78,14 +84,18 @@ def _tasks(a, name, grid):
     return out
 
 
-def _walk(rt, first, index, chunk_ptr, order):
+def _mask_words(sees):
+    return np.array([sum(1 << k for k in range(len(sees[64 * i:64 * i + 64])) if sees[64 * i + k]) for i in range(4)], np.uint64)
+
+
+def _walk(rt, first, ptr, dense_on, chunk_ptr, order):
     """Entries gathered by the launches from `first` on, per aggregation (main launches over one source table and output, with
     their reduces): {(transposed, earlier): entries of every (row, source)}; asserts that every row is finished once."""
     K, n, got, most = len(chunk_ptr) - 1, chunk_ptr[-1], {}, int(os.environ.get("GNNSTAGE_LAUNCH_BLOCKS", 2 ** 24 - 1))
     chunk_of = np.searchsorted(chunk_ptr, np.arange(n), side="right") - 1
     pos = np.empty(K, int)
     pos[order] = np.arange(K)
-    tables = main = None
+    tables = main = dense = None
     for i in range(first, rt.host_launches()):
         l = rt.host_launch(i).contents
         if b"stage_weights" in l.name:
@@ -95,10 +105,12 @@ def _walk(rt, first, index, chunk_ptr, order):
             assert l.grid[1] == begin.n + 1
             tables = begin.tables
             assert list(tables.pos[:K]) == list(pos)
-        if b"spmm" not in l.name or b"dense" in l.name:
+        if b"spmm" not in l.name:
             continue
-        a = _Spmm.from_buffer_copy(C.string_at(rt.host_operands(i), C.sizeof(_Spmm)))
-        drop, kind = bool(a.drop_unselected), 0
+        operands = _Dense if b"dense" in l.name else _Spmm
+        a = operands.from_buffer_copy(C.string_at(rt.host_operands(i), C.sizeof(operands)))
+        drop, kind = not a.src_unsel, 0
+        assert operands is _Dense or drop == bool(a.drop_unselected)
         if a.pass_:
             kind = {tables.forward: 0, tables.backward: 1, tables.earlier: 2}[a.pass_]
         elif K == 1 and drop:  # no tables
@@ -112,6 +124,20 @@ def _walk(rt, first, index, chunk_ptr, order):
         def classes(c):
             return 0xffffffff if not a.pass_ or kind == 0 else [0, tables.classes_backward, tables.classes_earlier][kind][c]
 
+        if operands is _Dense:  # what every item (a run of 128 x 64 blocks) adds to its rows, by place in the row block; None: not run
+            dense = []
+            for t in range(a.n_items):
+                c, b0, nb = (int(_arr(p + t * s, 1, d)[0]) for p, s, d in ((a.item_chunk, 4, "i4"), (a.item_b0, 8, "i8"), (a.item_nb, 4, "i4")))
+                bits = _arr(a.bits + 1024 * b0, nb * 256, "u4").reshape(nb, 128, 2)
+                words = np.stack([_arr(a.colslot + 256 * int(cb), 64, "u4") for cb in _arr(a.blk_cb + 4 * b0, nb, "i4")])
+                on = ((bits[:, :, :, None] >> np.arange(32, dtype=np.uint32)) & 1).astype(bool).reshape(nb, 128, 64)
+                assert (words[np.nonzero(on.any(1))] != 0xffffffff).all()
+                blk, place, column = np.nonzero(on)
+                words, run = words[blk, column], (_arr(a.item_chunks + 32 * t, 4, "u8") & _mask_words(sees(c))).any()
+                kept = sees(c)[words >> a.vbits] | (not drop)
+                assert run or not drop or not kept.any()
+                dense.append((c, None if drop and not run else list(zip(place[kept].tolist(), (words[kept] & ((1 << a.vbits) - 1)).tolist()))))
+            continue
         if b"reduce" not in l.name:
             main = a
             key = (a.src_sel, a.out, kind, drop)
@@ -127,7 +153,8 @@ def _walk(rt, first, index, chunk_ptr, order):
                 chunks[-1].add(c)
                 words = _arr(a.pidx + 4 * int(e0), int(ne) & 0xffffff, "u4")
                 src, kept = words & ((1 << a.vbits) - 1), sees(c)[words >> a.vbits]
-                assert (chunk_of[src] == words >> a.vbits).all() and index[drop][0][row] <= e0 and e0 + len(src) <= index[drop][0][row + 1]
+                assert (chunk_of[src] == words >> a.vbits).all()
+                assert dense_on or (ptr[drop][row] <= e0 and e0 + len(src) <= ptr[drop][row + 1])
                 if q >= 0 and not (classes(c) >> q) & 1:
                     assert not kept.any()  # left out: nothing to gather
                     continue
@@ -139,8 +166,11 @@ def _walk(rt, first, index, chunk_ptr, order):
                     rows.append(int(row))
             assert len(chunks[-1]) <= 1 or l.grid[0] <= most
         else:
-            assert (a.src_sel, a.out, a.slot0) == (main.src_sel, main.out, main.slot0) and l.grid[0] == a.n_long
-            entries, rows, slots, chunks = got[(a.src_sel, a.out, kind, drop)]
+            assert l.grid[0] == a.n_long
+            entries, rows, slots, chunks = got.setdefault((a.src_sel, a.out, kind, drop), ([], [], set(), []))
+            if main is None or (a.src_sel, a.out, a.slot0) != (main.src_sel, main.out, main.slot0):  # cut rows alone, none of whose pieces gathers
+                slots.clear()
+                chunks.append(set())
             assert len(chunks[-1]) <= 1 or l.grid[0] <= most
             for r in range(a.n_long):
                 row, s0, ns = (int(_arr(p + 4 * r, 1, "u4")[0]) for p in (a.lr_row, a.lr_slot0, a.lr_nslots))
@@ -150,7 +180,15 @@ def _walk(rt, first, index, chunk_ptr, order):
                     q = int(_arr(a.slot_class + s, 1, "u1")[0])
                     ran = q >= 32 or bool((a.active_classes & classes(c)) >> q & 1) or not drop
                     assert ran == (s in slots)
+                if a.lr_ndense:
+                    nd, first, it0 = (int(_arr(p + 4 * r, 1, "i4")[0]) for p in (a.lr_ndense, a.lr_dense0, a.lr_item0))
+                    for g in range(nd):
+                        at, place = divmod(first + (g - a.item0) * 128, 128)
+                        used = not drop or (_arr(a.item_chunks + 32 * (it0 + g), 4, "u8") & _mask_words(sees(c))).any()
+                        assert dense[at][0] == c and used == (dense[at][1] is not None)
+                        entries += [(row, u) for p, u in dense[at][1] or [] if p == place]
                 rows.append(row)
+            dense = None
     return got
 
 
@@ -203,7 +241,9 @@ def _pass(rt, variant, dims, K, n, deg, hub, bf16):
     assert lib.gnnstage_forward_pass(h, order.ctypes.data, K, None) == 0
     assert lib.gnnstage_backward_pass(h, order.ctypes.data, K, grad_out, None) == 0
     t_ptr = np.concatenate([[0], np.cumsum(np.bincount(col, minlength=n))])
-    got = _walk(rt, 0, [(row_ptr, col), (t_ptr, None)], chunk_ptr, order)
+    dense_on = lib.gnnstage_dense_entries(h, 0) > 0
+    assert dense_on == (lib.gnnstage_dense_entries(h, 1) > 0) == ("GNNSTAGE_DENSE_MIN_ENTRIES" in os.environ)
+    got = _walk(rt, 0, [row_ptr, t_ptr], dense_on, chunk_ptr, order)
     rows = np.repeat(np.arange(n), np.diff(row_ptr))
     chunk_of, pos = np.searchsorted(chunk_ptr, np.arange(n), side="right") - 1, np.empty(K, int)
     pos[order] = np.arange(K)
@@ -225,8 +265,8 @@ if __name__ == "__main__":
     _rt.host_launches.restype = C.c_size_t
     _rt.host_launch.restype, _rt.host_launch.argtypes = C.POINTER(_H._Launch), [C.c_size_t]
     _rt.host_operands.restype, _rt.host_operands.argtypes = C.c_void_p, [C.c_size_t]
-    _rt.host_operand_bytes.argtypes = [C.c_size_t, C.c_size_t]
-    _rt.host_operand_bytes(C.sizeof(_Spmm), C.sizeof(_Begin))
+    _rt.host_operand_bytes.argtypes = [C.c_size_t] * 3
+    _rt.host_operand_bytes(C.sizeof(_Spmm), C.sizeof(_Begin), C.sizeof(_Dense))
     _rt.host_clear.argtypes = [C.c_int64]
     sys.path.insert(0, os.path.dirname(HERE))
     print(json.dumps(_pass(_rt, *json.loads(sys.argv[2]))))
@@ -257,8 +297,23 @@ def test_a_pass_gathers_every_entry_once(runtime, variant, dims, bf16, seen, K, 
 
 @pytest.mark.parametrize("variant,dims,bf16,seen", [
     ("gcn", [24, 24, 24], 0, [2, 2, 0, 0]), ("gcn", [64, 32, 40], 1, [2, 2, 1, 0]), ("resgcn", [32] * 4, 0, [3, 3, 3, 0])])
-@pytest.mark.parametrize("K,n,env", [(7, 700, {"GNNSTAGE_LAUNCH_BLOCKS": "90"}), (70, 900, {"GNNSTAGE_LAUNCH_BLOCKS": "60"}), (5, 700, {"GNNSTAGE_LAUNCH_BLOCKS": "1"})])
+@pytest.mark.parametrize("K,n,env", [(7, 700, {"GNNSTAGE_LAUNCH_BLOCKS": "90"}), (70, 900, {"GNNSTAGE_LAUNCH_BLOCKS": "60"}), (5, 700, {"GNNSTAGE_LAUNCH_BLOCKS": "1"}),
+                                     (7, 700, {"GNNSTAGE_PARTIAL_ROOM": "0", "GNNSTAGE_CLASS_MIN_ROW": "4"}), (70, 900, {"GNNSTAGE_PARTIAL_ROOM": "5000", "GNNSTAGE_CLASS_MIN_ROW": "4"})])
 def test_a_layer_in_several_launches(runtime, variant, dims, bf16, seen, K, n, env):
-    """A layer that is too much for one launch is served in several runs of chunks, one chunk at least: the same rows and entries."""
+    """A layer that is too much for one launch, or whose partial sums have no room together, is served in several runs of chunks, one
+    chunk at least: the same rows and entries."""
     got, launches = _run(runtime, env, variant, dims, K, n, 5, 300, bf16)
     assert got == seen and min(launches) > 1
+
+
+@pytest.mark.parametrize("variant,dims,seen", [("gcn", [128] * 3, [2, 2, 0, 0]), ("gcn", [256, 128, 256], [2, 2, 1, 0]), ("resgcn", [128] * 3, [2, 2, 2, 0])])
+@pytest.mark.parametrize("K,n,env", [(1, 400, {}), (5, 900, {}), (5, 900, {"GNNSTAGE_PARTIAL_ROOM": "0"}), (70, 1200, {"GNNSTAGE_PARTIAL_ROOM": "200000"}),
+                                     (5, 900, {"GNNSTAGE_LAUNCH_BLOCKS": "40"})])
+def test_dense_blocks_and_the_rest_gather_every_entry_once(runtime, variant, dims, seen, K, n, env):
+    """Entries that are multiplied as blocks of a dense matrix, and those that are left: items by chunk and row block, their tiles
+    in the sums of the rows that they are of, in one launch and in several."""
+    env = {"GNNSTAGE_DENSE_MIN_ENTRIES": "0", "GNNSTAGE_DENSE_MIN_SHARE": "0", "GNNSTAGE_DENSE_MIN_NNZ": "30", **env}
+    if K == 1 and variant == "resgcn":
+        seen = seen[:2] + [0, 0]
+    got, launches = _run(runtime, env, variant, dims, K, n, 8, 300, 1)
+    assert got == seen and (min(launches) > 1 if len(env) > 3 else set(launches) == {1})

@@ -112,11 +112,11 @@ struct SpmmArgs {
   XcdRun xcd[8];
   int32_t n_class_blocks;
   int64_t tail0, n_tail;
-  // Whole rows of at most a few entries (no partial slot), every chunk's filled up to a multiple of four.  The matrix-core
-  // kernel gives them to extra workgroups of the same launch in which every 16-lane group owns a row of its own: a wave per
-  // row would spend its life waiting for three dependent round trips to move a kilobyte or two.  The vector-ALU kernel and
-  // rows wider than 256 columns take them like any other task.
-  int64_t short0, n_short;
+  // Whole rows of at most a few entries (no partial slot), every chunk's filled up to a multiple of four.  From short_from of
+  // them on the matrix-core kernel gives them to extra workgroups of the same launch whose waves serve four rows each: a wave per
+  // row would spend its life waiting for three dependent round trips to move a kilobyte or two.  Fewer rows, the vector-ALU
+  // kernel and rows wider than 256 columns: a row to a wave like any other task.
+  int64_t short0, n_short, short_from;
   // The two lists' workgroups are dealt out evenly, so that the launch goes through both in about the order of their rows:
   // workgroup p behind the class pieces serves short rows if p mix crosses a whole number of 2^32 (set by the launcher).
   // First all of the one and then of the other is slower where the gathers bound the launch: 3.6 M entries of 512-byte rows

@@ -25,6 +25,11 @@ constexpr int kMaxSplits = 512;
 constexpr size_t kAlign = 256;
 // Rows of a GraphSage layer whose two products follow each other (the first one's rows are fp32 and are read by the second).
 constexpr int64_t kSelfRows = 65536;
+// Short rows of a launch, per column, from which they go four to a wave.  With fewer the rows' waves are in flight at one time, and
+// four rows one after the other only make the launch's one chain longer.  A row to a wave / four, a pass of two layers in us:
+// width 64 4 k rows 80 / 81, 8 k 92 / 91, 12 k 98 / 93; width 128 4 k 90 / 92, 8 k 97 / 98, 12 k 105 / 101; width 256 6 k 113 / 118,
+// 12 k 128 / 130, 24 k 173 / 164.  Chunk calls of 75 rows of width 256: 2,160 / 2,613 us for 40 of them.
+constexpr int64_t kShortRowsPerColumn = 64;
 
 std::string g_create_error;
 
@@ -47,7 +52,7 @@ std::string g_create_error;
 //   GNNSTAGE_HOT_CLASSES (0 = off, 2..32: on whatever the table size)   classes of the hottest sources
 //   GNNSTAGE_HOT_ROWS                 sources per such class
 //   GNNSTAGE_HOT_MIN_ROW              rows from this length on are cut by hotness class
-//   GNNSTAGE_SHORT_ROW (0 = off, up to 16)   whole rows of at most this many entries are served a row per 16-lane group
+//   GNNSTAGE_SHORT_ROW (0 = off, up to 16)   whole rows of at most this many entries are served four to a wave, however few of them
 //   GNNSTAGE_LAUNCH_BLOCKS            workgroups that one aggregation launch over several chunks may have
 //   GNNSTAGE_PARTIAL_ROOM             bytes for partial rows, and as many for dense tiles, beyond those of the largest chunk
 struct Tuning {
@@ -971,6 +976,7 @@ void set_schedule(const gnnstage *st, int dir, int c0, int c1, Select sel, const
   a.short0 = t.first(t.n_classes + 1, c0);
   a.n_short = t.count(t.n_classes + 1, c0, c1);
   a.short_valu = st->s.short_valu() ? 1 : 0;
+  a.short_from = a.short_valu || st->s.tune.short_row >= 0 ? 1 : kShortRowsPerColumn * a.d;
   a.slot_class = st->at<uint8_t>(dir ? lay.b_slot_class : lay.f_slot_class);
   const int64_t l0 = t.lr_off[(size_t)c0];
   a.lr_row = st->at<int32_t>(dir ? lay.b_lr_row : lay.f_lr_row) + l0;

@@ -53,6 +53,20 @@ def test_short_rows_are_the_bits_of_whole_waves(n, k, dims, monkeypatch):
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("n,d", [(4090, 64), (4097, 64), (8190, 128), (8193, 128)])
+def test_short_rows_go_four_to_a_wave_from_64_per_column_on(n, d, monkeypatch):
+    """On both sides of the number of short rows from which they share waves: the bits of both forms."""
+    p = make_problem(small(n=n, k=1, dims=(d, d), dtype="bf16"), graph=_graph_of_lengths(n, np.array([1, 16, 2, 15, 4, 3, 8, 5, 9, 12, 7, 13]), 7), first_stage=False, noise_std=0.3)
+    p.val[:] = np.random.default_rng(2).uniform(0.02, 0.3, p.val.size)
+    runs = []
+    for most in (None, "0", "16"):
+        monkeypatch.setenv("GNNSTAGE_SHORT_ROW", most) if most else monkeypatch.delenv("GNNSTAGE_SHORT_ROW", raising=False)
+        runs.append(GpuRun(p).run())
+    for r in runs[1:]:
+        for a, b in zip(r.cur + [r.grad_in] + r.dW, runs[0].cur + [runs[0].grad_in] + runs[0].dW):
+            assert torch.equal(a, b)
+
+
 def test_short_rows_of_tables_beyond_the_caches(monkeypatch):
     """Tables of over 256 MB: rows of up to 4 entries on the vector ALU, four to a wave.  Against a row to a wave: weights in fp32 instead
     of two bf16 parts, another order of at most 4 products, so a bf16 rounding of the result apart."""

@@ -78,10 +78,11 @@ __global__ __launch_bounds__(256) void ln_relu_kernel(const LnArgs a) {
 // dr -> dx (+ res) for the rows of the launch; the column sums of the parameter gradients are added over the
 // four wavefronts of a workgroup in LDS and go to partial[workgroup][0][c] (gamma) and partial[workgroup][1][c]
 // (beta); ln_param_reduce_kernel adds those in a fixed order.
-// A wavefront adds kLnChain rows in one chain and then to its sums in LDS: over all rows of a layer a wavefront has hundreds (8 M rows
-// in 32 chunks: 977), whose one chain was off 64 bits by 5.2e-7 of the root of the sum of squares; in chains of 32 it is 1.8e-7.
+// LONG: a wavefront adds kLnChain rows in one chain and then to its sums in LDS: over all rows of a layer a wavefront has hundreds (8 M
+// rows in 32 chunks: 977), whose one chain was off 64 bits by 5.2e-7 of the root of the sum of squares; in chains of 32 it is 1.8e-7.
+// Fewer rows: an instance without that, which a launch over a chunk of some ten thousand rows would pay 0.3 - 0.4 us for.
 constexpr int kLnChain = 32;
-template <int NI>
+template <int NI, bool LONG>
 __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBackArgs> ba) {
   const LnBackArgs b = ba.sub[blockIdx.z];
   const LnArgs &a = b.f;
@@ -110,7 +111,7 @@ __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBac
   int chain = 0;
   bool waiting = false;  // earlier chains' sums wait in LDS
   for (int64_t r = w0; r < M; r += nw) {
-    if (chain == kLnChain) {
+    if (LONG && chain == kLnChain) {
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
         float *g = &red[wave][0][lane + 64 * i], *b = &red[wave][1][lane + 64 * i];
@@ -176,12 +177,14 @@ __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBac
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
     float *g = &red[wave][0][lane + 64 * i], *b = &red[wave][1][lane + 64 * i];
-    if (waiting) {
+    if (LONG && waiting) {
       dg[i] += *g;
       db[i] += *b;
     }
-    *g = dg[i];
-    *b = db[i];
+    if (wave > 0) {
+      *g = dg[i];
+      *b = db[i];
+    }
   }
   __syncthreads();
   if (wave == 0) {
@@ -254,7 +257,7 @@ __global__ __launch_bounds__(256) void ln_relu_vec_kernel(const LnArgs a) {
   }
 }
 
-template <int LPR>
+template <int LPR, bool LONG>
 __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<LnBackArgs> ba) {
   const LnBackArgs b = ba.sub[blockIdx.z];
   const LnArgs &a = b.f;
@@ -269,7 +272,7 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<L
   const int x_ld = a.x_ld, out_ld = a.out_ld, dr_ld = b.dr_ld, res_ld = b.res_ld;
   const LnDropout dp = a.drop;
   constexpr int RPW = 64 / LPR, d = LPR * 8;
-  __shared__ float red[4][2][RPW][LPR * 8];
+  __shared__ float red[4][2][LONG ? RPW : 1][LPR * 8];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane % LPR, rw = lane / LPR;
   const int64_t w0 = (int64_t)block * 4 + (threadIdx.x >> 6), nw = (int64_t)blocks * 4;
   float gam[8], bet[8], dg[8], db[8];
@@ -282,7 +285,7 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<L
   int chain = 0;
   bool waiting = false;
   for (int64_t r0 = w0 * RPW; r0 < M; r0 += nw * RPW) {
-    if (chain == kLnChain) {
+    if (LONG && chain == kLnChain) {
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
         float *g = &red[wave][0][rw][sub * 8 + t], *b = &red[wave][1][rw][sub * 8 + t];
@@ -344,7 +347,7 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<L
   // column sums: over the row groups of the wavefront (fixed order), then over the four wavefronts in LDS
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
-    if (waiting) {
+    if (LONG && waiting) {
       dg[t] += red[wave][0][rw][sub * 8 + t];
       db[t] += red[wave][1][rw][sub * 8 + t];
     }
@@ -496,13 +499,17 @@ int launch_ln_relu_backward(const LnBackArgs *l, int n, int max_waves, LnReduceA
     if (lpr) {
       const int rpw = 64 / lpr;
       gx[i] = (unsigned)(waves_for((a.M + rpw - 1) / rpw, max_waves) / 4);
-      fn[i] = lpr == 8 ? ln_relu_backward_vec_kernel<8> : lpr == 16 ? ln_relu_backward_vec_kernel<16>
-            : lpr == 32 ? ln_relu_backward_vec_kernel<32> : ln_relu_backward_vec_kernel<64>;
+      const bool more = a.M > (int64_t)gx[i] * 4 * rpw * kLnChain;
+#define LN_VEC(L) (more ? ln_relu_backward_vec_kernel<L, true> : ln_relu_backward_vec_kernel<L, false>)
+      fn[i] = lpr == 8 ? LN_VEC(8) : lpr == 16 ? LN_VEC(16) : lpr == 32 ? LN_VEC(32) : LN_VEC(64);
+#undef LN_VEC
     } else {
       const int ni = (std::max(a.d, a.out ? a.out_ld : a.d) + 63) / 64;
       gx[i] = (unsigned)(waves_for(a.M, max_waves) / 4);
-      fn[i] = ni <= 1 ? ln_relu_backward_kernel<1> : ni <= 2 ? ln_relu_backward_kernel<2> : ni <= 4 ? ln_relu_backward_kernel<4>
-            : ni <= 8 ? ln_relu_backward_kernel<8> : ln_relu_backward_kernel<16>;
+      const bool more = a.M > (int64_t)gx[i] * 4 * kLnChain;
+#define LN_ROW(N) (more ? ln_relu_backward_kernel<N, true> : ln_relu_backward_kernel<N, false>)
+      fn[i] = ni <= 1 ? LN_ROW(1) : ni <= 2 ? LN_ROW(2) : ni <= 4 ? LN_ROW(4) : ni <= 8 ? LN_ROW(8) : LN_ROW(16);
+#undef LN_ROW
     }
     red[i] = LnReduceArgs{b.partial, (int32_t)gx[i], a.d, b.dgamma, b.dbeta};
   }

@@ -1140,7 +1140,7 @@ struct LnSums {
     return GNNSTAGE_OK;
   }
 };
-// Backward of layer j's LayerNorm over the rows of a span but those of chunk `without` (-1: all): x = level rows, dr (n rows of ld_j)
+// Backward of layer j's LayerNorm over the rows of a span but those of chunk `without` (-1, or a chunk outside of the span: all): x = level rows, dr (n rows of ld_j)
 // the gradient of the activated rows, out (leading dimension out_ld, indexed by absolute row, or NULL) the gradient of x, res (n rows of ld_{j+1} or NULL)
 // the residual branch.
 int ln_backward(gnnstage *st, LnSums &sums, const std::vector<void *> &level, int j, const Span &sp, int without, const char *dr, char *out, int out_dtype, int out_ld,
@@ -1148,6 +1148,7 @@ int ln_backward(gnnstage *st, LnSums &sums, const std::vector<void *> &level, in
   const Shape &s = st->s;
   const size_t celt = s.elt();
   LnBackArgs l[kBatch];
+  if (without < sp.c0 || without >= sp.c1) without = -1;
   // runs of chunks in front of `without` and behind it: a group has rows of one of them
   const int mid = without < 0 ? sp.c1 : without, behind = without < 0 ? sp.c1 : without + 1, ahead = mid - sp.c0, rest = sp.c1 - behind;
   const int n_groups = std::min(ahead + rest, kBatch);

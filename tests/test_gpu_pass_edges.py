@@ -220,3 +220,17 @@ def test_history_that_nobody_reads_may_hold_anything(k, first, dtype, width):
     ref = run_oracle(p)
     tol = TOL_F32 if dtype == "f32" else TOL_BF16
     assert max(max_rel(b.np(x), y) for x, y in zip(b.d_ln_gamma + b.d_ln_beta, ref.d_ln_g + ref.d_ln_b)) <= tol
+
+
+@pytest.mark.parametrize("dtype,width", [("f32", 36), ("bf16", 128)])
+@pytest.mark.parametrize("k,first", [(2, 1), (9, 4)])
+def test_timed_passes_take_the_historical_part_of_layernorm_gradients(k, first, dtype, width):
+    """While launches are timed the historical rows go chunk by chunk behind a backward pass, all chunks but the first of the order."""
+    p = make_problem(small(n=900, k=k, dims=(width,) * 4, variant="resgcn", dtype=dtype, deg=9.0), bias_std=0.05, first_stage=False)
+    p.order = np.roll(np.arange(k, dtype=np.int32), -first)
+    r = GpuRun(p)
+    r.stage.gnnstage_profile_enable(True)
+    r.run()
+    ref = run_oracle(p)
+    tol = TOL_F32 if dtype == "f32" else TOL_BF16
+    assert max(max_rel(r.np(x), y) for x, y in zip(r.d_ln_gamma + r.d_ln_beta, ref.d_ln_g + ref.d_ln_b)) <= tol

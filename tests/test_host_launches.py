@@ -86,9 +86,10 @@ def _launches(rt):
     return [rt.host_launch(i).contents for i in range(rt.host_launches())]
 
 
-def _ln_reduces(rt, tied, whole):
+def _ln_reduces(rt, tied, whole, timed):
     """Destinations (gamma, beta) of every launch that adds up LayerNorm parameter gradients, a list per launch."""
     st = _Stage("resgcn", [32] * 5, 6, tied=tied)
+    assert st.lib.gnnstage_profile_enable(st.h, int(timed)) == 0
     rt.host_clear(-1)
     if whole:
         assert st.forward() == 0 and st.backward() == 0
@@ -177,16 +178,17 @@ if __name__ == "__main__":
 
 
 # ---- tests ------------------------------------------------------------------------------------------------------
-@pytest.mark.parametrize("whole", [True, False])
+@pytest.mark.parametrize("whole,timed", [(True, False), (False, False), (True, True), (False, True)])
 @pytest.mark.parametrize("tied", [True, False])
-def test_no_launch_adds_to_a_layernorm_gradient_twice(runtime, tied, whole):
-    """Layers may share a parameter-gradient buffer (tied parameters): the cells of one launch run side by side and add without
-    atomics, so a buffer may come up once per launch; buffers of their own go together."""
-    launches = _child(runtime, "_ln_reduces", tied, whole)
-    assert sum(len(l) for l in launches) == 2 * (6 + 5) * 4  # every cell, and the historical rows of all chunks but the first
+def test_no_launch_adds_to_a_layernorm_gradient_twice(runtime, tied, whole, timed):
+    """Layers may share a parameter-gradient buffer (tied parameters): the sums of one launch run side by side and add without
+    atomics, so a buffer may come up once per launch; buffers of their own go together, unless launches are timed."""
+    launches = _child(runtime, "_ln_reduces", tied, whole, timed)
+    # the rows of every chunk and layer, and the historical rows of all chunks but the first
+    assert sum(len(l) for l in launches) == 2 * (6 + 5) * 4
     for l in launches:
         assert len(set(l)) == len(l)
-    assert tied or max(len(l) for l in launches) == 2 * 4
+    assert tied or max(len(l) for l in launches) == (2 if timed else 2 * 4)
 
 
 @pytest.mark.parametrize("variant,dims", [("resgcn", [32] * 5), ("gcn", [64, 32, 16, 8])])

@@ -1227,7 +1227,7 @@ int begin_forward(gnnstage *st, const std::vector<int32_t> *order, hipStream_t s
 // Whether level j never changes: a first stage's input that is its own history.  One table of its rows then serves as current and as
 // historical ones.  (A level that is its own history and is computed - above 0, or level 0 of a stage that hands a gradient
 // down - holds rows of this pass and of the last one: what is made of the historical rows when the pass begins, and of a
-// chunk's current rows with the chunk, are two tables.)
+// chunk's current rows with the chunk, are two tables.  A whole pass finds all rows of its level 0 there when it begins: one table.)
 bool constant_level(const gnnstage *st, int j) { return j == 0 && !st->s.need_input_grad && st->hist[0] == st->cur[0]; }
 
 // Layer j of a span's chunks (which have rows).  The chunks of a whole pass go side by side: layer j of a chunk reads rows of
@@ -1243,7 +1243,7 @@ int forward_layer(gnnstage *st, int j, const Span &sp, hipStream_t stream) {
   const int cd = st->cdtype();
   const size_t celt = s.elt();
   const int64_t row0 = span_row0(st, sp), M = span_rows(st, sp);
-  const bool shared = constant_level(st, j);
+  const bool shared = constant_level(st, j) || (sp.whole && st->hist[j] == st->cur[j]);
   if (!shared && s.res()) {
     Timed t(st, stream, 1, j);
     HIP_TRY(st, launch_ln_relu(ln_args(st, st->cur, j, row0, M, st->at<char>(st->lay.Tc[j]) + (size_t)row0 * s.ld[j] * celt, cd, s.ld[j]), stream));

@@ -76,8 +76,8 @@ def test_fp32_forward_sums_do_not_depend_on_the_chunks(dims):
     assert torch.equal(top[0].cur[1], top[1].cur[1])
 
 
-def _whole_equals_chunks(p):
-    whole, by_chunk = GpuRun(p), GpuRun(p)
+def _whole_equals_chunks(p, **kw):
+    whole, by_chunk = GpuRun(p, **kw), GpuRun(p, **kw)
     for _ in range(2):  # the second pass finds the scratch of the first
         whole.run()
     for _ in range(2):

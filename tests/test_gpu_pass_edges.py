@@ -234,3 +234,12 @@ def test_timed_passes_take_the_historical_part_of_layernorm_gradients(k, first, 
     ref = run_oracle(p)
     tol = TOL_F32 if dtype == "f32" else TOL_BF16
     assert max(max_rel(r.np(x), y) for x, y in zip(r.d_ln_gamma + r.d_ln_beta, ref.d_ln_g + ref.d_ln_b)) <= tol
+
+
+@pytest.mark.parametrize("variant,dims,dtype", [("gcn", (40, 24, 32), "f32"), ("gcn", (256, 128, 64), "bf16"), ("resgcn", (36,) * 3, "f32"), ("resgcn", (64,) * 3, "bf16")])
+def test_a_level_0_that_is_its_own_history(variant, dims, dtype):
+    """Of a stage that hands a gradient down: whole passes make one table of it, chunk calls two; the same bits, the oracle's values."""
+    p = make_problem(small(n=700, k=5, dims=dims, variant=variant, dtype=dtype, deg=9.0), bias_std=0.05, first_stage=False, noise_std=0.3)
+    _whole_equals_chunks(p, alias_hist0=True)
+    p.hist[0] = p.x0
+    _parity(p, TOL_F32 if dtype == "f32" else TOL_BF16, alias_hist0=True)

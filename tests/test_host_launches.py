@@ -33,7 +33,7 @@ class _Launch(C.Structure):
 class _Stage:
     """A stage handle over host buffers (values never matter: nothing is computed)."""
 
-    def __init__(self, variant, dims, K, n=400, tied=False, bf16=False, dropout_p=0.0):
+    def __init__(self, variant, dims, K, n=400, tied=False, bf16=False, dropout_p=0.0, own_history=False):
         import paper_2308_10087_amd as g
         from paper_2308_10087_amd import binding
         self.g, self.lib = g, binding.lib
@@ -46,6 +46,8 @@ class _Stage:
         self.keep = dict(row_ptr=row_ptr, col_idx=col, chunk_ptr=chunk_ptr, dims=dims)
         lists = dict(W=[np.zeros((two * int(dims[j]), int(dims[j + 1])), np.float32) for j in range(L)], cur=rows(dims), hist=rows(dims[:-1]),
                      dW=[np.zeros((two * int(dims[j]), int(dims[j + 1])), np.float32) for j in range(L)], bias=vec(dims[1:]), dbias=vec(dims[1:]))
+        if own_history:
+            lists["hist"][0] = lists["cur"][0]
         if variant == "resgcn":
             lists.update(ln_gamma=vec(dims[:-1]), ln_beta=vec(dims[:-1]))
             for i, name in enumerate(("d_ln_gamma", "d_ln_beta")):
@@ -117,6 +119,18 @@ def _forward_kinds(rt, variant, dims, K):
     rt.host_clear(-1)
     assert st.forward() == 0
     return "".join("a" if b"spmm" in l.name else "p" if b"gemm_nt" in l.name else "" for l in _launches(rt))
+
+
+def _tables(rt, variant, dims, whole):
+    """Launches of a forward pass that make a table of a level's rows, where level 0 is its own history."""
+    st = _Stage(variant, dims, 6, own_history=True)
+    rt.host_clear(-1)
+    if whole:
+        assert st.forward() == 0
+    else:
+        for pos, k in enumerate(st.order):
+            assert st.lib.stage_forward_chunk(st.h, int(k), pos, None) == 0
+    return sum(b"ln_relu" in l.name if variant == "resgcn" else b"gemm_nt" in l.name for l in _launches(rt))
 
 
 def _timed(rt, variant, dims):
@@ -233,3 +247,10 @@ def test_graphsage_adds_its_two_products_one_after_the_other(runtime, K):
     have left the caches."""
     got = _child(runtime, "_forward_kinds", "sage", [32, 24, 40], K)
     assert set(got.replace("aa", "a").split("a")[1:]) == {"pp"}
+
+
+@pytest.mark.parametrize("variant,dims", [("gcn", [40, 24]), ("resgcn", [32, 32])])
+def test_a_level_0_that_is_its_own_history_is_one_table_in_a_whole_pass(runtime, variant, dims):
+    """Of a stage that hands a gradient down: a chunk's rows may come with the chunk, those of a whole pass are there when it begins."""
+    assert _child(runtime, "_tables", variant, dims, True) == 1
+    assert _child(runtime, "_tables", variant, dims, False) == 1 + 6

@@ -81,7 +81,7 @@ __host__ __device__ inline bool dropout_keep(const LnDropout &dp, int64_t u, int
 
 // What a row chunk selects in a launch over many chunks: the source chunks it reads as processed, and the source classes
 // from which it gathers anything (launches that drop unselected entries).  One entry per row chunk, written by
-// launch_pass_tables; 64 bytes, read through the scalar cache.
+// launch_stage_weights; 64 bytes, read through the scalar cache.
 struct PassChunk {
   ChunkMask mask;
   uint32_t classes;
@@ -376,7 +376,6 @@ struct LnArgs {
   void *out;
   int32_t out_dtype, out_ld;
   LnDropout drop;
-  int32_t blocks;  // set by the launcher
 };
 // Backward of the same for M rows (the fields above: out, which may be NULL, receives the gradient of x): dr is the gradient of
 // the activated rows, res (or NULL) rows that are added to out (the residual branch); dgamma / dbeta get "+=" of the column
@@ -389,6 +388,7 @@ struct LnBackArgs {
   int32_t res_dtype, res_ld;
   float *partial;
   float *dgamma, *dbeta;
+  int32_t blocks;  // set by the launcher
 };
 static_assert(sizeof(Batch<LnBackArgs>) <= 4096, "kernel arguments");
 // What a backward launch leaves to add up: n_parts blocks of [gamma sums | beta sums] that go to dgamma and dbeta.
@@ -416,10 +416,9 @@ struct StageWeightsArgs {
 };
 // n weights in launches of up to kBatch; tables (or NULL): written by a workgroup of the first one
 int launch_stage_weights(const StageWeightsArgs *w, int n, int dtype, const PassTableArgs *tables, hipStream_t s);
-// dY[m][c] = level[m][c] > 0 ? g[m][c] : 0 for c < d, zeros up to out_ld
 // x[r][c] <- survives ? x[r][c] * scale : 0 in place, r < M, c < d (rows of leading dimension ld; dp.u0 = vertex of row 0)
 int launch_dropout_rows(void *x, int dtype, int64_t M, int d, int ld, const LnDropout &dp, hipStream_t s);
-// out = level > 0 ? g * scale : 0 (the ReLU derivative on the way back; scale = 1 / (1 - rate) of a dropout behind it)
+// out[m][c] = level[m][c] > 0 ? g[m][c] * scale : 0 for c < d, zeros up to out_ld (the ReLU derivative on the way back; scale = 1 / (1 - rate) of a dropout behind it)
 int launch_relu_mask(const void *g, const void *level, int dtype, int64_t M, int d, void *out, int out_ld, float scale,
                      hipStream_t s);
 int launch_copy(const void *src, void *dst, size_t bytes, hipStream_t s);

@@ -376,7 +376,7 @@ struct Layout {
   size_t f_task_row, f_task_e0, f_task_ne, f_task_slot, f_lr_row, f_lr_slot0, f_lr_n;
   size_t b_task_row, b_task_e0, b_task_ne, b_task_slot, b_lr_row, b_lr_slot0, b_lr_n;
   size_t f_slot_class, b_slot_class;
-  size_t pass_tables;  // three tables of K entries (launch_pass_tables)
+  size_t pass_tables;  // three tables of K entries (PassTableArgs)
   size_t rem_ptr[2];  // row pointers of the remainder index per direction (dense plan active), else unused
   // dense plan per direction (0 forward, 1 transposed)
   size_t d_blk_cb[2], d_blk_e0[2], d_ent_pos[2], d_ent_w[2], d_colslot[2], d_tiles[2];
@@ -1120,7 +1120,7 @@ const char *level_rows(const gnnstage *st, const std::vector<void *> &level, int
 // res: rows [M x ld_{j+1}] of the residual branch or NULL)
 LnArgs ln_args(const gnnstage *st, const std::vector<void *> &level, int j, int64_t row0, int64_t M, void *out, int out_dtype, int out_ld) {
   return LnArgs{level_rows(st, level, j, row0), st->level_dtype(j), st->s.dims[j], st->ln_g[j], st->ln_b[j], st->ln_eps, M, st->s.dims[j], out, out_dtype, out_ld,
-                st->dropout(j, row0), 0};
+                st->dropout(j, row0)};
 }
 
 // LayerNorm parameter sums of whole passes, which wait in scratch until all layers' (or as many as there is scratch for) are

@@ -86,7 +86,7 @@ template <int NI, bool LONG>
 __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBackArgs> ba) {
   const LnBackArgs b = ba.sub[blockIdx.z];
   const LnArgs &a = b.f;
-  const unsigned block = blockIdx.x, blocks = a.blocks;
+  const unsigned block = blockIdx.x, blocks = b.blocks;
   if (block >= blocks) return;
   const void *x = a.x, *dr = b.dr, *res = b.res;
   void *out = a.out;
@@ -261,7 +261,7 @@ template <int LPR, bool LONG>
 __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<LnBackArgs> ba) {
   const LnBackArgs b = ba.sub[blockIdx.z];
   const LnArgs &a = b.f;
-  const unsigned block = blockIdx.x, blocks = a.blocks;
+  const unsigned block = blockIdx.x, blocks = b.blocks;
   if (block >= blocks) return;
   const bf16_t *x = static_cast<const bf16_t *>(a.x), *dr = static_cast<const bf16_t *>(b.dr), *res = static_cast<const bf16_t *>(b.res);
   bf16_t *out = static_cast<bf16_t *>(a.out);
@@ -425,7 +425,7 @@ int waves_for(int64_t M, int max_waves) {
 
 }  // namespace
 
-static void set_blocks(LnBackArgs &a, unsigned g) { a.f.blocks = (int32_t)g; }
+static void set_blocks(LnBackArgs &a, unsigned g) { a.blocks = (int32_t)g; }
 static void set_blocks(LnReduceArgs &, unsigned) {}
 // Runs sub-launches [0, n) (kernel fn[i], gx[i] workgroups; 0: nothing to do), those of one kernel together.
 template <typename A, typename Fn>

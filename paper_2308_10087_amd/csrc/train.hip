@@ -96,8 +96,9 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(const float *x, int64_t
   if (threadIdx.x == 0) out[blockIdx.x] = red[0] * scale;
 }
 
-// Weight updates: the parameters of a model are planes of one launch, as are the clears of their gradients. An epoch on two ResGCN+
-// stages of four layers made 26 + 26 launches of 2 - 3 us each: 1,636 us before, 1,444 with two.
+// Weight updates: the parameters of a model are planes of one launch, as are the clears of their gradients.  A GCN and a ResGCN+ stage
+// of four layers each and a head are 26 parameters, which made 26 + 26 launches of 2 - 3 us each: an epoch over 50 k vertices in 8 chunks
+// took 1,636 us, 1,444 with two.
 constexpr int kUpdates = 32;
 struct Update {
   float *p;

@@ -102,7 +102,7 @@ def _whole_equals_chunks(p, **kw):
     ("sage", "bf16", (64, 128, 128), 3, {}), ("gcnii", "bf16", (64,) * 12, 11, {}), ("gcnii", "f32", (40, 40), 6, {}),
     ("resgcn", "f32", (36,) * 5, 6, {"dropout_p": 0.3}), ("resgcn", "bf16", (128,) * 4, 9, {}), ("gcn", "bf16", (602, 100, 100), 3, {})])
 def test_whole_pass_calls_equal_the_chunk_calls(variant, dtype, dims, k, kw):
-    """More and fewer chunks than layers, more of both than cells run side by side, an empty chunk: levels and what flows back
+    """More and fewer chunks than layers, more and fewer than groups of LayerNorm sums, an empty chunk: levels and what flows back
     are the same bits; parameter gradients the same sums in another order (fp32, a few hundred terms)."""
     n = 700
     cp = np.sort(np.concatenate([[0, n], np.random.default_rng(3).integers(1, n, k - 1)])).astype(np.int64)
@@ -113,9 +113,9 @@ def test_whole_pass_calls_equal_the_chunk_calls(variant, dtype, dims, k, kw):
 
 
 @pytest.mark.parametrize("variant,dims", [("gcn", (64, 128, 128, 256, 256)), ("gcnii", (128,) * 6)])
-def test_whole_pass_products_that_only_together_are_long(variant, dims, monkeypatch):
-    """Chunks of 100 rows: below the rows from which the weight-stationary product runs, a diagonal of three and more above them.
-    Whole passes take that kernel, several products in a launch, the chunk calls the tiled one; the results are the same bits."""
+def test_whole_pass_weight_stationary_products_equal_tiled_ones_of_the_chunks(variant, dims, monkeypatch):
+    """Chunks of 100 rows are below the rows from which the weight-stationary product runs, all 700 rows above them: whole passes take
+    that kernel, the chunk calls the tiled one; the results are the same bits."""
     monkeypatch.setenv("GNNSTAGE_GEMM_WS_MIN_ROWS", "250")
     _whole_equals_chunks(make_problem(small(n=700, k=7, dims=dims, variant=variant, dtype="bf16", deg=9.0), bias_std=0.05, first_stage=False))
 
@@ -158,8 +158,8 @@ def test_fp32_weight_gradients_over_all_rows_against_64_bits(n, d):
 
 @pytest.mark.parametrize("dtype,width", [("f32", 36), ("bf16", 128)])
 def test_layers_with_one_layernorm_gradient_buffer(dtype, width):
-    """Tied LayerNorm parameters: the layers' gradients add up in the buffer that they share, in passes whose cells run side by
-    side and in the part of a backward pass that follows its last chunk."""
+    """Tied LayerNorm parameters: the layers' gradients add up in the buffer that they share, of the current rows and, in the part of a
+    backward pass that follows its last chunk, of the historical ones."""
     import paper_2308_10087_amd as g
     p = make_problem(small(n=900, k=6, dims=(width,) * 5, variant="resgcn", dtype=dtype, deg=9.0), bias_std=0.05, first_stage=False)
     ref = run_oracle(p)

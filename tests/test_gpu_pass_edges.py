@@ -94,8 +94,8 @@ def test_short_rows_of_tables_beyond_the_caches(monkeypatch):
 @pytest.mark.parametrize("width", [64, 128, 256])
 @pytest.mark.parametrize("n,k", [(513, 1), (1031, 4), (37, 2)])
 def test_identity_mapping_in_the_weight_stationary_product(width, n, k, monkeypatch):
-    """GCNII products from every row count on in the weight-stationary kernel (at 256 the other operand comes through LDS, half before
-    and half behind the products): the bits of the tiled kernel, and the oracle's values."""
+    """GCNII products from every row count on in the weight-stationary kernel (the identity mapping's other operand is the A tile in LDS,
+    grad_h0 comes half before and half behind the products): the bits of the tiled kernel, and the oracle's values."""
     p = make_problem(small(n=n, k=k, dims=(width,) * 4, variant="gcnii", dtype="bf16", deg=min(9.0, n / 8)), first_stage=False, noise_std=0.3)
     runs = []
     for least in ("1", "1000000"):

@@ -431,12 +431,13 @@ def test_workspace_size_and_validation_without_a_gpu():
     assert g.lib.gnnstage_destroy(None) == -1
 
 
-def _workspace(variant, n, dims, chunk_ptr):
-    """Workspace bytes of an fp32 stage over self-loops."""
+def _workspace(variant, n, dims, chunk_ptr, row_ptr=None, col=None):
+    """Workspace bytes of an fp32 stage, over self-loops unless a graph is given."""
     g = _lib()
-    arrays = dict(row_ptr=np.arange(n + 1, dtype=np.int64), col_idx=np.arange(n, dtype=np.int32), chunk_ptr=np.asarray(chunk_ptr, np.int64),
-                  dims=np.asarray(dims, np.int32))
-    d, keep = _desc(g, variant=variant, n_vertices=n, nnz=n, n_chunks=len(chunk_ptr) - 1, n_layers=len(dims) - 1, need_input_grad=1, ln_eps=1e-5,
+    if col is None:
+        row_ptr, col = np.arange(n + 1, dtype=np.int64), np.arange(n, dtype=np.int32)
+    arrays = dict(row_ptr=row_ptr, col_idx=col, chunk_ptr=np.asarray(chunk_ptr, np.int64), dims=np.asarray(dims, np.int32))
+    d, keep = _desc(g, variant=variant, n_vertices=n, nnz=len(col), n_chunks=len(chunk_ptr) - 1, n_layers=len(dims) - 1, need_input_grad=1, ln_eps=1e-5,
                     **{k: a.ctypes.data for k, a in arrays.items()})
     return g.lib.gnnstage_workspace_size(C.byref(d))
 
@@ -450,13 +451,27 @@ def test_resgcn_workspace_holds_four_tables_per_layer():
     assert 4 * L * table < size < (4 * L + 4) * table
 
 
-def test_scratch_of_cells_that_run_side_by_side_is_bounded():
-    """Equal chunks: a little more than one cell's.  Nearly all rows in one chunk: a cell takes 1.8 GB of scratch, and the stage
-    no more than 1 GiB beyond what it takes with one chunk, which runs one cell at a time."""
+def test_scratch_for_the_rows_of_a_chunk():
+    """Rows of one entry, which leave no partial sums: scratch is that of the largest chunk's rows."""
     n, dims = 300000, [512] * 5
     one = _workspace(2, n, dims, [0, n])
-    assert _workspace(2, n, dims, (np.arange(33) * n) // 32) < one  # chunk-sized scratch
-    assert _workspace(2, n, dims, [0, n - 300, n - 200, n - 100, n]) <= one + (1 << 30)
+    assert _workspace(2, n, dims, (np.arange(33) * n) // 32) < one
+    assert _workspace(2, n, dims, [0, n - 300, n - 200, n - 100, n]) <= one + (1 << 16)
+
+
+def test_room_for_the_partial_sums_of_all_chunks_is_bounded(monkeypatch):
+    """Rows of 150 entries, up to 5 pieces by length and 9 more by source class: 14 partial rows for each row beyond the largest of six
+    chunks, 459 MB of 4,096 columns, all of which there is room for; 1.8 GB of 16,384 columns, of which there is for 512 MiB."""
+    n, deg, K = 2400, 150, 6
+    col = ((np.arange(n)[:, None] + np.arange(deg) * 7) % n).astype(np.int32)
+    row_ptr, col = np.arange(n + 1, dtype=np.int64) * deg, np.sort(col, axis=1).ravel()
+    chunk_ptr = np.arange(K + 1, dtype=np.int64) * n // K
+    for width, room in ((4096, 14 * (n - n // K) * 4096 * 4), (16384, 512 << 20)):
+        sizes = []
+        for own in (None, "0"):
+            monkeypatch.setenv("GNNSTAGE_PARTIAL_ROOM", own) if own else monkeypatch.delenv("GNNSTAGE_PARTIAL_ROOM", raising=False)
+            sizes.append(_workspace(2, n, [width, 16], chunk_ptr, row_ptr, col))
+        assert room - 16384 * 4 <= sizes[0] - sizes[1] <= room + 256
 
 
 def _scratch_bytes():

@@ -108,9 +108,11 @@ __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBac
     gam[i] = c < d ? gamma[c] : 0.f;
     bet[i] = c < d ? beta[c] : 0.f;
   }
+  const int64_t gap_row = b.gap_row, gap = b.gap;
   int chain = 0;
   bool waiting = false;  // earlier chains' sums wait in LDS
-  for (int64_t r = w0; r < M; r += nw) {
+  for (int64_t i_row = w0; i_row < M; i_row += nw) {
+    const int64_t r = i_row < gap_row ? i_row : i_row + gap;
     if (LONG && chain == kLnChain) {
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
@@ -282,6 +284,7 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<L
     bet[t] = beta[sub * 8 + t];
     dg[t] = db[t] = 0.f;
   }
+  const int64_t gap_row = b.gap_row, gap = b.gap;
   int chain = 0;
   bool waiting = false;
   for (int64_t r0 = w0 * RPW; r0 < M; r0 += nw * RPW) {
@@ -297,9 +300,10 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<L
       chain = 0;
     }
     ++chain;
-    const int64_t r = r0 + rw;
-    const bool on = r < M;
-    const int64_t rr = on ? r : M - 1;
+    const int64_t i_row = r0 + rw;
+    const bool on = i_row < M;
+    int64_t rr = on ? i_row : M - 1;
+    rr += rr < gap_row ? 0 : gap;
     const bf16x8_ln xv = *reinterpret_cast<const bf16x8_ln *>(x + (size_t)rr * x_ld + sub * 8);
     const bf16x8_ln dv = *reinterpret_cast<const bf16x8_ln *>(dr + (size_t)rr * dr_ld + sub * 8);
     bf16x8_ln rv;
@@ -341,7 +345,7 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<L
         if (res != nullptr) v += (float)rv[t];
         o[t] = (bf16_t)v;
       }
-      *reinterpret_cast<bf16x8_ln *>(out + (size_t)r * out_ld + sub * 8) = o;
+      *reinterpret_cast<bf16x8_ln *>(out + (size_t)rr * out_ld + sub * 8) = o;
     }
   }
   // column sums: over the row groups of the wavefront (fixed order), then over the four wavefronts in LDS

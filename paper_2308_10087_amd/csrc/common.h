@@ -95,6 +95,8 @@ struct alignas(16) XcdRun {
   int32_t cls, group0, groups, unused;
 };
 
+enum ShortRows : int32_t { SHORT_ROWS_MFMA, SHORT_ROWS_VALU, SHORT_ROWS_SINGLE };  // VALU: fp32 weights on the vector ALU
+
 struct SpmmArgs {
   // sparse structure: packed index words (vertex | chunk << vbits) and weights
   const uint32_t *pidx;
@@ -112,17 +114,17 @@ struct SpmmArgs {
   XcdRun xcd[8];
   int32_t n_class_blocks;
   int64_t tail0, n_tail;
-  // Whole rows of at most a few entries (no partial slot), every chunk's filled up to a multiple of four.  From short_from of
-  // them on the matrix-core kernel gives them to extra workgroups of the same launch whose waves serve four rows each: a wave per
-  // row would spend its life waiting for three dependent round trips to move a kilobyte or two.  Fewer rows, the vector-ALU
-  // kernel and rows wider than 256 columns: a row to a wave like any other task.
-  int64_t short0, n_short, short_from;
+  // Whole rows of at most a few entries (no partial slot), every chunk's filled up to a multiple of four.  Where there are many of
+  // them the matrix-core kernel gives them to extra workgroups of the same launch whose waves serve four rows each: a wave per
+  // row would spend its life waiting for three dependent round trips to move a kilobyte or two.  Few of them (SHORT_ROWS_SINGLE), the
+  // vector-ALU kernel and rows wider than 256 columns: a row to a wave like any other task.
+  int64_t short0, n_short;
   // The two lists' workgroups are dealt out evenly, so that the launch goes through both in about the order of their rows:
   // workgroup p behind the class pieces serves short rows if p mix crosses a whole number of 2^32 (set by the launcher).
   // First all of the one and then of the other is slower where the gathers bound the launch: 3.6 M entries of 512-byte rows
   // 192 against 177 us.
   uint64_t mix;
-  int32_t short_valu;     // short rows: fp32 weights on the vector ALU
+  int32_t short_rows;     // ShortRows
   const uint8_t *slot_class;  // class of every partial slot (255: none); pieces of inactive classes are not run
   uint32_t active_classes;
   int32_t all_classes_active;

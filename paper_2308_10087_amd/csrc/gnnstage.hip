@@ -986,8 +986,7 @@ void set_schedule(const gnnstage *st, int dir, int c0, int c1, Select sel, const
   a.n_tail = t.count(t.n_classes, c0, c1);
   a.short0 = t.first(t.n_classes + 1, c0);
   a.n_short = t.count(t.n_classes + 1, c0, c1);
-  a.short_valu = st->s.short_valu() ? 1 : 0;
-  a.short_from = a.short_valu || st->s.tune.short_row >= 0 ? 1 : kShortRowsPerColumn * a.d;
+  a.short_rows = st->s.short_valu() ? SHORT_ROWS_VALU : st->s.tune.short_row >= 0 || a.n_short >= kShortRowsPerColumn * a.d ? SHORT_ROWS_MFMA : SHORT_ROWS_SINGLE;
   a.slot_class = st->at<uint8_t>(dir ? lay.b_slot_class : lay.f_slot_class);
   const int64_t l0 = t.lr_off[(size_t)c0];
   a.lr_row = st->at<int32_t>(dir ? lay.b_lr_row : lay.f_lr_row) + l0;

@@ -586,9 +586,9 @@ __global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ri
   __shared__ u32x4_t ring_all[4][R];
   if constexpr (NT <= 2) {
     const SpmmTurn turn = spmm_turn(a, blockIdx.x);
-    if ((int)blockIdx.x >= a.n_class_blocks && turn.is_short && a.n_short >= a.short_from) {  // 16 short rows
+    if ((int)blockIdx.x >= a.n_class_blocks && turn.is_short && a.short_rows != SHORT_ROWS_SINGLE) {  // 16 short rows
       const int64_t first = (int64_t)turn.index * 16 + (threadIdx.x >> 6) * 4;
-      if (a.short_valu == 0)
+      if (a.short_rows == SHORT_ROWS_MFMA)
         spmm_short_rows<Tout, NT, FULL>(a, first, ring_all[threadIdx.x >> 6]);
       else if (a.many_chunks != 0)
         spmm_short_rows_valu<Tout, NT, FULL, true>(a, first);
@@ -843,7 +843,7 @@ int launch_spmm(const SpmmArgs &a_in, int src_dtype, int out_dtype, hipStream_t 
   SpmmArgs a = a_in;
   const bool mfma = mfma_path(a, src_dtype);
   // short rows: 16 to a workgroup where four rows of them fit a wave's registers, else one to a wave like the others
-  const int64_t tail_blocks = (a.n_tail + 3) / 4, short_blocks = mfma && a.d <= 256 && a.n_short >= a.short_from ? (a.n_short + 15) / 16 : a.n_short / 4;
+  const int64_t tail_blocks = (a.n_tail + 3) / 4, short_blocks = mfma && a.d <= 256 && a.short_rows != SHORT_ROWS_SINGLE ? (a.n_short + 15) / 16 : a.n_short / 4;
   int64_t gx = a.n_class_blocks + tail_blocks + short_blocks;
   if (gx <= 0) return hipSuccess;
   if (gx + 7 > kMostBlocks) return hipErrorInvalidValue;

@@ -29,7 +29,7 @@ class _Mask(C.Structure):
 class _Spmm(C.Structure):  # SpmmArgs
     _fields_ = [("pidx", P), ("val", P), ("task_row", P), ("task_e0", P), ("task_ne", P), ("task_slot", P), ("cls_begin", I32 * 32), ("cls_end", I32 * 32),
                 ("xcd", (I32 * 4) * 8), ("n_class_blocks", I32), ("tail0", I64), ("n_tail", I64),
-                ("short0", I64), ("n_short", I64), ("short_from", I64), ("mix", C.c_uint64), ("short_valu", I32), ("slot_class", P), ("active_classes", U32), ("all_classes_active", I32),
+                ("short0", I64), ("n_short", I64), ("mix", C.c_uint64), ("short_rows", I32), ("slot_class", P), ("active_classes", U32), ("all_classes_active", I32),
                 ("lr_row", P), ("lr_slot0", P), ("lr_nslots", P), ("n_long", I64), ("partial", P), ("slot0", I64), ("lr_dense0", P), ("lr_ndense", P),
                 ("lr_item0", P), ("item_chunks", P), ("dense_partial", P), ("item0", I64), ("drop_unselected", I32), ("src_sel", P), ("src_unsel", P),
                 ("d", I32), ("src_ld", I32), ("vbits", I32), ("many_chunks", I32), ("pass_", P), ("mask", _Mask), ("out", P), ("out_ld", I32), ("out_row0", I64)]
@@ -59,7 +59,7 @@ def _tasks(a, name, grid):
     for b in range(grid[0]):
         p = b - a.n_class_blocks
         before, upto = p * a.mix >> 32, (p + 1) * a.mix >> 32
-        if ring and a.d <= 256 and a.n_short >= a.short_from and p >= 0 and upto > before:
+        if ring and a.d <= 256 and a.short_rows != 2 and p >= 0 and upto > before:
             out += [(a.short0 + t, -1) for t in range(before * 16, min(before * 16 + 16, a.n_short))]
             continue
         for w in range(4):

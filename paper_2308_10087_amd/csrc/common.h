@@ -15,10 +15,18 @@ constexpr int kMaxClasses = 32;  // source-id classes of the aggregation schedul
 
 // Workgroups of 256 along an axis of a grid: the runtime takes fewer than 2^32 work-items there.
 constexpr int64_t kMostBlocks = ((int64_t)1 << 24) - 1;
-// The grid of a kernel with one element (or vector of elements) per thread; kernels walk on by the grid's size behind its end.
-static inline unsigned element_blocks(int64_t threads) {
-  const int64_t b = (threads + 255) / 256;
-  return (unsigned)(b < kMostBlocks ? b : kMostBlocks);
+// Kernels with a thread per element (or vector of elements) of a matrix: launch(first row, rows, workgroups) for as many rows at a time as a
+// grid has threads.
+template <typename F>
+static inline int for_row_slabs(int64_t M, int64_t threads_per_row, F launch) {
+  const int64_t most = kMostBlocks * 256 / threads_per_row;
+  for (int64_t r = 0; r < M; r += most) {
+    const int64_t m = M - r < most ? M - r : most;
+    launch(r, m, (unsigned)((m * threads_per_row + 255) / 256));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
+  }
+  return hipSuccess;
 }
 
 // The word is picked with selects, not with an indexed access: a kernel that holds the mask as an argument

@@ -413,11 +413,11 @@ __global__ __launch_bounds__(1024) void ln_param_reduce_kernel(const Batch<LnRed
 }
 
 __global__ __launch_bounds__(256) void copy_rows_kernel(const void *src, int src_ld, void *dst, int dst_ld, int64_t M, int d, int dtype) {
-  for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < M * dst_ld; idx += (int64_t)gridDim.x * 256) {
-    const int64_t r = idx / dst_ld;
-    const int c = (int)(idx % dst_ld);
-    st_elt(dst, dtype, (size_t)idx, c < d ? ld_elt(src, dtype, (size_t)r * src_ld + c) : 0.f);
-  }
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= M * dst_ld) return;
+  const int64_t r = idx / dst_ld;
+  const int c = (int)(idx % dst_ld);
+  st_elt(dst, dtype, (size_t)idx, c < d ? ld_elt(src, dtype, (size_t)r * src_ld + c) : 0.f);
 }
 
 int waves_for(int64_t M, int max_waves) {
@@ -543,7 +543,9 @@ int launch_ln_param_reduce(const LnReduceArgs *red, int n, hipStream_t s) {
 }
 
 int launch_copy_rows(const void *src, int src_ld, void *dst, int dst_ld, int64_t M, int d, int dtype, hipStream_t s) {
-  if (M <= 0) return hipSuccess;
-  hipLaunchKernelGGL(copy_rows_kernel, dim3(element_blocks(M * dst_ld)), dim3(256), 0, s, src, src_ld, dst, dst_ld, M, d, dtype);
-  return (int)hipGetLastError();
+  const size_t elt = dtype == DT_BF16 ? 2 : 4;
+  return for_row_slabs(M, dst_ld, [&](int64_t r, int64_t m, unsigned gx) {
+    hipLaunchKernelGGL(copy_rows_kernel, dim3(gx), dim3(256), 0, s, static_cast<const char *>(src) + (size_t)r * src_ld * elt, src_ld,
+                       static_cast<char *>(dst) + (size_t)r * dst_ld * elt, dst_ld, m, d, dtype);
+  });
 }

@@ -87,25 +87,25 @@ __global__ __launch_bounds__(256) void stage_weights_kernel(const StageArgs a) {
 template <typename T>
 __global__ __launch_bounds__(256) void relu_mask_vec_kernel(const T *g, const T *level, int64_t M, int d, T *out, float scale) {
   typedef T vec_t __attribute__((ext_vector_type(8)));
-  for (int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8; idx < M * d; idx += (int64_t)gridDim.x * (256 * 8)) {
-    const T *gp = g + idx, *lp = level + idx;
-    T *op = out + idx;
-    if constexpr (sizeof(T) == 2) {
-      const vec_t x = *reinterpret_cast<const vec_t *>(gp), l = *reinterpret_cast<const vec_t *>(lp);
-      vec_t r;
+  const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
+  if (idx >= M * d) return;
+  const T *gp = g + idx, *lp = level + idx;
+  T *op = out + idx;
+  if constexpr (sizeof(T) == 2) {
+    const vec_t x = *reinterpret_cast<const vec_t *>(gp), l = *reinterpret_cast<const vec_t *>(lp);
+    vec_t r;
 #pragma unroll
-      for (int t = 0; t < 8; ++t) r[t] = to_f32(l[t]) > 0.f ? from_f32<T>(to_f32(x[t]) * scale) : from_f32<T>(0.f);
-      *reinterpret_cast<vec_t *>(op) = r;
-    } else {
-      typedef T half_t __attribute__((ext_vector_type(4)));
+    for (int t = 0; t < 8; ++t) r[t] = to_f32(l[t]) > 0.f ? from_f32<T>(to_f32(x[t]) * scale) : from_f32<T>(0.f);
+    *reinterpret_cast<vec_t *>(op) = r;
+  } else {
+    typedef T half_t __attribute__((ext_vector_type(4)));
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const half_t x = *reinterpret_cast<const half_t *>(gp + 4 * h), l = *reinterpret_cast<const half_t *>(lp + 4 * h);
-        half_t r;
+    for (int h = 0; h < 2; ++h) {
+      const half_t x = *reinterpret_cast<const half_t *>(gp + 4 * h), l = *reinterpret_cast<const half_t *>(lp + 4 * h);
+      half_t r;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) r[t] = to_f32(l[t]) > 0.f ? from_f32<T>(to_f32(x[t]) * scale) : from_f32<T>(0.f);
-        *reinterpret_cast<half_t *>(op + 4 * h) = r;
-      }
+      for (int t = 0; t < 4; ++t) r[t] = to_f32(l[t]) > 0.f ? from_f32<T>(to_f32(x[t]) * scale) : from_f32<T>(0.f);
+      *reinterpret_cast<half_t *>(op + 4 * h) = r;
     }
   }
 }
@@ -113,28 +113,28 @@ __global__ __launch_bounds__(256) void relu_mask_vec_kernel(const T *g, const T 
 // Dropout on rows that a layer has just written: 8 consecutive columns per thread when the row allows it.
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void dropout_rows_kernel(T *x, int64_t M, int d, int ld, LnDropout dp) {
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int per_row = d / VEC;
-  for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < M * per_row; idx += (int64_t)gridDim.x * 256) {
-    const int64_t r = idx / per_row;
-    const int c = (int)(idx % per_row) * VEC;
-    typedef T vec_t __attribute__((ext_vector_type(VEC)));
-    vec_t *p = reinterpret_cast<vec_t *>(x + r * ld + c);
-    vec_t v = *p;
+  if (idx >= M * per_row) return;
+  const int64_t r = idx / per_row;
+  const int c = (int)(idx % per_row) * VEC;
+  typedef T vec_t __attribute__((ext_vector_type(VEC)));
+  vec_t *p = reinterpret_cast<vec_t *>(x + r * ld + c);
+  vec_t v = *p;
 #pragma unroll
-    for (int t = 0; t < VEC; ++t) v[t] = dropout_keep(dp, dp.u0 + r, d, c + t) ? from_f32<T>(to_f32(v[t]) * dp.scale) : from_f32<T>(0.f);
-    *p = v;
-  }
+  for (int t = 0; t < VEC; ++t) v[t] = dropout_keep(dp, dp.u0 + r, d, c + t) ? from_f32<T>(to_f32(v[t]) * dp.scale) : from_f32<T>(0.f);
+  *p = v;
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void relu_mask_kernel(const T *g, const T *level, int64_t M, int d, T *out, int out_ld, float scale) {
-  for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < M * out_ld; idx += (int64_t)gridDim.x * 256) {
-    const int64_t m = idx / out_ld;
-    const int c = (int)(idx % out_ld);
-    float r = 0.f;
-    if (c < d && to_f32(level[m * d + c]) > 0.f) r = to_f32(g[m * d + c]) * scale;
-    out[idx] = from_f32<T>(r);
-  }
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= M * out_ld) return;
+  const int64_t m = idx / out_ld;
+  const int c = (int)(idx % out_ld);
+  float r = 0.f;
+  if (c < d && to_f32(level[m * d + c]) > 0.f) r = to_f32(g[m * d + c]) * scale;
+  out[idx] = from_f32<T>(r);
 }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -227,43 +227,39 @@ int launch_stage_weights(const StageWeightsArgs *w, int n, int dtype, const Pass
   return hipSuccess;
 }
 
+template <typename T, int VEC>
+static int dropout_rows(T *x, int64_t M, int d, int ld, const LnDropout &dp, hipStream_t s) {
+  return for_row_slabs(M, d / VEC, [&](int64_t r, int64_t m, unsigned gx) {
+    LnDropout at = dp;
+    at.u0 += r;
+    hipLaunchKernelGGL((dropout_rows_kernel<T, VEC>), dim3(gx), dim3(256), 0, s, x + (size_t)r * ld, m, d, ld, at);
+  });
+}
 int launch_dropout_rows(void *x, int dtype, int64_t M, int d, int ld, const LnDropout &dp, hipStream_t s) {
   if (M <= 0 || d <= 0 || dp.threshold == 0) return hipSuccess;
-  const bool vec = d % 8 == 0 && ld % 8 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0 && dtype == DT_BF16;
-  const dim3 grid(element_blocks(vec ? M * (d / 8) : M * d));
-  if (dtype == DT_BF16) {
-    if (vec)
-      hipLaunchKernelGGL((dropout_rows_kernel<bf16_t, 8>), grid, dim3(256), 0, s, static_cast<bf16_t *>(x), M, d, ld, dp);
-    else
-      hipLaunchKernelGGL((dropout_rows_kernel<bf16_t, 1>), grid, dim3(256), 0, s, static_cast<bf16_t *>(x), M, d, ld, dp);
-  } else {
-    hipLaunchKernelGGL((dropout_rows_kernel<float, 1>), grid, dim3(256), 0, s, static_cast<float *>(x), M, d, ld, dp);
-  }
-  return (int)hipGetLastError();
+  if (dtype != DT_BF16) return dropout_rows<float, 1>(static_cast<float *>(x), M, d, ld, dp, s);
+  const bool vec = d % 8 == 0 && ld % 8 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
+  return vec ? dropout_rows<bf16_t, 8>(static_cast<bf16_t *>(x), M, d, ld, dp, s) : dropout_rows<bf16_t, 1>(static_cast<bf16_t *>(x), M, d, ld, dp, s);
 }
 
+template <typename T>
+static int relu_mask(const T *g, const T *level, int64_t M, int d, T *out, int out_ld, float scale, hipStream_t s) {
+  const auto al = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
+  const bool vec = d % 8 == 0 && out_ld == d && al(g) && al(level) && al(out);
+  return for_row_slabs(M, vec ? d / 8 : out_ld, [&](int64_t r, int64_t m, unsigned gx) {
+    const T *gr = g + (size_t)r * d, *lr = level + (size_t)r * d;
+    T *o = out + (size_t)r * out_ld;
+    if (vec)
+      hipLaunchKernelGGL(relu_mask_vec_kernel<T>, dim3(gx), dim3(256), 0, s, gr, lr, m, d, o, scale);
+    else
+      hipLaunchKernelGGL(relu_mask_kernel<T>, dim3(gx), dim3(256), 0, s, gr, lr, m, d, o, out_ld, scale);
+  });
+}
 int launch_relu_mask(const void *g, const void *level, int dtype, int64_t M, int d, void *out, int out_ld, float scale,
                      hipStream_t s) {
-  if (M <= 0) return hipSuccess;
-  const auto al = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
-  if (d % 8 == 0 && out_ld == d && al(g) && al(level) && al(out)) {
-    const dim3 gv(element_blocks(M * d / 8));
-    if (dtype == DT_BF16)
-      hipLaunchKernelGGL(relu_mask_vec_kernel<bf16_t>, gv, dim3(256), 0, s, static_cast<const bf16_t *>(g),
-                         static_cast<const bf16_t *>(level), M, d, static_cast<bf16_t *>(out), scale);
-    else
-      hipLaunchKernelGGL(relu_mask_vec_kernel<float>, gv, dim3(256), 0, s, static_cast<const float *>(g),
-                         static_cast<const float *>(level), M, d, static_cast<float *>(out), scale);
-    return (int)hipGetLastError();
-  }
-  const dim3 grid(element_blocks(M * out_ld));
   if (dtype == DT_BF16)
-    hipLaunchKernelGGL(relu_mask_kernel<bf16_t>, grid, dim3(256), 0, s, static_cast<const bf16_t *>(g),
-                       static_cast<const bf16_t *>(level), M, d, static_cast<bf16_t *>(out), out_ld, scale);
-  else
-    hipLaunchKernelGGL(relu_mask_kernel<float>, grid, dim3(256), 0, s, static_cast<const float *>(g),
-                       static_cast<const float *>(level), M, d, static_cast<float *>(out), out_ld, scale);
-  return (int)hipGetLastError();
+    return relu_mask(static_cast<const bf16_t *>(g), static_cast<const bf16_t *>(level), M, d, static_cast<bf16_t *>(out), out_ld, scale, s);
+  return relu_mask(static_cast<const float *>(g), static_cast<const float *>(level), M, d, static_cast<float *>(out), out_ld, scale, s);
 }
 
 static unsigned stream_grid(size_t n16) {

@@ -174,7 +174,7 @@ def test_a_layer_whose_partial_sums_have_no_room_together(k, room, variant, dtyp
 
 
 def test_more_elements_than_a_grid_has_threads():
-    """4.29 M rows of 1002 bf16 columns: dropout and the ReLU derivative over all rows walk on behind the end of their grids; the
+    """4.29 M rows of 1002 bf16 columns: dropout and the ReLU derivative over all rows take two launches; the
     bits of launches over a chunk."""
     import paper_2308_10087_amd as g
     n, d0, d1, K, dev = 4_290_001, 1008, 1002, 3, "cuda:0"

@@ -389,8 +389,8 @@ struct LnArgs {
 };
 // Backward of the same for M rows (the fields above: out, which may be NULL, receives the gradient of x): dr is the gradient of
 // the activated rows, res (or NULL) rows that are added to out (the residual branch); dgamma / dbeta get "+=" of the column
-// sums in a fixed order (partial: fp32 scratch, kLnMaxWaves / 4 * 2 * d).  Rows from gap_row on lie gap rows further on, in x, out,
-// dr and res alike (rows in the middle that take no part).
+// sums in a fixed order (partial: fp32 scratch, kLnMaxWaves / 4 * 2 * d).  Rows [gap_row, gap_end) take no part and are not read;
+// the first row does.
 struct LnBackArgs {
   LnArgs f;
   const void *dr;
@@ -399,7 +399,7 @@ struct LnBackArgs {
   int32_t res_dtype, res_ld;
   float *partial;
   float *dgamma, *dbeta;
-  int64_t gap_row, gap;
+  int64_t gap_row, gap_end;
   int32_t blocks;  // set by the launcher
 };
 static_assert(sizeof(Batch<LnBackArgs>) <= 4096, "kernel arguments");

@@ -1149,24 +1149,22 @@ int ln_backward(gnnstage *st, LnSums &sums, const std::vector<void *> &level, in
   LnBackArgs l[kBatch];
   if (without < sp.c0 || without >= sp.c1) without = -1;
   // As many groups as chunks up to eight, of equal numbers of rows: a launch takes as long as its largest group.  The rows of `without`
-  // are a gap in one of them.  (Groups of whole chunks in front of the gap and behind it were up to a quarter larger than others:
-  // four layers of 89 k fp32 rows of width 100, 31 of 32 chunks, 342 instead of 325 us.)
-  const int n_groups = std::min(sp.c1 - sp.c0 - (without < 0 ? 0 : 1), kBatch);
-  if (n_groups == 0) return GNNSTAGE_OK;
-  const int64_t gap0 = without < 0 ? s.n : s.chunk_ptr[(size_t)without], gap = without < 0 ? 0 : s.chunk_ptr[(size_t)without + 1] - gap0;
-  const int64_t first = span_row0(st, sp), rows = span_rows(st, sp) - gap;
-  // wavefronts of a group: equal shares, in steps of what makes full rounds of the loads that add up its workgroups' sums (16 x 8 of them;
-  // sums of 292 workgroups took 4.2 us, of 256 3.6)
-  int max_waves = kLnMaxWaves / n_groups / 4 * 4;
-  if (max_waves > 512) max_waves = max_waves / 512 * 512;
+  // are a gap in them.  (Groups of whole chunks in front of the gap and behind it were up to a quarter larger than others: LayerNorm
+  // backward of four layers of 89 k fp32 rows of width 100, 31 of 32 chunks, 342 instead of 325 us.)
+  const int n_groups = std::min(sp.c1 - sp.c0, kBatch);
+  const int64_t gap0 = without < 0 ? s.n : s.chunk_ptr[(size_t)without], gap1 = without < 0 ? s.n : s.chunk_ptr[(size_t)without + 1];
+  const int64_t first = span_row0(st, sp), rows = span_rows(st, sp);
+  const int max_waves = kLnMaxWaves / n_groups / 4 * 4;
   float *scratch = st->at<float>(st->lay.ln_partial) + (size_t)sums.n_layers * st->lay.ln_stride;
   for (int g = 0; g < n_groups; ++g) {
-    const int64_t at = rows * g / n_groups, M = rows * (g + 1) / n_groups - at;  // counted without the gap
-    const int64_t row0 = first + at + (first + at < gap0 ? 0 : gap);
+    int64_t row0 = first + rows * g / n_groups, end = first + rows * (g + 1) / n_groups;
+    if (row0 >= gap0 && row0 < gap1) row0 = std::min(gap1, end);  // a gap at either end is cut off
+    if (end > gap0 && end <= gap1) end = std::max(gap0, row0);
+    const int64_t M = end - row0;
     LnBackArgs &x = l[g];
     x = LnBackArgs{};
-    x.gap_row = row0 < gap0 ? gap0 - row0 : M;
-    x.gap = gap;
+    x.gap_row = std::min(std::max<int64_t>(gap0 - row0, 0), M);
+    x.gap_end = std::min(std::max<int64_t>(gap1 - row0, 0), M);
     x.f = ln_args(st, level, j, row0, M, out ? out + (size_t)row0 * out_ld * (out_dtype == DT_BF16 ? 2 : 4) : nullptr, out_dtype, out_ld);
     x.dr = dr + (size_t)row0 * s.ld[j] * celt;
     x.dr_dtype = st->cdtype();

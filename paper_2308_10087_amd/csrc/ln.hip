@@ -82,20 +82,19 @@ __global__ __launch_bounds__(256) void ln_relu_kernel(const LnArgs a) {
 // rows in 32 chunks: 977), whose one chain was off 64 bits by 5.2e-7 of the root of the sum of squares; in chains of 32 it is 1.8e-7.
 // Fewer rows: an instance without that, which a launch over a chunk of some ten thousand rows would pay 0.3 - 0.4 us for.
 constexpr int kLnChain = 32;
-template <int NI, bool LONG>
+template <typename T, int NI, bool LONG>
 __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBackArgs> ba) {
   const LnBackArgs b = ba.sub[blockIdx.z];
   const LnArgs &a = b.f;
   const unsigned block = blockIdx.x, blocks = b.blocks;
   if (block >= blocks) return;
-  const void *x = a.x, *dr = b.dr, *res = b.res;
-  void *out = a.out;
+  const T *x = static_cast<const T *>(a.x), *dr = static_cast<const T *>(b.dr), *res = static_cast<const T *>(b.res);
+  T *out = static_cast<T *>(a.out);
   const float *gamma = a.gamma, *beta = a.beta;
   float *partial = b.partial;
   const float eps = a.eps;
   const int64_t M = a.M;
-  const int x_dtype = a.x_dtype, x_ld = a.x_ld, d = a.d, out_dtype = a.out_dtype, out_ld = a.out_ld;
-  const int dr_dtype = b.dr_dtype, dr_ld = b.dr_ld, res_dtype = b.res_dtype, res_ld = b.res_ld;
+  const int x_ld = a.x_ld, d = a.d, out_ld = a.out_ld, dr_ld = b.dr_ld, res_ld = b.res_ld;
   const LnDropout dp = a.drop;
   __shared__ float red[4][2][NI * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -108,11 +107,11 @@ __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBac
     gam[i] = c < d ? gamma[c] : 0.f;
     bet[i] = c < d ? beta[c] : 0.f;
   }
-  const int64_t gap_row = b.gap_row, gap = b.gap;
+  const int64_t gap_row = b.gap_row, gap_end = b.gap_end;
   int chain = 0;
   bool waiting = false;  // earlier chains' sums wait in LDS
-  for (int64_t i_row = w0; i_row < M; i_row += nw) {
-    const int64_t r = i_row < gap_row ? i_row : i_row + gap;
+  for (int64_t r = w0; r < M; r += nw) {
+    if (r >= gap_row && r < gap_end) continue;
     if (LONG && chain == kLnChain) {
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
@@ -130,7 +129,7 @@ __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBac
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int c = lane + 64 * i;
-      xh[i] = c < d ? ld_elt(x, x_dtype, (size_t)r * x_ld + c) : 0.f;
+      xh[i] = c < d ? (float)x[(size_t)r * x_ld + c] : 0.f;
       sum += xh[i];
     }
     const float mean = wave_sum(sum) / (float)d;
@@ -150,7 +149,7 @@ __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBac
       float dn = 0.f;
       if (c < d) {
         const float y = gam[i] * xh[i] + bet[i];
-        dn = y > 0.f ? ld_elt(dr, dr_dtype, (size_t)r * dr_ld + c) : 0.f;  // ReLU derivative, strict
+        dn = y > 0.f ? (float)dr[(size_t)r * dr_ld + c] : 0.f;  // ReLU derivative, strict
         if (dp.threshold > 0) dn = dropout_keep(dp, dp.u0 + r, d, c) ? dn * dp.scale : 0.f;
       }
       dg[i] += dn * xh[i];
@@ -169,9 +168,9 @@ __global__ __launch_bounds__(256) void ln_relu_backward_kernel(const Batch<LnBac
           float v = 0.f;
           if (c < d) {
             v = rstd * (dxh[i] - m1 - xh[i] * m2);
-            if (res != nullptr) v += ld_elt(res, res_dtype, (size_t)r * res_ld + c);
+            if (res != nullptr) v += (float)res[(size_t)r * res_ld + c];
           }
-          st_elt(out, out_dtype, (size_t)r * out_ld + c, v);
+          out[(size_t)r * out_ld + c] = (T)v;
         }
       }
     }
@@ -284,7 +283,7 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<L
     bet[t] = beta[sub * 8 + t];
     dg[t] = db[t] = 0.f;
   }
-  const int64_t gap_row = b.gap_row, gap = b.gap;
+  const int64_t gap_row = b.gap_row, gap_end = b.gap_end;
   int chain = 0;
   bool waiting = false;
   for (int64_t r0 = w0 * RPW; r0 < M; r0 += nw * RPW) {
@@ -300,10 +299,9 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<L
       chain = 0;
     }
     ++chain;
-    const int64_t i_row = r0 + rw;
-    const bool on = i_row < M;
-    int64_t rr = on ? i_row : M - 1;
-    rr += rr < gap_row ? 0 : gap;
+    const int64_t r = r0 + rw;
+    const bool on = r < M && (r < gap_row || r >= gap_end);
+    const int64_t rr = on ? r : 0;
     const bf16x8_ln xv = *reinterpret_cast<const bf16x8_ln *>(x + (size_t)rr * x_ld + sub * 8);
     const bf16x8_ln dv = *reinterpret_cast<const bf16x8_ln *>(dr + (size_t)rr * dr_ld + sub * 8);
     bf16x8_ln rv;
@@ -345,7 +343,7 @@ __global__ __launch_bounds__(256) void ln_relu_backward_vec_kernel(const Batch<L
         if (res != nullptr) v += (float)rv[t];
         o[t] = (bf16_t)v;
       }
-      *reinterpret_cast<bf16x8_ln *>(out + (size_t)rr * out_ld + sub * 8) = o;
+      *reinterpret_cast<bf16x8_ln *>(out + (size_t)r * out_ld + sub * 8) = o;
     }
   }
   // column sums: over the row groups of the wavefront (fixed order), then over the four wavefronts in LDS
@@ -511,8 +509,11 @@ int launch_ln_relu_backward(const LnBackArgs *l, int n, int max_waves, LnReduceA
       const int ni = (std::max(a.d, a.out ? a.out_ld : a.d) + 63) / 64;
       gx[i] = (unsigned)(waves_for(a.M, max_waves) / 4);
       const bool more = a.M > (int64_t)gx[i] * 4 * kLnChain;
-#define LN_ROW(N) (more ? ln_relu_backward_kernel<N, true> : ln_relu_backward_kernel<N, false>)
-      fn[i] = ni <= 1 ? LN_ROW(1) : ni <= 2 ? LN_ROW(2) : ni <= 4 ? LN_ROW(4) : ni <= 8 ? LN_ROW(8) : LN_ROW(16);
+      if (b.dr_dtype != a.x_dtype || (b.res && b.res_dtype != a.x_dtype) || (a.out && a.out_dtype != a.x_dtype)) return hipErrorInvalidValue;
+#define LN_ROW(T, N) (more ? ln_relu_backward_kernel<T, N, true> : ln_relu_backward_kernel<T, N, false>)
+#define LN_ROWS(T) (ni <= 1 ? LN_ROW(T, 1) : ni <= 2 ? LN_ROW(T, 2) : ni <= 4 ? LN_ROW(T, 4) : ni <= 8 ? LN_ROW(T, 8) : LN_ROW(T, 16))
+      fn[i] = a.x_dtype == DT_BF16 ? LN_ROWS(bf16_t) : LN_ROWS(float);
+#undef LN_ROWS
 #undef LN_ROW
     }
     red[i] = LnReduceArgs{b.partial, (int32_t)gx[i], a.d, b.dgamma, b.dbeta};

@@ -127,7 +127,8 @@ __global__ __launch_bounds__(256) void spmm_kernel(const SpmmArgs a) {
   constexpr int TILE_W = LPR * VEC;
   const int lane = threadIdx.x & 63;
   int cls;
-  const int64_t task = spmm_task_index(a, blockIdx.x, threadIdx.x >> 6, cls);
+  const SpmmHead head = spmm_head(a);
+  const int64_t task = spmm_task_index(a, head, blockIdx.x, threadIdx.x >> 6, cls);
   if (task < 0) return;  // whole wave leaves together
   const int grp = lane / LPR, lig = lane % LPR;
   const int d = a.d;
@@ -149,7 +150,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(const SpmmArgs a) {
   const int slot = __builtin_amdgcn_readfirstlane(slot_raw);
   uint32_t chunk_classes;
   const bool many = a.many_chunks != 0;
-  const WaveMask mask = wave_mask(spmm_row_mask(a.pass, a.mask, ne_chunk >> kTaskChunkShift, chunk_classes), many);
+  const WaveMask mask = wave_mask(spmm_row_mask(a, head, ne_chunk >> kTaskChunkShift, chunk_classes), many);
   if (cls >= 0 && !((chunk_classes >> cls) & 1u)) return;  // nothing of this class is gathered for the row's chunk
   const uint32_t vmask = (1u << a.vbits) - 1u;
   const bool drop_unsel = a.src_unsel == nullptr;
@@ -584,11 +585,12 @@ __global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ri
   static_assert(NT > 2 || 4 * kShortRowMost * sizeof(u32x4_t) + 3 * TILE_W * sizeof(float) <= R * sizeof(u32x4_t), "and so do those of short rows");
   static_assert((U & (U - 1)) == 0 && U <= 8, "slot count");
   __shared__ u32x4_t ring_all[4][R];
+  const SpmmHead head = spmm_head(a);
   if constexpr (NT <= 2) {
-    const SpmmTurn turn = spmm_turn(a, blockIdx.x);
-    if ((int)blockIdx.x >= a.n_class_blocks && turn.is_short && a.short_rows != SHORT_ROWS_SINGLE) {  // 16 short rows
+    const SpmmTurn turn = spmm_turn(head, blockIdx.x);
+    if ((int)blockIdx.x >= head.n_class_blocks && turn.is_short && head.short_rows != SHORT_ROWS_SINGLE) {  // 16 short rows
       const int64_t first = (int64_t)turn.index * 16 + (threadIdx.x >> 6) * 4;
-      if (a.short_rows == SHORT_ROWS_MFMA)
+      if (head.short_rows == SHORT_ROWS_MFMA)
         spmm_short_rows<Tout, NT, FULL>(a, first, ring_all[threadIdx.x >> 6]);
       else if (a.many_chunks != 0)
         spmm_short_rows_valu<Tout, NT, FULL, true>(a, first);
@@ -599,7 +601,7 @@ __global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ri
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int cls;
-  const int64_t task = spmm_task_index(a, blockIdx.x, wave, cls);
+  const int64_t task = spmm_task_index(a, head, blockIdx.x, wave, cls);
   if (task < 0) return;  // whole wave leaves together (no block-wide barrier below)
   u32x4_t *ring = ring_all[wave];
   const int g = lane >> 4, lig = lane & 15;
@@ -619,7 +621,7 @@ __global__ __launch_bounds__(256, NT * U > 8 ? 1 : NT == 4 ? 5 : 7) void spmm_ri
   const int slot = __builtin_amdgcn_readfirstlane(slot_raw);
   uint32_t chunk_classes;
   const bool many = a.many_chunks != 0;
-  const WaveMask mask = wave_mask(spmm_row_mask(a.pass, a.mask, ne_chunk >> kTaskChunkShift, chunk_classes), many);
+  const WaveMask mask = wave_mask(spmm_row_mask(a, head, ne_chunk >> kTaskChunkShift, chunk_classes), many);
   if (cls >= 0 && !((chunk_classes >> cls) & 1u)) return;  // nothing of this class is gathered for the row's chunk
   const uint32_t vmask = (1u << a.vbits) - 1u;
   const bool drop_unsel = a.src_unsel == nullptr;
